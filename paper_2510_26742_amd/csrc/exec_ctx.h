@@ -38,29 +38,38 @@ struct LaunchCtx {
 };
 
 // ------------------------------------------------------------------------------------------------
-// Grid barrier of the persistent kernel.  Arrivals are counted per die (hardware register XCC_ID names
-// the die a wave runs on); the block that completes a die's count performs ONE device-scope release for
-// the whole die (cache write-back, which also waits for the write-through stores in flight) and then tells
-// every die, in a word of that die's own cache line, that this die has completed the epoch; a block polls
-// its die's line (one 32-byte load) until all dies that hold blocks have.  One read-modify-write and one
-// store-to-poll hop per barrier; a root counter between the two cost a second read-modify-write round trip.  Arrive and wait are separate calls, so a block requests the next operation's constant
+// Grid barrier of the persistent kernel.  A block arrives by storing the epoch into its own word of its die's flag line
+// (hardware register XCC_ID names the die a wave runs on): an ordinary store, which stays in the die's L2, where the
+// other blocks of the die see it with an L1-bypassing load.  One block per die, the leader, polls those words - one
+// 128-byte line for 32 blocks - and then tells every die, in a word of that die's own cache line, that its die has
+// completed the epoch; a block polls its die's line (one 32-byte load) until all dies that hold blocks have.  Two
+// store-to-poll hops, one inside the die and one between dies, and no read-modify-write: a counter per die instead of
+// the flags serialises 32 atomics in the L2 (probe of 256 blocks, per barrier: 1.56 us with counters, 1.05 us with
+// flags; with a store before and a load after it 2.27 against 1.86).  There is no cache write-back in the barrier:
+// everything another block will read is stored write-through (PersistCtxT::st) and each wave waits until its own stores
+// are acknowledged.  The leader requests its own prefetch only after that (loads return in order per compute unit: its
+// polls would queue behind it), so it is chosen among the blocks that the attention leaves idle.  Arrive and wait are separate calls, so a block requests the next operation's constant
 // operands between them.  Every wait is bounded: when the bound runs out the error word is raised, every
 // later wait returns at once, and the host reports the failure.
-// Words (unsigned, 128 bytes apart so that no two are in one cache line):
+// Words (unsigned; groups 128 bytes apart so that no two are in one cache line):
 enum {
   GB_ERR = 0,          // != 0: a bounded wait ran out
   GB_START = 32,       // start-up counter: blocks registered
   GB_MEMBERS = 64,     // + 32 x: blocks resident on die x
-  GB_COUNT = 320,      // + 32 x: arrivals on die x (monotonic)
+  GB_LEADER = 320,     // + 32 x: 1 + index of the block that leads die x (+ 2^16 if it asked to)
   GB_DONE = 576,       // + 32 y + x: last epoch that die x completed, as told to die y (one cache line per reading die)
   GB_SINK = 832,       // never read: where a read-ahead block would store its folded loads (keeps the loads alive)
-  GB_WORDS = 864
+  GB_FLAGS = 864,      // + GB_MAX_BLOCKS x + r: last epoch that block r of die x arrived at
+  GB_MAX_BLOCKS = 256, // largest grid
+  GB_WORDS = GB_FLAGS + 8 * GB_MAX_BLOCKS
 };
 
 struct GridBarrier {
   unsigned* w;          // GB_WORDS words, zeroed before the launch
   unsigned xcc;         // die of this block
   unsigned members;     // blocks on this die
+  unsigned rank;        // this block's place among them
+  bool leader;          // this block tells the other dies when this one is complete
   unsigned present;     // bit x set: die x holds at least one block
   unsigned spin_limit;
   unsigned epoch;       // barriers this block has arrived at
@@ -71,15 +80,19 @@ struct GridBarrier {
   __device__ __forceinline__ static void st_dev(unsigned* p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
   // all threads of the block; one counter barrier, after which every block knows who shares its die
-  __device__ __forceinline__ void init(unsigned* words, unsigned limit) {
+  // may_lead: the block is one of those that should lead their die (if a die has none, another one does)
+  __device__ __forceinline__ void init(unsigned* words, unsigned limit, bool may_lead) {
     w = words;
     spin_limit = limit;
     epoch = 0;
     waited = 0;
     trace = nullptr;
     xcc = (unsigned)__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7u;   // XCC_ID, bits 3:0
+    __shared__ unsigned rank_s;
     if (threadIdx.x == 0) {
-      __hip_atomic_fetch_add(&w[GB_MEMBERS + 32 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_max(&w[GB_LEADER + 32 * xcc], (unsigned)blockIdx.x + 1u + (may_lead ? 1u << 16 : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      rank_s = __hip_atomic_fetch_add(&w[GB_MEMBERS + 32 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // both are in place before this block counts as registered
       __hip_atomic_fetch_add(&w[GB_START], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       unsigned spins = 0;
       while (ld_dev(&w[GB_START]) < gridDim.x) {
@@ -88,9 +101,16 @@ struct GridBarrier {
       }
     }
     __syncthreads();
+    rank = rank_s;
     members = ld_dev(&w[GB_MEMBERS + 32 * xcc]);
+    leader = (ld_dev(&w[GB_LEADER + 32 * xcc]) & 0xffffu) == (unsigned)blockIdx.x + 1u;
     present = 0;
     for (unsigned k = 0; k < 8u; k++) present |= ld_dev(&w[GB_MEMBERS + 32 * k]) != 0u ? 1u << k : 0u;
+  }
+
+  // the error word is looked at on every 64th poll: behind each poll it would double the time between two polls
+  __device__ __forceinline__ bool give_up(unsigned spins) const {
+    return spins > spin_limit || ((spins & 63u) == 0u && ld_dev(&w[GB_ERR]) != 0u);
   }
 
   // all threads of the block, after the block's last store of the operation
@@ -102,12 +122,23 @@ struct GridBarrier {
                                                         // fence does not wait for them)
     __syncthreads();
     epoch++;
-    if (threadIdx.x == 0) {
-      const unsigned old = __hip_atomic_fetch_add(&w[GB_COUNT + 32 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (old + 1u == epoch * members) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // the die's writes are in memory
-        for (unsigned k = 0; k < 8u; k++) st_dev(&w[GB_DONE + 32 * k + xcc], epoch);
+    unsigned* const flags = w + GB_FLAGS + GB_MAX_BLOCKS * xcc;
+    if (threadIdx.x == 0) __hip_atomic_store(flags + rank, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (leader) {
+      if (threadIdx.x < 64) {
+        unsigned spins = 0;
+        while (true) {
+          bool behind = false;
+          for (unsigned r = threadIdx.x; r < members; r += 64) behind |= ld_dev(flags + r) < epoch;
+          if (__builtin_amdgcn_ballot_w64(behind) == 0ull) break;
+          if (give_up(++spins)) {
+            if (threadIdx.x == 0) st_dev(&w[GB_ERR], 1u);
+            break;
+          }
+        }
+        if (threadIdx.x < 8) st_dev(&w[GB_DONE + 32 * threadIdx.x + xcc], epoch);
       }
+      __syncthreads();   // loads return in order per compute unit: no prefetch of the leader's other waves in front of its polls
     }
   }
 
@@ -120,8 +151,7 @@ struct GridBarrier {
       while (true) {
         const bool behind = counts && ld_dev(&w[GB_DONE + 32 * xcc + lane]) < epoch;
         if (__builtin_amdgcn_ballot_w64(behind) == 0ull) break;
-        __builtin_amdgcn_s_sleep(1);
-        if (++spins > spin_limit || ld_dev(&w[GB_ERR]) != 0u) {
+        if (give_up(++spins)) {
           if (lane == 0) st_dev(&w[GB_ERR], 1u);
           break;
         }

@@ -25,21 +25,21 @@ constexpr int PK_THREADS = 512;
 // step, so an operation's weight request - issued when the operation before ends - goes all the way to HBM (the same loop
 // run on one layer's weights throughout, i.e. from that cache, is 0.46 ms faster).  The attention has 64 items for 256
 // blocks: the blocks without one use the time to read the weights that the following operations will ask for, which puts
-// them into the memory-side cache.  Part `part` of `nparts` of [base, base + bytes): 16 bytes per lane, 8 loads in flight
-// (4 finish too late, 16 disturb the working blocks' loads more than they gain: same-box A/B 5.47 / 5.42 / 5.48 ms);
-// the values are folded into a word that is stored only if it equals a constant, so no result depends on them.
-__device__ __forceinline__ unsigned read_ahead_part(const void* base, size_t bytes, int part, int nparts, int tid, unsigned fold) {
-  const size_t n16 = bytes >> 4;
-  const size_t per = (n16 + (size_t)nparts - 1) / (size_t)nparts;
-  const size_t beg = (size_t)part * per;
-  const size_t end = beg + per < n16 ? beg + per : n16;
-  const u32x4_t* p = reinterpret_cast<const u32x4_t*>(base);
-  for (size_t i = beg + (size_t)tid; i < end; i += 8 * PK_THREADS) {
+// them into the memory-side cache.  Part `part` of `nparts` of n16 16-byte pieces, piece i at addr(i): 16 bytes per lane,
+// 8 loads in flight (4 finish too late, 16 disturb the working blocks' loads more than they gain: same-box A/B
+// 5.47 / 5.42 / 5.48 ms); the values are folded into a word that is stored only if it equals a constant, so no result
+// depends on them.
+template <class F>
+__device__ __forceinline__ unsigned read_ahead_part(unsigned n16, int part, int nparts, int tid, unsigned fold, F&& addr) {
+  const unsigned per = (n16 + (unsigned)nparts - 1) / (unsigned)nparts;
+  const unsigned beg = (unsigned)part * per;
+  const unsigned end = beg + per < n16 ? beg + per : n16;
+  for (unsigned i = beg + (unsigned)tid; i < end; i += 8 * PK_THREADS) {
     u32x4_t v[8];
 #pragma unroll
     for (int j = 0; j < 8; j++) {
-      const size_t idx = i + (size_t)j * PK_THREADS;
-      v[j] = p[idx < end ? idx : end - 1];   // clamped, unconditional
+      const unsigned idx = i + (unsigned)j * PK_THREADS;
+      v[j] = *reinterpret_cast<const u32x4_t*>(addr(idx < end ? idx : end - 1));   // clamped, unconditional
     }
 #pragma unroll
     for (int j = 0; j < 8; j++) fold ^= v[j][0] ^ v[j][1] ^ v[j][2] ^ v[j][3];
@@ -47,10 +47,36 @@ __device__ __forceinline__ unsigned read_ahead_part(const void* base, size_t byt
   return fold;
 }
 
+// The same for a packed weight matrix of n_tiles 32-feature tiles of kc16 KiB, shared out so that a block reads what
+// blocks of its own die will ask for (their L2 then holds it: the second request is one die-local round trip).  Work
+// items go to blocks in turn and consecutive blocks to different dies, so items u, u + 8, ... share a die.  UNIT: what
+// consecutive items take: 2 = pairs of tiles (gate||up), 1 = a tile (QKV), 0 = half a tile, i.e. 16 of its 32 features
+// (O and down).  Where the counts are no multiples of 8 the matrix is shared out without regard to dies.
+template <int UNIT>
+__device__ __forceinline__ unsigned read_ahead_weights(const bf16* w, int n_tiles, int kc16, int part, int nparts, bool by_die, int tid, unsigned fold) {
+  const char* base = reinterpret_cast<const char*>(w);
+  const unsigned unit16 = UNIT == 0 ? (unsigned)kc16 * 32u : (unsigned)UNIT * (unsigned)kc16 * 64u;   // 16-byte pieces per unit
+  const unsigned units = UNIT == 0 ? 2u * (unsigned)n_tiles : (unsigned)(n_tiles / UNIT);
+  unsigned u0 = 0, du = 1, n = units;
+  if (by_die && units % 8u == 0u) {
+    u0 = (unsigned)part & 7u;
+    du = 8;
+    n = units / 8u;
+    part >>= 3;
+    nparts >>= 3;
+  }
+  return read_ahead_part(n * unit16, part, nparts, tid, fold, [&](unsigned i) {
+    const unsigned j = i / unit16, c = i - j * unit16, u = u0 + j * du;
+    if (UNIT == 0) return base + (size_t)(u >> 1) * (unsigned)kc16 * 1024u + (c >> 5) * 1024u + ((c >> 4) & 1u) * 512u + (u & 1u) * 256u + (c & 15u) * 16u;
+    return base + (size_t)u * unit16 * 16u + (size_t)c * 16u;
+  });
+}
+
+// block: this block's place in the order in which the operation's items are handed out
 template <class F>
-__device__ __forceinline__ void for_items(int n_items, F&& f) {
+__device__ __forceinline__ void for_items(int n_items, F&& f, int block = (int)blockIdx.x) {
   bool first = true;
-  for (int it = (int)blockIdx.x; it < n_items; it += (int)gridDim.x) {
+  for (int it = block; it < n_items; it += (int)gridDim.x) {
     if (!first) __syncthreads();   // shared memory of the item before is free
     f(it);
     first = false;
@@ -72,7 +98,12 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   GridBarrier bar;
   const ExpertLoopParams& P = *Pg;
-  bar.init(P.sync, P.spin_limit);
+  // The attention's items start at the first block without a QKV item: such a block requests its share of the prefix
+  // cache when the QKV projection begins, and has it when the projection ends.
+  const int att_off = P.qkv.n_tiles * 2 < (int)gridDim.x ? P.qkv.n_tiles * 2 : 0;
+  const int att_block = (int)blockIdx.x >= att_off ? (int)blockIdx.x - att_off : (int)blockIdx.x + (int)gridDim.x - att_off;
+  const int part_die = (att_off | P.att_items | (int)gridDim.x) & 7;   // 0: consecutive idle blocks are on consecutive dies, starting with item 0's
+  bar.init(P.sync, P.spin_limit, att_block >= P.att_items);
   PersistCtx cx;
   cx.arena = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(P.arena), 0, (int)P.arena_bytes, 0x00020000);
   cx.arena_base = P.arena;
@@ -160,16 +191,12 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
             gemm_skinny_body<PRO_RMS, EPI_QKV, 1>(q, item(it % q.n_tiles, 0, it / q.n_tiles).template as<true>(), smem_raw);
           });
         }
-        if ((int)blockIdx.x >= q.n_tiles * 2 && (F.read_ahead & 48)) {   // no item: what the attention and O of this layer read
+        if (att_block >= F.att_items && (int)blockIdx.x >= q.n_tiles * 2 && (F.read_ahead & 48)) {   // no item here nor in the attention
           const int tid = item(0, 0, 0).thread;
-          const int part = (int)blockIdx.x - q.n_tiles * 2, nparts = (int)gridDim.x - q.n_tiles * 2;
+          const int idle = (int)gridDim.x - (q.n_tiles * 2 > att_off + F.att_items ? q.n_tiles * 2 : att_off + F.att_items);
+          const int part = (int)gridDim.x - 1 - (int)blockIdx.x;
           unsigned fold = 0;
-          if (F.read_ahead & 32) {   // this layer's slices of the prefix cache
-            const size_t cache_bytes = (size_t)F.att.chunks0 * 32 * 256 * 2;
-            fold = read_ahead_part(F.att.k0 + (size_t)l * F.kcache_stride, cache_bytes, part, nparts, tid, fold);
-            fold = read_ahead_part(F.att.v0 + (size_t)l * F.vcache_stride, cache_bytes, part, nparts, tid, fold);
-          }
-          if (F.read_ahead & 16) fold = read_ahead_part(F.o.W.w + (size_t)l * F.w_stride, (size_t)F.o.n_tiles * 64 * F.o.W.k_pad, part, nparts, tid, fold);
+          if (F.read_ahead & 16) fold = read_ahead_weights<0>(F.o.W.w + (size_t)l * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, idle, false, tid, fold);
           if (fold == 0x9e3779b9u) F.sync[GB_SINK] = fold;
         }
         op_end();
@@ -189,16 +216,17 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         const int att_gx = F.att_gx, att_gxy = F.att_gx * a.heads;
         for_items(F.att_items, [&](int it) {
           attention_body<256, 8, 1, 6, 5>(a, item(it % att_gx, (it % att_gxy) / att_gx, it / att_gxy).template as<true>(), smem_raw);
-        });
-        if ((int)blockIdx.x >= F.att_items && F.read_ahead != 0) {   // no item: read ahead (constants only, no wait needed)
-          const int part = (int)blockIdx.x - F.att_items, nparts = (int)gridDim.x - F.att_items;
+        }, att_block);
+        if (att_block >= F.att_items && (F.read_ahead & 15)) {   // no item: read ahead (constants only, no wait needed)
+          const int part = att_block - F.att_items, nparts = (int)gridDim.x - F.att_items;
           const int ln = l + 1 < layers ? l + 1 : 0;
+          const bool by_die = part_die == 0 && nparts % 8 == 0 && (F.read_ahead & 32) != 0;
           const int tid = item(0, 0, 0).thread;
           unsigned fold = 0;
-          if (F.read_ahead & 1) fold = read_ahead_part(F.gu.W.w + (size_t)l * F.w_stride, (size_t)F.gu.n_tiles * 64 * F.gu.W.k_pad, part, nparts, tid, fold);
-          if (F.read_ahead & 2) fold = read_ahead_part(F.dn.W.w + (size_t)l * F.w_stride, (size_t)F.dn.n_tiles * 64 * F.dn.W.k_pad, part, nparts, tid, fold);
-          if (F.read_ahead & 4) fold = read_ahead_part(F.qkv.W.w + (size_t)ln * F.w_stride, (size_t)F.qkv.n_tiles * 64 * F.qkv.W.k_pad, part, nparts, tid, fold);
-          if (F.read_ahead & 8) fold = read_ahead_part(F.o.W.w + (size_t)ln * F.w_stride, (size_t)F.o.n_tiles * 64 * F.o.W.k_pad, part, nparts, tid, fold);
+          if (F.read_ahead & 1) fold = read_ahead_weights<2>(F.gu.W.w + (size_t)l * F.w_stride, F.gu.n_tiles, F.gu.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+          if (F.read_ahead & 2) fold = read_ahead_weights<0>(F.dn.W.w + (size_t)l * F.w_stride, F.dn.n_tiles, F.dn.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+          if (F.read_ahead & 4) fold = read_ahead_weights<1>(F.qkv.W.w + (size_t)ln * F.w_stride, F.qkv.n_tiles, F.qkv.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+          if (F.read_ahead & 8) fold = read_ahead_weights<0>(F.o.W.w + (size_t)ln * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, nparts, by_die, tid, fold);
           if (fold == 0x9e3779b9u) F.sync[GB_SINK] = fold;
         }
         op_end();
@@ -285,7 +313,7 @@ hipError_t expert_loop_max_blocks_per_cu(int* out) {
 // Host-side checks of everything the kernel's indexing assumes; the caller has zeroed the barrier words.
 hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLoopParams* d_params, int blocks) {
   if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0) return hipErrorInvalidValue;
-  if (blocks < 1 || blocks > 1024 || P.sync == nullptr || P.arena == nullptr || P.arena_bytes == 0 || P.spin_limit == 0)
+  if (blocks < 1 || blocks > GB_MAX_BLOCKS || P.sync == nullptr || P.arena == nullptr || P.arena_bytes == 0 || P.spin_limit == 0)
     return hipErrorInvalidValue;
   if (P.layers < 1 || P.steps < 1 || P.x_elems < 1 || P.noise == nullptr || P.emb.x_rw == nullptr)
     return hipErrorInvalidValue;

@@ -377,9 +377,9 @@ struct Tune {
   int ras = 256, ral = 1, rat = 256, rad = 6;
   // the whole denoise loop as one persistent kernel with grid barriers (1) or one launch per operation (0)
   int pdn = 1;
-  // ... in which the blocks without an attention item read ahead (bits: gate||up, down, next layer's QKV, next layer's O; 16: this layer's O by the blocks
-  // without a QKV item)
-  int pra = 39;
+  // ... in which the blocks without an attention item read ahead (bits: gate||up, down, next layer's QKV, next layer's O; 16: this layer's O, by the blocks
+  // with neither a QKV nor an attention item; 32: each what its own die will ask for)
+  int pra = 35;
   // two-stream frames: blocks of the persistent loop beside the prefill (0: per-operation launches).  A resident block
   // of the loop holds a whole compute unit, so its grid decides how the chip is shared between the two streams
   int psb = -1;           // -1: from the number of prefix tokens (frame_loop_blocks)
