@@ -274,111 +274,6 @@ __global__ __launch_bounds__(64 * WN) __attribute__((amdgpu_waves_per_eu(OCC, OC
   }
 }
 
-// ------------------------------------------------------------------------------------------------
-// "Entry" GEMM: the skinny kernels' plan (every load of the block issued at entry, one wait, no
-// LDS staging) for the O projections of the vision tower (k = 1152) and of the prefix at one view
-// (k = 2048).  As split-K partial GEMMs these need a reduction launch behind them; as one tall
-// GEMM over the whole k range they spend their time on consecutive memory round trips (18 or 32
-// chunks at 6 in flight).  Here one block = 64 tokens x NT feature tiles; 8 waves split the k16
-// steps (at most EN_SPW each) and hold their slice of both operands in registers, so the block
-// pays one round trip, and the residual epilogue runs in the same launch.  Partial tiles meet in
-// LDS, one 32-token block at a time, and are added in wave order; wave mb * NT + j finishes tile
-// (mb, j).  Input row statistics (unused by the residual epilogue) would be whole-row sums.
-// ------------------------------------------------------------------------------------------------
-template <int PRO, int EPI, int NT, int EN_SPW>
-__global__ __launch_bounds__(64 * SK_WAVES) void gemm_entry_kernel(GemmParams p) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  float* red = reinterpret_cast<float*>(smem_raw);                 // [8 waves][NT][4][64][4]
-  const int t = threadIdx.x;
-  const int lane = t & 63;
-  const int w = t >> 6;
-  const int lq = lane & 31;
-  const int lh = lane >> 5;
-  // die-aware order: consecutive block ids go to different dies (an L2 each), so the token blocks that share one
-  // weight panel are given ids with equal (id % 8) and fetch it from memory once
-  // (measured: vision QKV, 8 MB of weights, 10.8 -> 10.1 us and 3.7 x -> 1 x of its bytes from memory; the O projections
-  // with one feature tile per block lose 0.3 us, so they keep the plain two-dimensional grid)
-  int nb = (int)blockIdx.x, mt = (int)blockIdx.y;
-  if (NT > 1) {
-    const int nblocks_n = (p.n_tiles + NT - 1) / NT;
-    const int slot = (int)blockIdx.x >> 3;
-    nb = ((int)blockIdx.x & 7) + 8 * (slot / p.m_tiles);
-    mt = slot % p.m_tiles;
-    if (nb >= nblocks_n) return;
-  }
-  const int nt0 = nb * NT;
-  const int m0 = mt * 64;
-  const int KC16 = p.W.k_pad >> 4;
-  const int XKC16 = p.ldx >> 4;
-  const int spw = (KC16 + SK_WAVES - 1) / SK_WAVES;        // host picks the instantiation with spw <= EN_SPW
-  const int s_beg = w * spw, s_end = min(s_beg + spw, KC16);
-  const int mb_last = (p.M - 1) >> 5;
-  bf16x8 wf[NT][EN_SPW], xf[2][EN_SPW];
-#pragma unroll
-  for (int i = 0; i < EN_SPW; i++) {
-    const int st = min(s_beg + i, KC16 - 1);   // clamped: steps beyond the wave's range are never used
-#pragma unroll
-    for (int j = 0; j < NT; j++)
-      wf[j][i] = *reinterpret_cast<const bf16x8*>(p.W.w + ((size_t)min(nt0 + j, p.n_tiles - 1) * KC16 + st) * 512 + lane * 8);
-#pragma unroll
-    for (int mb = 0; mb < 2; mb++)
-      xf[mb][i] = *reinterpret_cast<const bf16x8*>(p.X + ((size_t)min((m0 >> 5) + mb, mb_last) * XKC16 + st) * 512 + lane * 8);
-  }
-  const int fin_mb = w / NT, fin_j = w - fin_mb * NT;
-  const bool finisher = w < 2 * NT && nt0 + fin_j < p.n_tiles;
-  const int mrow = m0 + fin_mb * 32 + lq;
-  f32x16 acc[2][NT];
-#pragma unroll
-  for (int mb = 0; mb < 2; mb++)
-#pragma unroll
-    for (int j = 0; j < NT; j++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) acc[mb][j][r] = 0.f;
-#pragma unroll
-  for (int i = 0; i < EN_SPW; i++) {
-    if (s_beg + i < s_end) {
-#pragma unroll
-      for (int mb = 0; mb < 2; mb++)
-#pragma unroll
-        for (int j = 0; j < NT; j++) acc[mb][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j][i], xf[mb][i], acc[mb][j], 0, 0, 0);
-    }
-  }
-  // The finishing waves fetch what their epilogue needs once the operand registers are free; the
-  // round trip overlaps the reduction through LDS.
-  EpiOps ops;
-  float2 rst = make_float2(0.f, 0.f);
-  if (finisher && mrow < p.M) {
-    if (PRO != PRO_NONE) rst = *reinterpret_cast<const float2*>(p.rowstat + 2 * (size_t)mrow);
-    epilogue_preload<PRO, EPI>(p, nt0 + fin_j, mrow, lh, ops);
-  }
-  f32x16 sum;
-#pragma unroll
-  for (int r = 0; r < 16; r++) sum[r] = 0.f;
-#pragma unroll
-  for (int mb = 0; mb < 2; mb++) {
-    if (mb) __syncthreads();   // the readers of the first round are done
-#pragma unroll
-    for (int j = 0; j < NT; j++)
-#pragma unroll
-      for (int q = 0; q < 4; q++) {
-        const f32x4 v4 = {acc[mb][j][4 * q], acc[mb][j][4 * q + 1], acc[mb][j][4 * q + 2], acc[mb][j][4 * q + 3]};
-        *reinterpret_cast<f32x4*>(red + ((((size_t)w * NT + j) * 4 + q) * 64 + lane) * 4) = v4;
-      }
-    __syncthreads();
-    if (fin_mb == mb && w < 2 * NT) {
-#pragma unroll
-      for (int ww = 0; ww < SK_WAVES; ww++)
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          const f32x4 v4 = *reinterpret_cast<const f32x4*>(red + ((((size_t)ww * NT + fin_j) * 4 + q) * 64 + lane) * 4);
-#pragma unroll
-          for (int jj = 0; jj < 4; jj++) sum[4 * q + jj] += v4[jj];
-        }
-    }
-  }
-  if (finisher && mrow < p.M) epilogue_tile<PRO, EPI>(p, sum, nt0 + fin_j, mrow, lh, rst.x, rst.y, 0, ops);
-}
-
 // Skinny GEMM over the whole k range with the residual epilogue (the expert's O and down
 // projections, k = 2048 / 4096): one block per (32-feature tile, 32-token block), 8 waves each
 // owning 1/8 of k in NB batches of 16 k16 steps.  No split across blocks, so the residual add, the
@@ -458,10 +353,10 @@ int gemm_rows_per_tile(int tile) {
     case TILE_SMALL: return 64;
     case TILE_WIDE: return 256;
     case TILE_WIDE128: return 128;
-    case TILE_ENTRY: return 64;
     case TILE_SQ128: return 128;
     case TILE_T192: return 192;
     case TILE_MID2: return 64;
+    case TILE_STREAM: return 64;
     default: return -1;
   }
 }
@@ -514,14 +409,6 @@ static hipError_t set_attr() {
   X(T, MB, WN, D, PRO_RMS, EPI_QKV, 1, 2)
 #define GEMM_VARIANTS2(X) TALL_EPIS2(X, TILE_MID2, 2, 4, 6)
 
-// X(PRO, EPI, feature tiles per block, k16 steps per wave), ascending steps: vision O (k = 1152), prefix O
-// (k = 2048), vision QKV (k = 1152, 64 x 64 tiles)
-#define ENTRY_VARIANTS(X)       \
-  X(PRO_NONE, EPI_RESID, 1, 9)  \
-  X(PRO_NONE, EPI_RESID, 1, 16) \
-  X(PRO_LN, EPI_QKV, 2, 9)
-static constexpr int entry_smem_bytes(int nt) { return SK_WAVES * nt * 16 * 64 * 4; }
-
 #define SKINNY_VARIANTS(X)      \
   X(PRO_NONE, EPI_RESID)        \
   X(PRO_NONE, EPI_PARTIAL)      \
@@ -543,14 +430,6 @@ hipError_t gemm_init_attributes() {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, skinny_smem_bytes());
     if (e != hipSuccess) return e;
   }
-#define X(PRO, EPI, NT, SPW)                                                                                     \
-  {                                                                                                              \
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_entry_kernel<PRO, EPI, NT, SPW>),     \
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, entry_smem_bytes(NT));        \
-    if (e != hipSuccess) return e;                                                                               \
-  }
-  ENTRY_VARIANTS(X)
-#undef X
 #define X(T, MB, WN, D, PRO, EPI, NT)                                 \
   {                                                                   \
     hipError_t e = set_attr<MB, WN, D, PRO, EPI, NT>();               \
@@ -582,6 +461,7 @@ static bool prefetch_ok(const PrefetchDesc& d) {
 }
 
 hipError_t launch_gemm(hipStream_t s, int tile, int pro, int epi, const GemmParams& p, int z_splits) {
+  if (tile == TILE_STREAM) return z_splits == 1 ? launch_gemm_stream(s, pro, epi, p) : hipErrorInvalidValue;
   // Host-side shape checks: everything the kernel's indexing assumes.
   if (!prefetch_ok(p.pf)) return hipErrorInvalidValue;
   if (p.pf.blocks != 0 && ((tile != TILE_SKINNY && tile != TILE_SKINNY_FULLK && tile != TILE_SKINNY16) || z_splits != 1)) return hipErrorInvalidValue;
@@ -592,7 +472,7 @@ hipError_t launch_gemm(hipStream_t s, int tile, int pro, int epi, const GemmPara
   if (pro != PRO_NONE && (z_splits != 1 || p.rowstat == nullptr)) return hipErrorInvalidValue;
   if (epi != EPI_PARTIAL && z_splits != 1) return hipErrorInvalidValue;
   if (p.m_tiles < 1) return hipErrorInvalidValue;
-  if (tile == TILE_BIG || tile == TILE_MID || tile == TILE_SMALL || tile == TILE_WIDE || tile == TILE_WIDE128 || tile == TILE_T192 || tile == TILE_ENTRY || tile == TILE_MID2) {
+  if (tile == TILE_BIG || tile == TILE_MID || tile == TILE_SMALL || tile == TILE_WIDE || tile == TILE_WIDE128 || tile == TILE_T192 || tile == TILE_MID2 || tile == TILE_SQ128) {
     // partial row statistics: planes of stat_rows rows, every row a block touches inside a plane
     if (pro != PRO_NONE && p.rowstat_parts > 1 && (p.stat_rows < p.M || p.rowstat_parts > STAT_PARTS_MAX)) return hipErrorInvalidValue;
     if (epi == EPI_RESID && p.stat_out != nullptr && p.stat_rows < p.M + p.row_offset) return hipErrorInvalidValue;
@@ -611,23 +491,6 @@ hipError_t launch_gemm(hipStream_t s, int tile, int pro, int epi, const GemmPara
     if (kc16 == 128) gemm_skinny16_kernel<8><<<grid, dim3(64 * SK_WAVES), 0, s>>>(p);
     else gemm_skinny16_kernel<16><<<grid, dim3(64 * SK_WAVES), 0, s>>>(p);
     return hipGetLastError();
-  }
-  if (tile == TILE_ENTRY) {
-    // 64 tokens x NT feature tiles per block, the k16 steps split over 8 waves, at most EN_SPW each
-    const int kc16 = p.W.k_pad >> 4;
-    const int spw = (kc16 + SK_WAVES - 1) / SK_WAVES;
-    if (z_splits != 1 || p.m_tiles * 64 < p.M) return hipErrorInvalidValue;
-    if (pro != PRO_NONE && p.rowstat_parts > 1) return hipErrorInvalidValue;   // whole-row statistics only
-    if (epi == EPI_RESID && (p.out_f32 == nullptr || p.out_bf16 == nullptr)) return hipErrorInvalidValue;
-#define X(PRO, EPI, NT, SPW)                                                                                   \
-  if (pro == PRO && epi == EPI && spw <= SPW) {                                                                \
-    gemm_entry_kernel<PRO, EPI, NT, SPW><<<NT > 1 ? dim3(8 * (((p.n_tiles + NT - 1) / NT + 7) / 8) * p.m_tiles) : dim3(p.n_tiles, p.m_tiles), dim3(64 * SK_WAVES), \
-                                           entry_smem_bytes(NT), s>>>(p);                                      \
-    return hipGetLastError();                                                                                  \
-  }
-    ENTRY_VARIANTS(X)
-#undef X
-    return hipErrorInvalidValue;
   }
   if (tile == TILE_SKINNY_FULLK) {
     const int kc16 = p.W.k_pad >> 4;
@@ -712,7 +575,7 @@ __global__ __launch_bounds__(512) void splitk_reduce_kernel(ReduceParams p) {
     }
     a += extra;    // same order of additions as ever: partial sums, bias, residual
     a += rv;
-    *reinterpret_cast<f32x4*>(p.out_f32 + (size_t)ro * p.ldo + n) = a;
+    if (p.out_f32 != nullptr) *reinterpret_cast<f32x4*>(p.out_f32 + (size_t)ro * p.ldo + n) = a;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
       sa += a[j];
@@ -720,7 +583,7 @@ __global__ __launch_bounds__(512) void splitk_reduce_kernel(ReduceParams p) {
     }
     a *= gv;
     const bf16x4 ob = {(bf16)a[0], (bf16)a[1], (bf16)a[2], (bf16)a[3]};
-    *reinterpret_cast<bf16x4*>(p.out_bf16 + xf_index(ro, n, p.ldo2 >> 4)) = ob;
+    if (p.out_bf16 != nullptr) *reinterpret_cast<bf16x4*>(p.out_bf16 + xf_index(ro, n, p.ldo2 >> 4)) = ob;
     if (p.out8 != nullptr) {
       // MXFP8 copy of the same gain-scaled values: 8 threads hold one 32-column scale block (N is a multiple of
       // 256, so a block's threads are all inside the loop)
@@ -762,55 +625,9 @@ __global__ __launch_bounds__(512) void splitk_reduce_kernel(ReduceParams p) {
 }
 
 hipError_t launch_splitk_reduce(hipStream_t s, const ReduceParams& p) {
-  if (p.N % 4 != 0 || p.ldp < p.N || p.ldo < p.N || p.ldo2 < p.N || p.ldo2 % 16 != 0 || p.M <= 0 || p.Z < 1) return hipErrorInvalidValue;
+  if (p.N % 4 != 0 || p.ldp < p.N || p.ldo < p.N || p.ldo2 < p.N || p.ldo2 % 16 != 0 || p.M <= 0 || p.Z < 0) return hipErrorInvalidValue;
+  if (p.Z == 0 ? p.resid == nullptr : (p.part == nullptr || p.out_f32 == nullptr || p.out_bf16 == nullptr)) return hipErrorInvalidValue;
   if (p.out8 != nullptr && (p.N % 256 != 0 || p.out8_scales == nullptr)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)p.M), dim3(512), 0, s, p);
-  return hipGetLastError();
-}
-
-// Row statistics and gain-scaled bf16 XF copy of fp32 residual rows that were not produced by a
-// GEMM epilogue or the reduction kernel (prefix embeddings, first suffix tokens of a step).
-__global__ __launch_bounds__(256) void row_stats_kernel(const float* x, int ld, int K, const float* gain, bf16* out_xf,
-                                                        int kc16, float* stat_out) {
-  __shared__ float sred[2][4];
-  const int m = blockIdx.x;
-  float sa = 0.f, sb = 0.f;
-  for (int k = threadIdx.x * 8; k < K; k += 2048) {
-    f32x4 v0 = *reinterpret_cast<const f32x4*>(x + (size_t)m * ld + k);
-    f32x4 v1 = *reinterpret_cast<const f32x4*>(x + (size_t)m * ld + k + 4);
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      sa += v0[j] + v1[j];
-      sb += v0[j] * v0[j] + v1[j] * v1[j];
-    }
-    if (gain != nullptr) {
-      v0 *= *reinterpret_cast<const f32x4*>(gain + k);
-      v1 *= *reinterpret_cast<const f32x4*>(gain + k + 4);
-    }
-    const bf16x8 o = {(bf16)v0[0], (bf16)v0[1], (bf16)v0[2], (bf16)v0[3], (bf16)v1[0], (bf16)v1[1], (bf16)v1[2], (bf16)v1[3]};
-    *reinterpret_cast<bf16x8*>(out_xf + xf_index(m, k, kc16)) = o;
-  }
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    sa += __shfl_xor(sa, off, 64);
-    sb += __shfl_xor(sb, off, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    sred[0][threadIdx.x >> 6] = sa;
-    sred[1][threadIdx.x >> 6] = sb;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    stat_out[2 * m] = sred[0][0] + sred[0][1] + sred[0][2] + sred[0][3];
-    stat_out[2 * m + 1] = sred[1][0] + sred[1][1] + sred[1][2] + sred[1][3];
-  }
-}
-
-hipError_t launch_row_stats(hipStream_t s, const float* x, int ld, int M, int K, int k_pad, const float* gain, bf16* out_xf,
-                            float* stat_out) {
-  if (x == nullptr || out_xf == nullptr || stat_out == nullptr || M <= 0 || K % 8 != 0 || ld % 4 != 0 || ld < K ||
-      k_pad % 16 != 0 || K > k_pad)
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL(row_stats_kernel, dim3((unsigned)M), dim3(256), 0, s, x, ld, K, gain, out_xf, k_pad >> 4, stat_out);
   return hipGetLastError();
 }

@@ -101,6 +101,7 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
   static_assert(EPI != EPI_RESID || (I0 == 0 && I1 == 4), "row statistics are taken over the whole tile");
   static_assert(EPI != EPI_GEGLU || (I0 % 2 == 0 && I1 % 2 == 0), "gate / up steps are stored in pairs");
   const float inv_k = 1.0f / (float)p.k_true;
+  const float inv_hd = EPI == EPI_QKV ? 1.0f / (float)p.head_dim : 0.f;
   {
     float rs = 1.f, mu = 0.f;
     float st_a = 0.f, st_b = 0.f;   // EPI_RESID: sum / sum of squares of this lane's fp32 outputs
@@ -218,7 +219,7 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
               cx.st(reinterpret_cast<bf16x2*>(dst + (size_t)(d1 >> 4) * 512 + ((d1 & 15) >> 3) * 256 + (d1 & 7)), hi);
             }
           } else {
-            const int head = nl / p.head_dim;
+            const int head = (int)(((float)nl + 0.5f) * inv_hd);   // nl / head_dim: exact, nl < 2^16
             const int d = nl - head * p.head_dim;    // multiple of 4
             const bf16x4 ob = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
             {
@@ -229,7 +230,7 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
           }
         } else {
           const int nl = n4 - p.q_cols - p.k_cols;
-          const int head = nl / p.head_dim;
+          const int head = (int)(((float)nl + 0.5f) * inv_hd);
           const int d = nl - head * p.head_dim;
           if (head < p.kv_heads) {
             const int s2 = kk >> 4, g = (kk & 15) >> 3, hh = (kk & 7) >> 2, jp = kk & 3;

@@ -279,24 +279,57 @@ hipError_t launch_patchify(hipStream_t st, const float* images, int n_views, int
   return hipGetLastError();
 }
 
-// prompt rows: out[row0 + i][:] = scale * table[clamp(ids[i])][:]
-__global__ __launch_bounds__(256) void embed_prompt_kernel(const int32_t* ids, int n, const bf16* table, int vocab, int E,
-                                                           float scale, float* out_f32, bf16* out_bf16, int row0) {
-  const int i = blockIdx.y;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n || c >= E) return;
-  int id = ids[i];
+// prompt rows: out[row0 + i][:] = scale * table[clamp(ids[i])][:], one block per row; the gain-scaled bf16 copy and the
+// row statistics as the projector leaves them for the image rows (partial sums per plane: all in plane 0, zeros after)
+__global__ __launch_bounds__(256) void embed_prompt_kernel(const int32_t* ids, const bf16* table, int vocab, int E, float scale,
+                                                           float* out_f32, bf16* out_bf16, int row0, const float* gain,
+                                                           float* stat_parts, int planes, int stat_rows) {
+  __shared__ float sred[2][4];
+  const int row = row0 + (int)blockIdx.x;
+  int id = ids[blockIdx.x];
   id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);   // out-of-range ids are clamped, never read out of bounds
-  const float v = scale * (float)table[(size_t)id * E + c];
-  out_f32[(size_t)(row0 + i) * E + c] = v;
-  out_bf16[xf_index(row0 + i, c, E >> 4)] = (bf16)v;
+  float sa = 0.f, sb = 0.f;
+  for (int c = (int)threadIdx.x * 8; c < E; c += 2048) {
+    const bf16x8 src = *reinterpret_cast<const bf16x8*>(table + (size_t)id * E + c);
+    f32x4 v0, v1;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      v0[j] = scale * (float)src[j];
+      v1[j] = scale * (float)src[j + 4];
+      sa += v0[j] + v1[j];
+      sb += v0[j] * v0[j] + v1[j] * v1[j];
+    }
+    *reinterpret_cast<f32x4*>(out_f32 + (size_t)row * E + c) = v0;
+    *reinterpret_cast<f32x4*>(out_f32 + (size_t)row * E + c + 4) = v1;
+    v0 *= *reinterpret_cast<const f32x4*>(gain + c);
+    v1 *= *reinterpret_cast<const f32x4*>(gain + c + 4);
+    const bf16x8 o = {(bf16)v0[0], (bf16)v0[1], (bf16)v0[2], (bf16)v0[3], (bf16)v1[0], (bf16)v1[1], (bf16)v1[2], (bf16)v1[3]};
+    *reinterpret_cast<bf16x8*>(out_bf16 + xf_index(row, c, E >> 4)) = o;
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    sa += __shfl_xor(sa, off, 64);
+    sb += __shfl_xor(sb, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sred[0][threadIdx.x >> 6] = sa;
+    sred[1][threadIdx.x >> 6] = sb;
+  }
+  __syncthreads();
+  for (int k = (int)threadIdx.x; k < planes; k += 256) {
+    const float2 v = k == 0 ? make_float2(sred[0][0] + sred[0][1] + sred[0][2] + sred[0][3], sred[1][0] + sred[1][1] + sred[1][2] + sred[1][3])
+                            : make_float2(0.f, 0.f);
+    *reinterpret_cast<float2*>(stat_parts + 2 * ((size_t)k * stat_rows + row)) = v;
+  }
 }
 hipError_t launch_embed_prompt(hipStream_t st, const int32_t* ids, int n, const bf16* table, int vocab, int E, float scale,
-                               float* out_f32, bf16* out_bf16, int row0) {
+                               float* out_f32, bf16* out_bf16, int row0, const float* gain, float* stat_parts, int planes,
+                               int stat_rows) {
   if (n <= 0) return hipSuccess;
-  if (ids == nullptr || table == nullptr || vocab <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(embed_prompt_kernel, dim3((E + 255) / 256, n), dim3(256), 0, st, ids, n, table, vocab, E, scale,
-                     out_f32, out_bf16, row0);
+  if (ids == nullptr || table == nullptr || vocab <= 0 || E % 8 != 0 || gain == nullptr || stat_parts == nullptr || planes < 1 || stat_rows < row0 + n)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(embed_prompt_kernel, dim3(n), dim3(256), 0, st, ids, table, vocab, E, scale, out_f32, out_bf16, row0, gain,
+                     stat_parts, planes, stat_rows);
   return hipGetLastError();
 }
 

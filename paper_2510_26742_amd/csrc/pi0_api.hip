@@ -307,7 +307,7 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
   w.lx8s = cur.take((size_t)d.maxPc * 32 * d.E / 32 + 256);
   w.lmid8 = cur.take((size_t)d.maxPc * 32 * d.F);
   w.lmid8s = cur.take((size_t)d.maxPc * 32 * d.F / 32 + 256);
-  w.vstat_parts = cur.take((size_t)(d.Dv / 32) * d.maxI * 2 * 4);                     // [32-column tile][maxI][2]
+  w.vstat_parts = cur.take((size_t)(d.Dv / 32) * d.maxPc * 32 * 2 * 4);               // [32-column tile][maxPc * 32][2]
   w.lstat_parts = cur.take((size_t)(d.E / 32) * d.maxPc * 32 * 2 * 4);                // [32-column tile][maxPc * 32][2]
   w.esync = cur.take((size_t)GB_WORDS * 4);
   w.eparams = cur.take(sizeof(ExpertLoopParams));
@@ -349,12 +349,13 @@ enum { KIND_PREFILL = 0, KIND_DENOISE = 1, KIND_INFER = 2 };
 // gfx950 counterparts).  Overridable for tuning runs through pi0_tune,
 // e.g. "vis=1,lqkv=1,lgu=0,vo=1,vd=1,lo=0,ld=0,zvo=6,zlo=8,zld=16".
 struct Tune {
-  int vis = TILE_MID;     // vision patch / projector (and QKV / up unless overridden below)
-  int vqkv = -1, vup = -1; // vision QKV / up tile (-1: QKV on the entry kernel up to 256 tokens, else same as vis)
-  int lqkv = -1;          // prefix QKV (-1: 64 x 64 tiles up to 256 tokens, 64 x 128 beyond)
+  // -1 everywhere below: TILE_STREAM (gemm_stream.hip), whose tile follows from the shape
+  int vis = -1;           // vision patch / projector (and QKV / up unless overridden below)
+  int vqkv = -1, vup = -1; // vision QKV / up (-1: same as vis)
+  int lqkv = -1;          // prefix QKV
   int lgu = -1;           // prefix gate||up (-1: 128, 192 or 256 tokens x 256 features, whichever fills the 256 CUs at the least cost)
-  int vo = TILE_MID, vd = -1, lo = -1, ld = TILE_WIDE128;   // split-K partial GEMMs: vision O / down, prefix O / down
-  int zvo = -1, zlo = -1, zld = -1, zvd = -1;   // -1: chosen from the number of tokens (measured optima at 1 / 2 / 3 views)
+  int vo = -1, vd = -1, lo = -1, ld = TILE_WIDE128;   // tile of vision O / down, prefix O as split-K partial GEMMs; prefix down
+  int zvo = -1, zlo = -1, zld = -1, zvd = -1;   // their split counts (-1: chosen from the number of tokens)
   // warm-up blocks carried by the expert's launches (0 = none): QKV, attention, O, down.  Used instead of the read-ahead
   // kernel below with ras=0
   int pfq = 64, pfa = 64, pfo = 128, pfd = 128;
@@ -365,9 +366,9 @@ struct Tune {
   // scores (-1: 4 with one key share, 2 with several; measured -0.2 ms of denoise.  The prefix attention gains nothing)
   int avs = -1;
   int ae16 = 1;           // expert O / down on 16 x 16 tiles (256 blocks) instead of 32 x 32 (64 blocks)
-  // O projections as one launch over the whole k range (TILE_ENTRY: residual epilogue in the GEMM, no partial
-  // buffer, no reduction launch): vision O, prefix O.  -1: up to 256 tokens (measured: -0.06 ms at one view,
-  // nothing or a loss beyond, where the blocks' operand reads add up to more than the reduction launch costs)
+  // O projections (vision, prefix) as split-K partial GEMMs + reduction (0) or one launch over the whole k range (1:
+  // TILE_STREAM, the consumer adds up the partial row statistics).  -1: the latter unless vo / zvo (lo / zlo) ask for
+  // split-K; beyond 256 tokens a launch of its own adds up the statistics
   int fko = -1, fkl = -1;
   // read-ahead for the expert as one kernel on a second stream beside the compute launches: number of its
   // blocks (0 = warm-up blocks inside the launches instead, see pfq .. pfd), layer-steps it runs ahead,
@@ -526,10 +527,12 @@ void gemm_splitk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int 
 // the same operation as one GEMM over the whole k range: bias / residual / gain-scaled shadow in the
 // GEMM's epilogue, row statistics left as one partial sum per 32-column tile in parts[n tile][stat_rows][2]
 void gemm_fullk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int k_true, const float* bias, float* resid_io,
-                      bf16* shadow, int n_true, float* parts, int stat_rows, const float* gain, int tile = TILE_ENTRY) {
+                      bf16* shadow, int n_true, float* parts, int stat_rows, const float* gain, int tile,
+                      const float* resid_in = nullptr, int resid_mod = 0) {
   GemmParams p = gp_base(r.c, pw, X, ldx, M, tile, k_true);
   p.bias = bias;
-  p.resid = resid_io;
+  p.resid = resid_in != nullptr ? resid_in : resid_io;
+  p.resid_mod = resid_mod;
   p.out_f32 = resid_io;
   p.out_bf16 = shadow;
   p.ldo = n_true; p.ldo2 = n_true; p.n_valid = n_true;
@@ -555,29 +558,63 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   const WsLayout& w = c->wl;
   const Tune& T = c->tune;
   const int I = n_views * d.T, P = I + n_prompt;
+  // Row statistics of the two residual streams: whole-row sums (a reduction launch wrote them), or partial sums per
+  // 32-column tile (a GEMM over the whole k range did); `planes` says which the last writer left.
+  int vplanes = 0, lplanes = 0;
+  const int stat_rows = d.maxPc * 32;   // rows per plane, both streams
+  auto vision_stats = [&](GemmParams& p) {
+    p.rowstat = vplanes > 0 ? at<float>(c, w.vstat_parts) : at<float>(c, w.vstat);
+    p.rowstat_parts = vplanes; p.stat_rows = stat_rows;
+  };
+  auto prefix_stats = [&](GemmParams& p) {
+    p.rowstat = lplanes > 0 ? at<float>(c, w.lstat_parts) : at<float>(c, w.lstat);
+    p.rowstat_parts = lplanes; p.stat_rows = stat_rows;
+  };
+  // Beyond 256 tokens the O projection's partial sums are added up by a launch of their own: the blocks of the GEMM
+  // behind it hold up to 256 rows, and each would read all planes of its rows (128 KB).  A consumer takes 64 planes at most.
+  auto sum_vision = [&](int tokens_over) {
+    if (vplanes > 64 || (vplanes > 0 && I > tokens_over)) {
+      RUN(r, launch_row_sums(r.s, at<float>(c, w.vstat_parts), vplanes, stat_rows, I, at<float>(c, w.vstat)));
+      vplanes = 0;
+    }
+  };
+  auto sum_prefix = [&](int tokens_over) {
+    if (lplanes > 64 || (lplanes > 0 && P > tokens_over)) {
+      RUN(r, launch_row_sums(r.s, at<float>(c, w.lstat_parts), lplanes, stat_rows, P, at<float>(c, w.lstat)));
+      lplanes = 0;
+    }
+  };
+  const int NEVER = 1 << 30;
   // A0: patches -> tokens (+bias, +position embedding)
   r.cls = PI0_OP_MISC;
   RUN(r, launch_patchify(r.s, at<float>(c, w.st_images), n_views, c->cfg.img_size, c->cfg.patch, at<bf16>(c, w.xpatch), d.PDp));
   r.cls = PI0_OP_VIS_PATCH;
-  gemm_splitk_resid(r, w.patch, at<bf16>(c, w.xpatch), d.PDp, I, d.PD, 1, w.patch.k_pad, at<float>(c, w.patch.bias),
-                    at<float>(c, w.vh), at<bf16>(c, w.vh_b), d.Dv, T.vis, at<float>(c, w.vstat), at<float>(c, w.g_v1[0]),
-                    at<float>(c, w.pos), d.T);
+  if (T.vis < 0) {
+    gemm_fullk_resid(r, w.patch, at<bf16>(c, w.xpatch), d.PDp, I, d.PD, at<float>(c, w.patch.bias), at<float>(c, w.vh), at<bf16>(c, w.vh_b),
+                     d.Dv, at<float>(c, w.vstat_parts), stat_rows, at<float>(c, w.g_v1[0]), TILE_STREAM, at<float>(c, w.pos), d.T);
+    vplanes = w.patch.n_pad / 32;
+    sum_vision(NEVER);
+  } else {
+    gemm_splitk_resid(r, w.patch, at<bf16>(c, w.xpatch), d.PDp, I, d.PD, 1, w.patch.k_pad, at<float>(c, w.patch.bias),
+                      at<float>(c, w.vh), at<bf16>(c, w.vh_b), d.Dv, T.vis, at<float>(c, w.vstat), at<float>(c, w.g_v1[0]),
+                      at<float>(c, w.pos), d.T);
+  }
   const int vchunks = I / 32;
   const int zvo = T.zvo > 0 ? T.zvo : (I <= 256 ? 3 : I <= 512 ? 2 : 1);
-  const int tvd = T.vd >= 0 ? T.vd : (I <= 256 ? TILE_MID : TILE_SQ128);
   const int zvd = T.zvd > 0 ? T.zvd : (I <= 512 ? 4 : 2);
-  // one view: the QKV GEMM has too few 64 x 128 tiles for 256 CUs; 64 x 64 tiles with every load issued at entry
-  // two and three views: 128 x 128 tiles need fewer operand bytes per CU than 64 x 128 once they still fill the chip
-  const int tqkv = T.vqkv >= 0 ? T.vqkv : (I <= 256 ? TILE_ENTRY : I <= 512 ? T.vis : TILE_MID2);   // 3 views: 324 blocks, two per CU
-  const int tup = T.vup >= 0 ? T.vup : (I <= 256 ? T.vis : TILE_SQ128);
-  const bool fko = T.fko >= 0 ? T.fko != 0 : I <= 256;
+  const int tproj = T.vis >= 0 ? T.vis : TILE_STREAM;
+  const int tqkv = T.vqkv >= 0 ? T.vqkv : tproj;
+  const int tup = T.vup >= 0 ? T.vup : tproj;
+  const int tvo = T.vo >= 0 ? T.vo : TILE_MID;
+  const bool vo_stream = T.fko == 1 || (T.fko < 0 && T.vo < 0 && T.zvo < 0), vd_stream = T.vd < 0 && T.zvd < 0;
+  const int tvd = T.vd >= 0 ? T.vd : (I <= 256 ? TILE_MID : TILE_SQ128);
   for (int l = 0; l < d.Lv; l++) {
     const WsVis& L = w.vis[l];
     {  // A1: LN -> QKV (+bias), keys/values straight into attention fragment order
       GemmParams p = gp_base(c, L.qkv, at<bf16>(c, w.vh_b), d.Dv, I, tqkv, d.Dv);
       p.bias = at<float>(c, L.qkv.bias);
       p.colsum = at<float>(c, L.qkv.colsum);
-      p.rowstat = at<float>(c, w.vstat);
+      vision_stats(p);
       p.out_bf16 = at<bf16>(c, w.vq);
       p.q_mbs = vchunks;
       p.kfrag = at<bf16>(c, w.vk);
@@ -604,20 +641,23 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     }
     // A3: O-projection + bias + residual
     r.cls = PI0_OP_VIS_O;
-    if (fko)
+    if (vo_stream) {
       gemm_fullk_resid(r, L.o, at<bf16>(c, w.vattn), d.Dv, I, d.Dv, at<float>(c, L.o.bias), at<float>(c, w.vh),
-                       at<bf16>(c, w.vh_b), d.Dv, at<float>(c, w.vstat_parts), d.maxI, at<float>(c, w.g_v2[l]),
-                       I <= 256 ? TILE_ENTRY : T.vo);
-    else
+                       at<bf16>(c, w.vh_b), d.Dv, at<float>(c, w.vstat_parts), stat_rows, at<float>(c, w.g_v2[l]),
+                       TILE_STREAM);
+      vplanes = L.o.n_pad / 32;
+      sum_vision(T.fko == 1 ? NEVER : 256);
+    } else {
       gemm_splitk_resid(r, L.o, at<bf16>(c, w.vattn), d.Dv, I, d.Dv, zvo, round_up(ceil_div(L.o.k_pad, zvo), 64),
-                        at<float>(c, L.o.bias), at<float>(c, w.vh), at<bf16>(c, w.vh_b), d.Dv, T.vo, at<float>(c, w.vstat),
+                        at<float>(c, L.o.bias), at<float>(c, w.vh), at<bf16>(c, w.vh_b), d.Dv, tvo, at<float>(c, w.vstat),
                         at<float>(c, w.g_v2[l]));
+      vplanes = 0;
+    }
     {  // A4: LN -> up (+bias, GELU)
       GemmParams p = gp_base(c, L.up, at<bf16>(c, w.vh_b), d.Dv, I, tup, d.Dv);
       p.bias = at<float>(c, L.up.bias);
       p.colsum = at<float>(c, L.up.colsum);
-      p.rowstat = at<float>(c, w.vstat);
-      if (fko) { p.rowstat = at<float>(c, w.vstat_parts); p.rowstat_parts = L.o.n_pad / 32; p.stat_rows = d.maxI; }
+      vision_stats(p);
       p.out_bf16 = at<bf16>(c, w.vmid);
       p.ldo = d.Fv_kp; p.n_valid = L.up.n_pad; p.act = ACT_GELU;
       r.cls = PI0_OP_VIS_UP;
@@ -625,37 +665,47 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     }
     // A5: down (+bias, residual)
     r.cls = PI0_OP_VIS_DOWN;
-    gemm_splitk_resid(r, L.down, at<bf16>(c, w.vmid), d.Fv_kp, I, d.Fv, zvd, round_up(ceil_div(L.down.k_pad, zvd), 64),
-                      at<float>(c, L.down.bias), at<float>(c, w.vh), at<bf16>(c, w.vh_b), d.Dv, tvd, at<float>(c, w.vstat),
-                      at<float>(c, l + 1 < d.Lv ? w.g_v1[l + 1] : w.g_vf));
+    const float* next_gain = at<float>(c, l + 1 < d.Lv ? w.g_v1[l + 1] : w.g_vf);
+    if (vd_stream) {
+      gemm_fullk_resid(r, L.down, at<bf16>(c, w.vmid), d.Fv_kp, I, d.Fv, at<float>(c, L.down.bias), at<float>(c, w.vh),
+                       at<bf16>(c, w.vh_b), d.Dv, at<float>(c, w.vstat_parts), stat_rows, next_gain, TILE_STREAM);
+      vplanes = L.down.n_pad / 32;
+      sum_vision(NEVER);
+    } else {
+      gemm_splitk_resid(r, L.down, at<bf16>(c, w.vmid), d.Fv_kp, I, d.Fv, zvd, round_up(ceil_div(L.down.k_pad, zvd), 64),
+                        at<float>(c, L.down.bias), at<float>(c, w.vh), at<bf16>(c, w.vh_b), d.Dv, tvd, at<float>(c, w.vstat), next_gain);
+      vplanes = 0;
+    }
     if (taps) taps->put(r, at<float>(c, w.vh), (size_t)I * d.Dv);
   }
   {  // A6: final LN -> projector (+bias) = prefix image embeddings
-    GemmParams p = gp_base(c, w.proj, at<bf16>(c, w.vh_b), d.Dv, I, T.vis, d.Dv);
+    GemmParams p = gp_base(c, w.proj, at<bf16>(c, w.vh_b), d.Dv, I, tproj, d.Dv);
     p.bias = at<float>(c, w.proj.bias);
     p.colsum = at<float>(c, w.proj.colsum);
-    p.rowstat = at<float>(c, w.vstat);
+    vision_stats(p);
     p.out_f32 = at<float>(c, w.lx);
     p.out_bf16 = at<bf16>(c, w.lx_b);
     p.ldo = d.E; p.ldo2 = d.E; p.n_valid = d.E;
+    p.gain = at<float>(c, w.g_l1[0]);
+    p.stat_out = at<float>(c, w.lstat_parts);
     r.cls = PI0_OP_VIS_PROJ;
-    RUN_GEMM(r, T.vis, PRO_LN, EPI_RESID, p, 1);
+    RUN_GEMM(r, tproj, PRO_LN, EPI_RESID, p, 1);
+    lplanes = d.E / 32;
     r.cls = PI0_OP_MISC;
   }
   if (taps) taps->put(r, at<float>(c, w.lx), (size_t)I * d.E);
-  if (n_prompt > 0) {  // B0: prompt embeddings after the image tokens
+  if (n_prompt > 0) {  // B0: prompt embeddings after the image tokens, with statistics and gain like the image rows
     RUN(r, launch_embed_prompt(r.s, at<int32_t>(c, w.st_ids), n_prompt, at<bf16>(c, w.embed), c->cfg.vocab, d.E,
-                               sqrtf((float)d.E), at<float>(c, w.lx), at<bf16>(c, w.lx_b), I));
+                               sqrtf((float)d.E), at<float>(c, w.lx), at<bf16>(c, w.lx_b), I, at<float>(c, w.g_l1[0]),
+                               at<float>(c, w.lstat_parts), lplanes, stat_rows));
   }
-  RUN(r, launch_row_stats(r.s, at<float>(c, w.lx), d.E, P, d.E, d.E, at<float>(c, w.g_l1[0]), at<bf16>(c, w.lx_b),
-                          at<float>(c, w.lstat)));
+  sum_prefix(NEVER);
   const int pchunks = ceil_div(P, 32);
-  const int tlqkv = T.lqkv >= 0 ? T.lqkv : (P <= 256 ? TILE_SMALL : P <= 512 ? TILE_MID : TILE_MID2);   // 3 views: 30.0 -> 25.3 us
+  const int tlqkv = T.lqkv >= 0 ? T.lqkv : TILE_STREAM;
+  const bool lo_stream = T.fkl == 1 || (T.fkl < 0 && T.lo < 0 && T.zlo < 0);
   const int tlo = T.lo >= 0 ? T.lo : (P <= 512 ? TILE_MID : TILE_SQ128);
   const int zlo = T.zlo > 0 ? T.zlo : (P <= 256 ? 4 : 2);
   const bool mx = c->precision == PI0_PRECISION_MXFP8_PREFIX_MLP;
-  // reduced precision: the GeGLU epilogue takes whole-row statistics, so the O projection keeps its reduction launch
-  const bool fkl = mx ? false : (T.fkl >= 0 ? T.fkl != 0 : P <= 256);
   // gate||up: 128 blocks of 256 features per token tile of 128, 192 or 256 tokens.  A block's time goes with its
   // height, so a choice costs height x rounds on 256 compute units; take the cheapest, the taller tile on ties
   // (fewer operand bytes per CU and flop).  256 / 512 / 768 / 816 tokens -> 128 / 256 / 192 / 256.
@@ -679,7 +729,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     bf16* vc = reinterpret_cast<bf16*>(c->ws + w.vcache + (size_t)r.slot_w * w.vcache_slot + (size_t)l * w.vcache_layer);
     {  // B1: RMS -> QKV, RoPE, keys/values into the cache (last layer: keys/values only)
       GemmParams p = gp_base(c, L.qkv, at<bf16>(c, w.lx_b), d.E, P, tlqkv, d.E);
-      p.rowstat = at<float>(c, w.lstat);
+      prefix_stats(p);
       p.out_bf16 = at<bf16>(c, w.lq);
       p.q_mbs = pchunks;
       p.kfrag = kc; p.vfrag = vc;
@@ -704,14 +754,31 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     }
     // B3: O-projection + residual
     r.cls = PI0_OP_LLM_O;
-    if (fkl)
+    if (lo_stream) {
       gemm_fullk_resid(r, L.o, at<bf16>(c, w.lattn), d.H * 256, P, d.H * 256, nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b),
-                       d.E, at<float>(c, w.lstat_parts), d.maxPc * 32, at<float>(c, w.g_l2[l]), P <= 256 ? TILE_ENTRY : tlo);
-    else
+                       d.E, at<float>(c, w.lstat_parts), stat_rows, at<float>(c, w.g_l2[l]), TILE_STREAM);
+      lplanes = d.E / 32;
+      if (mx) {   // the MXFP8 copy of x * (1 + g) for gate||up and whole-row statistics, from the rows just written
+        r.cls = PI0_OP_REDUCE;
+        ReduceParams q;
+        memset(&q, 0, sizeof(q));
+        q.M = P; q.N = d.E; q.ldp = d.E; q.ldo = d.E; q.ldo2 = d.E;
+        q.resid = at<float>(c, w.lx);
+        q.stat_out = at<float>(c, w.lstat);
+        q.gain = at<float>(c, w.g_l2[l]);
+        q.out8 = c->ws + w.lx8; q.out8_scales = c->ws + w.lx8s;
+        RUN(r, launch_splitk_reduce(r.s, q));
+        lplanes = 0;
+      } else {
+        sum_prefix(T.fkl == 1 ? NEVER : 256);
+      }
+    } else {
       gemm_splitk_resid(r, L.o, at<bf16>(c, w.lattn), d.H * 256, P, d.H * 256, zlo,
                         round_up(ceil_div(L.o.k_pad, zlo), 64), nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b), d.E, tlo,
                         at<float>(c, w.lstat), at<float>(c, w.g_l2[l]), nullptr, 0, false, false,
                         mx ? c->ws + w.lx8 : nullptr, mx ? c->ws + w.lx8s : nullptr);   // MXFP8 copy for gate||up
+      lplanes = 0;
+    }
     if (mx) {
       // B4 / B5 on MXFP8 operands: x * (1 + g) was quantised per 32 columns by the O projection's reduction, gate||up
       // quantises the GeGLU product in its epilogue, down goes as split-K partials into the usual reduction
@@ -754,8 +821,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     }
     {  // B4: RMS -> gate||up with fused GELU gate
       GemmParams p = gp_base(c, L.gu, at<bf16>(c, w.lx_b), d.E, P, tlgu, d.E);
-      p.rowstat = at<float>(c, w.lstat);
-      if (fkl) { p.rowstat = at<float>(c, w.lstat_parts); p.rowstat_parts = L.o.n_pad / 32; p.stat_rows = d.maxPc * 32; }
+      prefix_stats(p);
       p.out_bf16 = at<bf16>(c, w.lmid);
       p.ldo = d.F;
       r.cls = PI0_OP_LLM_GATEUP;
@@ -766,6 +832,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     gemm_splitk_resid(r, L.down, at<bf16>(c, w.lmid), d.F, P, d.F, zld,
                       round_up(ceil_div(L.down.k_pad, zld), 64), nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b),
                       d.E, T.ld, at<float>(c, w.lstat), at<float>(c, w.g_l1[l + 1]));
+    lplanes = 0;
     if (taps) taps->put(r, at<float>(c, w.lx), (size_t)P * d.E);
   }
   if (taps && taps->base) {
@@ -1439,6 +1506,9 @@ int pi0_tune(pi0_ctx* c, const char* env) {
         if (v >= k.lo && v <= k.hi) *k.dst = v;
       }
     }
+    for (int* v : {&c->tune.vis, &c->tune.vqkv, &c->tune.vup, &c->tune.lqkv, &c->tune.vo, &c->tune.vd, &c->tune.lo}) {
+      if (*v == 8) *v = -1;   // no such tile
+    }
     for (int* v : {&c->tune.pfq, &c->tune.pfa, &c->tune.pfo, &c->tune.pfd}) *v &= ~15;
     if (c->tune.rad == 7) c->tune.rad = 6;   // the read-ahead kernel exists with 1 .. 6 and 8 loads in flight
   }
@@ -1511,6 +1581,8 @@ int pi0_load_weights(pi0_ctx* c, const void* d_blob, size_t blob_bytes, void* d_
   hipError_t e;
   if (!c->attrs_set) {
     e = gemm_init_attributes();
+    if (e != hipSuccess) return fail_hip(c, e);
+    e = gemm_stream_init_attributes();
     if (e != hipSuccess) return fail_hip(c, e);
     e = attention_init_attributes();
     if (e != hipSuccess) return fail_hip(c, e);

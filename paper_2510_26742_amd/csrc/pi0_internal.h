@@ -170,10 +170,10 @@ enum GemmTile {
   // two feature tiles per wave: an activation fragment read from LDS feeds two MFMAs (prefix gate||up / down only)
   TILE_WIDE = 6,          // 256 tokens x 256 features per block (4 waves x 2 feature tiles), 2 stages
   TILE_WIDE128 = 7,       // 128 tokens x 256 features per block, 3 stages
-  TILE_ENTRY = 8,         // 64 tokens x 32 / 64 features per block, k <= 2048 split over 8 waves, every load issued at entry
   TILE_SQ128 = 9,         // 128 tokens x 128 features per block (4 waves), 5 stages: the mid-size GEMMs at three views
   TILE_T192 = 10,         // 192 tokens x 256 features per block, 2 stages: 768 tokens in four tiles
-  TILE_MID2 = 11          // 64 tokens x 128 features as TILE_MID, cut for two resident blocks per compute unit
+  TILE_MID2 = 11,         // 64 tokens x 128 features as TILE_MID, cut for two resident blocks per compute unit
+  TILE_STREAM = 12        // whole k range, split over the waves of a block (gemm_stream.hip); the tile follows from the shape
 };
 
 // ------------------------------------------------------------------------------------------
@@ -227,10 +227,17 @@ hipError_t launch_pack_weights_mx(hipStream_t s, const PackSrc& src, unsigned ch
 
 hipError_t launch_gemm(hipStream_t s, int tile, int pro, int epi, const GemmParams& p, int z_splits);
 int gemm_rows_per_tile(int tile);
+// the mid-size GEMMs of the vision tower and the prefix over the whole k range (gemm_stream.hip); the tile is chosen from
+// the shape.  (pro, epi): LN / RMS with QKV, LN with BF16, none / LN with RESID
+hipError_t launch_gemm_stream(hipStream_t s, int pro, int epi, const GemmParams& p);
+hipError_t gemm_stream_init_attributes();
+// out[m] = (sum, sum of squares) of row m from partial statistics [planes][stat_rows][2]
+hipError_t launch_row_sums(hipStream_t s, const float* parts, int planes, int stat_rows, int M, float* out);
 hipError_t gemm_init_attributes();
 
 // Split-K reduction: out[m][n] = sum_z part[z][m][n] (+bias[n]) (+resid[m % resid_mod][n]); bf16 shadow in XF
-// layout; (sum, sum sq) of each output row.
+// layout; (sum, sum sq) of each output row.  Z = 0: only the statistics and the MXFP8 copy of the rows in resid
+// (out_f32 and out_bf16 null).
 struct ReduceParams {
   const float* part;  // [Z][M][ldp]
   int Z, M, N, ldp;
@@ -246,9 +253,6 @@ struct ReduceParams {
   unsigned char* out8_scales;
 };
 hipError_t launch_splitk_reduce(hipStream_t s, const ReduceParams& p);
-// stat_out[m] = (sum, sum sq) of fp32 row m of x; out_xf = bf16(x * gain) in XF layout with k_pad columns
-hipError_t launch_row_stats(hipStream_t s, const float* x, int ld, int M, int K, int k_pad, const float* gain, bf16* out_xf,
-                            float* stat_out);
 // dst[i] = src[i] (+1 if one_plus): fp32 gain vectors of the norms
 hipError_t launch_gain_vector(hipStream_t s, const bf16* src, float* dst, int n, int one_plus);
 
@@ -308,7 +312,7 @@ hipError_t launch_time_fold(hipStream_t s, const bf16* wa, const bf16* ba, const
 
 hipError_t launch_patchify(hipStream_t s, const float* images, int n_views, int img, int patch, bf16* out, int ld);
 hipError_t launch_embed_prompt(hipStream_t s, const int32_t* ids, int n, const bf16* table, int vocab, int E, float scale,
-                               float* out_f32, bf16* out_bf16, int row0);
+                               float* out_f32, bf16* out_bf16, int row0, const float* gain, float* stat_parts, int planes, int stat_rows);
 hipError_t launch_state_token(hipStream_t s, const float* state, int state_dim, const float* ws, const float* bs, int X,
                               float* out, int* progress);
 // read-ahead kernel of the action expert: per layer RA_REGIONS byte ranges (weights of the four GEMMs, the

@@ -179,8 +179,8 @@ def class_rooflines(work: dict, timing: dict) -> list:
 
 # which kernel (template family, as rocprofv3 names it) runs each operation class
 KERNEL_OF_CLASS = {
-    "vis_patch": "gemm_kernel", "vis_qkv": "gemm_kernel", "vis_o": "gemm_kernel", "vis_up": "gemm_kernel",
-    "vis_down": "gemm_kernel", "vis_proj": "gemm_kernel", "llm_qkv": "gemm_kernel", "llm_o": "gemm_kernel",
+    "vis_patch": "gemm_stream_kernel", "vis_qkv": "gemm_stream_kernel", "vis_o": "gemm_stream_kernel", "vis_up": "gemm_stream_kernel",
+    "vis_down": "gemm_stream_kernel", "vis_proj": "gemm_stream_kernel", "llm_qkv": "gemm_stream_kernel", "llm_o": "gemm_stream_kernel",
     "llm_gateup": "gemm_kernel", "llm_down": "gemm_kernel",
     "vis_attn": "attention_kernel", "llm_attn": "attention_kernel", "exp_attn": "attention_kernel",
     "exp_qkv": "gemm_skinny_kernel", "exp_gateup": "gemm_skinny_kernel", "exp_out": "gemm_skinny_kernel",
@@ -190,11 +190,8 @@ KERNEL_OF_CLASS = {
 
 
 def kernel_of_class(name: str, prefix_tokens: int | None = None):
-    """Kernel template family that runs an operation class.  Up to 256 tokens the library's default schedule runs
-    the vision QKV projection and the vision and prefix O projections on gemm_entry_kernel (every load issued at
-    entry; the O projections over the whole k range with the residual epilogue in the GEMM)."""
-    if prefix_tokens is not None and prefix_tokens <= 256 and name in ("vis_qkv", "vis_o", "llm_o"):
-        return "gemm_entry_kernel"
+    """Kernel template family that runs an operation class in the library's default schedule (the same for every
+    number of tokens)."""
     return KERNEL_OF_CLASS.get(name)
 
 
