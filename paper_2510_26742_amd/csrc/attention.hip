@@ -39,6 +39,12 @@ __global__ __launch_bounds__(512, 4) void attention_vision2_kernel(AttnParams p)
   attention_body<80, 3, 1, VRING, 0>(p, LaunchCtx::from_block_idx(), smem_raw);
 }
 
+// the action expert's case (attention_suffix_body): 16 query rows per block
+__global__ __launch_bounds__(512) void attention_suffix_kernel(AttnParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  attention_suffix_body(p, LaunchCtx::from_block_idx(), smem_raw);
+}
+
 template <int DQK>
 static int attn_smem(int ntot) { return 3 * (DQK / 16) * 1024 + 2 * ATT_WAVES * 32 * 4 + ntot * 2048; }
 
@@ -57,6 +63,8 @@ hipError_t attention_init_attributes() {
   }
   ATTN_VARIANTS(X)
 #undef X
+  if (const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_suffix_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_SUFFIX_SMEM_MAX); e != hipSuccess)
+    return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_vision2_kernel<2>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              attn_smem<80>(8));
 }
@@ -85,7 +93,8 @@ hipError_t launch_attention(hipStream_t s, const AttnParams& p) {
   if (n0 > 32) return hipErrorInvalidValue;   // at most 1024 keys in segment 0 per query row
   if (p.v_split != 0 && p.v_split != 1 && ((p.v_split != 2 && p.v_split != 4 && p.v_split != 8) || p.head_dim != 256)) return hipErrorInvalidValue;
   const int vs = p.v_split > 1 ? p.v_split : 1;
-  dim3 grid(((p.Tq + 31) / 32) * vs, p.heads, p.key_splits > 1 ? p.key_splits : 1);
+  const bool suffix = attn_suffix_ok(p, n0);   // the action expert: 16 query rows per block
+  dim3 grid((suffix ? (p.Tq + 15) / 16 : (p.Tq + 31) / 32) * vs, p.heads, p.key_splits > 1 ? p.key_splits : 1);
   if (p.pf.blocks != 0) {   // warm-up blocks as extra grid rows
     const PrefetchDesc& d = p.pf;
     if (d.blocks < 0 || d.blocks % 16 != 0 || d.blocks > 1024 || d.sink == nullptr || d.blocks % (int)grid.x != 0) return hipErrorInvalidValue;
@@ -96,7 +105,9 @@ hipError_t launch_attention(hipStream_t s, const AttnParams& p) {
     }
     grid.y += d.blocks / grid.x;
   }
-  if (p.head_dim == 256) {
+  if (suffix) {
+    attention_suffix_kernel<<<grid, dim3(512), attn_suffix_smem_bytes(n0, vs), s>>>(p);
+  } else if (p.head_dim == 256) {
     if (n0 <= 8) attention_kernel<256, 8, 1, 8, 10><<<grid, dim3(512), attn_smem<256>(ntot), s>>>(p);
     else if (n0 <= 16) attention_kernel<256, 8, 2, 8, 0><<<grid, dim3(512), attn_smem<256>(ntot), s>>>(p);
     else attention_kernel<256, 8, 4, 8, 0><<<grid, dim3(512), attn_smem<256>(ntot), s>>>(p);

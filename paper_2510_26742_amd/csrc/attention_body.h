@@ -1,5 +1,5 @@
-// Body of the attention kernels (see attention.hip for the plan), templated on the execution context so that the
-// action expert's attention also runs inside the persistent kernel of the denoise loop (exec_ctx.h).
+// Bodies of the attention kernels: attention_body (see attention.hip for the plan), and attention_suffix_body for the
+// action expert, which also runs inside the persistent kernel of the denoise loop (exec_ctx.h).
 #pragma once
 #include "pi0_internal.h"
 #include "exec_ctx.h"
@@ -36,11 +36,9 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
   const int w = t >> 6;
   const int lq = lane & 31;
   const int lh = lane >> 5;
-  if (!Cx::kPersistent) {
-    if (cx.by >= p.heads) {   // warm-up block; rank = linear block index (mod 8)
-      if (cx.bz == 0) prefetch_role(p.pf, cx.bx + (int)gridDim.x * (cx.by - p.heads));
-      return;
-    }
+  if (cx.by >= p.heads) {   // warm-up block; rank = linear block index (mod 8)
+    if (cx.bz == 0) prefetch_role(p.pf, cx.bx + (int)gridDim.x * (cx.by - p.heads));
+    return;
   }
   // v_split > 1: the head dimension of the values (and of the output) is shared out over v_split blocks per
   // (query tile, head); each repeats phase 1 on all keys and runs phase 2 on its NVB / v_split slices only
@@ -72,8 +70,6 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
   const bf16* vslice0 = vbase0 + slice * 1024 + lane * 8;   // this wave's slice of the value fragments of segment 0
 
   // ---- issue every load of the first round (unconditional, clamped addresses) -----------------
-  // Keys and values of segment 0 are constants of a persistent kernel (the prefix cache): requested before the
-  // wait for this operation's inputs (Q and the second segment, which the QKV projection before produced).
   const bf16* qsrc = p.q + (size_t)head * p.q_head_stride + (size_t)tile * S16 * 512;
   bf16x8 qreg[QP];
   bf16x8 k1reg[KP1];
@@ -101,10 +97,6 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
       }
     }
   };
-  if (Cx::kPersistent) {
-    load_seg0();
-    cx.wait_inputs();
-  }
 #pragma unroll
   for (int i = 0; i < QP; i++) qreg[i] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(qsrc + (size_t)min(t + i * 512, NPQ - 1) * 8));
   if (n1 > 0) {
@@ -120,7 +112,7 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
       }
     }
   }
-  if (!Cx::kPersistent) load_seg0();
+  load_seg0();
   if (PVG && n1 > 0) {   // this wave's chunks that fall into segment 1 (after load_seg0, whose placeholders they replace)
 #pragma unroll
     for (int j = 0; j < (PVG ? CPW : 0); j++) {
@@ -145,7 +137,6 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
     }
   }
   __syncthreads();
-  cx.mark(1);   // Q and the second segment's keys are in LDS
 
   // ---- phase 1: scores of this wave's chunks ------------------------------------------------
   float sv[MAXR][16];
@@ -229,7 +220,6 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
   m_loc = fmaxf(m_loc, __shfl_xor(m_loc, 32, 64));
   if (lh == 0) mw[w * 32 + lq] = m_loc;
   __syncthreads();
-  cx.mark(2);   // scores done
   float m_all = NEG_BIG;
 #pragma unroll
   for (int i = 0; i < ATT_WAVES; i++) m_all = fmaxf(m_all, mw[i * 32 + lq]);
@@ -258,7 +248,6 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
   l_loc += __shfl_xor(l_loc, 32, 64);
   if (lh == 0) lw[w * 32 + lq] = l_loc;
   __syncthreads();
-  cx.mark(3);   // probabilities in LDS
   if (!pv_wave) return;
 
   // ---- phase 2: this wave's 32-wide slice of the head dimension over all chunks --------------
@@ -327,7 +316,6 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
 #pragma unroll
     for (int e = 0; e < 16; e++) o[e] += o1[e];
   }
-  cx.mark(4);   // P V done
   float l_all = 0.f;
 #pragma unroll
   for (int i = 0; i < ATT_WAVES; i++) l_all += lw[i * 32 + lq];
@@ -379,3 +367,262 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
 
 template <int DQK>
 static constexpr int attn_smem_bytes(int ntot) { return 3 * (DQK / 16) * 1024 + 2 * ATT_WAVES * 32 * 4 + ntot * 2048; }
+
+// ------------------------------------------------------------------------------------------------
+// Attention of the action expert: 64 suffix rows over a share of the prefix cache (at most 8 chunks of 32 keys) and,
+// in the last share, the suffix's own two chunks.  An item is 16 query rows of one head (and 1 / v_split of the head
+// dimension of the output): mfma_f32_16x16x32 throughout.
+// What bounds it in the persistent kernel is what follows the wait for the QKV projection, so everything that comes from
+// the prefix cache is in place before: wave w holds the keys of chunk w in registers, the values of the item's
+// slice of the head dimension are in LDS.  After the wait a wave fetches the 16 query rows (8 KB) straight into
+// registers, waves 4 .. 7 one 16-key tile of the suffix each, and every wave its columns of the suffix's values; then
+// scores, two LDS exchanges (row maximum, probabilities), and wave w accumulates columns 16 w .. (and 128 + 16 w .. with
+// v_split 1) over all chunks: no sum over waves.  Before, an item was 32 rows, waves 0 and 1 scored the suffix after
+// their own chunk, Q and the suffix keys went through LDS and partial outputs met in LDS: 5.0 us after the wait.
+// Probabilities: the accumulator of S^T (lane = query lane % 16, keys 4 (lane / 16) + r of a 16-key tile) gives each lane
+// keys {16 t + 4 g + r} of a chunk, which is the B operand of the second product in the key order t, r; the values are
+// read in the same order.
+// ------------------------------------------------------------------------------------------------
+template <class Cx>
+__device__ __forceinline__ void attention_suffix_body(const AttnParams p, const Cx cx, unsigned char* smem_raw) {
+  constexpr int S16 = 16;                      // head dimension 256
+  const int t = cx.tid();
+  const int lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int qi = lane & 15;
+  const int g = lane >> 4;
+  if (!Cx::kPersistent) {
+    if (cx.by >= p.heads) {   // warm-up block; rank = linear block index (mod 8)
+      if (cx.bz == 0) prefetch_role(p.pf, cx.bx + (int)gridDim.x * (cx.by - p.heads));
+      return;
+    }
+  }
+  const int vs = p.v_split > 1 ? p.v_split : 1;
+  const int qt = cx.bx / vs;                   // 16-row query tile
+  const int vpart = cx.bx - qt * vs;
+  const int head = cx.by;
+  const int row = qt * 16 + qi;
+  int cbeg0 = 0, n0 = p.chunks0, n1 = p.chunks1;
+  if (p.key_splits > 1) {   // this block's share of the prefix; the last share also takes the suffix
+    cbeg0 = cx.bz * p.chunks_per_split;
+    n0 = min(p.chunks_per_split, p.chunks0 - cbeg0);
+    if (cx.bz != p.key_splits - 1) n1 = 0;
+  }
+  const int nvb = 8 / vs;                      // 32-wide value slices of this item
+  bf16* vlds = reinterpret_cast<bf16*>(smem_raw);                             // [n0][nvb][2][64][8]
+  bf16* pf = vlds + (size_t)n0 * nvb * 1024;                                  // [n0 + 2][64][8]
+  float* mw = reinterpret_cast<float*>(pf + (size_t)(n0 + 2) * 512);          // [8][16]
+  float* lw = mw + ATT_WAVES * 16;                                            // [8][16]
+  // a 16-row operand of 32 k is half of two 32 x 16 fragments: lane (g, i) takes k = 8 g .. + 7 of row i
+  const unsigned piece = (unsigned)((g >> 1) * 1024 + ((g & 1) * 32 + qi) * 16);   // bytes; + 2 KiB per 32 k, + 256 for the odd 16-row tile
+  auto frag = [&](const bf16* base, int j) { return reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(base + (size_t)j * 1024) + piece); };
+
+  // ---- constants of the persistent kernel: keys to registers, values to LDS --------------------------
+  bf16x8 kf[2][8];
+  auto load_prefix = [&]() {
+    const bf16* kp = p.k0 + (size_t)(cbeg0 + min(w, n0 - 1)) * S16 * 512;
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+#pragma unroll
+      for (int h = 0; h < 2; h++) kf[h][j] = *frag(kp + h * 128, j);
+    // 16-byte pieces: 128 nvb of each chunk's 1024; 8 in flight per lane (4 KB, at most two batches)
+    const bf16* vsrc = p.v0 + (size_t)cbeg0 * 8 * 1024 + (size_t)vpart * nvb * 1024;
+    const int sh = vs == 1 ? 10 : vs == 2 ? 9 : vs == 4 ? 8 : 7, total = n0 << sh;
+    for (int i0 = t; i0 < total; i0 += 8 * 512) {
+      bf16x8 v[8];
+#pragma unroll
+      for (int j = 0; j < 8; j++) {
+        const int i = min(i0 + j * 512, total - 1);            // clamped, unconditional
+        v[j] = *reinterpret_cast<const bf16x8*>(vsrc + (size_t)(i >> sh) * 8 * 1024 + (size_t)(i & ((1 << sh) - 1)) * 8);
+      }
+#pragma unroll
+      for (int j = 0; j < 8; j++) {
+        if (i0 + j * 512 < total) *reinterpret_cast<bf16x8*>(vlds + (size_t)(i0 + j * 512) * 8) = v[j];
+      }
+    }
+  };
+  if (Cx::kPersistent) {
+    load_prefix();
+    cx.wait_inputs();
+  }
+  // ---- inputs: query rows, suffix keys (waves 4 .. 7: 16-key tile w - 4), suffix values ---------------
+  bf16x8 qf[8], k1f[8];
+  bf16x4 v1f[2][2][2];                         // [column tile][chunk][16-key half]
+  const bf16* qsrc = p.q + (size_t)head * p.q_head_stride + (size_t)(qt >> 1) * S16 * 512 + (qt & 1) * 128;
+#pragma unroll
+  for (int j = 0; j < 8; j++) qf[j] = cx.ld_bulk(frag(qsrc, j));
+  const bool seg1_wave = n1 > 0 && w >= 4;
+  const int tile1 = w - 4;
+  if (seg1_wave) {
+    const bf16* kp = p.k1 + (size_t)(tile1 >> 1) * S16 * 512 + (tile1 & 1) * 128;
+#pragma unroll
+    for (int j = 0; j < 8; j++) k1f[j] = cx.ld_bulk(frag(kp, j));
+  }
+  const int ntiles = 2 * nvb;                  // 16-column tiles of this item; this wave's are w and w + 8
+  if (n1 > 0) {
+#pragma unroll
+    for (int a = 0; a < 2; a++) {
+      const int dt = min(w + ATT_WAVES * a, ntiles - 1);
+      const bf16* vp = p.v1 + (size_t)(vpart * nvb + (dt >> 1)) * 1024 + ((g & 1) * 32 + (dt & 1) * 16 + qi) * 8 + (g >> 1) * 4;
+#pragma unroll
+      for (int c = 0; c < 2; c++)
+#pragma unroll
+        for (int h = 0; h < 2; h++)
+          if (a == 0 || vs == 1) v1f[a][c][h] = cx.ld_bulk(reinterpret_cast<const bf16x4*>(vp + (size_t)c * 8 * 1024 + h * 512));
+    }
+  }
+  if (!Cx::kPersistent) load_prefix();
+  cx.mark(1);   // inputs requested
+
+  // ---- scores ---------------------------------------------------------------------------------------
+  f32x4 sv[2], sv1, sodd[2], sodd1;   // even and odd k steps apart: half the dependent chain
+#pragma unroll
+  for (int h = 0; h < 2; h++) sv[h] = sodd[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  sv1 = sodd1 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      sv[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[h][j], qf[j], sv[h], 0, 0, 0);
+      sodd[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[h][j + 1], qf[j + 1], sodd[h], 0, 0, 0);
+    }
+  }
+  if (seg1_wave) {
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+      sv1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1f[j], qf[j], sv1, 0, 0, 0);
+      sodd1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1f[j + 1], qf[j + 1], sodd1, 0, 0, 0);
+    }
+    sv1 += sodd1;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; h++) sv[h] += sodd[h];
+  float m_loc = NEG_BIG;
+#pragma unroll
+  for (int h = 0; h < 2; h++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int key = (cbeg0 + w) * 32 + h * 16 + 4 * g + e;
+      sv[h][e] = w < n0 && key < p.valid0 ? sv[h][e] * p.scale : NEG_BIG;
+      m_loc = fmaxf(m_loc, sv[h][e]);
+    }
+  if (seg1_wave) {
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int key = tile1 * 16 + 4 * g + e;
+      const bool valid = !p.suffix_mask || row != 0 || key == 0;
+      sv1[e] = valid ? sv1[e] * p.scale : NEG_BIG;
+      m_loc = fmaxf(m_loc, sv1[e]);
+    }
+  }
+  m_loc = fmaxf(m_loc, __shfl_xor(m_loc, 16, 64));
+  m_loc = fmaxf(m_loc, __shfl_xor(m_loc, 32, 64));
+  if (g == 0) mw[w * 16 + qi] = m_loc;
+  __syncthreads();
+  cx.mark(2);   // scores done
+  float m_all = NEG_BIG;
+#pragma unroll
+  for (int i = 0; i < ATT_WAVES; i++) m_all = fmaxf(m_all, mw[i * 16 + qi]);
+
+  // ---- probabilities -> B operand of the second product, in LDS ---------------------------------------
+  float l_loc = 0.f;
+  auto prob = [&](float v) {
+    const float e = v > 0.5f * NEG_BIG ? __expf(v - m_all) : 0.f;   // masked keys: exactly 0
+    l_loc += e;
+    return e;
+  };
+  if (w < n0) {
+    bf16x8 pb;
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) pb[4 * h + e] = (bf16)prob(sv[h][e]);
+    *reinterpret_cast<bf16x8*>(pf + ((size_t)w * 64 + lane) * 8) = pb;
+  }
+  if (seg1_wave) {
+    bf16x4 pb;
+#pragma unroll
+    for (int e = 0; e < 4; e++) pb[e] = (bf16)prob(sv1[e]);
+    *reinterpret_cast<bf16x4*>(pf + ((size_t)(n0 + (tile1 >> 1)) * 64 + lane) * 8 + (tile1 & 1) * 4) = pb;
+  }
+  l_loc += __shfl_xor(l_loc, 16, 64);
+  l_loc += __shfl_xor(l_loc, 32, 64);
+  if (g == 0) lw[w * 16 + qi] = l_loc;
+  __syncthreads();
+  cx.mark(3);   // probabilities in LDS
+  if (w >= ntiles) return;
+
+  // ---- output columns: O^T tile = V^T P^T over all chunks, two chains per tile ------------------------
+  f32x4 o[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; a++)
+#pragma unroll
+    for (int b = 0; b < 2; b++) o[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto lds_v = [&](int c, int dt) {
+    const bf16* vp = vlds + ((size_t)c * nvb + (dt >> 1)) * 1024 + ((g & 1) * 32 + (dt & 1) * 16 + qi) * 8 + (g >> 1) * 4;
+    const bf16x4 lo = *reinterpret_cast<const bf16x4*>(vp), hi = *reinterpret_cast<const bf16x4*>(vp + 512);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  for (int c0 = 0; c0 < n0; c0 += 4) {
+    bf16x8 b[4], va[2][4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const int c = min(c0 + j, n0 - 1);
+      b[j] = *reinterpret_cast<const bf16x8*>(pf + ((size_t)c * 64 + lane) * 8);
+      va[0][j] = lds_v(c, w);
+      if (vs == 1) va[1][j] = lds_v(c, w + ATT_WAVES);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      if (c0 + j < n0) {   // uniform
+        o[0][j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[0][j], b[j], o[0][j & 1], 0, 0, 0);
+        if (vs == 1) o[1][j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[1][j], b[j], o[1][j & 1], 0, 0, 0);
+      }
+    }
+  }
+  if (n1 > 0) {
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(pf + ((size_t)(n0 + c) * 64 + lane) * 8);
+#pragma unroll
+      for (int a = 0; a < 2; a++) {
+        if (a == 0 || vs == 1)
+          o[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_shufflevector(v1f[a][c][0], v1f[a][c][1], 0, 1, 2, 3, 4, 5, 6, 7), b, o[a][c], 0, 0, 0);
+      }
+    }
+  }
+  cx.mark(4);   // P V done
+  float l_all = 0.f;
+#pragma unroll
+  for (int i = 0; i < ATT_WAVES; i++) l_all += lw[i * 16 + qi];
+  const float inv = 1.0f / l_all;
+  if (row >= p.Tq) return;
+  if (p.ml_out != nullptr && w == 0 && g == 0 && vpart == 0) {   // (row maximum, sum) of this share, for the consumer's merge
+    float* dst = p.ml_out + ((((size_t)cx.bz * p.heads + head) * ((p.Tq + 31) >> 5) * 32) + row) * 2;
+    cx.st(reinterpret_cast<float2*>(dst), make_float2(m_all, l_all));
+  }
+  bf16* outp = p.out + (size_t)cx.bz * p.out_split_stride;
+#pragma unroll
+  for (int a = 0; a < 2; a++) {
+    if (a == 0 || vs == 1) {
+      const int col = head * 256 + vpart * nvb * 32 + (w + ATT_WAVES * a) * 16 + 4 * g;
+      bf16x4 ob;
+#pragma unroll
+      for (int e = 0; e < 4; e++) ob[e] = (bf16)((o[a][0][e] + o[a][1][e]) * inv);
+      cx.st(reinterpret_cast<bf16x4*>(outp + ((size_t)(row >> 5) * (p.out_ld >> 4) + (col >> 4)) * 512 +
+                                      (((col & 15) >> 3) * 32 + (row & 31)) * 8 + (col & 7)), ob);
+    }
+  }
+}
+
+// values of n0 chunks, probabilities, row maxima and sums
+static constexpr int attn_suffix_smem_bytes(int n0, int v_split) {
+  return n0 * (8 / (v_split > 1 ? v_split : 1)) * 2048 + (n0 + 2) * 1024 + 2 * ATT_WAVES * 16 * 4;
+}
+static constexpr int ATTN_SUFFIX_SMEM_MAX = attn_suffix_smem_bytes(8, 1);
+// shapes attention_suffix_body covers: n0 = prefix chunks per share
+static inline bool attn_suffix_ok(const AttnParams& p, int n0) {
+  const int vs = p.v_split > 1 ? p.v_split : 1;
+  return p.head_dim == 256 && p.chunks1 == 2 && p.Tq == 64 && p.view_tokens == 0 && p.kv_head_stride0 == 0 && p.v_head_stride0 == 0 &&
+         n0 >= 1 && n0 <= 8 && (vs == 1 || vs == 2 || vs == 4 || vs == 8);
+}

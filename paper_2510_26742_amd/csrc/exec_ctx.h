@@ -22,6 +22,14 @@
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 
+// A pointer read from memory could point anywhere, so accesses through it are FLAT: they count towards both wait counters
+// and are waited for with everything else in flight.  This says that it points to global memory (kernel arguments need
+// no such help).
+template <class T>
+__device__ __forceinline__ T* as_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)p;
+}
+
 struct LaunchCtx {
   static constexpr bool kPersistent = false;
   int bx, by, bz;
@@ -64,7 +72,9 @@ enum {
   GB_WORDS = GB_FLAGS + 8 * GB_MAX_BLOCKS
 };
 
-struct GridBarrier {
+// TRACE: a timeline is recorded (a kernel of its own: the code for it in every operation costs instruction cache)
+template <bool TRACE>
+struct GridBarrierT {
   unsigned* w;          // GB_WORDS words, zeroed before the launch
   unsigned xcc;         // die of this block
   unsigned members;     // blocks on this die
@@ -82,7 +92,7 @@ struct GridBarrier {
   // all threads of the block; one counter barrier, after which every block knows who shares its die
   // may_lead: the block is one of those that should lead their die (if a die has none, another one does)
   __device__ __forceinline__ void init(unsigned* words, unsigned limit, bool may_lead) {
-    w = words;
+    w = as_global(words);
     spin_limit = limit;
     epoch = 0;
     waited = 0;
@@ -159,7 +169,7 @@ struct GridBarrier {
     }
     __syncthreads();
     waited = epoch;
-    if (trace != nullptr && threadIdx.x == 0) *trace = (long long)wall_clock64();
+    if (TRACE && trace != nullptr && threadIdx.x == 0) *trace = (long long)wall_clock64();
   }
 };
 
@@ -173,13 +183,13 @@ struct GridBarrier {
 // That is only coherent if no cache of the reading die can hold an older copy of those addresses, which the caller
 // guarantees by giving every operation instance of the loop its own never-read buffers whose cache lines are each
 // written by one block only ("fresh" data path of the barrier experiment).
-template <bool BULK_CACHED>
+template <bool BULK_CACHED, bool TRACE>
 struct PersistCtxT {
   static constexpr bool kPersistent = true;
   int bx, by, bz;                  // work item of the current operation
   __amdgpu_buffer_rsrc_t arena;    // buffer resource over the activation arena
   const char* arena_base;
-  GridBarrier* bar;
+  GridBarrierT<TRACE>* bar;
   int thread;                      // threadIdx.x, made opaque per operation: per-lane address arithmetic of one operation
                                    // is then not hoisted out of the layer loop, where it would hold registers throughout
 
@@ -210,13 +220,12 @@ struct PersistCtxT {
   __device__ __forceinline__ void wait_inputs() const { bar->wait(); }
   // timeline sample k (1 .. 4) of the current operation, by thread 0, when a timeline is being recorded
   __device__ __forceinline__ void mark(int k) const {
-    if (bar->trace != nullptr && thread == 0) bar->trace[2 + k] = (long long)wall_clock64();
+    if (TRACE && bar->trace != nullptr && thread == 0) bar->trace[2 + k] = (long long)wall_clock64();
   }
   template <bool B>
-  __device__ __forceinline__ PersistCtxT<B> as() const {
-    PersistCtxT<B> c;
+  __device__ __forceinline__ PersistCtxT<B, TRACE> as() const {
+    PersistCtxT<B, TRACE> c;
     c.bx = bx; c.by = by; c.bz = bz; c.arena = arena; c.arena_base = arena_base; c.bar = bar; c.thread = thread;
     return c;
   }
 };
-using PersistCtx = PersistCtxT<false>;

@@ -26,7 +26,7 @@ struct ExpertLoopParams {
   int parts_first, parts_rest;    // row-statistic partials the QKV projection of layer 0 / of the other layers reads
   int m16;                        // 16-token tiles of the O / down projections
   int dn_ns;                      // k steps per wave of the down projection: 16 (k = 4096) or 8 (k = 2048)
-  int att_gx, att_items;          // attention work items: att_gx = 2 query tiles x value parts; x heads x key shares
+  int att_gx, att_items;          // attention work items: att_gx = 4 query tiles x value parts; x heads x key shares
   // Ring of per-layer-step buffers (slot ls = step * layers + layer at ring + ls * ring_stride).  Every activation
   // that one operation writes and the next reads with cached loads has its own place per layer-step, which nothing
   // has read before in this launch (exec_ctx.h, BULK_CACHED); byte offsets inside a slot:

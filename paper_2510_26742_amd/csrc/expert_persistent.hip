@@ -84,20 +84,50 @@ __device__ __forceinline__ void for_items(int n_items, F&& f, int block = (int)b
 }
 
 // The parameter block lives in device memory and every operation reads its own part afresh: taken by value, the
-// operations' pointers and sizes stay live across the whole loop and the kernel spills hundreds of registers.
-__device__ __forceinline__ const ExpertLoopParams& fresh(const ExpertLoopParams* p) {
+// operations' pointers and sizes stay live across the whole loop and the kernel spills hundreds of registers.  It is read
+// through the constant address space (scalar loads; as generic memory it was read with FLAT vector loads that queued
+// behind the prefetches in flight), and the pointers in it are declared global.
+typedef const __attribute__((address_space(4))) ExpertLoopParams* ParamsPtr;
+__device__ __forceinline__ const ExpertLoopParams& fresh(ParamsPtr p) {
   asm volatile("" : "+s"(p));   // nothing read through the pointer before this point is reused after it
-  return *p;
+  return *(const ExpertLoopParams*)p;
+}
+__device__ __forceinline__ GemmParams global(const GemmParams& src) {
+  GemmParams p = src;
+  p.X = as_global(p.X);
+  p.W.w = as_global(p.W.w);
+  p.bias = as_global(p.bias);
+  p.colsum = as_global(p.colsum);
+  p.rowstat = as_global(p.rowstat);
+  p.stat_out = as_global(p.stat_out);
+  p.gain = as_global(p.gain);
+  p.out_f32 = as_global(p.out_f32);
+  p.out_bf16 = as_global(p.out_bf16);
+  p.resid = as_global(p.resid);
+  p.kfrag = as_global(p.kfrag);
+  p.vfrag = as_global(p.vfrag);
+  p.rope = as_global(p.rope);
+  p.xsplit_ml = as_global(p.xsplit_ml);
+  return p;
+}
+__device__ __forceinline__ AttnParams global(const AttnParams& src) {
+  AttnParams p = src;
+  p.k0 = as_global(p.k0);
+  p.v0 = as_global(p.v0);
+  return p;
 }
 
 __global__ void expert_loop_params_kernel(ExpertLoopParams P, ExpertLoopParams* dst) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *dst = P;
 }
 
-__global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoopParams* __restrict__ Pg) {
+template <bool TRACE>
+__global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoopParams* __restrict__ params) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  GridBarrier bar;
-  const ExpertLoopParams& P = *Pg;
+  using PersistCtx = PersistCtxT<false, TRACE>;
+  GridBarrierT<TRACE> bar;
+  const ParamsPtr Pg = (ParamsPtr)params;
+  const ExpertLoopParams& P = fresh(Pg);
   // The attention's items start at the first block without a QKV item: such a block requests its share of the prefix
   // cache when the QKV projection begins, and has it when the projection ends.
   const int att_off = P.qkv.n_tiles * 2 < (int)gridDim.x ? P.qkv.n_tiles * 2 : 0;
@@ -110,21 +140,25 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
   cx.bar = &bar;
   cx.bx = cx.by = cx.bz = 0;
   cx.thread = (int)threadIdx.x;
-  long long* const trace = P.trace;
+  long long* const trace = as_global(P.trace);
   const int trace_ops = P.trace_ops;
   int opi = 0;
   // timeline, 8 samples per (operation, block): 0 at the start of an operation, 1 by the barrier when the wait ends,
   // 2 after the body, 3 after arrive, 4 .. 7 by the body itself (cx.mark)
   auto op_begin = [&]() {
-    if (trace != nullptr && opi < trace_ops) {
+    if (TRACE && trace != nullptr && opi < trace_ops) {
       long long* slot = trace + ((size_t)opi * gridDim.x + blockIdx.x) * 8;
       bar.trace = slot + 1;
       if (threadIdx.x == 0) { slot[0] = (long long)wall_clock64(); slot[1] = slot[4] = slot[5] = slot[6] = slot[7] = 0; }
-    } else {
+    } else if (TRACE) {
       bar.trace = nullptr;
     }
   };
   auto op_end = [&]() {
+    if (!TRACE) {
+      bar.arrive();
+      return;
+    }
     long long* slot = trace != nullptr && opi < trace_ops ? trace + ((size_t)opi * gridDim.x + blockIdx.x) * 8 : nullptr;
     if (slot != nullptr && threadIdx.x == 0) slot[2] = (long long)wall_clock64();
     bar.trace = nullptr;
@@ -145,7 +179,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
   // ---- C0: state token; x <- noise ---------------------------------------------------------------
   for_items((P.stok.X + 255) / 256, [&](int it) { state_token_body(P.stok, item(it, 0, 0)); });
   if ((int)blockIdx.x == (int)gridDim.x - 1) {
-    for (int i = threadIdx.x; i < P.x_elems; i += PK_THREADS) cx.st(P.emb.x_rw + i, P.noise[i]);
+    for (int i = threadIdx.x; i < P.x_elems; i += PK_THREADS) cx.st(P.emb.x_rw + i, as_global(P.noise)[i]);
   }
   op_end();
 
@@ -166,7 +200,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
     op_begin();
     // ---- C2: second linear of the action/time MLP -> suffix rows 1 .. chunk --------------------------
     {
-      const GemmParams t = fresh(Pg).tout;
+      const GemmParams t = global(fresh(Pg).tout);
       for_items(t.n_tiles * 2, [&](int it) { gemm_skinny_body<PRO_NONE, EPI_RESID, 1>(t, item(it % t.n_tiles, 0, it / t.n_tiles), smem_raw); });
     }
     op_end();
@@ -174,9 +208,9 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
       op_begin();
       {  // ---- C3: RMS -> QKV, RoPE at positions P .. P + 63 -------------------------------------
         const ExpertLoopParams& F = fresh(Pg);
-        GemmParams q = F.qkv;
+        GemmParams q = global(F.qkv);
         q.W.w += (size_t)l * F.w_stride;
-        char* slot = F.ring + (size_t)(k * layers + l) * F.ring_stride;
+        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
         q.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_q);
         q.kfrag = reinterpret_cast<bf16*>(slot + F.r_k);
         q.vfrag = reinterpret_cast<bf16*>(slot + F.r_v);
@@ -196,18 +230,18 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
           const int idle = (int)gridDim.x - (q.n_tiles * 2 > att_off + F.att_items ? q.n_tiles * 2 : att_off + F.att_items);
           const int part = (int)gridDim.x - 1 - (int)blockIdx.x;
           unsigned fold = 0;
-          if (F.read_ahead & 16) fold = read_ahead_weights<0>(F.o.W.w + (size_t)l * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, idle, false, tid, fold);
-          if (fold == 0x9e3779b9u) F.sync[GB_SINK] = fold;
+          if (F.read_ahead & 16) fold = read_ahead_weights<0>(as_global(F.o.W.w) + (size_t)l * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, idle, false, tid, fold);
+          if (fold == 0x9e3779b9u) as_global(F.sync)[GB_SINK] = fold;
         }
         op_end();
       }
       op_begin();
       {  // ---- C4 + C5: scores, block mask, softmax, PV over [cache ; own keys] ---------------------
         const ExpertLoopParams& F = fresh(Pg);
-        AttnParams a = F.att;
+        AttnParams a = global(F.att);
         a.k0 += (size_t)l * F.kcache_stride;
         a.v0 += (size_t)l * F.vcache_stride;
-        char* slot = F.ring + (size_t)(k * layers + l) * F.ring_stride;
+        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
         a.q = reinterpret_cast<const bf16*>(slot + F.r_q);
         a.k1 = reinterpret_cast<const bf16*>(slot + F.r_k);
         a.v1 = reinterpret_cast<const bf16*>(slot + F.r_v);
@@ -215,7 +249,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         if (a.ml_out != nullptr) a.ml_out = reinterpret_cast<float*>(slot + F.r_ml);
         const int att_gx = F.att_gx, att_gxy = F.att_gx * a.heads;
         for_items(F.att_items, [&](int it) {
-          attention_body<256, 8, 1, 6, 5>(a, item(it % att_gx, (it % att_gxy) / att_gx, it / att_gxy).template as<true>(), smem_raw);
+          attention_suffix_body(a, item(it % att_gx, (it % att_gxy) / att_gx, it / att_gxy).template as<true>(), smem_raw);
         }, att_block);
         if (att_block >= F.att_items && (F.read_ahead & 15)) {   // no item: read ahead (constants only, no wait needed)
           const int part = att_block - F.att_items, nparts = (int)gridDim.x - F.att_items;
@@ -223,21 +257,21 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
           const bool by_die = part_die == 0 && nparts % 8 == 0 && (F.read_ahead & 32) != 0;
           const int tid = item(0, 0, 0).thread;
           unsigned fold = 0;
-          if (F.read_ahead & 1) fold = read_ahead_weights<2>(F.gu.W.w + (size_t)l * F.w_stride, F.gu.n_tiles, F.gu.W.k_pad >> 4, part, nparts, by_die, tid, fold);
-          if (F.read_ahead & 2) fold = read_ahead_weights<0>(F.dn.W.w + (size_t)l * F.w_stride, F.dn.n_tiles, F.dn.W.k_pad >> 4, part, nparts, by_die, tid, fold);
-          if (F.read_ahead & 4) fold = read_ahead_weights<1>(F.qkv.W.w + (size_t)ln * F.w_stride, F.qkv.n_tiles, F.qkv.W.k_pad >> 4, part, nparts, by_die, tid, fold);
-          if (F.read_ahead & 8) fold = read_ahead_weights<0>(F.o.W.w + (size_t)ln * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, nparts, by_die, tid, fold);
-          if (fold == 0x9e3779b9u) F.sync[GB_SINK] = fold;
+          if (F.read_ahead & 1) fold = read_ahead_weights<2>(as_global(F.gu.W.w) + (size_t)l * F.w_stride, F.gu.n_tiles, F.gu.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+          if (F.read_ahead & 2) fold = read_ahead_weights<0>(as_global(F.dn.W.w) + (size_t)l * F.w_stride, F.dn.n_tiles, F.dn.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+          if (F.read_ahead & 4) fold = read_ahead_weights<1>(as_global(F.qkv.W.w) + (size_t)ln * F.w_stride, F.qkv.n_tiles, F.qkv.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+          if (F.read_ahead & 8) fold = read_ahead_weights<0>(as_global(F.o.W.w) + (size_t)ln * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+          if (fold == 0x9e3779b9u) as_global(F.sync)[GB_SINK] = fold;
         }
         op_end();
       }
       op_begin();
       {  // ---- C6: O projection + residual ------------------------------------------------------
         const ExpertLoopParams& F = fresh(Pg);
-        GemmParams o = F.o;
+        GemmParams o = global(F.o);
         o.W.w += (size_t)l * F.w_stride;
-        o.gain = F.g_mlp0 + (size_t)l * F.gain_stride;
-        char* slot = F.ring + (size_t)(k * layers + l) * F.ring_stride;
+        o.gain = as_global(F.g_mlp0) + (size_t)l * F.gain_stride;
+        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
         o.X = reinterpret_cast<const bf16*>(slot + F.r_attn);
         if (o.xsplits > 1) o.xsplit_ml = reinterpret_cast<const float*>(slot + F.r_ml);
         o.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_yb_o);
@@ -249,9 +283,9 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
       op_begin();
       {  // ---- C7: RMS -> gate||up, fused gate -----------------------------------------------------
         const ExpertLoopParams& F = fresh(Pg);
-        GemmParams g = F.gu;
+        GemmParams g = global(F.gu);
         g.W.w += (size_t)l * F.w_stride;
-        char* slot = F.ring + (size_t)(k * layers + l) * F.ring_stride;
+        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
         g.X = reinterpret_cast<const bf16*>(slot + F.r_yb_o);
         g.rowstat = reinterpret_cast<const float*>(slot + F.r_st_o);
         g.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_mid);
@@ -264,10 +298,10 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
       op_begin();
       {  // ---- C8: down + residual -----------------------------------------------------------------
         const ExpertLoopParams& F = fresh(Pg);
-        GemmParams d = F.dn;
+        GemmParams d = global(F.dn);
         d.W.w += (size_t)l * F.w_stride;
-        d.gain = l + 1 < F.layers ? F.g_attn0 + (size_t)(l + 1) * F.gain_stride : F.g_final;
-        char* slot = F.ring + (size_t)(k * layers + l) * F.ring_stride;
+        d.gain = as_global(l + 1 < F.layers ? F.g_attn0 + (size_t)(l + 1) * F.gain_stride : F.g_final);
+        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
         d.X = reinterpret_cast<const bf16*>(slot + F.r_mid);
         d.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_yb_d);
         d.stat_out = reinterpret_cast<float*>(slot + F.r_st_d);
@@ -281,8 +315,8 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
     // ---- C9: final RMS -> out-projection (+bias), Euler update x <- x + dt * v ----------------------
     {
       const ExpertLoopParams& F = fresh(Pg);
-      GemmParams u = F.outp;
-      char* slot = F.ring + (size_t)(k * layers + layers - 1) * F.ring_stride;
+      GemmParams u = global(F.outp);
+      char* slot = as_global(F.ring) + (size_t)(k * layers + layers - 1) * F.ring_stride;
       u.X = reinterpret_cast<const bf16*>(slot + F.r_yb_d);
       u.rowstat = reinterpret_cast<const float*>(slot + F.r_st_d);
       // one item per (feature tile, token block): half the activation bytes per block
@@ -296,18 +330,26 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
 
 int expert_loop_smem_bytes() {
   const int sk = (SK_WAVES * 2 * 16 * 64 + 128 + SK_WAVES * 128) * 4;
-  const int at = attn_smem_bytes<256>(8 + 2);
+  const int at = ATTN_SUFFIX_SMEM_MAX;
   return sk > at ? sk : at;
 }
 
 hipError_t expert_loop_init_attributes() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&expert_loop_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&expert_loop_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           expert_loop_smem_bytes());
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&expert_loop_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              expert_loop_smem_bytes());
 }
 
 hipError_t expert_loop_max_blocks_per_cu(int* out) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(out, reinterpret_cast<const void*>(&expert_loop_kernel), PK_THREADS,
-                                                      expert_loop_smem_bytes());
+  int traced = 0;
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&traced, reinterpret_cast<const void*>(&expert_loop_kernel<true>), PK_THREADS,
+                                                              expert_loop_smem_bytes());
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(out, reinterpret_cast<const void*>(&expert_loop_kernel<false>), PK_THREADS,
+                                                                        expert_loop_smem_bytes());
+  if (e == hipSuccess && traced < *out) *out = traced;
+  return e;
 }
 
 // Host-side checks of everything the kernel's indexing assumes; the caller has zeroed the barrier words.
@@ -357,14 +399,12 @@ hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLo
     return hipErrorInvalidValue;
   const int shares = a.key_splits > 1 ? a.key_splits : 1;
   const int n0 = shares > 1 ? a.chunks_per_split : a.chunks0;
-  if (n0 < 1 || n0 > 8 || shares > 4 || (shares > 1 && (a.ml_out == nullptr || (shares - 1) * a.chunks_per_split >= a.chunks0 ||
-                                                        shares * a.chunks_per_split < a.chunks0)))
+  if (!attn_suffix_ok(a, n0)) return hipErrorInvalidValue;
+  if (shares > 4 || (shares > 1 && (a.ml_out == nullptr || (shares - 1) * a.chunks_per_split >= a.chunks0 ||
+                                    shares * a.chunks_per_split < a.chunks0)))
     return hipErrorInvalidValue;
   const int vs = a.v_split > 1 ? a.v_split : 1;
-  // value slices in groups of waves: at most 5 chunks of [segment 0 ; segment 1] per wave
-  if (vs != 2 && vs != 4 && vs != 8) return hipErrorInvalidValue;
-  if ((n0 + 2 + vs - 1) / vs > 5) return hipErrorInvalidValue;
-  if (P.att_gx != 2 * vs || P.att_items != 2 * vs * a.heads * shares || a.pf.blocks != 0) return hipErrorInvalidValue;
+  if (P.att_gx != 4 * vs || P.att_items != 4 * vs * a.heads * shares || a.pf.blocks != 0) return hipErrorInvalidValue;
   if (!in_arena(a.q, 2) || !in_arena(a.k1, 2) || !in_arena(a.v1, 2) || !in_arena(a.out, 2)) return hipErrorInvalidValue;
   if (P.emb.a.X % 32 != 0 || P.emb.a.gain == nullptr || P.emb.a.stat_parts == nullptr || P.emb.a.x != P.emb.x_rw) return hipErrorInvalidValue;
   if (!in_arena(P.emb.x_rw, (size_t)P.x_elems * 4) || !in_arena(P.stok.out, (size_t)P.stok.X * 4)) return hipErrorInvalidValue;
@@ -374,6 +414,7 @@ hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLo
   hipLaunchKernelGGL(expert_loop_params_kernel, dim3(1), dim3(64), 0, s, P, d_params);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(expert_loop_kernel, dim3(blocks), dim3(PK_THREADS), expert_loop_smem_bytes(), s, d_params);
+  if (P.trace != nullptr) hipLaunchKernelGGL(expert_loop_kernel<true>, dim3(blocks), dim3(PK_THREADS), expert_loop_smem_bytes(), s, d_params);
+  else hipLaunchKernelGGL(expert_loop_kernel<false>, dim3(blocks), dim3(PK_THREADS), expert_loop_smem_bytes(), s, d_params);
   return hipGetLastError();
 }

@@ -52,12 +52,13 @@ struct EpiOps {
 // DEP selects what is fetched: 1 = only what blocks of the operation before produced (the residual rows), 0 = only
 // constants (bias, column sums, gain, RoPE table), 2 = both.  A persistent kernel asks for the constants before it
 // waits for its inputs and for the rest after.
+// ib: added to the steps at run time (waves that share a tile's epilogue run one copy of the code)
 template <int PRO, int EPI, int I0 = 0, int I1 = 4, int DEP = 2, class Cx = LaunchCtx>
-__device__ __forceinline__ void epilogue_preload(const GemmParams& p, int nt, int m, int lh, EpiOps& o, const Cx& cx = Cx{}) {
+__device__ __forceinline__ void epilogue_preload(const GemmParams& p, int nt, int m, int lh, EpiOps& o, const Cx& cx = Cx{}, int ib = 0) {
   if (EPI == EPI_PARTIAL) return;
 #pragma unroll
   for (int i = I0; i < I1; i++) {
-    const int n4 = nt * 32 + 8 * i + 4 * lh;
+    const int n4 = nt * 32 + 8 * (i + ib) + 4 * lh;
     if (DEP != 1) {
       if (PRO == PRO_LN) o.colsum[i - I0] = *reinterpret_cast<const f32x4*>(p.colsum + n4);
       if (p.bias != nullptr) o.bias[i - I0] = *reinterpret_cast<const f32x4*>(p.bias + n4);
@@ -97,7 +98,7 @@ __device__ __forceinline__ void epilogue_preload(const GemmParams& p, int nt, in
 // row, (s_sum, s_sq) the row's sum and sum of squares over the true k columns.
 template <int PRO, int EPI, int I0 = 0, int I1 = 4, class Cx = LaunchCtx>
 __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16& acc, int nt, int m, int lh,
-                                              float s_sum, float s_sq, int zsplit, const EpiOps& ops, const Cx& cx = Cx{}) {
+                                              float s_sum, float s_sq, int zsplit, const EpiOps& ops, const Cx& cx = Cx{}, int ib = 0) {
   static_assert(EPI != EPI_RESID || (I0 == 0 && I1 == 4), "row statistics are taken over the whole tile");
   static_assert(EPI != EPI_GEGLU || (I0 % 2 == 0 && I1 % 2 == 0), "gate / up steps are stored in pairs");
   const float inv_k = 1.0f / (float)p.k_true;
@@ -115,7 +116,7 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
     }
 #pragma unroll
     for (int i = I0; i < I1; i++) {
-      const int n4 = nt * 32 + 8 * i + 4 * lh;
+      const int n4 = nt * 32 + 8 * (i + ib) + 4 * lh;
       float v[4];
 #pragma unroll
       for (int j = 0; j < 4; j++) v[j] = acc[4 * i + j];
@@ -182,7 +183,7 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
           const unsigned got = (unsigned)__shfl_xor((int)give, 32, 64);
           const unsigned lo = lh ? got : geglu_keep;                 // half 0: own i-1, partner's i-1
           const unsigned hi = lh ? mine : got;                       // half 1: partner's i, own i
-          const int col = nt * 16 + 4 * (i - 1) + 4 * lh;            // (n4 >> 1) of step i-1 for half 0, +4 for half 1
+          const int col = nt * 16 + 4 * (i + ib - 1) + 4 * lh;            // (n4 >> 1) of step i-1 for half 0, +4 for half 1
           const uint2 o2 = {lo, hi};
           cx.st(reinterpret_cast<uint2*>(p.out_bf16 + xf_index(m, col, p.ldo >> 4)), o2);
         }
@@ -270,38 +271,26 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
 
 // MS = 1: the two 32-token blocks go to separate blocks (gridDim.z = 2), which halves the activation
 // bytes per CU; used where the launch would otherwise leave most CUs idle (the expert's QKV).
-// Steps I0 .. I1-1 of one token block's tile: the 8 waves' partial tiles [wave][token block][step][lane][4] are
+// Steps ib .. ib + NSTEP - 1 of one token block's tile: the 8 waves' partial tiles [wave][token block][step][lane][4] are
 // added in wave order, then the epilogue runs on those steps.
-template <int PRO, int EPI, int I0, int I1, class Cx>
+template <int PRO, int EPI, int NSTEP, class Cx>
 __device__ __forceinline__ void skinny_finish(const GemmParams& p, const float* red, int mb /* slot */, int lane, int nt, int ml, int lh,
-                                              float ssum, float ssq, const EpiOps& ops, const Cx& cx) {
+                                              float ssum, float ssq, const EpiOps& ops, const Cx& cx, int ib) {
   f32x16 sum;
 #pragma unroll
   for (int r = 0; r < 16; r++) sum[r] = 0.f;
+  f32x4 part[SK_WAVES][NSTEP];
 #pragma unroll
   for (int ww = 0; ww < SK_WAVES; ww++)
 #pragma unroll
-    for (int q = I0; q < I1; q++) {
-      const f32x4 v4 = *reinterpret_cast<const f32x4*>(red + ((((size_t)ww * 2 + mb) * 4 + q) * 64 + lane) * 4);
+    for (int q = 0; q < NSTEP; q++) part[ww][q] = *reinterpret_cast<const f32x4*>(red + ((((size_t)ww * 2 + mb) * 4 + ib + q) * 64 + lane) * 4);
 #pragma unroll
-      for (int j = 0; j < 4; j++) sum[4 * q + j] += v4[j];
-    }
-  if (ml < p.M) epilogue_tile<PRO, EPI, I0, I1>(p, sum, nt, ml, lh, ssum, ssq, cx.by, ops, cx);
-}
-
-// the epilogue operands of finishing wave piece fpc (a tile's four 8-feature steps are shared out over PIECES waves)
-template <int PRO, int EPI, int PIECES, int DEP, class Cx>
-__device__ __forceinline__ void skinny_preload(const GemmParams& p, int nt, int mrow, int lh, int fpc, EpiOps& ops, const Cx& cx) {
-  if constexpr (PIECES == 1) epilogue_preload<PRO, EPI, 0, 4, DEP>(p, nt, mrow, lh, ops, cx);
-  else if constexpr (PIECES == 2) {
-    if (fpc == 0) epilogue_preload<PRO, EPI, 0, 2, DEP>(p, nt, mrow, lh, ops, cx);
-    else epilogue_preload<PRO, EPI, 2, 4, DEP>(p, nt, mrow, lh, ops, cx);
-  } else {
-    if (fpc == 0) epilogue_preload<PRO, EPI, 0, 1, DEP>(p, nt, mrow, lh, ops, cx);
-    else if (fpc == 1) epilogue_preload<PRO, EPI, 1, 2, DEP>(p, nt, mrow, lh, ops, cx);
-    else if (fpc == 2) epilogue_preload<PRO, EPI, 2, 3, DEP>(p, nt, mrow, lh, ops, cx);
-    else epilogue_preload<PRO, EPI, 3, 4, DEP>(p, nt, mrow, lh, ops, cx);
-  }
+  for (int ww = 0; ww < SK_WAVES; ww++)
+#pragma unroll
+    for (int q = 0; q < NSTEP; q++)
+#pragma unroll
+      for (int j = 0; j < 4; j++) sum[4 * q + j] += part[ww][q][j];
+  if (ml < p.M) epilogue_tile<PRO, EPI, 0, NSTEP>(p, sum, nt, ml, lh, ssum, ssq, cx.by, ops, cx, ib);
 }
 
 template <int PRO, int EPI, int MS, class Cx>
@@ -315,7 +304,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   float* red = reinterpret_cast<float*>(smem_raw);                 // [8 waves][2 slots][16][64]
   const int t = cx.tid();
   const int lane = t & 63;
-  const int w = t >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);   // uniform: addresses and branches below are scalar
   const int lq = lane & 31;
   const int lh = lane >> 5;
   if (!Cx::kPersistent) {
@@ -338,8 +327,9 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   // producer); wave w adds parts w, w+8, ... for row `lane`, the epilogue adds the 8 wave sums
   float* sstat8 = red + SK_WAVES * 2 * 16 * 64 + 128;   // [8 waves][64][2]
   bf16x8 wf[NTL][8], xf[NMB][8];
-  const bf16* wbase = p.W.w + ((size_t)nt * KC16 + (kbeg >> 4)) * 512 + lane * 8;   // tile j: + j * KC16 * 512
-  const bf16* xbase = p.X + (size_t)(kbeg >> 4) * 512 + lane * 8;
+  const unsigned voff = (unsigned)lane * 16u;    // a load is a uniform base plus this
+  const bf16* wbase = p.W.w + ((size_t)nt * KC16 + (kbeg >> 4)) * 512;   // tile j: + j * KC16 * 512
+  const bf16* xbase = p.X + (size_t)(kbeg >> 4) * 512;
   const int mb_last = p.M > 32 ? 1 : 0;        // last token block (clamps when M <= 32)
   const int mb_first = MS ? min(cx.bz, mb_last) : 0;   // global index of local token block 0
   // The tile of a token block is finished by PIECES waves, each taking 4 / PIECES of its four 8-feature steps
@@ -347,7 +337,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   // epilogue arithmetic are the tail of the launch, and one wave alone took 3.8 k cycles over them for the QKV
   // epilogue (2.2 k for GeGLU)
   constexpr int PIECES = EPI == EPI_QKV ? 4 : EPI == EPI_GEGLU ? 2 : 1;
-  constexpr int NFIN = NSLOT * PIECES;
+  constexpr int NFIN = NSLOT * PIECES, NSTEP = 4 / PIECES;
   static_assert(NFIN <= SK_WAVES, "finishing waves");
   EpiOps ops;
   const int fslot = w / PIECES, fpc = w % PIECES;   // finishing wave f: slot f / PIECES, piece f % PIECES
@@ -360,9 +350,9 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
     for (int i = 0; i < 8; i++) {
       const int st = min(w * 8 + i, n16 - 1);
 #pragma unroll
-      for (int j = 0; j < NTL; j++) wf[j][i] = *reinterpret_cast<const bf16x8*>(wbase + ((size_t)j * KC16 + st) * 512);
+      for (int j = 0; j < NTL; j++) wf[j][i] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(wbase + (size_t)(j * KC16 + st) * 512) + voff);
     }
-    if (w < NFIN && mrow < p.M) skinny_preload<PRO, EPI, PIECES, 0>(p, fnt, mrow, lh, fpc, ops, cx);
+    if (w < NFIN && mrow < p.M) epilogue_preload<PRO, EPI, 0, NSTEP, 0>(p, fnt, mrow, lh, ops, cx, fpc * NSTEP);
     cx.wait_inputs();
   }
   // statistics partials: issued ahead of the operand loads (same round trip), clamped and unconditional
@@ -379,16 +369,16 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
     const int st = min(w * 8 + i, n16 - 1);    // clamped: steps beyond the range are never used
     if (!Cx::kPersistent) {
 #pragma unroll
-      for (int j = 0; j < NTL; j++) wf[j][i] = *reinterpret_cast<const bf16x8*>(wbase + ((size_t)j * KC16 + st) * 512);
+      for (int j = 0; j < NTL; j++) wf[j][i] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(wbase + (size_t)(j * KC16 + st) * 512) + voff);
     }
 #pragma unroll
     for (int mb = 0; mb < NMB; mb++)
-      xf[mb][i] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(xbase + ((size_t)min(mb_first + mb, mb_last) * XKC16 + st) * 512));
+      xf[mb][i] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(xbase + (size_t)(min(mb_first + mb, mb_last) * XKC16 + st) * 512) + voff));
   }
   // operands of the epilogue, in the same round trip
   if (w < NFIN && mrow < p.M) {
-    if (Cx::kPersistent) skinny_preload<PRO, EPI, PIECES, 1>(p, fnt, mrow, lh, fpc, ops, cx);
-    else skinny_preload<PRO, EPI, PIECES, 2>(p, fnt, mrow, lh, fpc, ops, cx);
+    if (Cx::kPersistent) epilogue_preload<PRO, EPI, 0, NSTEP, 1>(p, fnt, mrow, lh, ops, cx, fpc * NSTEP);
+    else epilogue_preload<PRO, EPI, 0, NSTEP, 2>(p, fnt, mrow, lh, ops, cx, fpc * NSTEP);
   }
   f32x16 acc[NSLOT];   // slot = token block (NTL == 1) or feature tile (NTL == 2)
 #pragma unroll
@@ -436,16 +426,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
       ssq += sstat8[(ww * 64 + ml) * 2 + 1];
     }
   }
-  if constexpr (PIECES == 1) skinny_finish<PRO, EPI, 0, 4>(p, red, fslot, lane, fnt, ml, lh, ssum, ssq, ops, cx);
-  else if constexpr (PIECES == 2) {
-    if (fpc == 0) skinny_finish<PRO, EPI, 0, 2>(p, red, fslot, lane, fnt, ml, lh, ssum, ssq, ops, cx);
-    else skinny_finish<PRO, EPI, 2, 4>(p, red, fslot, lane, fnt, ml, lh, ssum, ssq, ops, cx);
-  } else {
-    if (fpc == 0) skinny_finish<PRO, EPI, 0, 1>(p, red, fslot, lane, fnt, ml, lh, ssum, ssq, ops, cx);
-    else if (fpc == 1) skinny_finish<PRO, EPI, 1, 2>(p, red, fslot, lane, fnt, ml, lh, ssum, ssq, ops, cx);
-    else if (fpc == 2) skinny_finish<PRO, EPI, 2, 3>(p, red, fslot, lane, fnt, ml, lh, ssum, ssq, ops, cx);
-    else skinny_finish<PRO, EPI, 3, 4>(p, red, fslot, lane, fnt, ml, lh, ssum, ssq, ops, cx);
-  }
+  skinny_finish<PRO, EPI, NSTEP>(p, red, fslot, lane, fnt, ml, lh, ssum, ssq, ops, cx, fpc * NSTEP);
 }
 
 template <int PRO, int EPI, int MS = 0>
@@ -470,7 +451,7 @@ __device__ __forceinline__ void gemm_skinny16_body(const GemmParams p, const Cx 
   float (*red)[64][4] = reinterpret_cast<float (*)[64][4]>(smem_raw);   // [SK_WAVES][64][4]
   const int t = cx.tid();
   const int lane = t & 63;
-  const int w = t >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int li = lane & 15;
   const int lg = lane >> 4;
   const int ntiles16 = p.n_tiles * 2;
@@ -484,10 +465,10 @@ __device__ __forceinline__ void gemm_skinny16_body(const GemmParams p, const Cx 
   const int mt16 = cx.by;
   const int KC16 = p.W.k_pad >> 4;
   const int XKC16 = p.ldx >> 4;
-  const int piece_w = ((lg & 1) * 32 + (nt16 & 1) * 16 + li) * 8;
-  const int piece_x = ((lg & 1) * 32 + (mt16 & 1) * 16 + li) * 8;
-  const bf16* wbase = p.W.w + ((size_t)(nt16 >> 1) * KC16 + (size_t)w * NS * 2 + (lg >> 1)) * 512 + piece_w;
-  const bf16* xbase = p.X + ((size_t)(mt16 >> 1) * XKC16 + (size_t)w * NS * 2 + (lg >> 1)) * 512 + piece_x;
+  // a load is a uniform base plus the lane's piece (the same for weights and activations, + 256 bytes for odd tiles)
+  const unsigned piece = (unsigned)((lg >> 1) * 1024 + ((lg & 1) * 32 + li) * 16);
+  const char* wbase = reinterpret_cast<const char*>(p.W.w + ((size_t)(nt16 >> 1) * KC16 + (size_t)w * NS * 2) * 512 + (nt16 & 1) * 128);
+  const char* xbase = reinterpret_cast<const char*>(p.X + ((size_t)(mt16 >> 1) * XKC16 + (size_t)w * NS * 2) * 512 + (mt16 & 1) * 128);
   bf16x8 wf[NS], xf[NS];
   const int m = mt16 * 16 + li;
   // operands of the epilogue (wave 0): the constants with the weights, the residual rows with the inputs
@@ -496,7 +477,7 @@ __device__ __forceinline__ void gemm_skinny16_body(const GemmParams p, const Cx 
   f32x4 rv = {0.f, 0.f, 0.f, 0.f}, gv = {1.f, 1.f, 1.f, 1.f}, bv = {0.f, 0.f, 0.f, 0.f};
   if (Cx::kPersistent) {   // constants before the wait
 #pragma unroll
-    for (int j = 0; j < NS; j++) wf[j] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)j * 1024);
+    for (int j = 0; j < NS; j++) wf[j] = *reinterpret_cast<const bf16x8*>(wbase + j * 2048 + piece);
     if (live) {
       if (p.gain != nullptr) gv = *reinterpret_cast<const f32x4*>(p.gain + n4);
       if (p.bias != nullptr) bv = *reinterpret_cast<const f32x4*>(p.bias + n4);
@@ -505,8 +486,8 @@ __device__ __forceinline__ void gemm_skinny16_body(const GemmParams p, const Cx 
   }
 #pragma unroll
   for (int j = 0; j < NS; j++) {
-    if (!Cx::kPersistent) wf[j] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)j * 1024);
-    xf[j] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(xbase + (size_t)j * 1024));
+    if (!Cx::kPersistent) wf[j] = *reinterpret_cast<const bf16x8*>(wbase + j * 2048 + piece);
+    xf[j] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(xbase + j * 2048 + piece));
   }
   // X given as attention shares over disjoint key ranges (k = 8 heads x 256, so wave w holds exactly
   // head w).  Share z carries its normalised output and (max, sum) of its exponentials; the merged
@@ -526,7 +507,7 @@ __device__ __forceinline__ void gemm_skinny16_body(const GemmParams p, const Cx 
     for (int z = 1; z < 4; z++) {
       if (z < nz) {
 #pragma unroll
-        for (int j = 0; j < NS; j++) xo[z - 1][j] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(xbase + (size_t)z * p.xsplit_stride + (size_t)j * 1024));
+        for (int j = 0; j < NS; j++) xo[z - 1][j] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(xbase + (size_t)z * p.xsplit_stride * 2 + j * 2048 + piece));
         ml[z] = cx.ld_bulk(reinterpret_cast<const float2*>(p.xsplit_ml + (((size_t)z * SK_WAVES + w) * 64 + mrow) * 2));
       }
     }
@@ -585,9 +566,12 @@ __device__ __forceinline__ void gemm_skinny16_body(const GemmParams p, const Cx 
   if (w != 0) return;
   float v[4];
   {
-    f32x4 a = {0.f, 0.f, 0.f, 0.f};
+    f32x4 part[SK_WAVES], a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ww = 0; ww < SK_WAVES; ww++) a += *reinterpret_cast<const f32x4*>(&red[ww][lane][0]);
+    for (int ww = 0; ww < SK_WAVES; ww++) part[ww] = *reinterpret_cast<const f32x4*>(&red[ww][lane][0]);
+    __builtin_amdgcn_sched_barrier(0);   // all eight reads in flight (left alone they are read and added one by one)
+#pragma unroll
+    for (int ww = 0; ww < SK_WAVES; ww++) a += part[ww];
 #pragma unroll
     for (int r = 0; r < 4; r++) v[r] = a[r] + bv[r] + rv[r];
   }

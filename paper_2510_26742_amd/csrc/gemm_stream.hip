@@ -211,42 +211,30 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W
             ssq += s2.y;
           }
         }
-        auto fin = [&](auto i0, auto i1) {
-          constexpr int I0 = decltype(i0)::value, I1 = decltype(i1)::value;
-          f32x16 sum;
+        constexpr int NSTEP = 4 / PIECES;
+        const int ib = pc * NSTEP;
+        f32x16 sum;
 #pragma unroll
-          for (int r = 0; r < 16; r++) sum[r] = 0.f;
+        for (int r = 0; r < 16; r++) sum[r] = 0.f;
 #pragma unroll
-          for (int ww = 0; ww < W; ww++)
+        for (int ww = 0; ww < W; ww++)
 #pragma unroll
-            for (int q = I0; q < I1; q++) {
-              const f32x4 v4 = *reinterpret_cast<const f32x4*>(red + ((((size_t)ww * TPR + unit / PIECES) * 4 + q) * 64 + lane) * 4);
+          for (int q = 0; q < NSTEP; q++) {
+            const f32x4 v4 = *reinterpret_cast<const f32x4*>(red + ((((size_t)ww * TPR + unit / PIECES) * 4 + ib + q) * 64 + lane) * 4);
 #pragma unroll
-              for (int jj = 0; jj < 4; jj++) sum[4 * q + jj] += v4[jj];
-            }
-          EpiOps ops;
-#pragma unroll
-          for (int q = I0; q < I1; q++) {
-            const float* c4 = cols + (tile % NB) * 32 + 8 * q + 4 * lh;
-            if (p.bias != nullptr) ops.bias[q - I0] = *reinterpret_cast<const f32x4*>(c4);
-            if (PRO == PRO_LN) ops.colsum[q - I0] = *reinterpret_cast<const f32x4*>(c4 + NB * 32);
-            if (EPI == EPI_RESID && p.gain != nullptr) ops.gain[q - I0] = *reinterpret_cast<const f32x4*>(c4 + 2 * NB * 32);
-            if (EPI == EPI_RESID) ops.aux[q - I0] = resid[v][q];
-            if (EPI == EPI_QKV) ops.aux[q - I0] = rope[rd][v][q - I0];
+            for (int jj = 0; jj < 4; jj++) sum[4 * q + jj] += v4[jj];
           }
-          epilogue_tile<PRO, EPI, I0, I1>(p, sum, nt, m, lh, ssum, ssq, 0, ops);
-        };
-        using std::integral_constant;
-        if constexpr (PIECES == 1) fin(integral_constant<int, 0>{}, integral_constant<int, 4>{});
-        else if constexpr (PIECES == 2) {
-          if (pc == 0) fin(integral_constant<int, 0>{}, integral_constant<int, 2>{});
-          else fin(integral_constant<int, 2>{}, integral_constant<int, 4>{});
-        } else {
-          if (pc == 0) fin(integral_constant<int, 0>{}, integral_constant<int, 1>{});
-          else if (pc == 1) fin(integral_constant<int, 1>{}, integral_constant<int, 2>{});
-          else if (pc == 2) fin(integral_constant<int, 2>{}, integral_constant<int, 3>{});
-          else fin(integral_constant<int, 3>{}, integral_constant<int, 4>{});
+        EpiOps ops;
+#pragma unroll
+        for (int q = 0; q < NSTEP; q++) {
+          const float* c4 = cols + (tile % NB) * 32 + 8 * (ib + q) + 4 * lh;
+          if (p.bias != nullptr) ops.bias[q] = *reinterpret_cast<const f32x4*>(c4);
+          if (PRO == PRO_LN) ops.colsum[q] = *reinterpret_cast<const f32x4*>(c4 + NB * 32);
+          if (EPI == EPI_RESID && p.gain != nullptr) ops.gain[q] = *reinterpret_cast<const f32x4*>(c4 + 2 * NB * 32);
+          if (EPI == EPI_RESID) ops.aux[q] = resid[v][q];
+          if (EPI == EPI_QKV) ops.aux[q] = rope[rd][v][q];
         }
+        epilogue_tile<PRO, EPI, 0, NSTEP>(p, sum, nt, m, lh, ssum, ssq, 0, ops, LaunchCtx{}, ib);
       }
     }
   }

@@ -361,9 +361,9 @@ struct Tune {
   int pfq = 64, pfa = 64, pfo = 128, pfd = 128;
   int qms = 1;            // expert QKV: token blocks on separate blocks (160 instead of 80)
   int ksplit = 1;         // expert attention: key shares for prefixes beyond kcps chunks
-  int kcps = 8;
+  int kcps = -1;          // key chunks per share (-1: expert_shares)
   // expert attention: the 8 value slices of a (query tile, head) shared out over this many blocks, each repeating the
-  // scores (-1: 4 with one key share, 2 with several; measured -0.2 ms of denoise.  The prefix attention gains nothing)
+  // scores (-1: expert_shares)
   int avs = -1;
   int ae16 = 1;           // expert O / down on 16 x 16 tiles (256 blocks) instead of 32 x 32 (64 blocks)
   // O projections (vision, prefix) as split-K partial GEMMs + reduction (0) or one launch over the whole k range (1:
@@ -848,6 +848,21 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
 }
 
 
+// How the expert's attention over `pchunks` chunks of prefix keys is cut: key shares (merged by the O projection, whose
+// inputs they multiply), chunks per share, blocks that share a head's values.
+struct ExpertShares { int shares, per_share, v_split; };
+ExpertShares expert_shares(const pi0_ctx* c, int pchunks) {
+  const Tune& T = c->tune;
+  ExpertShares s{1, pchunks, 1};
+  const int per = T.kcps > 0 ? T.kcps : 8;   // a chunk per wave; the last share, with the suffix, is the short one
+  if (T.ksplit && T.ae16 && c->d.H == 8 && pchunks > per && ceil_div(pchunks, per) <= 4) {
+    s.shares = ceil_div(pchunks, per);
+    s.per_share = per;
+  }
+  s.v_split = T.avs > 0 ? T.avs : s.per_share > 8 ? 4 : s.shares >= 2 ? 1 : 2;
+  return s;
+}
+
 // The denoise loop as ONE persistent kernel (expert_persistent.hip): the operations' parameters exactly as the
 // per-operation launches below fill them for layer 0 / step 0, plus the strides between layers.  Returns false
 // (nothing launched) when the shape or the tuning choices are outside what the kernel covers; the caller then
@@ -861,11 +876,8 @@ bool persistent_feasible(const pi0_ctx* c, int P) {
   if (!T.pdn || !c->pk_ok) return false;
   const int pchunks = ceil_div(P, 32);
   if (!T.ae16 || !T.qms || d.H != 8 || d.X > SK_KMAX_HOST || d.X % 256 != 0) return false;
-  const int shares = pchunks > T.kcps ? ceil_div(pchunks, T.kcps) : 1;
-  if (T.kcps > 8 || shares > 4 || (shares > 1 && !T.ksplit)) return false;
-  const int vs = T.avs > 0 ? T.avs : (shares == 1 ? 4 : 2);
-  if (vs != 2 && vs != 4 && vs != 8) return false;   // the kernel's attention keeps at most 5 chunks per wave
-  if (ceil_div((shares > 1 ? T.kcps : pchunks) + 2, vs) > 5) return false;
+  const ExpertShares es = expert_shares(c, pchunks);
+  if (es.shares > 4 || es.per_share > 8 || (es.v_split & (es.v_split - 1)) != 0) return false;
   const WsTr& L0 = w.exp[0];
   if (L0.o.k_pad != 2048 || (L0.down.k_pad != 2048 && L0.down.k_pad != 4096)) return false;
   if (d.Le > 1) {
@@ -888,7 +900,8 @@ bool run_denoise_persistent(Run& r, int P) {
   if (!r.persistent_ok || r.timer != nullptr || !persistent_feasible(c, P)) return false;
   const int chunk = c->cfg.chunk;
   const int pchunks = ceil_div(P, 32);
-  const int shares = pchunks > T.kcps ? ceil_div(pchunks, T.kcps) : 1;
+  const ExpertShares es = expert_shares(c, pchunks);
+  const int shares = es.shares;
   const WsTr& L0 = w.exp[0];
   const size_t wst = d.Le > 1 ? w.exp[1].qkv.w - w.exp[0].qkv.w : 0, gst = d.Le > 1 ? w.g_e1[1] - w.g_e1[0] : 0;
   const size_t arena_bytes = w.total - w.act_begin;
@@ -956,13 +969,13 @@ bool run_denoise_persistent(Run& r, int P) {
     a.out = at<bf16>(c, w.eattn); a.out_ld = d.H * 256; a.head_dim = 256;
     if (shares > 1) {
       a.key_splits = shares;
-      a.chunks_per_split = T.kcps;
+      a.chunks_per_split = es.per_share;
       a.out_split_stride = (size_t)64 * d.H * 256;
       a.ml_out = at<float>(c, w.eml);
     }
-    a.v_split = T.avs > 0 ? T.avs : (shares == 1 ? 4 : 2);
+    a.v_split = es.v_split;
     E.att = a;
-    E.att_gx = 2 * a.v_split;
+    E.att_gx = 4 * a.v_split;
     E.att_items = E.att_gx * d.H * shares;
   }
   auto resid = [&](const PW& pw, const bf16* X, int K, const float* gain) {
@@ -1064,8 +1077,8 @@ void run_denoise(Run& r, int P, Taps* taps) {
   const Tune& T = c->tune;
   // prefixes beyond 256 keys: the attention of the expert is shared out over ceil(chunks / 8) blocks per
   // (query tile, head); needs the 16 x 16 O projection (which merges the shares) and 8 heads of 256
-  const int kcps = T.kcps;   // key chunks per share
-  const int ksplits = (T.ae16 && T.ksplit && d.H == 8 && pchunks > kcps && ceil_div(pchunks, kcps) <= 4) ? ceil_div(pchunks, kcps) : 1;
+  const ExpertShares es = expert_shares(c, pchunks);
+  const int ksplits = es.shares;
   int o_splits = 1;
   // read-ahead kernel on its own stream, forked here and joined after the last Euler step (in a captured graph:
   // a branch beside the chain of compute launches); it replaces the warm-up blocks inside the launches
@@ -1188,11 +1201,11 @@ void run_denoise(Run& r, int P, Taps* taps) {
         a.out = ex<bf16>(r, w.eattn); a.out_ld = d.H * 256; a.head_dim = 256;
         if (ksplits > 1) {   // long prefix: key shares over more blocks, merged by the O projection
           a.key_splits = ksplits;
-          a.chunks_per_split = kcps;
+          a.chunks_per_split = es.per_share;
           a.out_split_stride = (size_t)64 * d.H * 256;
           a.ml_out = ex<float>(r, w.eml);
         }
-        a.v_split = T.avs > 0 ? T.avs : (ksplits == 1 ? 4 : 2);
+        a.v_split = es.v_split;
         a.pf = pf_begin(pfa);
         pf_weights(a.pf, 0, L.gu);
         r.cls = PI0_OP_EXP_ATTN;

@@ -1,0 +1,13 @@
+"""The action expert's attention kernel (16 query rows per block) at the edges of what it takes: prefixes shorter than a
+16-key tile, ending inside one, exactly full shares, and every way of sharing out the values."""
+import pytest
+
+from tests import test_gpu_attention as base
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("P,chunks_per_share", [(1, 0), (15, 0), (17, 0), (225, 0), (256, 0), (257, 8), (512, 8), (300, 3), (1024, 8)])
+@pytest.mark.parametrize("v_split", [1, 2, 4, 8])
+def test_prefix_lengths_and_value_splits(P, chunks_per_share, v_split):
+    base.test_expert_attention_block_mask_and_key_shares(P, chunks_per_share, v_split)
