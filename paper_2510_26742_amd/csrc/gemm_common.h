@@ -325,7 +325,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
 
   // row statistics of the input: parts partial sums per row (1, or one per 32-column tile of the
   // producer); wave w adds parts w, w+8, ... for row `lane`, the epilogue adds the 8 wave sums
-  float* sstat8 = red + SK_WAVES * 2 * 16 * 64 + 128;   // [8 waves][64][2]
+  float* sstat8 = red + SK_WAVES * 2 * 16 * 64 + 128;   // [8 waves][64]
   bf16x8 wf[NTL][8], xf[NMB][8];
   const unsigned voff = (unsigned)lane * 16u;    // a load is a uniform base plus this
   const bf16* wbase = p.W.w + ((size_t)nt * KC16 + (kbeg >> 4)) * 512;   // tile j: + j * KC16 * 512
@@ -339,6 +339,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   constexpr int PIECES = EPI == EPI_QKV ? 4 : EPI == EPI_GEGLU ? 2 : 1;
   constexpr int NFIN = NSLOT * PIECES, NSTEP = 4 / PIECES;
   static_assert(NFIN <= SK_WAVES, "finishing waves");
+  static_assert(PRO != PRO_LN, "the statistics are sums of squares");
   EpiOps ops;
   const int fslot = w / PIECES, fpc = w % PIECES;   // finishing wave f: slot f / PIECES, piece f % PIECES
   const int fmb = NTL == 1 ? fslot : 0;             // its token block (local) ...
@@ -355,13 +356,16 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
     if (w < NFIN && mrow < p.M) epilogue_preload<PRO, EPI, 0, NSTEP, 0>(p, fnt, mrow, lh, ops, cx, fpc * NSTEP);
     cx.wait_inputs();
   }
-  // statistics partials: issued ahead of the operand loads (same round trip), clamped and unconditional
-  float2 sp[8];
+  // statistics partials (sums of squares; RMS needs nothing else): issued ahead of the operand loads (same round trip),
+  // clamped and unconditional.  Wave w adds parts w, w + 8, ... of a row, the even and the odd ones of these apart: with
+  // one token block the lane halves take one half of the parts each, so that nobody loads rows of the other block.
+  constexpr int NSP = NMB == 1 ? 4 : 8;
+  float sp[NSP];
   if (PRO != PRO_NONE) {
 #pragma unroll
-    for (int jj = 0; jj < 8; jj++) {
-      const int j = min(w + SK_WAVES * jj, p.rowstat_parts - 1);
-      sp[jj] = cx.ld_bulk(reinterpret_cast<const float2*>(p.rowstat + ((size_t)j * 64 + lane) * 2));
+    for (int jj = 0; jj < NSP; jj++) {
+      const int j = min(w + SK_WAVES * (NMB == 1 ? 2 * jj + lh : jj), p.rowstat_parts - 1);
+      sp[jj] = cx.ld_bulk(p.rowstat + ((size_t)j * 64 + (NMB == 1 ? mb_first * 32 + lq : lane)) * 2 + 1);
     }
   }
 #pragma unroll
@@ -402,31 +406,36 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
     }
   cx.mark(1);   // operands arrived, products done
   if (PRO != PRO_NONE) {
-    float pa = 0.f, pb = 0.f;
+    float pe = 0.f, po = 0.f;
+    if constexpr (NMB == 1) {
 #pragma unroll
-    for (int jj = 0; jj < 8; jj++) {
-      if (w + SK_WAVES * jj < p.rowstat_parts) {
-        pa += sp[jj].x;
-        pb += sp[jj].y;
+      for (int jj = 0; jj < NSP; jj++) {
+        if (w + SK_WAVES * (2 * jj + lh) < p.rowstat_parts) pe += sp[jj];
       }
+      sstat8[w * 64 + lane] = pe;       // [wave][half][32 rows]
+    } else {
+#pragma unroll
+      for (int jj = 0; jj < NSP; jj += 2) {
+        if (w + SK_WAVES * jj < p.rowstat_parts) pe += sp[jj];
+        if (w + SK_WAVES * (jj + 1) < p.rowstat_parts) po += sp[jj + 1];
+      }
+      sstat8[w * 64 + lane] = pe + po;  // [wave][64 rows]
     }
-    sstat8[(w * 64 + lane) * 2] = pa;
-    sstat8[(w * 64 + lane) * 2 + 1] = pb;
   }
   __syncthreads();
   cx.mark(2);   // partial tiles of all waves in LDS
   if (w >= NFIN) return;
   if (MS && cx.bz > mb_last) return;   // M <= 32: the second block of a split launch has nothing to store
   const int ml = mrow;
-  float ssum = 0.f, ssq = 0.f;
+  float ssq = 0.f;
   if (PRO != PRO_NONE) {   // statistics of the lane's own row: the 8 waves' partial sums, in wave order
+    float part[SK_WAVES];
 #pragma unroll
-    for (int ww = 0; ww < SK_WAVES; ww++) {
-      ssum += sstat8[(ww * 64 + ml) * 2];
-      ssq += sstat8[(ww * 64 + ml) * 2 + 1];
-    }
+    for (int ww = 0; ww < SK_WAVES; ww++) part[ww] = NMB == 1 ? sstat8[ww * 64 + lq] + sstat8[ww * 64 + 32 + lq] : sstat8[ww * 64 + ml];
+#pragma unroll
+    for (int ww = 0; ww < SK_WAVES; ww++) ssq += part[ww];
   }
-  skinny_finish<PRO, EPI, NSTEP>(p, red, fslot, lane, fnt, ml, lh, ssum, ssq, ops, cx, fpc * NSTEP);
+  skinny_finish<PRO, EPI, NSTEP>(p, red, fslot, lane, fnt, ml, lh, 0.f, ssq, ops, cx, fpc * NSTEP);
 }
 
 template <int PRO, int EPI, int MS = 0>

@@ -1205,7 +1205,10 @@ void run_denoise(Run& r, int P, Taps* taps) {
           a.out_split_stride = (size_t)64 * d.H * 256;
           a.ml_out = ex<float>(r, w.eml);
         }
+        // a launch requests the prefix keys and values itself: as many blocks as there are compute units, each with fewer
+        // values (the sums do not depend on it: a column of the output is one wave's work either way)
         a.v_split = es.v_split;
+        if (T.avs <= 0 && es.per_share <= 8) a.v_split = es.shares == 1 ? 8 : es.shares == 2 ? 4 : 2;
         a.pf = pf_begin(pfa);
         pf_weights(a.pf, 0, L.gu);
         r.cls = PI0_OP_EXP_ATTN;
