@@ -217,7 +217,7 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
       m_loc = fmaxf(m_loc, sv1[e]);
     }
   }
-  m_loc = fmaxf(m_loc, __shfl_xor(m_loc, 32, 64));
+  m_loc = max_xor32(m_loc);
   if (lh == 0) mw[w * 32 + lq] = m_loc;
   __syncthreads();
   float m_all = NEG_BIG;
@@ -245,7 +245,7 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
     if (ci < n0) emit(sv[r], ci);
   }
   if (seg1_wave) emit(sv1, n0 + w);
-  l_loc += __shfl_xor(l_loc, 32, 64);
+  l_loc = add_xor32(l_loc);
   if (lh == 0) lw[w * 32 + lq] = l_loc;
   __syncthreads();
   if (!pv_wave) return;
@@ -515,8 +515,8 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
       m_loc = fmaxf(m_loc, sv1[e]);
     }
   }
-  m_loc = fmaxf(m_loc, __shfl_xor(m_loc, 16, 64));
-  m_loc = fmaxf(m_loc, __shfl_xor(m_loc, 32, 64));
+  m_loc = max_xor16(m_loc);
+  m_loc = max_xor32(m_loc);
   if (g == 0) mw[w * 16 + qi] = m_loc;
   __syncthreads();
   cx.mark(2);   // scores done
@@ -545,8 +545,8 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
     for (int e = 0; e < 4; e++) pb[e] = (bf16)prob(sv1[e]);
     *reinterpret_cast<bf16x4*>(pf + ((size_t)(n0 + (tile1 >> 1)) * 64 + lane) * 8 + (tile1 & 1) * 4) = pb;
   }
-  l_loc += __shfl_xor(l_loc, 16, 64);
-  l_loc += __shfl_xor(l_loc, 32, 64);
+  l_loc = add_xor16(l_loc);
+  l_loc = add_xor32(l_loc);
   if (g == 0) lw[w * 16 + qi] = l_loc;
   __syncthreads();
   cx.mark(3);   // probabilities in LDS

@@ -30,6 +30,36 @@ __device__ __forceinline__ T* as_global(T* p) {
   return (T*)(__attribute__((address_space(1))) T*)p;
 }
 
+// the same for a uniform pointer, and it is in scalar registers from here on: its arithmetic does not move behind a wait
+__device__ __forceinline__ const char* computed_global(const char* p) {
+  typedef const __attribute__((address_space(1))) char* Global;
+  Global g = (Global)p;
+  asm volatile("" : "+s"(g));
+  return (const char*)g;
+}
+
+// Exchange between lanes l and l ^ 32 / l ^ 16 in one vector instruction (v_permlane32_swap_b32 and v_permlane16_swap_b32:
+// the upper half (odd rows of 16) of the first operand changes places with the lower half (even rows) of the second), where
+// a shuffle is a round trip through the LDS crossbar in the tail of a kernel body.
+// swap_halves(a, b): lanes 0 .. 31 get (a, a of lane + 32), lanes 32 .. 63 get (b of lane - 32, b)
+__device__ __forceinline__ u32x2_t swap_halves(unsigned a, unsigned b) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); }
+__device__ __forceinline__ float add_xor32(float v) {
+  const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_xor16(float v) {
+  const u32x2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float max_xor32(float v) {
+  const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float max_xor16(float v) {
+  const u32x2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 struct LaunchCtx {
   static constexpr bool kPersistent = false;
   int bx, by, bz;
@@ -40,6 +70,9 @@ struct LaunchCtx {
   __device__ __forceinline__ T ld_bulk(const T* p) const { return *p; }
   template <class T>
   __device__ __forceinline__ void st(T* p, const T& v) const { *p = v; }
+  __device__ __forceinline__ unsigned off(const void*) const { return 0; }
+  template <class T>
+  __device__ __forceinline__ void st_off(unsigned, const T&) const {}
   __device__ __forceinline__ void wait_inputs() const {}
   __device__ __forceinline__ void mark(int) const {}
   __device__ __forceinline__ int tid() const { return (int)threadIdx.x; }
@@ -204,13 +237,18 @@ struct PersistCtxT {
     else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(arena, off(p), 0, PI0_AUX_DEVICE_SCOPE));
     else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(arena, off(p), 0, PI0_AUX_DEVICE_SCOPE));
   }
+  // store at an arena offset that was computed ahead of the wait, plus a constant
+  template <class T>
+  __device__ __forceinline__ void st_off(unsigned o, const T& v) const {
+    static_assert(sizeof(T) == 16 || sizeof(T) == 8 || sizeof(T) == 4 || sizeof(T) == 2, "access size");
+    if constexpr (sizeof(T) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), arena, o, 0, PI0_AUX_DEVICE_SCOPE);
+    else if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), arena, o, 0, PI0_AUX_DEVICE_SCOPE);
+    else if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), arena, o, 0, PI0_AUX_DEVICE_SCOPE);
+    else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), arena, o, 0, PI0_AUX_DEVICE_SCOPE);
+  }
   template <class T>
   __device__ __forceinline__ void st(T* p, const T& v) const {
-    static_assert(sizeof(T) == 16 || sizeof(T) == 8 || sizeof(T) == 4 || sizeof(T) == 2, "access size");
-    if constexpr (sizeof(T) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), arena, off(p), 0, PI0_AUX_DEVICE_SCOPE);
-    else if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), arena, off(p), 0, PI0_AUX_DEVICE_SCOPE);
-    else if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), arena, off(p), 0, PI0_AUX_DEVICE_SCOPE);
-    else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), arena, off(p), 0, PI0_AUX_DEVICE_SCOPE);
+    st_off(off(p), v);
   }
   template <class T>
   __device__ __forceinline__ T ld_bulk(const T* p) const {

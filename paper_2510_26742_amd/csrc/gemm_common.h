@@ -45,7 +45,36 @@ __device__ __forceinline__ size_t xf_index(int m, int k, int kc16) {
 // slot j holds the operands of the tile's step I0 + j of the wave that asked for steps I0 .. I1 - 1
 struct EpiOps {
   f32x4 bias[4], colsum[4], aux[4], gain[4];
+  unsigned dst[4];   // persistent kernel: where the step's results go (epilogue_dst), computed ahead of the wait
 };
+
+// Where step i of the tile goes: EPI_QKV: the query, key or value fragments (null for padding); EPI_GEGLU: the 4 product
+// columns that a lane stores after the odd step i
+template <int EPI>
+__device__ __forceinline__ bf16* epilogue_dst(const GemmParams& p, int nt, int i, int m, int lh) {
+  if (EPI == EPI_GEGLU) return p.out_bf16 + xf_index(m, nt * 16 + 4 * (i - 1) + 4 * lh, p.ldo >> 4);
+  const int n4 = nt * 32 + 8 * i + 4 * lh;
+  const int S16 = p.dqk_pad >> 4;
+  const int kc = m >> 5, kk = m & 31;
+  // rotary models have heads of 256: all lanes of a step are on one side of the boundaries between q, k and v
+  const int n_side = p.rope != nullptr ? nt * 32 + 8 * i : n4;
+  if (n_side < p.q_cols + p.k_cols) {
+    const bool is_q = n_side < p.q_cols;
+    const int nl = is_q ? n4 : n4 - p.q_cols;
+    const int head = p.rope != nullptr ? nl >> 8 : (int)(((float)nl + 0.5f) * (1.0f / (float)p.head_dim));   // nl / head_dim: exact, nl < 2^16
+    // packed head layout with rotation: row 2 i = dimension i, row 2 i + 1 = dimension i + 128
+    const int dd = p.rope != nullptr ? (nl & 255) >> 1 : nl - head * p.head_dim;                            // even with rotation, else a multiple of 4
+    bf16* dst = is_q ? p.out_bf16 + ((size_t)head * p.q_mbs + kc) * S16 * 512
+                     : p.kfrag + ((size_t)(p.rope != nullptr ? 0 : head * p.kv_chunks) + kc) * S16 * 512;
+    return dst + kk * 8 + (size_t)(dd >> 4) * 512 + ((dd & 15) >> 3) * 256 + (dd & 7);
+  }
+  const int nl = n4 - p.q_cols - p.k_cols;
+  const int head = (int)(((float)nl + 0.5f) * (1.0f / (float)p.head_dim));
+  const int dd = nl - head * p.head_dim;    // multiple of 4: the lane's four columns are 8 elements apart
+  if (head >= p.kv_heads) return nullptr;
+  const int s2 = kk >> 4, g = (kk & 15) >> 3, hh = (kk & 7) >> 2, jp = kk & 3;
+  return p.vfrag + (((size_t)head * p.kv_chunks + kc) * p.nvb) * 1024 + s2 * 512 + hh * 256 + 4 * g + jp + (size_t)(dd >> 5) * 1024 + (dd & 31) * 8;
+}
 
 // Steps I0 .. I1-1 of the tile's four 8-feature steps (all of them unless a kernel shares a tile's epilogue out
 // over several waves; the residual epilogue's row statistics need the whole tile, the GeGLU one whole pairs).
@@ -61,7 +90,7 @@ __device__ __forceinline__ void epilogue_preload(const GemmParams& p, int nt, in
     const int n4 = nt * 32 + 8 * (i + ib) + 4 * lh;
     if (DEP != 1) {
       if (PRO == PRO_LN) o.colsum[i - I0] = *reinterpret_cast<const f32x4*>(p.colsum + n4);
-      if (p.bias != nullptr) o.bias[i - I0] = *reinterpret_cast<const f32x4*>(p.bias + n4);
+      o.bias[i - I0] = p.bias != nullptr ? *reinterpret_cast<const f32x4*>(p.bias + n4) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     if (EPI == EPI_RESID) {
       if (n4 < p.n_valid) {
@@ -76,6 +105,16 @@ __device__ __forceinline__ void epilogue_preload(const GemmParams& p, int nt, in
         const int nl = n4 < p.q_cols ? n4 : n4 - p.q_cols;
         const int i0 = (nl & 255) >> 1;
         o.aux[i - I0] = *reinterpret_cast<const f32x4*>(p.rope + ((size_t)(p.pos0 + m) * 128 + i0) * 2);
+      }
+      if (DEP != 1 && Cx::kPersistent) {
+        const bf16* dst = epilogue_dst<EPI>(p, nt, i + ib, m, lh);
+        o.dst[i - I0] = dst != nullptr ? cx.off(dst) : ~0u;
+        asm volatile("" : "+v"(o.dst[i - I0]));
+      }
+    } else if (EPI == EPI_GEGLU) {
+      if (DEP != 1 && Cx::kPersistent && (i & 1)) {
+        o.dst[i - I0] = cx.off(epilogue_dst<EPI>(p, nt, i + ib, m, lh));
+        asm volatile("" : "+v"(o.dst[i - I0]));
       }
     } else if (EPI == EPI_EULER) {
       // the x values this lane updates, with the other inputs (read inside the epilogue they cost one round trip per
@@ -102,7 +141,6 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
   static_assert(EPI != EPI_RESID || (I0 == 0 && I1 == 4), "row statistics are taken over the whole tile");
   static_assert(EPI != EPI_GEGLU || (I0 % 2 == 0 && I1 % 2 == 0), "gate / up steps are stored in pairs");
   const float inv_k = 1.0f / (float)p.k_true;
-  const float inv_hd = EPI == EPI_QKV ? 1.0f / (float)p.head_dim : 0.f;
   {
     float rs = 1.f, mu = 0.f;
     float st_a = 0.f, st_b = 0.f;   // EPI_RESID: sum / sum of squares of this lane's fp32 outputs
@@ -133,11 +171,9 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
 #pragma unroll
         for (int j = 0; j < 4; j++) v[j] = rs * (v[j] - mu * cs[j]);
       }
-      if (p.bias != nullptr) {
-        const f32x4 bb = ops.bias[i - I0];
+      const f32x4 bb = ops.bias[i - I0];   // zero without a bias
 #pragma unroll
-        for (int j = 0; j < 4; j++) v[j] += bb[j];
-      }
+      for (int j = 0; j < 4; j++) v[j] += bb[j];
       if (EPI == EPI_RESID) {
         if (n4 < p.n_valid) {
           if (p.resid != nullptr) {
@@ -179,13 +215,10 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
         if ((i & 1) == 0) {
           geglu_keep = mine;
         } else {
-          const unsigned give = lh ? geglu_keep : mine;            // half 0 gives step i, half 1 gives step i-1
-          const unsigned got = (unsigned)__shfl_xor((int)give, 32, 64);
-          const unsigned lo = lh ? got : geglu_keep;                 // half 0: own i-1, partner's i-1
-          const unsigned hi = lh ? mine : got;                       // half 1: partner's i, own i
-          const int col = nt * 16 + 4 * (i + ib - 1) + 4 * lh;            // (n4 >> 1) of step i-1 for half 0, +4 for half 1
-          const uint2 o2 = {lo, hi};
-          cx.st(reinterpret_cast<uint2*>(p.out_bf16 + xf_index(m, col, p.ldo >> 4)), o2);
+          const u32x2_t both = swap_halves(geglu_keep, mine);        // half 0: own i-1, partner's i-1; half 1: partner's i, own i
+          const uint2 o2 = {both[0], both[1]};
+          if (Cx::kPersistent) cx.st_off(ops.dst[i - I0], o2);
+          else cx.st(reinterpret_cast<uint2*>(epilogue_dst<EPI>(p, nt, i + ib, m, lh)), o2);
         }
       } else if (EPI == EPI_EULER) {
         if (m >= 1 && n4 < p.n_valid) {
@@ -197,58 +230,35 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
           }
         }
       } else if (EPI == EPI_QKV) {
-        const int S16 = p.dqk_pad >> 4;
-        const int key = m;
-        const int kc = key >> 5, kk = key & 31;
-        if (n4 < p.q_cols + p.k_cols) {
-          const bool is_q = n4 < p.q_cols;
-          const int nl = is_q ? n4 : n4 - p.q_cols;
+        bf16* const dst = Cx::kPersistent ? nullptr : epilogue_dst<EPI>(p, nt, i + ib, m, lh);
+        auto store = [&](int elem, auto v2) {
+          if (Cx::kPersistent) cx.st_off(ops.dst[i - I0] + (unsigned)elem * 2u, v2);
+          else cx.st(reinterpret_cast<decltype(v2)*>(dst + elem), v2);
+        };
+        const int n_side = p.rope != nullptr ? nt * 32 + 8 * (i + ib) : n4;
+        if (n_side < p.q_cols + p.k_cols) {
           if (p.rope != nullptr) {
-            // packed head layout: row 2i = dim i, row 2i+1 = dim i + 128
-            const int head = nl >> 8;
-            const int i0 = (nl & 255) >> 1;          // even
             const f32x4 c4 = ops.aux[i - I0];   // cos i0, sin i0, cos i0+1, sin i0+1
             const float lo0 = v[0] * c4[0] - v[1] * c4[1], hi0 = v[1] * c4[0] + v[0] * c4[1];
             const float lo1 = v[2] * c4[2] - v[3] * c4[3], hi1 = v[3] * c4[2] + v[2] * c4[3];
             const bf16x2 lo = {(bf16)lo0, (bf16)lo1};
             const bf16x2 hi = {(bf16)hi0, (bf16)hi1};
-            {
-              bf16* dst = (is_q ? p.out_bf16 + ((size_t)head * p.q_mbs + kc) * S16 * 512 : p.kfrag + ((size_t)kc * S16) * 512) +
-                          kk * 8;
-              const int d0 = i0, d1 = i0 + 128;
-              cx.st(reinterpret_cast<bf16x2*>(dst + (size_t)(d0 >> 4) * 512 + ((d0 & 15) >> 3) * 256 + (d0 & 7)), lo);
-              cx.st(reinterpret_cast<bf16x2*>(dst + (size_t)(d1 >> 4) * 512 + ((d1 & 15) >> 3) * 256 + (d1 & 7)), hi);
-            }
+            store(0, lo);
+            store(8 * 512, hi);   // 128 dimensions on
           } else {
-            const int head = (int)(((float)nl + 0.5f) * inv_hd);   // nl / head_dim: exact, nl < 2^16
-            const int d = nl - head * p.head_dim;    // multiple of 4
             const bf16x4 ob = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
-            {
-              bf16* dst = (is_q ? p.out_bf16 + ((size_t)head * p.q_mbs + kc) * S16 * 512
-                                : p.kfrag + ((size_t)head * p.kv_chunks + kc) * S16 * 512) + kk * 8;
-              cx.st(reinterpret_cast<bf16x4*>(dst + (size_t)(d >> 4) * 512 + ((d & 15) >> 3) * 256 + (d & 7)), ob);
-            }
+            store(0, ob);
           }
-        } else {
-          const int nl = n4 - p.q_cols - p.k_cols;
-          const int head = (int)(((float)nl + 0.5f) * inv_hd);
-          const int d = nl - head * p.head_dim;
-          if (head < p.kv_heads) {
-            const int s2 = kk >> 4, g = (kk & 15) >> 3, hh = (kk & 7) >> 2, jp = kk & 3;
-            bf16* dst = p.vfrag + (((size_t)head * p.kv_chunks + kc) * p.nvb) * 1024 + s2 * 512 + hh * 256 + 4 * g + jp;
+        } else if (Cx::kPersistent ? ops.dst[i - I0] != ~0u : dst != nullptr) {
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-              const int dd = d + j;
-              cx.st(dst + (size_t)(dd >> 5) * 1024 + (dd & 31) * 8, (bf16)v[j]);
-            }
-          }
+          for (int j = 0; j < 4; j++) store(8 * j, (bf16)v[j]);
         }
       }
     }
     if (EPI == EPI_RESID && p.stat_out != nullptr) {
       // partial row statistics over this tile's 32 columns: [n tile][stat_rows (64 if not given)][2]
-      st_a += __shfl_xor(st_a, 32, 64);
-      st_b += __shfl_xor(st_b, 32, 64);
+      st_a = add_xor32(st_a);
+      st_b = add_xor32(st_b);
       if (lh == 0) {
         float* dst = p.stat_out + ((size_t)nt * (p.stat_rows > 0 ? p.stat_rows : 64) + m + p.row_offset) * 2;
         cx.st(reinterpret_cast<float2*>(dst), make_float2(st_a, st_b));
@@ -272,25 +282,40 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
 // MS = 1: the two 32-token blocks go to separate blocks (gridDim.z = 2), which halves the activation
 // bytes per CU; used where the launch would otherwise leave most CUs idle (the expert's QKV).
 // Steps ib .. ib + NSTEP - 1 of one token block's tile: the 8 waves' partial tiles [wave][token block][step][lane][4] are
-// added in wave order, then the epilogue runs on those steps.
-template <int PRO, int EPI, int NSTEP, class Cx>
-__device__ __forceinline__ void skinny_finish(const GemmParams& p, const float* red, int mb /* slot */, int lane, int nt, int ml, int lh,
-                                              float ssum, float ssq, const EpiOps& ops, const Cx& cx, int ib) {
+// added in wave order, then the epilogue runs on those steps.  stat: the 8 waves' sums of squares for this lane's row, 64
+// apart (with HALVES each in two parts, 32 apart).
+template <int PRO, int EPI, int NSTEP, bool HALVES, class Cx>
+__device__ __forceinline__ void skinny_finish(const GemmParams& p, const float* red, const float* stat, int mb /* slot */, int lane, int nt,
+                                              int ml, int lh, const EpiOps& ops, const Cx& cx, int ib) {
+  f32x4 part[SK_WAVES][NSTEP];
+  float sq[SK_WAVES][2];
+  if (PRO != PRO_NONE) {
+#pragma unroll
+    for (int ww = 0; ww < SK_WAVES; ww++) {
+      sq[ww][0] = stat[ww * 64];
+      sq[ww][1] = HALVES ? stat[ww * 64 + 32] : 0.f;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NSTEP; q++)
+#pragma unroll
+    for (int ww = 0; ww < SK_WAVES; ww++) part[ww][q] = *reinterpret_cast<const f32x4*>(red + ((((size_t)ww * 2 + mb) * 4 + ib + q) * 64 + lane) * 4);
+  __builtin_amdgcn_sched_barrier(0);   // every read in flight (left alone they are read and added one by one)
+  float ssq = 0.f;
+  if (PRO != PRO_NONE) {
+#pragma unroll
+    for (int ww = 0; ww < SK_WAVES; ww++) ssq += HALVES ? sq[ww][0] + sq[ww][1] : sq[ww][0];
+  }
   f32x16 sum;
 #pragma unroll
   for (int r = 0; r < 16; r++) sum[r] = 0.f;
-  f32x4 part[SK_WAVES][NSTEP];
 #pragma unroll
-  for (int ww = 0; ww < SK_WAVES; ww++)
+  for (int q = 0; q < NSTEP; q++)
 #pragma unroll
-    for (int q = 0; q < NSTEP; q++) part[ww][q] = *reinterpret_cast<const f32x4*>(red + ((((size_t)ww * 2 + mb) * 4 + ib + q) * 64 + lane) * 4);
-#pragma unroll
-  for (int ww = 0; ww < SK_WAVES; ww++)
-#pragma unroll
-    for (int q = 0; q < NSTEP; q++)
+    for (int ww = 0; ww < SK_WAVES; ww++)
 #pragma unroll
       for (int j = 0; j < 4; j++) sum[4 * q + j] += part[ww][q][j];
-  if (ml < p.M) epilogue_tile<PRO, EPI, 0, NSTEP>(p, sum, nt, ml, lh, ssum, ssq, cx.by, ops, cx, ib);
+  if (ml < p.M) epilogue_tile<PRO, EPI, 0, NSTEP>(p, sum, nt, ml, lh, 0.f, ssq, cx.by, ops, cx, ib);
 }
 
 template <int PRO, int EPI, int MS, class Cx>
@@ -319,7 +344,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   const int k_pad = p.W.k_pad;
   const int kbeg = cx.by * p.k_per_split;
   const int kend = min(kbeg + p.k_per_split, k_pad);
-  const int n16 = (kend - kbeg) >> 4;          // k16 steps of this block (<= 64)
+  const int n16 = (kend - kbeg) >> 4;          // k16 steps of this block (<= 64, a multiple of 4)
   const int KC16 = k_pad >> 4;
   const int XKC16 = p.ldx >> 4;
 
@@ -327,9 +352,10 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   // producer); wave w adds parts w, w+8, ... for row `lane`, the epilogue adds the 8 wave sums
   float* sstat8 = red + SK_WAVES * 2 * 16 * 64 + 128;   // [8 waves][64]
   bf16x8 wf[NTL][8], xf[NMB][8];
-  const unsigned voff = (unsigned)lane * 16u;    // a load is a uniform base plus this
-  const bf16* wbase = p.W.w + ((size_t)nt * KC16 + (kbeg >> 4)) * 512;   // tile j: + j * KC16 * 512
-  const bf16* xbase = p.X + (size_t)(kbeg >> 4) * 512;
+  // Wave w takes steps 8 w .. 8 w + 7 in two groups of 4 (a group beyond the range reads the last one and is not used).  A
+  // load is a uniform base, a 32-bit offset that is in a register before the wait, and a constant.
+  unsigned off[2] = {(unsigned)lane * 16u + (unsigned)min(w * 8, n16 - 4) * 1024u, (unsigned)lane * 16u + (unsigned)min(w * 8 + 4, n16 - 4) * 1024u};
+  const char* wbase = reinterpret_cast<const char*>(p.W.w + ((size_t)nt * KC16 + (kbeg >> 4)) * 512);   // tile j: + j * KC16 * 1024
   const int mb_last = p.M > 32 ? 1 : 0;        // last token block (clamps when M <= 32)
   const int mb_first = MS ? min(cx.bz, mb_last) : 0;   // global index of local token block 0
   // The tile of a token block is finished by PIECES waves, each taking 4 / PIECES of its four 8-feature steps
@@ -345,40 +371,61 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   const int fmb = NTL == 1 ? fslot : 0;             // its token block (local) ...
   const int fnt = nt + (NTL == 1 ? 0 : fslot);      // ... and feature tile
   const int mrow = (mb_first + fmb) * 32 + lq;   // the row this lane finishes if w < NFIN
+  const char* xbase[NMB];
+#pragma unroll
+  for (int mb = 0; mb < NMB; mb++) xbase[mb] = reinterpret_cast<const char*>(p.X + ((size_t)min(mb_first + mb, mb_last) * XKC16 + (kbeg >> 4)) * 512);
+  // Statistics partials (sums of squares; RMS needs nothing else).  Wave w adds parts w, w + 8, ... of a row, the even and
+  // the odd ones of these apart: with one token block the lane halves take one half of the parts each, so that nobody loads
+  // rows of the other block.
+  constexpr int NSP = NMB == 1 ? 4 : 8;
+  unsigned soff[NSP];
+#pragma unroll
+  for (int jj = 0; jj < NSP; jj++) {
+    const int j = min(w + SK_WAVES * (NMB == 1 ? 2 * jj + lh : jj), p.rowstat_parts - 1);   // clamped, unconditional
+    soff[jj] = PRO != PRO_NONE ? (unsigned)(j * 64 + (NMB == 1 ? mb_first * 32 + lq : lane)) * 8u + 4u : 0u;
+  }
+  // groups beyond the range: zero weights, so that the products need no branch (one in front of each costs copies of the
+  // accumulators and a wait for all operands)
+  auto load_w = [&]() {
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      if (w * 8 + 4 * h < n16) {   // uniform
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+          for (int j = 0; j < NTL; j++) wf[j][4 * h + i] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)j * KC16 * 1024 + off[h] + i * 1024);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+          for (int j = 0; j < NTL; j++) wf[j][4 * h + i] = __builtin_bit_cast(bf16x8, u32x4_t{0u, 0u, 0u, 0u});
+      }
+    }
+  };
   if (Cx::kPersistent) {
     // constants first (weights, then the epilogue's vectors); the inputs are requested once they exist
-#pragma unroll
-    for (int i = 0; i < 8; i++) {
-      const int st = min(w * 8 + i, n16 - 1);
-#pragma unroll
-      for (int j = 0; j < NTL; j++) wf[j][i] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(wbase + (size_t)(j * KC16 + st) * 512) + voff);
-    }
+    asm volatile("" : "+v"(off[0]), "+v"(off[1]));
+    load_w();
     if (w < NFIN && mrow < p.M) epilogue_preload<PRO, EPI, 0, NSTEP, 0>(p, fnt, mrow, lh, ops, cx, fpc * NSTEP);
+    if (PRO != PRO_NONE) {
+#pragma unroll
+      for (int jj = 0; jj < NSP; jj++) asm volatile("" : "+v"(soff[jj]));
+    }
+#pragma unroll
+    for (int mb = 0; mb < NMB; mb++) xbase[mb] = computed_global(xbase[mb]);
     cx.wait_inputs();
   }
-  // statistics partials (sums of squares; RMS needs nothing else): issued ahead of the operand loads (same round trip),
-  // clamped and unconditional.  Wave w adds parts w, w + 8, ... of a row, the even and the odd ones of these apart: with
-  // one token block the lane halves take one half of the parts each, so that nobody loads rows of the other block.
-  constexpr int NSP = NMB == 1 ? 4 : 8;
+  // statistics ahead of the operands (same round trip)
   float sp[NSP];
   if (PRO != PRO_NONE) {
 #pragma unroll
-    for (int jj = 0; jj < NSP; jj++) {
-      const int j = min(w + SK_WAVES * (NMB == 1 ? 2 * jj + lh : jj), p.rowstat_parts - 1);
-      sp[jj] = cx.ld_bulk(p.rowstat + ((size_t)j * 64 + (NMB == 1 ? mb_first * 32 + lq : lane)) * 2 + 1);
-    }
+    for (int jj = 0; jj < NSP; jj++) sp[jj] = cx.ld_bulk(reinterpret_cast<const float*>(reinterpret_cast<const char*>(p.rowstat) + soff[jj]));
   }
+  if (!Cx::kPersistent) load_w();
 #pragma unroll
-  for (int i = 0; i < 8; i++) {
-    const int st = min(w * 8 + i, n16 - 1);    // clamped: steps beyond the range are never used
-    if (!Cx::kPersistent) {
+  for (int i = 0; i < 8; i++)
 #pragma unroll
-      for (int j = 0; j < NTL; j++) wf[j][i] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(wbase + (size_t)(j * KC16 + st) * 512) + voff);
-    }
-#pragma unroll
-    for (int mb = 0; mb < NMB; mb++)
-      xf[mb][i] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(xbase + (size_t)(min(mb_first + mb, mb_last) * XKC16 + st) * 512) + voff));
-  }
+    for (int mb = 0; mb < NMB; mb++) xf[mb][i] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(xbase[mb] + off[i >> 2] + (i & 3) * 1024));
   // operands of the epilogue, in the same round trip
   if (w < NFIN && mrow < p.M) {
     if (Cx::kPersistent) epilogue_preload<PRO, EPI, 0, NSTEP, 1>(p, fnt, mrow, lh, ops, cx, fpc * NSTEP);
@@ -389,22 +436,9 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   for (int sl = 0; sl < NSLOT; sl++)
 #pragma unroll
     for (int r = 0; r < 16; r++) acc[sl][r] = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; i++) {
-    if (w * 8 + i < n16) {
-#pragma unroll
-      for (int sl = 0; sl < NSLOT; sl++)
-        acc[sl] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[NTL == 1 ? 0 : sl][i], xf[NTL == 1 ? sl : 0][i], acc[sl], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int sl = 0; sl < NSLOT; sl++)
-#pragma unroll
-    for (int q = 0; q < 4; q++) {   // 16-byte pieces: [wave][slot][q][lane][4]
-      const f32x4 v4 = {acc[sl][4 * q], acc[sl][4 * q + 1], acc[sl][4 * q + 2], acc[sl][4 * q + 3]};
-      *reinterpret_cast<f32x4*>(red + ((((size_t)w * 2 + sl) * 4 + q) * 64 + lane) * 4) = v4;
-    }
-  cx.mark(1);   // operands arrived, products done
+  // requests stay above, in this order: the products start with the first operands
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
   if (PRO != PRO_NONE) {
     float pe = 0.f, po = 0.f;
     if constexpr (NMB == 1) {
@@ -422,20 +456,25 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
       sstat8[w * 64 + lane] = pe + po;  // [wave][64 rows]
     }
   }
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+#pragma unroll
+    for (int sl = 0; sl < NSLOT; sl++)
+      acc[sl] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[NTL == 1 ? 0 : sl][i], xf[NTL == 1 ? sl : 0][i], acc[sl], 0, 0, 0);
+#pragma unroll
+  for (int sl = 0; sl < NSLOT; sl++)
+#pragma unroll
+    for (int q = 0; q < 4; q++) {   // 16-byte pieces: [wave][slot][q][lane][4]
+      const f32x4 v4 = {acc[sl][4 * q], acc[sl][4 * q + 1], acc[sl][4 * q + 2], acc[sl][4 * q + 3]};
+      *reinterpret_cast<f32x4*>(red + ((((size_t)w * 2 + sl) * 4 + q) * 64 + lane) * 4) = v4;
+    }
+  cx.mark(1);   // operands arrived, products done
   __syncthreads();
   cx.mark(2);   // partial tiles of all waves in LDS
   if (w >= NFIN) return;
   if (MS && cx.bz > mb_last) return;   // M <= 32: the second block of a split launch has nothing to store
   const int ml = mrow;
-  float ssq = 0.f;
-  if (PRO != PRO_NONE) {   // statistics of the lane's own row: the 8 waves' partial sums, in wave order
-    float part[SK_WAVES];
-#pragma unroll
-    for (int ww = 0; ww < SK_WAVES; ww++) part[ww] = NMB == 1 ? sstat8[ww * 64 + lq] + sstat8[ww * 64 + 32 + lq] : sstat8[ww * 64 + ml];
-#pragma unroll
-    for (int ww = 0; ww < SK_WAVES; ww++) ssq += part[ww];
-  }
-  skinny_finish<PRO, EPI, NSTEP>(p, red, fslot, lane, fnt, ml, lh, 0.f, ssq, ops, cx, fpc * NSTEP);
+  skinny_finish<PRO, EPI, NSTEP, NMB == 1>(p, red, sstat8 + (NMB == 1 ? lq : ml), fslot, lane, fnt, ml, lh, ops, cx, fpc * NSTEP);
 }
 
 template <int PRO, int EPI, int MS = 0>
@@ -474,29 +513,42 @@ __device__ __forceinline__ void gemm_skinny16_body(const GemmParams p, const Cx 
   const int mt16 = cx.by;
   const int KC16 = p.W.k_pad >> 4;
   const int XKC16 = p.ldx >> 4;
-  // a load is a uniform base plus the lane's piece (the same for weights and activations, + 256 bytes for odd tiles)
-  const unsigned piece = (unsigned)((lg >> 1) * 1024 + ((lg & 1) * 32 + li) * 16);
+  // a load is a uniform base, the lane's piece (the same for weights and activations, + 256 bytes for odd tiles) in groups of
+  // 4 steps, and a constant
+  unsigned piece[NS / 4];
+#pragma unroll
+  for (int j = 0; j < NS / 4; j++) piece[j] = (unsigned)((lg >> 1) * 1024 + ((lg & 1) * 32 + li) * 16 + j * 8192 + 4096);
+  auto at = [&](const char* base, int j) { return reinterpret_cast<const bf16x8*>(base + piece[j >> 2] + ((j & 3) * 2048 - 4096)); };
   const char* wbase = reinterpret_cast<const char*>(p.W.w + ((size_t)(nt16 >> 1) * KC16 + (size_t)w * NS * 2) * 512 + (nt16 & 1) * 128);
   const char* xbase = reinterpret_cast<const char*>(p.X + ((size_t)(mt16 >> 1) * XKC16 + (size_t)w * NS * 2) * 512 + (mt16 & 1) * 128);
   bf16x8 wf[NS], xf[NS];
   const int m = mt16 * 16 + li;
+  const int mo = m + p.row_offset;
   // operands of the epilogue (wave 0): the constants with the weights, the residual rows with the inputs
   const int n4 = nt16 * 16 + 4 * lg;
   const bool live = w == 0 && m < p.M && n4 < p.n_valid;
+  float* const dst_f32 = p.out_f32 + (size_t)mo * p.ldo + n4;
+  bf16* const dst_bf16 = p.out_bf16 + xf_index(mo, n4, p.ldo2 >> 4);
+  float2* const dst_stat = reinterpret_cast<float2*>(p.stat_out + ((size_t)nt16 * 64 + mo) * 2);   // [16-column tile][64 rows]
+  unsigned off_f32 = cx.off(dst_f32), off_bf16 = cx.off(dst_bf16), off_stat = cx.off(dst_stat);
   f32x4 rv = {0.f, 0.f, 0.f, 0.f}, gv = {1.f, 1.f, 1.f, 1.f}, bv = {0.f, 0.f, 0.f, 0.f};
   if (Cx::kPersistent) {   // constants before the wait
 #pragma unroll
-    for (int j = 0; j < NS; j++) wf[j] = *reinterpret_cast<const bf16x8*>(wbase + j * 2048 + piece);
+    for (int j = 0; j < NS / 4; j++) asm volatile("" : "+v"(piece[j]));
+#pragma unroll
+    for (int j = 0; j < NS; j++) wf[j] = *at(wbase, j);
     if (live) {
       if (p.gain != nullptr) gv = *reinterpret_cast<const f32x4*>(p.gain + n4);
       if (p.bias != nullptr) bv = *reinterpret_cast<const f32x4*>(p.bias + n4);
     }
+    xbase = computed_global(xbase);
+    asm volatile("" : "+v"(off_f32), "+v"(off_bf16), "+v"(off_stat));   // not behind the wait
     cx.wait_inputs();
   }
 #pragma unroll
   for (int j = 0; j < NS; j++) {
-    if (!Cx::kPersistent) wf[j] = *reinterpret_cast<const bf16x8*>(wbase + j * 2048 + piece);
-    xf[j] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(xbase + j * 2048 + piece));
+    if (!Cx::kPersistent) wf[j] = *at(wbase, j);
+    xf[j] = cx.ld_bulk(at(xbase, j));
   }
   // X given as attention shares over disjoint key ranges (k = 8 heads x 256, so wave w holds exactly
   // head w).  Share z carries its normalised output and (max, sum) of its exponentials; the merged
@@ -516,7 +568,7 @@ __device__ __forceinline__ void gemm_skinny16_body(const GemmParams p, const Cx 
     for (int z = 1; z < 4; z++) {
       if (z < nz) {
 #pragma unroll
-        for (int j = 0; j < NS; j++) xo[z - 1][j] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(xbase + (size_t)z * p.xsplit_stride * 2 + j * 2048 + piece));
+        for (int j = 0; j < NS; j++) xo[z - 1][j] = cx.ld_bulk(at(xbase + (size_t)z * p.xsplit_stride * 2, j));
         ml[z] = cx.ld_bulk(reinterpret_cast<const float2*>(p.xsplit_ml + (((size_t)z * SK_WAVES + w) * 64 + mrow) * 2));
       }
     }
@@ -585,26 +637,25 @@ __device__ __forceinline__ void gemm_skinny16_body(const GemmParams p, const Cx 
     for (int r = 0; r < 4; r++) v[r] = a[r] + bv[r] + rv[r];
   }
   float st_a = 0.f, st_b = 0.f;
-  const int mo = m + p.row_offset;
   if (live) {
     const f32x4 o = {v[0], v[1], v[2], v[3]};
-    cx.st(reinterpret_cast<f32x4*>(p.out_f32 + (size_t)mo * p.ldo + n4), o);
+    if (Cx::kPersistent) cx.st_off(off_f32, o);
+    else cx.st(reinterpret_cast<f32x4*>(dst_f32), o);
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       st_a += v[r];
       st_b += v[r] * v[r];
     }
     const bf16x4 ob = {(bf16)(v[0] * gv[0]), (bf16)(v[1] * gv[1]), (bf16)(v[2] * gv[2]), (bf16)(v[3] * gv[3])};
-    cx.st(reinterpret_cast<bf16x4*>(p.out_bf16 + xf_index(mo, n4, p.ldo2 >> 4)), ob);
+    if (Cx::kPersistent) cx.st_off(off_bf16, ob);
+    else cx.st(reinterpret_cast<bf16x4*>(dst_bf16), ob);
   }
-  if (p.stat_out != nullptr) {   // partial row statistics over this tile's 16 columns: [16-column tile][64 rows][2]
-    st_a += __shfl_xor(st_a, 16, 64);
-    st_b += __shfl_xor(st_b, 16, 64);
-    st_a += __shfl_xor(st_a, 32, 64);
-    st_b += __shfl_xor(st_b, 32, 64);
+  if (p.stat_out != nullptr) {   // partial row statistics over this tile's 16 columns
+    st_a = add_xor32(add_xor16(st_a));
+    st_b = add_xor32(add_xor16(st_b));
     if (lg == 0 && m < p.M) {
-      float* dst = p.stat_out + ((size_t)nt16 * 64 + mo) * 2;
-      cx.st(reinterpret_cast<float2*>(dst), make_float2(st_a, st_b));
+      if (Cx::kPersistent) cx.st_off(off_stat, make_float2(st_a, st_b));
+      else cx.st(dst_stat, make_float2(st_a, st_b));
     }
   }
 }

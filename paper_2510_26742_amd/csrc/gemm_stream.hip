@@ -228,7 +228,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W
 #pragma unroll
         for (int q = 0; q < NSTEP; q++) {
           const float* c4 = cols + (tile % NB) * 32 + 8 * (ib + q) + 4 * lh;
-          if (p.bias != nullptr) ops.bias[q] = *reinterpret_cast<const f32x4*>(c4);
+          ops.bias[q] = p.bias != nullptr ? *reinterpret_cast<const f32x4*>(c4) : f32x4{0.f, 0.f, 0.f, 0.f};
           if (PRO == PRO_LN) ops.colsum[q] = *reinterpret_cast<const f32x4*>(c4 + NB * 32);
           if (EPI == EPI_RESID && p.gain != nullptr) ops.gain[q] = *reinterpret_cast<const f32x4*>(c4 + 2 * NB * 32);
           if (EPI == EPI_RESID) ops.aux[q] = resid[v][q];
