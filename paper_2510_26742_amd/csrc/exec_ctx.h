@@ -116,7 +116,6 @@ struct GridBarrierT {
   unsigned present;     // bit x set: die x holds at least one block
   unsigned spin_limit;
   unsigned epoch;       // barriers this block has arrived at
-  unsigned waited;      // last barrier this block has seen completed
   long long* trace;     // optional: where thread 0 notes the wall clock (100 MHz) when a wait ends
 
   __device__ __forceinline__ static unsigned ld_dev(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -128,7 +127,6 @@ struct GridBarrierT {
     w = as_global(words);
     spin_limit = limit;
     epoch = 0;
-    waited = 0;
     trace = nullptr;
     xcc = (unsigned)__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7u;   // XCC_ID, bits 3:0
     __shared__ unsigned rank_s;
@@ -158,9 +156,8 @@ struct GridBarrierT {
 
   // all threads of the block, after the block's last store of the operation
   __device__ __forceinline__ void arrive() {
-    // A block with no work item in an operation does not wait for that operation's inputs; it must still see the
-    // barrier before completed, or its two arrivals in a row would be counted towards one barrier of its die.
-    if (waited != epoch) wait();
+    // A block without a work item in an operation arrives without having waited for the operation before (flags and epochs
+    // only grow, so a later epoch stands for the earlier ones too), and goes on to prefetch for the one after.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores have been acknowledged (a workgroup-scope
                                                         // fence does not wait for them)
     __syncthreads();
@@ -201,7 +198,6 @@ struct GridBarrierT {
       }
     }
     __syncthreads();
-    waited = epoch;
     if (TRACE && trace != nullptr && threadIdx.x == 0) *trace = (long long)wall_clock64();
   }
 };
