@@ -63,8 +63,6 @@ hipError_t attention_init_attributes() {
   }
   ATTN_VARIANTS(X)
 #undef X
-  if (const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_suffix_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, ATTN_SUFFIX_SMEM_MAX); e != hipSuccess)
-    return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_vision2_kernel<2>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              attn_smem<80>(8));
 }
@@ -106,7 +104,7 @@ hipError_t launch_attention(hipStream_t s, const AttnParams& p) {
     grid.y += d.blocks / grid.x;
   }
   if (suffix) {
-    attention_suffix_kernel<<<grid, dim3(512), attn_suffix_smem_bytes(n0, vs), s>>>(p);
+    attention_suffix_kernel<<<grid, dim3(512), ATTN_SUFFIX_SMEM, s>>>(p);
   } else if (p.head_dim == 256) {
     if (n0 <= 8) attention_kernel<256, 8, 1, 8, 10><<<grid, dim3(512), attn_smem<256>(ntot), s>>>(p);
     else if (n0 <= 16) attention_kernel<256, 8, 2, 8, 0><<<grid, dim3(512), attn_smem<256>(ntot), s>>>(p);

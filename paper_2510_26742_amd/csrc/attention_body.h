@@ -373,15 +373,16 @@ static constexpr int attn_smem_bytes(int ntot) { return 3 * (DQK / 16) * 1024 + 
 // in the last share, the suffix's own two chunks.  An item is 16 query rows of one head (and 1 / v_split of the head
 // dimension of the output): mfma_f32_16x16x32 throughout.
 // What bounds it in the persistent kernel is what follows the wait for the QKV projection, so everything that comes from
-// the prefix cache is in place before: wave w holds the keys of chunk w in registers, the values of the item's
-// slice of the head dimension are in LDS.  After the wait a wave fetches the 16 query rows (8 KB) straight into
-// registers, waves 4 .. 7 one 16-key tile of the suffix each, and every wave its columns of the suffix's values; then
-// scores, two LDS exchanges (row maximum, probabilities), and wave w accumulates columns 16 w .. (and 128 + 16 w .. with
-// v_split 1) over all chunks: no sum over waves.  Before, an item was 32 rows, waves 0 and 1 scored the suffix after
-// their own chunk, Q and the suffix keys went through LDS and partial outputs met in LDS: 5.0 us after the wait.
-// Probabilities: the accumulator of S^T (lane = query lane % 16, keys 4 (lane / 16) + r of a 16-key tile) gives each lane
-// keys {16 t + 4 g + r} of a chunk, which is the B operand of the second product in the key order t, r; the values are
-// read in the same order.
+// the prefix cache is in registers before: wave w holds the keys of chunk w, and of the values its own 16 columns (two
+// tiles of 16 with v_split 1) of every chunk.  After the wait each wave fetches one eighth of the 16 query rows (they
+// meet in LDS: read by every wave from memory they were 64 of the 112 KB that the first-level cache, 64 bytes per clock,
+// handed out behind the wait), waves 4 .. 7 one 16-key tile of the suffix each, and every wave its columns of the
+// suffix's values; then scores, two LDS exchanges (row maximum, probabilities), and a wave accumulates its columns over
+// all chunks: no sum over waves.  Chunks that a share does not have count as zero probabilities and values, so the
+// products have no branches between them.
+// Order of the keys inside a chunk: row i of 16-key tile t is key 16 (i / 8) + 8 t + i % 8 of the chunk.  The accumulator
+// of S^T (lane = query lane % 16, rows 4 (lane / 16) + r of a tile) then gives each lane 8 keys that are one 16-byte piece
+// of the value fragments, which makes them the B operand of the second product as they are.
 // ------------------------------------------------------------------------------------------------
 template <class Cx>
 __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const Cx cx, unsigned char* smem_raw) {
@@ -409,72 +410,96 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
     if (cx.bz != p.key_splits - 1) n1 = 0;
   }
   const int nvb = 8 / vs;                      // 32-wide value slices of this item
-  bf16* vlds = reinterpret_cast<bf16*>(smem_raw);                             // [n0][nvb][2][64][8]
-  bf16* pf = vlds + (size_t)n0 * nvb * 1024;                                  // [n0 + 2][64][8]
-  float* mw = reinterpret_cast<float*>(pf + (size_t)(n0 + 2) * 512);          // [8][16]
+  const int ntiles = 2 * nvb;                  // 16-column tiles of this item; this wave's are w and w + 8
+  bf16* qlds = reinterpret_cast<bf16*>(smem_raw);                             // [8 steps of 32 k][64][8]
+  bf16* pf = qlds + 8 * 512;                                                  // [8 + 2 chunks][64][8]
+  float* mw = reinterpret_cast<float*>(pf + (ATT_WAVES + 2) * 512);           // [8][16]
   float* lw = mw + ATT_WAVES * 16;                                            // [8][16]
-  // a 16-row operand of 32 k is half of two 32 x 16 fragments: lane (g, i) takes k = 8 g .. + 7 of row i
-  const unsigned piece = (unsigned)((g >> 1) * 1024 + ((g & 1) * 32 + qi) * 16);   // bytes; + 2 KiB per 32 k, + 256 for the odd 16-row tile
-  auto frag = [&](const bf16* base, int j) { return reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(base + (size_t)j * 1024) + piece); };
+  const bf16x8 zero8 = __builtin_bit_cast(bf16x8, u32x4_t{0u, 0u, 0u, 0u});
+  // a 16-row operand of 32 k is half of two 32 x 16 fragments: lane (g, i) takes k = 8 g .. + 7 of row i (bytes; + 2 KiB per 32 k)
+  const unsigned qpiece = (unsigned)((g >> 1) * 1024 + ((g & 1) * 32 + qi) * 16);                              // + 256 for the odd 16-row tile
+  const unsigned kpiece = (unsigned)((g >> 1) * 1024 + ((g & 1) * 32 + (qi >> 3) * 16 + (qi & 7)) * 16);       // + 128 for tile 1
+  const unsigned vpiece = (unsigned)((g >> 1) * 1024 + (g & 1) * 512 + qi * 16);                              // + 256 for the odd 16-column tile
+  auto at = [](const char* base, unsigned off) { return reinterpret_cast<const bf16x8*>(base + off); };
+  auto vtile = [&](const bf16* v, int dt) {    // values of chunk 0, 16-column tile dt of this item
+    return reinterpret_cast<const char*>(v + (size_t)(vpart * nvb + (dt >> 1)) * 1024 + (dt & 1) * 128);
+  };
 
-  // ---- constants of the persistent kernel: keys to registers, values to LDS --------------------------
-  bf16x8 kf[2][8];
+  // ---- constants of the persistent kernel: keys and values of the prefix -------------------------------
+  bf16x8 kf[2][8], vf[2][ATT_WAVES];
   auto load_prefix = [&]() {
-    const bf16* kp = p.k0 + (size_t)(cbeg0 + min(w, n0 - 1)) * S16 * 512;
+    if (w < n0) {   // uniform
+      const char* kp = reinterpret_cast<const char*>(p.k0 + (size_t)(cbeg0 + w) * S16 * 512);
 #pragma unroll
-    for (int j = 0; j < 8; j++)
+      for (int j = 0; j < 8; j++)
 #pragma unroll
-      for (int h = 0; h < 2; h++) kf[h][j] = *frag(kp + h * 128, j);
-    // 16-byte pieces: 128 nvb of each chunk's 1024; 8 in flight per lane (4 KB, at most two batches)
-    const bf16* vsrc = p.v0 + (size_t)cbeg0 * 8 * 1024 + (size_t)vpart * nvb * 1024;
-    const int sh = vs == 1 ? 10 : vs == 2 ? 9 : vs == 4 ? 8 : 7, total = n0 << sh;
-    for (int i0 = t; i0 < total; i0 += 8 * 512) {
-      bf16x8 v[8];
+        for (int h = 0; h < 2; h++) kf[h][j] = *at(kp, kpiece + h * 128 + j * 2048);
+    } else {
 #pragma unroll
-      for (int j = 0; j < 8; j++) {
-        const int i = min(i0 + j * 512, total - 1);            // clamped, unconditional
-        v[j] = *reinterpret_cast<const bf16x8*>(vsrc + (size_t)(i >> sh) * 8 * 1024 + (size_t)(i & ((1 << sh) - 1)) * 8);
-      }
+      for (int j = 0; j < 8; j++) kf[0][j] = kf[1][j] = zero8;
+    }
 #pragma unroll
-      for (int j = 0; j < 8; j++) {
-        if (i0 + j * 512 < total) *reinterpret_cast<bf16x8*>(vlds + (size_t)(i0 + j * 512) * 8) = v[j];
+    for (int a = 0; a < 2; a++) {
+      const char* vp = vtile(p.v0 + (size_t)cbeg0 * 8 * 1024, w + ATT_WAVES * a);
+#pragma unroll
+      for (int c = 0; c < ATT_WAVES; c++) {
+        if (c < n0 && w + ATT_WAVES * a < ntiles) vf[a][c] = *at(vp + (size_t)c * 16384, vpiece);   // uniform
+        else vf[a][c] = zero8;
       }
     }
   };
+  const bool seg1_wave = n1 > 0 && w >= 4;
+  const int tile1 = w - 4;
+  const char* qsrc = reinterpret_cast<const char*>(p.q + (size_t)head * p.q_head_stride + (size_t)(qt >> 1) * S16 * 512 + (qt & 1) * 128 + w * 1024);
+  const char* k1src = reinterpret_cast<const char*>(p.k1 + (size_t)(max(tile1, 0) >> 1) * S16 * 512 + (tile1 & 1) * 64);
+  const char* v1src[2] = {vtile(p.v1, min(w, ntiles - 1)), vtile(p.v1, min(w + ATT_WAVES, ntiles - 1))};
+  // where the results go
+  bf16* outp[2];
+  unsigned off_out[2];
+#pragma unroll
+  for (int a = 0; a < 2; a++) {
+    const int col = head * 256 + vpart * nvb * 32 + (w + ATT_WAVES * a) * 16 + 4 * g;
+    outp[a] = p.out + (size_t)cx.bz * p.out_split_stride + ((size_t)(row >> 5) * (p.out_ld >> 4) + (col >> 4)) * 512 +
+              (((col & 15) >> 3) * 32 + (row & 31)) * 8 + (col & 7);
+    off_out[a] = cx.off(outp[a]);
+  }
   if (Cx::kPersistent) {
     load_prefix();
+    qsrc = computed_global(qsrc);
+    k1src = computed_global(k1src);
+    v1src[0] = computed_global(v1src[0]);
+    v1src[1] = computed_global(v1src[1]);
+    asm volatile("" : "+v"(off_out[0]), "+v"(off_out[1]));
     cx.wait_inputs();
   }
   // ---- inputs: query rows, suffix keys (waves 4 .. 7: 16-key tile w - 4), suffix values ---------------
-  bf16x8 qf[8], k1f[8];
-  bf16x4 v1f[2][2][2];                         // [column tile][chunk][16-key half]
-  const bf16* qsrc = p.q + (size_t)head * p.q_head_stride + (size_t)(qt >> 1) * S16 * 512 + (qt & 1) * 128;
-#pragma unroll
-  for (int j = 0; j < 8; j++) qf[j] = cx.ld_bulk(frag(qsrc, j));
-  const bool seg1_wave = n1 > 0 && w >= 4;
-  const int tile1 = w - 4;
+  bf16x8 k1f[8], v1f[2][2];                    // v1f: [column tile][chunk]
+  const bf16x8 qv = cx.ld_bulk(at(qsrc, qpiece));
   if (seg1_wave) {
-    const bf16* kp = p.k1 + (size_t)(tile1 >> 1) * S16 * 512 + (tile1 & 1) * 128;
 #pragma unroll
-    for (int j = 0; j < 8; j++) k1f[j] = cx.ld_bulk(frag(kp, j));
+    for (int j = 0; j < 8; j++) k1f[j] = cx.ld_bulk(at(k1src, kpiece + j * 2048));
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; j++) k1f[j] = zero8;
   }
-  const int ntiles = 2 * nvb;                  // 16-column tiles of this item; this wave's are w and w + 8
-  if (n1 > 0) {
 #pragma unroll
-    for (int a = 0; a < 2; a++) {
-      const int dt = min(w + ATT_WAVES * a, ntiles - 1);
-      const bf16* vp = p.v1 + (size_t)(vpart * nvb + (dt >> 1)) * 1024 + ((g & 1) * 32 + (dt & 1) * 16 + qi) * 8 + (g >> 1) * 4;
+  for (int a = 0; a < 2; a++)
 #pragma unroll
-      for (int c = 0; c < 2; c++)
-#pragma unroll
-        for (int h = 0; h < 2; h++)
-          if (a == 0 || vs == 1) v1f[a][c][h] = cx.ld_bulk(reinterpret_cast<const bf16x4*>(vp + (size_t)c * 8 * 1024 + h * 512));
+    for (int c = 0; c < 2; c++) {
+      if (n1 > 0 && (a == 0 || vs == 1)) v1f[a][c] = cx.ld_bulk(at(v1src[a] + c * 16384, vpiece));
+      else v1f[a][c] = zero8;
     }
-  }
   if (!Cx::kPersistent) load_prefix();
-  cx.mark(1);   // inputs requested
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);   // all requested before the first one is waited for
+  cx.mark(1);
+  *reinterpret_cast<bf16x8*>(qlds + ((size_t)w * 64 + lane) * 8) = qv;
+  __syncthreads();
 
   // ---- scores ---------------------------------------------------------------------------------------
+  bf16x8 qf[8];
+#pragma unroll
+  for (int j = 0; j < 8; j++) qf[j] = *reinterpret_cast<const bf16x8*>(qlds + ((size_t)j * 64 + lane) * 8);
   f32x4 sv[2], sv1, sodd[2], sodd1;   // even and odd k steps apart: half the dependent chain
 #pragma unroll
   for (int h = 0; h < 2; h++) sv[h] = sodd[h] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -487,51 +512,55 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
       sodd[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[h][j + 1], qf[j + 1], sodd[h], 0, 0, 0);
     }
   }
-  if (seg1_wave) {
+  __builtin_amdgcn_sched_barrier(0);   // the suffix keys are not waited for above
 #pragma unroll
-    for (int j = 0; j < 8; j += 2) {
-      sv1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1f[j], qf[j], sv1, 0, 0, 0);
-      sodd1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1f[j + 1], qf[j + 1], sodd1, 0, 0, 0);
-    }
-    sv1 += sodd1;
+  for (int j = 0; j < 8; j += 2) {
+    sv1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1f[j], qf[j], sv1, 0, 0, 0);
+    sodd1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1f[j + 1], qf[j + 1], sodd1, 0, 0, 0);
   }
 #pragma unroll
-  for (int h = 0; h < 2; h++) sv[h] += sodd[h];
-  float m_loc = NEG_BIG;
+  for (int h = 0; h < 2; h++) sv[h] = (sv[h] + sodd[h]) * p.scale;
+  sv1 = (sv1 + sodd1) * p.scale;
+  const int kg = 16 * (g >> 1) + 4 * (g & 1);   // first of this lane's keys in a chunk; + 8 for tile 1
+  if (w >= n0 || (cbeg0 + w + 1) * 32 > p.valid0) {   // uniform: no chunk, or one with keys beyond the last
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) sv[h][e] = w < n0 && (cbeg0 + w) * 32 + kg + 8 * h + e < p.valid0 ? sv[h][e] : NEG_BIG;
+  }
+  if (!seg1_wave) {   // uniform
+    sv1 = f32x4{NEG_BIG, NEG_BIG, NEG_BIG, NEG_BIG};
+  } else if (p.suffix_mask) {
+#pragma unroll
+    for (int e = 0; e < 4; e++) sv1[e] = row != 0 || (tile1 >> 1) * 32 + kg + 8 * (tile1 & 1) + e == 0 ? sv1[e] : NEG_BIG;
+  }
+  float m_loc = fmaxf(fmaxf(fmaxf(sv1[0], sv1[1]), fmaxf(sv1[2], sv1[3])), NEG_BIG);
 #pragma unroll
   for (int h = 0; h < 2; h++)
 #pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const int key = (cbeg0 + w) * 32 + h * 16 + 4 * g + e;
-      sv[h][e] = w < n0 && key < p.valid0 ? sv[h][e] * p.scale : NEG_BIG;
-      m_loc = fmaxf(m_loc, sv[h][e]);
-    }
-  if (seg1_wave) {
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const int key = tile1 * 16 + 4 * g + e;
-      const bool valid = !p.suffix_mask || row != 0 || key == 0;
-      sv1[e] = valid ? sv1[e] * p.scale : NEG_BIG;
-      m_loc = fmaxf(m_loc, sv1[e]);
-    }
-  }
-  m_loc = max_xor16(m_loc);
-  m_loc = max_xor32(m_loc);
+    for (int e = 0; e < 4; e++) m_loc = fmaxf(m_loc, sv[h][e]);
+  m_loc = max_xor32(max_xor16(m_loc));
   if (g == 0) mw[w * 16 + qi] = m_loc;
   __syncthreads();
   cx.mark(2);   // scores done
+  float m_part[ATT_WAVES];
+#pragma unroll
+  for (int i = 0; i < ATT_WAVES; i++) m_part[i] = mw[i * 16 + qi];
+  __builtin_amdgcn_sched_barrier(0);
   float m_all = NEG_BIG;
 #pragma unroll
-  for (int i = 0; i < ATT_WAVES; i++) m_all = fmaxf(m_all, mw[i * 16 + qi]);
+  for (int i = 0; i < ATT_WAVES; i++) m_all = fmaxf(m_all, m_part[i]);
 
   // ---- probabilities -> B operand of the second product, in LDS ---------------------------------------
+  // Masked keys come out as exactly 0: far below any maximum, or (a row without a key) below half of the mask value
+  const float m_sub = fmaxf(m_all, 0.5f * NEG_BIG);
   float l_loc = 0.f;
   auto prob = [&](float v) {
-    const float e = v > 0.5f * NEG_BIG ? __expf(v - m_all) : 0.f;   // masked keys: exactly 0
+    const float e = __expf(v - m_sub);
     l_loc += e;
     return e;
   };
-  if (w < n0) {
+  {
     bf16x8 pb;
 #pragma unroll
     for (int h = 0; h < 2; h++)
@@ -539,87 +568,60 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
       for (int e = 0; e < 4; e++) pb[4 * h + e] = (bf16)prob(sv[h][e]);
     *reinterpret_cast<bf16x8*>(pf + ((size_t)w * 64 + lane) * 8) = pb;
   }
-  if (seg1_wave) {
+  if (w >= 4) {   // uniform
     bf16x4 pb;
 #pragma unroll
     for (int e = 0; e < 4; e++) pb[e] = (bf16)prob(sv1[e]);
-    *reinterpret_cast<bf16x4*>(pf + ((size_t)(n0 + (tile1 >> 1)) * 64 + lane) * 8 + (tile1 & 1) * 4) = pb;
+    *reinterpret_cast<bf16x4*>(pf + ((size_t)(ATT_WAVES + (tile1 >> 1)) * 64 + lane) * 8 + (tile1 & 1) * 4) = pb;
   }
-  l_loc = add_xor16(l_loc);
-  l_loc = add_xor32(l_loc);
+  l_loc = add_xor32(add_xor16(l_loc));
   if (g == 0) lw[w * 16 + qi] = l_loc;
   __syncthreads();
   cx.mark(3);   // probabilities in LDS
   if (w >= ntiles) return;
 
   // ---- output columns: O^T tile = V^T P^T over all chunks, two chains per tile ------------------------
+  bf16x8 b[ATT_WAVES + 2];
+#pragma unroll
+  for (int c = 0; c < ATT_WAVES + 2; c++) b[c] = *reinterpret_cast<const bf16x8*>(pf + ((size_t)c * 64 + lane) * 8);
+  float l_part[ATT_WAVES];
+#pragma unroll
+  for (int i = 0; i < ATT_WAVES; i++) l_part[i] = lw[i * 16 + qi];
+  __builtin_amdgcn_sched_barrier(0);   // every read in flight
   f32x4 o[2][2];
 #pragma unroll
   for (int a = 0; a < 2; a++)
 #pragma unroll
-    for (int b = 0; b < 2; b++) o[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto lds_v = [&](int c, int dt) {
-    const bf16* vp = vlds + ((size_t)c * nvb + (dt >> 1)) * 1024 + ((g & 1) * 32 + (dt & 1) * 16 + qi) * 8 + (g >> 1) * 4;
-    const bf16x4 lo = *reinterpret_cast<const bf16x4*>(vp), hi = *reinterpret_cast<const bf16x4*>(vp + 512);
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  };
-  for (int c0 = 0; c0 < n0; c0 += 4) {
-    bf16x8 b[4], va[2][4];
+    for (int c = 0; c < 2; c++) o[a][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int c = min(c0 + j, n0 - 1);
-      b[j] = *reinterpret_cast<const bf16x8*>(pf + ((size_t)c * 64 + lane) * 8);
-      va[0][j] = lds_v(c, w);
-      if (vs == 1) va[1][j] = lds_v(c, w + ATT_WAVES);
-    }
+  for (int c = 0; c < ATT_WAVES + 2; c++)
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-      if (c0 + j < n0) {   // uniform
-        o[0][j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[0][j], b[j], o[0][j & 1], 0, 0, 0);
-        if (vs == 1) o[1][j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[1][j], b[j], o[1][j & 1], 0, 0, 0);
-      }
-    }
-  }
-  if (n1 > 0) {
-#pragma unroll
-    for (int c = 0; c < 2; c++) {
-      const bf16x8 b = *reinterpret_cast<const bf16x8*>(pf + ((size_t)(n0 + c) * 64 + lane) * 8);
-#pragma unroll
-      for (int a = 0; a < 2; a++) {
-        if (a == 0 || vs == 1)
-          o[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_shufflevector(v1f[a][c][0], v1f[a][c][1], 0, 1, 2, 3, 4, 5, 6, 7), b, o[a][c], 0, 0, 0);
-      }
-    }
-  }
+    for (int a = 0; a < 2; a++)
+      o[a][c & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c < ATT_WAVES ? vf[a][c] : v1f[a][c - ATT_WAVES], b[c], o[a][c & 1], 0, 0, 0);
   cx.mark(4);   // P V done
   float l_all = 0.f;
 #pragma unroll
-  for (int i = 0; i < ATT_WAVES; i++) l_all += lw[i * 16 + qi];
+  for (int i = 0; i < ATT_WAVES; i++) l_all += l_part[i];
   const float inv = 1.0f / l_all;
   if (row >= p.Tq) return;
   if (p.ml_out != nullptr && w == 0 && g == 0 && vpart == 0) {   // (row maximum, sum) of this share, for the consumer's merge
     float* dst = p.ml_out + ((((size_t)cx.bz * p.heads + head) * ((p.Tq + 31) >> 5) * 32) + row) * 2;
     cx.st(reinterpret_cast<float2*>(dst), make_float2(m_all, l_all));
   }
-  bf16* outp = p.out + (size_t)cx.bz * p.out_split_stride;
 #pragma unroll
   for (int a = 0; a < 2; a++) {
     if (a == 0 || vs == 1) {
-      const int col = head * 256 + vpart * nvb * 32 + (w + ATT_WAVES * a) * 16 + 4 * g;
       bf16x4 ob;
 #pragma unroll
       for (int e = 0; e < 4; e++) ob[e] = (bf16)((o[a][0][e] + o[a][1][e]) * inv);
-      cx.st(reinterpret_cast<bf16x4*>(outp + ((size_t)(row >> 5) * (p.out_ld >> 4) + (col >> 4)) * 512 +
-                                      (((col & 15) >> 3) * 32 + (row & 31)) * 8 + (col & 7)), ob);
+      if (Cx::kPersistent) cx.st_off(off_out[a], ob);
+      else cx.st(reinterpret_cast<bf16x4*>(outp[a]), ob);
     }
   }
 }
 
-// values of n0 chunks, probabilities, row maxima and sums
-static constexpr int attn_suffix_smem_bytes(int n0, int v_split) {
-  return n0 * (8 / (v_split > 1 ? v_split : 1)) * 2048 + (n0 + 2) * 1024 + 2 * ATT_WAVES * 16 * 4;
-}
-static constexpr int ATTN_SUFFIX_SMEM_MAX = attn_suffix_smem_bytes(8, 1);
+// query rows, probabilities, row maxima and sums
+static constexpr int ATTN_SUFFIX_SMEM = 8 * 1024 + (ATT_WAVES + 2) * 1024 + 2 * ATT_WAVES * 16 * 4;
 // shapes attention_suffix_body covers: n0 = prefix chunks per share
 static inline bool attn_suffix_ok(const AttnParams& p, int n0) {
   const int vs = p.v_split > 1 ? p.v_split : 1;

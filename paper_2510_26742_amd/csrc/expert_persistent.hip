@@ -330,7 +330,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
 
 int expert_loop_smem_bytes() {
   const int sk = (SK_WAVES * 2 * 16 * 64 + 128 + SK_WAVES * 128) * 4;
-  const int at = ATTN_SUFFIX_SMEM_MAX;
+  const int at = ATTN_SUFFIX_SMEM;
   return sk > at ? sk : at;
 }
 
