@@ -482,6 +482,13 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
 #pragma unroll
     for (int j = 0; j < 8; j++) k1f[j] = zero8;
   }
+  if (!Cx::kPersistent) load_prefix();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);   // all requested before the first one is waited for
+  cx.mark(1);
+  *reinterpret_cast<bf16x8*>(qlds + ((size_t)w * 64 + lane) * 8) = qv;
+  __syncthreads();
+  // the suffix's values come last: in front of the keys' requests they would delay the scores
 #pragma unroll
   for (int a = 0; a < 2; a++)
 #pragma unroll
@@ -489,12 +496,8 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
       if (n1 > 0 && (a == 0 || vs == 1)) v1f[a][c] = cx.ld_bulk(at(v1src[a] + c * 16384, vpiece));
       else v1f[a][c] = zero8;
     }
-  if (!Cx::kPersistent) load_prefix();
   asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);   // all requested before the first one is waited for
-  cx.mark(1);
-  *reinterpret_cast<bf16x8*>(qlds + ((size_t)w * 64 + lane) * 8) = qv;
-  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
 
   // ---- scores ---------------------------------------------------------------------------------------
   bf16x8 qf[8];

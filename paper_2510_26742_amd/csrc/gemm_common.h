@@ -362,7 +362,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   // (finishing wave f: token block f / PIECES, piece f % PIECES): the sum over the 8 waves' partial tiles and the
   // epilogue arithmetic are the tail of the launch, and one wave alone took 3.8 k cycles over them for the QKV
   // epilogue (2.2 k for GeGLU)
-  constexpr int PIECES = EPI == EPI_QKV ? 4 : EPI == EPI_GEGLU ? 2 : 1;
+  constexpr int PIECES = EPI == EPI_QKV || EPI == EPI_EULER ? 4 : EPI == EPI_GEGLU ? 2 : 1;
   constexpr int NFIN = NSLOT * PIECES, NSTEP = 4 / PIECES;
   static_assert(NFIN <= SK_WAVES, "finishing waves");
   static_assert(PRO != PRO_LN, "the statistics are sums of squares");
