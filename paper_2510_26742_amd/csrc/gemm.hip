@@ -357,6 +357,7 @@ int gemm_rows_per_tile(int tile) {
     case TILE_T192: return 192;
     case TILE_MID2: return 64;
     case TILE_STREAM: return 64;
+    case TILE_LDS: return 256;
     default: return -1;
   }
 }
@@ -462,6 +463,7 @@ static bool prefetch_ok(const PrefetchDesc& d) {
 
 hipError_t launch_gemm(hipStream_t s, int tile, int pro, int epi, const GemmParams& p, int z_splits) {
   if (tile == TILE_STREAM) return z_splits == 1 ? launch_gemm_stream(s, pro, epi, p) : hipErrorInvalidValue;
+  if (tile == TILE_LDS) return launch_gemm_lds(s, pro, epi, p, z_splits);
   // Host-side shape checks: everything the kernel's indexing assumes.
   if (!prefetch_ok(p.pf)) return hipErrorInvalidValue;
   if (p.pf.blocks != 0 && ((tile != TILE_SKINNY && tile != TILE_SKINNY_FULLK && tile != TILE_SKINNY16) || z_splits != 1)) return hipErrorInvalidValue;

@@ -353,8 +353,10 @@ struct Tune {
   int vis = -1;           // vision patch / projector (and QKV / up unless overridden below)
   int vqkv = -1, vup = -1; // vision QKV / up (-1: same as vis)
   int lqkv = -1;          // prefix QKV
-  int lgu = -1;           // prefix gate||up (-1: 128, 192 or 256 tokens x 256 features, whichever fills the 256 CUs at the least cost)
-  int vo = -1, vd = -1, lo = -1, ld = TILE_WIDE128;   // tile of vision O / down, prefix O as split-K partial GEMMs; prefix down
+  // prefix gate||up and down (ld): -1 = TILE_LDS (gemm_tile.hip) where the contraction is a multiple of 128, else gate||up
+  // 128, 192 or 256 tokens x 256 features, whichever fills the 256 CUs at the least cost, and down 128 x 256
+  int lgu = -1;
+  int vo = -1, vd = -1, lo = -1, ld = -1;   // tile of vision O / down, prefix O as split-K partial GEMMs; prefix down
   int zvo = -1, zlo = -1, zld = -1, zvd = -1;   // their split counts (-1: chosen from the number of tokens)
   // warm-up blocks carried by the expert's launches (0 = none): QKV, attention, O, down.  Used instead of the read-ahead
   // kernel below with ras=0
@@ -712,7 +714,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   // height, so a choice costs height x rounds on 256 compute units; take the cheapest, the taller tile on ties
   // (fewer operand bytes per CU and flop).  256 / 512 / 768 / 816 tokens -> 128 / 256 / 192 / 256.
   const int gu_cols = ceil_div(w.llm[0].gu.n_pad, 256);
-  int tlgu = T.lgu;
+  int tlgu = T.lgu >= 0 ? T.lgu : gemm_lds_ok(w.llm[0].gu.k_pad) ? TILE_LDS : -1;
   if (tlgu < 0) {
     const int heights[3] = {128, 192, 256}, ids[3] = {TILE_WIDE128, TILE_T192, TILE_WIDE};
     int best = 0;
@@ -721,9 +723,15 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
       if (tlgu < 0 || cost <= best) { best = cost; tlgu = ids[i]; }
     }
   }
-  // down: as many k slices as keep all blocks in one round (measured optima 16 / 8 / 5 at 256 / 512 / 768 tokens)
-  const int down_tiles = ceil_div(P, gemm_rows_per_tile(T.ld)) * ceil_div(w.llm[0].down.n_pad, T.ld == TILE_WIDE || T.ld == TILE_WIDE128 || T.ld == TILE_T192 ? 256 : 128);
-  const int zld = T.zld > 0 ? T.zld : std::max(1, std::min(16, 256 / std::max(1, down_tiles)));
+  // down: TILE_LDS knows its best number of k ranges; otherwise as many as keep all blocks in one round (measured optima
+  // 16 / 8 / 5 at 256 / 512 / 768 tokens)
+  const WsTr& L0 = w.llm[0];
+  const int tld = T.ld >= 0 ? T.ld : gemm_lds_ok(L0.down.k_pad) ? TILE_LDS : TILE_WIDE128;
+  const int down_tiles = ceil_div(P, gemm_rows_per_tile(tld)) * ceil_div(L0.down.n_pad, tld == TILE_WIDE || tld == TILE_WIDE128 || tld == TILE_T192 ? 256 : 128);
+  const int zld_rule = tld == TILE_LDS ? gemm_lds_splits(P, L0.down.n_pad / 32, L0.down.k_pad, 16) : std::max(1, std::min(16, 256 / std::max(1, down_tiles)));
+  // the k range of a slice: a multiple of 64, for TILE_LDS of 128 (and then no slice empty)
+  const int kps_ld = round_up(ceil_div(L0.down.k_pad, T.zld > 0 ? T.zld : zld_rule), tld == TILE_LDS ? 128 : 64);
+  const int zld = tld == TILE_LDS ? ceil_div(L0.down.k_pad, kps_ld) : T.zld > 0 ? T.zld : zld_rule;
   for (int l = 0; l < d.Ll; l++) {
     const WsTr& L = w.llm[l];
     const bool last = l == d.Ll - 1;
@@ -831,9 +839,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     }
     // B5: down + residual
     r.cls = PI0_OP_LLM_DOWN;
-    gemm_splitk_resid(r, L.down, at<bf16>(c, w.lmid), d.F, P, d.F, zld,
-                      round_up(ceil_div(L.down.k_pad, zld), 64), nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b),
-                      d.E, T.ld, at<float>(c, w.lstat), at<float>(c, w.g_l1[l + 1]));
+    gemm_splitk_resid(r, L.down, at<bf16>(c, w.lmid), d.F, P, d.F, zld, kps_ld, nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b),
+                      d.E, tld, at<float>(c, w.lstat), at<float>(c, w.g_l1[l + 1]));
     lplanes = 0;
     if (taps) taps->put(r, at<float>(c, w.lx), (size_t)P * d.E);
   }
@@ -1601,6 +1608,8 @@ int pi0_load_weights(pi0_ctx* c, const void* d_blob, size_t blob_bytes, void* d_
     e = gemm_init_attributes();
     if (e != hipSuccess) return fail_hip(c, e);
     e = gemm_stream_init_attributes();
+    if (e != hipSuccess) return fail_hip(c, e);
+    e = gemm_lds_init_attributes();
     if (e != hipSuccess) return fail_hip(c, e);
     e = attention_init_attributes();
     if (e != hipSuccess) return fail_hip(c, e);

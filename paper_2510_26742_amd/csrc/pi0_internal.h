@@ -173,6 +173,7 @@ enum GemmTile {
   TILE_SQ128 = 9,         // 128 tokens x 128 features per block (4 waves), 5 stages: the mid-size GEMMs at three views
   TILE_T192 = 10,         // 192 tokens x 256 features per block, 2 stages: 768 tokens in four tiles
   TILE_MID2 = 11,         // 64 tokens x 128 features as TILE_MID, cut for two resident blocks per compute unit
+  TILE_LDS = 13,          // the prefix's gate||up and down, k ranges in multiples of 128 (gemm_tile.hip); tile from the shape
   TILE_STREAM = 12        // whole k range, split over the waves of a block (gemm_stream.hip); the tile follows from the shape
 };
 
@@ -230,6 +231,10 @@ int gemm_rows_per_tile(int tile);
 // the mid-size GEMMs of the vision tower and the prefix over the whole k range (gemm_stream.hip); the tile is chosen from
 // the shape.  (pro, epi): LN / RMS with QKV, LN with BF16, none / LN with RESID
 hipError_t launch_gemm_stream(hipStream_t s, int pro, int epi, const GemmParams& p);
+hipError_t launch_gemm_lds(hipStream_t s, int pro, int epi, const GemmParams& p, int z_splits);
+bool gemm_lds_ok(int k_pad);                                             // TILE_LDS takes this contraction
+int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max);           // k ranges of a split-K launch
+hipError_t gemm_lds_init_attributes();
 hipError_t gemm_stream_init_attributes();
 // out[m] = (sum, sum of squares) of row m from partial statistics [planes][stat_rows][2]
 hipError_t launch_row_sums(hipStream_t s, const float* parts, int planes, int stat_rows, int M, float* out);
