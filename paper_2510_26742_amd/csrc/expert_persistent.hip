@@ -117,8 +117,14 @@ __device__ __forceinline__ AttnParams global(const AttnParams& src) {
   return p;
 }
 
-__global__ void expert_loop_params_kernel(ExpertLoopParams P, ExpertLoopParams* dst) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *dst = P;
+// parameter block to device memory and barrier words to zero (the error word, first, stays as it is).  A piece per thread,
+// both in one launch: the block copied by one thread took 7 us and the words a launch of their own.
+constexpr int PREP_THREADS = 256;
+static_assert(sizeof(ExpertLoopParams) % 4 == 0 && (GB_WORDS - GB_START) % 4 == 0, "whole pieces");
+__global__ __launch_bounds__(PREP_THREADS) void expert_loop_prepare_kernel(ExpertLoopParams P, ExpertLoopParams* dst, unsigned* sync) {
+  const unsigned i = blockIdx.x * PREP_THREADS + threadIdx.x;
+  if (i < sizeof(ExpertLoopParams) / 4) reinterpret_cast<unsigned*>(dst)[i] = reinterpret_cast<const unsigned*>(&P)[i];
+  if (i < (GB_WORDS - GB_START) / 4) reinterpret_cast<uint4*>(sync + GB_START)[i] = uint4{0u, 0u, 0u, 0u};
 }
 
 template <bool TRACE>
@@ -352,10 +358,10 @@ hipError_t expert_loop_max_blocks_per_cu(int* out) {
   return e;
 }
 
-// Host-side checks of everything the kernel's indexing assumes; the caller has zeroed the barrier words.
+// Host-side checks of everything the kernel's indexing assumes.
 hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLoopParams* d_params, int blocks) {
   if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0) return hipErrorInvalidValue;
-  if (blocks < 1 || blocks > GB_MAX_BLOCKS || P.sync == nullptr || P.arena == nullptr || P.arena_bytes == 0 || P.spin_limit == 0)
+  if (blocks < 1 || blocks > GB_MAX_BLOCKS || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.arena == nullptr || P.arena_bytes == 0 || P.spin_limit == 0)
     return hipErrorInvalidValue;
   if (P.layers < 1 || P.steps < 1 || P.x_elems < 1 || P.noise == nullptr || P.emb.x_rw == nullptr)
     return hipErrorInvalidValue;
@@ -411,7 +417,8 @@ hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLo
   if (P.stok.sd < 1 || P.stok.sd > 32) return hipErrorInvalidValue;
   if (P.ring == nullptr || P.ring_stride % 256 != 0 || !in_arena(P.ring, P.ring_stride * (size_t)P.layers * P.steps)) return hipErrorInvalidValue;
   if (P.r_mid >= P.ring_stride || P.r_attn >= P.ring_stride) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(expert_loop_params_kernel, dim3(1), dim3(64), 0, s, P, d_params);
+  constexpr int pieces = (int)sizeof(ExpertLoopParams) / 4 > (GB_WORDS - GB_START) / 4 ? (int)sizeof(ExpertLoopParams) / 4 : (GB_WORDS - GB_START) / 4;
+  hipLaunchKernelGGL(expert_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, P.sync);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (P.trace != nullptr) hipLaunchKernelGGL(expert_loop_kernel<true>, dim3(blocks), dim3(PK_THREADS), expert_loop_smem_bytes(), s, d_params);

@@ -1034,11 +1034,9 @@ bool run_denoise_persistent(Run& r, int P) {
   E.trace = c->loop_trace;
   E.trace_ops = c->loop_trace_ops;
   r.cls = PI0_OP_MISC;
-  // barrier words restart at zero (the error word, first, stays as it is)
-  RUN(r, launch_fill_zero(r.s, at<unsigned>(c, w.esync) + GB_START, (size_t)(GB_WORDS - GB_START) * 4));
   if (r.ok()) {
     r.did(launch_expert_loop(r.s, E, at<ExpertLoopParams>(c, w.eparams), r.persist_blocks > 0 ? r.persist_blocks : PK_BLOCKS));
-    r.launches++;   // two launches: parameter block, loop kernel
+    r.launches++;   // two launches: parameter block and barrier words, loop kernel
   }
   return true;
 }
@@ -1280,12 +1278,21 @@ void run_denoise(Run& r, int P, Taps* taps) {
   if (taps) taps->off = tap_step_base + (size_t)2 * d.Le * 64 * d.X + (size_t)d.steps * chunk * d.A;
 }
 
-// inputs -> static staging buffers (replayed graphs read constant addresses)
+// inputs -> static staging buffers (replayed graphs read constant addresses).  16 bytes per lane where a segment's ends
+// allow it: a view is 602 KB, and in 4-byte pieces on 64 blocks three of them took 13 us.
 struct CopySeg { const uint32_t* src; uint32_t* dst; unsigned n; };
 struct CopyArgs { CopySeg seg[4]; };
 __global__ __launch_bounds__(256) void copy_segments_kernel(CopyArgs a) {
   const CopySeg s = a.seg[blockIdx.y];
-  for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < s.n; i += gridDim.x * 256) s.dst[i] = s.src[i];
+  const unsigned first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
+  unsigned done = 0;
+  if (((reinterpret_cast<uintptr_t>(s.src) | reinterpret_cast<uintptr_t>(s.dst)) & 15) == 0) {
+    const uint4* src = reinterpret_cast<const uint4*>(s.src);
+    uint4* dst = reinterpret_cast<uint4*>(s.dst);
+    for (unsigned i = first; i < s.n / 4; i += stride) dst[i] = src[i];
+    done = s.n / 4 * 4;
+  }
+  for (unsigned i = done + first; i < s.n; i += stride) s.dst[i] = s.src[i];
 }
 
 hipError_t stage_inputs(pi0_ctx* c, hipStream_t s, const float* images, int n_views, const int32_t* ids, int n_prompt,
@@ -1308,7 +1315,9 @@ hipError_t stage_inputs(pi0_ctx* c, hipStream_t s, const float* images, int n_vi
                          (unsigned)(c->cfg.chunk * c->d.A)};
   }
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(copy_segments_kernel, dim3(64, n), dim3(256), 0, s, a);
+  unsigned longest = 0;
+  for (int i = 0; i < n; i++) longest = std::max(longest, a.seg[i].n);
+  hipLaunchKernelGGL(copy_segments_kernel, dim3(std::min(256u, (longest + 1023) / 1024), n), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
