@@ -1336,10 +1336,13 @@ hipError_t ensure_read_ahead(pi0_ctx* c) {
   return e;
 }
 
-// grid of the persistent denoise loop inside a two-stream frame (0: per-operation launches)
+// Grid of the persistent denoise loop inside a two-stream frame (0: per-operation launches).  128 blocks take two rounds
+// over the 256 items of most operations, 160 take the QKV projection in one; what lies between wastes part of a round.
+// With one view the prefill is the shorter stream and leaves the loop more.  Frame, ms, at 96 / 128 / 160 blocks: 256 tokens 8.69 /
+// 6.58 / 6.15, 304 9.0 / 7.04 / 6.75, 512 9.28 / 7.46 / 8.07, 768 9.49 / 9.27 / 9.57, 816 10.3 / 9.51 / 10.7.
 int frame_loop_blocks(const pi0_ctx* c, int P) {
   if (c->tune.psb >= 0) return c->tune.psb;
-  return P <= 256 ? 160 : P <= 512 ? 128 : P <= 768 ? 96 : 128;   // measured optima at 256 / 512 / 768 / 816 prefix tokens
+  return P <= 384 ? 160 : 128;
 }
 
 // Runs `kind` either through a cached graph or eagerly.
