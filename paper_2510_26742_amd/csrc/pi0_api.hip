@@ -1095,9 +1095,14 @@ void run_denoise(Run& r, int P, Taps* taps) {
     const size_t st = w.exp[1].qkv.w - w.exp[0].qkv.w;
     ras = B.qkv.w - A.qkv.w == st && B.o.w - A.o.w == st && B.gu.w - A.gu.w == st && B.down.w - A.down.w == st && st % 16 == 0;
   }
-  // warm-up blocks inside the launches only where the read-ahead kernel was asked for but is not used (ras=0)
+  // Warm-up blocks inside the launches where the read-ahead kernel was asked for but is not used (ras=0), and in the static
+  // entry, whose launches have the chip to themselves and no second stream: there the QKV launch (160 blocks) reads the O
+  // weights and an attention launch that is left at 128 blocks reads gate||up's.  pi0_denoise_static, ms, without / with QKV's / with
+  // both: 1 view 5.67 / 5.60 / 5.41, 2 views 5.89 / 5.81 / 5.72; beyond two key shares the attention needs the compute units
+  // itself (3 views: 6.11 against 6.02).  More of them, or in the O and down launches, cost more than they give.
   const bool pfb = r.read_ahead && !ras;
-  const int pfq = pfb ? T.pfq : 0, pfa = pfb ? T.pfa : 0, pfo = pfb ? T.pfo : 0, pfd = pfb ? T.pfd : 0;
+  const bool warm = r.ebase != nullptr && !r.read_ahead;
+  const int pfq = pfb ? T.pfq : warm ? 64 : 0, pfo = pfb ? T.pfo : 0, pfd = pfb ? T.pfd : 0;
   if (ras && !r.count_only && r.ok()) {
     ReadAheadParams ra;
     memset(&ra, 0, sizeof(ra));
@@ -1215,8 +1220,8 @@ void run_denoise(Run& r, int P, Taps* taps) {
         // a launch requests the prefix keys and values itself: as many blocks as there are compute units, each with fewer
         // values (the sums do not depend on it: a column of the output is one wave's work either way)
         a.v_split = es.v_split;
-        if (T.avs <= 0 && es.per_share <= 8) a.v_split = es.shares == 1 ? 8 : es.shares == 2 ? 4 : 2;
-        a.pf = pf_begin(pfa);
+        if (T.avs <= 0 && es.per_share <= 8) a.v_split = (es.shares == 1 ? 8 : es.shares == 2 ? 4 : 2) / (warm && es.shares <= 2 ? 2 : 1);
+        a.pf = pf_begin(pfb ? T.pfa : warm && 4 * std::max(1, a.v_split) * d.H * es.shares <= 128 ? 128 : 0);
         pf_weights(a.pf, 0, L.gu);
         r.cls = PI0_OP_EXP_ATTN;
         RUN(r, launch_attention(r.s, a));
