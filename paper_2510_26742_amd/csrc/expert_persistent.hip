@@ -382,7 +382,7 @@ hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLo
     if (g->k_per_split != g->W.k_pad || g->W.k_pad > SK_KMAX || g->m_tiles != 1) return hipErrorInvalidValue;
   }
   if (P.read_ahead < 0 || P.read_ahead > 63) return hipErrorInvalidValue;
-  if (P.gu.n_tiles % 2 != 0 || P.gu.M <= 32) return hipErrorInvalidValue;   // gate||up: pairs of feature tiles, two token blocks
+  if (P.gu.n_tiles % 2 != 0 || P.gu.M <= 32 || P.gu.bias != nullptr) return hipErrorInvalidValue;   // gate||up: pairs of feature tiles, two token blocks
   if (P.qkv.rowstat == nullptr || P.gu.rowstat == nullptr || P.outp.rowstat == nullptr) return hipErrorInvalidValue;
   if (P.parts_first < 1 || P.parts_first > 8 * SK_WAVES || P.parts_rest < 1 || P.parts_rest > 8 * SK_WAVES) return hipErrorInvalidValue;
   if (P.gu.rowstat_parts < 1 || P.gu.rowstat_parts > 8 * SK_WAVES || P.outp.rowstat_parts < 1 || P.outp.rowstat_parts > 8 * SK_WAVES)

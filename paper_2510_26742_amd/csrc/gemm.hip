@@ -473,6 +473,7 @@ hipError_t launch_gemm(hipStream_t s, int tile, int pro, int epi, const GemmPara
   if (p.k_per_split % 64 != 0 || (long)p.k_per_split * z_splits < p.W.k_pad) return hipErrorInvalidValue;
   if (pro != PRO_NONE && (z_splits != 1 || p.rowstat == nullptr)) return hipErrorInvalidValue;
   if (epi != EPI_PARTIAL && z_splits != 1) return hipErrorInvalidValue;
+  if (epi == EPI_GEGLU && p.bias != nullptr) return hipErrorInvalidValue;   // the gated epilogue adds none
   if (p.m_tiles < 1) return hipErrorInvalidValue;
   if (tile == TILE_BIG || tile == TILE_MID || tile == TILE_SMALL || tile == TILE_WIDE || tile == TILE_WIDE128 || tile == TILE_T192 || tile == TILE_MID2 || tile == TILE_SQ128) {
     // partial row statistics: planes of stat_rows rows, every row a block touches inside a plane

@@ -7,9 +7,12 @@
 #include <type_traits>
 
 __device__ __forceinline__ float gelu_tanh_f(float x) {
-  // 0.5 x (1 + tanh u) = x * sigmoid(2u) = x / (1 + exp(-2u)); hardware exp2 and reciprocal
-  const float u2 = -1.5957691216057308f * (x + 0.044715f * x * x * x);
-  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(1.4426950408889634f * u2));
+  // 0.5 x (1 + tanh u) = x * sigmoid(2u) = x / (1 + exp(-2u)), u = sqrt(2/pi) (x + 0.044715 x^3), with hardware exp2 and
+  // reciprocal: the exponent -2u log2(e) is x (A + B x^2), three operations.  The gated epilogue of a large tile is a few
+  // microseconds of nothing but these.
+  const float t = x * x;
+  const float e = x * __builtin_fmaf(t, -2.3022081984f * 0.044715f, -2.3022081984f);
+  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(e));
 }
 
 // Sum over groups of 8 adjacent lanes with DPP (no LDS traffic): xor 1, xor 2 inside quads, then
@@ -90,7 +93,7 @@ __device__ __forceinline__ void epilogue_preload(const GemmParams& p, int nt, in
     const int n4 = nt * 32 + 8 * (i + ib) + 4 * lh;
     if (DEP != 1) {
       if (PRO == PRO_LN) o.colsum[i - I0] = *reinterpret_cast<const f32x4*>(p.colsum + n4);
-      o.bias[i - I0] = p.bias != nullptr ? *reinterpret_cast<const f32x4*>(p.bias + n4) : f32x4{0.f, 0.f, 0.f, 0.f};
+      if (EPI != EPI_GEGLU) o.bias[i - I0] = p.bias != nullptr ? *reinterpret_cast<const f32x4*>(p.bias + n4) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     if (EPI == EPI_RESID) {
       if (n4 < p.n_valid) {
@@ -171,9 +174,11 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
 #pragma unroll
         for (int j = 0; j < 4; j++) v[j] = rs * (v[j] - mu * cs[j]);
       }
-      const f32x4 bb = ops.bias[i - I0];   // zero without a bias
+      if (EPI != EPI_GEGLU) {   // gate||up has none
+        const f32x4 bb = ops.bias[i - I0];   // zero without a bias
 #pragma unroll
-      for (int j = 0; j < 4; j++) v[j] += bb[j];
+        for (int j = 0; j < 4; j++) v[j] += bb[j];
+      }
       if (EPI == EPI_RESID) {
         if (n4 < p.n_valid) {
           if (p.resid != nullptr) {

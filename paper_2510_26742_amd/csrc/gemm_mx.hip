@@ -34,9 +34,9 @@ __device__ __forceinline__ i32x8 cat(const i32x4& lo, const i32x4& hi) {
 }
 
 __device__ __forceinline__ float gelu_tanh_mx(float x) {
-  // 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)), u = sqrt(2/pi) (x + 0.044715 x^3)
-  const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-  return x * __builtin_amdgcn_rcpf(1.0f + exp2f(-2.885390081777927f * u));
+  // 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)), u = sqrt(2/pi) (x + 0.044715 x^3); the exponent as in gelu_tanh_f
+  const float e = x * __builtin_fmaf(x * x, -2.3022081984f * 0.044715f, -2.3022081984f);
+  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(e));
 }
 
 // OCC = blocks per CU the register budget is cut for: with more blocks than CUs, two resident blocks hide each

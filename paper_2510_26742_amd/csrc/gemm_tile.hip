@@ -274,7 +274,7 @@ hipError_t launch_gemm_lds(hipStream_t s, int pro, int epi, const GemmParams& p,
   if (p.n_tiles < 1 || p.n_tiles * 32 != p.W.n_pad || p.ldx < p.W.k_pad || p.ldx % 16 != 0) return hipErrorInvalidValue;
   if ((size_t)p.W.k_pad * 64 > 0x7fffffffu) return hipErrorInvalidValue;   // a row of fragments is addressed with 32 bits
   if (pro == PRO_RMS && epi == EPI_GEGLU) {
-    if (z != 1 || p.rowstat == nullptr || p.out_bf16 == nullptr || (p.rowstat_parts > 1 && p.stat_rows < p.M))
+    if (z != 1 || p.rowstat == nullptr || p.out_bf16 == nullptr || p.bias != nullptr || (p.rowstat_parts > 1 && p.stat_rows < p.M))
       return hipErrorInvalidValue;
   } else if (pro != PRO_NONE || epi != EPI_PARTIAL || p.out_f32 == nullptr || p.ldo < p.W.n_pad) {
     return hipErrorInvalidValue;
