@@ -1,0 +1,28 @@
+"""The prefix's gate||up and down through LDS (gemm_tile.hip) at the edges of what they take: a contraction of one turn of the loop, one
+that splits into unequal ranges, feature counts that fill no tile, token counts around every tile height, against the
+CPU oracle through the whole pass (all per-layer taps)."""
+import dataclasses
+
+import pytest
+
+from paper_2510_26742_amd import synth
+from tests.test_gpu_parity import Case, check_against_oracle
+
+pytestmark = pytest.mark.gpu
+
+# gate||up: k 128 (one turn), 1280 features; down: k 640 in ranges of 128 and 256, 128 features
+ONE_TURN = dataclasses.replace(synth.reduced_config(vocab=64), llm_width=128, llm_mlp=640, llm_q_heads=3, exp_width=128, exp_mlp=192)
+# gate||up: k 384, 1792 features; down: k 896, 384 features
+ODD_TILES = dataclasses.replace(synth.reduced_config(vocab=64), llm_width=384, llm_mlp=896, llm_q_heads=3, exp_width=128, exp_mlp=192)
+
+
+@pytest.fixture(scope="module", params=["one turn", "odd tiles"])
+def case(request):
+    c = Case({"one turn": ONE_TURN, "odd tiles": ODD_TILES}[request.param])
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("n_views,n_prompt", [(1, 0), (1, 1), (1, 48), (2, 0), (2, 1), (3, 0), (3, 48)])
+def test_large_prefix_gemms_match_the_oracle(case, n_views, n_prompt):
+    check_against_oracle(case, n_views, n_prompt, seed_shift=11 * n_prompt, label=f"{case.cfg.llm_width} wide, {n_views} views + {n_prompt}")
