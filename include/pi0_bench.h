@@ -134,8 +134,8 @@ int pi0_clock_sample(long long* d_out, void* hip_stream);
 int pi0_read_ahead_probe(const void* d_buf, size_t bytes, int layers, int steps, int lead, const int* d_progress,
                          long long wait_ticks, int blocks, unsigned* d_sink, double* h_ms, void* hip_stream);
 
-/* Number of kernel launches one pi0_infer issues on hip_stream for the given shape (0 on bad
- * arguments); the read-ahead kernel on the ctx's own stream is not counted. */
+/* Number of kernel launches of one pi0_infer's graph for the given shape (0 on bad arguments).  The copies of the inputs
+ * before it and of the actions behind it (a launch each) and the read-ahead kernel on the ctx's own stream are not counted. */
 int pi0_kernel_count(const pi0_ctx* ctx, int n_views, int n_prompt);
 
 /*

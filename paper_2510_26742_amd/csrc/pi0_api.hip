@@ -915,7 +915,7 @@ bool run_denoise_persistent(Run& r, int P) {
   const size_t wst = d.Le > 1 ? w.exp[1].qkv.w - w.exp[0].qkv.w : 0, gst = d.Le > 1 ? w.g_e1[1] - w.g_e1[0] : 0;
   const size_t arena_bytes = w.total - w.act_begin;
   if (r.count_only) {
-    r.launches += 3;   // barrier words cleared, parameter block written, the loop kernel
+    r.launches += 2;   // parameter block and barrier words, the loop kernel
     return true;
   }
   if (!r.ok()) return true;
