@@ -606,10 +606,9 @@ def test_persistent_denoise_loop_equals_per_operation_launches():
 def test_reading_ahead_changes_no_bit():
     """The expert's read-ahead kernel and the warm-up blocks only load: the actions of a pass with either of them,
     with neither, and with another shape of the read-ahead kernel are the same bits (graph replay and eager), and the
-    persistent loop gives the bits of the per-operation launches, whatever its idle blocks read ahead (pra).  The number of blocks that share the value slices of the
-    expert attention fixes how the second product is shared out over a block's waves, i.e. the order of an fp32 sum:
-    for each such number the persistent loop and the launches agree bit for bit, and between the numbers the actions
-    differ by rounding only."""
+    persistent loop gives the bits of the per-operation launches, whatever its idle blocks read ahead (pra); nor does the
+    number of blocks that share the values of the expert attention (avs): an output column is one wave's work, so it
+    orders no sum."""
     import os
     outs = {}
     for tune in ("", "pdn=0", "pdn=0,ras=0", "pdn=0,ras=0,pfq=0,pfa=0,pfo=0,pfd=0", "pdn=0,ras=128,rat=128,rad=3,ral=2", "pdn=0,avs=1",
@@ -633,17 +632,7 @@ def test_reading_ahead_changes_no_bit():
         finally:
             case.close()
     for tune, a in outs.items():
-        if "avs" not in tune:
-            np.testing.assert_array_equal(a, outs[""], err_msg=f"PI0_TUNE={tune}")
-    for n in (1, 2, 8):   # avs=1 has no persistent form: both runs are the launches
-        np.testing.assert_array_equal(outs[f"avs={n}"], outs[f"pdn=0,avs={n}"], err_msg=f"avs={n}")
-        rms = float(np.sqrt(np.mean(outs[""].astype(np.float64) ** 2)))
-        d = float(np.abs(outs[f"avs={n}"].astype(np.float64) - outs[""]).max())
-        say(f"[parity] avs={n} vs default: max|delta| {d / rms:.2e} of RMS")
-        # another order of an fp32 sum flips a bf16 rounding of the attention output here and there, and a flipped rounding
-        # travels like any other: the bar is that of rounding alone (3e-3 of RMS moves the ORACLE under bf16 operands,
-        # tests/test_bf16_sensitivity.py), measured 2.3e-3
-        assert d <= 5e-3 * rms
+        np.testing.assert_array_equal(a, outs[""], err_msg=f"PI0_TUNE={tune}")
 
 
 @pytest.mark.parametrize("tune", [

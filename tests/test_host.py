@@ -207,12 +207,12 @@ def test_kernel_count_and_taps(L):
     assert L.pi0_create(ctypes.byref(c), ctypes.byref(ctx)) == 0
     n1 = L.pi0_kernel_count(ctx, 1, 0)
     n2 = L.pi0_kernel_count(ctx, 2, 0)
-    # up to 256 tokens the O projections carry their residual epilogue themselves; beyond, each is followed
-    # by a split-K reduction launch: 27 vision layers, 17 prefix layers with an O projection
+    # up to 256 tokens the GEMM behind an O projection adds up its partial row statistics itself; beyond, a launch of its
+    # own does: 27 vision layers, 17 prefix layers with an O projection
     assert 900 < n1 < 2000 and n2 == n1 + cfg.vis_layers + (cfg.llm_layers - 1)
     assert L.pi0_kernel_count(ctx, 3, 0) == n2
     assert L.pi0_kernel_count(ctx, 0, 0) == 0
-    # 261 prefix tokens: the prompt embedding gather, and the prefix reductions are back
+    # 261 prefix tokens: the prompt embedding gather, and the launches that add up the prefix's row statistics
     assert L.pi0_kernel_count(ctx, 1, 5) == n1 + 1 + (cfg.llm_layers - 1)
     assert L.pi0_kernel_count(ctx, 1, 49) == 0
     L.pi0_destroy(ctx)
@@ -223,8 +223,9 @@ def test_kernel_count_and_taps(L):
 
 def test_tuning_variable_is_parsed_by_key_and_range(L):
     """pi0_tune parses whole keys only (`vo` is not found inside `zvo`), values outside a key's range
-    are ignored, unknown keys do nothing.  Seen through the launch count: a one-launch O projection drops a reduction
-    launch per layer, the plain expert QKV / 32 x 32 expert tiles change nothing in the count."""
+    are ignored, unknown keys do nothing.  Seen through the launch count: a one-launch O projection drops
+    the launch that follows a split-K one (up to 256 tokens; beyond, only with fko / fkl = 1), the plain expert QKV /
+    32 x 32 expert tiles change nothing in the count."""
     import os
     cfg = synth.full_config()
     c = binding.to_c_config(cfg)
