@@ -190,8 +190,11 @@ KERNEL_OF_CLASS = {
 
 
 def kernel_of_class(name: str, prefix_tokens: int | None = None):
-    """Kernel template family that runs an operation class in the library's default schedule (the same for every
-    number of tokens)."""
+    """Kernel template family that runs an operation class in the library's default schedule.  The vision attention has a
+    second form for launches of more than 256 blocks (32 rows of one of 16 heads each), i.e. beyond 512 tokens (of the images:
+    with an empty prompt, as here, those of the prefix)."""
+    if name == "vis_attn" and prefix_tokens is not None and prefix_tokens > 512:
+        return "attention_vision2_kernel"
     return KERNEL_OF_CLASS.get(name)
 
 

@@ -301,5 +301,9 @@ def test_traffic_profile_is_what_bench_reads():
         row = t["by_views"][v]
         assert algorithmic < row["expert_loop_kernel"] < 4 * algorithmic
         assert row["families"]["expert_loop_kernel"]["launches"] == 1
-        for fam in ("gemm_kernel", "attention_kernel", "splitk_reduce_kernel"):
+        # the families that the default schedule runs at this view count, all of them and each as measured at that commit
+        prefill = {roofline.kernel_of_class(c, int(v) * 256) for c in roofline.KERNEL_OF_CLASS if not c.startswith("exp_")}
+        for fam in prefill:
             assert row["families"][fam]["bytes_per_launch"] > 0
+        rest = {"copy_segments_kernel", "patchify_kernel", "row_sums_kernel", "expert_loop_prepare_kernel", "expert_loop_kernel", "copy_f32_kernel"}
+        assert set(row["families"]) <= prefill | rest and not any("note" in f for f in row["families"].values())
