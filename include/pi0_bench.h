@@ -23,16 +23,16 @@ enum pi0_op_class {
   PI0_OP_VIS_PATCH,       /* patch embedding GEMM */
   PI0_OP_VIS_QKV,         /* LayerNorm-folded QKV projection */
   PI0_OP_VIS_ATTN,
-  PI0_OP_VIS_O,           /* split-K partial GEMM of the output projection */
+  PI0_OP_VIS_O,           /* output projection + residual */
   PI0_OP_VIS_UP,
-  PI0_OP_VIS_DOWN,        /* split-K partial GEMM */
+  PI0_OP_VIS_DOWN,        /* down projection + residual */
   PI0_OP_VIS_PROJ,        /* final LayerNorm + projector */
-  PI0_OP_REDUCE,          /* split-K reductions (bias, residual, row statistics) of any stage */
+  PI0_OP_REDUCE,          /* split-K reductions (bias, residual, row statistics), sums of partial row statistics, any stage */
   PI0_OP_LLM_QKV,         /* RMSNorm-folded QKV + RoPE, writes the key/value cache */
   PI0_OP_LLM_ATTN,
   PI0_OP_LLM_O,
   PI0_OP_LLM_GATEUP,
-  PI0_OP_LLM_DOWN,
+  PI0_OP_LLM_DOWN,        /* split-K partial GEMM */
   PI0_OP_EXP_EMBED,       /* folded action/time embedding and its second linear layer */
   PI0_OP_EXP_QKV,
   PI0_OP_EXP_ATTN,

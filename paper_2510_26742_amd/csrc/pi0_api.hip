@@ -578,12 +578,14 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   // behind it hold up to 256 rows, and each would read all planes of its rows (128 KB).  A consumer takes 64 planes at most.
   auto sum_vision = [&](int tokens_over) {
     if (vplanes > 64 || (vplanes > 0 && I > tokens_over)) {
+      r.cls = PI0_OP_REDUCE;
       RUN(r, launch_row_sums(r.s, at<float>(c, w.vstat_parts), vplanes, stat_rows, I, at<float>(c, w.vstat)));
       vplanes = 0;
     }
   };
   auto sum_prefix = [&](int tokens_over) {
     if (lplanes > 64 || (lplanes > 0 && P > tokens_over)) {
+      r.cls = PI0_OP_REDUCE;
       RUN(r, launch_row_sums(r.s, at<float>(c, w.lstat_parts), lplanes, stat_rows, P, at<float>(c, w.lstat)));
       lplanes = 0;
     }

@@ -272,6 +272,24 @@ def test_prefill_then_denoise_and_streaming(reduced):
         assert err <= ACTION_TOL
 
 
+def test_profile_counts_launches_by_operation_class(reduced):
+    """pi0_debug_profile prices an operation by its own launches: every class of Table 2 has one per layer (and step), at one
+    view and at two, where the partial row statistics behind the O projections are added up by launches of their own."""
+    cfg, passes = reduced.cfg, 2
+    Lv, Ll, Le = cfg.vis_layers, cfg.llm_layers, cfg.exp_layers
+    for n_views in (1, 2):
+        d_img, d_st, d_nz, _ = reduced.to_dev(*reduced.inputs(n_views, 0))
+        d_act = torch.empty((cfg.chunk, cfg.action_dim), dtype=torch.float32, device=reduced.dev)
+        say(f"[gpu] pi0_debug_profile views={n_views}")
+        got = reduced.m.pi0_debug_profile(d_img, n_views, None, 0, d_st, d_nz, d_act, passes=passes, stream=reduced.stream)
+        per_layer = dict.fromkeys(("vis_qkv", "vis_attn", "vis_o", "vis_up", "vis_down"), Lv)
+        per_layer.update(dict.fromkeys(("llm_attn", "llm_o", "llm_gateup", "llm_down"), Ll - 1), llm_qkv=Ll, vis_patch=1, vis_proj=1)
+        per_layer.update(dict.fromkeys(("exp_qkv", "exp_attn", "exp_o", "exp_gateup", "exp_down"), cfg.steps * Le), exp_out=cfg.steps)
+        per_layer["reduce"] = Ll - 1 + (Lv + Ll - 1 if n_views > 1 else 0)     # prefix down, and the statistics
+        for name, n in per_layer.items():
+            assert got[name][1] == passes * n, (n_views, name, got[name][1], passes * n)
+
+
 def test_denoise_without_prefill_is_an_error():
     cfg = synth.reduced_config()
     m = binding.Pi0(cfg)
