@@ -182,7 +182,7 @@ KERNEL_OF_CLASS = {
     "vis_patch": "gemm_stream_kernel", "vis_qkv": "gemm_stream_kernel", "vis_o": "gemm_stream_kernel", "vis_up": "gemm_stream_kernel",
     "vis_down": "gemm_stream_kernel", "vis_proj": "gemm_stream_kernel", "llm_qkv": "gemm_stream_kernel", "llm_o": "gemm_stream_kernel",
     "llm_gateup": "gemm_lds_kernel", "llm_down": "gemm_lds_kernel",
-    "vis_attn": "attention_kernel", "llm_attn": "attention_kernel", "exp_attn": "attention_kernel",
+    "vis_attn": "attention_kernel", "llm_attn": "attention_kernel", "exp_attn": "attention_suffix_kernel",
     "exp_qkv": "gemm_skinny_kernel", "exp_gateup": "gemm_skinny_kernel", "exp_out": "gemm_skinny_kernel",
     "exp_o": "gemm_skinny16_kernel", "exp_down": "gemm_skinny16_kernel",
     "reduce": "splitk_reduce_kernel",

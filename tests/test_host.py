@@ -303,6 +303,8 @@ def test_traffic_profile_is_what_bench_reads():
         assert row["families"]["expert_loop_kernel"]["launches"] == 1
         # the families that the default schedule runs at this view count, all of them and each as measured at that commit
         prefill = {roofline.kernel_of_class(c, int(v) * 256) for c in roofline.KERNEL_OF_CLASS if not c.startswith("exp_")}
+        # bench.py leaves families with an operation of the expert out: none of the prefill's may be one of them
+        assert not prefill & {roofline.kernel_of_class(c) for c in roofline.KERNEL_OF_CLASS if c.startswith("exp_")}
         for fam in prefill:
             assert row["families"][fam]["bytes_per_launch"] > 0
         rest = {"copy_segments_kernel", "patchify_kernel", "row_sums_kernel", "expert_loop_prepare_kernel", "expert_loop_kernel", "copy_f32_kernel"}
