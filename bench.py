@@ -59,7 +59,7 @@ def main() -> int:
     ap.add_argument("--tune", type=str, default=None, help="kernel choices for tuning runs (pi0_tune)")
     args = ap.parse_args()
     if args.gpus != 1:
-        print("bench.py: this build runs on exactly one GPU (batch-1 latency path, no sharding); use --gpus 1",
+        print("bench.py: runs on exactly one GPU (batch-1 latency path, no sharding); use --gpus 1",
               file=sys.stderr)
         return 2
 
@@ -193,12 +193,12 @@ def main() -> int:
                  "marks": [float(np.median((a[:, k] - waited)[work & (a[:, k] > 0)])) * 10 if (work & (a[:, k] > 0)).any() else 0.0
                            for k in range(4, 8)]}
             rows.setdefault(names[i], []).append(d)
-        print(f"persistent denoise loop, full pi0, {args.views} view(s), {args.prompt} prompt tokens; pi0_denoise {plain_ms:.3f} ms "
+        print(f"persistent denoise loop, {'reduced-depth' if args.reduced else 'full'} pi0, {args.views} view(s), {args.prompt} prompt tokens; pi0_denoise {plain_ms:.3f} ms "
               f"({traced_ms:.3f} ms while recording); averages over Euler steps 4 and 5, nanoseconds")
         print("items  = blocks with a work item in the operation (of 256)")
         print("wait   = median time a working block spends between its previous arrive and the end of the barrier wait")
         print("body   = end of wait -> last store issued (median / max over working blocks)")
-        print("arrive = last store issued -> arrival counted (stores acknowledged, block barrier, atomic)")
+        print("arrive = last store issued -> arrival announced (stores acknowledged, block barrier, flag stored)")
         print("span   = first working block released -> last working block arrived")
         print("next   = last working block arrived -> first working block of the NEXT operation released (barrier latency)")
         print("marks  = medians of the in-body samples relative to the end of the wait (GEMMs: activations in registers and")
@@ -313,7 +313,7 @@ def main() -> int:
     # the kernel with the largest share of the pass: the persistent denoise loop, one launch per pass.  Algorithmic
     # bytes of a launch = what its operations must move if every operand crossed HBM once (roofline.class_work, per
     # operation of Table 2: weights + input activations + outputs) times their count; duration = the denoise call
-    # (event pair on the stream around graph replays of barrier-word clear + parameter block + loop kernel)
+    # (event pair on the stream around the call: input staging, parameter block and barrier words, loop kernel, copy of the actions)
     hv = headline_views
     work = roofline.class_work(cfg, hv, 0)
     per_layer = sum(work[k][0] for k in ("exp_qkv", "exp_attn", "exp_o", "exp_gateup", "exp_down"))

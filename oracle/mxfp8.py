@@ -1,7 +1,7 @@
 """MXFP8 rounding for the oracle (test infrastructure, not a product path).
 
 The paper names 8-bit multiplication only as a future direction (Section 9.1); it fixes no format.  This
-build's reduced-precision mode for the prefix feed-forward GEMMs uses the public OCP Microscaling
+project's reduced-precision mode for the prefix feed-forward GEMMs uses the public OCP Microscaling
 format MXFP8: elements in FP8 E4M3 (OCP "e4m3fn": bias 7, no infinities, one NaN mantissa, largest
 finite value 448), one shared power-of-two scale (E8M0, bias 127) per 32 consecutive elements of
 the contraction axis.  This file is that definition written out in numpy: it shares no code with

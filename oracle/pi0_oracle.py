@@ -14,7 +14,7 @@ all arithmetic runs in `dtype` (float32 by default, float64 for cross-checks)
 with no intermediate rounding.  numpy's matmul is the only library primitive.
 
 Readings of points the paper leaves to its citations (all are conventions of
-this build, "parity unpinned" against a trained pi0 because the paper prints no
+this project, "parity unpinned" against a trained pi0 because the paper prints no
 activations): LayerNorm/RMSNorm eps 1e-6; RMSNorm gain (1 + g); tanh-GELU
 everywhere; attention scale head_dim**-0.5; RoPE base 10000 with rotate-half
 pairing (i, i + d/2); vision attention per view; learned additive position
@@ -186,7 +186,7 @@ def _gemma_mlp(W, p, x):
 
 def _gemma_mlp_mxfp8(W, p, x):
     """The same feed-forward block with every GEMM operand rounded through MXFP8 (blocks of 32 along the
-    contraction axis).  A convention of this build, not of the paper: the gain-scaled input x * (1 + g) is
+    contraction axis).  A convention of this project, not of the paper: the gain-scaled input x * (1 + g) is
     what gets quantised and the row's 1 / rms is applied to the products (power-of-two block scales do not
     commute with an arbitrary row factor, so the order is part of the definition); the gated product
     gelu(gate) * up is quantised before the down projection."""

@@ -6,8 +6,10 @@
 // Keys and values arrive already in MFMA fragment order (written that way by the QKV GEMM's
 // epilogue), so every operand fetch is one coalesced 16-byte-per-lane read from L2.
 //
-// One block of 8 waves owns 32 query rows of one head.  The kernels of this pass are short and
-// bound by memory round trips, not by arithmetic, so the block is organised to need one round
+// One block of 8 waves owns 32 query rows of one head (attention_body).  The action expert has a body of its own, 16 query
+// rows per block, for shares of up to 8 prefix chunks (attention_suffix_body, attn_suffix_ok).  Wider shares (geometries
+// without 8 heads, pi0_tune) and other numbers of rows (pi0_attention_probe only) run here, with the second segment below.
+// The kernels of this pass are short and bound by memory round trips, not by arithmetic, so the block is organised to need one round
 // trip when the prefix has at most 8 chunks of 32 keys: at entry every wave issues its loads of Q
 // (to LDS), of the key fragments of "its" prefix chunks (chunk index = wave, wave + 8, ...), of
 // the value fragments of "its" 32-wide slice of the head dimension, and the block copies the
@@ -17,7 +19,8 @@
 //            are per-lane scalars; the probabilities in the accumulator registers are, without
 //            any data movement, B-operand fragments of the second product and go to LDS as such;
 //   phase 2  O^T = V^T P^T: wave w accumulates head-dimension slice w over ALL chunks, reading
-//            the probability fragments of every wave from LDS.  No cross-wave merge of O.
+//            the probability fragments of every wave from LDS.  No cross-wave merge of O, except where
+//            all chunks fit one round and the waves share them out too (CPW > 0, attention_body).
 // The softmax uses the exact row maximum (two LDS exchanges), so results do not depend on the
 // chunk-to-wave assignment.
 #include "pi0_internal.h"

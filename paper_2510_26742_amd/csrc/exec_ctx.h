@@ -11,8 +11,8 @@
 // PersistCtx is one persistent kernel for the whole denoise loop (Section 5.2: software barriers instead of
 // kernel boundaries, weights requested before the wait).  The chip has eight dies with an L2 each that
 // ordinary accesses do not keep coherent inside a kernel, so data that crosses blocks is stored write-through
-// and loaded past the L2 (device-scope bits of the buffer instructions), and a barrier releases a die's
-// writes once per die; see grid barrier below.  Weights, tables and the prefix key/value cache are constant
+// and loaded past the L2 (device-scope bits of the buffer instructions), so a barrier writes nothing back: it
+// waits for stores to be acknowledged and exchanges flags; see grid barrier below.  Weights, tables and the prefix key/value cache are constant
 // during the kernel and are read with ordinary loads before the wait.
 // Both contexts run the same arithmetic in the same order, so the two paths agree bit for bit.
 #pragma once
@@ -90,8 +90,9 @@ struct LaunchCtx {
 // everything another block will read is stored write-through (PersistCtxT::st) and each wave waits until its own stores
 // are acknowledged.  The leader requests its own prefetch only after that (loads return in order per compute unit: its
 // polls would queue behind it), so it is chosen among the blocks that the attention leaves idle.  Arrive and wait are separate calls, so a block requests the next operation's constant
-// operands between them.  Every wait is bounded: when the bound runs out the error word is raised, every
-// later wait returns at once, and the host reports the failure.
+// operands between them.  Every wait is bounded: when the bound runs out the error word is raised,
+// every wait that is not complete by then or starts later gives up within 64 polls (give_up), so the kernel drains, and the
+// host reports the failure.
 // Words (unsigned; groups 128 bytes apart so that no two are in one cache line):
 enum {
   GB_ERR = 0,          // != 0: a bounded wait ran out

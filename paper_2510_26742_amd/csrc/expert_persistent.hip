@@ -13,7 +13,8 @@
 // the other constants BEFORE it waits for the operation before to complete everywhere, so the weights' trip
 // from HBM overlaps the barrier; and there is no dispatch, no cold instruction / argument fetch, no end-of-kernel
 // cache write-back per operation.  What it costs: data that crosses blocks must be written through to memory
-// and read past the per-die L2 (exec_ctx.h), and a barrier costs two dependent atomics plus a poll.
+// and read past the per-die L2 or from places never read before (exec_ctx.h), and a barrier costs two store-to-poll hops,
+// one inside a die and one between dies.
 #include "attention_body.h"
 #include "expert_loop.h"
 
@@ -26,8 +27,8 @@ constexpr int PK_THREADS = 512;
 // run on one layer's weights throughout, i.e. from that cache, is 0.46 ms faster).  The attention has 64 items for 256
 // blocks: the blocks without one use the time to read the weights that the following operations will ask for, which puts
 // them into the memory-side cache.  Part `part` of `nparts` of n16 16-byte pieces, piece i at addr(i): 16 bytes per lane,
-// 8 loads in flight (4 finish too late, 16 disturb the working blocks' loads more than they gain: same-box A/B
-// 5.47 / 5.42 / 5.48 ms); the values are folded into a word that is stored only if it equals a constant, so no result
+// 8 loads in flight (4 finish too late, 16 disturb the working blocks' loads more than they gain: pi0_denoise
+// 5.47 / 5.42 / 5.48 ms on one device, before the flag barrier); the values are folded into a word that is stored only if it equals a constant, so no result
 // depends on them.
 template <class F>
 __device__ __forceinline__ unsigned read_ahead_part(unsigned n16, int part, int nparts, int tid, unsigned fold, F&& addr) {

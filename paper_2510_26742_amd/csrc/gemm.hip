@@ -13,7 +13,10 @@
 
 #include "gemm_common.h"
 
-// Tall GEMM (256 .. 816 tokens): the vision tower and the prefix transformer.
+// Tall GEMM (256 .. 816 tokens), operands staged through registers and LDS.  The default schedule runs it only where the
+// prefix's gate||up or down contracts over no multiple of 128 (TILE_WIDE, TILE_WIDE128, TILE_T192); gemm_stream.hip and
+// gemm_tile.hip took the other prefill GEMMs over.  The remaining tiles (TILE_BIG, MID, MID2, SMALL, SQ128) are reached
+// through pi0_tune alone: the split-K forms and the tiles to compare a new one with.
 // Block = WN waves, each owning NT adjacent 32-feature tiles, all sharing one MB*32-token activation
 // tile that is staged through LDS in chunks of 64 k (4 fragments per 32-token block, copied 1 KiB at
 // a time from the XF layout, so global reads, LDS writes and LDS reads are all contiguous).  A

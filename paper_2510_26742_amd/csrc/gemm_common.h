@@ -279,7 +279,7 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
 // wave w owns k16 steps w*8 .. w*8+7 and reads exactly the activation fragments of those steps
 // (both 32-token blocks) from the XF layout straight into registers: no LDS staging, no barrier
 // before the MFMAs.  Partial tiles and partial row statistics are summed through LDS in wave order
-// (deterministic); waves 0 and 1 finish one 32-token tile each.
+// (deterministic); the sums and the epilogue of a tile are done by 4 waves (QKV, Euler), 2 (GeGLU) or 1.
 // ------------------------------------------------------------------------------------------------
 #define SK_WAVES 8
 #define SK_KMAX 1024

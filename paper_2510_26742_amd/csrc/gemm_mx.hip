@@ -2,7 +2,7 @@
 // split-K partials) on MXFP8 operands: FP8 E4M3 elements with one power-of-two scale per 32 consecutive
 // k, multiplied by mfma_scale_f32_32x32x64_f8f6f4, which applies the block scales in hardware.  The
 // paper only names 8-bit multiplication as a direction (Section 9.1); the format and where the rounding
-// happens are choices of this build.
+// happens are choices of this library.
 //
 // Same plan as the bf16 tall kernel with two feature tiles per wave: block = 128 tokens x 256 features,
 // 4 waves x 2 feature tiles; the activation chunk (128 tokens x 64 k = 8 KiB) is staged through LDS, the

@@ -204,15 +204,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 }
 
 // tiles (MT, NT): 256 x 128, 320 x 128, 192 x 256, 256 x 256 (tokens x features).  One token tile of 320 takes a view and its
-// prompt, of 192 two of them three views.
+// prompt, one of 256 a view; four of 192 take three views.
 #define LDS_TILES(X) X(4, 2) X(5, 2) X(3, 4) X(4, 4)
 
 // Time of a launch in microseconds, for the choice of the tile and of the number of k ranges.  A round of 256 blocks takes
 // the larger of the operands' way to the compute units (46 KB per us and unit with all of them asking; a round that leaves
 // units idle is quicker, down to 3/4) and the products (32 cycles each at the 1.35 GHz the chip then runs at), and 3 us
 // plus the epilogue, which goes with the tile (0.8 us per 32 x 32 tile and wave with the gate, 0.35 us for partial sums).
-// The partial sums are then read and written once more (6 TB/s, and a launch).  Against measurement (42.7 / 48 / 51 / 65 us
-// for one round of the four tiles, down in 36 .. 90 us with 4 .. 16 ranges) it is within 15 %.
+// The partial sums are then read and written once more (6 TB/s, and a launch).  The constants are fitted to single launches
+// (42.7 / 48 / 51 / 65 us for one round of the four tiles, down in 36 .. 90 us with 4 .. 16 ranges).  In a traced pass at
+// 256 / 512 / 768 / 816 tokens gate||up takes 43.1 / 58.6 / 88.3 / 112.3 us and the formula says 42.8 / 64.3 / 103.1 / 128.7
+// (within 1 %, then 10 .. 17 % high); down with its reduction 38.4 / 54.7 / 71.3 / 76.3 and it says 36.4 / 52.6 /
+// 65.0 / 72.8 (4 .. 9 % low, of which the GEMM alone 11 .. 25 % low and the reduction 26 .. 73 % high).  It ranks tiles and
+// ranges; it does not predict a time.
 float lds_tile_cost(int MT, int NT, int M, int n_tiles, int k_per_split, int z, bool partial) {
   const int blocks = ceil_div(M, 2 * MT * 32) * ceil_div(n_tiles, 2 * NT) * z;
   const int rounds = ceil_div(blocks, 256);

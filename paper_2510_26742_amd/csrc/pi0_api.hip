@@ -712,7 +712,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   const int tlo = T.lo >= 0 ? T.lo : (P <= 512 ? TILE_MID : TILE_SQ128);
   const int zlo = T.zlo > 0 ? T.zlo : (P <= 256 ? 4 : 2);
   const bool mx = c->precision == PI0_PRECISION_MXFP8_PREFIX_MLP;
-  // gate||up: 128 blocks of 256 features per token tile of 128, 192 or 256 tokens.  A block's time goes with its
+  // gate||up: TILE_LDS, which chooses its own tile, where the contraction is a multiple of 128.  Otherwise blocks of 256
+  // features per token tile of 128, 192 or 256 tokens: a block's time goes with its
   // height, so a choice costs height x rounds on 256 compute units; take the cheapest, the taller tile on ties
   // (fewer operand bytes per CU and flop).  256 / 512 / 768 / 816 tokens -> 128 / 256 / 192 / 256.
   const int gu_cols = ceil_div(w.llm[0].gu.n_pad, 256);
@@ -1857,10 +1858,10 @@ int pi0_stream_frame(pi0_ctx* c, const float* d_images, int n_views, const int32
   if (e != hipSuccess) return fail_hip(c, e);
   // The denoise of a frame is the persistent loop on a part of the chip (frame_loop_blocks): a resident block of the
   // loop holds a whole compute unit, so its grid is what shares the chip between the two streams - the prefill's blocks
-  // run on the compute units it leaves (measured at 1 view: 7.8 ms per frame with 160 blocks, 8.5 with 128, 9.1 as
-  // per-operation launches).  With psb=0 it is per-operation launches without any reading ahead: the read-ahead kernel
-  // keeps a wave on every SIMD for the whole loop, and the prefill's kernels have waves that take a SIMD's whole register
-  // file (they would wait for the loop's end: +0.8 .. +1.2 ms); warm-up blocks inside the launches cost +0.2 .. +0.3 ms.
+  // run on the compute units it leaves (6.15 ms per frame at 1 view with 160 blocks, 6.58 with 128).  With psb=0 it is
+  // per-operation launches without any reading ahead: the read-ahead kernel keeps a wave on every SIMD for the whole loop,
+  // and the prefill's kernels have waves that take a SIMD's whole register file (they would wait for the loop's end: +0.8 ..
+  // +1.2 ms); warm-up blocks inside the launches cost +0.2 .. +0.3 ms.
   rc = execute(c, KIND_DENOISE, c->cur_views, c->cur_prompt, sd, cur, cur, false);
   if (rc != PI0_OK) return rc;
   e = launch_copy_f32(sd, at<float>(c, c->wl.xa), d_actions, (size_t)c->cfg.chunk * c->d.A);

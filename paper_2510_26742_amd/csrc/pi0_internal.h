@@ -159,19 +159,21 @@ struct GemmParams {
   PrefetchDesc pf;
 };
 
-// Tile configuration ids (template instantiations that exist)
+// Tile configuration ids (template instantiations that exist).  The default schedule of the prefill takes TILE_STREAM and
+// TILE_LDS, and TILE_WIDE, TILE_WIDE128 or TILE_T192 for contractions that TILE_LDS does not take; BIG, MID, MID2, SMALL and
+// SQ128 only run when pi0_tune asks for them.
 enum GemmTile {
   TILE_BIG = 0,     // 256 tokens x 128 features per block (4 waves), 3 register stages in flight
   TILE_MID = 1,     // 64 tokens x 128 features per block (4 waves), 6 register stages in flight
   TILE_SKINNY = 2,  // <= 64 tokens, one 32-feature tile per block, 8 waves split k <= 1024, loads issued at once
   TILE_SKINNY_FULLK = 3,  // <= 64 tokens, k = 2048 or 4096 in one block per (feature tile, 32-token block), residual epilogue
   TILE_SKINNY16 = 4,      // same on 16-feature x 16-token tiles (mfma 16x16x32): 256 blocks for the expert's O / down
-  TILE_SMALL = 5,         // 64 tokens x 64 features per block (2 waves), 6 stages: small GEMMs of the vision tower
+  TILE_SMALL = 5,         // 64 tokens x 64 features per block (2 waves), 6 stages
   // two feature tiles per wave: an activation fragment read from LDS feeds two MFMAs (prefix gate||up / down only)
   TILE_WIDE = 6,          // 256 tokens x 256 features per block (4 waves x 2 feature tiles), 2 stages
   TILE_WIDE128 = 7,       // 128 tokens x 256 features per block, 3 stages
-  TILE_SQ128 = 9,         // 128 tokens x 128 features per block (4 waves), 5 stages: the mid-size GEMMs at three views
-  TILE_T192 = 10,         // 192 tokens x 256 features per block, 2 stages: 768 tokens in four tiles
+  TILE_SQ128 = 9,         // 128 tokens x 128 features per block (4 waves), 5 stages
+  TILE_T192 = 10,         // 192 tokens x 256 features per block, 3 stages (2 for partial sums): 768 tokens in four tiles
   TILE_MID2 = 11,         // 64 tokens x 128 features as TILE_MID, cut for two resident blocks per compute unit
   TILE_LDS = 13,          // the prefix's gate||up and down, k ranges in multiples of 128 (gemm_tile.hip); tile from the shape
   TILE_STREAM = 12        // whole k range, split over the waves of a block (gemm_stream.hip); the tile follows from the shape
