@@ -529,11 +529,11 @@ void gemm_splitk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int 
 }
 
 // the same operation as one GEMM over the whole k range: bias / residual / gain-scaled shadow in the
-// GEMM's epilogue, row statistics left as one partial sum per 32-column tile in parts[n tile][stat_rows][2]
-void gemm_fullk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int k_true, const float* bias, float* resid_io,
-                      bf16* shadow, int n_true, float* parts, int stat_rows, const float* gain, int tile,
+// GEMM's epilogue, row statistics left as one partial sum per block column in parts[plane][stat_rows][2]; returns the planes
+int gemm_fullk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int k_true, const float* bias, float* resid_io,
+                      bf16* shadow, int n_true, float* parts, int stat_rows, const float* gain,
                       const float* resid_in = nullptr, int resid_mod = 0) {
-  GemmParams p = gp_base(r.c, pw, X, ldx, M, tile, k_true);
+  GemmParams p = gp_base(r.c, pw, X, ldx, M, TILE_STREAM, k_true);
   p.bias = bias;
   p.resid = resid_in != nullptr ? resid_in : resid_io;
   p.resid_mod = resid_mod;
@@ -543,7 +543,8 @@ void gemm_fullk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int k
   p.gain = gain;
   p.stat_out = parts;
   p.stat_rows = stat_rows;
-  RUN_GEMM(r, tile, PRO_NONE, EPI_RESID, p, 1);
+  RUN_GEMM(r, TILE_STREAM, PRO_NONE, EPI_RESID, p, 1);
+  return gemm_stream_stat_planes(PRO_NONE, M, p.n_tiles, pw.k_pad);
 }
 
 struct Taps {
@@ -596,9 +597,9 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   RUN(r, launch_patchify(r.s, at<float>(c, w.st_images), n_views, c->cfg.img_size, c->cfg.patch, at<bf16>(c, w.xpatch), d.PDp));
   r.cls = PI0_OP_VIS_PATCH;
   if (T.vis < 0) {
-    gemm_fullk_resid(r, w.patch, at<bf16>(c, w.xpatch), d.PDp, I, d.PD, at<float>(c, w.patch.bias), at<float>(c, w.vh), at<bf16>(c, w.vh_b),
-                     d.Dv, at<float>(c, w.vstat_parts), stat_rows, at<float>(c, w.g_v1[0]), TILE_STREAM, at<float>(c, w.pos), d.T);
-    vplanes = w.patch.n_pad / 32;
+    vplanes = gemm_fullk_resid(r, w.patch, at<bf16>(c, w.xpatch), d.PDp, I, d.PD, at<float>(c, w.patch.bias), at<float>(c, w.vh),
+                               at<bf16>(c, w.vh_b), d.Dv, at<float>(c, w.vstat_parts), stat_rows, at<float>(c, w.g_v1[0]),
+                               at<float>(c, w.pos), d.T);
     sum_vision(NEVER);
   } else {
     gemm_splitk_resid(r, w.patch, at<bf16>(c, w.xpatch), d.PDp, I, d.PD, 1, w.patch.k_pad, at<float>(c, w.patch.bias),
@@ -648,10 +649,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     // A3: O-projection + bias + residual
     r.cls = PI0_OP_VIS_O;
     if (vo_stream) {
-      gemm_fullk_resid(r, L.o, at<bf16>(c, w.vattn), d.Dv, I, d.Dv, at<float>(c, L.o.bias), at<float>(c, w.vh),
-                       at<bf16>(c, w.vh_b), d.Dv, at<float>(c, w.vstat_parts), stat_rows, at<float>(c, w.g_v2[l]),
-                       TILE_STREAM);
-      vplanes = L.o.n_pad / 32;
+      vplanes = gemm_fullk_resid(r, L.o, at<bf16>(c, w.vattn), d.Dv, I, d.Dv, at<float>(c, L.o.bias), at<float>(c, w.vh),
+                                 at<bf16>(c, w.vh_b), d.Dv, at<float>(c, w.vstat_parts), stat_rows, at<float>(c, w.g_v2[l]));
       sum_vision(T.fko == 1 ? NEVER : 256);
     } else {
       gemm_splitk_resid(r, L.o, at<bf16>(c, w.vattn), d.Dv, I, d.Dv, zvo, round_up(ceil_div(L.o.k_pad, zvo), 64),
@@ -673,9 +672,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     r.cls = PI0_OP_VIS_DOWN;
     const float* next_gain = at<float>(c, l + 1 < d.Lv ? w.g_v1[l + 1] : w.g_vf);
     if (vd_stream) {
-      gemm_fullk_resid(r, L.down, at<bf16>(c, w.vmid), d.Fv_kp, I, d.Fv, at<float>(c, L.down.bias), at<float>(c, w.vh),
-                       at<bf16>(c, w.vh_b), d.Dv, at<float>(c, w.vstat_parts), stat_rows, next_gain, TILE_STREAM);
-      vplanes = L.down.n_pad / 32;
+      vplanes = gemm_fullk_resid(r, L.down, at<bf16>(c, w.vmid), d.Fv_kp, I, d.Fv, at<float>(c, L.down.bias), at<float>(c, w.vh),
+                                 at<bf16>(c, w.vh_b), d.Dv, at<float>(c, w.vstat_parts), stat_rows, next_gain);
       sum_vision(NEVER);
     } else {
       gemm_splitk_resid(r, L.down, at<bf16>(c, w.vmid), d.Fv_kp, I, d.Fv, zvd, round_up(ceil_div(L.down.k_pad, zvd), 64),
@@ -696,7 +694,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     p.stat_out = at<float>(c, w.lstat_parts);
     r.cls = PI0_OP_VIS_PROJ;
     RUN_GEMM(r, tproj, PRO_LN, EPI_RESID, p, 1);
-    lplanes = d.E / 32;
+    lplanes = tproj == TILE_STREAM ? gemm_stream_stat_planes(PRO_LN, I, p.n_tiles, w.proj.k_pad) : d.E / 32;
     r.cls = PI0_OP_MISC;
   }
   if (taps) taps->put(r, at<float>(c, w.lx), (size_t)I * d.E);
@@ -768,9 +766,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     // B3: O-projection + residual
     r.cls = PI0_OP_LLM_O;
     if (lo_stream) {
-      gemm_fullk_resid(r, L.o, at<bf16>(c, w.lattn), d.H * 256, P, d.H * 256, nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b),
-                       d.E, at<float>(c, w.lstat_parts), stat_rows, at<float>(c, w.g_l2[l]), TILE_STREAM);
-      lplanes = d.E / 32;
+      lplanes = gemm_fullk_resid(r, L.o, at<bf16>(c, w.lattn), d.H * 256, P, d.H * 256, nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b),
+                                 d.E, at<float>(c, w.lstat_parts), stat_rows, at<float>(c, w.g_l2[l]));
       if (mx) {   // the MXFP8 copy of x * (1 + g) for gate||up and whole-row statistics, from the rows just written
         r.cls = PI0_OP_REDUCE;
         ReduceParams q;
