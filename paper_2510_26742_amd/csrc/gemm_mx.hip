@@ -168,16 +168,15 @@ __global__ __launch_bounds__(64 * MX_WN) __attribute__((amdgpu_waves_per_eu(OCC,
   // ---- epilogue: lane -> token lq of each 32-token block, features nt * 32 + 8 * (r / 4) + 4 * lh + r % 4 ----
   if (EPI == MX_EPI_PARTIAL) {
 #pragma unroll
-    for (int mb = 0; mb < MX_MB; mb++) {
-      const int m = m0 + mb * 32 + lq;
-      if (m < p.M) {
+    for (int mb = 0; mb < MX_MB; mb++) {   // whole tiles, see partial_tile_at; rows beyond the last are never read
+      const int mbs = (p.M + 31) >> 5, mbg = (m0 >> 5) + mb;
+      if (mbg < mbs) {
 #pragma unroll
         for (int j = 0; j < MX_NT; j++)
 #pragma unroll
           for (int i = 0; i < 4; i++) {
-            const int n4 = (nt0 + j) * 32 + 8 * i + 4 * lh;
             const f32x4 o = {acc[j][mb][4 * i], acc[j][mb][4 * i + 1], acc[j][mb][4 * i + 2], acc[j][mb][4 * i + 3]};
-            *reinterpret_cast<f32x4*>(p.out_f32 + ((size_t)blockIdx.y * p.M + m) * p.ldo + n4) = o;
+            *reinterpret_cast<f32x4*>(p.out_f32 + (((size_t)blockIdx.y * mbs + mbg) * (p.n_pad >> 5) + nt0 + j) * 1024 + i * 256 + lane * 4) = o;
           }
       }
     }
@@ -254,7 +253,7 @@ hipError_t launch_gemm_mx(hipStream_t s, int epi, const MxGemmParams& p, int z_s
   if ((long)p.k_per_split * (z_splits - 1) >= p.k_pad) return hipErrorInvalidValue;     // no empty slice
   if (p.m_tiles < 1 || p.m_tiles * MX_MB * 32 < p.M) return hipErrorInvalidValue;
   if (epi == MX_EPI_PARTIAL) {
-    if (p.out_f32 == nullptr || p.ldo < p.n_pad || p.ldo % 4 != 0) return hipErrorInvalidValue;
+    if (p.out_f32 == nullptr) return hipErrorInvalidValue;
   } else if (epi == MX_EPI_GEGLU) {
     if (z_splits != 1 || p.rowstat == nullptr || p.out8 == nullptr || p.out_scales == nullptr || p.k_true <= 0) return hipErrorInvalidValue;
     if (p.ldo8 % 256 != 0 || p.ldo8 < p.n_pad / 2) return hipErrorInvalidValue;

@@ -180,6 +180,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   for (int g = 0; g + 1 < groups; g++) group(Int<0>{});
   group(Int<1>{});
 
+  if constexpr (EPI == EPI_PARTIAL) {   // whole tiles, see partial_tile_at; rows beyond the last are never read
+    const int mbs = (p.M + 31) >> 5;
+#pragma unroll
+    for (int i = 0; i < MT; i++) {
+      const int mb = (m0 >> 5) + wm * MT + i;
+#pragma unroll
+      for (int j = 0; j < NT; j++) {
+        const int nt = nb * WB + wn * NT + j;
+        if (mb < mbs && nt < p.n_tiles) {   // uniform
+          float* const dst = p.out_f32 + (((size_t)blockIdx.y * mbs + mb) * p.n_tiles + nt) * 1024 + lane * 4;
+#pragma unroll
+          for (int q = 0; q < 4; q++) *reinterpret_cast<f32x4*>(dst + q * 256) = f32x4{acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
+        }
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < MT; i++) {
     const int row = (wm * MT + i) * 32 + lq, m = m0 + row;
@@ -209,23 +226,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 // Time of a launch in microseconds, for the choice of the tile and of the number of k ranges.  A round of 256 blocks takes
 // the larger of the operands' way to the compute units (46 KB per us and unit with all of them asking; a round that leaves
-// units idle is quicker, down to 3/4) and the products (32 cycles each at the 1.35 GHz the chip then runs at), and 3 us
-// plus the epilogue, which goes with the tile (0.8 us per 32 x 32 tile and wave with the gate, 0.35 us for partial sums).
-// The partial sums are then read and written once more (6 TB/s, and a launch).  The constants are fitted to single launches
-// (42.7 / 48 / 51 / 65 us for one round of the four tiles, down in 36 .. 90 us with 4 .. 16 ranges).  In a traced pass at
-// 256 / 512 / 768 / 816 tokens gate||up takes 43.1 / 58.6 / 88.3 / 112.3 us and the formula says 42.8 / 64.3 / 103.1 / 128.7
-// (within 1 %, then 10 .. 17 % high); down with its reduction 38.4 / 54.7 / 71.3 / 76.3 and it says 36.4 / 52.6 /
-// 65.0 / 72.8 (4 .. 9 % low, of which the GEMM alone 11 .. 25 % low and the reduction 26 .. 73 % high).  It ranks tiles and
-// ranges; it does not predict a time.
+// units idle is quicker, gate||up down to 3/4, partial sums 0.9) and the products (32 cycles each at the 1.35 GHz the chip
+// then runs at), and 3 us plus the epilogue, which goes with the tile (0.8 us per 32 x 32 tile and wave with the gate, 0.12 us
+// for partial sums).  The partial sums are then read and written once more (5 TB/s, and a launch).  It ranks tiles and
+// ranges; it does not predict a time.  gate||up in a traced pass at 256 / 512 / 768 / 816 tokens: 43.1 / 58.6 / 88.3 / 112.3 us,
+// the formula 42.8 / 64.3 / 103.1 / 128.7.  Number of ranges, prefill in ms at 256 tokens with 8 / 10 / 11 / 12 / 16 ranges:
+// 3.078 / 3.046 / 3.024 / 3.030 / 3.031; 512 with 6 / 7 / 8 / 10 / 12: 4.336 / 4.306 / 4.248 / 4.300 / 4.208 .. 4.31; 768 with
+// 5 / 6 / 7 / 8 / 9: 5.523 / 5.451 / 5.393 / 5.393 / 5.425; 816 with 5 / 6 / 7 / 8: 5.998 / 5.948 / 6.033 / 6.038.
 float lds_tile_cost(int MT, int NT, int M, int n_tiles, int k_per_split, int z, bool partial) {
   const int blocks = ceil_div(M, 2 * MT * 32) * ceil_div(n_tiles, 2 * NT) * z;
   const int rounds = ceil_div(blocks, 256);
   const float steps = (float)(k_per_split >> 4);
   const float feed = 2.f * (float)(MT + NT) / 46.f, products = (float)(MT * NT) * 0.0237f;
   const float full = steps * (feed > products ? feed : products);
-  const float fill = (float)blocks / (256.f * (float)rounds);
-  float us = (float)rounds * (full * (fill > 0.75f ? fill : 0.75f) + 3.f + (partial ? 0.35f : 0.8f) * (float)(MT * NT));
-  if (partial) us += (float)z * (float)M * (float)n_tiles * 32.f * 8.f / 6.0e6f + 5.f;
+  const float fill = (float)blocks / (256.f * (float)rounds), least = partial ? 0.9f : 0.75f;
+  float us = (float)rounds * (full * (fill > least ? fill : least) + 3.f + (partial ? 0.12f : 0.8f) * (float)(MT * NT));
+  if (partial) us += (float)z * (float)M * (float)n_tiles * 32.f * 8.f / 5.0e6f + 5.f;
   return us;
 }
 
@@ -280,7 +296,7 @@ hipError_t launch_gemm_lds(hipStream_t s, int pro, int epi, const GemmParams& p,
   if (pro == PRO_RMS && epi == EPI_GEGLU) {
     if (z != 1 || p.rowstat == nullptr || p.out_bf16 == nullptr || p.bias != nullptr || (p.rowstat_parts > 1 && p.stat_rows < p.M))
       return hipErrorInvalidValue;
-  } else if (pro != PRO_NONE || epi != EPI_PARTIAL || p.out_f32 == nullptr || p.ldo < p.W.n_pad) {
+  } else if (pro != PRO_NONE || epi != EPI_PARTIAL || p.out_f32 == nullptr) {
     return hipErrorInvalidValue;
   }
   hipError_t (*best)(hipStream_t, GemmParams, int) = nullptr;

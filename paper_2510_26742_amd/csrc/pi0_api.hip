@@ -262,7 +262,7 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
   w.zmax = Z_MAX;
   {
     size_t a = (size_t)w.zmax * d.maxI * round_up(d.Dv, 32) * 4;
-    size_t b = (size_t)w.zmax * d.maxP * d.E * 4;
+    size_t b = (size_t)w.zmax * d.maxPc * 32 * d.E * 4;
     w.part = cur.take(a > b ? a : b);
   }
   w.lx = cur.take((size_t)d.maxP * d.E * 4);
@@ -497,11 +497,13 @@ GemmParams gp_base(pi0_ctx* c, const PW& pw, const bf16* X, int ldx, int M, int 
 #define RUN(r, call) \
   do { if ((r).count_only) (r).launches++; else if ((r).ok()) { (r).before(); (r).did(call); (r).after(); } } while (0)
 
-// split-K GEMM into the partial buffer followed by the fixed-order reduction with bias/residual
-void gemm_splitk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int k_true, int z, int k_per_split,
+// split-K GEMM into the partial buffer followed by the fixed-order reduction with bias/residual; returns the planes of the row
+// statistics in stat_out (0: whole rows in `stat_out`; else planes of stat_rows rows in `stat_planes`)
+int gemm_splitk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int k_true, int z, int k_per_split,
                        const float* bias, float* resid_io, bf16* shadow, int n_true, int tile, float* stat_out,
                        const float* gain, const float* resid_in = nullptr, int resid_mod = 0, bool no_resid = false,
-                       bool expert_scratch = false, unsigned char* out8 = nullptr, unsigned char* out8_scales = nullptr) {
+                       bool expert_scratch = false, unsigned char* out8 = nullptr, unsigned char* out8_scales = nullptr,
+                       float* stat_planes = nullptr, int stat_rows = 0) {
   pi0_ctx* c = r.c;
   if (z > Z_MAX) z = Z_MAX;
   if ((long)k_per_split * z < pw.k_pad) k_per_split = round_up(ceil_div(pw.k_pad, z), 64);
@@ -513,12 +515,15 @@ void gemm_splitk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int 
   const int cls_gemm = r.cls;
   r.cls = PI0_OP_REDUCE;
   ReduceParams q;
+  memset(&q, 0, sizeof(q));
   q.part = p.out_f32;
+  q.tiled = tile == TILE_LDS;
   q.Z = z; q.M = M; q.N = n_true; q.ldp = pw.n_pad;
   q.bias = bias;
   q.resid = no_resid ? nullptr : (resid_in ? resid_in : resid_io);
   q.resid_mod = resid_mod;
-  q.stat_out = stat_out;
+  q.stat_out = q.tiled ? stat_planes : stat_out;
+  q.stat_rows = stat_rows;
   q.gain = gain;
   q.out_f32 = resid_io;
   q.out_bf16 = shadow;
@@ -526,6 +531,7 @@ void gemm_splitk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int 
   q.out8 = out8; q.out8_scales = out8_scales;
   RUN(r, launch_splitk_reduce(r.s, q));
   r.cls = cls_gemm;
+  return q.tiled ? ceil_div(n_true, 256) : 0;
 }
 
 // the same operation as one GEMM over the whole k range: bias / residual / gain-scaled shadow in the
@@ -814,18 +820,22 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
       RUN(r, launch_gemm_mx(r.s, MX_EPI_PARTIAL, u, zeff));
       r.cls = PI0_OP_REDUCE;
       ReduceParams rq;
+      memset(&rq, 0, sizeof(rq));
+      rq.tiled = 1;
       rq.part = u.out_f32;
       rq.Z = zeff; rq.M = P; rq.N = d.E; rq.ldp = L.down.n_pad;
       rq.bias = nullptr;
       rq.resid = at<float>(c, w.lx);
       rq.resid_mod = 0;
-      rq.stat_out = at<float>(c, w.lstat);
+      rq.stat_out = at<float>(c, w.lstat_parts);
+      rq.stat_rows = stat_rows;
       rq.gain = at<float>(c, w.g_l1[l + 1]);
       rq.out_f32 = at<float>(c, w.lx);
       rq.out_bf16 = at<bf16>(c, w.lx_b);
       rq.ldo = d.E; rq.ldo2 = d.E;
       rq.out8 = nullptr; rq.out8_scales = nullptr;
       RUN(r, launch_splitk_reduce(r.s, rq));
+      lplanes = ceil_div(d.E, 256);
       if (taps) taps->put(r, at<float>(c, w.lx), (size_t)P * d.E);
       continue;
     }
@@ -839,9 +849,9 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     }
     // B5: down + residual
     r.cls = PI0_OP_LLM_DOWN;
-    gemm_splitk_resid(r, L.down, at<bf16>(c, w.lmid), d.F, P, d.F, zld, kps_ld, nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b),
-                      d.E, tld, at<float>(c, w.lstat), at<float>(c, w.g_l1[l + 1]));
-    lplanes = 0;
+    lplanes = gemm_splitk_resid(r, L.down, at<bf16>(c, w.lmid), d.F, P, d.F, zld, kps_ld, nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b),
+                                d.E, tld, at<float>(c, w.lstat), at<float>(c, w.g_l1[l + 1]), nullptr, 0, false, false, nullptr, nullptr,
+                                at<float>(c, w.lstat_parts), stat_rows);
     if (taps) taps->put(r, at<float>(c, w.lx), (size_t)P * d.E);
   }
   if (taps && taps->base) {

@@ -247,13 +247,19 @@ hipError_t gemm_init_attributes();
 // Split-K reduction: out[m][n] = sum_z part[z][m][n] (+bias[n]) (+resid[m % resid_mod][n]); bf16 shadow in XF
 // layout; (sum, sum sq) of each output row.  Z = 0: only the statistics and the MXFP8 copy of the rows in resid
 // (out_f32 and out_bf16 null).
+// Split-K partial sums of the LDS-staged GEMMs leave a block as its accumulators are: tile (32 tokens x 32 features) after
+// tile, 16 bytes per lane and 8-feature step, so that every store is 1 KiB in a row (row-major, a store of the accumulator
+// layout touches 32 rows of 32 bytes: 6 .. 11 us of the prefix down projection's 30 .. 60).  Element (row m, feature n) of a tile:
+static __device__ __forceinline__ int partial_tile_at(int m, int n) { return (n >> 3) * 256 + ((n >> 2) & 1) * 128 + m * 4 + (n & 3); }
 struct ReduceParams {
-  const float* part;  // [Z][M][ldp]
+  const float* part;  // [Z][M][ldp], or with tiled whole accumulator tiles [Z][ceil(M / 32)][ldp / 32][partial_tile_at]
   int Z, M, N, ldp;
+  int tiled;
   const float* bias;
   const float* resid;
   int resid_mod;      // row index of resid taken modulo this (0 = no modulo)
-  float* stat_out;    // [rows][2] or null
+  float* stat_out;    // [rows][2], tiled: one plane per 256 columns [ceil(N / 256)][stat_rows][2]; or null
+  int stat_rows;
   const float* gain;  // per-column scale of the bf16 shadow (gain of the norm that follows), or null
   float* out_f32;
   bf16* out_bf16;     // XF layout with ldo2 padded columns
