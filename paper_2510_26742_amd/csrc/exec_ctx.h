@@ -76,7 +76,18 @@ struct LaunchCtx {
   __device__ __forceinline__ void wait_inputs() const {}
   __device__ __forceinline__ void mark(int) const {}
   __device__ __forceinline__ int tid() const { return (int)threadIdx.x; }
+  static constexpr bool staged = false;
 };
+
+// Requests 1 KiB of a wave straight into LDS: lane l's 16 bytes at base + off land at byte address lds + 16 l.  Assembly,
+// because behind the builtin the compiler makes every LDS read wait for all loads in flight; whoever reads the data waits
+// for vmcnt(0) first.  base, lds: uniform
+__device__ __forceinline__ void request_to_lds(const char* base, unsigned off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ unsigned lds_address(const unsigned char* p) {
+  return (unsigned)(size_t)(__attribute__((address_space(3))) const unsigned char*)p;
+}
 
 // ------------------------------------------------------------------------------------------------
 // Grid barrier of the persistent kernel.  A block arrives by storing the epoch into its own word of its die's flag line
@@ -220,6 +231,7 @@ struct PersistCtxT {
   __amdgpu_buffer_rsrc_t arena;    // buffer resource over the activation arena
   const char* arena_base;
   GridBarrierT<TRACE>* bar;
+  bool staged = false;             // weights of the item's first feature tile are in the body's shared memory already
   int thread;                      // threadIdx.x, made opaque per operation: per-lane address arithmetic of one operation
                                    // is then not hoisted out of the layer loop, where it would hold registers throughout
 
@@ -260,7 +272,7 @@ struct PersistCtxT {
   template <bool B>
   __device__ __forceinline__ PersistCtxT<B, TRACE> as() const {
     PersistCtxT<B, TRACE> c;
-    c.bx = bx; c.by = by; c.bz = bz; c.arena = arena; c.arena_base = arena_base; c.bar = bar; c.thread = thread;
+    c.bx = bx; c.by = by; c.bz = bz; c.arena = arena; c.arena_base = arena_base; c.bar = bar; c.staged = staged; c.thread = thread;
     return c;
   }
 };

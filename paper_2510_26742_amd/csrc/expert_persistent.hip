@@ -21,6 +21,10 @@
 namespace {
 
 constexpr int PK_THREADS = 512;
+// Shared memory of a block: first the weights of one of gate||up's two feature tiles, which wait there, and then the partial
+// tiles of the 32-feature bodies; behind it the attention and the partial tiles of O and down, which run meanwhile.
+constexpr int PK_TAIL = (2 * 16 * 64 + 64) * SK_WAVES * 4;
+static_assert(PK_TAIL >= SK_WAVES * 8 * 1024 && ATTN_SUFFIX_SMEM >= SK_WAVES * 64 * 4 * 4, "the staged weights; the partial tiles of O and down");
 
 // Reading ahead inside the loop.  The expert's weights (623 MB) cycle through the 256 MB memory-side cache once per Euler
 // step, so an operation's weight request - issued when the operation before ends - goes all the way to HBM (the same loop
@@ -139,6 +143,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
   // cache when the QKV projection begins, and has it when the projection ends.
   const int att_off = P.qkv.n_tiles * 2 < (int)gridDim.x ? P.qkv.n_tiles * 2 : 0;
   const int att_block = (int)blockIdx.x >= att_off ? (int)blockIdx.x - att_off : (int)blockIdx.x + (int)gridDim.x - att_off;
+  const bool idle = att_block >= P.att_items;   // no item in the attention
   const int part_die = (att_off | P.att_items | (int)gridDim.x) & 7;   // 0: consecutive idle blocks are on consecutive dies, starting with item 0's
   bar.init(P.sync, P.spin_limit, att_block >= P.att_items);
   PersistCtx cx;
@@ -256,7 +261,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         if (a.ml_out != nullptr) a.ml_out = reinterpret_cast<float*>(slot + F.r_ml);
         const int att_gx = F.att_gx, att_gxy = F.att_gx * a.heads;
         for_items(F.att_items, [&](int it) {
-          attention_suffix_body(a, item(it % att_gx, (it % att_gxy) / att_gx, it / att_gxy).template as<true>(), smem_raw);
+          attention_suffix_body(a, item(it % att_gx, (it % att_gxy) / att_gx, it / att_gxy).template as<true>(), smem_raw + PK_TAIL);
         }, att_block);
         if (att_block >= F.att_items && (F.read_ahead & 15)) {   // no item: read ahead (constants only, no wait needed)
           const int part = att_block - F.att_items, nparts = (int)gridDim.x - F.att_items;
@@ -271,6 +276,14 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
           if (fold == 0x9e3779b9u) as_global(F.sync)[GB_SINK] = fold;
         }
         op_end();
+        // Behind the arrival, so behind nothing that anybody waits for: the first of the two feature tiles of this block's
+        // gate||up item, straight into LDS.  A gate||up block takes 128 KB of weights through its compute unit, 2.5 us between
+        // two operations that are 1.8 apart; half of them ahead, by the 160 .. 192 blocks that are idle here, take its span from
+        // 4.1 to 3.6 us and the hand-over in front of it from 1.5 to 0.6 (the others find the lines in their die's L2).  All of
+        // them, or the attention blocks' too, cost the attention's own loads more than they give: 1 / 3 views 3.66 .. 3.85 ms /
+        // 3.98 .. 4.2, none 3.71 / 4.05, half 3.63 / 3.95.  Ahead of the arrival or of the down weights it is slower.
+        if (idle && (int)blockIdx.x < F.gu.n_tiles)
+          skinny_stage_weights(as_global(F.gu.W.w) + (size_t)l * F.w_stride, F.gu.W.k_pad, (int)blockIdx.x % (F.gu.n_tiles / 2) * 2, lds_address(smem_raw), item(0, 0, 0).thread);
       }
       op_begin();
       {  // ---- C6: O projection + residual ------------------------------------------------------
@@ -284,7 +297,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         o.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_yb_o);
         o.stat_out = reinterpret_cast<float*>(slot + F.r_st_o);
         const int nx = o.n_tiles * 2;
-        for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<8>(o, item(it % nx, it / nx, 0).template as<true>(), smem_raw); });
+        for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<8>(o, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
         op_end();
       }
       op_begin();
@@ -299,7 +312,11 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         // two feature tiles x one token block per item: the same sums as one tile x both token blocks, half the
         // activation bytes per block behind the wait
         const int pairs = g.n_tiles / 2;
-        for_items(pairs * 2, [&](int it) { gemm_skinny_body<PRO_RMS, EPI_GEGLU, 2>(g, item(it % pairs, 0, it / pairs).template as<true>(), smem_raw); });
+        for_items(pairs * 2, [&](int it) {
+          auto c = item(it % pairs, 0, it / pairs).template as<true>();
+          c.staged = idle && it == (int)blockIdx.x;
+          gemm_skinny_body<PRO_RMS, EPI_GEGLU, 2>(g, c, smem_raw);
+        });
         op_end();
       }
       op_begin();
@@ -313,8 +330,8 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         d.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_yb_d);
         d.stat_out = reinterpret_cast<float*>(slot + F.r_st_d);
         const int nx = d.n_tiles * 2;
-        if (F.dn_ns == 16) for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<16>(d, item(it % nx, it / nx, 0).template as<true>(), smem_raw); });
-        else for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<8>(d, item(it % nx, it / nx, 0).template as<true>(), smem_raw); });
+        if (F.dn_ns == 16) for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<16>(d, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
+        else for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<8>(d, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
         op_end();
       }
     }
@@ -335,11 +352,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
 
 }  // namespace
 
-int expert_loop_smem_bytes() {
-  const int sk = (SK_WAVES * 2 * 16 * 64 + 128 + SK_WAVES * 128) * 4;
-  const int at = ATTN_SUFFIX_SMEM;
-  return sk > at ? sk : at;
-}
+int expert_loop_smem_bytes() { return PK_TAIL + ATTN_SUFFIX_SMEM; }
 
 hipError_t expert_loop_init_attributes() {
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&expert_loop_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -286,10 +286,10 @@ __device__ __forceinline__ void epilogue_tile(const GemmParams& p, const f32x16&
 
 // MS = 1: the two 32-token blocks go to separate blocks (gridDim.z = 2), which halves the activation
 // bytes per CU; used where the launch would otherwise leave most CUs idle (the expert's QKV).
-// Steps ib .. ib + NSTEP - 1 of one token block's tile: the 8 waves' partial tiles [wave][token block][step][lane][4] are
+// Steps ib .. ib + NSTEP - 1 of one token block's tile: the 8 waves' partial tiles [wave][slot][step][lane][4] are
 // added in wave order, then the epilogue runs on those steps.  stat: the 8 waves' sums of squares for this lane's row, 64
 // apart (with HALVES each in two parts, 32 apart).
-template <int PRO, int EPI, int NSTEP, bool HALVES, class Cx>
+template <int PRO, int EPI, int NSTEP, bool HALVES, int NSLOT, class Cx>
 __device__ __forceinline__ void skinny_finish(const GemmParams& p, const float* red, const float* stat, int mb /* slot */, int lane, int nt,
                                               int ml, int lh, const EpiOps& ops, const Cx& cx, int ib) {
   f32x4 part[SK_WAVES][NSTEP];
@@ -304,7 +304,7 @@ __device__ __forceinline__ void skinny_finish(const GemmParams& p, const float* 
 #pragma unroll
   for (int q = 0; q < NSTEP; q++)
 #pragma unroll
-    for (int ww = 0; ww < SK_WAVES; ww++) part[ww][q] = *reinterpret_cast<const f32x4*>(red + ((((size_t)ww * 2 + mb) * 4 + ib + q) * 64 + lane) * 4);
+    for (int ww = 0; ww < SK_WAVES; ww++) part[ww][q] = *reinterpret_cast<const f32x4*>(red + ((((size_t)ww * NSLOT + mb) * 4 + ib + q) * 64 + lane) * 4);
   __builtin_amdgcn_sched_barrier(0);   // every read in flight (left alone they are read and added one by one)
   float ssq = 0.f;
   if (PRO != PRO_NONE) {
@@ -323,6 +323,15 @@ __device__ __forceinline__ void skinny_finish(const GemmParams& p, const float* 
   if (ml < p.M) epilogue_tile<PRO, EPI, 0, NSTEP>(p, sum, nt, ml, lh, 0.f, ssq, cx.by, ops, cx, ib);
 }
 
+// The weights of feature tile nt into LDS, each wave what it will multiply: [wave][8 steps][1 KiB].  A wave reads back only what
+// it requested itself, after a vmcnt(0) of its own.
+__device__ __forceinline__ void skinny_stage_weights(const bf16* weights, int k_pad, int nt, unsigned lds, int t) {
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6), n16 = k_pad >> 4;
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+    request_to_lds(reinterpret_cast<const char*>(weights + ((size_t)nt * n16 + min(w * 8 + i, n16 - 1)) * 512), (unsigned)(t & 63) * 16u, lds + (unsigned)(w * 8 + i) * 1024u);
+}
+
 template <int PRO, int EPI, int MS, class Cx>
 __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx, unsigned char* smem_raw) {
   // MS = 0: one feature tile, both token blocks; 1: one feature tile, one token block (cx.bz); 2: two adjacent feature
@@ -331,7 +340,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   constexpr int NMB = MS == 0 ? 2 : 1;         // token blocks per block
   constexpr int NTL = MS == 2 ? 2 : 1;         // feature tiles per block
   constexpr int NSLOT = NMB * NTL;
-  float* red = reinterpret_cast<float*>(smem_raw);                 // [8 waves][2 slots][16][64]
+  float* red = reinterpret_cast<float*>(smem_raw);                 // [8 waves][slots][16][64]
   const int t = cx.tid();
   const int lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);   // uniform: addresses and branches below are scalar
@@ -355,7 +364,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
 
   // row statistics of the input: parts partial sums per row (1, or one per 32-column tile of the
   // producer); wave w adds parts w, w+8, ... for row `lane`, the epilogue adds the 8 wave sums
-  float* sstat8 = red + SK_WAVES * 2 * 16 * 64 + 128;   // [8 waves][64]
+  float* sstat8 = red + SK_WAVES * NSLOT * 16 * 64;   // [8 waves][64]
   bf16x8 wf[NTL][8], xf[NMB][8];
   // Wave w takes steps 8 w .. 8 w + 7 in two groups of 4 (a group beyond the range reads the last one and is not used).  A
   // load is a uniform base, a 32-bit offset that is in a register before the wait, and a constant.
@@ -395,10 +404,19 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
 #pragma unroll
     for (int h = 0; h < 2; h++) {
       if (w * 8 + 4 * h < n16) {   // uniform
+        if (cx.staged) {           // uniform: skinny_stage_weights put those of the first tile into LDS
 #pragma unroll
-        for (int i = 0; i < 4; i++)
+          for (int i = 0; i < 4; i++) {
+            wf[0][4 * h + i] = *reinterpret_cast<const bf16x8*>(smem_raw + (w * 8 + 4 * h + i) * 1024 + lane * 16);
 #pragma unroll
-          for (int j = 0; j < NTL; j++) wf[j][4 * h + i] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)j * KC16 * 1024 + off[h] + i * 1024);
+            for (int j = 1; j < NTL; j++) wf[j][4 * h + i] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)j * KC16 * 1024 + off[h] + i * 1024);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int j = 0; j < NTL; j++) wf[j][4 * h + i] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)j * KC16 * 1024 + off[h] + i * 1024);
+        }
       } else {
 #pragma unroll
         for (int i = 0; i < 4; i++)
@@ -471,7 +489,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
 #pragma unroll
     for (int q = 0; q < 4; q++) {   // 16-byte pieces: [wave][slot][q][lane][4]
       const f32x4 v4 = {acc[sl][4 * q], acc[sl][4 * q + 1], acc[sl][4 * q + 2], acc[sl][4 * q + 3]};
-      *reinterpret_cast<f32x4*>(red + ((((size_t)w * 2 + sl) * 4 + q) * 64 + lane) * 4) = v4;
+      *reinterpret_cast<f32x4*>(red + ((((size_t)w * NSLOT + sl) * 4 + q) * 64 + lane) * 4) = v4;
     }
   cx.mark(1);   // operands arrived, products done
   __syncthreads();
@@ -479,7 +497,7 @@ __device__ __forceinline__ void gemm_skinny_body(const GemmParams p, const Cx cx
   if (w >= NFIN) return;
   if (MS && cx.bz > mb_last) return;   // M <= 32: the second block of a split launch has nothing to store
   const int ml = mrow;
-  skinny_finish<PRO, EPI, NSTEP, NMB == 1>(p, red, sstat8 + (NMB == 1 ? lq : ml), fslot, lane, fnt, ml, lh, ops, cx, fpc * NSTEP);
+  skinny_finish<PRO, EPI, NSTEP, NMB == 1, NSLOT>(p, red, sstat8 + (NMB == 1 ? lq : ml), fslot, lane, fnt, ml, lh, ops, cx, fpc * NSTEP);
 }
 
 template <int PRO, int EPI, int MS = 0>

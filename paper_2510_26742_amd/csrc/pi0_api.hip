@@ -381,10 +381,10 @@ struct Tune {
   // the whole denoise loop as one persistent kernel with grid barriers (1) or one launch per operation (0)
   int pdn = 1;
   // ... in which the blocks without an attention item read ahead (bits: gate||up, down, next layer's QKV, next layer's O; 16: this layer's O, by the blocks
-  // with neither a QKV nor an attention item; 32: each what its own die will ask for).  Down and the next QKV: what the short
-  // attention leaves time for (pi0_denoise at 1 / 2 / 3 views, ms: nothing 3.87 / 4.06 / 4.19, gate||up 3.79 / 3.99 / 4.11,
-  // gate||up and down 3.87 / 4.09 / 4.26 - later than the attention ends -, down 3.77 / 3.97 / 4.11, these two 3.74 / 3.95 / 4.11)
-  int pra = 38;
+  // with neither a QKV nor an attention item; 32: each what its own die will ask for), ahead of staging half of their gate||up
+  // weights in LDS: down, by die.  pi0_denoise at 1 / 2 / 3 views and 3 views + 48 tokens, ms: nothing 3.74 / - / 4.06 / 4.34, next
+  // QKV 3.664 / 3.825 / 3.969 / 4.269, down and next QKV 3.684 / 3.853 / 4.010 / 4.297, down 3.630 / 3.787 / 3.945 / 4.249
+  int pra = 34;
   // two-stream frames: blocks of the persistent loop beside the prefill (0: per-operation launches).  A resident block
   // of the loop holds a whole compute unit, so its grid decides how the chip is shared between the two streams
   int psb = -1;           // -1: from the number of prefix tokens (frame_loop_blocks)
