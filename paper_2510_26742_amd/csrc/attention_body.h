@@ -6,6 +6,7 @@
 
 #define NEG_BIG (-1.0e30f)
 #define ATT_WAVES 8
+#define ATT_SHARE 10   // most chunks of prefix keys in a share of the expert's attention
 
 // MAXR: key rounds per wave over segment 0 (8 * MAXR chunks = 256 * MAXR keys); VRING: value
 // chunks in flight per wave.
@@ -369,11 +370,12 @@ template <int DQK>
 static constexpr int attn_smem_bytes(int ntot) { return 3 * (DQK / 16) * 1024 + 2 * ATT_WAVES * 32 * 4 + ntot * 2048; }
 
 // ------------------------------------------------------------------------------------------------
-// Attention of the action expert: 64 suffix rows over a share of the prefix cache (at most 8 chunks of 32 keys) and,
+// Attention of the action expert: 64 suffix rows over a share of the prefix cache (at most 10 chunks of 32 keys) and,
 // in the last share, the suffix's own two chunks.  An item is 16 query rows of one head (and 1 / v_split of the head
 // dimension of the output): mfma_f32_16x16x32 throughout.
 // What bounds it in the persistent kernel is what follows the wait for the QKV projection, so everything that comes from
-// the prefix cache is in registers before: wave w holds the keys of chunk w, and of the values its own 16 columns (two
+// the prefix cache is in registers before: wave w holds the keys of chunk w, waves 0 .. 3 one 16-key tile each of chunks 8 and
+// 9 (a prompt of up to 48 tokens behind whole views takes no share of its own), and of the values its own 16 columns (two
 // tiles of 16 with v_split 1) of every chunk.  After the wait each wave fetches one eighth of the 16 query rows (they
 // meet in LDS: read by every wave from memory they were 64 of the 112 KB that the first-level cache, 64 bytes per clock,
 // handed out behind the wait), waves 4 .. 7 one 16-key tile of the suffix each, and every wave its columns of the
@@ -412,8 +414,8 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
   const int nvb = 8 / vs;                      // 32-wide value slices of this item
   const int ntiles = 2 * nvb;                  // 16-column tiles of this item; this wave's are w and w + 8
   bf16* qlds = reinterpret_cast<bf16*>(smem_raw);                             // [8 steps of 32 k][64][8]
-  bf16* pf = qlds + 8 * 512;                                                  // [8 + 2 chunks][64][8]
-  float* mw = reinterpret_cast<float*>(pf + (ATT_WAVES + 2) * 512);           // [8][16]
+  bf16* pf = qlds + 8 * 512;                                                  // [8 + 2 of the suffix + 2 more][64][8]
+  float* mw = reinterpret_cast<float*>(pf + (ATT_SHARE + 2) * 512);           // [8][16]
   float* lw = mw + ATT_WAVES * 16;                                            // [8][16]
   const bf16x8 zero8 = __builtin_bit_cast(bf16x8, u32x4_t{0u, 0u, 0u, 0u});
   // a 16-row operand of 32 k is half of two 32 x 16 fragments: lane (g, i) takes k = 8 g .. + 7 of row i (bytes; + 2 KiB per 32 k)
@@ -426,7 +428,8 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
   };
 
   // ---- constants of the persistent kernel: keys and values of the prefix -------------------------------
-  bf16x8 kf[2][8], vf[2][ATT_WAVES];
+  bf16x8 kf[2][8], k1f[8], vf[2][ATT_SHARE];
+  const bool extra_wave = w < 4 && ATT_WAVES + (w >> 1) < n0;   // holds a 16-key tile of chunks 8 and 9
   auto load_prefix = [&]() {
     if (w < n0) {   // uniform
       const char* kp = reinterpret_cast<const char*>(p.k0 + (size_t)(cbeg0 + w) * S16 * 512);
@@ -438,11 +441,16 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
 #pragma unroll
       for (int j = 0; j < 8; j++) kf[0][j] = kf[1][j] = zero8;
     }
+    if (extra_wave) {
+      const char* kp = reinterpret_cast<const char*>(p.k0 + (size_t)(cbeg0 + ATT_WAVES + (w >> 1)) * S16 * 512 + (w & 1) * 64);
+#pragma unroll
+      for (int j = 0; j < 8; j++) k1f[j] = *at(kp, kpiece + j * 2048);
+    }
 #pragma unroll
     for (int a = 0; a < 2; a++) {
       const char* vp = vtile(p.v0 + (size_t)cbeg0 * 8 * 1024, w + ATT_WAVES * a);
 #pragma unroll
-      for (int c = 0; c < ATT_WAVES; c++) {
+      for (int c = 0; c < ATT_SHARE; c++) {
         if (c < n0 && w + ATT_WAVES * a < ntiles) vf[a][c] = *at(vp + (size_t)c * 16384, vpiece);   // uniform
         else vf[a][c] = zero8;
       }
@@ -473,12 +481,12 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
     cx.wait_inputs();
   }
   // ---- inputs: query rows, suffix keys (waves 4 .. 7: 16-key tile w - 4), suffix values ---------------
-  bf16x8 k1f[8], v1f[2][2];                    // v1f: [column tile][chunk]
+  bf16x8 v1f[2][2];                            // [column tile][chunk]
   const bf16x8 qv = cx.ld_bulk(at(qsrc, qpiece));
   if (seg1_wave) {
 #pragma unroll
     for (int j = 0; j < 8; j++) k1f[j] = cx.ld_bulk(at(k1src, kpiece + j * 2048));
-  } else {
+  } else if (!extra_wave) {
 #pragma unroll
     for (int j = 0; j < 8; j++) k1f[j] = zero8;
   }
@@ -531,7 +539,10 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
 #pragma unroll
       for (int e = 0; e < 4; e++) sv[h][e] = w < n0 && (cbeg0 + w) * 32 + kg + 8 * h + e < p.valid0 ? sv[h][e] : NEG_BIG;
   }
-  if (!seg1_wave) {   // uniform
+  if (extra_wave) {   // uniform
+#pragma unroll
+    for (int e = 0; e < 4; e++) sv1[e] = (cbeg0 + ATT_WAVES + (w >> 1)) * 32 + kg + 8 * (w & 1) + e < p.valid0 ? sv1[e] : NEG_BIG;
+  } else if (!seg1_wave) {
     sv1 = f32x4{NEG_BIG, NEG_BIG, NEG_BIG, NEG_BIG};
   } else if (p.suffix_mask) {
 #pragma unroll
@@ -571,11 +582,11 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
       for (int e = 0; e < 4; e++) pb[4 * h + e] = (bf16)prob(sv[h][e]);
     *reinterpret_cast<bf16x8*>(pf + ((size_t)w * 64 + lane) * 8) = pb;
   }
-  if (w >= 4) {   // uniform
+  if (w >= 4 || n0 > ATT_WAVES) {   // uniform: the suffix's from waves 4 .. 7, then chunks 8 and 9 from waves 0 .. 3
     bf16x4 pb;
 #pragma unroll
     for (int e = 0; e < 4; e++) pb[e] = (bf16)prob(sv1[e]);
-    *reinterpret_cast<bf16x4*>(pf + ((size_t)(ATT_WAVES + (tile1 >> 1)) * 64 + lane) * 8 + (tile1 & 1) * 4) = pb;
+    *reinterpret_cast<bf16x4*>(pf + ((size_t)(ATT_WAVES + ((w ^ 4) >> 1)) * 64 + lane) * 8 + (w & 1) * 4) = pb;
   }
   l_loc = add_xor32(add_xor16(l_loc));
   if (g == 0) lw[w * 16 + qi] = l_loc;
@@ -601,6 +612,14 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
 #pragma unroll
     for (int a = 0; a < 2; a++)
       o[a][c & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c < ATT_WAVES ? vf[a][c] : v1f[a][c - ATT_WAVES], b[c], o[a][c & 1], 0, 0, 0);
+  if (n0 > ATT_WAVES) {   // uniform; without the branch these two chunks cost the shares that have none 0.15 us
+#pragma unroll
+    for (int c = ATT_WAVES; c < ATT_SHARE; c++) {
+      const bf16x8 bc = *reinterpret_cast<const bf16x8*>(pf + ((size_t)(c + 2) * 64 + lane) * 8);
+#pragma unroll
+      for (int a = 0; a < 2; a++) o[a][c & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[a][c], bc, o[a][c & 1], 0, 0, 0);
+    }
+  }
   cx.mark(4);   // P V done
   float l_all = 0.f;
 #pragma unroll
@@ -624,10 +643,10 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
 }
 
 // query rows, probabilities, row maxima and sums
-static constexpr int ATTN_SUFFIX_SMEM = 8 * 1024 + (ATT_WAVES + 2) * 1024 + 2 * ATT_WAVES * 16 * 4;
+static constexpr int ATTN_SUFFIX_SMEM = 8 * 1024 + (ATT_SHARE + 2) * 1024 + 2 * ATT_WAVES * 16 * 4;
 // shapes attention_suffix_body covers: n0 = prefix chunks per share
 static inline bool attn_suffix_ok(const AttnParams& p, int n0) {
   const int vs = p.v_split > 1 ? p.v_split : 1;
   return p.head_dim == 256 && p.chunks1 == 2 && p.Tq == 64 && p.view_tokens == 0 && p.kv_head_stride0 == 0 && p.v_head_stride0 == 0 &&
-         n0 >= 1 && n0 <= 8 && (vs == 1 || vs == 2 || vs == 4 || vs == 8);
+         n0 >= 1 && n0 <= ATT_SHARE && (vs == 1 || vs == 2 || vs == 4 || vs == 8);
 }

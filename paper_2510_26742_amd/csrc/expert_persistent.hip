@@ -132,7 +132,9 @@ __global__ __launch_bounds__(PREP_THREADS) void expert_loop_prepare_kernel(Exper
   if (i < (GB_WORDS - GB_START) / 4) reinterpret_cast<uint4*>(sync + GB_START)[i] = uint4{0u, 0u, 0u, 0u};
 }
 
-template <bool TRACE>
+// DN_NS: k steps per wave of the down projection, 16 or 8.  A kernel for each: the other one's code, never run, pushed the
+// kernel over the 64 KB of instruction cache that two compute units share (pi0_denoise +25 us).
+template <bool TRACE, int DN_NS>
 __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoopParams* __restrict__ params) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   using PersistCtx = PersistCtxT<false, TRACE>;
@@ -330,8 +332,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         d.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_yb_d);
         d.stat_out = reinterpret_cast<float*>(slot + F.r_st_d);
         const int nx = d.n_tiles * 2;
-        if (F.dn_ns == 16) for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<16>(d, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
-        else for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<8>(d, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
+        for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<DN_NS>(d, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
         op_end();
       }
     }
@@ -354,22 +355,28 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
 
 int expert_loop_smem_bytes() { return PK_TAIL + ATTN_SUFFIX_SMEM; }
 
+namespace {
+const void* const kernels[4] = {reinterpret_cast<const void*>(&expert_loop_kernel<false, 8>), reinterpret_cast<const void*>(&expert_loop_kernel<false, 16>),
+                                reinterpret_cast<const void*>(&expert_loop_kernel<true, 8>), reinterpret_cast<const void*>(&expert_loop_kernel<true, 16>)};
+}
+
 hipError_t expert_loop_init_attributes() {
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&expert_loop_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           expert_loop_smem_bytes());
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&expert_loop_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             expert_loop_smem_bytes());
+  for (const void* k : kernels) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, expert_loop_smem_bytes());
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t expert_loop_max_blocks_per_cu(int* out) {
-  int traced = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&traced, reinterpret_cast<const void*>(&expert_loop_kernel<true>), PK_THREADS,
-                                                              expert_loop_smem_bytes());
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(out, reinterpret_cast<const void*>(&expert_loop_kernel<false>), PK_THREADS,
-                                                                        expert_loop_smem_bytes());
-  if (e == hipSuccess && traced < *out) *out = traced;
-  return e;
+  *out = 1 << 30;
+  for (const void* k : kernels) {
+    int n = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, PK_THREADS, expert_loop_smem_bytes());
+    if (e != hipSuccess) return e;
+    if (n < *out) *out = n;
+  }
+  return hipSuccess;
 }
 
 // Host-side checks of everything the kernel's indexing assumes.
@@ -412,7 +419,7 @@ hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLo
   }
   if ((P.o.W.k_pad >> 4) != 128 || P.dn_ns != ((P.dn.W.k_pad >> 4) == 256 ? 16 : 8) || P.m16 != (P.o.M + 15) / 16) return hipErrorInvalidValue;
   if (P.o.xsplits > 1 && (P.o.xsplits > 4 || P.o.xsplit_ml == nullptr || P.o.xsplit_stride < (size_t)64 * P.o.ldx)) return hipErrorInvalidValue;
-  // attention: head dim 256, at most 8 prefix chunks per share, the suffix's own 2 chunks as second segment
+  // attention: head dim 256, at most 10 prefix chunks per share, the suffix's own 2 chunks as second segment
   const AttnParams& a = P.att;
   if (a.q == nullptr || a.k0 == nullptr || a.v0 == nullptr || a.k1 == nullptr || a.v1 == nullptr || a.out == nullptr) return hipErrorInvalidValue;
   if (a.head_dim != 256 || a.Tq != 64 || a.chunks1 != 2 || a.heads < 1 || a.chunks0 < 1 || a.valid0 < 1 || a.valid0 > a.chunks0 * 32)
@@ -435,7 +442,6 @@ hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLo
   hipLaunchKernelGGL(expert_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, P.sync);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (P.trace != nullptr) hipLaunchKernelGGL(expert_loop_kernel<true>, dim3(blocks), dim3(PK_THREADS), expert_loop_smem_bytes(), s, d_params);
-  else hipLaunchKernelGGL(expert_loop_kernel<false>, dim3(blocks), dim3(PK_THREADS), expert_loop_smem_bytes(), s, d_params);
-  return hipGetLastError();
+  void* args[] = {&d_params};
+  return hipLaunchKernel(kernels[(P.trace != nullptr ? 2 : 0) + (P.dn_ns == 16 ? 1 : 0)], dim3(blocks), dim3(PK_THREADS), args, expert_loop_smem_bytes(), s);
 }

@@ -877,12 +877,15 @@ struct ExpertShares { int shares, per_share, v_split; };
 ExpertShares expert_shares(const pi0_ctx* c, int pchunks) {
   const Tune& T = c->tune;
   ExpertShares s{1, pchunks, 1};
-  const int per = T.kcps > 0 ? T.kcps : 8;   // a chunk per wave; the last share, with the suffix, is the short one
-  if (T.ksplit && T.ae16 && c->d.H == 8 && pchunks > per && ceil_div(pchunks, per) <= 4) {
-    s.shares = ceil_div(pchunks, per);
-    s.per_share = per;
+  // As few shares as the attention's registers allow (10 chunks), because the O projection reads every one of them, and of one
+  // size.  Shares of 8 gave a prompt behind whole views one of its own: pi0_denoise with shares of 8 / 10, ms, 1 view + 7 tokens
+  // 3.822 / 3.640, 2 views + 21 3.974 / 3.832, 3 views + 48 4.299 / 3.965.
+  const int most = T.kcps > 0 ? T.kcps : 10, shares = ceil_div(pchunks, most);
+  if (T.ksplit && T.ae16 && c->d.H == 8 && shares > 1 && shares <= 4) {
+    s.shares = shares;
+    s.per_share = T.kcps > 0 ? T.kcps : ceil_div(pchunks, shares);
   }
-  s.v_split = T.avs > 0 ? T.avs : s.per_share > 8 ? 4 : s.shares >= 2 ? 1 : 2;
+  s.v_split = T.avs > 0 ? T.avs : s.per_share > 10 ? 4 : s.shares >= 2 ? 1 : 2;
   return s;
 }
 
@@ -900,7 +903,7 @@ bool persistent_feasible(const pi0_ctx* c, int P) {
   const int pchunks = ceil_div(P, 32);
   if (!T.ae16 || !T.qms || d.H != 8 || d.X > SK_KMAX_HOST || d.X % 256 != 0) return false;
   const ExpertShares es = expert_shares(c, pchunks);
-  if (es.shares > 4 || es.per_share > 8 || (es.v_split & (es.v_split - 1)) != 0) return false;
+  if (es.shares > 4 || es.per_share > 10 || (es.v_split & (es.v_split - 1)) != 0) return false;
   const WsTr& L0 = w.exp[0];
   if (L0.o.k_pad != 2048 || (L0.down.k_pad != 2048 && L0.down.k_pad != 4096)) return false;
   if (d.Le > 1) {
@@ -1234,7 +1237,7 @@ void run_denoise(Run& r, int P, Taps* taps) {
         // a launch requests the prefix keys and values itself: as many blocks as there are compute units, each with fewer
         // values (the sums do not depend on it: a column of the output is one wave's work either way)
         a.v_split = es.v_split;
-        if (T.avs <= 0 && es.per_share <= 8) a.v_split = (es.shares == 1 ? 8 : es.shares == 2 ? 4 : 2) / (warm && es.shares <= 2 ? 2 : 1);
+        if (T.avs <= 0 && es.per_share <= 10) a.v_split = (es.shares == 1 ? 8 : es.shares == 2 ? 4 : 2) / (warm && es.shares <= 2 ? 2 : 1);
         a.pf = pf_begin(pfb ? T.pfa : warm && 4 * std::max(1, a.v_split) * d.H * es.shares <= 128 ? 128 : 0);
         pf_weights(a.pf, 0, L.gu);
         r.cls = PI0_OP_EXP_ATTN;

@@ -11,3 +11,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("v_split", [1, 2, 4, 8])
 def test_prefix_lengths_and_value_splits(P, chunks_per_share, v_split):
     base.test_expert_attention_block_mask_and_key_shares(P, chunks_per_share, v_split)
+
+
+# a ninth and a tenth chunk, each with its first 16-key tile only, ending inside a tile, and full; the last share with fewer
+@pytest.mark.parametrize("P,chunks_per_share", [(257, 0), (271, 0), (288, 0), (290, 0), (305, 0), (320, 0), (530, 9), (561, 9), (625, 10), (816, 9)])
+@pytest.mark.parametrize("v_split", [1, 2, 8])
+def test_shares_of_nine_and_ten_chunks(P, chunks_per_share, v_split):
+    base.test_expert_attention_block_mask_and_key_shares(P, chunks_per_share, v_split)
