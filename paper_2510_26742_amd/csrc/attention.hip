@@ -7,8 +7,11 @@
 // epilogue), so every operand fetch is one coalesced 16-byte-per-lane read from L2.
 //
 // One block of 8 waves owns 32 query rows of one head (attention_body).  The action expert has a body of its own, 16 query
-// rows per block, for shares of up to 8 prefix chunks (attention_suffix_body, attn_suffix_ok).  Wider shares (geometries
-// without 8 heads, pi0_tune) and other numbers of rows (pi0_attention_probe only) run here, with the second segment below.
+// rows per block, for shares of up to 10 prefix chunks (attention_suffix_body, attn_suffix_ok), which also takes the prefix's own
+// attention over up to 10 chunks: half the products per block, twice the blocks (17 launches at 256 / 263 / 304 tokens, prefill
+// 3.125 / 3.360 / 3.441 -> 3.101 / 3.304 / 3.395 ms; a head's values shared out over two blocks 3.103 / 3.371 / 3.455).  Wider shares
+// (geometries without 8 heads, pi0_tune), longer prefixes and other numbers of rows (pi0_attention_probe only) run here, with
+// the second segment below.
 // The kernels of this pass are short and bound by memory round trips, not by arithmetic, so the block is organised to need one round
 // trip when the prefix has at most 8 chunks of 32 keys: at entry every wave issues its loads of Q
 // (to LDS), of the key fragments of "its" prefix chunks (chunk index = wave, wave + 8, ...), of

@@ -644,9 +644,10 @@ __device__ __forceinline__ void attention_suffix_body(const AttnParams p, const 
 
 // query rows, probabilities, row maxima and sums
 static constexpr int ATTN_SUFFIX_SMEM = 8 * 1024 + (ATT_SHARE + 2) * 1024 + 2 * ATT_WAVES * 16 * 4;
-// shapes attention_suffix_body covers: n0 = prefix chunks per share
+// shapes attention_suffix_body covers: n0 = prefix chunks per share; the expert's rows with their own two chunks, or any number
+// of rows without
 static inline bool attn_suffix_ok(const AttnParams& p, int n0) {
   const int vs = p.v_split > 1 ? p.v_split : 1;
-  return p.head_dim == 256 && p.chunks1 == 2 && p.Tq == 64 && p.view_tokens == 0 && p.kv_head_stride0 == 0 && p.v_head_stride0 == 0 &&
+  return p.head_dim == 256 && (p.chunks1 == 0 || (p.chunks1 == 2 && p.Tq == 64)) && p.view_tokens == 0 && p.kv_head_stride0 == 0 && p.v_head_stride0 == 0 &&
          n0 >= 1 && n0 <= ATT_SHARE && (vs == 1 || vs == 2 || vs == 4 || vs == 8);
 }

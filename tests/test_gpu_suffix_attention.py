@@ -18,3 +18,9 @@ def test_prefix_lengths_and_value_splits(P, chunks_per_share, v_split):
 @pytest.mark.parametrize("v_split", [1, 2, 8])
 def test_shares_of_nine_and_ten_chunks(P, chunks_per_share, v_split):
     base.test_expert_attention_block_mask_and_key_shares(P, chunks_per_share, v_split)
+
+
+# the prefix's own attention, any number of query rows over up to ten chunks, and one row more than this kernel takes
+@pytest.mark.parametrize("P", [1, 17, 31, 33, 255, 257, 273, 288, 320, 321])
+def test_prefix_of_up_to_ten_chunks(P):
+    base.test_prefix_attention_shared_head(P)
