@@ -181,8 +181,11 @@ def main() -> int:
         lo, hi = 1 + 4 * per_step, 1 + 6 * per_step          # Euler steps 4 and 5: steady state
         rows = {}
         for i in range(lo, hi):
-            a, nxt = t[i], t[i + 1]
+            a = t[i]
             work = a[:, 1] > 0
+            if not work.any():      # part of the operation before
+                continue
+            nxt = next(x for x in t[i + 1:] if (x[:, 1] > 0).any())
             enter, waited, done, arr = a[:, 0], a[:, 1], a[:, 2], a[:, 3]
             nwork = nxt[:, 1] > 0
             d = {"items": int(work.sum()),

@@ -200,7 +200,8 @@ int pi0_sync_dep_bench(int barrier, int data, int fan, int n_ops, int reps, floa
  * attention - Q in shared memory, scores done, probabilities in shared memory, P V done.
  *   d_trace  device, int64 [ops_cap][256 blocks][8], 8-byte aligned; NULL with ops_cap 0 switches the timeline off
  *   operations are numbered in execution order: 0 = state token; per Euler step: embed, second linear, per layer
- *   QKV, attention, O, gate||up, down; then out-projection + Euler.  pi0_loop_trace_ops gives their number.
+ *   QKV, attention, O, gate||up, down; then out-projection + Euler, which is one with the embedding of the next step (whose
+ *   own entry then holds zeros).  pi0_loop_trace_ops gives their number.
  * Drops every captured graph.  Must not be called while work of this ctx is in flight.  Errors: EINVAL.
  */
 int pi0_loop_trace_ops(const pi0_ctx* ctx);

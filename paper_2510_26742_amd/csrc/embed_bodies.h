@@ -45,8 +45,20 @@ struct ActionEmbedArgs {
 // Rows (cx.by) 0 .. chunk-1 -> z[r]; row chunk -> state token copy and zero z[chunk].
 // The state row also gets its gain-scaled bf16 copy and, per 32 columns, its (sum, sum of squares) in
 // stat_parts[tile][64 rows][2] (row 0), the form the first QKV GEMM of the step reads.
+// In two parts, so that the persistent kernel can request the weights ahead of its wait; x_of(j): the row's values (at most 32).
+struct ActionEmbedWeights { float w[32], bias; };
+
 template <class Cx>
-__device__ __forceinline__ void action_embed_body(const ActionEmbedArgs a, const Cx cx) {
+__device__ __forceinline__ void action_embed_load(const ActionEmbedArgs& a, const Cx& cx, ActionEmbedWeights& e) {
+  const int n = cx.bx * 256 + cx.tid();
+  if (cx.tid() >= 256 || n >= a.X || cx.by >= a.chunk) return;
+  e.bias = a.bias_k[n];
+#pragma unroll
+  for (int u = 0; u < 32; u++) e.w[u] = a.wfold[(size_t)min(u, a.A - 1) * a.X + n];   // clamped, unconditional
+}
+
+template <class Cx, class XOf>
+__device__ __forceinline__ void action_embed_finish(const ActionEmbedArgs& a, const Cx& cx, const ActionEmbedWeights& e, XOf&& x_of) {
   const int tx = cx.tid();
   if (tx >= 256) return;
   const int n = cx.bx * 256 + tx;
@@ -54,22 +66,14 @@ __device__ __forceinline__ void action_embed_body(const ActionEmbedArgs a, const
   const int X = a.X, A = a.A, chunk = a.chunk;
   if (n >= X) return;
   if (r < chunk) {
-    // all loads of (up to) 32 terms issued together - the x values cross blocks, i.e. come from memory, and a batch
-    // that waits for the one before costs a round trip each (4 batches of 8: 3.9 us per operation) - then accumulated
-    // in index order
-    float acc = a.bias_k[n];
-    for (int j0 = 0; j0 < A; j0 += 32) {
-      float wv[32], xv[32];
+    // all values requested together - a batch that waits for the one before costs a round trip each (4 batches of 8: 3.9 us
+    // per operation) - then accumulated in index order
+    float xv[32], acc = e.bias;
 #pragma unroll
-      for (int u = 0; u < 32; u++) {
-        const int j = min(j0 + u, A - 1);
-        xv[u] = cx.ld(a.x + (size_t)r * A + j);
-        wv[u] = a.wfold[(size_t)j * X + n];
-      }
+    for (int u = 0; u < 32; u++) xv[u] = x_of(min(u, A - 1));
 #pragma unroll
-      for (int u = 0; u < 32; u++) {
-        if (j0 + u < A) acc += xv[u] * wv[u];
-      }
+    for (int u = 0; u < 32; u++) {
+      if (u < A) acc += xv[u] * e.w[u];
     }
     const float sv = acc / (1.0f + __expf(-acc));
     cx.st(a.z + xf_index(r, n, X >> 4), (bf16)sv);
@@ -86,4 +90,11 @@ __device__ __forceinline__ void action_embed_body(const ActionEmbedArgs a, const
     }
     if ((tx & 31) == 0) cx.st(reinterpret_cast<float2*>(a.stat_parts + (size_t)(n >> 5) * 128), make_float2(sa, sb));
   }
+}
+
+template <class Cx>
+__device__ __forceinline__ void action_embed_body(const ActionEmbedArgs a, const Cx cx) {
+  ActionEmbedWeights e;
+  action_embed_load(a, cx, e);
+  action_embed_finish(a, cx, e, [&](int j) { return cx.ld(a.x + (size_t)cx.by * a.A + j); });
 }

@@ -10,10 +10,11 @@ struct ExpertLoopParams {
   AttnParams att;
   StateTokenArgs stok;
   struct {
-    ActionEmbedArgs a;            // a.bias_k = row of step 0 (rows a.X floats apart); a.x == x_rw
-    float* x_rw;                  // x of the Euler integration [chunk][action_dim], inside the arena; holds the actions at the end
+    ActionEmbedArgs a;            // a.bias_k = row of step 0 (rows a.X floats apart)
+    float* x_rw[2];               // x of the Euler integration [chunk][action_dim], inside the arena: a step reads what the one before
+                                  // wrote into the other buffer; [0] holds the actions at the end
   } emb;
-  const float* noise;             // [x_elems] initial x (staged input, constant during the kernel)
+  const float* noise;             // [x_elems] initial x (staged input, constant during the kernel), inside the arena
   int x_elems;
   int layers, steps;
   int read_ahead;                 // bit i set: blocks without an attention item read ahead range i of {gate||up, down, next QKV, next O}; 16: blocks with no QKV item either read this layer's O; 32: shared out by die

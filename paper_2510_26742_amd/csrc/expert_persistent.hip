@@ -122,6 +122,25 @@ __device__ __forceinline__ AttnParams global(const AttnParams& src) {
   return p;
 }
 
+// The out-projection's context where every block computes the rows of x that it goes on with: they come from one buffer and go
+// to LDS and, from one block, to another buffer.
+template <bool TRACE>
+struct EulerCtx : PersistCtxT<true, TRACE> {
+  const float* from;
+  float* to;
+  float* lds;
+  int first;      // element of x that comes first in LDS
+  bool publish;
+  __device__ __forceinline__ EulerCtx(const PersistCtxT<true, TRACE>& c, const float* from_, float* to_, float* lds_, int first_, bool publish_)
+      : PersistCtxT<true, TRACE>(c), from(from_), to(to_), lds(lds_), first(first_), publish(publish_) {}
+  using PersistCtxT<true, TRACE>::st;
+  __device__ __forceinline__ void st(float* p, const float& v) const {
+    const int i = (int)(p - from);
+    lds[i - first] = v;
+    if (publish) PersistCtxT<true, TRACE>::st(to + i, v);
+  }
+};
+
 // parameter block to device memory and barrier words to zero (the error word, first, stays as it is).  A piece per thread,
 // both in one launch: the block copied by one thread took 7 us and the words a launch of their own.
 constexpr int PREP_THREADS = 256;
@@ -180,6 +199,10 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
     if (slot != nullptr && threadIdx.x == 0) slot[3] = (long long)wall_clock64();
     opi++;
   };
+  auto op_skip = [&]() {   // an operation of the timeline's numbering that nobody has an item in
+    if (TRACE && trace != nullptr && opi < trace_ops && threadIdx.x < 8) trace[((size_t)opi * gridDim.x + blockIdx.x) * 8 + threadIdx.x] = 0;
+    if (TRACE) opi++;
+  };
   auto item = [&](int bx, int by, int bz) {
     PersistCtx c = cx;
     c.bx = bx; c.by = by; c.bz = bz;
@@ -190,164 +213,180 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
   };
 
   op_begin();
-  // ---- C0: state token; x <- noise ---------------------------------------------------------------
+  // ---- C0: state token -----------------------------------------------------------------------------
   for_items((P.stok.X + 255) / 256, [&](int it) { state_token_body(P.stok, item(it, 0, 0)); });
-  if ((int)blockIdx.x == (int)gridDim.x - 1) {
-    for (int i = threadIdx.x; i < P.x_elems; i += PK_THREADS) cx.st(P.emb.x_rw + i, as_global(P.noise)[i]);
-  }
   op_end();
 
   const int emb_cols = (P.emb.a.X + 255) / 256;
   const int steps = P.steps, layers = P.layers;
-  for (int k = 0; k < steps; k++) {
-    op_begin();
-    {  // ---- C1: folded action/time embedding + SiLU; suffix row 0 <- state token ----------------
-      ActionEmbedArgs a = fresh(Pg).emb.a;
-      a.bias_k += (size_t)k * a.X;
-      bool waited = false;
-      for_items(emb_cols * (a.chunk + 1), [&](int it) {
-        if (!waited) { bar.wait(); waited = true; }
-        action_embed_body(a, item(it % emb_cols, it / emb_cols, 0));
-      });
+  // ---- C9 of step k: final RMS -> out-projection (+bias), Euler update x <- x + dt * v; C1 of step k + 1: folded action/time
+  // embedding + SiLU, suffix row 0 <- state token.  One operation: the 32 rows of x that hold a block's row are one item of
+  // the out-projection, which every block computes for itself (64 KB behind the wait, as for QKV) and leaves in LDS; one block
+  // of each half also writes them out.  As two operations they were 3.4 + 0.6 + 3.1 us, ten times.  k = -1: the embedding alone.
+  auto euler_embed = [&](int k) {
+    const ExpertLoopParams& F = fresh(Pg);
+    const bool more = k + 1 < steps;
+    ActionEmbedArgs a = F.emb.a;
+    a.wfold = as_global(a.wfold);
+    a.gain = as_global(a.gain);
+    a.bias_k = as_global(a.bias_k) + (size_t)(k + 1) * a.X;
+    GemmParams u = global(F.outp);
+    char* slot = as_global(F.ring) + (size_t)(max(k, 0) * layers + layers - 1) * F.ring_stride;
+    u.X = reinterpret_cast<const bf16*>(slot + F.r_yb_d);
+    u.rowstat = reinterpret_cast<const float*>(slot + F.r_st_d);
+    float* const written = F.emb.x_rw[(steps - 1 - k) & 1];
+    const float* const read = k <= 0 ? F.noise : F.emb.x_rw[(steps - k) & 1];
+    u.out_f32 = const_cast<float*>(read);
+    float* const xs = reinterpret_cast<float*>(smem_raw + PK_TAIL);   // [32 rows][A]
+    for_items(emb_cols * (a.chunk + 1), [&](int it) {
+      const int bx = it % emb_cols, r = it / emb_cols, half = (r + 1) >> 5;   // x row r is suffix row r + 1
+      const bool row = r < a.chunk, publish = bx == 0 && (r == 0 || ((r + 1) & 31) == 0);
+      if (!more && !(row && publish)) return;
+      const PersistCtx c = item(bx, r, 0);
+      ActionEmbedWeights e;
+      if (more) action_embed_load(a, c, e);
+      if (k >= 0 && row) {
+        gemm_skinny_body<PRO_RMS, EPI_EULER, 1>(u, EulerCtx<TRACE>(item(0, 0, half).template as<true>(), read, written, xs, (32 * half - 1) * a.A, publish), smem_raw);
+      } else {
+        bar.wait();
+        if (row && c.thread < a.A) xs[((r + 1) & 31) * a.A + c.thread] = cx.ld(read + (size_t)r * a.A + c.thread);
+      }
+      __syncthreads();
+      if (more) action_embed_finish(a, c, e, [&](int j) { return xs[((r + 1) & 31) * a.A + j]; });
+    });
+  };
+  for (int k = -1; k < steps; k++) {
+    if (k >= 0) {
+      op_begin();
+      // ---- C2: second linear of the action/time MLP -> suffix rows 1 .. chunk --------------------------
+      {
+        const GemmParams t = global(fresh(Pg).tout);
+        for_items(t.n_tiles * 2, [&](int it) { gemm_skinny_body<PRO_NONE, EPI_RESID, 1>(t, item(it % t.n_tiles, 0, it / t.n_tiles), smem_raw); });
+      }
       op_end();
-    }
-    op_begin();
-    // ---- C2: second linear of the action/time MLP -> suffix rows 1 .. chunk --------------------------
-    {
-      const GemmParams t = global(fresh(Pg).tout);
-      for_items(t.n_tiles * 2, [&](int it) { gemm_skinny_body<PRO_NONE, EPI_RESID, 1>(t, item(it % t.n_tiles, 0, it / t.n_tiles), smem_raw); });
-    }
-    op_end();
-    for (int l = 0; l < layers; l++) {
-      op_begin();
-      {  // ---- C3: RMS -> QKV, RoPE at positions P .. P + 63 -------------------------------------
-        const ExpertLoopParams& F = fresh(Pg);
-        GemmParams q = global(F.qkv);
-        q.W.w += (size_t)l * F.w_stride;
-        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
-        q.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_q);
-        q.kfrag = reinterpret_cast<bf16*>(slot + F.r_k);
-        q.vfrag = reinterpret_cast<bf16*>(slot + F.r_v);
-        if (l == 0) {   // input: the step's embedding (two operations wrote its rows)
-          q.rowstat_parts = F.parts_first;
-          for_items(q.n_tiles * 2, [&](int it) { gemm_skinny_body<PRO_RMS, EPI_QKV, 1>(q, item(it % q.n_tiles, 0, it / q.n_tiles), smem_raw); });
-        } else {
-          q.rowstat_parts = F.parts_rest;
-          q.X = reinterpret_cast<const bf16*>(slot - F.ring_stride + F.r_yb_d);
-          q.rowstat = reinterpret_cast<const float*>(slot - F.ring_stride + F.r_st_d);
-          for_items(q.n_tiles * 2, [&](int it) {
-            gemm_skinny_body<PRO_RMS, EPI_QKV, 1>(q, item(it % q.n_tiles, 0, it / q.n_tiles).template as<true>(), smem_raw);
+      for (int l = 0; l < layers; l++) {
+        op_begin();
+        {  // ---- C3: RMS -> QKV, RoPE at positions P .. P + 63 -------------------------------------
+          const ExpertLoopParams& F = fresh(Pg);
+          GemmParams q = global(F.qkv);
+          q.W.w += (size_t)l * F.w_stride;
+          char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
+          q.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_q);
+          q.kfrag = reinterpret_cast<bf16*>(slot + F.r_k);
+          q.vfrag = reinterpret_cast<bf16*>(slot + F.r_v);
+          if (l == 0) {   // input: the step's embedding (two operations wrote its rows)
+            q.rowstat_parts = F.parts_first;
+            for_items(q.n_tiles * 2, [&](int it) { gemm_skinny_body<PRO_RMS, EPI_QKV, 1>(q, item(it % q.n_tiles, 0, it / q.n_tiles), smem_raw); });
+          } else {
+            q.rowstat_parts = F.parts_rest;
+            q.X = reinterpret_cast<const bf16*>(slot - F.ring_stride + F.r_yb_d);
+            q.rowstat = reinterpret_cast<const float*>(slot - F.ring_stride + F.r_st_d);
+            for_items(q.n_tiles * 2, [&](int it) {
+              gemm_skinny_body<PRO_RMS, EPI_QKV, 1>(q, item(it % q.n_tiles, 0, it / q.n_tiles).template as<true>(), smem_raw);
+            });
+          }
+          if (att_block >= F.att_items && (int)blockIdx.x >= q.n_tiles * 2 && (F.read_ahead & 48)) {   // no item here nor in the attention
+            const int tid = item(0, 0, 0).thread;
+            const int idle = (int)gridDim.x - (q.n_tiles * 2 > att_off + F.att_items ? q.n_tiles * 2 : att_off + F.att_items);
+            const int part = (int)gridDim.x - 1 - (int)blockIdx.x;
+            unsigned fold = 0;
+            if (F.read_ahead & 16) fold = read_ahead_weights<0>(as_global(F.o.W.w) + (size_t)l * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, idle, false, tid, fold);
+            if (fold == 0x9e3779b9u) as_global(F.sync)[GB_SINK] = fold;
+          }
+          op_end();
+        }
+        op_begin();
+        {  // ---- C4 + C5: scores, block mask, softmax, PV over [cache ; own keys] ---------------------
+          const ExpertLoopParams& F = fresh(Pg);
+          AttnParams a = global(F.att);
+          a.k0 += (size_t)l * F.kcache_stride;
+          a.v0 += (size_t)l * F.vcache_stride;
+          char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
+          a.q = reinterpret_cast<const bf16*>(slot + F.r_q);
+          a.k1 = reinterpret_cast<const bf16*>(slot + F.r_k);
+          a.v1 = reinterpret_cast<const bf16*>(slot + F.r_v);
+          a.out = reinterpret_cast<bf16*>(slot + F.r_attn);
+          if (a.ml_out != nullptr) a.ml_out = reinterpret_cast<float*>(slot + F.r_ml);
+          const int att_gx = F.att_gx, att_gxy = F.att_gx * a.heads;
+          for_items(F.att_items, [&](int it) {
+            attention_suffix_body(a, item(it % att_gx, (it % att_gxy) / att_gx, it / att_gxy).template as<true>(), smem_raw + PK_TAIL);
+          }, att_block);
+          if (att_block >= F.att_items && (F.read_ahead & 15)) {   // no item: read ahead (constants only, no wait needed)
+            const int part = att_block - F.att_items, nparts = (int)gridDim.x - F.att_items;
+            const int ln = l + 1 < layers ? l + 1 : 0;
+            const bool by_die = part_die == 0 && nparts % 8 == 0 && (F.read_ahead & 32) != 0;
+            const int tid = item(0, 0, 0).thread;
+            unsigned fold = 0;
+            if (F.read_ahead & 1) fold = read_ahead_weights<2>(as_global(F.gu.W.w) + (size_t)l * F.w_stride, F.gu.n_tiles, F.gu.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+            if (F.read_ahead & 2) fold = read_ahead_weights<0>(as_global(F.dn.W.w) + (size_t)l * F.w_stride, F.dn.n_tiles, F.dn.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+            if (F.read_ahead & 4) fold = read_ahead_weights<1>(as_global(F.qkv.W.w) + (size_t)ln * F.w_stride, F.qkv.n_tiles, F.qkv.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+            if (F.read_ahead & 8) fold = read_ahead_weights<0>(as_global(F.o.W.w) + (size_t)ln * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, nparts, by_die, tid, fold);
+            if (fold == 0x9e3779b9u) as_global(F.sync)[GB_SINK] = fold;
+          }
+          op_end();
+          // Behind the arrival, so behind nothing that anybody waits for: the first of the two feature tiles of this block's
+          // gate||up item, straight into LDS.  A gate||up block takes 128 KB of weights through its compute unit, 2.5 us between
+          // two operations that are 1.8 apart; half of them ahead, by the 160 .. 192 blocks that are idle here, take its span from
+          // 4.1 to 3.6 us and the hand-over in front of it from 1.5 to 0.6 (the others find the lines in their die's L2).  All of
+          // them, or the attention blocks' too, cost the attention's own loads more than they give: 1 / 3 views 3.66 .. 3.85 ms /
+          // 3.98 .. 4.2, none 3.71 / 4.05, half 3.63 / 3.95.  Ahead of the arrival or of the down weights it is slower.
+          if (idle && (int)blockIdx.x < F.gu.n_tiles)
+            skinny_stage_weights(as_global(F.gu.W.w) + (size_t)l * F.w_stride, F.gu.W.k_pad, (int)blockIdx.x % (F.gu.n_tiles / 2) * 2, lds_address(smem_raw), item(0, 0, 0).thread);
+        }
+        op_begin();
+        {  // ---- C6: O projection + residual ------------------------------------------------------
+          const ExpertLoopParams& F = fresh(Pg);
+          GemmParams o = global(F.o);
+          o.W.w += (size_t)l * F.w_stride;
+          o.gain = as_global(F.g_mlp0) + (size_t)l * F.gain_stride;
+          char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
+          o.X = reinterpret_cast<const bf16*>(slot + F.r_attn);
+          if (o.xsplits > 1) o.xsplit_ml = reinterpret_cast<const float*>(slot + F.r_ml);
+          o.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_yb_o);
+          o.stat_out = reinterpret_cast<float*>(slot + F.r_st_o);
+          const int nx = o.n_tiles * 2;
+          for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<8>(o, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
+          op_end();
+        }
+        op_begin();
+        {  // ---- C7: RMS -> gate||up, fused gate -----------------------------------------------------
+          const ExpertLoopParams& F = fresh(Pg);
+          GemmParams g = global(F.gu);
+          g.W.w += (size_t)l * F.w_stride;
+          char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
+          g.X = reinterpret_cast<const bf16*>(slot + F.r_yb_o);
+          g.rowstat = reinterpret_cast<const float*>(slot + F.r_st_o);
+          g.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_mid);
+          // two feature tiles x one token block per item: the same sums as one tile x both token blocks, half the
+          // activation bytes per block behind the wait
+          const int pairs = g.n_tiles / 2;
+          for_items(pairs * 2, [&](int it) {
+            auto c = item(it % pairs, 0, it / pairs).template as<true>();
+            c.staged = idle && it == (int)blockIdx.x;
+            gemm_skinny_body<PRO_RMS, EPI_GEGLU, 2>(g, c, smem_raw);
           });
+          op_end();
         }
-        if (att_block >= F.att_items && (int)blockIdx.x >= q.n_tiles * 2 && (F.read_ahead & 48)) {   // no item here nor in the attention
-          const int tid = item(0, 0, 0).thread;
-          const int idle = (int)gridDim.x - (q.n_tiles * 2 > att_off + F.att_items ? q.n_tiles * 2 : att_off + F.att_items);
-          const int part = (int)gridDim.x - 1 - (int)blockIdx.x;
-          unsigned fold = 0;
-          if (F.read_ahead & 16) fold = read_ahead_weights<0>(as_global(F.o.W.w) + (size_t)l * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, idle, false, tid, fold);
-          if (fold == 0x9e3779b9u) as_global(F.sync)[GB_SINK] = fold;
+        op_begin();
+        {  // ---- C8: down + residual -----------------------------------------------------------------
+          const ExpertLoopParams& F = fresh(Pg);
+          GemmParams d = global(F.dn);
+          d.W.w += (size_t)l * F.w_stride;
+          d.gain = as_global(l + 1 < F.layers ? F.g_attn0 + (size_t)(l + 1) * F.gain_stride : F.g_final);
+          char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
+          d.X = reinterpret_cast<const bf16*>(slot + F.r_mid);
+          d.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_yb_d);
+          d.stat_out = reinterpret_cast<float*>(slot + F.r_st_d);
+          const int nx = d.n_tiles * 2;
+          for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<DN_NS>(d, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
+          op_end();
         }
-        op_end();
-      }
-      op_begin();
-      {  // ---- C4 + C5: scores, block mask, softmax, PV over [cache ; own keys] ---------------------
-        const ExpertLoopParams& F = fresh(Pg);
-        AttnParams a = global(F.att);
-        a.k0 += (size_t)l * F.kcache_stride;
-        a.v0 += (size_t)l * F.vcache_stride;
-        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
-        a.q = reinterpret_cast<const bf16*>(slot + F.r_q);
-        a.k1 = reinterpret_cast<const bf16*>(slot + F.r_k);
-        a.v1 = reinterpret_cast<const bf16*>(slot + F.r_v);
-        a.out = reinterpret_cast<bf16*>(slot + F.r_attn);
-        if (a.ml_out != nullptr) a.ml_out = reinterpret_cast<float*>(slot + F.r_ml);
-        const int att_gx = F.att_gx, att_gxy = F.att_gx * a.heads;
-        for_items(F.att_items, [&](int it) {
-          attention_suffix_body(a, item(it % att_gx, (it % att_gxy) / att_gx, it / att_gxy).template as<true>(), smem_raw + PK_TAIL);
-        }, att_block);
-        if (att_block >= F.att_items && (F.read_ahead & 15)) {   // no item: read ahead (constants only, no wait needed)
-          const int part = att_block - F.att_items, nparts = (int)gridDim.x - F.att_items;
-          const int ln = l + 1 < layers ? l + 1 : 0;
-          const bool by_die = part_die == 0 && nparts % 8 == 0 && (F.read_ahead & 32) != 0;
-          const int tid = item(0, 0, 0).thread;
-          unsigned fold = 0;
-          if (F.read_ahead & 1) fold = read_ahead_weights<2>(as_global(F.gu.W.w) + (size_t)l * F.w_stride, F.gu.n_tiles, F.gu.W.k_pad >> 4, part, nparts, by_die, tid, fold);
-          if (F.read_ahead & 2) fold = read_ahead_weights<0>(as_global(F.dn.W.w) + (size_t)l * F.w_stride, F.dn.n_tiles, F.dn.W.k_pad >> 4, part, nparts, by_die, tid, fold);
-          if (F.read_ahead & 4) fold = read_ahead_weights<1>(as_global(F.qkv.W.w) + (size_t)ln * F.w_stride, F.qkv.n_tiles, F.qkv.W.k_pad >> 4, part, nparts, by_die, tid, fold);
-          if (F.read_ahead & 8) fold = read_ahead_weights<0>(as_global(F.o.W.w) + (size_t)ln * F.w_stride, F.o.n_tiles, F.o.W.k_pad >> 4, part, nparts, by_die, tid, fold);
-          if (fold == 0x9e3779b9u) as_global(F.sync)[GB_SINK] = fold;
-        }
-        op_end();
-        // Behind the arrival, so behind nothing that anybody waits for: the first of the two feature tiles of this block's
-        // gate||up item, straight into LDS.  A gate||up block takes 128 KB of weights through its compute unit, 2.5 us between
-        // two operations that are 1.8 apart; half of them ahead, by the 160 .. 192 blocks that are idle here, take its span from
-        // 4.1 to 3.6 us and the hand-over in front of it from 1.5 to 0.6 (the others find the lines in their die's L2).  All of
-        // them, or the attention blocks' too, cost the attention's own loads more than they give: 1 / 3 views 3.66 .. 3.85 ms /
-        // 3.98 .. 4.2, none 3.71 / 4.05, half 3.63 / 3.95.  Ahead of the arrival or of the down weights it is slower.
-        if (idle && (int)blockIdx.x < F.gu.n_tiles)
-          skinny_stage_weights(as_global(F.gu.W.w) + (size_t)l * F.w_stride, F.gu.W.k_pad, (int)blockIdx.x % (F.gu.n_tiles / 2) * 2, lds_address(smem_raw), item(0, 0, 0).thread);
-      }
-      op_begin();
-      {  // ---- C6: O projection + residual ------------------------------------------------------
-        const ExpertLoopParams& F = fresh(Pg);
-        GemmParams o = global(F.o);
-        o.W.w += (size_t)l * F.w_stride;
-        o.gain = as_global(F.g_mlp0) + (size_t)l * F.gain_stride;
-        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
-        o.X = reinterpret_cast<const bf16*>(slot + F.r_attn);
-        if (o.xsplits > 1) o.xsplit_ml = reinterpret_cast<const float*>(slot + F.r_ml);
-        o.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_yb_o);
-        o.stat_out = reinterpret_cast<float*>(slot + F.r_st_o);
-        const int nx = o.n_tiles * 2;
-        for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<8>(o, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
-        op_end();
-      }
-      op_begin();
-      {  // ---- C7: RMS -> gate||up, fused gate -----------------------------------------------------
-        const ExpertLoopParams& F = fresh(Pg);
-        GemmParams g = global(F.gu);
-        g.W.w += (size_t)l * F.w_stride;
-        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
-        g.X = reinterpret_cast<const bf16*>(slot + F.r_yb_o);
-        g.rowstat = reinterpret_cast<const float*>(slot + F.r_st_o);
-        g.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_mid);
-        // two feature tiles x one token block per item: the same sums as one tile x both token blocks, half the
-        // activation bytes per block behind the wait
-        const int pairs = g.n_tiles / 2;
-        for_items(pairs * 2, [&](int it) {
-          auto c = item(it % pairs, 0, it / pairs).template as<true>();
-          c.staged = idle && it == (int)blockIdx.x;
-          gemm_skinny_body<PRO_RMS, EPI_GEGLU, 2>(g, c, smem_raw);
-        });
-        op_end();
-      }
-      op_begin();
-      {  // ---- C8: down + residual -----------------------------------------------------------------
-        const ExpertLoopParams& F = fresh(Pg);
-        GemmParams d = global(F.dn);
-        d.W.w += (size_t)l * F.w_stride;
-        d.gain = as_global(l + 1 < F.layers ? F.g_attn0 + (size_t)(l + 1) * F.gain_stride : F.g_final);
-        char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
-        d.X = reinterpret_cast<const bf16*>(slot + F.r_mid);
-        d.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_yb_d);
-        d.stat_out = reinterpret_cast<float*>(slot + F.r_st_d);
-        const int nx = d.n_tiles * 2;
-        for_items(nx * F.m16, [&](int it) { gemm_skinny16_body<DN_NS>(d, item(it % nx, it / nx, 0).template as<true>(), smem_raw + PK_TAIL); });
-        op_end();
       }
     }
     op_begin();
-    // ---- C9: final RMS -> out-projection (+bias), Euler update x <- x + dt * v ----------------------
-    {
-      const ExpertLoopParams& F = fresh(Pg);
-      GemmParams u = global(F.outp);
-      char* slot = as_global(F.ring) + (size_t)(k * layers + layers - 1) * F.ring_stride;
-      u.X = reinterpret_cast<const bf16*>(slot + F.r_yb_d);
-      u.rowstat = reinterpret_cast<const float*>(slot + F.r_st_d);
-      // one item per (feature tile, token block): half the activation bytes per block
-      for_items(u.n_tiles * 2, [&](int it) { gemm_skinny_body<PRO_RMS, EPI_EULER, 1>(u, item(it % u.n_tiles, 0, it / u.n_tiles).template as<true>(), smem_raw); });
-    }
+    euler_embed(k);   // one copy of its code
     op_end();
+    if (k >= 0 && k + 1 < steps) op_skip();   // the embedding was part of it
   }
 }
 
@@ -384,8 +423,7 @@ hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLo
   if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0) return hipErrorInvalidValue;
   if (blocks < 1 || blocks > GB_MAX_BLOCKS || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.arena == nullptr || P.arena_bytes == 0 || P.spin_limit == 0)
     return hipErrorInvalidValue;
-  if (P.layers < 1 || P.steps < 1 || P.x_elems < 1 || P.noise == nullptr || P.emb.x_rw == nullptr)
-    return hipErrorInvalidValue;
+  if (P.layers < 1 || P.steps < 1 || P.x_elems < 1) return hipErrorInvalidValue;
   // every buffer that blocks exchange lies inside the arena (offsets are 32-bit)
   auto in_arena = [&](const void* p, size_t bytes) {
     const char* c = reinterpret_cast<const char*>(p);
@@ -433,8 +471,12 @@ hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLo
   const int vs = a.v_split > 1 ? a.v_split : 1;
   if (P.att_gx != 4 * vs || P.att_items != 4 * vs * a.heads * shares || a.pf.blocks != 0) return hipErrorInvalidValue;
   if (!in_arena(a.q, 2) || !in_arena(a.k1, 2) || !in_arena(a.v1, 2) || !in_arena(a.out, 2)) return hipErrorInvalidValue;
-  if (P.emb.a.X % 32 != 0 || P.emb.a.gain == nullptr || P.emb.a.stat_parts == nullptr || P.emb.a.x != P.emb.x_rw) return hipErrorInvalidValue;
-  if (!in_arena(P.emb.x_rw, (size_t)P.x_elems * 4) || !in_arena(P.stok.out, (size_t)P.stok.X * 4)) return hipErrorInvalidValue;
+  if (P.emb.a.X % 32 != 0 || P.emb.a.gain == nullptr || P.emb.a.stat_parts == nullptr) return hipErrorInvalidValue;
+  // x: 63 rows of at most 32 values, one tile of the out-projection
+  if (P.emb.a.chunk != 63 || P.emb.a.A < 1 || P.emb.a.A > 32 || P.x_elems != 63 * P.emb.a.A || P.outp.n_tiles != 1 || P.outp.M != 64 || P.outp.ldo != P.emb.a.A ||
+      P.outp.n_valid != P.emb.a.A || P.emb.x_rw[0] == P.emb.x_rw[1])
+    return hipErrorInvalidValue;
+  if (!in_arena(P.emb.x_rw[0], (size_t)P.x_elems * 4) || !in_arena(P.emb.x_rw[1], (size_t)P.x_elems * 4) || !in_arena(P.noise, (size_t)P.x_elems * 4) || !in_arena(P.stok.out, (size_t)P.stok.X * 4)) return hipErrorInvalidValue;
   if (P.stok.sd < 1 || P.stok.sd > 32) return hipErrorInvalidValue;
   if (P.ring == nullptr || P.ring_stride % 256 != 0 || !in_arena(P.ring, P.ring_stride * (size_t)P.layers * P.steps)) return hipErrorInvalidValue;
   if (P.r_mid >= P.ring_stride || P.r_attn >= P.ring_stride) return hipErrorInvalidValue;

@@ -154,7 +154,7 @@ struct WsLayout {
   size_t stok, z, y, y_b, eq, ek, ev, eattn, eml, emid;
   size_t vstat, lstat, estat, estat_parts, pf_sink, vstat_parts, lstat_parts, progress;
   size_t es_begin, es_end;           // the expert's scratch block [es_begin, es_end)
-  size_t esync, eparams;             // persistent denoise kernel: barrier words, parameter block
+  size_t esync, eparams, xb;         // persistent denoise kernel: barrier words, parameter block, second buffer of x
   size_t ering, ering_slot;          // ... its ring of per-layer-step activation buffers, bytes per slot
   unsigned r_yb_o, r_st_o, r_yb_d, r_st_d, r_q, r_k, r_v, r_attn, r_ml, r_mid;   // byte offsets inside a slot
   size_t lx8, lx8s, lmid8, lmid8s;   // MXFP8 copies of the prefix feed-forward inputs
@@ -311,6 +311,7 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
   w.lstat_parts = cur.take((size_t)(d.E / 32) * d.maxPc * 32 * 2 * 4);                // [32-column tile][maxPc * 32][2]
   w.esync = cur.take((size_t)GB_WORDS * 4);
   w.eparams = cur.take(sizeof(ExpertLoopParams));
+  w.xb = cur.take((size_t)c.chunk * d.A * 4);
   {  // one slot per (Euler step, expert layer): the same buffers as stok .. emid above, each 256-byte aligned
     WsCursor sl;
     w.r_yb_o = (unsigned)sl.take((size_t)64 * d.X * 2);
@@ -942,7 +943,8 @@ bool run_denoise_persistent(Run& r, int P) {
   E.stok = StateTokenArgs{at<float>(c, w.st_state), d.SD, at<float>(c, w.state_w), at<float>(c, w.state_b), d.X, at<float>(c, w.stok), nullptr};
   E.emb.a = ActionEmbedArgs{xa, chunk, d.A, at<float>(c, w.wfold), at<float>(c, w.bias_tab), d.X, at<bf16>(c, w.z), at<float>(c, w.stok),
                             at<float>(c, w.y), at<bf16>(c, w.y_b), at<float>(c, w.g_e1[0]), at<float>(c, w.estat_parts)};
-  E.emb.x_rw = xa;
+  E.emb.x_rw[0] = xa;
+  E.emb.x_rw[1] = at<float>(c, w.xb);
   E.noise = at<float>(c, w.st_noise);
   E.x_elems = chunk * d.A;
   E.layers = d.Le;
