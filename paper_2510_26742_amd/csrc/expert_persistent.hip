@@ -330,7 +330,10 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
           // 4.1 to 3.6 us and the hand-over in front of it from 1.5 to 0.6 (the others find the lines in their die's L2).  All of
           // them, or the attention blocks' too, cost the attention's own loads more than they give: 1 / 3 views 3.66 .. 3.85 ms /
           // 3.98 .. 4.2, none 3.71 / 4.05, half 3.63 / 3.95.  Ahead of the arrival or of the down weights it is slower.
-          if (idle && (int)blockIdx.x < F.gu.n_tiles)
+          // Not a block that leads its die: its arrival ends with the whole die's, so the request would stand in front of its
+          // out-projection weights while the others have theirs, and everybody waits for it (1 / 1+7 / 3 views 3.605 / 3.620 /
+          // 3.927 ms, without 3.585 / 3.600 / 3.927; requested ahead of the arrival instead, along with those weights, +20 .. +50 us).
+          if (idle && !bar.leader && (int)blockIdx.x < F.gu.n_tiles)
             skinny_stage_weights(as_global(F.gu.W.w) + (size_t)l * F.w_stride, F.gu.W.k_pad, (int)blockIdx.x % (F.gu.n_tiles / 2) * 2, lds_address(smem_raw), item(0, 0, 0).thread);
         }
         op_begin();
@@ -362,7 +365,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
           const int pairs = g.n_tiles / 2;
           for_items(pairs * 2, [&](int it) {
             auto c = item(it % pairs, 0, it / pairs).template as<true>();
-            c.staged = idle && it == (int)blockIdx.x;
+            c.staged = idle && !bar.leader && it == (int)blockIdx.x;
             gemm_skinny_body<PRO_RMS, EPI_GEGLU, 2>(g, c, smem_raw);
           });
           op_end();
