@@ -255,19 +255,6 @@ hipError_t lds_tile_launch(hipStream_t s, GemmParams p, int z) {
 
 }  // namespace
 
-int gemm_lds_gateup_rows(int M, int n_tiles, int k_pad) {
-  int rows = 0;
-  float best = 0.f;
-#define X(MT, NT)                                                                  \
-  {                                                                                \
-    const float c = lds_tile_cost(MT, NT, M, n_tiles, k_pad, 1, false);            \
-    if (rows == 0 || c < best) { best = c; rows = 2 * (MT) * 32; }                 \
-  }
-  LDS_TILES(X)
-#undef X
-  return rows;
-}
-
 bool gemm_lds_ok(int k_pad) { return k_pad % (16 * LT_GROUP) == 0; }
 
 int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max) {

@@ -582,11 +582,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     p.rowstat = lplanes > 0 ? at<float>(c, w.lstat_parts) : at<float>(c, w.lstat);
     p.rowstat_parts = lplanes; p.stat_rows = stat_rows;
   };
-  // Who adds up the partial sums that an O projection leaves, the GEMM behind it (64 planes at most) or a launch of its own.
-  // The consumer is quicker wherever its blocks read their planes in one round trip (prefill with / without the launches, ms:
-  // 2 views 4.260 / 4.178, 3 views 5.524 / 5.448), so beyond 512 tokens there is no launch.  Between 257 and 512 the launches
-  // stay all the same: pi0_debug_profile's launches by class at 2 views are pinned with them.  A gate||up block of 320 rows
-  // (257 .. 320 tokens) needs two round trips, there the launch is the quicker way (1 view + 7 tokens 3.245 / 3.273).
+  // Beyond 256 tokens the O projection's partial sums are added up by a launch of their own: the blocks of the GEMM
+  // behind it hold up to 256 rows, and each would read all planes of its rows (128 KB).  A consumer takes 64 planes at most.
   auto sum_vision = [&](int tokens_over) {
     if (vplanes > 64 || (vplanes > 0 && I > tokens_over)) {
       r.cls = PI0_OP_REDUCE;
@@ -661,7 +658,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     if (vo_stream) {
       vplanes = gemm_fullk_resid(r, L.o, at<bf16>(c, w.vattn), d.Dv, I, d.Dv, at<float>(c, L.o.bias), at<float>(c, w.vh),
                                  at<bf16>(c, w.vh_b), d.Dv, at<float>(c, w.vstat_parts), stat_rows, at<float>(c, w.g_v2[l]));
-      sum_vision(T.fko == 1 || I > 512 ? NEVER : 256);
+      sum_vision(T.fko == 1 ? NEVER : 256);
     } else {
       gemm_splitk_resid(r, L.o, at<bf16>(c, w.vattn), d.Dv, I, d.Dv, zvo, round_up(ceil_div(L.o.k_pad, zvo), 64),
                         at<float>(c, L.o.bias), at<float>(c, w.vh), at<bf16>(c, w.vh_b), d.Dv, tvo, at<float>(c, w.vstat),
@@ -734,7 +731,6 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
       if (tlgu < 0 || cost <= best) { best = cost; tlgu = ids[i]; }
     }
   }
-  const int gu_rows = tlgu == TILE_LDS ? gemm_lds_gateup_rows(P, w.llm[0].gu.n_pad / 32, w.llm[0].gu.k_pad) : 0;
   // down: TILE_LDS knows its best number of k ranges; otherwise as many as keep all blocks in one round (measured optima
   // 16 / 8 / 5 at 256 / 512 / 768 tokens)
   const WsTr& L0 = w.llm[0];
@@ -791,7 +787,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
         RUN(r, launch_splitk_reduce(r.s, q));
         lplanes = 0;
       } else {
-        sum_prefix(T.fkl == 1 || (P > 512 && tlgu == TILE_LDS && gu_rows <= 256) ? NEVER : 256);
+        sum_prefix(T.fkl == 1 ? NEVER : 256);
       }
     } else {
       gemm_splitk_resid(r, L.o, at<bf16>(c, w.lattn), d.H * 256, P, d.H * 256, zlo,

@@ -236,7 +236,6 @@ hipError_t launch_gemm_stream(hipStream_t s, int pro, int epi, const GemmParams&
 hipError_t launch_gemm_lds(hipStream_t s, int pro, int epi, const GemmParams& p, int z_splits);
 bool gemm_lds_ok(int k_pad);                                             // TILE_LDS takes this contraction
 int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max);           // k ranges of a split-K launch
-int gemm_lds_gateup_rows(int M, int n_tiles, int k_pad);                    // tokens of a gate||up block
 hipError_t gemm_lds_init_attributes();
 hipError_t gemm_stream_init_attributes();
 // planes of row statistics that the residual projection of this shape leaves (one per block column; 0: no such kernel)
