@@ -41,7 +41,13 @@ constexpr int LT_KC = 2;                       // k16 steps of a stage
 constexpr int LT_GROUP = LT_STAGES * LT_KC;    // k16 steps of a turn of the loop: k ranges are multiples of 128
 
 constexpr int lds_tile_fragments(int MT, int NT) { return 2 * (MT + NT) * LT_KC; }   // of a stage
-constexpr int lds_tile_smem(int MT, int NT) { return LT_STAGES * lds_tile_fragments(MT, NT) * 1024 + 2 * MT * 32 * 8; }
+constexpr int LT_SMEM = 160 * 1024;             // of a compute unit, which a block has to itself
+constexpr int lds_tile_stat_bytes(int MT) { return (2 * MT * 32 * 8 + 1023) / 1024 * 1024; }   // row statistics, whole requests of 1 KiB
+constexpr int lds_tile_smem(int MT, int NT) { return lds_tile_stat_bytes(MT) + LT_STAGES * lds_tile_fragments(MT, NT) * 1024; }
+// planes of partial row statistics that fit behind the three stages requested first (the last request may be half empty)
+constexpr int lds_tile_planes(int MT, int NT) {
+  return (LT_SMEM - lds_tile_stat_bytes(MT) - (LT_STAGES - 1) * lds_tile_fragments(MT, NT) * 1024 - 1024) / (2 * MT * 32 * 8);
+}
 
 template <int MT, int NT, int PRO, int EPI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_lds_kernel(GemmParams p) {
@@ -51,8 +57,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int L = NF / W;                      // fragments a wave requests per stage
   static_assert(NF % W == 0, "even shares");
   constexpr int ROWS = XB * 32;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];      // [stage][fragment][1 KiB], then row statistics
-  float2* sstat = reinterpret_cast<float2*>(smem_raw + LT_STAGES * NF * 1024);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];          // row statistics, then [stage][fragment][1 KiB]
+  float2* sstat = reinterpret_cast<float2*>(smem);
+  unsigned char* const smem_raw = smem + lds_tile_stat_bytes(MT);
 
   const int t = threadIdx.x;
   const int lane = t & 63;
@@ -84,7 +91,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                               : reinterpret_cast<const char*>(p.W.w) + (size_t)min(nb * WB + (b - XB), p.n_tiles - 1) * KC16 * 1024;
     src[i] = base + (size_t)(kbeg + k) * 1024;
   }
-  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem_raw + (unsigned)w * 1024u;
+  const unsigned lds0 = lds_address(smem_raw) + (unsigned)w * 1024u;
   unsigned voff = (unsigned)lane * 16u + 4096u;      // of the current group: its stage q is at 2048 q - 4096, a 13-bit constant
   // request the wave's fragment I of stage Q of the group at v; the constant counts towards both addresses
   auto issue = [&](auto Q, auto I, unsigned v) {
@@ -95,28 +102,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                  "n"((q * NF + W * i) * 1024 - (q * 2048 - 4096)), "n"(q * 2048 - 4096)
                  : "memory", "scc");
   };
-  for_each<LT_STAGES - 1>([&](auto Q) { for_each<L>([&](auto I) { issue(Q, I, voff); }); });
-
-  // Row statistics: whole-row sums, or one partial sum per 32-column tile of the producer; thread r adds its row's planes
-  if (PRO != PRO_NONE) {
-    for (int r = t; r < ROWS; r += 64 * W) {
-      const size_t rowg = (size_t)min(m0 + r, p.M - 1);
-      const int parts = p.rowstat_parts > 1 ? p.rowstat_parts : 1;
-      float a = 0.f, b = 0.f;
-      for (int j0 = 0; j0 < parts; j0 += 16) {
-        float2 v[16];
-#pragma unroll
-        for (int j = 0; j < 16; j++) v[j] = *reinterpret_cast<const float2*>(p.rowstat + 2 * ((size_t)min(j0 + j, parts - 1) * p.stat_rows + rowg));
-#pragma unroll
-        for (int j = 0; j < 16; j++) {
-          if (j0 + j < parts) {
-            a += v[j].x;
-            b += v[j].y;
-          }
-        }
-      }
-      sstat[r] = make_float2(a, b);
+  // Row statistics: whole-row sums, or partial sums in planes, one per block column of the producer, which the thread of the
+  // row adds up.  They go to LDS like the operands and in front of them: loaded into registers behind the first stages, as
+  // they were, they kept every block until all of those stages had come, a burst of 18 - 25 MB from memory (start of a block
+  // to its first product 4.3 us at 256 and 512 tokens, as against 1.9 without statistics;
+  // prefill at 512 / 768 / 816 tokens 4.432 / 5.822 / 6.350 -> 4.414 / 5.790 / 6.310 ms).
+  constexpr int PLANES = lds_tile_planes(MT, NT), PAIRS = ROWS / 2, RR = (ROWS + 64 * W - 1) / (64 * W);
+  static_assert(PLANES >= 1, "room for a plane");
+  float2 sum[RR] = {};
+  const int parts = PRO != PRO_NONE ? p.rowstat_parts : 0;
+  unsigned char* const planes = smem_raw + (LT_STAGES - 1) * NF * 1024;
+  auto request_planes = [&](int first_plane, int n, unsigned char* to) {   // 16 bytes per lane: two rows
+    const int last = (p.M - 1) & ~1;
+    for (int q = w; q * 64 < n * PAIRS; q += W) {
+      const int u = min(q * 64 + lane, n * PAIRS - 1), pl = u / PAIRS;
+      const int row = min(m0 + 2 * (u - pl * PAIRS), last);
+      request_to_lds(reinterpret_cast<const char*>(p.rowstat), (unsigned)((first_plane + pl) * p.stat_rows + row) * 8u, lds_address(to) + (unsigned)q * 1024u);
     }
+  };
+  auto add_planes = [&](int n) {
+    const float2* const v = reinterpret_cast<const float2*>(planes);
+#pragma unroll
+    for (int i = 0; i < RR; i++) {
+      const int r = min(t + i * 64 * W, ROWS - 1);
+#pragma unroll 8
+      for (int j = 0; j < n; j++) {
+        const float2 x = v[j * ROWS + r];
+        sum[i].x += x.x;
+        sum[i].y += x.y;
+      }
+    }
+  };
+  int plane = 0;
+  if (PRO != PRO_NONE) {
+    if (parts > 1) {
+      for (; parts - plane > PLANES; plane += PLANES) {   // more than fit: in turns
+        request_planes(plane, PLANES, planes);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        add_planes(PLANES);
+        __syncthreads();
+      }
+      request_planes(plane, parts - plane, planes);
+    } else {
+      request_planes(0, 1, smem);
+    }
+  }
+  for_each<LT_STAGES - 1>([&](auto Q) { for_each<L>([&](auto I) { issue(Q, I, voff); }); });
+  if (PRO != PRO_NONE && parts > 1) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((LT_STAGES - 1) * L) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    add_planes(parts - plane);
+#pragma unroll
+    for (int i = 0; i < RR; i++) sstat[min(t + i * 64 * W, ROWS - 1)] = sum[i];   // the last row's extra threads store the same
   }
 
   f32x16 acc[NT][MT];
@@ -249,7 +288,7 @@ template <int MT, int NT, int PRO, int EPI>
 hipError_t lds_tile_launch(hipStream_t s, GemmParams p, int z) {
   p.m_tiles = ceil_div(p.M, 2 * MT * 32);
   const int total = ceil_div(p.n_tiles, 2 * NT) * p.m_tiles;
-  gemm_lds_kernel<MT, NT, PRO, EPI><<<dim3(8 * ceil_div(total, 8), z), dim3(256), lds_tile_smem(MT, NT), s>>>(p);
+  gemm_lds_kernel<MT, NT, PRO, EPI><<<dim3(8 * ceil_div(total, 8), z), dim3(256), PRO != PRO_NONE ? LT_SMEM : lds_tile_smem(MT, NT), s>>>(p);
   return hipGetLastError();
 }
 
@@ -278,7 +317,7 @@ hipError_t gemm_lds_init_attributes() {
   hipError_t e = hipSuccess;
 #define X(MT, NT)                                                                                                                       \
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_lds_kernel<MT, NT, PRO_RMS, EPI_GEGLU>),             \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_tile_smem(MT, NT));                      \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, LT_SMEM);                                    \
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_lds_kernel<MT, NT, PRO_NONE, EPI_PARTIAL>),          \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, lds_tile_smem(MT, NT));
   LDS_TILES(X)
@@ -294,8 +333,9 @@ hipError_t launch_gemm_lds(hipStream_t s, int pro, int epi, const GemmParams& p,
   if (p.n_tiles < 1 || p.n_tiles * 32 != p.W.n_pad || p.ldx < p.W.k_pad || p.ldx % 16 != 0) return hipErrorInvalidValue;
   if ((size_t)p.W.k_pad * 64 > 0x7fffffffu) return hipErrorInvalidValue;   // a row of fragments is addressed with 32 bits
   if (pro == PRO_RMS && epi == EPI_GEGLU) {
-    if (z != 1 || p.rowstat == nullptr || p.out_bf16 == nullptr || p.bias != nullptr || (p.rowstat_parts > 1 && p.stat_rows < p.M))
-      return hipErrorInvalidValue;
+    if (z != 1 || p.rowstat == nullptr || p.out_bf16 == nullptr || p.bias != nullptr) return hipErrorInvalidValue;
+    // statistics are read two rows at a time
+    if (p.rowstat_parts > 1 && (p.stat_rows < p.M || p.stat_rows % 2 != 0)) return hipErrorInvalidValue;
   } else if (pro != PRO_NONE || epi != EPI_PARTIAL || p.out_f32 == nullptr) {
     return hipErrorInvalidValue;
   }
