@@ -92,7 +92,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     src[i] = base + (size_t)(kbeg + k) * 1024;
   }
   const unsigned lds0 = lds_address(smem_raw) + (unsigned)w * 1024u;
-  unsigned voff = (unsigned)lane * 16u + 4096u;      // of the current group: its stage q is at 2048 q - 4096, a 13-bit constant
+  // Where a round of blocks reads the whole weight matrix (one token tile), all blocks would ask for the same k of their own
+  // weight rows, a power of two apart: each starts elsewhere in its range and goes round (prefill at 256 / 263 tokens
+  // 3.133 / 3.348 -> 3.099 / 3.338 ms).  With more token tiles the blocks that share weights set the pace, and 816 tokens are
+  // 25 us slower that way
+  int turn = p.m_tiles == 1 ? (int)((unsigned)nb % (unsigned)groups) : 0;
+  const unsigned vfirst = (unsigned)lane * 16u + 4096u;
+  unsigned voff = vfirst + (unsigned)turn * (LT_GROUP * 1024u);      // of the current group: its stage q is at 2048 q - 4096, a 13-bit constant
   // request the wave's fragment I of stage Q of the group at v; the constant counts towards both addresses
   auto issue = [&](auto Q, auto I, unsigned v) {
     constexpr int q = decltype(Q)::value, i = decltype(I)::value;
@@ -189,7 +195,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // (one more may be on its way); everybody has then read stage q - 1, whose place stage q + 3 takes.
   auto group = [&](auto last_group) {
     constexpr bool LAST = decltype(last_group)::value != 0;
-    const unsigned vnext = voff + LT_GROUP * 1024u;
+    turn = turn + 1 == groups ? 0 : turn + 1;
+    const unsigned vnext = vfirst + (unsigned)turn * (LT_GROUP * 1024u);
     for_each<LT_GROUP>([&](auto SS) {
       constexpr int s = decltype(SS)::value, q = s / LT_KC, u = s & 1;
       constexpr bool boundary = u == 1 && !(LAST && q == LT_STAGES - 1);
