@@ -49,7 +49,7 @@ constexpr int lds_tile_planes(int MT, int NT) {
   return (LT_SMEM - lds_tile_stat_bytes(MT) - (LT_STAGES - 1) * lds_tile_fragments(MT, NT) * 1024 - 1024) / (2 * MT * 32 * 8);
 }
 
-template <int MT, int NT, int PRO, int EPI>
+template <int MT, int NT, int PRO, int EPI, bool WALK>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_lds_kernel(GemmParams p) {
   constexpr int W = 4;
   constexpr int XB = 2 * MT, WB = 2 * NT;        // 32-row blocks of the two operands
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int ROWS = XB * 32;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];          // row statistics, then [stage][fragment][1 KiB]
   float2* sstat = reinterpret_cast<float2*>(smem);
-  unsigned char* const smem_raw = smem + lds_tile_stat_bytes(MT);
+  unsigned char* const smem_raw = smem + (WALK ? 2 : 1) * lds_tile_stat_bytes(MT);
 
   const int t = threadIdx.x;
   const int lane = t & 63;
@@ -71,8 +71,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // tiles as in gemm_stream.hip: consecutive ids on different dies, a die takes a contiguous eighth, token tiles fastest
   const int total = (p.n_tiles + WB - 1) / WB * p.m_tiles;
   const int die = (int)blockIdx.x & 7, die_rank = (int)blockIdx.x >> 3;
-  const int first = die * (total >> 3) + min(die, total & 7);
-  if (die_rank >= (total >> 3) + (die < (total & 7) ? 1 : 0)) return;
+  const int first = die * (total >> 3) + min(die, total & 7), of_die = (total >> 3) + (die < (total & 7) ? 1 : 0);
+  if (die_rank >= of_die) return;
   const int nb = (first + die_rank) / p.m_tiles;
   const int mt = (first + die_rank) - nb * p.m_tiles;
   const int m0 = mt * ROWS;
@@ -84,13 +84,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // The wave's fragment i of a stage is fragment w + 4 i of the block's: operand block f / 2 (tokens first), k16 step f % 2;
   // blocks beyond the operands repeat the last one and are not stored
   const char* src[L];
+  auto set_sources = [&](int nb, int m0) {
 #pragma unroll
-  for (int i = 0; i < L; i++) {
-    const int f = w + W * i, b = f / LT_KC, k = f % LT_KC;
-    const char* base = b < XB ? reinterpret_cast<const char*>(p.X) + (size_t)min((m0 >> 5) + b, mb_last) * XKC16 * 1024
-                              : reinterpret_cast<const char*>(p.W.w) + (size_t)min(nb * WB + (b - XB), p.n_tiles - 1) * KC16 * 1024;
-    src[i] = base + (size_t)(kbeg + k) * 1024;
-  }
+    for (int i = 0; i < L; i++) {
+      const int f = w + W * i, b = f / LT_KC, k = f % LT_KC;
+      const char* base = b < XB ? reinterpret_cast<const char*>(p.X) + (size_t)min((m0 >> 5) + b, mb_last) * XKC16 * 1024
+                                : reinterpret_cast<const char*>(p.W.w) + (size_t)min(nb * WB + (b - XB), p.n_tiles - 1) * KC16 * 1024;
+      src[i] = base + (size_t)(kbeg + k) * 1024;
+    }
+  };
+  set_sources(nb, m0);
   const unsigned lds0 = lds_address(smem_raw) + (unsigned)w * 1024u;
   // Where a round of blocks reads the whole weight matrix (one token tile), all blocks would ask for the same k of their own
   // weight rows, a power of two apart: each starts elsewhere in its range and goes round (prefill at 256 / 263 tokens
@@ -118,7 +121,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   float2 sum[RR] = {};
   const int parts = PRO != PRO_NONE ? p.rowstat_parts : 0;
   unsigned char* const planes = smem_raw + (LT_STAGES - 1) * NF * 1024;
-  auto request_planes = [&](int first_plane, int n, unsigned char* to) {   // 16 bytes per lane: two rows
+  auto request_planes = [&](int m0, int first_plane, int n, unsigned char* to) {   // 16 bytes per lane: two rows
     const int last = (p.M - 1) & ~1;
     for (int q = w; q * 64 < n * PAIRS; q += W) {
       const int u = min(q * 64 + lane, n * PAIRS - 1), pl = u / PAIRS;
@@ -143,15 +146,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   if (PRO != PRO_NONE) {
     if (parts > 1) {
       for (; parts - plane > PLANES; plane += PLANES) {   // more than fit: in turns
-        request_planes(plane, PLANES, planes);
+        request_planes(m0, plane, PLANES, planes);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         add_planes(PLANES);
         __syncthreads();
       }
-      request_planes(plane, parts - plane, planes);
+      request_planes(m0, plane, parts - plane, planes);
     } else {
-      request_planes(0, 1, smem);
+      request_planes(m0, 0, 1, smem);
     }
   }
   for_each<LT_STAGES - 1>([&](auto Q) { for_each<L>([&](auto I) { issue(Q, I, voff); }); });
@@ -164,6 +167,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     for (int i = 0; i < RR; i++) sstat[min(t + i * 64 * W, ROWS - 1)] = sum[i];   // the last row's extra threads store the same
   }
 
+  // WALK: a block takes its tiles one after the other, and the next one's first stages and row statistics (in the other of two
+  // places) are on their way during the epilogue
+  int nb_now = nb, m0_now = m0;
+  for (int next = die_rank + ((int)gridDim.x >> 3);; next += (int)gridDim.x >> 3) {
   f32x16 acc[NT][MT];
 #pragma unroll
   for (int j = 0; j < NT; j++)
@@ -225,15 +232,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   };
   for (int g = 0; g + 1 < groups; g++) group(Int<0>{});
   group(Int<1>{});
-
+  const float2* const stat = sstat;
+  int nb_next = 0, m0_next = 0;
+  if (WALK && next < of_die) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();   // everybody has read the last stage
+    nb_next = (first + next) / p.m_tiles;
+    m0_next = ((first + next) - nb_next * p.m_tiles) * ROWS;
+    set_sources(nb_next, m0_next);
+    sstat = reinterpret_cast<float2*>(smem + (sstat == reinterpret_cast<float2*>(smem) ? lds_tile_stat_bytes(MT) : 0));
+    if (PRO != PRO_NONE) request_planes(m0_next, 0, 1, reinterpret_cast<unsigned char*>(sstat));
+    voff = vfirst;
+    for_each<LT_STAGES - 1>([&](auto Q) { for_each<L>([&](auto I) { issue(Q, I, voff); }); });
+  }
   if constexpr (EPI == EPI_PARTIAL) {   // whole tiles, see partial_tile_at; rows beyond the last are never read
     const int mbs = (p.M + 31) >> 5;
 #pragma unroll
     for (int i = 0; i < MT; i++) {
-      const int mb = (m0 >> 5) + wm * MT + i;
+      const int mb = (m0_now >> 5) + wm * MT + i;
 #pragma unroll
       for (int j = 0; j < NT; j++) {
-        const int nt = nb * WB + wn * NT + j;
+        const int nt = nb_now * WB + wn * NT + j;
         if (mb < mbs && nt < p.n_tiles) {   // uniform
           float* const dst = p.out_f32 + (((size_t)blockIdx.y * mbs + mb) * p.n_tiles + nt) * 1024 + lane * 4;
 #pragma unroll
@@ -245,17 +264,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 #pragma unroll
   for (int i = 0; i < MT; i++) {
-    const int row = (wm * MT + i) * 32 + lq, m = m0 + row;
+    const int row = (wm * MT + i) * 32 + lq, m = m0_now + row;
     if (m < p.M) {
       float ssum = 0.f, ssq = 0.f;
       if (PRO != PRO_NONE) {
-        const float2 v = sstat[row];
+        const float2 v = stat[row];
         ssum = v.x;
         ssq = v.y;
       }
 #pragma unroll
       for (int j = 0; j < NT; j++) {
-        const int nt = nb * WB + wn * NT + j;
+        const int nt = nb_now * WB + wn * NT + j;
         if (nt < p.n_tiles) {
           EpiOps ops;
           epilogue_preload<PRO, EPI>(p, nt, m, lh, ops);
@@ -263,6 +282,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         }
       }
     }
+  }
+  if (!WALK || next >= of_die) return;
+  nb_now = nb_next;
+  m0_now = m0_next;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the counts below take no stores
   }
 }
 
@@ -295,7 +319,17 @@ template <int MT, int NT, int PRO, int EPI>
 hipError_t lds_tile_launch(hipStream_t s, GemmParams p, int z) {
   p.m_tiles = ceil_div(p.M, 2 * MT * 32);
   const int total = ceil_div(p.n_tiles, 2 * NT) * p.m_tiles;
-  gemm_lds_kernel<MT, NT, PRO, EPI><<<dim3(8 * ceil_div(total, 8), z), dim3(256), PRO != PRO_NONE ? LT_SMEM : lds_tile_smem(MT, NT), s>>>(p);
+  // More tiles than compute units: blocks that stay and walk save the start of the second round, 2 of 88 us at 768 tokens
+  // (prefill at 533 / 768 tokens 4.650 / 5.280 -> 4.621 / 5.255 ms).  Where one round is enough the same code is slower (3.23 -> 3.28 ms
+  // at 256 tokens): its registers take part in the loop.  Tiles of 256 x 256 have none left for it and spill: 816 tokens
+  // alone 20 us faster, beside a denoise loop on half of the chip 9.50 -> 9.55 ms
+  if constexpr (EPI == EPI_GEGLU && MT * NT <= 12) {
+    if (total > 256 && p.m_tiles > 1 && p.rowstat_parts <= 1) {
+      gemm_lds_kernel<MT, NT, PRO, EPI, true><<<dim3(256), dim3(256), LT_SMEM, s>>>(p);
+      return hipGetLastError();
+    }
+  }
+  gemm_lds_kernel<MT, NT, PRO, EPI, false><<<dim3(8 * ceil_div(total, 8), z), dim3(256), PRO != PRO_NONE ? LT_SMEM : lds_tile_smem(MT, NT), s>>>(p);
   return hipGetLastError();
 }
 
@@ -323,10 +357,16 @@ int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max) {
 hipError_t gemm_lds_init_attributes() {
   hipError_t e = hipSuccess;
 #define X(MT, NT)                                                                                                                       \
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_lds_kernel<MT, NT, PRO_RMS, EPI_GEGLU>),             \
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_lds_kernel<MT, NT, PRO_RMS, EPI_GEGLU, false>),             \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, LT_SMEM);                                    \
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_lds_kernel<MT, NT, PRO_NONE, EPI_PARTIAL>),          \
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_lds_kernel<MT, NT, PRO_NONE, EPI_PARTIAL, false>),          \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, lds_tile_smem(MT, NT));
+  LDS_TILES(X)
+#undef X
+#define X(MT, NT)                                                                                                                       \
+  if constexpr (MT * NT <= 12)                                                                                                          \
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_lds_kernel<MT, NT, PRO_RMS, EPI_GEGLU, MT * NT <= 12>), \
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, LT_SMEM);
   LDS_TILES(X)
 #undef X
   return e;
