@@ -185,14 +185,17 @@ KERNEL_OF_CLASS = {
     "vis_attn": "attention_kernel", "llm_attn": "attention_kernel", "exp_attn": "attention_suffix_kernel",
     "exp_qkv": "gemm_skinny_kernel", "exp_gateup": "gemm_skinny_kernel", "exp_out": "gemm_skinny_kernel",
     "exp_o": "gemm_skinny16_kernel", "exp_down": "gemm_skinny16_kernel",
-    "reduce": "splitk_reduce_kernel",
+    "reduce": "tile_reduce_kernel",
 }
 
 
 def kernel_of_class(name: str, prefix_tokens: int | None = None):
     """Kernel template family that runs an operation class in the library's default schedule.  The vision attention has a
     second form for launches of more than 256 blocks (32 rows of one of 16 heads each), i.e. beyond 512 tokens (of the images:
-    with an empty prompt, as here, those of the prefix)."""
+    with an empty prompt, as here, those of the prefix).  Up to 320 prefix tokens the prefix attention runs the expert's kernel,
+    which is a family of its own here."""
+    if name == "llm_attn" and prefix_tokens is not None and prefix_tokens <= 320:
+        return "attention_suffix_kernel (prefix)"
     if name == "vis_attn" and prefix_tokens is not None and prefix_tokens > 512:
         return "attention_vision2_kernel"
     return KERNEL_OF_CLASS.get(name)
