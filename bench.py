@@ -215,7 +215,7 @@ def main() -> int:
             print(f"{nm:7s} {f('items'):5.0f} {f('wait'):7.0f} {f('body'):7.0f} {f('body_max'):7.0f} {f('arrive'):7.0f} {f('span'):7.0f} "
                   f"{f('barrier'):7.0f}   " + " ".join(f"{x:6.0f}" for x in mk if x > 0))
         print(f"sum of span + next over the operations of one Euler step: {total / 2e3:.1f} us "
-              f"({total / 2e3 / cfg.exp_layers:.2f} us per layer incl. the step's three own operations)")
+              f"({total / 2e3 / cfg.exp_layers:.2f} us per layer incl. the step's own operations)")
         print(f"kernel span (first entry -> last arrive): {(t[-1][:, 3].max() - t[0][:, 0].min()) * 10 / 1e6:.3f} ms")
         m.close()
         return 0
@@ -333,7 +333,7 @@ def main() -> int:
                 "frac": round(loop_gbps / 8000.0, 4), "traffic": loop_traffic,
                 "kernel": "expert_loop_kernel", "launches_per_pass": 1, "avg_us": round(denoise_ms[hv] * 1e3, 1),
                 "algorithmic_bytes_per_launch": int(loop_bytes), "algorithmic_flops_per_launch": int(loop_flops),
-                "units_per_launch": f"{cfg.steps} Euler steps x {cfg.exp_layers} layers x 5 operations (+ 3 per step)",
+                "units_per_launch": f"{cfg.steps} Euler steps x {cfg.exp_layers} layers x 5 operations (+ 2 per step)",
                 "traffic_profile_commit": traffic_commit}
     log(f"[bench] expert_loop_kernel: {loop_bytes / 1e9:.3f} GB algorithmic in {denoise_ms[hv]:.3f} ms = {loop_gbps:.0f} GB/s "
         f"= {loop_gbps / 8000.0:.3f} of the HBM peak")

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(512, 4) void attention_vision2_kernel(AttnParams p)
   attention_body<80, 3, 1, VRING, 0>(p, LaunchCtx::from_block_idx(), smem_raw);
 }
 
-// the action expert's case (attention_suffix_body): 16 query rows per block
+// the action expert's case (attention_suffix_body), and queries over at most ten key chunks: 16 query rows per block
 __global__ __launch_bounds__(512) void attention_suffix_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   attention_suffix_body(p, LaunchCtx::from_block_idx(), smem_raw);
@@ -97,7 +97,7 @@ hipError_t launch_attention(hipStream_t s, const AttnParams& p) {
   if (n0 > 32) return hipErrorInvalidValue;   // at most 1024 keys in segment 0 per query row
   if (p.v_split != 0 && p.v_split != 1 && ((p.v_split != 2 && p.v_split != 4 && p.v_split != 8) || p.head_dim != 256)) return hipErrorInvalidValue;
   const int vs = p.v_split > 1 ? p.v_split : 1;
-  const bool suffix = attn_suffix_ok(p, n0);   // the action expert: 16 query rows per block
+  const bool suffix = attn_suffix_ok(p, n0);   // 16 query rows per block
   dim3 grid((suffix ? (p.Tq + 15) / 16 : (p.Tq + 31) / 32) * vs, p.heads, p.key_splits > 1 ? p.key_splits : 1);
   if (p.pf.blocks != 0) {   // warm-up blocks as extra grid rows
     const PrefetchDesc& d = p.pf;
