@@ -298,7 +298,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // the larger of the operands' way to the compute units (46 KB per us and unit with all of them asking; a round that leaves
 // units idle is quicker, gate||up down to 3/4, partial sums 0.9) and the products (32 cycles each at the 1.35 GHz the chip
 // then runs at), and 3 us plus the epilogue, which goes with the tile (0.8 us per 32 x 32 tile and wave with the gate, 0.12 us
-// for partial sums).  The partial sums are then read and written once more (5 TB/s, and a launch).  It ranks tiles and
+// for partial sums).  The partial sums are then read and written once more (5 TB/s, a launch, and
+// 3 us for each round trip of eight ranges beyond the first: 533 tokens, prefill in ms with 7 / 8 / 9 / 10 ranges 4.870 / 4.816 /
+// 4.862 / 4.974).  It ranks tiles and
 // ranges; it does not predict a time.  gate||up in a traced pass at 256 / 512 / 768 / 816 tokens: 43.1 / 58.6 / 88.3 / 112.3 us,
 // the formula 42.8 / 64.3 / 103.1 / 128.7.  Number of ranges, prefill in ms at 256 tokens with 8 / 10 / 11 / 12 / 16 ranges:
 // 3.078 / 3.046 / 3.024 / 3.030 / 3.031; 512 with 6 / 7 / 8 / 10 / 12: 4.336 / 4.306 / 4.248 / 4.300 / 4.208 .. 4.31; 768 with
@@ -311,7 +313,7 @@ float lds_tile_cost(int MT, int NT, int M, int n_tiles, int k_per_split, int z, 
   const float full = steps * (feed > products ? feed : products);
   const float fill = (float)blocks / (256.f * (float)rounds), least = partial ? 0.9f : 0.75f;
   float us = (float)rounds * (full * (fill > least ? fill : least) + 3.f + (partial ? 0.12f : 0.8f) * (float)(MT * NT));
-  if (partial) us += (float)z * (float)M * (float)n_tiles * 32.f * 8.f / 5.0e6f + 5.f;
+  if (partial) us += (float)z * (float)M * (float)n_tiles * 32.f * 8.f / 5.0e6f + 5.f + (float)((z - 1) / 8) * 3.f;
   return us;
 }
 
