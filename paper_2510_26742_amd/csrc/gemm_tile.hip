@@ -301,7 +301,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // for partial sums).  The partial sums are then read and written once more (5 TB/s, a launch, and
 // 3 us for each round trip of eight ranges beyond the first: 533 tokens, prefill in ms with 7 / 8 / 9 / 10 ranges 4.870 / 4.816 /
 // 4.862 / 4.974).  It ranks tiles and
-// ranges; it does not predict a time.  gate||up in a traced pass at 256 / 512 / 768 / 816 tokens: 43.1 / 58.6 / 88.3 / 112.3 us,
+// ranges; it does not predict a time.  gate||up in a traced pass at 256 / 512 / 768 / 816 tokens: 42.5 / 59.9 / 87.7 / 112.4 us,
 // the formula 42.8 / 64.3 / 103.1 / 128.7.  Number of ranges, prefill in ms at 256 tokens with 8 / 10 / 11 / 12 / 16 ranges:
 // 3.078 / 3.046 / 3.024 / 3.030 / 3.031; 512 with 6 / 7 / 8 / 10 / 12: 4.336 / 4.306 / 4.248 / 4.300 / 4.208 .. 4.31; 768 with
 // 5 / 6 / 7 / 8 / 9: 5.523 / 5.451 / 5.393 / 5.393 / 5.425; 816 with 5 / 6 / 7 / 8: 5.998 / 5.948 / 6.033 / 6.038.
