@@ -171,122 +171,122 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // places) are on their way during the epilogue
   int nb_now = nb, m0_now = m0;
   for (int next = die_rank + ((int)gridDim.x >> 3);; next += (int)gridDim.x >> 3) {
-  f32x16 acc[NT][MT];
+    f32x16 acc[NT][MT];
 #pragma unroll
-  for (int j = 0; j < NT; j++)
+    for (int j = 0; j < NT; j++)
 #pragma unroll
-    for (int i = 0; i < MT; i++)
+      for (int i = 0; i < MT; i++)
 #pragma unroll
-      for (int r = 0; r < 16; r++) acc[j][i][r] = 0.f;
+        for (int r = 0; r < 16; r++) acc[j][i][r] = 0.f;
 
-  bf16x8 xf[2][MT], wf[2][NT];
-  constexpr int R = MT + NT, P = MT * NT;        // reads and products of a step
-  const unsigned char* const xs = smem_raw + lane * 16 + wm * MT * LT_KC * 1024;
-  const unsigned char* const ws = smem_raw + lane * 16 + (XB + wn * NT) * LT_KC * 1024;
-  // read r of step s of a group, in the order in which the products need them: x0, w0 .. , x1 ..
-  auto read = [&](int u, int s, int r) {
-    const int o = (s / LT_KC) * NF * 1024 + (s % LT_KC) * 1024;
-    if (r == 0) xf[u][0] = *reinterpret_cast<const bf16x8*>(xs + o);
-    else if (r <= NT) wf[u][r - 1] = *reinterpret_cast<const bf16x8*>(ws + o + (r - 1) * LT_KC * 1024);
-    else xf[u][r - NT] = *reinterpret_cast<const bf16x8*>(xs + o + (r - NT) * LT_KC * 1024);
-  };
-  // stage 0 (stages 1 and 2 may be on their way) and the row statistics are complete for everybody
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * L) : "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-#pragma unroll
-  for (int r = 0; r < R; r++) read(0, 0, r);
-
-  // One group of four stages; LAST: nothing beyond it is requested.  Step s multiplies the fragments of set s % 2 and reads
-  // those of step s + 1 into the other set.  In the second step of stage q the next stage must be complete for everybody
-  // (one more may be on its way); everybody has then read stage q - 1, whose place stage q + 3 takes.
-  auto group = [&](auto last_group) {
-    constexpr bool LAST = decltype(last_group)::value != 0;
-    turn = turn + 1 == groups ? 0 : turn + 1;
-    const unsigned vnext = vfirst + (unsigned)turn * (LT_GROUP * 1024u);
-    for_each<LT_GROUP>([&](auto SS) {
-      constexpr int s = decltype(SS)::value, q = s / LT_KC, u = s & 1;
-      constexpr bool boundary = u == 1 && !(LAST && q == LT_STAGES - 1);
-      constexpr bool request = u == 1 && (!LAST || q == 0);
-      constexpr bool more = !(LAST && s == LT_GROUP - 1);
-      if constexpr (boundary) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LAST && q == LT_STAGES - 2 ? 0 : L) : "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-      }
-      for_each<P>([&](auto MM) {
-        constexpr int m = decltype(MM)::value;
-#pragma unroll
-        for (int r = 0; r < R; r++)
-          if (r * P / R == m && more) read(u ^ 1, (s + 1) % LT_GROUP, r);
-        if constexpr (request) {
-          for_each<L>([&](auto I) {
-            if constexpr ((2 * decltype(I)::value + 1) * P / (2 * L) == m) issue(Int<(q + 3) % LT_STAGES>{}, I, q == 0 ? voff : vnext);
-          });
-        }
-        acc[m % NT][m / NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][m % NT], xf[u][m / NT], acc[m % NT][m / NT], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);   // this order
-      });
-    });
-    voff = vnext;
-  };
-  for (int g = 0; g + 1 < groups; g++) group(Int<0>{});
-  group(Int<1>{});
-  const float2* const stat = sstat;
-  int nb_next = 0, m0_next = 0;
-  if (WALK && next < of_die) {
+    bf16x8 xf[2][MT], wf[2][NT];
+    constexpr int R = MT + NT, P = MT * NT;        // reads and products of a step
+    const unsigned char* const xs = smem_raw + lane * 16 + wm * MT * LT_KC * 1024;
+    const unsigned char* const ws = smem_raw + lane * 16 + (XB + wn * NT) * LT_KC * 1024;
+    // read r of step s of a group, in the order in which the products need them: x0, w0 .. , x1 ..
+    auto read = [&](int u, int s, int r) {
+      const int o = (s / LT_KC) * NF * 1024 + (s % LT_KC) * 1024;
+      if (r == 0) xf[u][0] = *reinterpret_cast<const bf16x8*>(xs + o);
+      else if (r <= NT) wf[u][r - 1] = *reinterpret_cast<const bf16x8*>(ws + o + (r - 1) * LT_KC * 1024);
+      else xf[u][r - NT] = *reinterpret_cast<const bf16x8*>(xs + o + (r - NT) * LT_KC * 1024);
+    };
+    // stage 0 (stages 1 and 2 may be on their way) and the row statistics are complete for everybody
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * L) : "memory");
+    __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();   // everybody has read the last stage
-    nb_next = (first + next) / p.m_tiles;
-    m0_next = ((first + next) - nb_next * p.m_tiles) * ROWS;
-    set_sources(nb_next, m0_next);
-    sstat = reinterpret_cast<float2*>(smem + (sstat == reinterpret_cast<float2*>(smem) ? lds_tile_stat_bytes(MT) : 0));
-    if (PRO != PRO_NONE) request_planes(m0_next, 0, 1, reinterpret_cast<unsigned char*>(sstat));
-    voff = vfirst;
-    for_each<LT_STAGES - 1>([&](auto Q) { for_each<L>([&](auto I) { issue(Q, I, voff); }); });
-  }
-  if constexpr (EPI == EPI_PARTIAL) {   // whole tiles, see partial_tile_at; rows beyond the last are never read
-    const int mbs = (p.M + 31) >> 5;
+#pragma unroll
+    for (int r = 0; r < R; r++) read(0, 0, r);
+
+    // One group of four stages; LAST: nothing beyond it is requested.  Step s multiplies the fragments of set s % 2 and reads
+    // those of step s + 1 into the other set.  In the second step of stage q the next stage must be complete for everybody
+    // (one more may be on its way); everybody has then read stage q - 1, whose place stage q + 3 takes.
+    auto group = [&](auto last_group) {
+      constexpr bool LAST = decltype(last_group)::value != 0;
+      turn = turn + 1 == groups ? 0 : turn + 1;
+      const unsigned vnext = vfirst + (unsigned)turn * (LT_GROUP * 1024u);
+      for_each<LT_GROUP>([&](auto SS) {
+        constexpr int s = decltype(SS)::value, q = s / LT_KC, u = s & 1;
+        constexpr bool boundary = u == 1 && !(LAST && q == LT_STAGES - 1);
+        constexpr bool request = u == 1 && (!LAST || q == 0);
+        constexpr bool more = !(LAST && s == LT_GROUP - 1);
+        if constexpr (boundary) {
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LAST && q == LT_STAGES - 2 ? 0 : L) : "memory");
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+        }
+        for_each<P>([&](auto MM) {
+          constexpr int m = decltype(MM)::value;
+#pragma unroll
+          for (int r = 0; r < R; r++)
+            if (r * P / R == m && more) read(u ^ 1, (s + 1) % LT_GROUP, r);
+          if constexpr (request) {
+            for_each<L>([&](auto I) {
+              if constexpr ((2 * decltype(I)::value + 1) * P / (2 * L) == m) issue(Int<(q + 3) % LT_STAGES>{}, I, q == 0 ? voff : vnext);
+            });
+          }
+          acc[m % NT][m / NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][m % NT], xf[u][m / NT], acc[m % NT][m / NT], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);   // this order
+        });
+      });
+      voff = vnext;
+    };
+    for (int g = 0; g + 1 < groups; g++) group(Int<0>{});
+    group(Int<1>{});
+    const float2* const stat = sstat;
+    int nb_next = 0, m0_next = 0;
+    if (WALK && next < of_die) {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();   // everybody has read the last stage
+      nb_next = (first + next) / p.m_tiles;
+      m0_next = ((first + next) - nb_next * p.m_tiles) * ROWS;
+      set_sources(nb_next, m0_next);
+      sstat = reinterpret_cast<float2*>(smem + (sstat == reinterpret_cast<float2*>(smem) ? lds_tile_stat_bytes(MT) : 0));
+      if (PRO != PRO_NONE) request_planes(m0_next, 0, 1, reinterpret_cast<unsigned char*>(sstat));
+      voff = vfirst;
+      for_each<LT_STAGES - 1>([&](auto Q) { for_each<L>([&](auto I) { issue(Q, I, voff); }); });
+    }
+    if constexpr (EPI == EPI_PARTIAL) {   // whole tiles, see partial_tile_at; rows beyond the last are never read
+      const int mbs = (p.M + 31) >> 5;
+#pragma unroll
+      for (int i = 0; i < MT; i++) {
+        const int mb = (m0_now >> 5) + wm * MT + i;
+#pragma unroll
+        for (int j = 0; j < NT; j++) {
+          const int nt = nb_now * WB + wn * NT + j;
+          if (mb < mbs && nt < p.n_tiles) {   // uniform
+            float* const dst = p.out_f32 + (((size_t)blockIdx.y * mbs + mb) * p.n_tiles + nt) * 1024 + lane * 4;
+#pragma unroll
+            for (int q = 0; q < 4; q++) *reinterpret_cast<f32x4*>(dst + q * 256) = f32x4{acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
+          }
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < MT; i++) {
-      const int mb = (m0_now >> 5) + wm * MT + i;
+      const int row = (wm * MT + i) * 32 + lq, m = m0_now + row;
+      if (m < p.M) {
+        float ssum = 0.f, ssq = 0.f;
+        if (PRO != PRO_NONE) {
+          const float2 v = stat[row];
+          ssum = v.x;
+          ssq = v.y;
+        }
 #pragma unroll
-      for (int j = 0; j < NT; j++) {
-        const int nt = nb_now * WB + wn * NT + j;
-        if (mb < mbs && nt < p.n_tiles) {   // uniform
-          float* const dst = p.out_f32 + (((size_t)blockIdx.y * mbs + mb) * p.n_tiles + nt) * 1024 + lane * 4;
-#pragma unroll
-          for (int q = 0; q < 4; q++) *reinterpret_cast<f32x4*>(dst + q * 256) = f32x4{acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
+        for (int j = 0; j < NT; j++) {
+          const int nt = nb_now * WB + wn * NT + j;
+          if (nt < p.n_tiles) {
+            EpiOps ops;
+            epilogue_preload<PRO, EPI>(p, nt, m, lh, ops);
+            epilogue_tile<PRO, EPI>(p, acc[j][i], nt, m, lh, ssum, ssq, blockIdx.y, ops);
+          }
         }
       }
     }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < MT; i++) {
-    const int row = (wm * MT + i) * 32 + lq, m = m0_now + row;
-    if (m < p.M) {
-      float ssum = 0.f, ssq = 0.f;
-      if (PRO != PRO_NONE) {
-        const float2 v = stat[row];
-        ssum = v.x;
-        ssq = v.y;
-      }
-#pragma unroll
-      for (int j = 0; j < NT; j++) {
-        const int nt = nb_now * WB + wn * NT + j;
-        if (nt < p.n_tiles) {
-          EpiOps ops;
-          epilogue_preload<PRO, EPI>(p, nt, m, lh, ops);
-          epilogue_tile<PRO, EPI>(p, acc[j][i], nt, m, lh, ssum, ssq, blockIdx.y, ops);
-        }
-      }
-    }
-  }
-  if (!WALK || next >= of_die) return;
-  nb_now = nb_next;
-  m0_now = m0_next;
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the counts below take no stores
+    if (!WALK || next >= of_die) return;
+    nb_now = nb_next;
+    m0_now = m0_next;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the counts below take no stores
   }
 }
 
