@@ -273,6 +273,9 @@ __global__ __launch_bounds__(64 * WN) __attribute__((amdgpu_waves_per_eu(OCC, OC
         epilogue_preload<PRO, EPI>(p, nt + j, m, lh, ops);
         epilogue_tile<PRO, EPI>(p, acc[j][mb], nt + j, m, lh, ssum, ssq, blockIdx.y, ops);
       }
+    } else if (EPI == EPI_QKV && (m >> 5) <= (p.M - 1) >> 5) {
+#pragma unroll
+      for (int j = 0; j < NT; j++) zero_values(p, nt + j, m, lh);
     }
   }
 }

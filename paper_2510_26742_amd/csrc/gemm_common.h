@@ -79,6 +79,20 @@ __device__ __forceinline__ bf16* epilogue_dst(const GemmParams& p, int nt, int i
   return p.vfrag + (((size_t)head * p.kv_chunks + kc) * p.nvb) * 1024 + s2 * 512 + hh * 256 + 4 * g + jp + (size_t)(dd >> 5) * 1024 + (dd & 31) * 8;
 }
 
+// EPI_QKV, a token behind the last one of its 32-token chunk: zeros where its values would go.  Its probabilities are zeros, but
+// an earlier, longer call may have left NaN there.  Keys need none: their scores are replaced, not multiplied.  (The stream GEMMs
+// store whole chunks of values by themselves.)
+__device__ __forceinline__ void zero_values(const GemmParams& p, int nt, int m, int lh) {
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    if (nt * 32 + 8 * i + 4 * lh < p.q_cols + p.k_cols) continue;
+    bf16* const dst = epilogue_dst<EPI_QKV>(p, nt, i, m, lh);
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+      if (dst != nullptr) dst[8 * j] = (bf16)0.f;
+  }
+}
+
 // Steps I0 .. I1-1 of the tile's four 8-feature steps (all of them unless a kernel shares a tile's epilogue out
 // over several waves; the residual epilogue's row statistics need the whole tile, the GeGLU one whole pairs).
 // DEP selects what is fetched: 1 = only what blocks of the operation before produced (the residual rows), 0 = only
