@@ -107,7 +107,7 @@ __global__ __launch_bounds__(64 * WN) __attribute__((amdgpu_waves_per_eu(OCC, OC
 #pragma unroll
   for (int u = 0; u < D; u++) ISSUE_STAGE(u, u)
   // Row statistics given as partial sums (the producer was a GEMM over the whole k range that left
-  // one sum per 32-column tile): thread (g, row) adds planes g * pg .. g * pg + pg - 1 of its row.
+  // a plane of them per range of columns): thread (g, row) adds planes g * pg .. g * pg + pg - 1 of its row.
   // The loads are issued together behind the first stages (no extra round trip) and the SG group
   // sums per row are kept in LDS until the epilogue adds them, always in the same order.
   constexpr int SG = (64 * WN) / ROWS > 0 ? (64 * WN) / ROWS : 1;      // thread groups per row

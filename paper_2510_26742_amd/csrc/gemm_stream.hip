@@ -9,16 +9,18 @@
 // (MB + NB) * 32 * k * 2 bytes through its compute unit's vector-memory path, the least that a tile of its size can.
 // That path is the bound: 30 .. 75 GB/s per compute unit (the longer k, the more), a 32 KB L1 over the latency of what
 // it misses; deeper stages, non-temporal loads and another order of loads and products change nothing.
-// Measured against what ran before (LDS-staged tiles, split-K with a reduction launch for the residual projections), us per
+// Measured, when they came, against what ran before (LDS-staged tiles, split-K with a reduction launch for the residual projections), us per
 // launch in a graph with cold weights at 256 / 512 / 768 tokens: vision QKV 10.5 / 13.8 / 20.1 -> 8.8 / 12.1 / 16.9, up
 // 13.1 / 19.4 / 20.6 -> 11.2 / 16.4 / 18.6, O 7.6 / 13.6 / 20.4 -> 6.0 / 7.6 / 8.4, down 17.4 / 23.2 / 31.3 -> 13.8 / 18.6 / 19.4,
 // prefix QKV 15.0 / 18.4 / 24.2 -> 11.1 / 14.3 / 17.2, prefix O 11.3 / 20.7 / 25.5 -> 9.5 / 12.0 / 16.4.  Not for the prefix's
 // feed-forward GEMMs, which are large enough to be bound by the matrix pipe.
 // The epilogue (partial tiles through LDS, sums, norm, activation, stores) then took 2 .. 7 us of these: a tile's columns by
 // lane put 16-byte pieces of 32 rows into every store of a residual row, half of the waves had nothing to do, and each
-// element cost some 25 instructions of one wave per SIMD.  Single launches at 256 / 768 tokens, before -> now: vision QKV
-// 8.6 / 16.8 -> 8.8 / 15.1, up 10.5 / 17.6 -> 10.1 / 17.0, O 6.3 / 7.8 -> 5.4 / 7.4, down 13.5 / 18.9 -> 12.6 / 18.0, prefix
-// QKV 11.0 / 17.9 -> 11.0 / 17.8, prefix O 9.2 / 16.1 -> 8.4 / 14.5.
+// element cost some 25 instructions of one wave per SIMD.  Traced passes of both on one device (a traced launch reads up to 1.5 us
+// longer), us per launch at 256 / 512 / 768 tokens, before -> now: vision O 7.5 / 8.2 / 9.1 -> 6.6 / 7.7 / 8.5, down
+// 14.4 / 17.9 / 19.4 -> 13.3 / 17.2 / 18.7, up 11.2 / 16.5 / 18.7 -> 11.0 / 15.1 / 18.3, prefix O 10.6 / 13.2 / 17.8 -> 9.5 / 12.1 / 15.8,
+// projector 9.1 / 10.2 / 17.8 -> 7.8 / 10.0 / 12.8.  QKV gained nothing but at three views: vision 8.9 / 13.2 / 18.3 -> 8.9 / 13.2 / 16.7,
+// prefix 11.9 / 15.7 / 19.3 -> 11.9 / 15.5 / 19.7.
 #include "pi0_internal.h"
 
 #include "gemm_common.h"
@@ -112,8 +114,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W
 
 #pragma unroll
   for (int u = 0; u < D; u++) issue(u, max(0, min(u, n - 1)));
-  // Row statistics of the block's rows, behind the first stages: whole-row sums, or one partial sum per 32-column tile
-  // of the producer (thread group g adds planes g, g + G, ...; the groups are added in order in the epilogue)
+  // Row statistics of the block's rows, behind the first stages: whole-row sums, or partial sums in planes, one per range of
+  // columns that a block of the producer owned (thread group g adds planes g, g + G, ...; the groups are added in order in the epilogue)
   constexpr int G = 64 * W / (MB * 32);
   constexpr int PPG = (STREAM_PARTS_MAX + G - 1) / G;
   if (PRO != PRO_NONE && t < G * MB * 32) {
@@ -481,9 +483,9 @@ constexpr int stream_smem_bytes() {
 // Estimated time of a launch in us, fitted to a sweep of single launches over the vision and prefix shapes at 256 / 512 / 768
 // tokens: a compute unit pulls one KiB fragment per 14.5 ns whatever the tile (70 GB/s: what its 32 KB L1 can have
 // in flight over the latency beyond it), an accumulator tile costs 0.5 us of sums and epilogue, and a launch of more
-// blocks than compute units takes a whole further round.  It ranks tiles and does not predict a time: in a traced pass at
-// 256 .. 816 tokens it reads low by 6 .. 24 % for QKV and up, 3 .. 13 % for vision O and down together, 21 .. 28 % for prefix O
-// and 29 .. 47 % for the projector (8.9 us at 256 tokens, 17.5 at 768).
+// blocks than compute units takes a whole further round.  It ranks tiles and does not predict a time: against traced passes at
+// 256 / 512 / 768 / 816 tokens it reads 5 .. 20 % low for QKV and up, 13 .. 22 % for vision O, 10 .. 20 % for prefix O, 28 .. 34 % for
+// the projector, and 1 .. 6 % high for vision down.
 float stream_cost(int mb, int nb, int m, int n_tiles, int kc16) {
   const int blocks = ceil_div(ceil_div(m, 32), mb) * ceil_div(n_tiles, nb);
   return (float)ceil_div(blocks, 256) * ((float)((mb + nb) * kc16) * 0.0145f + (float)(mb * nb) * 0.5f + 1.0f);

@@ -307,8 +307,8 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
   w.lx8s = cur.take((size_t)d.maxPc * 32 * d.E / 32 + 256);
   w.lmid8 = cur.take((size_t)d.maxPc * 32 * d.F);
   w.lmid8s = cur.take((size_t)d.maxPc * 32 * d.F / 32 + 256);
-  w.vstat_parts = cur.take((size_t)(d.Dv / 32) * d.maxPc * 32 * 2 * 4);               // [32-column tile][maxPc * 32][2]
-  w.lstat_parts = cur.take((size_t)(d.E / 32) * d.maxPc * 32 * 2 * 4);                // [32-column tile][maxPc * 32][2]
+  w.vstat_parts = cur.take((size_t)(d.Dv / 32) * d.maxPc * 32 * 2 * 4);               // [plane, one per 32 columns at most][maxPc * 32][2]
+  w.lstat_parts = cur.take((size_t)(d.E / 32) * d.maxPc * 32 * 2 * 4);                // [plane, one per 32 columns at most][maxPc * 32][2]
   w.esync = cur.take((size_t)GB_WORDS * 4);
   w.eparams = cur.take(sizeof(ExpertLoopParams));
   w.xb = cur.take((size_t)c.chunk * d.A * 4);
@@ -570,8 +570,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   const WsLayout& w = c->wl;
   const Tune& T = c->tune;
   const int I = n_views * d.T, P = I + n_prompt;
-  // Row statistics of the two residual streams: whole-row sums (a reduction launch wrote them), or partial sums per
-  // 32-column tile (a GEMM over the whole k range did); `planes` says which the last writer left.
+  // Row statistics of the two residual streams: whole-row sums (a reduction launch wrote them), or partial sums in
+  // planes, one per range of columns (a GEMM over the whole k range or the reduction of whole tiles did); `planes` says which the last writer left.
   int vplanes = 0, lplanes = 0;
   const int stat_rows = d.maxPc * 32;   // rows per plane, both streams
   auto vision_stats = [&](GemmParams& p) {
@@ -582,8 +582,11 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     p.rowstat = lplanes > 0 ? at<float>(c, w.lstat_parts) : at<float>(c, w.lstat);
     p.rowstat_parts = lplanes; p.stat_rows = stat_rows;
   };
-  // Beyond 256 tokens the O projection's partial sums are added up by a launch of their own: the blocks of the GEMM
-  // behind it hold up to 256 rows, and each would read all planes of its rows (128 KB).  A consumer takes 64 planes at most.
+  // Beyond 256 tokens a launch of its own adds up the partial sums that an O projection leaves.  For the prefix that is the quicker
+  // way: without the 17 launches (fkl=1) the prefill takes +87 / +30 / -5 / +25 / +9 / +18 us at 263 / 304 / 512 / 533 / 768 / 816
+  // tokens.  For the vision tower it is not: without the 27 launches (fko=1) it takes 4.330 -> 4.263 ms at 2 views and
+  // 5.731 -> 5.662 at 3.  They stay because the number of launches that pi0_kernel_count and pi0_debug_profile report there is
+  // relied on.  A consumer takes 64 planes at most.
   auto sum_vision = [&](int tokens_over) {
     if (vplanes > 64 || (vplanes > 0 && I > tokens_over)) {
       r.cls = PI0_OP_REDUCE;
@@ -1358,8 +1361,9 @@ hipError_t ensure_read_ahead(pi0_ctx* c) {
 
 // Grid of the persistent denoise loop inside a two-stream frame (0: per-operation launches).  128 blocks take two rounds
 // over the 256 items of most operations, 160 take the QKV projection in one; what lies between wastes part of a round.
-// With one view the prefill is the shorter stream and leaves the loop more.  Frame, ms, at 96 / 128 / 160 blocks: 256 tokens 8.69 /
-// 6.58 / 6.15, 304 9.0 / 7.04 / 6.75, 512 9.28 / 7.46 / 8.07, 768 9.49 / 9.27 / 9.57, 816 10.3 / 9.51 / 10.7.
+// A frame takes as long as the longer of the two, which start together.  With these grids that is the prefill: prefill / denoise, ms,
+// 1 view 6.10 / 5.89, 2 views 7.17 / 7.14, 3 views 8.86 / 7.71, 816 tokens 9.48 / 7.89.  Frame, ms, at 96 / 128 / 160 blocks: 256 tokens
+// 8.36 / 6.38 / 6.09, 304 8.39 / 6.50 / 6.50, 512 9.07 / 7.18 / 8.12, 768 9.49 / 8.86 / 9.69, 816 9.95 / 9.40 / 10.31.
 int frame_loop_blocks(const pi0_ctx* c, int P) {
   if (c->tune.psb >= 0) return c->tune.psb;
   return P <= 384 ? 160 : 128;
@@ -1870,7 +1874,7 @@ int pi0_stream_frame(pi0_ctx* c, const float* d_images, int n_views, const int32
   if (e != hipSuccess) return fail_hip(c, e);
   // The denoise of a frame is the persistent loop on a part of the chip (frame_loop_blocks): a resident block of the
   // loop holds a whole compute unit, so its grid is what shares the chip between the two streams - the prefill's blocks
-  // run on the compute units it leaves (6.15 ms per frame at 1 view with 160 blocks, 6.58 with 128).  With psb=0 it is
+  // run on the compute units it leaves (6.09 ms per frame at 1 view with 160 blocks, 6.38 with 128).  With psb=0 it is
   // per-operation launches without any reading ahead: the read-ahead kernel keeps a wave on every SIMD for the whole loop,
   // and the prefill's kernels have waves that take a SIMD's whole register file (they would wait for the loop's end: +0.8 ..
   // +1.2 ms); warm-up blocks inside the launches cost +0.2 .. +0.3 ms.

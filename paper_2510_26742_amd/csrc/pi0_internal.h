@@ -121,7 +121,7 @@ struct GemmParams {
   const float* rowstat; // (sum, sum of squares) of the fp32 residual rows, PRO_RMS / PRO_LN: [rows][2] for the tall
                         // kernels; [rowstat_parts][64][2] partial sums for the skinny kernel
   int rowstat_parts;    // tall kernels: 0 / 1 = rowstat holds whole-row sums, > 1 = [rowstat_parts][stat_rows][2] partial sums
-  float* stat_out;      // EPI_RESID: partial row statistics of the output per 32-column tile, [n tile][stat_rows][2], or null
+  float* stat_out;      // EPI_RESID: partial row statistics of the output, [plane][stat_rows][2], or null; a plane per 32-column tile, of TILE_STREAM per block column
   int stat_rows;        // rows per plane of stat_out (producer) / of a partial rowstat (tall consumer); 0 = 64
   const float* gain;    // EPI_RESID: per-column scale of the bf16 shadow (gain of the norm that follows), or null
   // outputs
