@@ -19,7 +19,7 @@
 // element cost some 25 instructions of one wave per SIMD.  Traced passes of both on one device (a traced launch reads up to 1.5 us
 // longer), us per launch at 256 / 512 / 768 tokens, before -> now: vision O 7.5 / 8.2 / 9.1 -> 6.6 / 7.7 / 8.5, down
 // 14.4 / 17.9 / 19.4 -> 13.3 / 17.2 / 18.7, up 11.2 / 16.5 / 18.7 -> 11.0 / 15.1 / 18.3, prefix O 10.6 / 13.2 / 17.8 -> 9.5 / 12.1 / 15.8,
-// projector 9.1 / 10.2 / 17.8 -> 7.8 / 10.0 / 12.8.  QKV gained nothing but at three views: vision 8.9 / 13.2 / 18.3 -> 8.9 / 13.2 / 16.7,
+// projector 9.1 / 10.2 / 17.8 -> 7.8 / 10.0 / 12.8.  QKV gained nothing, except vision's at three views: vision 8.9 / 13.2 / 18.3 -> 8.9 / 13.2 / 16.7,
 // prefix 11.9 / 15.7 / 19.3 -> 11.9 / 15.5 / 19.7.
 #include "pi0_internal.h"
 
