@@ -134,7 +134,8 @@ int pi0_clock_sample(long long* d_out, void* hip_stream);
 int pi0_read_ahead_probe(const void* d_buf, size_t bytes, int layers, int steps, int lead, const int* d_progress,
                          long long wait_ticks, int blocks, unsigned* d_sink, double* h_ms, void* hip_stream);
 
-/* Number of kernel launches of one pi0_infer's graph for the given shape (0 on bad arguments).  The copies of the inputs
+/* Number of kernel launches of one inference for the given shape (0 on bad arguments), the prefill launch by launch as pi0_prefill
+ * issues it.  (Where pi0_infer runs the vision tower's layers as one kernel its graph has two launches in their place.)  The copies of the inputs
  * before it and of the actions behind it (a launch each) and the read-ahead kernel on the ctx's own stream are not counted. */
 int pi0_kernel_count(const pi0_ctx* ctx, int n_views, int n_prompt);
 
@@ -215,7 +216,8 @@ int pi0_set_loop_trace(pi0_ctx* ctx, long long* d_trace, int ops_cap);
  * warm-up block counts (pfq, pfa, pfo, pfd), switches (ae16, qms, ksplit, kcps, avs, fko, fkl), pdn (1: the denoise loop as
  * one persistent kernel, 0: one launch per operation) and pra (what the persistent kernel's blocks without a work item read
  * ahead: 1 gate||up, 2 down, 4 next layer's QKV, 8 next layer's O weights during the attention; 16 this layer's O weights
- * during QKV; 32: every block what blocks of its own die will ask for) and psb (blocks of the persistent kernel inside a two-stream frame;
+ * during QKV; 32: every block what blocks of its own die will ask for), pvl (pi0_infer: 1 the vision tower as one
+ * persistent kernel, 0 as launches) and psb (blocks of the persistent kernel inside a two-stream frame;
  * 0: per-operation launches there, -1: chosen from the prefix size).
  * Drops every captured graph, so the next call of a shape captures again.  Must not be called while work of this
  * ctx is in flight.  The library itself never reads the environment.  Errors: EINVAL (null).

@@ -366,6 +366,148 @@ __device__ __forceinline__ void attention_body(const AttnParams p, const Cx cx, 
 }
 
 
+// ------------------------------------------------------------------------------------------------
+// Attention inside a view of 256 tokens (head dimension 72 or 80 in 80 columns, three value slices) by WR waves, inside the
+// persistent kernel of the vision tower: an item is QT tiles of 32 query rows of one head.  The sums of attention_body in their
+// order, so the same bits: a chunk's scores as two interleaved products, its sum of exponentials on its own, the chunks' sums
+// added in order, an output tile as two accumulators over the chunks.  Everything is requested at once behind the wait, Q straight into
+// registers (5 KiB per tile that the compute unit's cache serves to all waves).
+// ------------------------------------------------------------------------------------------------
+constexpr int VIEW_CHUNKS = 8;
+constexpr int attn_view_smem(int qt) { return qt * (2 * VIEW_CHUNKS * 32 * 4 + VIEW_CHUNKS * 2048); }
+
+template <int WR, int QT, class Cx>
+__device__ __forceinline__ void attention_view_body(const AttnParams& p, const Cx& cx, unsigned char* smem_raw) {
+  constexpr int S16 = 5, NVB = 3, R = VIEW_CHUNKS / WR;
+  float* mw = reinterpret_cast<float*>(smem_raw);                                                   // [QT][WR][32]
+  float* lw = mw + QT * VIEW_CHUNKS * 32;                                                           // [QT][8 chunks][32]
+  bf16* pf = reinterpret_cast<bf16*>(smem_raw + QT * 2 * VIEW_CHUNKS * 32 * 4);                     // [QT][8 chunks][2][64][8]
+  const int t = cx.tid();
+  const int lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lq = lane & 31;
+  const int lh = lane >> 5;
+  const int tile = cx.bx * QT, head = cx.by;
+  const int cbeg = tile >> 3 << 3;   // the view's first chunk
+
+  const bf16* qsrc = p.q + ((size_t)head * p.q_head_stride + (size_t)tile * S16 * 512);
+  const bf16* kbase = p.k0 + ((size_t)head * p.kv_head_stride0 + (size_t)cbeg * S16 * 512);
+  const bf16* vbase = p.v0 + ((size_t)head * p.v_head_stride0 + (size_t)cbeg * NVB * 1024 + (size_t)min(w, NVB - 1) * 1024);
+  const unsigned l8 = (unsigned)lane * 8u;
+  bf16x8 qf[QT][S16], kf[R][S16], vf[VIEW_CHUNKS][2];
+#pragma unroll
+  for (int q = 0; q < QT; q++)
+#pragma unroll
+    for (int s = 0; s < S16; s++) qf[q][s] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(qsrc + ((q * S16 + s) * 512 + l8)));
+#pragma unroll
+  for (int r = 0; r < R; r++)
+#pragma unroll
+    for (int s = 0; s < S16; s++) kf[r][s] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(kbase + ((unsigned)((w + WR * r) * S16 + s) * 512u + l8)));
+  if (w < NVB) {
+#pragma unroll
+    for (int c = 0; c < VIEW_CHUNKS; c++)
+#pragma unroll
+      for (int s2 = 0; s2 < 2; s2++) vf[c][s2] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(vbase + (unsigned)(c * NVB * 1024 + s2 * 512) + l8));
+  }
+
+  // The padding columns of queries and keys are nobody's: whatever is there counts as zero
+  const bf16x8 zero8v = {(bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f};
+  const bool padding = (S16 - 1) * 16 + 8 * lh >= p.head_dim;   // a lane's 8 columns of the last fragment
+#pragma unroll
+  for (int q = 0; q < QT; q++) qf[q][S16 - 1] = padding ? zero8v : qf[q][S16 - 1];
+#pragma unroll
+  for (int r = 0; r < R; r++) kf[r][S16 - 1] = padding ? zero8v : kf[r][S16 - 1];
+
+  // ---- scores ------------------------------------------------------------------------------------
+  float sv[QT][R][16];
+#pragma unroll
+  for (int q = 0; q < QT; q++) {
+    float m_loc = NEG_BIG;
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      f32x16 sacc, sacc1;
+#pragma unroll
+      for (int e = 0; e < 16; e++) sacc[e] = 0.f, sacc1[e] = 0.f;
+#pragma unroll
+      for (int s = 0; s < S16; s++) {
+        if (s & 1) sacc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[r][s], qf[q][s], sacc1, 0, 0, 0);
+        else sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[r][s], qf[q][s], sacc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 16; e++) {
+        sv[q][r][e] = (sacc[e] + sacc1[e]) * p.scale;
+        m_loc = fmaxf(m_loc, sv[q][r][e]);
+      }
+    }
+    m_loc = max_xor32(m_loc);
+    if (lh == 0) mw[(q * WR + w) * 32 + lq] = m_loc;
+  }
+  __syncthreads();
+  // ---- probabilities -> B-operand fragments in LDS -----------------------------------------------
+#pragma unroll
+  for (int q = 0; q < QT; q++) {
+    float m_all = NEG_BIG;
+#pragma unroll
+    for (int i = 0; i < WR; i++) m_all = fmaxf(m_all, mw[(q * WR + i) * 32 + lq]);
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      float pr[16], l_loc = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; e++) {
+        pr[e] = sv[q][r][e] > 0.5f * NEG_BIG ? __expf(sv[q][r][e] - m_all) : 0.f;
+        l_loc += pr[e];
+      }
+      const int c = w + WR * r;
+#pragma unroll
+      for (int s2 = 0; s2 < 2; s2++) {
+        bf16x8 pb;
+#pragma unroll
+        for (int j = 0; j < 8; j++) pb[j] = (bf16)pr[8 * s2 + j];
+        *reinterpret_cast<bf16x8*>(pf + ((size_t)((q * VIEW_CHUNKS + c) * 2 + s2) * 64 + lane) * 8) = pb;
+      }
+      l_loc = add_xor32(l_loc);
+      if (lh == 0) lw[(q * VIEW_CHUNKS + c) * 32 + lq] = l_loc;
+    }
+  }
+  __syncthreads();
+  if (w >= NVB) return;
+  // ---- output: wave w the columns 32 w .. of the head --------------------------------------------
+#pragma unroll 1
+  for (int q = 0; q < QT; q++) {
+    bf16x8 bp[VIEW_CHUNKS][2];
+    float l_part[VIEW_CHUNKS];
+#pragma unroll
+    for (int c = 0; c < VIEW_CHUNKS; c++) {
+#pragma unroll
+      for (int s2 = 0; s2 < 2; s2++) bp[c][s2] = *reinterpret_cast<const bf16x8*>(pf + ((size_t)((q * VIEW_CHUNKS + c) * 2 + s2) * 64 + lane) * 8);
+      l_part[c] = lw[(q * VIEW_CHUNKS + c) * 32 + lq];
+    }
+    f32x16 o, o1;
+#pragma unroll
+    for (int e = 0; e < 16; e++) o[e] = 0.f, o1[e] = 0.f;
+#pragma unroll
+    for (int c = 0; c < VIEW_CHUNKS; c++) {
+      o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[c][0], bp[c][0], o, 0, 0, 0);
+      o1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[c][1], bp[c][1], o1, 0, 0, 0);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; e++) o[e] += o1[e];
+    float l_all = 0.f;
+#pragma unroll
+    for (int c = 0; c < VIEW_CHUNKS; c++) l_all += l_part[c];
+    const float inv = 1.0f / l_all;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int d = w * 32 + 8 * i + 4 * lh;
+      if (d < p.head_dim) {
+        const bf16x4 ob = {(bf16)(o[4 * i] * inv), (bf16)(o[4 * i + 1] * inv), (bf16)(o[4 * i + 2] * inv), (bf16)(o[4 * i + 3] * inv)};
+        const int col = head * p.head_dim + d;
+        cx.st(reinterpret_cast<bf16x4*>(p.out + ((size_t)(tile + q) * (p.out_ld >> 4) + (col >> 4)) * 512 + (((col & 15) >> 3) * 32 + lq) * 8 + (col & 7)), ob);
+      }
+    }
+  }
+}
+
 template <int DQK>
 static constexpr int attn_smem_bytes(int ntot) { return 3 * (DQK / 16) * 1024 + 2 * ATT_WAVES * 32 * 4 + ntot * 2048; }
 

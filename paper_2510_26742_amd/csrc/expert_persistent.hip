@@ -17,6 +17,7 @@
 // one inside a die and one between dies.
 #include "attention_body.h"
 #include "expert_loop.h"
+#include "persistent_common.h"
 
 namespace {
 
@@ -34,24 +35,6 @@ static_assert(PK_TAIL >= SK_WAVES * 8 * 1024 && ATTN_SUFFIX_SMEM >= SK_WAVES * 6
 // 8 loads in flight (4 finish too late, 16 disturb the working blocks' loads more than they gain: pi0_denoise
 // 5.47 / 5.42 / 5.48 ms on one device, before the flag barrier); the values are folded into a word that is stored only if it equals a constant, so no result
 // depends on them.
-template <class F>
-__device__ __forceinline__ unsigned read_ahead_part(unsigned n16, int part, int nparts, int tid, unsigned fold, F&& addr) {
-  const unsigned per = (n16 + (unsigned)nparts - 1) / (unsigned)nparts;
-  const unsigned beg = (unsigned)part * per;
-  const unsigned end = beg + per < n16 ? beg + per : n16;
-  for (unsigned i = beg + (unsigned)tid; i < end; i += 8 * PK_THREADS) {
-    u32x4_t v[8];
-#pragma unroll
-    for (int j = 0; j < 8; j++) {
-      const unsigned idx = i + (unsigned)j * PK_THREADS;
-      v[j] = *reinterpret_cast<const u32x4_t*>(addr(idx < end ? idx : end - 1));   // clamped, unconditional
-    }
-#pragma unroll
-    for (int j = 0; j < 8; j++) fold ^= v[j][0] ^ v[j][1] ^ v[j][2] ^ v[j][3];
-  }
-  return fold;
-}
-
 // The same for a packed weight matrix of n_tiles 32-feature tiles of kc16 KiB, shared out so that a block reads what
 // blocks of its own die will ask for (their L2 then holds it: the second request is one die-local round trip).  Work
 // items go to blocks in turn and consecutive blocks to different dies, so items u, u + 8, ... share a die.  UNIT: what
@@ -70,56 +53,11 @@ __device__ __forceinline__ unsigned read_ahead_weights(const bf16* w, int n_tile
     part >>= 3;
     nparts >>= 3;
   }
-  return read_ahead_part(n * unit16, part, nparts, tid, fold, [&](unsigned i) {
+  return read_ahead_part<PK_THREADS>(n * unit16, part, nparts, tid, fold, [&](unsigned i) {
     const unsigned j = i / unit16, c = i - j * unit16, u = u0 + j * du;
     if (UNIT == 0) return base + (size_t)(u >> 1) * (unsigned)kc16 * 1024u + (c >> 5) * 1024u + ((c >> 4) & 1u) * 512u + (u & 1u) * 256u + (c & 15u) * 16u;
     return base + (size_t)u * unit16 * 16u + (size_t)c * 16u;
   });
-}
-
-// block: this block's place in the order in which the operation's items are handed out
-template <class F>
-__device__ __forceinline__ void for_items(int n_items, F&& f, int block = (int)blockIdx.x) {
-  bool first = true;
-  for (int it = block; it < n_items; it += (int)gridDim.x) {
-    if (!first) __syncthreads();   // shared memory of the item before is free
-    f(it);
-    first = false;
-  }
-}
-
-// The parameter block lives in device memory and every operation reads its own part afresh: taken by value, the
-// operations' pointers and sizes stay live across the whole loop and the kernel spills hundreds of registers.  It is read
-// through the constant address space (scalar loads; as generic memory it was read with FLAT vector loads that queued
-// behind the prefetches in flight), and the pointers in it are declared global.
-typedef const __attribute__((address_space(4))) ExpertLoopParams* ParamsPtr;
-__device__ __forceinline__ const ExpertLoopParams& fresh(ParamsPtr p) {
-  asm volatile("" : "+s"(p));   // nothing read through the pointer before this point is reused after it
-  return *(const ExpertLoopParams*)p;
-}
-__device__ __forceinline__ GemmParams global(const GemmParams& src) {
-  GemmParams p = src;
-  p.X = as_global(p.X);
-  p.W.w = as_global(p.W.w);
-  p.bias = as_global(p.bias);
-  p.colsum = as_global(p.colsum);
-  p.rowstat = as_global(p.rowstat);
-  p.stat_out = as_global(p.stat_out);
-  p.gain = as_global(p.gain);
-  p.out_f32 = as_global(p.out_f32);
-  p.out_bf16 = as_global(p.out_bf16);
-  p.resid = as_global(p.resid);
-  p.kfrag = as_global(p.kfrag);
-  p.vfrag = as_global(p.vfrag);
-  p.rope = as_global(p.rope);
-  p.xsplit_ml = as_global(p.xsplit_ml);
-  return p;
-}
-__device__ __forceinline__ AttnParams global(const AttnParams& src) {
-  AttnParams p = src;
-  p.k0 = as_global(p.k0);
-  p.v0 = as_global(p.v0);
-  return p;
 }
 
 // The out-projection's context where every block computes the rows of x that it goes on with: they come from one buffer and go
@@ -158,8 +96,8 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   using PersistCtx = PersistCtxT<false, TRACE>;
   GridBarrierT<TRACE> bar;
-  const ParamsPtr Pg = (ParamsPtr)params;
-  const ExpertLoopParams& P = fresh(Pg);
+  const ParamsPtr<ExpertLoopParams> Pg = (ParamsPtr<ExpertLoopParams>)params;
+  const ExpertLoopParams& P = fresh<ExpertLoopParams>(Pg);
   // The attention's items start at the first block without a QKV item: such a block requests its share of the prefix
   // cache when the QKV projection begins, and has it when the projection ends.
   const int att_off = P.qkv.n_tiles * 2 < (int)gridDim.x ? P.qkv.n_tiles * 2 : 0;
@@ -224,7 +162,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
   // the out-projection, which every block computes for itself (64 KB behind the wait, as for QKV) and leaves in LDS; one block
   // of each half also writes them out.  As two operations they were 3.4 + 0.6 + 3.1 us, ten times.  k = -1: the embedding alone.
   auto euler_embed = [&](int k) {
-    const ExpertLoopParams& F = fresh(Pg);
+    const ExpertLoopParams& F = fresh<ExpertLoopParams>(Pg);
     const bool more = k + 1 < steps;
     ActionEmbedArgs a = F.emb.a;
     a.wfold = as_global(a.wfold);
@@ -260,14 +198,14 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
       op_begin();
       // ---- C2: second linear of the action/time MLP -> suffix rows 1 .. chunk --------------------------
       {
-        const GemmParams t = global(fresh(Pg).tout);
+        const GemmParams t = global(fresh<ExpertLoopParams>(Pg).tout);
         for_items(t.n_tiles * 2, [&](int it) { gemm_skinny_body<PRO_NONE, EPI_RESID, 1>(t, item(it % t.n_tiles, 0, it / t.n_tiles), smem_raw); });
       }
       op_end();
       for (int l = 0; l < layers; l++) {
         op_begin();
         {  // ---- C3: RMS -> QKV, RoPE at positions P .. P + 63 -------------------------------------
-          const ExpertLoopParams& F = fresh(Pg);
+          const ExpertLoopParams& F = fresh<ExpertLoopParams>(Pg);
           GemmParams q = global(F.qkv);
           q.W.w += (size_t)l * F.w_stride;
           char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
@@ -297,7 +235,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         }
         op_begin();
         {  // ---- C4 + C5: scores, block mask, softmax, PV over [cache ; own keys] ---------------------
-          const ExpertLoopParams& F = fresh(Pg);
+          const ExpertLoopParams& F = fresh<ExpertLoopParams>(Pg);
           AttnParams a = global(F.att);
           a.k0 += (size_t)l * F.kcache_stride;
           a.v0 += (size_t)l * F.vcache_stride;
@@ -338,7 +276,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         }
         op_begin();
         {  // ---- C6: O projection + residual ------------------------------------------------------
-          const ExpertLoopParams& F = fresh(Pg);
+          const ExpertLoopParams& F = fresh<ExpertLoopParams>(Pg);
           GemmParams o = global(F.o);
           o.W.w += (size_t)l * F.w_stride;
           o.gain = as_global(F.g_mlp0) + (size_t)l * F.gain_stride;
@@ -353,7 +291,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         }
         op_begin();
         {  // ---- C7: RMS -> gate||up, fused gate -----------------------------------------------------
-          const ExpertLoopParams& F = fresh(Pg);
+          const ExpertLoopParams& F = fresh<ExpertLoopParams>(Pg);
           GemmParams g = global(F.gu);
           g.W.w += (size_t)l * F.w_stride;
           char* slot = as_global(F.ring) + (size_t)(k * layers + l) * F.ring_stride;
@@ -372,7 +310,7 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
         }
         op_begin();
         {  // ---- C8: down + residual -----------------------------------------------------------------
-          const ExpertLoopParams& F = fresh(Pg);
+          const ExpertLoopParams& F = fresh<ExpertLoopParams>(Pg);
           GemmParams d = global(F.dn);
           d.W.w += (size_t)l * F.w_stride;
           d.gain = as_global(l + 1 < F.layers ? F.g_attn0 + (size_t)(l + 1) * F.gain_stride : F.g_final);

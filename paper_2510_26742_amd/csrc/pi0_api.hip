@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "expert_loop.h"
+#include "vision_loop.h"
 #include "pi0_internal.h"
 
 namespace {
@@ -157,6 +158,10 @@ struct WsLayout {
   size_t esync, eparams, xb;         // persistent denoise kernel: barrier words, parameter block, second buffer of x
   size_t ering, ering_slot;          // ... its ring of per-layer-step activation buffers, bytes per slot
   unsigned r_yb_o, r_st_o, r_yb_d, r_st_d, r_q, r_k, r_v, r_attn, r_ml, r_mid;   // byte offsets inside a slot
+  // persistent vision tower: barrier words, parameter block, ring of per-layer activation buffers (where the expert's is; vring_slot 0: the
+  // shape is not one it covers), byte offsets inside a slot
+  size_t vsync, vparams, vring, vring_slot = 0;
+  unsigned rv_xb_o, rv_st_o, rv_xb_d, rv_st_d, rv_q, rv_k, rv_v, rv_attn, rv_mid;
   size_t lx8, lx8s, lmid8, lmid8s;   // MXFP8 copies of the prefix feed-forward inputs
   bool mx_ok = false;                // the prefix feed-forward shapes fit the MXFP8 kernels (multiples of 256)
   size_t total;
@@ -178,6 +183,12 @@ struct WsCursor {
 const int SK_KMAX_HOST = 1024;   // widest contraction of the expert's 32-feature skinny kernels
 const int PK_BLOCKS = 256;   // blocks of the persistent denoise kernel
 const int Z_MAX = 32;   // upper bound on split-K slices (sizes the partial-sum buffer)
+
+// Shapes of the vision tower that its persistent kernel may cover (vision_tower_persistent decides per call): whole views of 256
+// tokens, heads that 8 features never straddle, feed-forward and width in whole parts of the k range.
+bool vision_loop_geometry(const Dims& d) {
+  return d.T == 256 && d.hdv % 8 == 0 && d.hdv > 64 && d.hdv <= 80 && d.Dv % 128 == 0 && d.Fv_kp % 128 == 0 && d.Lv >= 1;
+}
 
 void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
   WsCursor cur;
@@ -312,6 +323,9 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
   w.esync = cur.take((size_t)GB_WORDS * 4);
   w.eparams = cur.take(sizeof(ExpertLoopParams));
   w.xb = cur.take((size_t)c.chunk * d.A * 4);
+  w.vsync = cur.take((size_t)GB_WORDS * 4);
+  w.vparams = cur.take(sizeof(VisionLoopParams));
+  size_t ering_bytes = 0;
   {  // one slot per (Euler step, expert layer): the same buffers as stok .. emid above, each 256-byte aligned
     WsCursor sl;
     w.r_yb_o = (unsigned)sl.take((size_t)64 * d.X * 2);
@@ -325,7 +339,25 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
     w.r_ml = (unsigned)sl.take((size_t)4 * d.H * 64 * 2 * 4);
     w.r_mid = (unsigned)sl.take((size_t)64 * d.Fx * 2);
     w.ering_slot = sl.off;
-    w.ering = cur.take(w.ering_slot * (size_t)d.steps * d.Le);
+    ering_bytes = round_up_sz(w.ering_slot * (size_t)d.steps * d.Le, 256);
+    w.ering = cur.take(ering_bytes);
+  }
+  if (vision_loop_geometry(d)) {   // one slot per vision layer: the buffers vh_b .. vmid above, each 256-byte aligned
+    const size_t I = d.maxI, heads = (size_t)d.Hv * (d.maxI / 32), planes = (size_t)(d.Dv / 32) * d.maxPc * 32 * 2 * 4;
+    WsCursor sl;
+    w.rv_xb_o = (unsigned)sl.take(I * d.Dv * 2);
+    w.rv_st_o = (unsigned)sl.take(planes);
+    w.rv_xb_d = (unsigned)sl.take(I * d.Dv * 2);
+    w.rv_st_d = (unsigned)sl.take(planes);
+    w.rv_q = (unsigned)sl.take(heads * 5 * 512 * 2);
+    w.rv_k = (unsigned)sl.take(heads * 5 * 512 * 2);
+    w.rv_v = (unsigned)sl.take(heads * 3 * 1024 * 2);
+    w.rv_attn = (unsigned)sl.take(I * d.Dv * 2);
+    w.rv_mid = (unsigned)sl.take(I * d.Fv_kp * 2);
+    w.vring_slot = sl.off;
+    const size_t bytes = w.vring_slot * (size_t)d.Lv;   // in the place of the expert's ring: the two kernels run one after the other
+    w.vring = w.ering;
+    if (bytes > ering_bytes) cur.take(bytes - ering_bytes);
   }
   w.total = cur.off;
 }
@@ -386,6 +418,8 @@ struct Tune {
   // weights in LDS: down, by die.  pi0_denoise at 1 / 2 / 3 views and 3 views + 48 tokens, ms: nothing 3.74 / - / 4.06 / 4.34, next
   // QKV 3.664 / 3.825 / 3.969 / 4.269, down and next QKV 3.684 / 3.853 / 4.010 / 4.297, down 3.630 / 3.787 / 3.945 / 4.249
   int pra = 34;
+  // the vision tower of pi0_infer as one persistent kernel (1) or as launches (0)
+  int pvl = 1;
   // two-stream frames: blocks of the persistent loop beside the prefill (0: per-operation launches).  A resident block
   // of the loop holds a whole compute unit, so its grid decides how the chip is shared between the two streams
   int psb = -1;           // -1: from the number of prefix tokens (frame_loop_blocks)
@@ -404,6 +438,7 @@ struct pi0_ctx {
   unsigned char* static_scratch = nullptr;   // that device's copy of the library's static scratch array
   long long* loop_trace = nullptr;     // optional timeline buffer of the persistent denoise kernel (pi0_set_loop_trace)
   int loop_trace_ops = 0;
+  bool vk_ok = false;                  // ... and the persistent vision kernel's
   bool pk_ok = false;                  // the device can hold the persistent denoise kernel's 256 blocks at once
   bool graph_mode = true;
   int precision = PI0_PRECISION_BF16;   // PI0_PRECISION_MXFP8_PREFIX_MLP: prefix gate||up / down on MXFP8 operands
@@ -436,6 +471,7 @@ struct Run {
                                 // blocks inside the launches with pi0_tune "ras=0"); false: neither
   int cls = PI0_OP_MISC;        // class of the launches that follow
   OpTimer* timer = nullptr;     // when set, every RUN / RUN_GEMM launch is bracketed by an event pair
+  bool vision_loop = false;     // the vision tower may run as one persistent kernel (plain pi0_infer calls)
   bool persistent_ok = false;   // the denoise loop may run as one persistent kernel (plain pi0_denoise / pi0_infer calls)
   int persist_blocks = 0;       // its grid (0: one block per compute unit)
   unsigned char* ebase = nullptr;   // where the expert's scratch block lives minus its workspace offset (null: in the workspace)
@@ -535,21 +571,28 @@ int gemm_splitk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int k
   return q.tiled ? ceil_div(n_true, 256) : 0;
 }
 
-// the same operation as one GEMM over the whole k range: bias / residual / gain-scaled shadow in the
-// GEMM's epilogue, row statistics left as one partial sum per block column in parts[plane][stat_rows][2]; returns the planes
-int gemm_fullk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int k_true, const float* bias, float* resid_io,
-                      bf16* shadow, int n_true, float* parts, int stat_rows, const float* gain,
-                      const float* resid_in = nullptr, int resid_mod = 0) {
-  GemmParams p = gp_base(r.c, pw, X, ldx, M, TILE_STREAM, k_true);
+GemmParams fullk_resid_params(pi0_ctx* c, const PW& pw, const bf16* X, int ldx, int M, int k_true, const float* bias, float* resid_io,
+                              bf16* shadow, int n_true, float* parts, int stat_rows, const float* gain) {
+  GemmParams p = gp_base(c, pw, X, ldx, M, TILE_STREAM, k_true);
   p.bias = bias;
-  p.resid = resid_in != nullptr ? resid_in : resid_io;
-  p.resid_mod = resid_mod;
+  p.resid = resid_io;
   p.out_f32 = resid_io;
   p.out_bf16 = shadow;
   p.ldo = n_true; p.ldo2 = n_true; p.n_valid = n_true;
   p.gain = gain;
   p.stat_out = parts;
   p.stat_rows = stat_rows;
+  return p;
+}
+
+// the same operation as one GEMM over the whole k range: bias / residual / gain-scaled shadow in the
+// GEMM's epilogue, row statistics left as one partial sum per block column in parts[plane][stat_rows][2]; returns the planes
+int gemm_fullk_resid(Run& r, const PW& pw, const bf16* X, int ldx, int M, int k_true, const float* bias, float* resid_io,
+                      bf16* shadow, int n_true, float* parts, int stat_rows, const float* gain,
+                      const float* resid_in = nullptr, int resid_mod = 0) {
+  GemmParams p = fullk_resid_params(r.c, pw, X, ldx, M, k_true, bias, resid_io, shadow, n_true, parts, stat_rows, gain);
+  if (resid_in != nullptr) p.resid = resid_in;
+  p.resid_mod = resid_mod;
   RUN_GEMM(r, TILE_STREAM, PRO_NONE, EPI_RESID, p, 1);
   return gemm_stream_stat_planes(PRO_NONE, M, p.n_tiles, pw.k_pad);
 }
@@ -563,6 +606,124 @@ struct Taps {
     off += n;
   }
 };
+
+// Parameters of a vision layer's operations, for their launches and for the persistent kernel
+GemmParams vision_qkv_params(pi0_ctx* c, const WsVis& L, int I, int tile) {
+  const Dims& d = c->d;
+  const WsLayout& w = c->wl;
+  const int vchunks = I / 32;
+  GemmParams p = gp_base(c, L.qkv, at<bf16>(c, w.vh_b), d.Dv, I, tile, d.Dv);
+  p.bias = at<float>(c, L.qkv.bias);
+  p.colsum = at<float>(c, L.qkv.colsum);
+  p.out_bf16 = at<bf16>(c, w.vq);
+  p.q_mbs = vchunks;
+  p.kfrag = at<bf16>(c, w.vk);
+  p.vfrag = at<bf16>(c, w.vv);
+  p.rope = nullptr;
+  p.q_cols = d.Dv; p.k_cols = d.Dv;
+  p.head_dim = d.hdv; p.dqk_pad = 80; p.nvb = 3; p.kv_heads = d.Hv; p.kv_chunks = vchunks;
+  return p;
+}
+AttnParams vision_attn_params(pi0_ctx* c, int I) {
+  const Dims& d = c->d;
+  const WsLayout& w = c->wl;
+  const int vchunks = I / 32;
+  AttnParams a;
+  memset(&a, 0, sizeof(a));
+  a.q = at<bf16>(c, w.vq); a.q_head_stride = vchunks * 5 * 512;
+  a.Tq = I; a.heads = d.Hv;
+  a.k0 = at<bf16>(c, w.vk); a.v0 = at<bf16>(c, w.vv);
+  a.chunks0 = vchunks; a.valid0 = I;
+  a.kv_head_stride0 = vchunks * 5 * 512; a.v_head_stride0 = vchunks * 3 * 1024;
+  a.view_tokens = d.T;
+  a.scale = 1.0f / sqrtf((float)d.hdv);
+  a.out = at<bf16>(c, w.vattn); a.out_ld = d.Dv; a.head_dim = d.hdv;
+  return a;
+}
+GemmParams vision_up_params(pi0_ctx* c, const WsVis& L, int I, int tile) {
+  const Dims& d = c->d;
+  GemmParams p = gp_base(c, L.up, at<bf16>(c, c->wl.vh_b), d.Dv, I, tile, d.Dv);
+  p.bias = at<float>(c, L.up.bias);
+  p.colsum = at<float>(c, L.up.colsum);
+  p.out_bf16 = at<bf16>(c, c->wl.vmid);
+  p.ldo = d.Fv_kp; p.n_valid = L.up.n_pad; p.act = ACT_GELU;
+  return p;
+}
+
+// The vision tower's layers as ONE persistent kernel (vision_persistent.hip): the operations' parameters exactly as the launches
+// have them for layer 0, plus the strides between layers.  Returns false (nothing launched) when the call, the shape or the tuning choices
+// are outside what the kernel covers.  planes: of the row statistics that the patch embedding left.  The projector's input, its statistics and
+// their planes are where *out, *stats and *planes_out say.
+bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_rows, const bf16** out, const float** stats, int* planes_out) {
+  pi0_ctx* c = r.c;
+  const Dims& d = c->d;
+  const WsLayout& w = c->wl;
+  const Tune& T = c->tune;
+  if (!r.vision_loop || r.count_only || r.timer != nullptr || !T.pvl || !c->vk_ok || w.vring_slot == 0) return false;
+  // the launches' own choices, so that both give the same bits
+  if (T.vis >= 0 || T.vqkv >= 0 || T.vup >= 0 || T.vo >= 0 || T.zvo >= 0 || T.vd >= 0 || T.zvd >= 0 || T.fko >= 0) return false;
+  VisionTiles tiles;
+  if (!vision_loop_tiles(n_views, &tiles) || planes < 1) return false;
+  const WsVis& L0 = w.vis[0];
+  auto same = [&](const VisionTile& t, int pro, int epi, const PW& pw) {
+    int mb, nb, parts;
+    return gemm_stream_tile(pro, epi, I, pw.n_pad / 32, pw.k_pad, &mb, &nb, &parts) && mb == t.mb && nb == t.nb && parts == t.parts && t.takes(pw.k_pad);
+  };
+  if (!same(tiles.qkv, PRO_LN, EPI_QKV, L0.qkv) || !same(tiles.resid, PRO_NONE, EPI_RESID, L0.o) || !same(tiles.up, PRO_LN, EPI_BF16, L0.up) ||
+      !same(tiles.resid, PRO_NONE, EPI_RESID, L0.down))
+    return false;
+  const int rest = ceil_div(L0.o.n_pad / 32, tiles.resid.nb);
+  if (planes != vision_loop_planes(n_views) || rest != planes) return false;
+  const size_t stride = d.Lv > 1 ? w.vis[1].qkv.w - L0.qkv.w : 0, gst = d.Lv > 1 ? w.g_v1[1] - w.g_v1[0] : 0;
+  for (int l = 1; l < d.Lv; l++) {
+    const PW *A[4] = {&w.vis[l - 1].qkv, &w.vis[l - 1].o, &w.vis[l - 1].up, &w.vis[l - 1].down}, *B[4] = {&w.vis[l].qkv, &w.vis[l].o, &w.vis[l].up, &w.vis[l].down};
+    for (int i = 0; i < 4; i++) {
+      if (B[i]->w - A[i]->w != stride || B[i]->bias - A[i]->bias != stride || (A[i]->colsum != 0 && B[i]->colsum - A[i]->colsum != stride)) return false;
+    }
+    if (w.g_v1[l] - w.g_v1[l - 1] != gst || w.g_v2[l] - w.g_v2[l - 1] != gst) return false;
+  }
+  const size_t arena_bytes = w.total - w.act_begin;
+  if (arena_bytes >= (size_t)1 << 32) return false;   // offsets inside the arena are 32-bit
+  VisionLoopParams E;
+  memset(&E, 0, sizeof(E));
+  E.qkv = vision_qkv_params(c, L0, I, TILE_STREAM);
+  E.qkv.rowstat = at<float>(c, w.vstat_parts);
+  E.qkv.rowstat_parts = planes;
+  E.qkv.stat_rows = stat_rows;
+  E.att = vision_attn_params(c, I);
+  E.o = fullk_resid_params(c, L0.o, at<bf16>(c, w.vattn), d.Dv, I, d.Dv, at<float>(c, L0.o.bias), at<float>(c, w.vh), at<bf16>(c, w.vh_b), d.Dv,
+                           at<float>(c, w.vstat_parts), stat_rows, nullptr);
+  E.up = vision_up_params(c, L0, I, TILE_STREAM);
+  E.up.stat_rows = stat_rows;
+  E.down = fullk_resid_params(c, L0.down, at<bf16>(c, w.vmid), d.Fv_kp, I, d.Fv, at<float>(c, L0.down.bias), at<float>(c, w.vh), at<bf16>(c, w.vh_b),
+                              d.Dv, at<float>(c, w.vstat_parts), stat_rows, nullptr);
+  GemmParams* gs[4] = {&E.qkv, &E.o, &E.up, &E.down};
+  const VisionTile* ts[4] = {&tiles.qkv, &tiles.resid, &tiles.up, &tiles.resid};
+  for (int i = 0; i < 4; i++) gs[i]->m_tiles = ceil_div(I, ts[i]->mb * 32);
+  E.att_items = vision_loop_attention_items(n_views, d.Hv);
+  E.layers = d.Lv;
+  E.layer_stride = stride;
+  E.gain_stride = gst;
+  E.g_attn0 = at<float>(c, w.g_v1[0]);
+  E.g_mlp0 = at<float>(c, w.g_v2[0]);
+  E.g_final = at<float>(c, w.g_vf);
+  E.planes_rest = rest;
+  E.ring = reinterpret_cast<char*>(c->ws + w.vring);
+  E.ring_stride = w.vring_slot;
+  E.arena = reinterpret_cast<const char*>(c->ws + w.act_begin);
+  E.arena_bytes = (unsigned)arena_bytes;
+  E.r_xb_o = w.rv_xb_o; E.r_st_o = w.rv_st_o; E.r_xb_d = w.rv_xb_d; E.r_st_d = w.rv_st_d;
+  E.r_q = w.rv_q; E.r_k = w.rv_k; E.r_v = w.rv_v; E.r_attn = w.rv_attn; E.r_mid = w.rv_mid;
+  E.sync = at<unsigned>(c, w.vsync);
+  E.spin_limit = 1u << 20;
+  r.cls = PI0_OP_MISC;
+  RUN(r, launch_vision_loop(r.s, n_views, E, at<VisionLoopParams>(c, w.vparams), PK_BLOCKS));
+  const size_t last = w.vring + w.vring_slot * (size_t)(d.Lv - 1);
+  *out = at<bf16>(c, last + w.rv_xb_d);
+  *stats = at<float>(c, last + w.rv_st_d);
+  *planes_out = rest;
+  return true;
+}
 
 void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   pi0_ctx* c = r.c;
@@ -616,7 +777,6 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
                       at<float>(c, w.vh), at<bf16>(c, w.vh_b), d.Dv, T.vis, at<float>(c, w.vstat), at<float>(c, w.g_v1[0]),
                       at<float>(c, w.pos), d.T);
   }
-  const int vchunks = I / 32;
   const int zvo = T.zvo > 0 ? T.zvo : (I <= 256 ? 3 : I <= 512 ? 2 : 1);
   const int zvd = T.zvd > 0 ? T.zvd : (I <= 512 ? 4 : 2);
   const int tproj = T.vis >= 0 ? T.vis : TILE_STREAM;
@@ -625,36 +785,20 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   const int tvo = T.vo >= 0 ? T.vo : TILE_MID;
   const bool vo_stream = T.fko == 1 || (T.fko < 0 && T.vo < 0 && T.zvo < 0), vd_stream = T.vd < 0 && T.zvd < 0;
   const int tvd = T.vd >= 0 ? T.vd : (I <= 256 ? TILE_MID : TILE_SQ128);
-  for (int l = 0; l < d.Lv; l++) {
+  const bf16* tower_out = at<bf16>(c, w.vh_b);   // what the projector reads
+  const float* tower_stats = nullptr;            // its row statistics, if not where vision_stats says
+  const bool persistent = vision_tower_persistent(r, I, n_views, vplanes, stat_rows, &tower_out, &tower_stats, &vplanes);
+  for (int l = 0; l < d.Lv && !persistent; l++) {
     const WsVis& L = w.vis[l];
     {  // A1: LN -> QKV (+bias), keys/values straight into attention fragment order
-      GemmParams p = gp_base(c, L.qkv, at<bf16>(c, w.vh_b), d.Dv, I, tqkv, d.Dv);
-      p.bias = at<float>(c, L.qkv.bias);
-      p.colsum = at<float>(c, L.qkv.colsum);
+      GemmParams p = vision_qkv_params(c, L, I, tqkv);
       vision_stats(p);
-      p.out_bf16 = at<bf16>(c, w.vq);
-      p.q_mbs = vchunks;
-      p.kfrag = at<bf16>(c, w.vk);
-      p.vfrag = at<bf16>(c, w.vv);
-      p.rope = nullptr;
-      p.q_cols = d.Dv; p.k_cols = d.Dv;
-      p.head_dim = d.hdv; p.dqk_pad = 80; p.nvb = 3; p.kv_heads = d.Hv; p.kv_chunks = vchunks;
       r.cls = PI0_OP_VIS_QKV;
       RUN_GEMM(r, tqkv, PRO_LN, EPI_QKV, p, 1);
     }
     {  // A2: attention inside each view
-      AttnParams a;
-      memset(&a, 0, sizeof(a));
-      a.q = at<bf16>(c, w.vq); a.q_head_stride = vchunks * 5 * 512;
-      a.Tq = I; a.heads = d.Hv;
-      a.k0 = at<bf16>(c, w.vk); a.v0 = at<bf16>(c, w.vv);
-      a.chunks0 = vchunks; a.valid0 = I;
-      a.kv_head_stride0 = vchunks * 5 * 512; a.v_head_stride0 = vchunks * 3 * 1024;
-      a.view_tokens = d.T;
-      a.scale = 1.0f / sqrtf((float)d.hdv);
-      a.out = at<bf16>(c, w.vattn); a.out_ld = d.Dv; a.head_dim = d.hdv;
       r.cls = PI0_OP_VIS_ATTN;
-      RUN(r, launch_attention(r.s, a));
+      RUN(r, launch_attention(r.s, vision_attn_params(c, I)));
     }
     // A3: O-projection + bias + residual
     r.cls = PI0_OP_VIS_O;
@@ -669,12 +813,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
       vplanes = 0;
     }
     {  // A4: LN -> up (+bias, GELU)
-      GemmParams p = gp_base(c, L.up, at<bf16>(c, w.vh_b), d.Dv, I, tup, d.Dv);
-      p.bias = at<float>(c, L.up.bias);
-      p.colsum = at<float>(c, L.up.colsum);
+      GemmParams p = vision_up_params(c, L, I, tup);
       vision_stats(p);
-      p.out_bf16 = at<bf16>(c, w.vmid);
-      p.ldo = d.Fv_kp; p.n_valid = L.up.n_pad; p.act = ACT_GELU;
       r.cls = PI0_OP_VIS_UP;
       RUN_GEMM(r, tup, PRO_LN, EPI_BF16, p, 1);
     }
@@ -693,10 +833,11 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     if (taps) taps->put(r, at<float>(c, w.vh), (size_t)I * d.Dv);
   }
   {  // A6: final LN -> projector (+bias) = prefix image embeddings
-    GemmParams p = gp_base(c, w.proj, at<bf16>(c, w.vh_b), d.Dv, I, tproj, d.Dv);
+    GemmParams p = gp_base(c, w.proj, tower_out, d.Dv, I, tproj, d.Dv);
     p.bias = at<float>(c, w.proj.bias);
     p.colsum = at<float>(c, w.proj.colsum);
     vision_stats(p);
+    if (tower_stats != nullptr) p.rowstat = tower_stats;
     p.out_f32 = at<float>(c, w.lx);
     p.out_bf16 = at<bf16>(c, w.lx_b);
     p.ldo = d.E; p.ldo2 = d.E; p.n_valid = d.E;
@@ -1391,6 +1532,7 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     // two-stream frames: per-operation launches, or the loop on a part of the chip (the prefill's blocks need compute units too)
     r.persist_blocks = read_ahead ? 0 : frame_loop_blocks(c, P);
     r.persistent_ok = read_ahead || r.persist_blocks > 0;
+    r.vision_loop = kind == KIND_INFER;
     body(r);
     return r.ok() ? PI0_OK : fail_hip(c, r.err);
   }
@@ -1407,6 +1549,7 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     // two-stream frames: per-operation launches, or the loop on a part of the chip (the prefill's blocks need compute units too)
     r.persist_blocks = read_ahead ? 0 : frame_loop_blocks(c, P);
     r.persistent_ok = read_ahead || r.persist_blocks > 0;
+    r.vision_loop = kind == KIND_INFER;
     body(r);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(s, &g);
@@ -1558,7 +1701,7 @@ int pi0_tune(pi0_ctx* c, const char* env) {
         {"zld", &c->tune.zld, 1, Z_MAX}, {"zvd", &c->tune.zvd, 1, Z_MAX},
         {"pfq", &c->tune.pfq, 0, 1024}, {"pfa", &c->tune.pfa, 0, 1024}, {"pfo", &c->tune.pfo, 0, 1024},
         {"pfd", &c->tune.pfd, 0, 1024}, {"ae16", &c->tune.ae16, 0, 1}, {"ksplit", &c->tune.ksplit, 0, 1}, {"kcps", &c->tune.kcps, 2, 16}, {"qms", &c->tune.qms, 0, 1},
-        {"fko", &c->tune.fko, 0, 1}, {"fkl", &c->tune.fkl, 0, 1}, {"ras", &c->tune.ras, 0, 4096}, {"ral", &c->tune.ral, 1, 8}, {"rat", &c->tune.rat, 64, 256}, {"rad", &c->tune.rad, 1, 8 /* 7: no such variant, see below */}, {"avs", &c->tune.avs, 1, 8}, {"pdn", &c->tune.pdn, 0, 1}, {"pra", &c->tune.pra, 0, 63}, {"psb", &c->tune.psb, -1, 256}};
+        {"fko", &c->tune.fko, 0, 1}, {"fkl", &c->tune.fkl, 0, 1}, {"ras", &c->tune.ras, 0, 4096}, {"ral", &c->tune.ral, 1, 8}, {"rat", &c->tune.rat, 64, 256}, {"rad", &c->tune.rad, 1, 8 /* 7: no such variant, see below */}, {"avs", &c->tune.avs, 1, 8}, {"pdn", &c->tune.pdn, 0, 1}, {"pra", &c->tune.pra, 0, 63}, {"psb", &c->tune.psb, -1, 256}, {"pvl", &c->tune.pvl, 0, 1}};
     for (auto& k : keys) {
       const char* f = strstr(env, k.key);
       while (f != nullptr && !((f == env || f[-1] == ',') && f[strlen(k.key)] == '=')) f = strstr(f + 1, k.key);
@@ -1608,11 +1751,12 @@ int pi0_device_status(pi0_ctx* c, void* hip_stream) {
   if (c == nullptr) return PI0_EINVAL;
   if (!c->loaded) return PI0_ESTATE;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  unsigned flag = 0;
-  hipError_t e = hipMemcpyAsync(&flag, at<unsigned>(c, c->wl.esync) + GB_ERR, sizeof(flag), hipMemcpyDeviceToHost, s);
+  unsigned flags[2] = {0, 0};
+  hipError_t e = hipMemcpyAsync(&flags[0], at<unsigned>(c, c->wl.esync) + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(&flags[1], at<unsigned>(c, c->wl.vsync) + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail_hip(c, e);
-  return flag == 0u ? PI0_OK : PI0_ESTATE;
+  return flags[0] == 0u && flags[1] == 0u ? PI0_OK : PI0_ESTATE;
 }
 
 int pi0_kernel_count(const pi0_ctx* c, int n_views, int n_prompt) {
@@ -1653,6 +1797,8 @@ int pi0_load_weights(pi0_ctx* c, const void* d_blob, size_t blob_bytes, void* d_
     if (e != hipSuccess) return fail_hip(c, e);
     e = expert_loop_init_attributes();
     if (e != hipSuccess) return fail_hip(c, e);
+    e = vision_loop_init_attributes();
+    if (e != hipSuccess) return fail_hip(c, e);
     {  // the persistent kernel's barrier needs all of its blocks resident: one per compute unit, 256 of them
       int dev = 0, cus = 0, per_cu = 0;
       e = hipGetDevice(&dev);
@@ -1660,6 +1806,9 @@ int pi0_load_weights(pi0_ctx* c, const void* d_blob, size_t blob_bytes, void* d_
       if (e == hipSuccess) e = expert_loop_max_blocks_per_cu(&per_cu);
       if (e != hipSuccess) return fail_hip(c, e);
       c->pk_ok = cus >= PK_BLOCKS && per_cu >= 1;
+      e = vision_loop_max_blocks_per_cu(&per_cu);
+      if (e != hipSuccess) return fail_hip(c, e);
+      c->vk_ok = cus >= PK_BLOCKS && per_cu >= 1;
     }
     c->attrs_set = true;
   }

@@ -240,6 +240,8 @@ hipError_t gemm_lds_init_attributes();
 hipError_t gemm_stream_init_attributes();
 // planes of row statistics that the residual projection of this shape leaves (one per block column; 0: no such kernel)
 int gemm_stream_stat_planes(int pro, int M, int n_tiles, int k_pad);
+// token blocks, feature tiles and parts of the k range of the tile that launch_gemm_stream takes (M a multiple of 32); false: none
+bool gemm_stream_tile(int pro, int epi, int M, int n_tiles, int k_pad, int* mb, int* nb, int* parts);
 // out[m] = (sum, sum of squares) of row m from partial statistics [planes][stat_rows][2]
 hipError_t launch_row_sums(hipStream_t s, const float* parts, int planes, int stat_rows, int M, float* out);
 hipError_t gemm_init_attributes();
