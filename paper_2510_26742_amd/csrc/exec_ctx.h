@@ -141,10 +141,10 @@ struct GridBarrierT {
     epoch = 0;
     trace = nullptr;
     xcc = (unsigned)__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7u;   // XCC_ID, bits 3:0
-    __shared__ unsigned rank_s;
+    unsigned r = 0;
     if (threadIdx.x == 0) {
       __hip_atomic_fetch_max(&w[GB_LEADER + 32 * xcc], (unsigned)blockIdx.x + 1u + (may_lead ? 1u << 16 : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      rank_s = __hip_atomic_fetch_add(&w[GB_MEMBERS + 32 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      r = __hip_atomic_fetch_add(&w[GB_MEMBERS + 32 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // both are in place before this block counts as registered
       __hip_atomic_fetch_add(&w[GB_START], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       unsigned spins = 0;
@@ -154,7 +154,7 @@ struct GridBarrierT {
       }
     }
     __syncthreads();
-    rank = rank_s;
+    rank = (unsigned)__builtin_amdgcn_readfirstlane((int)r);   // of the first wave, which alone uses it (no shared memory: a kernel may want all of it)
     members = ld_dev(&w[GB_MEMBERS + 32 * xcc]);
     leader = (ld_dev(&w[GB_LEADER + 32 * xcc]) & 0xffffu) == (unsigned)blockIdx.x + 1u;
     present = 0;

@@ -167,8 +167,8 @@ int gemm_stream_stat_planes(int pro, int M, int n_tiles, int k_pad) {
   return c.launch == nullptr ? 0 : ceil_div(n_tiles, c.nb);
 }
 
-bool gemm_stream_tile(int pro, int epi, int M, int n_tiles, int k_pad, int* mb, int* nb, int* parts) {
-  const StreamChoice c = stream_choose(pro, epi, M, n_tiles, k_pad >> 4);
+bool gemm_stream_tile(int pro, int epi, int M, int n_tiles, int k_pad, int* mb, int* nb, int* parts, int value_tile) {
+  const StreamChoice c = stream_choose(pro, epi, M, n_tiles, k_pad >> 4, value_tile);
   *mb = c.mb;
   *nb = c.nb;
   *parts = c.parts;

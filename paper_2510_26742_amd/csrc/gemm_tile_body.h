@@ -1,0 +1,335 @@
+// Body of the prefix's large bf16 GEMMs (gemm_tile.hip says what they are), for an execution context (exec_ctx.h): the launches of
+// gemm_tile.hip, and the prefix as one persistent kernel (prefix_persistent.hip), where the weights of the first stages are requested
+// ahead of the wait for the inputs.
+#pragma once
+#include "pi0_internal.h"
+
+#include <utility>
+
+#include "gemm_common.h"
+
+template <int V>
+struct Int {
+  static constexpr int value = V;
+};
+template <class F, int... I>
+__device__ __forceinline__ void for_each_in(F&& f, std::integer_sequence<int, I...>) {
+  (f(Int<I>{}), ...);
+}
+// f(Int<0>), f(Int<1>), ...: an unrolled loop whose index is a constant for assembly operands
+template <int N, class F>
+__device__ __forceinline__ void for_each(F&& f) {
+  for_each_in(f, std::make_integer_sequence<int, N>{});
+}
+
+constexpr int lds_tile_stages(int MT, int NT) { return MT * NT <= 6 ? 8 : 4; }   // stages in LDS
+constexpr int LT_KC = 2;                       // k16 steps of a stage
+constexpr int lds_tile_group(int MT, int NT) { return 16 * LT_KC * lds_tile_stages(MT, NT); }   // of k, of a turn of the loop: k ranges are multiples of it
+
+constexpr int lds_tile_fragments(int MT, int NT) { return 2 * (MT + NT) * LT_KC; }   // of a stage
+constexpr int LT_SMEM = 160 * 1024;             // of a compute unit, which a block has to itself
+constexpr int lds_tile_stat_bytes(int MT) { return (2 * MT * 32 * 8 + 1023) / 1024 * 1024; }   // row statistics, whole requests of 1 KiB
+constexpr int lds_tile_smem(int MT, int NT) { return (MT * NT <= 6 ? 0 : lds_tile_stat_bytes(MT)) + lds_tile_stages(MT, NT) * lds_tile_fragments(MT, NT) * 1024; }
+// planes of partial row statistics that fit behind the three stages requested first (the last request may be half empty)
+constexpr int lds_tile_planes(int MT, int NT) {
+  return (LT_SMEM - lds_tile_stat_bytes(MT) - (lds_tile_stages(MT, NT) - 1) * lds_tile_fragments(MT, NT) * 1024 - 1024) / (2 * MT * 32 * 8);
+}
+// SG: groups in which planes of row statistics are added (group g: planes g, g + SG, ...; then the groups in order).
+// cx.bx, cx.by: the tile, in the order of stream_share unless p.range_per_die, and the k range.
+template <int MT, int NT, int SG, int PRO, int EPI, bool WALK, class Cx>
+__device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx, unsigned char* smem) {
+  constexpr int W = 4, LT_STAGES = lds_tile_stages(MT, NT), LT_GROUP = LT_STAGES * LT_KC;
+  constexpr int XB = 2 * MT, WB = 2 * NT;        // 32-row blocks of the two operands
+  constexpr int NF = lds_tile_fragments(MT, NT);
+  constexpr int L = NF / W;                      // fragments a wave requests per stage
+  static_assert(NF % W == 0, "even shares");
+  constexpr int ROWS = XB * 32;
+  // shared memory: row statistics, then [stage][fragment][1 KiB]; in the persistent kernel, where planes want the room, the stages first
+  float2* sstat = reinterpret_cast<float2*>(smem + (Cx::kPersistent ? LT_STAGES * NF * 1024 : 0));
+  unsigned char* const smem_raw = smem + (Cx::kPersistent || PRO == PRO_NONE ? 0 : (WALK ? 2 : 1) * lds_tile_stat_bytes(MT));
+
+  const int t = cx.tid();
+  const int lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = w & 1, wn = w >> 1;
+  const int lq = lane & 31;
+  const int lh = lane >> 5;
+
+  // tiles as in gemm_stream.hip: consecutive ids on different dies, a die takes a contiguous eighth, token tiles fastest
+  const int total = (p.n_tiles + WB - 1) / WB * p.m_tiles;
+  // ... or in order, where a die has a k range to itself
+  const bool ranges = EPI == EPI_PARTIAL && p.range_per_die != 0;
+  const int die = cx.bx & 7, die_rank = ranges ? cx.bx : cx.bx >> 3;
+  const int first = ranges ? 0 : die * (total >> 3) + min(die, total & 7), of_die = ranges ? total : (total >> 3) + (die < (total & 7) ? 1 : 0);
+  if (die_rank >= of_die) return;
+  const int nb = (first + die_rank) / p.m_tiles;
+  const int mt = (first + die_rank) - nb * p.m_tiles;
+  const int m0 = mt * ROWS;
+  const int mb_last = (p.M - 1) >> 5;
+  const int KC16 = p.W.k_pad >> 4, XKC16 = p.ldx >> 4;
+  const int kbeg = cx.by * (p.k_per_split >> 4);
+  const int groups = (min(kbeg + (p.k_per_split >> 4), KC16) - kbeg) / LT_GROUP;
+
+  // The wave's fragment i of a stage is fragment w + 4 i of the block's: operand block f / 2 (tokens first), k16 step f % 2;
+  // blocks beyond the operands repeat the last one and are not stored
+  const char* src[L];
+  auto set_sources = [&](int nb, int m0) {
+#pragma unroll
+    for (int i = 0; i < L; i++) {
+      const int f = w + W * i, b = f / LT_KC, k = f % LT_KC;
+      const char* base = b < XB ? reinterpret_cast<const char*>(p.X) + (size_t)min((m0 >> 5) + b, mb_last) * XKC16 * 1024
+                                : reinterpret_cast<const char*>(p.W.w) + (size_t)min(nb * WB + (b - XB), p.n_tiles - 1) * KC16 * 1024;
+      src[i] = base + (size_t)(kbeg + k) * 1024;
+    }
+  };
+  set_sources(nb, m0);
+  const unsigned lds0 = lds_address(smem_raw) + (unsigned)w * 1024u;
+  // Where a round of blocks reads the whole weight matrix (one token tile), all blocks would ask for the same k of their own
+  // weight rows, a power of two apart: each starts elsewhere in its range and goes round (prefill at 256 / 263 tokens
+  // 3.133 / 3.348 -> 3.099 / 3.338 ms).  With more token tiles the blocks that share weights set the pace, and 816 tokens are
+  // 25 us slower that way
+  int turn = p.m_tiles == 1 || (EPI == EPI_PARTIAL && p.M <= 320) ? (int)((unsigned)nb % (unsigned)groups) : 0;
+  const unsigned vfirst = (unsigned)lane * 16u + 4096u;
+  unsigned voff = vfirst + (unsigned)turn * (LT_GROUP * 1024u);      // of the current group: stages 0 .. 3 are at 2048 q - 4096, a 13-bit constant
+  // request the wave's fragment I of stage Q of the group at v; the constant counts towards both addresses
+  auto issue = [&](auto Q, auto I, unsigned v) {
+    constexpr int q = decltype(Q)::value, i = decltype(I)::value;
+    const unsigned l0 = lds0;
+    const char* const s = src[i];
+    constexpr int off = q % 4 * 2048 - 4096;
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4" ::"s"(l0), "v"(v + (unsigned)(q / 4) * 8192u), "s"(s),
+                 "n"((q * NF + W * i) * 1024 - off), "n"(off)
+                 : "memory", "scc");
+  };
+  // Row statistics: whole-row sums, or partial sums in planes, one per block column of the producer, which the thread of the
+  // row adds up.  They go to LDS like the operands and in front of them: loaded into registers behind the first stages, as
+  // they were, they kept every block until all of those stages had come, a burst of 18 - 25 MB from memory (start of a block
+  // to its first product 4.3 us at 256 and 512 tokens, as against 1.9 without statistics;
+  // prefill at 512 / 768 / 816 tokens 4.432 / 5.822 / 6.350 -> 4.414 / 5.790 / 6.310 ms).
+  constexpr int PAIRS = ROWS / 2, RR = (ROWS + 64 * W - 1) / (64 * W);
+  constexpr int PLANES = Cx::kPersistent ? (LT_SMEM - (LT_STAGES - 1) * NF * 1024) / (ROWS * 8) : lds_tile_planes(MT, NT);
+  static_assert(PRO == PRO_NONE || PLANES >= 1, "room for a plane");
+  float2 sum[RR] = {};
+  const int parts = PRO != PRO_NONE ? p.rowstat_parts : 0;
+  unsigned char* const planes = smem_raw + (LT_STAGES - 1) * NF * 1024;
+  auto request_planes = [&](int m0, int first_plane, int n, unsigned char* to) {   // 16 bytes per lane: two rows
+    const int last = (p.M - 1) & ~1;
+    for (int q = w; q * 64 < n * PAIRS; q += W) {
+      const int u = min(q * 64 + lane, n * PAIRS - 1), pl = u / PAIRS;
+      const int row = min(m0 + 2 * (u - pl * PAIRS), last);
+      request_to_lds(reinterpret_cast<const char*>(p.rowstat), (unsigned)((first_plane + pl) * p.stat_rows + row) * 8u, lds_address(to) + (unsigned)q * 1024u);
+    }
+  };
+  auto add_planes = [&](int n) {
+    const float2* const v = reinterpret_cast<const float2*>(planes);
+#pragma unroll
+    for (int i = 0; i < RR; i++) {
+      const int r = min(t + i * 64 * W, ROWS - 1);
+#pragma unroll 8
+      for (int j = 0; j < n; j++) {
+        const float2 x = v[j * ROWS + r];
+        sum[i].x += x.x;
+        sum[i].y += x.y;
+      }
+    }
+  };
+  int plane = 0;
+  constexpr int LX = XB * LT_KC / W;   // of the wave's fragments of a stage, those of the tokens: the first ones
+  static_assert(!Cx::kPersistent || XB * LT_KC % W == 0, "tokens and weights apart");
+  if constexpr (Cx::kPersistent) {   // the weights of the first stages are constant: ahead of the wait for the inputs
+    for_each<LT_STAGES - 1>([&](auto Q) { for_each<L - LX>([&](auto I) { issue(Q, Int<LX + decltype(I)::value>{}, voff); }); });
+    cx.wait_inputs();
+  }
+  // Added in groups (the sum of squares is all that RMS wants), planes go to registers: a wave takes two groups of all rows.  In one
+  // round trip with the stages behind them; through LDS 64 planes of 320 rows took three turns, 7.2 us to the first product.
+  constexpr int RC = ROWS / 64;
+  float gsum[SG > 1 ? 2 : 1][SG > 1 ? RC : 1] = {};
+  float gv[SG > 1 ? 2 : 1][SG > 1 ? SG : 1][SG > 1 ? RC : 1];
+  static_assert(SG == 1 || (SG == 2 * W && PRO == PRO_RMS && Cx::kPersistent), "two groups for each wave");
+  if constexpr (SG > 1) {
+#pragma unroll
+    for (int g = 0; g < 2; g++)
+#pragma unroll
+      for (int j = 0; j < SG; j++)
+#pragma unroll
+        for (int c = 0; c < RC; c++)
+          gv[g][j][c] = cx.ld_bulk(p.rowstat + 2 * ((size_t)min(w + W * g + SG * j, parts - 1) * p.stat_rows + min(m0 + 64 * c + lane, p.M - 1)) + 1);   // clamped, unconditional
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  } else if (PRO != PRO_NONE) {
+    if (parts > 1) {
+      for (; parts - plane > PLANES; plane += PLANES) {   // more than fit: in turns
+        request_planes(m0, plane, PLANES, planes);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        add_planes(PLANES);
+        __syncthreads();
+      }
+      request_planes(m0, plane, parts - plane, planes);
+    } else {
+      request_planes(m0, 0, 1, smem);
+    }
+  }
+  constexpr int LF = Cx::kPersistent ? LX : L;   // requests of a first stage that are behind the planes
+  for_each<LT_STAGES - 1>([&](auto Q) { for_each<LF>([&](auto I) { issue(Q, I, voff); }); });
+  if constexpr (SG > 1) {
+    float* const groups = reinterpret_cast<float*>(planes);   // [SG][ROWS]
+#pragma unroll
+    for (int g = 0; g < 2; g++)
+#pragma unroll
+      for (int c = 0; c < RC; c++) {
+#pragma unroll
+        for (int j = 0; j < SG; j++) gsum[g][c] += w + W * g + SG * j < parts ? gv[g][j][c] : 0.f;
+        groups[(w + W * g) * ROWS + 64 * c + lane] = gsum[g][c];
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < RR; i++) {
+      const int r = min(t + i * 64 * W, ROWS - 1);
+      float a = groups[r];
+#pragma unroll
+      for (int g = 1; g < SG; g++) a += groups[g * ROWS + r];
+      sstat[r] = make_float2(0.f, a);   // the last row's extra threads store the same
+    }
+  } else if (PRO != PRO_NONE && parts > 1) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((LT_STAGES - 1) * LF) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    add_planes(parts - plane);
+    if (Cx::kPersistent) {   // the statistics' place is behind the stages, where planes were
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int i = 0; i < RR; i++) sstat[min(t + i * 64 * W, ROWS - 1)] = sum[i];   // the last row's extra threads store the same
+  }
+
+  // WALK: a block takes its tiles one after the other, and the next one's first stages and row statistics (in the other of two
+  // places) are on their way during the epilogue.  The persistent kernel walks where the tiles of a block are in the same
+  // rows, and keeps the statistics.
+  int nb_now = nb, m0_now = m0;
+  for (int next = die_rank + ((int)gridDim.x >> 3);; next += (int)gridDim.x >> 3) {
+    f32x16 acc[NT][MT];
+#pragma unroll
+    for (int j = 0; j < NT; j++)
+#pragma unroll
+      for (int i = 0; i < MT; i++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) acc[j][i][r] = 0.f;
+
+    bf16x8 xf[2][MT], wf[2][NT];
+    constexpr int R = MT + NT, P = MT * NT;        // reads and products of a step
+    const unsigned char* const xs = smem_raw + lane * 16 + wm * MT * LT_KC * 1024;
+    const unsigned char* const ws = smem_raw + lane * 16 + (XB + wn * NT) * LT_KC * 1024;
+    // read r of step s of a group, in the order in which the products need them: x0, w0 .. , x1 ..
+    auto read = [&](int u, int s, int r) {
+      const int o = (s / LT_KC) * NF * 1024 + (s % LT_KC) * 1024;
+      if (r == 0) xf[u][0] = *reinterpret_cast<const bf16x8*>(xs + o);
+      else if (r <= NT) wf[u][r - 1] = *reinterpret_cast<const bf16x8*>(ws + o + (r - 1) * LT_KC * 1024);
+      else xf[u][r - NT] = *reinterpret_cast<const bf16x8*>(xs + o + (r - NT) * LT_KC * 1024);
+    };
+    // stage 0 (stages 1 and 2 may be on their way) and the row statistics are complete for everybody; where the weights went
+    // ahead stage 1 too, because the count in front of it below takes its requests for whole ones
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(Cx::kPersistent ? LX : (LT_STAGES - 2) * L) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int r = 0; r < R; r++) read(0, 0, r);
+
+    // One group of four stages; LAST: nothing beyond it is requested.  Step s multiplies the fragments of set s % 2 and reads
+    // those of step s + 1 into the other set.  In the second step of stage q the next stage must be complete for everybody
+    // (one more may be on its way); everybody has then read stage q - 1, whose place stage q + 3 takes.
+    auto group = [&](auto last_group) {
+      constexpr bool LAST = decltype(last_group)::value != 0;
+      turn = turn + 1 == groups ? 0 : turn + 1;
+      const unsigned vnext = vfirst + (unsigned)turn * (LT_GROUP * 1024u);
+      for_each<LT_GROUP>([&](auto SS) {
+        constexpr int s = decltype(SS)::value, q = s / LT_KC, u = s & 1;
+        constexpr bool boundary = u == 1 && !(LAST && q == LT_STAGES - 1);
+        constexpr bool request = u == 1 && (!LAST || q == 0);
+        constexpr bool more = !(LAST && s == LT_GROUP - 1);
+        if constexpr (boundary) {
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"((LAST && q > 1 ? LT_STAGES - 2 - q : LT_STAGES - 3) * L) : "memory");
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+        }
+        for_each<P>([&](auto MM) {
+          constexpr int m = decltype(MM)::value;
+#pragma unroll
+          for (int r = 0; r < R; r++)
+            if (r * P / R == m && more) read(u ^ 1, (s + 1) % LT_GROUP, r);
+          if constexpr (request) {
+            for_each<L>([&](auto I) {
+              if constexpr ((2 * decltype(I)::value + 1) * P / (2 * L) == m) issue(Int<(q + LT_STAGES - 1) % LT_STAGES>{}, I, q == 0 ? voff : vnext);
+            });
+          }
+          acc[m % NT][m / NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][m % NT], xf[u][m / NT], acc[m % NT][m / NT], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);   // this order
+        });
+      });
+      voff = vnext;
+    };
+    for (int g = 0; g + 1 < groups; g++) group(Int<0>{});
+    group(Int<1>{});
+    const float2* const stat = sstat;
+    int nb_next = 0, m0_next = 0;
+    if (WALK && next < of_die) {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();   // everybody has read the last stage
+      nb_next = (first + next) / p.m_tiles;
+      m0_next = ((first + next) - nb_next * p.m_tiles) * ROWS;
+      set_sources(nb_next, m0_next);
+      if constexpr (!Cx::kPersistent) {
+        sstat = reinterpret_cast<float2*>(smem + (sstat == reinterpret_cast<float2*>(smem) ? lds_tile_stat_bytes(MT) : 0));
+        if (PRO != PRO_NONE) request_planes(m0_next, 0, 1, reinterpret_cast<unsigned char*>(sstat));
+      }
+      voff = vfirst;
+      for_each<LT_STAGES - 1>([&](auto Q) { for_each<L>([&](auto I) { issue(Q, I, voff); }); });
+    }
+    if constexpr (EPI == EPI_PARTIAL) {   // whole tiles, see partial_tile_at; rows beyond the last are never read
+      const int mbs = (p.M + 31) >> 5;
+#pragma unroll
+      for (int i = 0; i < MT; i++) {
+        const int mb = (m0_now >> 5) + wm * MT + i;
+#pragma unroll
+        for (int j = 0; j < NT; j++) {
+          const int nt = nb_now * WB + wn * NT + j;
+          if (mb < mbs && nt < p.n_tiles) {   // uniform
+            float* const dst = p.out_f32 + (((size_t)cx.by * mbs + mb) * p.n_tiles + nt) * 1024 + lane * 4;
+#pragma unroll
+            for (int q = 0; q < 4; q++) cx.st(reinterpret_cast<f32x4*>(dst + q * 256), f32x4{acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]});
+          }
+        }
+      }
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < MT; i++) {
+      const int row = (wm * MT + i) * 32 + lq, m = m0_now + row;
+      if (m < p.M) {
+        float ssum = 0.f, ssq = 0.f;
+        if (PRO != PRO_NONE) {
+          const float2 v = stat[row];
+          ssum = v.x;
+          ssq = v.y;
+        }
+#pragma unroll
+        for (int j = 0; j < NT; j++) {
+          const int nt = nb_now * WB + wn * NT + j;
+          if (nt < p.n_tiles) {
+            EpiOps ops;
+            epilogue_preload<PRO, EPI>(p, nt, m, lh, ops, cx);
+            epilogue_tile<PRO, EPI>(p, acc[j][i], nt, m, lh, ssum, ssq, cx.by, ops, cx);
+          }
+        }
+      }
+    }
+    if (!WALK || next >= of_die) return;
+    nb_now = nb_next;
+    m0_now = m0_next;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the counts below take no stores
+  }
+}

@@ -112,6 +112,7 @@ struct GemmParams {
   int k_per_split;    // k range of one blockIdx.z slice, multiple of 64 * WK
   int k_true;         // divisor of the row statistics
   int m_tiles;        // number of MB*32 row tiles
+  int range_per_die;  // TILE_LDS, partial sums: 1 = eight k ranges, die x takes all tiles of range x
   int m_split;        // TILE_SKINNY QKV: 1 = one block per (feature tile, 32-token block)
   int* progress;      // TILE_SKINNY: when set, the launch stores progress_value there on entry (read-ahead kernel's pace)
   int progress_value;
@@ -235,13 +236,17 @@ int gemm_rows_per_tile(int tile);
 hipError_t launch_gemm_stream(hipStream_t s, int pro, int epi, const GemmParams& p);
 hipError_t launch_gemm_lds(hipStream_t s, int pro, int epi, const GemmParams& p, int z_splits);
 bool gemm_lds_ok(int k_pad);                                             // TILE_LDS takes this contraction
+constexpr int LDS_DIES = 8;
 int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max);           // k ranges of a split-K launch
 hipError_t gemm_lds_init_attributes();
 hipError_t gemm_stream_init_attributes();
 // planes of row statistics that the residual projection of this shape leaves (one per block column; 0: no such kernel)
 int gemm_stream_stat_planes(int pro, int M, int n_tiles, int k_pad);
-// token blocks, feature tiles and parts of the k range of the tile that launch_gemm_stream takes (M a multiple of 32); false: none
-bool gemm_stream_tile(int pro, int epi, int M, int n_tiles, int k_pad, int* mb, int* nb, int* parts);
+// token blocks, feature tiles and parts of the k range of the tile that launch_gemm_stream takes (value_tile: of QKV where M is no multiple
+// of 32, the feature tile that the values start at); false: none
+bool gemm_stream_tile(int pro, int epi, int M, int n_tiles, int k_pad, int* mb, int* nb, int* parts, int value_tile = 0);
+// the tile that launch_gemm_lds takes: 64 mt tokens x 64 nt features
+void gemm_lds_tile(int M, int n_tiles, int k_pad, int k_per_split, int z, bool partial, int* mt, int* nt);
 // out[m] = (sum, sum of squares) of row m from partial statistics [planes][stat_rows][2]
 hipError_t launch_row_sums(hipStream_t s, const float* parts, int planes, int stat_rows, int M, float* out);
 hipError_t gemm_init_attributes();
