@@ -793,3 +793,363 @@ static inline bool attn_suffix_ok(const AttnParams& p, int n0) {
   return p.head_dim == 256 && (p.chunks1 == 0 || (p.chunks1 == 2 && p.Tq == 64)) && p.view_tokens == 0 && p.kv_head_stride0 == 0 && p.v_head_stride0 == 0 &&
          n0 >= 1 && n0 <= ATT_SHARE && (vs == 1 || vs == 2 || vs == 4 || vs == 8);
 }
+
+// ------------------------------------------------------------------------------------------------
+// Attention of the prefix inside its persistent kernel, by four waves.  An item is 16 query rows of one head over at most 10 chunks of
+// keys (attention_prefix16_body: the sums of attention_suffix_body without a suffix) or 32 query rows over more
+// (attention_prefix32_body: those of attention_body with several key rounds), in the same order, so the same bits: a wave does what
+// waves w and w + 4 of those do.  512 registers per wave hold all keys and values of the former; the latter keeps two chunks of
+// keys and a ring of values on their way.
+// ------------------------------------------------------------------------------------------------
+constexpr int PREFIX_WAVES = 4;
+constexpr int ATTN_PREFIX16_SMEM = 8 * 1024 + ATT_SHARE * 1024 + 2 * ATT_WAVES * 16 * 4;
+template <class Cx>
+__device__ __forceinline__ void attention_prefix16_body(const AttnParams p, const Cx cx, unsigned char* smem_raw) {
+  constexpr int S16 = 16, V = ATT_WAVES / PREFIX_WAVES;   // head dimension 256
+  const int t = cx.tid();
+  const int lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int qi = lane & 15;
+  const int g = lane >> 4;
+  const int qt = cx.bx, head = cx.by, n0 = p.chunks0;
+  const int row = qt * 16 + qi;
+  bf16* qlds = reinterpret_cast<bf16*>(smem_raw);                             // [8 steps of 32 k][64][8]
+  bf16* pf = qlds + 8 * 512;                                                  // [10 chunks][64][8]
+  float* mw = reinterpret_cast<float*>(pf + ATT_SHARE * 512);                 // [8][16]
+  float* lw = mw + ATT_WAVES * 16;                                            // [8][16]
+  const bf16x8 zero8 = __builtin_bit_cast(bf16x8, u32x4_t{0u, 0u, 0u, 0u});
+  const unsigned qpiece = (unsigned)((g >> 1) * 1024 + ((g & 1) * 32 + qi) * 16);                              // + 256 for the odd 16-row tile
+  const unsigned kpiece = (unsigned)((g >> 1) * 1024 + ((g & 1) * 32 + (qi >> 3) * 16 + (qi & 7)) * 16);       // + 128 for tile 1
+  const unsigned vpiece = (unsigned)((g >> 1) * 1024 + (g & 1) * 512 + qi * 16);                              // + 256 for the odd 16-column tile
+  auto ld = [&](const char* base, unsigned off) { return cx.ld_bulk(reinterpret_cast<const bf16x8*>(base + off)); };
+
+  bf16x8 qv[V], kf[V][2][8], k1f[8], vf[V][2][ATT_SHARE];
+  const char* const qsrc = reinterpret_cast<const char*>(p.q + (size_t)head * p.q_head_stride + (size_t)(qt >> 1) * S16 * 512 + (qt & 1) * 128);
+#pragma unroll
+  for (int v = 0; v < V; v++) qv[v] = ld(qsrc, qpiece + (unsigned)(w + PREFIX_WAVES * v) * 2048u);
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    const int c = w + PREFIX_WAVES * v;
+    const char* const kp = reinterpret_cast<const char*>(p.k0 + (size_t)c * S16 * 512);
+    if (c < n0) {   // uniform
+#pragma unroll
+      for (int j = 0; j < 8; j++)
+#pragma unroll
+        for (int h = 0; h < 2; h++) kf[v][h][j] = ld(kp, kpiece + h * 128 + j * 2048);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; j++) kf[v][0][j] = kf[v][1][j] = zero8;
+    }
+  }
+  const bool extra = ATT_WAVES + (w >> 1) < n0;   // this wave also has a 16-key tile of chunks 8 and 9
+  if (extra) {
+    const char* const kp = reinterpret_cast<const char*>(p.k0 + (size_t)(ATT_WAVES + (w >> 1)) * S16 * 512 + (w & 1) * 64);
+#pragma unroll
+    for (int j = 0; j < 8; j++) k1f[j] = ld(kp, kpiece + j * 2048);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; j++) k1f[j] = zero8;
+  }
+  // 16-column tiles w, w + 4, w + 8, w + 12 of the values
+#pragma unroll
+  for (int c = 0; c < ATT_SHARE; c++)
+#pragma unroll
+    for (int v = 0; v < V; v++)
+#pragma unroll
+      for (int a = 0; a < 2; a++) {
+        const int dt = w + PREFIX_WAVES * v + ATT_WAVES * a;
+        if (c < n0) vf[v][a][c] = ld(reinterpret_cast<const char*>(p.v0 + (size_t)(dt >> 1) * 1024 + (dt & 1) * 128) + (size_t)c * 16384, vpiece);   // uniform
+        else vf[v][a][c] = zero8;
+      }
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);   // all requested before the first one is waited for
+#pragma unroll
+  for (int v = 0; v < V; v++) *reinterpret_cast<bf16x8*>(qlds + ((size_t)(w + PREFIX_WAVES * v) * 64 + lane) * 8) = qv[v];
+  __syncthreads();
+
+  // ---- scores ---------------------------------------------------------------------------------------
+  bf16x8 qf[8];
+#pragma unroll
+  for (int j = 0; j < 8; j++) qf[j] = *reinterpret_cast<const bf16x8*>(qlds + ((size_t)j * 64 + lane) * 8);
+  f32x4 sv[V][2], sodd[V][2], sv1 = {0.f, 0.f, 0.f, 0.f}, sodd1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int v = 0; v < V; v++)
+#pragma unroll
+    for (int h = 0; h < 2; h++) sv[v][h] = sodd[v][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 8; j += 2)
+#pragma unroll
+    for (int v = 0; v < V; v++)
+#pragma unroll
+      for (int h = 0; h < 2; h++) {
+        sv[v][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[v][h][j], qf[j], sv[v][h], 0, 0, 0);
+        sodd[v][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[v][h][j + 1], qf[j + 1], sodd[v][h], 0, 0, 0);
+      }
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+    sv1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1f[j], qf[j], sv1, 0, 0, 0);
+    sodd1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1f[j + 1], qf[j + 1], sodd1, 0, 0, 0);
+  }
+#pragma unroll
+  for (int v = 0; v < V; v++)
+#pragma unroll
+    for (int h = 0; h < 2; h++) sv[v][h] = (sv[v][h] + sodd[v][h]) * p.scale;
+  sv1 = (sv1 + sodd1) * p.scale;
+  const int kg = 16 * (g >> 1) + 4 * (g & 1);   // first of this lane's keys in a chunk; + 8 for tile 1
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    const int c = w + PREFIX_WAVES * v;
+    float m_loc = NEG_BIG;
+    if (c >= n0 || (c + 1) * 32 > p.valid0) {   // uniform: no chunk, or one with keys beyond the last
+#pragma unroll
+      for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) sv[v][h][e] = c < n0 && c * 32 + kg + 8 * h + e < p.valid0 ? sv[v][h][e] : NEG_BIG;
+    }
+    if (v == 0) {
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        sv1[e] = extra && (ATT_WAVES + (w >> 1)) * 32 + kg + 8 * (w & 1) + e < p.valid0 ? sv1[e] : NEG_BIG;
+        m_loc = fmaxf(m_loc, sv1[e]);
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) m_loc = fmaxf(m_loc, sv[v][h][e]);
+    m_loc = max_xor32(max_xor16(m_loc));
+    if (g == 0) mw[c * 16 + qi] = m_loc;
+  }
+  __syncthreads();
+  float m_part[ATT_WAVES];
+#pragma unroll
+  for (int i = 0; i < ATT_WAVES; i++) m_part[i] = mw[i * 16 + qi];
+  __builtin_amdgcn_sched_barrier(0);
+  float m_all = NEG_BIG;
+#pragma unroll
+  for (int i = 0; i < ATT_WAVES; i++) m_all = fmaxf(m_all, m_part[i]);
+
+  // ---- probabilities -> B operand of the second product, in LDS ---------------------------------------
+  const float m_sub = fmaxf(m_all, 0.5f * NEG_BIG);
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    float l_loc = 0.f;
+    auto prob = [&](float x) {
+      const float e = __expf(x - m_sub);
+      l_loc += e;
+      return e;
+    };
+    bf16x8 pb;
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) pb[4 * h + e] = (bf16)prob(sv[v][h][e]);
+    *reinterpret_cast<bf16x8*>(pf + ((size_t)(w + PREFIX_WAVES * v) * 64 + lane) * 8) = pb;
+    if (v == 0 && n0 > ATT_WAVES) {   // uniform
+      bf16x4 p1;
+#pragma unroll
+      for (int e = 0; e < 4; e++) p1[e] = (bf16)prob(sv1[e]);
+      *reinterpret_cast<bf16x4*>(pf + ((size_t)(ATT_WAVES + (w >> 1)) * 64 + lane) * 8 + (w & 1) * 4) = p1;
+    }
+    l_loc = add_xor32(add_xor16(l_loc));
+    if (g == 0) lw[(w + PREFIX_WAVES * v) * 16 + qi] = l_loc;
+  }
+  __syncthreads();
+
+  // ---- output columns: O^T tile = V^T P^T over all chunks, two chains per tile ------------------------
+  float l_part[ATT_WAVES];
+#pragma unroll
+  for (int i = 0; i < ATT_WAVES; i++) l_part[i] = lw[i * 16 + qi];
+  bf16x8 b[ATT_WAVES];
+#pragma unroll
+  for (int c = 0; c < ATT_WAVES; c++) b[c] = *reinterpret_cast<const bf16x8*>(pf + ((size_t)c * 64 + lane) * 8);
+  __builtin_amdgcn_sched_barrier(0);   // every read in flight
+  f32x4 o[V][2][2];
+#pragma unroll
+  for (int v = 0; v < V; v++)
+#pragma unroll
+    for (int a = 0; a < 2; a++) o[v][a][0] = o[v][a][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < ATT_WAVES; c++)
+#pragma unroll
+    for (int v = 0; v < V; v++)
+#pragma unroll
+      for (int a = 0; a < 2; a++) o[v][a][c & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[v][a][c], b[c], o[v][a][c & 1], 0, 0, 0);
+  if (n0 > ATT_WAVES) {   // uniform
+#pragma unroll
+    for (int c = ATT_WAVES; c < ATT_SHARE; c++) {
+      const bf16x8 bc = *reinterpret_cast<const bf16x8*>(pf + ((size_t)c * 64 + lane) * 8);
+#pragma unroll
+      for (int v = 0; v < V; v++)
+#pragma unroll
+        for (int a = 0; a < 2; a++) o[v][a][c & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[v][a][c], bc, o[v][a][c & 1], 0, 0, 0);
+    }
+  }
+  float l_all = 0.f;
+#pragma unroll
+  for (int i = 0; i < ATT_WAVES; i++) l_all += l_part[i];
+  const float inv = 1.0f / l_all;
+  if (row >= p.Tq) return;
+#pragma unroll
+  for (int v = 0; v < V; v++)
+#pragma unroll
+    for (int a = 0; a < 2; a++) {
+      const int col = head * 256 + (w + PREFIX_WAVES * v + ATT_WAVES * a) * 16 + 4 * g;
+      bf16x4 ob;
+#pragma unroll
+      for (int e = 0; e < 4; e++) ob[e] = (bf16)((o[v][a][0][e] + o[v][a][1][e]) * inv);
+      cx.st(reinterpret_cast<bf16x4*>(p.out + ((size_t)(row >> 5) * (p.out_ld >> 4) + (col >> 4)) * 512 + (((col & 15) >> 3) * 32 + (row & 31)) * 8 + (col & 7)), ob);
+    }
+}
+
+// CM: most chunks of a wave (4 CM in all); RING: chunks of values in flight, EARLY of them from the start
+constexpr int attn_prefix32_smem(int cm) { return 16 * 1024 + 2 * ATT_WAVES * 32 * 4 + 4 * cm * 2048; }
+template <int CM, int EARLY, int RING, class Cx>
+__device__ __forceinline__ void attention_prefix32_body(const AttnParams& p, const Cx& cx, unsigned char* smem_raw) {
+  constexpr int S16 = 16, NVB = 8, V = 2;
+  bf16* qs = reinterpret_cast<bf16*>(smem_raw);                               // [16][64][8]
+  float* mw = reinterpret_cast<float*>(qs + S16 * 512);                       // [4][32]
+  float* lw = mw + ATT_WAVES * 32;                                            // [8][32]
+  bf16* pf = reinterpret_cast<bf16*>(lw + ATT_WAVES * 32);                    // [chunks][2][64][8]
+  const int t = cx.tid();
+  const int lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lq = lane & 31;
+  const int lh = lane >> 5;
+  const int tile = cx.bx, head = cx.by, n0 = p.chunks0;
+  const int row = tile * 32 + lq;
+  const unsigned l16 = (unsigned)lane * 16u;
+  auto ld = [&](const char* base, unsigned off) { return cx.ld_bulk(reinterpret_cast<const bf16x8*>(base + off)); };
+  const char* const qsrc = reinterpret_cast<const char*>(p.q + (size_t)head * p.q_head_stride + (size_t)tile * S16 * 512);
+  const char* const kbase = reinterpret_cast<const char*>(p.k0);
+  const char* const vbase = reinterpret_cast<const char*>(p.v0) + w * 2048;   // slice w; slice w + 4: + 8 KiB
+
+  bf16x8 qreg[4], kf[2][S16], vf[RING][V][2];
+#pragma unroll
+  for (int i = 0; i < 4; i++) qreg[i] = ld(qsrc, (unsigned)(w * 4 + i) * 1024u + l16);
+  auto kchunk = [&](int i) { return kbase + (size_t)min(w + PREFIX_WAVES * i, n0 - 1) * (S16 * 1024); };   // the wave's chunk i, clamped
+#pragma unroll
+  for (int u = 0; u < 2; u++)
+#pragma unroll
+    for (int s = 0; s < S16; s++) kf[u][s] = ld(kchunk(u), (unsigned)s * 1024u + l16);
+  auto load_v = [&](int r, int c) {
+    const char* const vp = vbase + (size_t)min(c, n0 - 1) * (NVB * 2048);
+#pragma unroll
+    for (int v = 0; v < V; v++)
+#pragma unroll
+      for (int s2 = 0; s2 < 2; s2++) vf[r][v][s2] = ld(vp, (unsigned)(v * 8192 + s2 * 1024) + l16);
+  };
+#pragma unroll
+  for (int r = 0; r < EARLY; r++) load_v(r, r);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 4; i++) *reinterpret_cast<bf16x8*>(qs + ((size_t)(w * 4 + i) * 64 + lane) * 8) = qreg[i];
+  __syncthreads();
+
+  // ---- scores of chunks w, w + 4, ..., two at a time --------------------------------------------------
+  float sv[CM][16], m_loc = NEG_BIG;
+#pragma unroll
+  for (int i = 0; i < CM; i += 2) {
+    if (w + PREFIX_WAVES * i < n0) {   // uniform
+      const bool more = i + 2 < CM && w + PREFIX_WAVES * (i + 2) < n0;
+      f32x16 acc[2];
+#pragma unroll
+      for (int e = 0; e < 16; e++) acc[0][e] = acc[1][e] = 0.f;
+#pragma unroll
+      for (int s0 = 0; s0 < S16; s0 += 4) {
+        bf16x8 qb[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) qb[j] = *reinterpret_cast<const bf16x8*>(qs + ((size_t)(s0 + j) * 64 + lane) * 8);
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+          for (int u = 0; u < 2; u++) {
+            const bf16x8 a = kf[u][s0 + j];
+            if (more) kf[u][s0 + j] = ld(kchunk(i + 2 + u), (unsigned)(s0 + j) * 1024u + l16);
+            acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qb[j], acc[u], 0, 0, 0);
+          }
+      }
+#pragma unroll
+      for (int u = 0; u < 2; u++) {
+        if (i + u >= CM) continue;
+        const int c = w + PREFIX_WAVES * (i + u);
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          const int key = c * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
+          sv[i + u < CM ? i + u : 0][e] = c < n0 && key < p.valid0 ? acc[u][e] * p.scale : NEG_BIG;
+          m_loc = fmaxf(m_loc, sv[i + u < CM ? i + u : 0][e]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int r = EARLY; r < RING; r++) load_v(r, r);   // in the keys' registers
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  m_loc = max_xor32(m_loc);
+  if (lh == 0) mw[w * 32 + lq] = m_loc;
+  __syncthreads();
+  float m_all = NEG_BIG;
+#pragma unroll
+  for (int i = 0; i < PREFIX_WAVES; i++) m_all = fmaxf(m_all, mw[i * 32 + lq]);
+  float l_loc[V] = {0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < CM; i++) {
+    const int c = w + PREFIX_WAVES * i;
+    if (c < n0) {   // uniform
+      float pr[16];
+#pragma unroll
+      for (int e = 0; e < 16; e++) {
+        pr[e] = sv[i][e] > 0.5f * NEG_BIG ? __expf(sv[i][e] - m_all) : 0.f;   // masked keys: exactly 0
+        l_loc[i & 1] += pr[e];
+      }
+#pragma unroll
+      for (int s2 = 0; s2 < 2; s2++) {
+        bf16x8 pb;
+#pragma unroll
+        for (int j = 0; j < 8; j++) pb[j] = (bf16)pr[8 * s2 + j];
+        *reinterpret_cast<bf16x8*>(pf + ((size_t)(c * 2 + s2) * 64 + lane) * 8) = pb;
+      }
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    l_loc[v] = add_xor32(l_loc[v]);
+    if (lh == 0) lw[(w + PREFIX_WAVES * v) * 32 + lq] = l_loc[v];
+  }
+  __syncthreads();
+
+  // ---- output: slices w and w + 4 of the head over all chunks -------------------------------------------
+  f32x16 o[V];
+#pragma unroll
+  for (int e = 0; e < 16; e++) o[0][e] = o[1][e] = 0.f;
+  for (int c0 = 0; c0 < n0; c0 += RING) {
+#pragma unroll
+    for (int r = 0; r < RING; r++) {
+      const int c = c0 + r;
+      if (c >= n0) break;   // uniform
+      bf16x8 bp[2];
+#pragma unroll
+      for (int s2 = 0; s2 < 2; s2++) bp[s2] = *reinterpret_cast<const bf16x8*>(pf + ((size_t)(c * 2 + s2) * 64 + lane) * 8);
+#pragma unroll
+      for (int s2 = 0; s2 < 2; s2++)
+#pragma unroll
+        for (int v = 0; v < V; v++) o[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[r][v][s2], bp[s2], o[v], 0, 0, 0);
+      if (c + RING < n0) load_v(r, c + RING);
+    }
+  }
+  float l_all = 0.f;
+#pragma unroll
+  for (int i = 0; i < ATT_WAVES; i++) l_all += lw[i * 32 + lq];
+  const float inv = 1.0f / l_all;
+  if (row >= p.Tq) return;
+#pragma unroll
+  for (int v = 0; v < V; v++)
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int col = head * 256 + (w + PREFIX_WAVES * v) * 32 + 8 * i + 4 * lh;
+      const bf16x4 ob = {(bf16)(o[v][4 * i] * inv), (bf16)(o[v][4 * i + 1] * inv), (bf16)(o[v][4 * i + 2] * inv), (bf16)(o[v][4 * i + 3] * inv)};
+      cx.st(reinterpret_cast<bf16x4*>(p.out + ((size_t)(row >> 5) * (p.out_ld >> 4) + (col >> 4)) * 512 + (((col & 15) >> 3) * 32 + (row & 31)) * 8 + (col & 7)), ob);
+    }
+}

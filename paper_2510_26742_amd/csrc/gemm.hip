@@ -633,57 +633,9 @@ __global__ __launch_bounds__(512) void splitk_reduce_kernel(ReduceParams p) {
   }
 }
 
-// The same from whole accumulator tiles (partial_tile_at).  A block takes 8 rows x 256 columns, a thread 4 columns of a row, a
-// wave 8 rows of a tile: 128-byte runs of the partial sums, of the rows and of the XF copy alike.  The row statistics come
-// out as one plane per 256 columns.  Bound: the partial sums' bytes, 4 - 5 TB/s with the launch.
 __global__ __launch_bounds__(512) void tile_reduce_kernel(ReduceParams p) {
   __shared__ float2 sred[8][8];
-  const int t = threadIdx.x, r = t & 7, m = blockIdx.x * 8 + r, n = blockIdx.y * 256 + (t >> 3) * 4;
-  const int mc = min(m, p.M - 1), nc = min(n, p.N - 4);   // clamped, unconditional
-  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  const f32x4 rv = p.resid != nullptr ? *reinterpret_cast<const f32x4*>(p.resid + (size_t)(p.resid_mod > 0 ? mc % p.resid_mod : mc) * p.ldo + nc) : zero;
-  const f32x4 extra = p.bias != nullptr ? *reinterpret_cast<const f32x4*>(p.bias + nc) : zero;
-  const f32x4 gv = p.gain != nullptr ? *reinterpret_cast<const f32x4*>(p.gain + nc) : f32x4{1.f, 1.f, 1.f, 1.f};
-  const int n_tiles = p.ldp >> 5;
-  const size_t slice = (size_t)((p.M + 31) >> 5) * n_tiles * 1024;
-  const float* const part = p.part + ((size_t)(mc >> 5) * n_tiles + (nc >> 5)) * 1024 + partial_tile_at(mc & 31, nc & 31);
-  f32x4 a = zero;
-  for (int z0 = 0; z0 < p.Z; z0 += 8) {   // batches of 8 loads in flight, added in slice order
-    f32x4 v[8];
-#pragma unroll
-    for (int j = 0; j < 8; j++) v[j] = *reinterpret_cast<const f32x4*>(part + (size_t)min(z0 + j, p.Z - 1) * slice);
-#pragma unroll
-    for (int j = 0; j < 8; j++) {
-      if (z0 + j < p.Z) a += v[j];
-    }
-  }
-  a += extra;
-  a += rv;
-  float sa = 0.f, sb = 0.f;
-  if (m < p.M && n < p.N) {
-    *reinterpret_cast<f32x4*>(p.out_f32 + (size_t)m * p.ldo + n) = a;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      sa += a[j];
-      sb += a[j] * a[j];
-    }
-    a *= gv;
-    *reinterpret_cast<bf16x4*>(p.out_bf16 + xf_index(m, n, p.ldo2 >> 4)) = bf16x4{(bf16)a[0], (bf16)a[1], (bf16)a[2], (bf16)a[3]};
-  }
-  if (p.stat_out == nullptr) return;
-  sa = add_xor32(add_xor16(sa + __shfl_xor(sa, 8, 64)));
-  sb = add_xor32(add_xor16(sb + __shfl_xor(sb, 8, 64)));
-  if ((t & 63) < 8) sred[t >> 6][r] = make_float2(sa, sb);
-  __syncthreads();
-  if (t < 8 && m < p.M) {
-    sa = sb = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; i++) {
-      sa += sred[i][r].x;
-      sb += sred[i][r].y;
-    }
-    *reinterpret_cast<float2*>(p.stat_out + ((size_t)blockIdx.y * p.stat_rows + m) * 2) = make_float2(sa, sb);
-  }
+  tile_reduce_body<512>(p, LaunchCtx::from_block_idx(), sred);
 }
 
 hipError_t launch_splitk_reduce(hipStream_t s, const ReduceParams& p) {

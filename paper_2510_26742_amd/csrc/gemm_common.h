@@ -703,3 +703,77 @@ __global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny16_kernel(GemmParams
   gemm_skinny16_body<NS>(p, LaunchCtx::from_block_idx(), smem16);
 }
 
+// Split-K reduction from whole accumulator tiles (partial_tile_at; ReduceParams).  An item is 8 rows x 256 columns, a thread takes 4
+// columns of a row (512 threads, or 256 with two such places each), a wave 8 rows of a tile: 128-byte runs of the partial sums, of the
+// rows and of the XF copy alike.  The row statistics come out as one plane per 256 columns.  Bound: the partial sums' bytes, 4 - 5 TB/s
+// with the launch.
+template <int THREADS, class Cx>
+__device__ __forceinline__ void tile_reduce_body(const ReduceParams& p, const Cx& cx, float2 (*sred)[8]) {
+  constexpr int V = 512 / THREADS;
+  const int t0 = cx.tid(), r = t0 & 7, m = cx.bx * 8 + r, mc = min(m, p.M - 1);   // clamped, unconditional
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  const int n_tiles = p.ldp >> 5;
+  const size_t slice = (size_t)((p.M + 31) >> 5) * n_tiles * 1024;
+  f32x4 extra[V], gv[V], rv[V], a[V];
+  const float* part[V];
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    const int nc = min(cx.by * 256 + ((t0 + v * THREADS) >> 3) * 4, p.N - 4);
+    extra[v] = p.bias != nullptr ? *reinterpret_cast<const f32x4*>(p.bias + nc) : zero;
+    gv[v] = p.gain != nullptr ? *reinterpret_cast<const f32x4*>(p.gain + nc) : f32x4{1.f, 1.f, 1.f, 1.f};
+    part[v] = p.part + ((size_t)(mc >> 5) * n_tiles + (nc >> 5)) * 1024 + partial_tile_at(mc & 31, nc & 31);
+    a[v] = zero;
+  }
+  cx.wait_inputs();
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    const int nc = min(cx.by * 256 + ((t0 + v * THREADS) >> 3) * 4, p.N - 4);
+    rv[v] = p.resid != nullptr ? cx.ld(reinterpret_cast<const f32x4*>(p.resid + (size_t)(p.resid_mod > 0 ? mc % p.resid_mod : mc) * p.ldo + nc)) : zero;
+  }
+  for (int z0 = 0; z0 < p.Z; z0 += 8) {   // batches of 8 loads in flight, added in slice order
+    f32x4 x[V][8];
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+#pragma unroll
+      for (int v = 0; v < V; v++) x[v][j] = cx.ld(reinterpret_cast<const f32x4*>(part[v] + (size_t)min(z0 + j, p.Z - 1) * slice));
+#pragma unroll
+    for (int v = 0; v < V; v++)
+#pragma unroll
+      for (int j = 0; j < 8; j++) {
+        if (z0 + j < p.Z) a[v] += x[v][j];
+      }
+  }
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    const int t = t0 + v * THREADS, n = cx.by * 256 + (t >> 3) * 4;
+    a[v] += extra[v];
+    a[v] += rv[v];
+    float sa = 0.f, sb = 0.f;
+    if (m < p.M && n < p.N) {
+      cx.st(reinterpret_cast<f32x4*>(p.out_f32 + (size_t)m * p.ldo + n), a[v]);
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        sa += a[v][j];
+        sb += a[v][j] * a[v][j];
+      }
+      a[v] *= gv[v];
+      cx.st(reinterpret_cast<bf16x4*>(p.out_bf16 + xf_index(m, n, p.ldo2 >> 4)), bf16x4{(bf16)a[v][0], (bf16)a[v][1], (bf16)a[v][2], (bf16)a[v][3]});
+    }
+    if (p.stat_out != nullptr) {
+      sa = add_xor32(add_xor16(sa + __shfl_xor(sa, 8, 64)));
+      sb = add_xor32(add_xor16(sb + __shfl_xor(sb, 8, 64)));
+      if ((t & 63) < 8) sred[t >> 6][r] = make_float2(sa, sb);
+    }
+  }
+  if (p.stat_out == nullptr) return;
+  __syncthreads();
+  if (t0 < 8 && m < p.M) {
+    float sa = 0.f, sb = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      sa += sred[i][r].x;
+      sb += sred[i][r].y;
+    }
+    cx.st(reinterpret_cast<float2*>(p.stat_out + ((size_t)cx.by * p.stat_rows + m) * 2), make_float2(sa, sb));
+  }
+}

@@ -37,7 +37,7 @@ __device__ __forceinline__ void stream_share(int die, int tiles, int& first, int
 template <int MB, int NB, int W, int V, int D, int SG, int PARTS, int NS, int PRO, int EPI, class Cx>
 __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& cx, unsigned char* smem_raw) {
   constexpr int WR = W / V;   // waves
-  static_assert(W % V == 0 && (V == 1 || EPI == EPI_RESID), "several parts per wave: residual epilogue only");
+  static_assert(W % V == 0 && (WR == 4 || WR == 8), "four or eight waves");
   using Rounds = StreamRounds<MB, NB, W, EPI>;
   constexpr int TILES = MB * NB, ROUNDS = Rounds::ROUNDS, TPR = Rounds::TPR;
   float* red = reinterpret_cast<float*>(smem_raw);                        // [W][TPR][8 groups of 4 columns][32 rows, rotated by the group][4]
@@ -386,12 +386,12 @@ __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& 
       if (EPI == EPI_QKV && values) {   // uniform
         // A unit is 16 tokens of a tile: a lane takes 8 of them of one feature (lane % 32) from LDS, which are the 16-byte
         // piece of the value fragments with tokens 4 lh .. + 3 and 8 + 4 lh .. + 3; tokens beyond the last come out as zeros
-        constexpr int VUPW = (TPR * 2 + W - 1) / W;
+        constexpr int VUPW = (TPR * 2 + WR - 1) / WR;
         float pt[VUPW][W][8];
         const int s2 = w & 1;
         auto tile_at = [&](int v, int& k) {
-          k = min((W / 2) * v + (w >> 1), TPR - 1);
-          return rd * TPR + (W / 2) * v + (w >> 1);
+          k = min((WR / 2) * v + (w >> 1), TPR - 1);
+          return rd * TPR + (WR / 2) * v + (w >> 1);
         };
 #pragma unroll
         for (int v = 0; v < VUPW; v++) {
@@ -407,7 +407,7 @@ __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& 
         for (int v = 0; v < VUPW; v++) {
           int k;
           const int tile = tile_at(v, k), tb = tile / NB, j = tile % NB, mt0 = m0 + tb * 32;
-          if ((W / 2) * v + (w >> 1) >= TPR || tile >= TILES || nt0 + j >= p.n_tiles || mt0 >= p.M) continue;   // uniform
+          if ((WR / 2) * v + (w >> 1) >= TPR || tile >= TILES || nt0 + j >= p.n_tiles || mt0 >= p.M) continue;   // uniform
           const int col = j * 32 + lq, n = nt0 * 32 + col - p.q_cols - p.k_cols;
           const float bias = cols[col], cs = PRO == PRO_LN ? cols[NB * 32 + col] : 0.f;
           const int head = (int)(((float)n + 0.5f) * (1.0f / (float)p.head_dim)), dd = n - head * p.head_dim;   // exact: n < 2^16
@@ -454,7 +454,7 @@ __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& 
       } else {
         // A unit is 8 features of a tile (features 8 q .. of it).  4 waves: wave w takes features 8 w of every tile, so token
         // block and column are constants; 8 waves: waves w and w + 4 share the tiles of a round.
-        constexpr int UPW = (TPR * 4 + W - 1) / W, UG = W == 4 ? (TPR % 4 == 0 ? 4 : 3) : 2;   // units of a wave, of a group
+        constexpr int UPW = (TPR * 4 + WR - 1) / WR, UG = W == 4 ? (TPR % 4 == 0 ? 4 : 3) : 2;   // units of a wave, of a group
         const int q = w & 3;
         // query / key stores: 8 features lie in one head if the head dimension is a multiple of 8; heads by a 32-bit reciprocal
         const bool whole = EPI == EPI_BF16 || ((nt0 + NB) * 32 <= p.q_cols + p.k_cols && (p.head_dim & 7) == 0);   // uniform
@@ -481,7 +481,7 @@ __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& 
           if (!whole) {   // a block with queries or keys and values, or heads that 8 features straddle: unit by unit
 #pragma unroll 1
             for (int v = 0; v < UPW; v++) {
-              const int k = W == 4 ? v : 2 * v + (w >> 2), tile = rd * TPR + k, tb = tile / NB, j = tile % NB, nt = nt0 + j, m = m0 + tb * 32 + lq;
+              const int k = WR == 4 ? v : 2 * v + (w >> 2), tile = rd * TPR + k, tb = tile / NB, j = tile % NB, nt = nt0 + j, m = m0 + tb * 32 + lq;
               if (k >= TPR || tile >= TILES || nt >= p.n_tiles) continue;   // uniform
               f32x16 sum;
               f32x4 pt[W];
@@ -507,18 +507,18 @@ __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& 
             continue;   // next round
           }
         }
-        char* base_j[W == 4 ? NB : 1];   // 4 waves: a wave's features are the same in every tile of a column
-        unsigned off_j[W == 4 ? NB : 1];
-        if (W == 4) {
+        char* base_j[WR == 4 ? NB : 1];   // 4 waves: a wave's features are the same in every tile of a column
+        unsigned off_j[WR == 4 ? NB : 1];
+        if (WR == 4) {
 #pragma unroll
-          for (int j = 0; j < (W == 4 ? NB : 0); j++) column(j, base_j[j], off_j[j]);
+          for (int j = 0; j < (WR == 4 ? NB : 0); j++) column(j, base_j[j], off_j[j]);
         }
 #pragma unroll
         for (int v0 = 0; v0 < UPW; v0 += UG) {
           f32x4 pt[UG][W], x[UG], rope[UG], bias[UG], cs[UG];
 #pragma unroll
           for (int u = 0; u < UG; u++) {   // (beyond the last tile: a copy of it, not stored)
-            const int k = min(W == 4 ? v0 + u : 2 * (v0 + u) + (w >> 2), TPR - 1), tile = min(rd * TPR + k, TILES - 1), tb = tile / NB, j = tile % NB;
+            const int k = min(WR == 4 ? v0 + u : 2 * (v0 + u) + (w >> 2), TPR - 1), tile = min(rd * TPR + k, TILES - 1), tb = tile / NB, j = tile % NB;
             if (EPI == EPI_QKV && p.rope != nullptr)
               rope[u] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(p.rope) + (size_t)(p.pos0 + m0) * 1024 +
                                                         ((unsigned)min(tb * 32 + lq, p.M - 1 - m0) * 1024u + (unsigned)((nt0 * 32 + j * 32 + 8 * q) & 255) * 4u + (unsigned)lh * 16u));
@@ -531,7 +531,7 @@ __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& 
           __builtin_amdgcn_sched_barrier(0);   // every read in flight (left alone they are read and added one by one)
 #pragma unroll
           for (int u = 0; u < UG; u++) {
-            const int k = W == 4 ? v0 + u : 2 * (v0 + u) + (w >> 2), tb = min(rd * TPR + k, TILES - 1) / NB;
+            const int k = WR == 4 ? v0 + u : 2 * (v0 + u) + (w >> 2), tb = min(rd * TPR + k, TILES - 1) / NB;
             float rs_t = rs[0], mu_t = mu[0];
 #pragma unroll
             for (int b = 1; b < MB; b++) {
@@ -553,14 +553,14 @@ __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& 
           }
 #pragma unroll
           for (int u = 0; u < UG; u++) {
-            const int k = W == 4 ? v0 + u : 2 * (v0 + u) + (w >> 2), tile = rd * TPR + k, tb = tile / NB, j = tile % NB;
+            const int k = WR == 4 ? v0 + u : 2 * (v0 + u) + (w >> 2), tile = rd * TPR + k, tb = tile / NB, j = tile % NB;
             if (v0 + u >= UPW || k >= TPR || tile >= TILES) continue;   // uniform
             const int m = m0 + tb * 32 + lq, m_end = nt0 + j < p.n_tiles ? p.M : 0;
             char* base;
             unsigned off;
-            if (W == 4) {
-              base = base_j[W == 4 ? j : 0];
-              off = off_j[W == 4 ? j : 0];
+            if (WR == 4) {
+              base = base_j[WR == 4 ? j : 0];
+              off = off_j[WR == 4 ? j : 0];
             } else {
               column(j, base, off);
             }

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "expert_loop.h"
+#include "prefix_loop.h"
 #include "vision_loop.h"
 #include "pi0_internal.h"
 
@@ -162,6 +163,8 @@ struct WsLayout {
   // shape is not one it covers), byte offsets inside a slot
   size_t vsync, vparams, vring, vring_slot = 0;
   unsigned rv_xb_o, rv_st_o, rv_xb_d, rv_st_d, rv_q, rv_k, rv_v, rv_attn, rv_mid;
+  size_t psync, pparams, pring, pring_slot = 0;   // the same for the persistent prefix
+  unsigned rp_xb_o, rp_st_o, rp_xb_d, rp_st_d, rp_q, rp_attn, rp_mid;
   size_t lx8, lx8s, lmid8, lmid8s;   // MXFP8 copies of the prefix feed-forward inputs
   bool mx_ok = false;                // the prefix feed-forward shapes fit the MXFP8 kernels (multiples of 256)
   size_t total;
@@ -189,6 +192,9 @@ const int Z_MAX = 32;   // upper bound on split-K slices (sizes the partial-sum 
 bool vision_loop_geometry(const Dims& d) {
   return d.T == 256 && d.hdv % 8 == 0 && d.hdv > 64 && d.hdv <= 80 && d.Dv % 128 == 0 && d.Fv_kp % 128 == 0 && d.Lv >= 1;
 }
+
+// Shapes of the prefix transformer that its persistent kernel may cover (prefix_persistent decides per call)
+bool prefix_loop_geometry(const Dims& d) { return d.E == 256 * PREFIX_QKV_PLANES && d.H == 8 && d.F % 128 == 0; }
 
 void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
   WsCursor cur;
@@ -325,6 +331,8 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
   w.xb = cur.take((size_t)c.chunk * d.A * 4);
   w.vsync = cur.take((size_t)GB_WORDS * 4);
   w.vparams = cur.take(sizeof(VisionLoopParams));
+  w.psync = cur.take((size_t)GB_WORDS * 4);
+  w.pparams = cur.take(sizeof(PrefixLoopParams));
   size_t ering_bytes = 0;
   {  // one slot per (Euler step, expert layer): the same buffers as stok .. emid above, each 256-byte aligned
     WsCursor sl;
@@ -355,8 +363,26 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
     w.rv_attn = (unsigned)sl.take(I * d.Dv * 2);
     w.rv_mid = (unsigned)sl.take(I * d.Fv_kp * 2);
     w.vring_slot = sl.off;
-    const size_t bytes = w.vring_slot * (size_t)d.Lv;   // in the place of the expert's ring: the two kernels run one after the other
+    const size_t bytes = round_up_sz(w.vring_slot * (size_t)d.Lv, 256);   // in the place of the expert's ring: the two kernels run one after the other
     w.vring = w.ering;
+    if (bytes > ering_bytes) {
+      cur.take(bytes - ering_bytes);
+      ering_bytes = bytes;
+    }
+  }
+  if (prefix_loop_geometry(d)) {   // one slot per whole prefix layer, in the same place.  The tower's last slot is read (projector) before the prefix begins
+    const size_t rows = (size_t)d.maxPc * 32;
+    WsCursor sl;
+    w.rp_xb_o = (unsigned)sl.take(rows * d.E * 2);
+    w.rp_st_o = (unsigned)sl.take((size_t)(d.E / 32) * rows * 2 * 4);
+    w.rp_xb_d = (unsigned)sl.take(rows * d.E * 2);
+    w.rp_st_d = (unsigned)sl.take((size_t)PREFIX_QKV_PLANES * rows * 2 * 4);
+    w.rp_q = (unsigned)sl.take(rows * d.H * 256 * 2);
+    w.rp_attn = (unsigned)sl.take(rows * d.H * 256 * 2);
+    w.rp_mid = (unsigned)sl.take(rows * d.F * 2);
+    w.pring_slot = sl.off;
+    const size_t bytes = w.pring_slot * (size_t)(d.Ll - 1);
+    w.pring = w.ering;
     if (bytes > ering_bytes) cur.take(bytes - ering_bytes);
   }
   w.total = cur.off;
@@ -420,6 +446,7 @@ struct Tune {
   int pra = 34;
   // the vision tower of pi0_infer as one persistent kernel (1) or as launches (0)
   int pvl = 1;
+  int ppl = 1;            // the same for the prefix's layers
   // two-stream frames: blocks of the persistent loop beside the prefill (0: per-operation launches).  A resident block
   // of the loop holds a whole compute unit, so its grid decides how the chip is shared between the two streams
   int psb = -1;           // -1: from the number of prefix tokens (frame_loop_blocks)
@@ -438,7 +465,7 @@ struct pi0_ctx {
   unsigned char* static_scratch = nullptr;   // that device's copy of the library's static scratch array
   long long* loop_trace = nullptr;     // optional timeline buffer of the persistent denoise kernel (pi0_set_loop_trace)
   int loop_trace_ops = 0;
-  bool vk_ok = false;                  // ... and the persistent vision kernel's
+  bool vk_ok = false, xk_ok = false;   // ... and the persistent vision and prefix kernels'
   bool pk_ok = false;                  // the device can hold the persistent denoise kernel's 256 blocks at once
   bool graph_mode = true;
   int precision = PI0_PRECISION_BF16;   // PI0_PRECISION_MXFP8_PREFIX_MLP: prefix gate||up / down on MXFP8 operands
@@ -471,7 +498,7 @@ struct Run {
                                 // blocks inside the launches with pi0_tune "ras=0"); false: neither
   int cls = PI0_OP_MISC;        // class of the launches that follow
   OpTimer* timer = nullptr;     // when set, every RUN / RUN_GEMM launch is bracketed by an event pair
-  bool vision_loop = false;     // the vision tower may run as one persistent kernel (plain pi0_infer calls)
+  bool prefill_loops = false;   // the vision tower and the prefix may run as one persistent kernel each (plain pi0_infer calls)
   bool persistent_ok = false;   // the denoise loop may run as one persistent kernel (plain pi0_denoise / pi0_infer calls)
   int persist_blocks = 0;       // its grid (0: one block per compute unit)
   unsigned char* ebase = nullptr;   // where the expert's scratch block lives minus its workspace offset (null: in the workspace)
@@ -659,7 +686,7 @@ bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_ro
   const Dims& d = c->d;
   const WsLayout& w = c->wl;
   const Tune& T = c->tune;
-  if (!r.vision_loop || r.count_only || r.timer != nullptr || !T.pvl || !c->vk_ok || w.vring_slot == 0) return false;
+  if (!r.prefill_loops || r.count_only || r.timer != nullptr || !T.pvl || !c->vk_ok || w.vring_slot == 0) return false;
   // the launches' own choices, so that both give the same bits
   if (T.vis >= 0 || T.vqkv >= 0 || T.vup >= 0 || T.vo >= 0 || T.zvo >= 0 || T.vd >= 0 || T.zvd >= 0 || T.fko >= 0) return false;
   VisionTiles tiles;
@@ -723,6 +750,127 @@ bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_ro
   *stats = at<float>(c, last + w.rv_st_d);
   *planes_out = rest;
   return true;
+}
+
+// Parameters of a prefix layer's operations, for their launches and for the persistent kernel.  kc, vc: the layer's part of the cache
+GemmParams prefix_qkv_params(pi0_ctx* c, const WsTr& L, int P, int tile, bool last, bf16* kc, bf16* vc) {
+  const Dims& d = c->d;
+  const WsLayout& w = c->wl;
+  GemmParams p = gp_base(c, L.qkv, at<bf16>(c, w.lx_b), d.E, P, tile, d.E);
+  p.out_bf16 = at<bf16>(c, w.lq);
+  p.q_mbs = ceil_div(P, 32);
+  p.kfrag = kc; p.vfrag = vc;
+  p.rope = at<float>(c, w.rope);
+  p.pos0 = 0;
+  p.q_cols = last ? 0 : d.H * 256; p.k_cols = 256;
+  p.head_dim = 256; p.dqk_pad = 256; p.nvb = 8; p.kv_heads = 1; p.kv_chunks = d.maxPc;
+  return p;
+}
+AttnParams prefix_attn_params(pi0_ctx* c, int P, const bf16* kc, const bf16* vc) {
+  const Dims& d = c->d;
+  const int pchunks = ceil_div(P, 32);
+  AttnParams a;
+  memset(&a, 0, sizeof(a));
+  a.q = at<bf16>(c, c->wl.lq); a.q_head_stride = pchunks * 16 * 512;
+  a.Tq = P; a.heads = d.H;
+  a.k0 = kc; a.v0 = vc; a.chunks0 = pchunks; a.valid0 = P;
+  a.scale = 1.0f / 16.0f;
+  a.out = at<bf16>(c, c->wl.lattn); a.out_ld = d.H * 256; a.head_dim = 256;
+  return a;
+}
+GemmParams prefix_gu_params(pi0_ctx* c, const WsTr& L, int P, int tile) {
+  GemmParams p = gp_base(c, L.gu, at<bf16>(c, c->wl.lx_b), c->d.E, P, tile, c->d.E);
+  p.out_bf16 = at<bf16>(c, c->wl.lmid);
+  p.ldo = c->d.F;
+  return p;
+}
+
+// The prefix's whole layers as ONE persistent kernel (prefix_persistent.hip): its parameters and the variant that has the launches' own tiles
+// for this shape.  Returns -1 when the call, the shape or the tuning choices are outside what the kernel covers.  z, k_per_split: of down.
+int prefix_persistent(Run& r, int P, int stat_rows, int z, int k_per_split, PrefixLoopParams& E) {
+  pi0_ctx* c = r.c;
+  const Dims& d = c->d;
+  const WsLayout& w = c->wl;
+  const Tune& T = c->tune;
+  if (!r.prefill_loops || r.count_only || r.timer != nullptr || !T.ppl || !c->xk_ok || w.pring_slot == 0 || c->precision != PI0_PRECISION_BF16) return -1;
+  if (T.lqkv >= 0 || T.lgu >= 0 || T.lo >= 0 || T.zlo >= 0 || T.fkl >= 0 || T.ld >= 0 || T.zld >= 0) return -1;
+  const WsTr& L0 = w.llm[0];
+  const int chunks = ceil_div(P, 32), o_tiles = L0.o.n_pad / 32;
+  PrefixTiles t;
+  int variant = -1;
+  for (int v = 0; v < prefix_loop_variants() && variant < 0; v++) {
+    t = prefix_loop_tiles(v);
+    auto stream = [&](const auto& s, int pro, int epi, const PW& pw, int value_tile) {
+      int mb, nb, parts;
+      return gemm_stream_tile(pro, epi, P, pw.n_pad / 32, pw.k_pad, &mb, &nb, &parts, value_tile) && mb == s.mb && nb == s.nb && parts == s.parts && pw.k_pad == 16 * s.steps * s.parts;
+    };
+    auto tile = [&](const auto& s, const PW& pw, int kps, int ranges, bool partial) {
+      int mt, nt;
+      gemm_lds_tile(P, pw.n_pad / 32, pw.k_pad, kps, ranges, partial, &mt, &nt);
+      return mt == s.mt && nt == s.nt;
+    };
+    const int gu_rows = ceil_div(P, t.gu.mt * 64);
+    if (stream(t.qkv, PRO_RMS, EPI_QKV, L0.qkv, P % 32 != 0 ? (d.H + 1) * 8 : 0) && stream(t.o, PRO_NONE, EPI_RESID, L0.o, 0) &&
+        tile(t.gu, L0.gu, L0.gu.k_pad, 1, false) && tile(t.dn, L0.down, k_per_split, z, true) && chunks <= t.att_chunks && (t.att_rows == 16) == (chunks <= 10) &&
+        t.o_groups == (P > 256 ? 8 : 1) && (!t.walk || PK_BLOCKS / 8 % gu_rows == 0))
+      variant = v;
+  }
+  if (variant < 0) return -1;
+  const int layers = d.Ll - 1;
+  const size_t stride = layers > 1 ? w.llm[1].qkv.w - L0.qkv.w : 0, gst = w.g_l1[1] - w.g_l1[0];
+  for (int l = 1; l < layers; l++) {
+    const PW *A[4] = {&w.llm[l - 1].qkv, &w.llm[l - 1].o, &w.llm[l - 1].gu, &w.llm[l - 1].down}, *B[4] = {&w.llm[l].qkv, &w.llm[l].o, &w.llm[l].gu, &w.llm[l].down};
+    for (int i = 0; i < 4; i++)
+      if (B[i]->w - A[i]->w != stride) return -1;
+    if (w.g_l1[l + 1] - w.g_l1[l] != gst || w.g_l2[l] - w.g_l2[l - 1] != gst) return -1;
+  }
+  const size_t arena_bytes = w.total - w.act_begin;
+  if (arena_bytes >= (size_t)1 << 32) return -1;   // offsets inside the arena are 32-bit
+  bf16* const kc = reinterpret_cast<bf16*>(c->ws + w.kcache + (size_t)r.slot_w * w.kcache_slot);
+  bf16* const vc = reinterpret_cast<bf16*>(c->ws + w.vcache + (size_t)r.slot_w * w.vcache_slot);
+  memset(&E, 0, sizeof(E));
+  E.qkv = prefix_qkv_params(c, L0, P, TILE_STREAM, false, kc, vc);
+  E.qkv.stat_rows = stat_rows;
+  E.att = prefix_attn_params(c, P, kc, vc);
+  E.o = fullk_resid_params(c, L0.o, at<bf16>(c, w.lattn), d.H * 256, P, d.H * 256, nullptr, at<float>(c, w.lx), at<bf16>(c, w.lx_b), d.E,
+                           at<float>(c, w.lstat_parts), stat_rows, at<float>(c, w.g_l2[0]));
+  E.gu = prefix_gu_params(c, L0, P, TILE_LDS);
+  E.gu.rowstat_parts = ceil_div(o_tiles, t.o.nb);
+  E.gu.stat_rows = stat_rows;
+  E.dn = gp_base(c, L0.down, at<bf16>(c, w.lmid), d.F, P, TILE_LDS, d.F);
+  E.dn.k_per_split = k_per_split;
+  E.dn.out_f32 = at<float>(c, w.part);
+  E.dn.range_per_die = z == LDS_DIES;
+  E.red.part = E.dn.out_f32;
+  E.red.Z = z; E.red.M = P; E.red.N = d.E; E.red.ldp = L0.down.n_pad;
+  E.red.tiled = 1;
+  E.red.resid = at<float>(c, w.lx);
+  E.red.stat_rows = stat_rows;
+  E.red.gain = at<float>(c, w.g_l1[1]);
+  E.red.out_f32 = at<float>(c, w.lx);
+  E.red.ldo = d.E; E.red.ldo2 = d.E;
+  E.qkv.m_tiles = ceil_div(P, t.qkv.mb * 32);
+  E.o.m_tiles = ceil_div(P, t.o.mb * 32);
+  E.gu.m_tiles = ceil_div(P, t.gu.mt * 64);
+  E.dn.m_tiles = ceil_div(P, t.dn.mt * 64);
+  E.gu_blocks = round_up(ceil_div(E.gu.n_tiles, 2 * t.gu.nt) * E.gu.m_tiles, 8);
+  E.dn_blocks = ceil_div(E.dn.n_tiles, 2 * t.dn.nt) * E.dn.m_tiles;
+  if (!E.dn.range_per_die) E.dn_blocks = round_up(E.dn_blocks, 8);
+  E.att_tiles = ceil_div(P, t.att_rows);
+  E.layers = layers;
+  E.layer_stride = stride;
+  E.gain_stride = gst;
+  E.kcache_stride = w.kcache_layer;
+  E.vcache_stride = w.vcache_layer;
+  E.ring = reinterpret_cast<char*>(c->ws + w.pring);
+  E.ring_stride = w.pring_slot;
+  E.r_xb_o = w.rp_xb_o; E.r_st_o = w.rp_st_o; E.r_xb_d = w.rp_xb_d; E.r_st_d = w.rp_st_d;
+  E.r_q = w.rp_q; E.r_attn = w.rp_attn; E.r_mid = w.rp_mid;
+  E.arena = reinterpret_cast<const char*>(c->ws + w.act_begin);
+  E.arena_bytes = (unsigned)arena_bytes;
+  E.sync = at<unsigned>(c, w.psync);
+  E.spin_limit = 1u << 20;
+  return variant;
 }
 
 void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
@@ -855,7 +1003,6 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
                                at<float>(c, w.lstat_parts), lplanes, stat_rows));
   }
   sum_prefix(NEVER);
-  const int pchunks = ceil_div(P, 32);
   const int tlqkv = T.lqkv >= 0 ? T.lqkv : TILE_STREAM;
   const bool lo_stream = T.fkl == 1 || (T.fkl < 0 && T.lo < 0 && T.zlo < 0);
   const int tlo = T.lo >= 0 ? T.lo : (P <= 512 ? TILE_MID : TILE_SQ128);
@@ -884,36 +1031,36 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   // the k range of a slice: a multiple of 64, for TILE_LDS of 128 (and then no slice empty)
   const int kps_ld = round_up(ceil_div(L0.down.k_pad, T.zld > 0 ? T.zld : zld_rule), tld == TILE_LDS ? 128 : 64);
   const int zld = tld == TILE_LDS ? ceil_div(L0.down.k_pad, kps_ld) : T.zld > 0 ? T.zld : zld_rule;
+  PrefixLoopParams E;
+  const int loop = prefix_persistent(r, P, stat_rows, zld, kps_ld, E);
   for (int l = 0; l < d.Ll; l++) {
     const WsTr& L = w.llm[l];
     const bool last = l == d.Ll - 1;
     bf16* kc = reinterpret_cast<bf16*>(c->ws + w.kcache + (size_t)r.slot_w * w.kcache_slot + (size_t)l * w.kcache_layer);
     bf16* vc = reinterpret_cast<bf16*>(c->ws + w.vcache + (size_t)r.slot_w * w.vcache_slot + (size_t)l * w.vcache_layer);
     {  // B1: RMS -> QKV, RoPE, keys/values into the cache (last layer: keys/values only)
-      GemmParams p = gp_base(c, L.qkv, at<bf16>(c, w.lx_b), d.E, P, tlqkv, d.E);
+      GemmParams p = prefix_qkv_params(c, L, P, tlqkv, last, kc, vc);
       prefix_stats(p);
-      p.out_bf16 = at<bf16>(c, w.lq);
-      p.q_mbs = pchunks;
-      p.kfrag = kc; p.vfrag = vc;
-      p.rope = at<float>(c, w.rope);
-      p.pos0 = 0;
-      p.q_cols = last ? 0 : d.H * 256; p.k_cols = 256;
-      p.head_dim = 256; p.dqk_pad = 256; p.nvb = 8; p.kv_heads = 1; p.kv_chunks = d.maxPc;
+      if (loop >= 0 && l == 0) p.out_bf16 = reinterpret_cast<bf16*>(E.ring + E.r_q);   // for the persistent kernel
+      if (loop >= 0 && last) {                                                         // from it
+        const char* const slot = E.ring + E.ring_stride * (size_t)(E.layers - 1);
+        p.X = reinterpret_cast<const bf16*>(slot + E.r_xb_d);
+        p.rowstat = reinterpret_cast<const float*>(slot + E.r_st_d);
+        p.rowstat_parts = PREFIX_QKV_PLANES;
+      }
       r.cls = PI0_OP_LLM_QKV;
       RUN_GEMM(r, tlqkv, PRO_RMS, EPI_QKV, p, 1);
     }
     if (last) break;
-    {  // B2: attention, whole prefix visible
-      AttnParams a;
-      memset(&a, 0, sizeof(a));
-      a.q = at<bf16>(c, w.lq); a.q_head_stride = pchunks * 16 * 512;
-      a.Tq = P; a.heads = d.H;
-      a.k0 = kc; a.v0 = vc; a.chunks0 = pchunks; a.valid0 = P;
-      a.scale = 1.0f / 16.0f;
-      a.out = at<bf16>(c, w.lattn); a.out_ld = d.H * 256; a.head_dim = 256;
-      r.cls = PI0_OP_LLM_ATTN;
-      RUN(r, launch_attention(r.s, a));
+    if (loop >= 0) {   // everything between the first layer's QKV projection and the last one's
+      r.cls = PI0_OP_MISC;
+      RUN(r, launch_prefix_loop(r.s, loop, E, at<PrefixLoopParams>(c, w.pparams), PK_BLOCKS));
+      l = d.Ll - 2;
+      continue;
     }
+    // B2: attention, whole prefix visible
+    r.cls = PI0_OP_LLM_ATTN;
+    RUN(r, launch_attention(r.s, prefix_attn_params(c, P, kc, vc)));
     // B3: O-projection + residual
     r.cls = PI0_OP_LLM_O;
     if (lo_stream) {
@@ -985,10 +1132,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
       continue;
     }
     {  // B4: RMS -> gate||up with fused GELU gate
-      GemmParams p = gp_base(c, L.gu, at<bf16>(c, w.lx_b), d.E, P, tlgu, d.E);
+      GemmParams p = prefix_gu_params(c, L, P, tlgu);
       prefix_stats(p);
-      p.out_bf16 = at<bf16>(c, w.lmid);
-      p.ldo = d.F;
       r.cls = PI0_OP_LLM_GATEUP;
       RUN_GEMM(r, tlgu, PRO_RMS, EPI_GEGLU, p, 1);
     }
@@ -1532,7 +1677,7 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     // two-stream frames: per-operation launches, or the loop on a part of the chip (the prefill's blocks need compute units too)
     r.persist_blocks = read_ahead ? 0 : frame_loop_blocks(c, P);
     r.persistent_ok = read_ahead || r.persist_blocks > 0;
-    r.vision_loop = kind == KIND_INFER;
+    r.prefill_loops = kind == KIND_INFER;
     body(r);
     return r.ok() ? PI0_OK : fail_hip(c, r.err);
   }
@@ -1549,7 +1694,7 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     // two-stream frames: per-operation launches, or the loop on a part of the chip (the prefill's blocks need compute units too)
     r.persist_blocks = read_ahead ? 0 : frame_loop_blocks(c, P);
     r.persistent_ok = read_ahead || r.persist_blocks > 0;
-    r.vision_loop = kind == KIND_INFER;
+    r.prefill_loops = kind == KIND_INFER;
     body(r);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(s, &g);
@@ -1701,7 +1846,7 @@ int pi0_tune(pi0_ctx* c, const char* env) {
         {"zld", &c->tune.zld, 1, Z_MAX}, {"zvd", &c->tune.zvd, 1, Z_MAX},
         {"pfq", &c->tune.pfq, 0, 1024}, {"pfa", &c->tune.pfa, 0, 1024}, {"pfo", &c->tune.pfo, 0, 1024},
         {"pfd", &c->tune.pfd, 0, 1024}, {"ae16", &c->tune.ae16, 0, 1}, {"ksplit", &c->tune.ksplit, 0, 1}, {"kcps", &c->tune.kcps, 2, 16}, {"qms", &c->tune.qms, 0, 1},
-        {"fko", &c->tune.fko, 0, 1}, {"fkl", &c->tune.fkl, 0, 1}, {"ras", &c->tune.ras, 0, 4096}, {"ral", &c->tune.ral, 1, 8}, {"rat", &c->tune.rat, 64, 256}, {"rad", &c->tune.rad, 1, 8 /* 7: no such variant, see below */}, {"avs", &c->tune.avs, 1, 8}, {"pdn", &c->tune.pdn, 0, 1}, {"pra", &c->tune.pra, 0, 63}, {"psb", &c->tune.psb, -1, 256}, {"pvl", &c->tune.pvl, 0, 1}};
+        {"ppl", &c->tune.ppl, 0, 1}, {"fko", &c->tune.fko, 0, 1}, {"fkl", &c->tune.fkl, 0, 1}, {"ras", &c->tune.ras, 0, 4096}, {"ral", &c->tune.ral, 1, 8}, {"rat", &c->tune.rat, 64, 256}, {"rad", &c->tune.rad, 1, 8 /* 7: no such variant, see below */}, {"avs", &c->tune.avs, 1, 8}, {"pdn", &c->tune.pdn, 0, 1}, {"pra", &c->tune.pra, 0, 63}, {"psb", &c->tune.psb, -1, 256}, {"pvl", &c->tune.pvl, 0, 1}};
     for (auto& k : keys) {
       const char* f = strstr(env, k.key);
       while (f != nullptr && !((f == env || f[-1] == ',') && f[strlen(k.key)] == '=')) f = strstr(f + 1, k.key);
@@ -1751,12 +1896,13 @@ int pi0_device_status(pi0_ctx* c, void* hip_stream) {
   if (c == nullptr) return PI0_EINVAL;
   if (!c->loaded) return PI0_ESTATE;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  unsigned flags[2] = {0, 0};
-  hipError_t e = hipMemcpyAsync(&flags[0], at<unsigned>(c, c->wl.esync) + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(&flags[1], at<unsigned>(c, c->wl.vsync) + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
+  unsigned flags[3] = {0, 0, 0};
+  const size_t words[3] = {c->wl.esync, c->wl.vsync, c->wl.psync};
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < 3 && e == hipSuccess; i++) e = hipMemcpyAsync(&flags[i], at<unsigned>(c, words[i]) + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail_hip(c, e);
-  return flags[0] == 0u && flags[1] == 0u ? PI0_OK : PI0_ESTATE;
+  return flags[0] == 0u && flags[1] == 0u && flags[2] == 0u ? PI0_OK : PI0_ESTATE;
 }
 
 int pi0_kernel_count(const pi0_ctx* c, int n_views, int n_prompt) {
@@ -1799,6 +1945,8 @@ int pi0_load_weights(pi0_ctx* c, const void* d_blob, size_t blob_bytes, void* d_
     if (e != hipSuccess) return fail_hip(c, e);
     e = vision_loop_init_attributes();
     if (e != hipSuccess) return fail_hip(c, e);
+    e = prefix_loop_init_attributes();
+    if (e != hipSuccess) return fail_hip(c, e);
     {  // the persistent kernel's barrier needs all of its blocks resident: one per compute unit, 256 of them
       int dev = 0, cus = 0, per_cu = 0;
       e = hipGetDevice(&dev);
@@ -1809,6 +1957,9 @@ int pi0_load_weights(pi0_ctx* c, const void* d_blob, size_t blob_bytes, void* d_
       e = vision_loop_max_blocks_per_cu(&per_cu);
       if (e != hipSuccess) return fail_hip(c, e);
       c->vk_ok = cus >= PK_BLOCKS && per_cu >= 1;
+      e = prefix_loop_max_blocks_per_cu(&per_cu);
+      if (e != hipSuccess) return fail_hip(c, e);
+      c->xk_ok = cus >= PK_BLOCKS && per_cu >= 1;
     }
     c->attrs_set = true;
   }

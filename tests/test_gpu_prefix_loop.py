@@ -1,0 +1,55 @@
+"""The prefix of pi0_infer runs as one persistent kernel with grid barriers; pi0_prefill launches its operations one by one.  Both add up
+every sum in the same order, so they agree bit for bit at both ends of every range of prefix tokens that has a variant of its own,
+whatever a replay before left in the kernel's buffers.  (The launches are compared with the oracle in test_gpu_parity.py.)"""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_26742_amd import binding, build, synth
+from tests.test_gpu_parity import Case, say
+from tests.test_loop_code_size import code_objects, symbols
+
+CFG = dataclasses.replace(synth.reduced_config(vocab=64), llm_layers=4, exp_layers=4, max_prompt=48)   # three whole prefix layers
+
+
+def by_launches(case, img, st, nz, ids):
+    d_img, d_st, d_nz, d_ids = case.to_dev(img, st, nz, ids)
+    d_act = torch.empty((case.cfg.chunk, case.cfg.action_dim), dtype=torch.float32, device=case.dev)
+    case.m.pi0_prefill(d_img, img.shape[0], d_ids, len(ids), case.stream)
+    case.m.pi0_denoise(d_st, d_nz, d_act, case.stream)
+    case.stream.synchronize()
+    return d_act.cpu().numpy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("graphs", [True, False])
+def test_infer_equals_prefill_and_denoise(graphs):
+    case = Case(CFG)
+    try:
+        case.m.pi0_set_graph_mode(graphs)
+        for n_views, n_prompt in ((1, 0), (1, 1), (3, 48), (1, 48), (2, 0), (2, 31), (2, 1), (3, 0), (2, 48), (3, 1), (1, 7), (1, 0)):
+            img, st, nz, ids = case.inputs(n_views, n_prompt)
+            say(f"[gpu] prefix loop views={n_views} prompt={n_prompt} graphs={graphs}")
+            want = by_launches(case, img, st, nz, ids)
+            np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            assert np.isnan(case.infer(np.full_like(img, np.nan), st, nz, ids)).all()
+            for _ in range(2):
+                np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            case.m.pi0_tune("ppl=0")
+            np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            case.m.pi0_tune("ppl=1")
+        case.m.pi0_device_status(case.stream)   # raises if a bounded wait ran out
+    finally:
+        case.close()
+
+
+@pytest.mark.parametrize("variant", range(5))
+def test_prefix_loop_spills_no_registers(variant):
+    binding.lib()
+    with open(build.LIB, "rb") as f:
+        library = f.read()
+    found = {k: v for code in code_objects(library) for k, v in symbols(code).items() if f"prefix_loop_kernelILi{variant}EE" in k}
+    (name, _), = [(k, v) for k, v in found.items() if "." not in k]
+    assert found[name + ".private_seg_size"][0] == 0, "registers spilled"
