@@ -371,12 +371,12 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
     }
   }
   if (prefix_loop_geometry(d)) {   // one slot per whole prefix layer, in the same place.  The tower's last slot is read (projector) before the prefix begins
-    const size_t rows = (size_t)d.maxPc * 32;
+    const size_t rows = (size_t)std::min(d.maxPc, PREFIX_LOOP_CHUNKS) * 32, planes = (size_t)d.maxPc * 32 * 2 * 4;
     WsCursor sl;
     w.rp_xb_o = (unsigned)sl.take(rows * d.E * 2);
-    w.rp_st_o = (unsigned)sl.take((size_t)(d.E / 32) * rows * 2 * 4);
+    w.rp_st_o = (unsigned)sl.take((size_t)(d.E / 32) * planes);
     w.rp_xb_d = (unsigned)sl.take(rows * d.E * 2);
-    w.rp_st_d = (unsigned)sl.take((size_t)PREFIX_QKV_PLANES * rows * 2 * 4);
+    w.rp_st_d = (unsigned)sl.take((size_t)PREFIX_QKV_PLANES * planes);
     w.rp_q = (unsigned)sl.take(rows * d.H * 256 * 2);
     w.rp_attn = (unsigned)sl.take(rows * d.H * 256 * 2);
     w.rp_mid = (unsigned)sl.take(rows * d.F * 2);
@@ -792,7 +792,7 @@ int prefix_persistent(Run& r, int P, int stat_rows, int z, int k_per_split, Pref
   const Dims& d = c->d;
   const WsLayout& w = c->wl;
   const Tune& T = c->tune;
-  if (!r.prefill_loops || r.count_only || r.timer != nullptr || !T.ppl || !c->xk_ok || w.pring_slot == 0 || c->precision != PI0_PRECISION_BF16) return -1;
+  if (!r.prefill_loops || r.count_only || r.timer != nullptr || !T.ppl || !c->xk_ok || w.pring_slot == 0 || P > 32 * PREFIX_LOOP_CHUNKS || c->precision != PI0_PRECISION_BF16) return -1;
   if (T.lqkv >= 0 || T.lgu >= 0 || T.lo >= 0 || T.zlo >= 0 || T.fkl >= 0 || T.ld >= 0 || T.zld >= 0) return -1;
   const WsTr& L0 = w.llm[0];
   const int chunks = ceil_div(P, 32), o_tiles = L0.o.n_pad / 32;

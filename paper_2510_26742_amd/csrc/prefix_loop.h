@@ -37,6 +37,7 @@ struct PrefixTiles {
 };
 int prefix_loop_variants();
 PrefixTiles prefix_loop_tiles(int variant);
+constexpr int PREFIX_LOOP_CHUNKS = 24;            // most chunks of 32 tokens that a variant takes
 constexpr int PREFIX_QKV_PLANES = 8;              // planes of row statistics that the reduction behind down leaves
 
 hipError_t prefix_loop_init_attributes();

@@ -300,7 +300,7 @@ hipError_t launch_prefix_loop(hipStream_t s, int variant, const PrefixLoopParams
   const AttnParams& a = P.att;
   if (a.Tq != M || a.chunks0 != chunks || a.valid0 != M || a.chunks1 != 0 || a.heads * 256 != P.qkv.q_cols || a.head_dim != 256 || a.view_tokens != 0 || a.key_splits > 1 ||
       a.v_split > 1 || a.kv_head_stride0 != 0 || a.v_head_stride0 != 0 || a.q_head_stride != chunks * 8192 || a.out_ld != a.heads * 256 || P.o.W.k_pad != a.out_ld || P.o.ldx != a.out_ld ||
-      a.k0 != P.qkv.kfrag || a.v0 != P.qkv.vfrag || chunks > T.att_chunks || P.att_tiles != ceil_div(M, T.att_rows) || P.att_tiles * a.heads > blocks)
+      a.k0 != P.qkv.kfrag || a.v0 != P.qkv.vfrag || chunks > T.att_chunks || chunks > PREFIX_LOOP_CHUNKS || P.att_tiles != ceil_div(M, T.att_rows) || P.att_tiles * a.heads > blocks)
     return hipErrorInvalidValue;
   // every buffer of a slot lies inside it
   const size_t rows = (size_t)chunks * 32;
