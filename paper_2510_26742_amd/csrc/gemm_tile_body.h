@@ -34,6 +34,12 @@ constexpr int lds_tile_smem(int MT, int NT) { return (MT * NT <= 6 ? 0 : lds_til
 constexpr int lds_tile_planes(int MT, int NT) {
   return (LT_SMEM - lds_tile_stat_bytes(MT) - (lds_tile_stages(MT, NT) - 1) * lds_tile_fragments(MT, NT) * 1024 - 1024) / (2 * MT * 32 * 8);
 }
+// tiles of a launch as in gemm_stream.hip: consecutive block ids on different dies, a die takes a contiguous eighth
+__device__ __forceinline__ void lds_tile_share(int die, int tiles, int& first, int& count) {
+  first = die * (tiles >> 3) + min(die, tiles & 7);
+  count = (tiles >> 3) + (die < (tiles & 7) ? 1 : 0);
+}
+
 // SG: groups in which planes of row statistics are added (group g: planes g, g + SG, ...; then the groups in order).
 // cx.bx, cx.by: the tile, in the order of stream_share unless p.range_per_die, and the k range.
 template <int MT, int NT, int SG, int PRO, int EPI, bool WALK, class Cx>
@@ -331,5 +337,148 @@ __device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx,
     nb_now = nb_next;
     m0_now = m0_next;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the counts below take no stores
+  }
+}
+
+// gate||up of up to 256 rows: the four waves split the rows (two blocks of 32 each) and share four feature tiles.  A wave's
+// activations are nobody else's and go from memory straight into registers, sixteen steps ahead; the weights go to LDS, eight stages.  A step
+// then takes 20 KiB through LDS instead of the 36 of gemm_lds_body<4, 2>, which need longer than its 256 cycles of products.  Same tile,
+// order of k and of the row statistics' planes, so the same bits.  In the persistent prefix (2048 x 32768 at 256 tokens, pi0_infer): 6396 -> 6320 us;
+// as a launch, behind whose start everything waits for, it is 1.3 us slower than gemm_lds_body and does not exist.
+constexpr int ROWS_STAGES = 8, ROWS_NT = 4, ROWS_PARTS = 32;   // stages, feature tiles, most planes of row statistics
+constexpr int ROWS_GROUP = 16;   // k16 steps of a turn of the loop
+constexpr int GEMM_ROWS_SMEM = ROWS_STAGES * ROWS_NT * LT_KC * 1024 + 256 * 4;
+template <class Cx>
+__device__ __forceinline__ void gemm_rows_body(const GemmParams& p, const Cx& cx, unsigned char* smem) {
+  constexpr int W = 4, MT = 2, NT = ROWS_NT, SF = NT * LT_KC, L = SF / W;   // fragments of a stage, of a wave's share of it
+  static_assert(SF % W == 0, "even shares");
+  float* const ssq = reinterpret_cast<float*>(smem + ROWS_STAGES * SF * 1024);   // [256]
+  const int t = cx.tid();
+  const int lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lq = lane & 31;
+  const int lh = lane >> 5;
+  const int total = (p.n_tiles + NT - 1) / NT;
+  int first, of_die;
+  const int die_rank = cx.bx >> 3;
+  lds_tile_share(cx.bx & 7, total, first, of_die);
+  if (die_rank >= of_die) return;
+  const int nb = first + die_rank;
+  const int mb_last = (p.M - 1) >> 5;
+  const int KC16 = p.W.k_pad >> 4, XKC16 = p.ldx >> 4;
+  const int groups = KC16 / ROWS_GROUP, halves = 2 * groups;
+
+  const char* wsrc[L];
+#pragma unroll
+  for (int i = 0; i < L; i++) {
+    const int f = w + W * i;
+    wsrc[i] = reinterpret_cast<const char*>(p.W.w) + ((size_t)min(nb * NT + f / LT_KC, p.n_tiles - 1) * KC16 + f % LT_KC) * 1024;
+  }
+  const char* xsrc[MT];
+#pragma unroll
+  for (int i = 0; i < MT; i++) xsrc[i] = reinterpret_cast<const char*>(p.X) + ((size_t)min(w * MT + i, mb_last) * XKC16) * 1024;
+  const unsigned lds0 = lds_address(smem) + (unsigned)w * 1024u;
+  // all blocks read the whole k range of their own weight rows, a power of two apart: each starts elsewhere and goes round.  In halves of
+  // a group, as gemm_lds_body's groups are: stages 0 .. 3 and steps 0 .. 7 at va, the rest at vb
+  int turn = (int)((unsigned)nb % (unsigned)halves);
+  const unsigned vfirst = (unsigned)lane * 16u + 4096u;
+  auto half_at = [&](int h) { return vfirst + (unsigned)(h >= halves ? h - halves : h) * (ROWS_GROUP * 512u); };
+  unsigned va = half_at(turn), vb = half_at(turn + 1);
+  auto request = [&](auto Q, auto I, unsigned v) {   // the wave's fragment I of stage Q of the half at v
+    constexpr int q = decltype(Q)::value, i = decltype(I)::value, off = q % 4 * 2048 - 4096;
+    const unsigned l0 = lds0;
+    const char* const s = wsrc[i];
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4" ::"s"(l0), "v"(v), "s"(s),
+                 "n"((q * SF + W * i) * 1024 - off), "n"(off)
+                 : "memory", "scc");
+  };
+  bf16x8 xr[ROWS_GROUP][MT];
+  auto load_x = [&](int s, int i, unsigned v) { xr[s][i] = cx.ld_bulk(reinterpret_cast<const bf16x8*>(xsrc[i] + (v - 4096u) + s % 8 * 1024)); };
+
+  for_each<ROWS_STAGES - 1>([&](auto Q) { for_each<L>([&](auto I) { request(Q, I, decltype(Q)::value < 4 ? va : vb); }); });
+  if constexpr (Cx::kPersistent) cx.wait_inputs();
+  const int parts = p.rowstat_parts > 1 ? p.rowstat_parts : 1;
+  float gv[ROWS_PARTS];   // the sum of squares is all that RMS wants; clamped, unconditional
+#pragma unroll
+  for (int j = 0; j < ROWS_PARTS; j++) gv[j] = cx.ld_bulk(p.rowstat + 2 * ((size_t)min(j, parts - 1) * p.stat_rows + min(t, p.M - 1)) + 1);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = 0; s < ROWS_GROUP; s++)
+#pragma unroll
+    for (int i = 0; i < MT; i++) load_x(s, i, s < 8 ? va : vb);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  {
+    float a = 0.f;
+#pragma unroll
+    for (int j = 0; j < ROWS_PARTS; j++) a += j < parts ? gv[j] : 0.f;
+    ssq[t] = a;
+  }
+
+  f32x16 acc[NT][MT];
+#pragma unroll
+  for (int j = 0; j < NT; j++)
+#pragma unroll
+    for (int i = 0; i < MT; i++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[j][i][r] = 0.f;
+  bf16x8 wf[2][NT];
+  const unsigned char* const ws = smem + lane * 16;
+  auto read = [&](int u, int s, int j) { wf[u][j] = *reinterpret_cast<const bf16x8*>(ws + (((s / LT_KC) * NT + j) * LT_KC + s % LT_KC) * 1024); };
+  // stage 0 is complete for everybody; the other stages' requests and the activations are behind it
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((ROWS_STAGES - 2) * L + ROWS_GROUP * MT) : "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int j = 0; j < NT; j++) read(0, 0, j);
+  // One group of eight stages.  Step s multiplies the weights of set s % 2 and reads those of step s + 1 into the other set.  In the
+  // second step of stage q the next stage must be complete for everybody.  Behind its requests are, at least: the activations
+  // of 2 (ROWS_STAGES - 2) steps (LAST asks for none: not counted) and the requests of ROWS_STAGES - 3 stages.
+  auto group = [&](auto last_group) {
+    constexpr bool LAST = decltype(last_group)::value != 0;
+    turn = turn + 2 >= halves ? turn + 2 - halves : turn + 2;
+    const unsigned na = half_at(turn), nb_ = half_at(turn + 1);
+    for_each<ROWS_GROUP>([&](auto SS) {
+      constexpr int s = decltype(SS)::value, q = s / LT_KC, u = s & 1, P = NT * MT;
+      if constexpr (u == 1 && !(LAST && q == ROWS_STAGES - 1)) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LAST ? (q > 1 ? ROWS_STAGES - 2 - q : ROWS_STAGES - 3) * L : 2 * MT * (ROWS_STAGES - 2) + (ROWS_STAGES - 3) * L) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if constexpr (!LAST || q == 0) {
+          for_each<L>([&](auto I) { request(Int<(q + ROWS_STAGES - 1) % ROWS_STAGES>{}, I, q == 0 ? vb : q - 1 < 4 ? na : nb_); });
+        }
+      }
+      for_each<P>([&](auto MM) {
+        constexpr int m = decltype(MM)::value;
+        if constexpr (m < NT && !(LAST && s == ROWS_GROUP - 1)) read(u ^ 1, (s + 1) % ROWS_GROUP, m);
+        if constexpr (m == NT && !LAST) load_x(s, 0, s < 8 ? na : nb_);
+        acc[m % NT][m / NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[u][m % NT], xr[s][m / NT], acc[m % NT][m / NT], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);   // this order
+      });
+      if constexpr (!LAST) load_x(s, 1, s < 8 ? na : nb_);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    va = na;
+    vb = nb_;
+  };
+  for (int g = 0; g + 1 < groups; g++) group(Int<0>{});
+  group(Int<1>{});
+
+#pragma unroll
+  for (int i = 0; i < MT; i++) {
+    const int row = (w * MT + i) * 32 + lq;
+    if (row < p.M) {
+#pragma unroll
+      for (int j = 0; j < NT; j++) {
+        const int nt = nb * NT + j;
+        if (nt < p.n_tiles) {
+          EpiOps ops;
+          epilogue_preload<PRO_RMS, EPI_GEGLU>(p, nt, row, lh, ops, cx);
+          epilogue_tile<PRO_RMS, EPI_GEGLU>(p, acc[j][i], nt, row, lh, 0.f, ssq[row], 0, ops, cx);
+        }
+      }
+    }
   }
 }

@@ -812,7 +812,7 @@ int prefix_persistent(Run& r, int P, int stat_rows, int z, int k_per_split, Pref
     const int gu_rows = ceil_div(P, t.gu.mt * 64);
     if (stream(t.qkv, PRO_RMS, EPI_QKV, L0.qkv, P % 32 != 0 ? (d.H + 1) * 8 : 0) && stream(t.o, PRO_NONE, EPI_RESID, L0.o, 0) &&
         tile(t.gu, L0.gu, L0.gu.k_pad, 1, false) && tile(t.dn, L0.down, k_per_split, z, true) && chunks <= t.att_chunks && (t.att_rows == 16) == (chunks <= 10) &&
-        t.o_groups == (P > 256 ? 8 : 1) && (!t.walk || PK_BLOCKS / 8 % gu_rows == 0))
+        (!t.gu_rows || (P <= 256 && L0.gu.k_pad % 256 == 0)) && t.o_groups == (P > 256 ? 8 : 1) && (!t.walk || PK_BLOCKS / 8 % gu_rows == 0))
       variant = v;
   }
   if (variant < 0) return -1;

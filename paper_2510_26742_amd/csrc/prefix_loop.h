@@ -34,6 +34,7 @@ struct PrefixTiles {
   bool walk;                                     // gate||up: a block's tiles one after the other in the same rows
   int att_rows, att_chunks;                      // query rows of an attention item, most chunks of keys
   int o_groups;                                  // groups in which the planes of the O projection's row statistics are added
+  bool gu_rows;                                  // gate||up by gemm_rows_body
 };
 int prefix_loop_variants();
 PrefixTiles prefix_loop_tiles(int variant);

@@ -30,17 +30,17 @@ template <int MB_, int NB_, int W_, int D_, int SG_, int NS_>
 struct StreamOp { static constexpr int MB = MB_, NB = NB_, W = W_, V = W_ / 4, D = D_, SG = SG_, NS = NS_; };
 template <int MT_, int NT_>
 struct TileOp { static constexpr int MT = MT_, NT = NT_; };
-template <class QKV, class O, class GU, class DN, bool WALK_, int ATT_CM_, int O_GROUPS_>
+template <class QKV, class O, class GU, class DN, bool WALK_, int ATT_CM_, int O_GROUPS_, bool ROWS_ = false>
 struct Variant {
   using Qkv = QKV;
   using Out = O;
   using Gu = GU;
   using Dn = DN;
-  static constexpr bool WALK = WALK_;
+  static constexpr bool WALK = WALK_, ROWS = ROWS_;   // ROWS: gemm_rows_body for gate||up
   static constexpr int ATT_CM = ATT_CM_, O_GROUPS = O_GROUPS_;   // ATT_CM: 0: 16 query rows over at most 10 chunks, else 32 over at most 4 ATT_CM
 };
 template <int I> struct Variants;
-template <> struct Variants<0> { using T = Variant<StreamOp<2, 2, 8, 8, 8, 16>, StreamOp<1, 2, 8, 9, 1, 16>, TileOp<4, 2>, TileOp<2, 2>, false, 0, 1>; };
+template <> struct Variants<0> { using T = Variant<StreamOp<2, 2, 8, 8, 8, 16>, StreamOp<1, 2, 8, 9, 1, 16>, TileOp<4, 2>, TileOp<2, 2>, false, 0, 1, true>; };
 template <> struct Variants<1> { using T = Variant<StreamOp<2, 2, 8, 8, 8, 16>, StreamOp<3, 1, 8, 8, 1, 16>, TileOp<5, 2>, TileOp<3, 2>, false, 0, 8>; };
 template <> struct Variants<2> { using T = Variant<StreamOp<2, 3, 8, 5, 8, 16>, StreamOp<2, 2, 8, 6, 1, 16>, TileOp<4, 4>, TileOp<4, 2>, false, 4, 8>; };
 template <> struct Variants<3> { using T = Variant<StreamOp<2, 3, 8, 5, 8, 16>, StreamOp<3, 2, 8, 5, 1, 16>, TileOp<3, 4>, TileOp<5, 2>, false, 5, 8>; };
@@ -129,7 +129,10 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       g.rowstat = reinterpret_cast<const float*>(slot + F.r_st_o);
       g.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_mid);
       using G = typename C::Gu;
-      if constexpr (C::WALK) {
+      if constexpr (C::ROWS) {
+        static_assert(G::MT == 4 && G::NT == 2 && C::O_GROUPS == 1, "the same tile and order of the planes");
+        for_items(F.gu_blocks, [&](int it) { gemm_rows_body(g, item(it, 0), smem_raw); });
+      } else if constexpr (C::WALK) {
         gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, true>(g, item(blockIdx.x, 0), smem_raw);
       } else {
         for_items(F.gu_blocks, [&](int it) { gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, false>(g, item(it, 0), smem_raw); });
@@ -208,7 +211,7 @@ Kernel kernel_of() {
   using O = typename C::Out;
   return Kernel{reinterpret_cast<const void*>(&prefix_loop_kernel<I>), smem_of<C>(),
                 PrefixTiles{{Q::MB, Q::NB, Q::W, Q::NS}, {O::MB, O::NB, O::W, O::NS}, {C::Gu::MT, C::Gu::NT}, {C::Dn::MT, C::Dn::NT}, C::WALK,
-                            C::ATT_CM == 0 ? 16 : 32, C::ATT_CM == 0 ? ATT_SHARE : 4 * C::ATT_CM, C::O_GROUPS}};
+                            C::ATT_CM == 0 ? 16 : 32, C::ATT_CM == 0 ? ATT_SHARE : 4 * C::ATT_CM, C::O_GROUPS, C::ROWS}};
 }
 Kernel kernel_for(int v) {
   switch (v) {
@@ -292,6 +295,7 @@ hipError_t launch_prefix_loop(hipStream_t s, int variant, const PrefixLoopParams
       P.dn.k_per_split % lds_tile_group(T.dn.mt, T.dn.nt) != 0 || (P.dn.W.k_pad - P.dn.k_per_split * (P.red.Z - 1)) % lds_tile_group(T.dn.mt, T.dn.nt) != 0 ||
       (long)P.dn.k_per_split * P.red.Z < P.dn.W.k_pad || (long)P.dn.k_per_split * (P.red.Z - 1) >= P.dn.W.k_pad)
     return hipErrorInvalidValue;
+  if (T.gu_rows && (M > 256 || P.gu.W.k_pad % (16 * ROWS_GROUP) != 0 || P.gu.rowstat_parts > ROWS_PARTS)) return hipErrorInvalidValue;
   if (T.walk && ((blocks >> 3) % P.gu.m_tiles != 0)) return hipErrorInvalidValue;   // a block's tiles are in the same rows
   if (P.gu.ldo * 2 != P.gu.W.n_pad || P.dn.ldx != P.gu.ldo || P.dn.W.k_pad != P.gu.ldo) return hipErrorInvalidValue;
   if (P.red.M != M || P.red.N != E || P.red.ldp != E || P.red.ldo != E || P.red.ldo2 != E || P.red.part != P.dn.out_f32 || P.red.out_f32 != P.o.out_f32 ||
