@@ -329,10 +329,6 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
   w.esync = cur.take((size_t)GB_WORDS * 4);
   w.eparams = cur.take(sizeof(ExpertLoopParams));
   w.xb = cur.take((size_t)c.chunk * d.A * 4);
-  w.vsync = cur.take((size_t)GB_WORDS * 4);
-  w.vparams = cur.take(sizeof(VisionLoopParams));
-  w.psync = cur.take((size_t)GB_WORDS * 4);
-  w.pparams = cur.take(sizeof(PrefixLoopParams));
   size_t ering_bytes = 0;
   {  // one slot per (Euler step, expert layer): the same buffers as stok .. emid above, each 256-byte aligned
     WsCursor sl;
@@ -385,6 +381,10 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
     w.pring = w.ering;
     if (bytes > ering_bytes) cur.take(bytes - ering_bytes);
   }
+  w.vsync = cur.take((size_t)GB_WORDS * 4);
+  w.vparams = cur.take(sizeof(VisionLoopParams));
+  w.psync = cur.take((size_t)GB_WORDS * 4);
+  w.pparams = cur.take(sizeof(PrefixLoopParams));
   w.total = cur.off;
 }
 
