@@ -45,8 +45,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // for partial sums).  The partial sums are then read and written once more (5 TB/s, a launch, and
 // 3 us for each round trip of eight ranges beyond the first: 533 tokens, prefill in ms with 7 / 8 / 9 / 10 ranges 4.870 / 4.816 /
 // 4.862 / 4.974).  It ranks tiles and ranges; it does not predict a time.  In a traced pass at 256 / 512 / 768 / 816 tokens gate||up
-// takes 42.5 / 59.9 / 87.7 / 112.4 us, the formula says 42.8 / 64.3 / 103.1 / 128.7 (1 % high, then 7 .. 18 %); down with its reduction
-// takes 35.6 / 51.4 / 69.5 / 74.8, the formula says 41.6 / 55.8 / 68.5 / 75.7 (17 and 9 % high, then within 1.5 %: the GEMM alone
+// takes 42.5 / 59.9 / 87.7 / 112.4 us, the formula says 42.8 / 64.3 / 103.1 / 128.7 (1 % high, then 7 .. 18 %); down with its reduction, when all dies took all ranges,
+// 35.6 / 51.4 / 69.5 / 74.8, the formula says 41.6 / 55.8 / 68.5 / 75.7 (17 and 9 % high, then within 1.5 %: the GEMM alone
 // 13 .. 25 % low, the reduction 1.8 .. 2.7 times too long).
 // Number of ranges when all dies took all of them, prefill in ms at 512 tokens with 6 / 7 / 8 / 10 / 12: 4.336 / 4.306 / 4.248 / 4.300 /
 // 4.208 .. 4.31; 768 with 5 / 6 / 7 / 8 / 9: 5.523 / 5.451 / 5.393 / 5.393 / 5.425; 816 with 5 / 6 / 7 / 8: 5.998 / 5.948 / 6.033 / 6.038.

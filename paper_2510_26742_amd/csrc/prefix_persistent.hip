@@ -9,8 +9,8 @@
 // memory path hand out, beyond the clock that the matrix cores' power leaves).  Between two operations lie 1.0 .. 1.5 us from the
 // last block's end to the first block's release, where launches have a boundary, cold code and arguments, and from 257 tokens on a
 // launch that adds up row statistics; the partial sums of down take another 5 .. 8 us to reach memory at two and three views.
-// Per layer at 1 / 2 / 3 views, us: attention 6.5 / 11.2 / 16.3, O 8.1 / 12.3 / 16.2, gate||up 39 / 60 / 91, down 25.6 / 41 / 54, its reduction
-// 6.4 / 6.2 / 7.0, QKV 10.3 / 14.3 / 15.8.  pi0_infer, one device, ms, launches -> here: 1 view 6.408 -> 6.259, 1 view + 7 tokens 6.640 -> 6.511,
+// Per layer at 1 / 2 / 3 views, us: attention 6.5 / 11.2 / 16.3, O 8.1 / 12.3 / 16.2, gate||up 37 (gemm_rows_body) / 60 / 91, down 25.6 / 41 / 54, its reduction
+// 6.4 / 6.2 / 7.0, QKV 10.3 / 14.3 / 15.8.  pi0_infer, one device, ms, launches -> here: 1 view 6.408 -> 6.259 (-> 6.18 with gemm_rows_body), 1 view + 7 tokens 6.640 -> 6.511,
 // 2 views 7.837 -> 7.752, 3 views 9.252 -> 9.061.  Not beyond 768 tokens: 816 tokens 9.867 -> 9.843 .. 9.89 with the tiles of that range
 // (256 x 256 for gate||up in two rounds, 192 x 256 for down).
 #include "attention_body.h"
