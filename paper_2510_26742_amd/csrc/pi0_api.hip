@@ -743,6 +743,7 @@ bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_ro
   E.r_q = w.rv_q; E.r_k = w.rv_k; E.r_v = w.rv_v; E.r_attn = w.rv_attn; E.r_mid = w.rv_mid;
   E.sync = at<unsigned>(c, w.vsync);
   E.spin_limit = 1u << 20;
+  if (!vision_loop_takes(n_views, E, PK_BLOCKS)) return false;
   r.cls = PI0_OP_MISC;
   RUN(r, launch_vision_loop(r.s, n_views, E, at<VisionLoopParams>(c, w.vparams), PK_BLOCKS));
   const size_t last = w.vring + w.vring_slot * (size_t)(d.Lv - 1);

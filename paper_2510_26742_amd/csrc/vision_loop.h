@@ -42,5 +42,6 @@ int vision_loop_attention_items(int views, int heads);
 
 hipError_t vision_loop_init_attributes();
 hipError_t vision_loop_max_blocks_per_cu(int* out);
+bool vision_loop_takes(int views, const VisionLoopParams& P, int blocks);   // the kernel covers this shape
 // d_params: device memory for one VisionLoopParams (16-byte aligned), written by a small launch ahead of the kernel
 hipError_t launch_vision_loop(hipStream_t s, int views, const VisionLoopParams& P, VisionLoopParams* d_params, int blocks);

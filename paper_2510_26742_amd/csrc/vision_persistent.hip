@@ -277,54 +277,57 @@ hipError_t vision_loop_max_blocks_per_cu(int* out) {
   return hipSuccess;
 }
 
-// Host-side checks of everything the kernel's indexing assumes.
-hipError_t launch_vision_loop(hipStream_t s, int views, const VisionLoopParams& P, VisionLoopParams* d_params, int blocks) {
+// Everything that the kernel's indexing and its division of the blocks assume, so that what is not covered takes the launches
+bool vision_loop_takes(int views, const VisionLoopParams& P, int blocks) {
   VisionTiles T;
-  if (!vision_loop_tiles(views, &T)) return hipErrorInvalidValue;
-  if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0) return hipErrorInvalidValue;
-  if (blocks < 8 || blocks > GB_MAX_BLOCKS || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.spin_limit == 0) return hipErrorInvalidValue;
+  if (!vision_loop_tiles(views, &T)) return false;
+  if (blocks != 8 * (LEADER_RANK + 1) || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.spin_limit == 0) return false;
   if (P.layers < 1 || P.ring == nullptr || (reinterpret_cast<uintptr_t>(P.ring) & 255) != 0 || P.ring_stride % 256 != 0 ||
       P.arena == nullptr || P.arena_bytes == 0 || P.ring < P.arena || P.ring + P.ring_stride * (size_t)P.layers > P.arena + P.arena_bytes || P.layer_stride % 16 != 0 || P.gain_stride % 16 != 0)
-    return hipErrorInvalidValue;
+    return false;
   const int M = P.qkv.M;
   const GemmParams* gs[4] = {&P.qkv, &P.o, &P.up, &P.down};
   const VisionTile* ts[4] = {&T.qkv, &T.resid, &T.up, &T.resid};
   for (int i = 0; i < 4; i++) {
     const GemmParams& g = *gs[i];
     const int m_tiles = ceil_div(g.M, ts[i]->mb * 32);
-    if (g.M != M || g.X == nullptr || g.W.w == nullptr || g.bias == nullptr || g.pf.blocks != 0 || g.m_tiles != m_tiles) return hipErrorInvalidValue;
-    if (g.W.k_pad < 64 || g.W.k_pad % 64 != 0 || g.n_tiles < 1 || g.n_tiles * 32 != g.W.n_pad || g.ldx < g.W.k_pad || g.ldx % 16 != 0) return hipErrorInvalidValue;
-    if ((size_t)g.W.k_pad * 64 > 0x7fffffffu) return hipErrorInvalidValue;
-    if (ceil_div(g.n_tiles, ts[i]->nb) * m_tiles > blocks) return hipErrorInvalidValue;   // one round
-    if (!ts[i]->takes(g.W.k_pad)) return hipErrorInvalidValue;
+    if (g.M != M || g.X == nullptr || g.W.w == nullptr || g.bias == nullptr || g.pf.blocks != 0 || g.m_tiles != m_tiles) return false;
+    if (g.W.k_pad < 64 || g.W.k_pad % 64 != 0 || g.n_tiles < 1 || g.n_tiles * 32 != g.W.n_pad || g.ldx < g.W.k_pad || g.ldx % 16 != 0) return false;
+    if ((size_t)g.W.k_pad * 64 > 0x7fffffffu) return false;
+    if (ceil_div(g.n_tiles, ts[i]->nb) * m_tiles > 8 * READER_RANK) return false;   // one round of the blocks that run GEMM items
+    if (!ts[i]->takes(g.W.k_pad)) return false;
   }
-  if (blocks % 8 != 0) return hipErrorInvalidValue;   // items are dealt to dies in eighths
-  if (M % 32 != 0 || P.qkv.colsum == nullptr || P.up.colsum == nullptr || P.qkv.rowstat == nullptr) return hipErrorInvalidValue;
-  if (P.up.ldo != P.down.ldx || P.up.n_valid % 16 != 0 || P.up.n_valid > P.down.ldx || P.up.n_valid != P.up.W.n_pad) return hipErrorInvalidValue;
+  if (M % 32 != 0 || P.qkv.colsum == nullptr || P.up.colsum == nullptr || P.qkv.rowstat == nullptr) return false;
+  if (P.up.ldo != P.down.ldx || P.up.n_valid % 16 != 0 || P.up.n_valid > P.down.ldx || P.up.n_valid != P.up.W.n_pad) return false;
   const int most = vision_loop_planes(views);
   if (P.qkv.rowstat_parts != most || P.planes_rest != most || P.qkv.stat_rows < M || P.up.stat_rows < M ||
       P.planes_rest != ceil_div(P.o.n_tiles, T.resid.nb) || P.down.n_tiles != P.o.n_tiles)
-    return hipErrorInvalidValue;
+    return false;
   if (P.o.ldo % 4 != 0 || P.o.ldo2 % 16 != 0 || P.down.ldo != P.o.ldo || P.down.ldo2 != P.o.ldo2 || P.o.stat_rows != P.up.stat_rows || P.down.stat_rows != P.qkv.stat_rows ||
       P.o.out_f32 == nullptr || P.o.resid != P.o.out_f32 || P.down.resid != P.o.resid || P.down.out_f32 != P.o.out_f32 ||
       reinterpret_cast<const char*>(P.o.out_f32) < P.arena || reinterpret_cast<const char*>(P.o.out_f32 + (size_t)M * P.o.ldo) > P.arena + P.arena_bytes || P.o.resid_mod != 0 || P.o.row_offset != 0 || P.down.resid_mod != 0 || P.down.row_offset != 0 || P.g_attn0 == nullptr ||
       P.g_mlp0 == nullptr || P.g_final == nullptr)
-    return hipErrorInvalidValue;
+    return false;
   // no block of the QKV projection straddles the boundary of keys and values, 8 features lie in one head
   const int value_tile = (P.qkv.q_cols + P.qkv.k_cols) / 32;
-  if ((P.qkv.q_cols + P.qkv.k_cols) % 32 != 0 || value_tile % T.qkv.nb != 0 || P.qkv.head_dim % 8 != 0 || P.qkv.rope != nullptr || P.up.act != ACT_GELU) return hipErrorInvalidValue;
+  if ((P.qkv.q_cols + P.qkv.k_cols) % 32 != 0 || value_tile % T.qkv.nb != 0 || P.qkv.head_dim % 8 != 0 || P.qkv.rope != nullptr || P.up.act != ACT_GELU) return false;
   const AttnParams& a = P.att;
   if (a.view_tokens != 256 || M != views * 256 || a.Tq != M || a.chunks0 != M / 32 || a.valid0 != M || a.chunks1 != 0 || a.heads < 1 || a.head_dim <= 64 || a.head_dim > 80 ||
       a.head_dim % 4 != 0 || a.out_ld % 16 != 0 || a.out_ld < a.heads * a.head_dim || a.key_splits > 1 || a.v_split > 1 || P.att_items != vision_loop_attention_items(views, a.heads) || (views != 2 && P.att_items > READER_RANK * 8))
-    return hipErrorInvalidValue;
+    return false;
   // every buffer of a slot lies inside it
   const size_t rows = (size_t)M, planes = (size_t)P.planes_rest * P.qkv.stat_rows * 8, head = (size_t)a.heads * (M / 32);
   const size_t ends[9] = {P.r_xb_o + rows * P.o.ldo2 * 2, P.r_xb_d + rows * P.o.ldo2 * 2,
                            P.r_st_o + planes, P.r_st_d + planes, P.r_q + head * 5 * 1024, P.r_k + head * 5 * 1024, P.r_v + head * 3 * 2048,
                            P.r_attn + rows * a.out_ld * 2, P.r_mid + rows * P.down.ldx * 2};
   for (size_t e : ends) {
-    if (e > P.ring_stride) return hipErrorInvalidValue;
+    if (e > P.ring_stride) return false;
   }
+  return true;
+}
+
+hipError_t launch_vision_loop(hipStream_t s, int views, const VisionLoopParams& P, VisionLoopParams* d_params, int blocks) {
+  if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0 || !vision_loop_takes(views, P, blocks)) return hipErrorInvalidValue;
   constexpr int pieces = (int)sizeof(VisionLoopParams) / 4 > (GB_WORDS - GB_START) / 4 ? (int)sizeof(VisionLoopParams) / 4 : (GB_WORDS - GB_START) / 4;
   hipLaunchKernelGGL(vision_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, P.sync);
   const hipError_t e = hipGetLastError();

@@ -46,6 +46,23 @@ def test_infer_equals_prefill_and_denoise(graphs):
         case.close()
 
 
+# 216 blocks of the kernel run GEMM items; up needs, with the tiles that the launches choose as well: 216 of them (the most that fit),
+# 224 and 228 (more than run items), 390 (more than the grid).  Where they do not fit pi0_infer launches the tower's operations.
+@pytest.mark.gpu
+@pytest.mark.parametrize("vis_mlp,views", [(5120, 1), (5376, 1), (4608, 2), (4864, 2), (4608, 3), (4864, 3), (8320, 3)])
+def test_feed_forward_widths_around_one_round(vis_mlp, views):
+    case = Case(dataclasses.replace(CFG, vis_mlp=vis_mlp))
+    try:
+        img, st, nz, ids = case.inputs(views, 0)
+        say(f"[gpu] vision loop vis_mlp={vis_mlp} views={views}")
+        want = by_launches(case, img, st, nz, ids)
+        for _ in range(2):
+            np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+        case.m.pi0_device_status(case.stream)
+    finally:
+        case.close()
+
+
 @pytest.mark.parametrize("views", [1, 2, 3])
 def test_vision_loop_fits_the_instruction_cache(views):
     """as test_loop_code_size.py for the denoise loop; nothing spilled"""
