@@ -871,7 +871,7 @@ int prefix_persistent(Run& r, int P, int stat_rows, int z, int k_per_split, Pref
   E.arena_bytes = (unsigned)arena_bytes;
   E.sync = at<unsigned>(c, w.psync);
   E.spin_limit = 1u << 20;
-  return variant;
+  return prefix_loop_takes(variant, E, PK_BLOCKS) ? variant : -1;
 }
 
 void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {

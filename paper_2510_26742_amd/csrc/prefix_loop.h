@@ -43,5 +43,6 @@ constexpr int PREFIX_QKV_PLANES = 8;              // planes of row statistics th
 
 hipError_t prefix_loop_init_attributes();
 hipError_t prefix_loop_max_blocks_per_cu(int* out);
+bool prefix_loop_takes(int variant, const PrefixLoopParams& P, int blocks);   // the variant covers this shape
 // d_params: device memory for one PrefixLoopParams (16-byte aligned), written by a small launch ahead of the kernel
 hipError_t launch_prefix_loop(hipStream_t s, int variant, const PrefixLoopParams& P, PrefixLoopParams* d_params, int blocks);

@@ -249,70 +249,74 @@ hipError_t prefix_loop_max_blocks_per_cu(int* out) {
   return hipSuccess;
 }
 
-// Host-side checks of everything the kernel's indexing assumes.
-hipError_t launch_prefix_loop(hipStream_t s, int variant, const PrefixLoopParams& P, PrefixLoopParams* d_params, int blocks) {
-  if (variant < 0 || variant >= VARIANTS) return hipErrorInvalidValue;
-  const Kernel k = kernel_for(variant);
-  const PrefixTiles& T = k.tiles;
-  if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0) return hipErrorInvalidValue;
+// Everything that the kernel's indexing assumes, so that what is not covered takes the launches
+bool prefix_loop_takes(int variant, const PrefixLoopParams& P, int blocks) {
+  if (variant < 0 || variant >= VARIANTS) return false;
+  const PrefixTiles T = prefix_loop_tiles(variant);
   if (blocks < 8 || blocks > GB_MAX_BLOCKS || blocks % 8 != 0 || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.spin_limit == 0)
-    return hipErrorInvalidValue;
+    return false;
   if (P.layers < 1 || P.ring == nullptr || (reinterpret_cast<uintptr_t>(P.ring) & 255) != 0 || P.ring_stride % 256 != 0 || P.arena == nullptr || P.arena_bytes == 0 ||
       P.layer_stride % 16 != 0 || P.gain_stride % 16 != 0 || P.kcache_stride % 16 != 0 || P.vcache_stride % 16 != 0)
-    return hipErrorInvalidValue;
+    return false;
   auto in_arena = [&](const void* p, size_t bytes) {
     const char* c = reinterpret_cast<const char*>(p);
     return p != nullptr && c >= P.arena && c + bytes <= P.arena + P.arena_bytes;
   };
-  if (!in_arena(P.ring, P.ring_stride * (size_t)P.layers)) return hipErrorInvalidValue;
+  if (!in_arena(P.ring, P.ring_stride * (size_t)P.layers)) return false;
   const int M = P.qkv.M, chunks = ceil_div(M, 32);
   const GemmParams* gs[4] = {&P.qkv, &P.o, &P.gu, &P.dn};
   for (const GemmParams* g : gs) {
-    if (g->M != M || M < 1 || g->W.w == nullptr || g->bias != nullptr || g->pf.blocks != 0) return hipErrorInvalidValue;
-    if (g->W.k_pad < 64 || g->W.k_pad % 64 != 0 || g->n_tiles < 1 || g->n_tiles * 32 != g->W.n_pad || g->ldx < g->W.k_pad || g->ldx % 16 != 0) return hipErrorInvalidValue;
-    if ((size_t)g->W.k_pad * 64 > 0x7fffffffu) return hipErrorInvalidValue;
+    if (g->M != M || M < 1 || g->W.w == nullptr || g->bias != nullptr || g->pf.blocks != 0) return false;
+    if (g->W.k_pad < 64 || g->W.k_pad % 64 != 0 || g->n_tiles < 1 || g->n_tiles * 32 != g->W.n_pad || g->ldx < g->W.k_pad || g->ldx % 16 != 0) return false;
+    if ((size_t)g->W.k_pad * 64 > 0x7fffffffu) return false;
   }
   // stream GEMMs: one round of blocks, parts of the k range as built
-  if (P.qkv.m_tiles != ceil_div(M, T.qkv.mb * 32) || ceil_div(P.qkv.n_tiles, T.qkv.nb) * P.qkv.m_tiles > blocks || P.qkv.W.k_pad != 16 * T.qkv.steps * T.qkv.parts) return hipErrorInvalidValue;
-  if (P.o.m_tiles != ceil_div(M, T.o.mb * 32) || ceil_div(P.o.n_tiles, T.o.nb) * P.o.m_tiles > blocks || P.o.W.k_pad != 16 * T.o.steps * T.o.parts) return hipErrorInvalidValue;
+  if (P.qkv.m_tiles != ceil_div(M, T.qkv.mb * 32) || ceil_div(P.qkv.n_tiles, T.qkv.nb) * P.qkv.m_tiles > blocks || P.qkv.W.k_pad != 16 * T.qkv.steps * T.qkv.parts) return false;
+  if (P.o.m_tiles != ceil_div(M, T.o.mb * 32) || ceil_div(P.o.n_tiles, T.o.nb) * P.o.m_tiles > blocks || P.o.W.k_pad != 16 * T.o.steps * T.o.parts) return false;
   const int value_tile = (P.qkv.q_cols + P.qkv.k_cols) / 32;
   if (P.qkv.rope == nullptr || P.qkv.head_dim != 256 || P.qkv.dqk_pad != 256 || P.qkv.nvb != 8 || P.qkv.kv_heads != 1 || P.qkv.k_cols != 256 || P.qkv.q_cols % 256 != 0 ||
       P.qkv.n_tiles != value_tile + 8 || value_tile % T.qkv.nb != 0 || P.qkv.kv_chunks < chunks || P.qkv.q_mbs != chunks || P.qkv.pos0 != 0)
-    return hipErrorInvalidValue;
+    return false;
   const size_t cache = (size_t)chunks * 16384;   // of a layer, in use
   if (P.kcache_stride < cache || P.vcache_stride < cache || !in_arena(P.qkv.kfrag, P.kcache_stride * (size_t)(P.layers - 1) + cache) ||
       !in_arena(P.qkv.vfrag, P.vcache_stride * (size_t)(P.layers - 1) + cache))
-    return hipErrorInvalidValue;
+    return false;
   const int E = P.o.W.n_pad;
-  if (E != 256 * PREFIX_QKV_PLANES || P.qkv.W.k_pad != E || P.gu.W.k_pad != E || P.dn.W.n_pad != E || P.qkv.ldx != E || P.gu.ldx != E || P.qkv.k_true != E || P.gu.k_true != E) return hipErrorInvalidValue;
-  if (P.qkv.stat_rows < M || P.qkv.stat_rows % 2 != 0 || P.o.stat_rows != P.qkv.stat_rows || P.gu.stat_rows != P.qkv.stat_rows || P.red.stat_rows != P.qkv.stat_rows) return hipErrorInvalidValue;
-  if (P.gu.rowstat_parts != ceil_div(P.o.n_tiles, T.o.nb) || P.gu.rowstat_parts < 2) return hipErrorInvalidValue;
-  if (P.o.ldo != E || P.o.ldo2 != E || P.o.n_valid != E || P.o.gain == nullptr || P.o.resid != P.o.out_f32 || !in_arena(P.o.out_f32, (size_t)M * E * 4)) return hipErrorInvalidValue;
+  if (E != 256 * PREFIX_QKV_PLANES || P.qkv.W.k_pad != E || P.gu.W.k_pad != E || P.dn.W.n_pad != E || P.qkv.ldx != E || P.gu.ldx != E || P.qkv.k_true != E || P.gu.k_true != E) return false;
+  if (P.qkv.stat_rows < M || P.qkv.stat_rows % 2 != 0 || P.o.stat_rows != P.qkv.stat_rows || P.gu.stat_rows != P.qkv.stat_rows || P.red.stat_rows != P.qkv.stat_rows) return false;
+  if (P.gu.rowstat_parts != ceil_div(P.o.n_tiles, T.o.nb) || P.gu.rowstat_parts < 2) return false;
+  if (P.o.ldo != E || P.o.ldo2 != E || P.o.n_valid != E || P.o.gain == nullptr || P.o.resid != P.o.out_f32 || !in_arena(P.o.out_f32, (size_t)M * E * 4)) return false;
   // gate||up and down
   const int gu_total = ceil_div(P.gu.n_tiles, 2 * T.gu.nt) * P.gu.m_tiles, dn_total = ceil_div(P.dn.n_tiles, 2 * T.dn.nt) * P.dn.m_tiles;
-  if (P.gu.m_tiles != ceil_div(M, T.gu.mt * 64) || P.dn.m_tiles != ceil_div(M, T.dn.mt * 64) || P.gu_blocks != 8 * ceil_div(gu_total, 8) || P.dn_blocks != (P.dn.range_per_die ? dn_total : 8 * ceil_div(dn_total, 8))) return hipErrorInvalidValue;
+  if (P.gu.m_tiles != ceil_div(M, T.gu.mt * 64) || P.dn.m_tiles != ceil_div(M, T.dn.mt * 64) || P.gu_blocks != 8 * ceil_div(gu_total, 8) || P.dn_blocks != (P.dn.range_per_die ? dn_total : 8 * ceil_div(dn_total, 8))) return false;
   if (P.gu.W.k_pad % 128 != 0 || P.gu.k_per_split != P.gu.W.k_pad || P.dn.k_per_split % 128 != 0 || P.dn.W.k_pad % 128 != 0 || P.red.Z < 1 || P.dn.range_per_die != (P.red.Z == LDS_DIES) ||
       P.dn.k_per_split % lds_tile_group(T.dn.mt, T.dn.nt) != 0 || (P.dn.W.k_pad - P.dn.k_per_split * (P.red.Z - 1)) % lds_tile_group(T.dn.mt, T.dn.nt) != 0 ||
       (long)P.dn.k_per_split * P.red.Z < P.dn.W.k_pad || (long)P.dn.k_per_split * (P.red.Z - 1) >= P.dn.W.k_pad)
-    return hipErrorInvalidValue;
-  if (T.gu_rows && (M > 256 || P.gu.W.k_pad % (16 * ROWS_GROUP) != 0 || P.gu.rowstat_parts > ROWS_PARTS)) return hipErrorInvalidValue;
-  if (T.walk && ((blocks >> 3) % P.gu.m_tiles != 0)) return hipErrorInvalidValue;   // a block's tiles are in the same rows
-  if (P.gu.ldo * 2 != P.gu.W.n_pad || P.dn.ldx != P.gu.ldo || P.dn.W.k_pad != P.gu.ldo) return hipErrorInvalidValue;
+    return false;
+  if (T.gu_rows && (M > 256 || P.gu.W.k_pad % (16 * ROWS_GROUP) != 0 || P.gu.rowstat_parts > ROWS_PARTS)) return false;
+  if (T.walk && ((blocks >> 3) % P.gu.m_tiles != 0)) return false;   // a block's tiles are in the same rows
+  if (P.gu.ldo * 2 != P.gu.W.n_pad || P.dn.ldx != P.gu.ldo || P.dn.W.k_pad != P.gu.ldo) return false;
   if (P.red.M != M || P.red.N != E || P.red.ldp != E || P.red.ldo != E || P.red.ldo2 != E || P.red.part != P.dn.out_f32 || P.red.out_f32 != P.o.out_f32 ||
       P.red.resid != P.o.out_f32 || P.red.bias != nullptr || P.red.gain == nullptr || P.red.out8 != nullptr || !in_arena(P.red.part, (size_t)P.red.Z * chunks * 32 * E * 4))
-    return hipErrorInvalidValue;
+    return false;
   const AttnParams& a = P.att;
   if (a.Tq != M || a.chunks0 != chunks || a.valid0 != M || a.chunks1 != 0 || a.heads * 256 != P.qkv.q_cols || a.head_dim != 256 || a.view_tokens != 0 || a.key_splits > 1 ||
       a.v_split > 1 || a.kv_head_stride0 != 0 || a.v_head_stride0 != 0 || a.q_head_stride != chunks * 8192 || a.out_ld != a.heads * 256 || P.o.W.k_pad != a.out_ld || P.o.ldx != a.out_ld ||
       a.k0 != P.qkv.kfrag || a.v0 != P.qkv.vfrag || chunks > T.att_chunks || chunks > PREFIX_LOOP_CHUNKS || P.att_tiles != ceil_div(M, T.att_rows) || P.att_tiles * a.heads > blocks)
-    return hipErrorInvalidValue;
+    return false;
   // every buffer of a slot lies inside it
   const size_t rows = (size_t)chunks * 32;
   const size_t ends[7] = {P.r_xb_o + rows * E * 2, P.r_xb_d + rows * E * 2, P.r_st_o + (size_t)P.gu.rowstat_parts * P.o.stat_rows * 8,
                           P.r_st_d + (size_t)PREFIX_QKV_PLANES * P.o.stat_rows * 8, P.r_q + rows * a.out_ld * 2, P.r_attn + rows * a.out_ld * 2, P.r_mid + rows * P.gu.ldo * 2};
   for (size_t e : ends) {
-    if (e > P.ring_stride) return hipErrorInvalidValue;
+    if (e > P.ring_stride) return false;
   }
+  return true;
+}
+
+hipError_t launch_prefix_loop(hipStream_t s, int variant, const PrefixLoopParams& P, PrefixLoopParams* d_params, int blocks) {
+  if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0 || !prefix_loop_takes(variant, P, blocks)) return hipErrorInvalidValue;
+  const Kernel k = kernel_for(variant);
   constexpr int pieces = (int)sizeof(PrefixLoopParams) / 4 > (GB_WORDS - GB_START) / 4 ? (int)sizeof(PrefixLoopParams) / 4 : (GB_WORDS - GB_START) / 4;
   hipLaunchKernelGGL(prefix_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, P.sync);
   const hipError_t e = hipGetLastError();
