@@ -33,8 +33,9 @@ __device__ __forceinline__ void stream_share(int die, int tiles, int& first, int
 
 // W: parts of the k range, added in order; V: parts that one wave accumulates (W / V waves in the block).  D: k steps in flight.
 // SG: groups in which the planes of row statistics are added (group g: planes g, g + SG, ...; then the groups in order).
-// PARTS: most planes.  NS: k steps of a wave if known, else 0.  cx.bx: the item.
-template <int MB, int NB, int W, int V, int D, int SG, int PARTS, int NS, int PRO, int EPI, class Cx>
+// PARTS: most planes.  NS: k steps of a wave if known, else 0.  LINES_SHARED: blocks of different dies wrote parts of one cache line
+// of the row statistics, which are then read past the caches (exec_ctx.h, BULK_CACHED).  cx.bx: the item.
+template <int MB, int NB, int W, int V, int D, int SG, int PARTS, int NS, int PRO, int EPI, bool LINES_SHARED = false, class Cx>
 __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& cx, unsigned char* smem_raw) {
   constexpr int WR = W / V;   // waves
   static_assert(W % V == 0 && (WR == 4 || WR == 8), "four or eight waves");
@@ -182,7 +183,11 @@ __device__ __forceinline__ void gemm_stream_body(const GemmParams& p, const Cx& 
   // stages in front of it.  A launch takes one load for whole-row sums, else batches of 36 planes.
   const int parts = Cx::kPersistent ? PARTS : p.rowstat_parts > 1 ? p.rowstat_parts : 1;
   const size_t stat_rowg = (size_t)min(m0 + stat_row, p.M - 1);
-  auto plane = [&](int k) { return cx.ld_bulk(reinterpret_cast<const float2*>(p.rowstat + 2 * ((size_t)min(k, parts - 1) * p.stat_rows + stat_rowg))); };
+  auto plane = [&](int k) {
+    const float2* const v = reinterpret_cast<const float2*>(p.rowstat + 2 * ((size_t)min(k, parts - 1) * p.stat_rows + stat_rowg));
+    if constexpr (LINES_SHARED) return cx.ld(v);
+    else return cx.ld_bulk(v);
+  };
   float2 planes[Cx::kPersistent && PRO != PRO_NONE ? SG : 1][Cx::kPersistent && PRO != PRO_NONE ? PPG : 1];
   if (Cx::kPersistent && stat_thread) {
 #pragma unroll

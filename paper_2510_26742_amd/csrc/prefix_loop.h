@@ -17,7 +17,8 @@ struct PrefixLoopParams {
   size_t kcache_stride, vcache_stride;   // bytes between consecutive layers of the cache
   // Ring of per-layer buffers (layer l at ring + l * ring_stride), as VisionLoopParams has it: gain-scaled bf16 copy of the residual stream and row
   // statistics after the O and the down projection, queries, the attention's output, the GeGLU product.  Layer 0's queries
-  // are there before the launch.  (The residual stream and down's partial sums stay where they are: they are read past the caches.)
+  // are there before the launch.  (The residual stream and down's partial sums stay where they are: they are read past the caches.  So are
+  // the row statistics after the down projection: an item of the reduction leaves half a cache line of each plane, the next block the other.)
   char* ring;
   size_t ring_stride;
   unsigned r_xb_o, r_st_o, r_xb_d, r_st_d, r_q, r_attn, r_mid;

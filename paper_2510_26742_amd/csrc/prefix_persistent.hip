@@ -184,7 +184,7 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       q.kfrag = reinterpret_cast<bf16*>(reinterpret_cast<char*>(q.kfrag) + (size_t)(l + 1) * F.kcache_stride);
       q.vfrag = reinterpret_cast<bf16*>(reinterpret_cast<char*>(q.vfrag) + (size_t)(l + 1) * F.vcache_stride);
       using O = typename C::Qkv;
-      gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, PREFIX_QKV_PLANES, O::NS, PRO_RMS, EPI_QKV>(q, item(blockIdx.x, 0), smem_raw);
+      gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, PREFIX_QKV_PLANES, O::NS, PRO_RMS, EPI_QKV, true>(q, item(blockIdx.x, 0), smem_raw);
       bar.arrive();
     }
   }
@@ -311,6 +311,11 @@ bool prefix_loop_takes(int variant, const PrefixLoopParams& P, int blocks) {
   for (size_t e : ends) {
     if (e > P.ring_stride) return false;
   }
+  // ... on cache lines of its own, planes of row statistics too
+  for (unsigned at : {P.r_xb_o, P.r_st_o, P.r_xb_d, P.r_st_d, P.r_q, P.r_attn, P.r_mid}) {
+    if (at % 128 != 0) return false;
+  }
+  if (P.o.stat_rows * 8 % 128 != 0) return false;
   return true;
 }
 

@@ -323,6 +323,11 @@ bool vision_loop_takes(int views, const VisionLoopParams& P, int blocks) {
   for (size_t e : ends) {
     if (e > P.ring_stride) return false;
   }
+  // ... on cache lines of its own, planes of row statistics too
+  for (unsigned at : {P.r_xb_o, P.r_st_o, P.r_xb_d, P.r_st_d, P.r_q, P.r_k, P.r_v, P.r_attn, P.r_mid}) {
+    if (at % 128 != 0) return false;
+  }
+  if (P.o.stat_rows * 8 % 128 != 0) return false;
   return true;
 }
 

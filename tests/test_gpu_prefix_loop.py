@@ -2,6 +2,9 @@
 every sum in the same order, so they agree bit for bit at both ends of every range of prefix tokens that has a variant of its own,
 whatever a replay before left in the kernel's buffers.  (The launches are compared with the oracle in test_gpu_parity.py.)"""
 import dataclasses
+import os
+import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -53,3 +56,24 @@ def test_prefix_loop_spills_no_registers(variant):
     found = {k: v for code in code_objects(library) for k, v in symbols(code).items() if f"prefix_loop_kernelILi{variant}EE" in k}
     (name, _), = [(k, v) for k, v in found.items() if "." not in k]
     assert found[name + ".private_seg_size"][0] == 0, "registers spilled"
+
+
+OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+@pytest.mark.parametrize("variant", range(5))
+def test_row_statistics_of_down_are_read_past_the_caches(variant, tmp_path):
+    """An item of the reduction behind down leaves 64 bytes of a plane of row statistics, half a cache line, and the other half comes from
+    another die.  A cached load of such a line could find the half that the reading die wrote and an older other one, which no parity
+    test would show reliably: the QKV projection's eight loads of them (one per plane) have device scope.  Read from the code as built
+    here; everything else that is read past the caches there goes 16 bytes at a time."""
+    binding.lib()
+    with open(build.LIB, "rb") as f:
+        library = f.read()
+    code, = [c for c in code_objects(library) if any(f"prefix_loop_kernelILi{variant}EE" in k for k in symbols(c))]
+    at = tmp_path / "code.o"
+    at.write_bytes(code)
+    text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(at)], check=True, capture_output=True, text=True).stdout
+    kernel, = [p for p in re.split(r"\n(?=[0-9a-f]+ <)", text) if f"prefix_loop_kernelILi{variant}EE" in p.split("\n", 1)[0]]
+    assert len(re.findall(r"\bbuffer_load_dword(?:x2)? [^\n]*\bsc1\b", kernel)) == 8
