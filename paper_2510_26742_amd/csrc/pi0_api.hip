@@ -347,7 +347,7 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
     w.ering = cur.take(ering_bytes);
   }
   if (vision_loop_geometry(d)) {   // one slot per vision layer: the buffers vh_b .. vmid above, each 256-byte aligned
-    const size_t I = d.maxI, heads = (size_t)d.Hv * (d.maxI / 32), planes = (size_t)(d.Dv / 32) * d.maxPc * 32 * 2 * 4;
+    const size_t I = std::min(d.maxI, VISION_LOOP_VIEWS * d.T), heads = (size_t)d.Hv * (I / 32), planes = (size_t)(d.Dv / 32) * d.maxPc * 32 * 2 * 4;
     WsCursor sl;
     w.rv_xb_o = (unsigned)sl.take(I * d.Dv * 2);
     w.rv_st_o = (unsigned)sl.take(planes);

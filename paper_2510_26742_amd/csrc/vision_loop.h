@@ -36,6 +36,7 @@ struct VisionTile {
   bool takes(int k_pad) const { return steps != 0 ? (k_pad >> 4) == steps * parts : (k_pad >> 4) % parts == 0; }
 };
 struct VisionTiles { VisionTile qkv, resid, up; };
+constexpr int VISION_LOOP_VIEWS = 3;                      // most views that the kernel takes
 bool vision_loop_tiles(int views, VisionTiles* out);
 int vision_loop_planes(int views);                        // planes of row statistics that it adds up
 int vision_loop_attention_items(int views, int heads);

@@ -251,13 +251,13 @@ int vision_loop_attention_items(int views, int heads) {
 }
 
 bool vision_loop_tiles(int views, VisionTiles* out) {
-  if (views < 1 || views > 3) return false;
+  if (views < 1 || views > VISION_LOOP_VIEWS) return false;
   *out = views == 1 ? tiles_of<1>() : views == 2 ? tiles_of<2>() : tiles_of<3>();
   return true;
 }
 
 hipError_t vision_loop_init_attributes() {
-  for (int v = 1; v <= 3; v++) {
+  for (int v = 1; v <= VISION_LOOP_VIEWS; v++) {
     const Kernel k = kernel_for(v);
     const hipError_t e = hipFuncSetAttribute(k.f, hipFuncAttributeMaxDynamicSharedMemorySize, k.smem);
     if (e != hipSuccess) return e;
@@ -267,7 +267,7 @@ hipError_t vision_loop_init_attributes() {
 
 hipError_t vision_loop_max_blocks_per_cu(int* out) {
   *out = 1 << 30;
-  for (int v = 1; v <= 3; v++) {
+  for (int v = 1; v <= VISION_LOOP_VIEWS; v++) {
     const Kernel k = kernel_for(v);
     int n = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k.f, k.threads, k.smem);

@@ -55,6 +55,14 @@ def test_full_model_sizes_are_plausible(L):
     assert binding.pi0_workspace_bytes(cfg) < 8e9
 
 
+def test_workspace_of_a_view_the_loops_do_not_take(L):
+    """The persistent kernels' rings end at three views: a fourth adds its own buffers (as the second does, whose ring lies in the expert's
+    place) and, planes of row statistics being as long as the most rows, 4 MB of the ring (4 %).  A narrow feed-forward, so that the vision
+    tower's ring is the largest of the three."""
+    b = [binding.pi0_workspace_bytes(synth.dataclasses.replace(synth.full_config(), llm_mlp=2048, max_prompt=0, max_views=v)) for v in (1, 2, 3, 4)]
+    assert b[3] - b[2] < 1.05 * (b[1] - b[0])
+
+
 def test_create_rejects_bad_geometry(L):
     good = synth.reduced_config()
     bad = [dict(head_dim=128), dict(chunk=31), dict(vis_width=1150), dict(exp_layers=3), dict(steps=0),
