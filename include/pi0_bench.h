@@ -134,9 +134,9 @@ int pi0_clock_sample(long long* d_out, void* hip_stream);
 int pi0_read_ahead_probe(const void* d_buf, size_t bytes, int layers, int steps, int lead, const int* d_progress,
                          long long wait_ticks, int blocks, unsigned* d_sink, double* h_ms, void* hip_stream);
 
-/* Number of kernel launches of one inference for the given shape (0 on bad arguments), the prefill launch by launch as pi0_prefill
- * issues it.  (Where pi0_infer runs the vision tower's layers as one kernel its graph has two launches in their place.)  The copies of the inputs
- * before it and of the actions behind it (a launch each) and the read-ahead kernel on the ctx's own stream are not counted. */
+/* Number of kernel launches of one pi0_infer's graph for the given shape (0 on bad arguments); before the weights are loaded, on a device
+ * that runs none of the persistent kernels.  The copies of the inputs before it and of the actions behind it (a launch each) and the
+ * read-ahead kernel on the ctx's own stream are not counted. */
 int pi0_kernel_count(const pi0_ctx* ctx, int n_views, int n_prompt);
 
 /*

@@ -686,7 +686,7 @@ bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_ro
   const Dims& d = c->d;
   const WsLayout& w = c->wl;
   const Tune& T = c->tune;
-  if (!r.prefill_loops || r.count_only || r.timer != nullptr || !T.pvl || !c->vk_ok || w.vring_slot == 0) return false;
+  if (!r.prefill_loops || r.timer != nullptr || !T.pvl || !c->vk_ok || w.vring_slot == 0) return false;
   // the launches' own choices, so that both give the same bits
   if (T.vis >= 0 || T.vqkv >= 0 || T.vup >= 0 || T.vo >= 0 || T.zvo >= 0 || T.vd >= 0 || T.zvd >= 0 || T.fko >= 0) return false;
   VisionTiles tiles;
@@ -746,6 +746,7 @@ bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_ro
   if (!vision_loop_takes(n_views, E, PK_BLOCKS)) return false;
   r.cls = PI0_OP_MISC;
   RUN(r, launch_vision_loop(r.s, n_views, E, at<VisionLoopParams>(c, w.vparams), PK_BLOCKS));
+  r.launches++;   // two launches: parameter block and barrier words, loop kernel
   const size_t last = w.vring + w.vring_slot * (size_t)(d.Lv - 1);
   *out = at<bf16>(c, last + w.rv_xb_d);
   *stats = at<float>(c, last + w.rv_st_d);
@@ -793,7 +794,7 @@ int prefix_persistent(Run& r, int P, int stat_rows, int z, int k_per_split, Pref
   const Dims& d = c->d;
   const WsLayout& w = c->wl;
   const Tune& T = c->tune;
-  if (!r.prefill_loops || r.count_only || r.timer != nullptr || !T.ppl || !c->xk_ok || w.pring_slot == 0 || P > 32 * PREFIX_LOOP_CHUNKS || c->precision != PI0_PRECISION_BF16) return -1;
+  if (!r.prefill_loops || r.timer != nullptr || !T.ppl || !c->xk_ok || w.pring_slot == 0 || P > 32 * PREFIX_LOOP_CHUNKS || c->precision != PI0_PRECISION_BF16) return -1;
   if (T.lqkv >= 0 || T.lgu >= 0 || T.lo >= 0 || T.zlo >= 0 || T.fkl >= 0 || T.ld >= 0 || T.zld >= 0) return -1;
   const WsTr& L0 = w.llm[0];
   const int chunks = ceil_div(P, 32), o_tiles = L0.o.n_pad / 32;
@@ -1056,6 +1057,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     if (loop >= 0) {   // everything between the first layer's QKV projection and the last one's
       r.cls = PI0_OP_MISC;
       RUN(r, launch_prefix_loop(r.s, loop, E, at<PrefixLoopParams>(c, w.pparams), PK_BLOCKS));
+      r.launches++;   // two launches, as for the tower
       l = d.Ll - 2;
       continue;
     }
@@ -1909,7 +1911,7 @@ int pi0_device_status(pi0_ctx* c, void* hip_stream) {
 int pi0_kernel_count(const pi0_ctx* c, int n_views, int n_prompt) {
   if (c == nullptr || n_views < 1 || n_views > c->cfg.max_views || n_prompt < 0 || n_prompt > c->cfg.max_prompt) return 0;
   Run r{const_cast<pi0_ctx*>(c), nullptr, true};
-  r.persistent_ok = true;
+  r.persistent_ok = r.prefill_loops = true;   // (before weights are loaded no device is known to hold them)
   run_prefill(r, n_views, n_prompt, nullptr);
   run_denoise(r, n_views * c->d.T + n_prompt, nullptr);
   return r.launches;

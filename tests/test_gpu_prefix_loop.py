@@ -40,8 +40,13 @@ def test_infer_equals_prefill_and_denoise(graphs):
             assert np.isnan(case.infer(np.full_like(img, np.nan), st, nz, ids)).all()
             for _ in range(2):
                 np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            launches = case.m.pi0_kernel_count(n_views, n_prompt)
             case.m.pi0_tune("ppl=0")
             np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            # five operations a whole layer, and beyond 256 tokens a launch that adds up row statistics, and the QKV projections between
+            # them become two launches in all
+            tokens, layers = 256 * n_views + n_prompt, CFG.llm_layers - 1
+            assert case.m.pi0_kernel_count(n_views, n_prompt) - launches == (0 if tokens > 768 else layers * (5 + (tokens > 256)) + layers - 1 - 2)
             case.m.pi0_tune("ppl=1")
         case.m.pi0_device_status(case.stream)   # raises if a bounded wait ran out
     finally:

@@ -38,8 +38,11 @@ def test_infer_equals_prefill_and_denoise(graphs):
             assert np.isnan(case.infer(np.full_like(img, np.nan), st, nz, ids)).all()
             for _ in range(3):
                 np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            launches = case.m.pi0_kernel_count(n_views, 0)
             case.m.pi0_tune("pvl=0")
             np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            # five operations a layer, and beyond 256 tokens a launch that adds up row statistics, become two launches in all
+            assert case.m.pi0_kernel_count(n_views, 0) - launches == (0 if n_views > 3 else CFG.vis_layers * (5 + (n_views > 1)) - 2)
             case.m.pi0_tune("pvl=1")
         case.m.pi0_device_status(case.stream)   # raises if a bounded wait ran out
     finally:
