@@ -1,6 +1,7 @@
 """The prefix of pi0_infer runs as one persistent kernel with grid barriers; pi0_prefill launches its operations one by one.  Both add up
-every sum in the same order, so they agree bit for bit at both ends of every range of prefix tokens that has a variant of its own,
-whatever a replay before left in the kernel's buffers.  (The launches are compared with the oracle in test_gpu_parity.py.)"""
+every sum in the same order, so they agree bit for bit: at both ends of every range of prefix tokens that has a variant of its own, inside it
+and next to it, and whatever a replay before left in the kernel's buffers.  (The launches are compared with the oracle in
+test_gpu_parity.py.)"""
 import dataclasses
 import os
 import re
@@ -49,6 +50,60 @@ def test_infer_equals_prefill_and_denoise(graphs):
             assert case.m.pi0_kernel_count(n_views, n_prompt) - launches == (0 if tokens > 768 else layers * (5 + (tokens > 256)) + layers - 1 - 2)
             case.m.pi0_tune("ppl=1")
         case.m.pi0_device_status(case.stream)   # raises if a bounded wait ran out
+    finally:
+        case.close()
+
+
+# The variants and where they end, with the full model's feed-forward: 193 .. 256, 257 .. 320, 385 .. 512, 513 .. 576, 641 .. 768 tokens
+# (prefix_loop_tiles says which tiles, gemm_stream_tile and gemm_lds_tile where the launches choose the same ones).  What lies between runs
+# as launches.  (views, prompt) of 256-token views, and of 64-token ones for fewer than 256.
+RANGES = [(193, 256), (257, 320), (385, 512), (513, 576), (641, 768)]
+WHOLE_VIEWS = dict(shapes=[(1, 0), (1, 64), (1, 65), (1, 128), (1, 129), (1, 135), (1, 191), (1, 255), (2, 1), (2, 33), (2, 64), (2, 65), (2, 128), (2, 129),
+                           (2, 188), (2, 255), (3, 0), (3, 1)], max_prompt=255)
+SMALL_VIEWS = dict(shapes=[(3, 0), (3, 1), (3, 8), (3, 31), (3, 33), (3, 63), (4, 0)], max_views=4, img_size=112, max_prompt=63)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("small", [False, True])
+def test_ragged_lengths_of_every_variant(small):
+    kw = dict(SMALL_VIEWS if small else WHOLE_VIEWS)
+    shapes = kw.pop("shapes")
+    case = Case(dataclasses.replace(CFG, **kw))
+    try:
+        for n_views, n_prompt in shapes:
+            tokens = n_views * case.cfg.tokens_per_view + n_prompt
+            say(f"[gpu] prefix loop, {tokens} tokens")
+            img, st, nz, ids = case.inputs(n_views, n_prompt)
+            want = by_launches(case, img, st, nz, ids)
+            np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            assert np.isnan(case.infer(np.full_like(img, np.nan), st, nz, ids)).all()
+            np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            launches = case.m.pi0_kernel_count(n_views, n_prompt)
+            case.m.pi0_tune("ppl=0")
+            assert (case.m.pi0_kernel_count(n_views, n_prompt) > launches) == any(a <= tokens <= b for a, b in RANGES)
+            case.m.pi0_tune("ppl=1")
+        case.m.pi0_device_status(case.stream)
+    finally:
+        case.close()
+
+
+# A narrow feed-forward sends every prefix of up to 256 tokens to the first variant, however short
+@pytest.mark.gpu
+@pytest.mark.parametrize("llm_mlp", [2048, 4096])
+def test_short_prefixes_of_a_narrow_feed_forward(llm_mlp):
+    case = Case(dataclasses.replace(CFG, llm_mlp=llm_mlp, max_views=4, img_size=112, max_prompt=63))
+    try:
+        for n_views, n_prompt in ((1, 0), (1, 1), (1, 31), (2, 0), (2, 37), (3, 0), (4, 0)):
+            say(f"[gpu] prefix loop, llm_mlp {llm_mlp}, {64 * n_views + n_prompt} tokens")
+            img, st, nz, ids = case.inputs(n_views, n_prompt)
+            want = by_launches(case, img, st, nz, ids)
+            for _ in range(2):
+                np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            launches = case.m.pi0_kernel_count(n_views, n_prompt)
+            case.m.pi0_tune("ppl=0")
+            assert case.m.pi0_kernel_count(n_views, n_prompt) > launches
+            case.m.pi0_tune("ppl=1")
+        case.m.pi0_device_status(case.stream)
     finally:
         case.close()
 
