@@ -3,10 +3,10 @@
 // Orientation and epilogues as in gemm.hip.  A block of 4 waves owns 2 MT * 32 tokens x 2 NT * 32 features, a wave MT x NT
 // tiles of 32 x 32.  Operands are in fragment order in memory, so a stage (2 k16 steps) is a list of 1 KiB fragments; they
 // go from memory straight to LDS (global_load_lds_dwordx4: lane l's 16 bytes land at base + 16 l) and come back as whole
-// fragments, one k16 step ahead of the products.  Four stages rotate: one is being multiplied, the next is complete, two are
-// on their way; eight with tiles small enough (down at one view, four stages: loop 22.1 us, eight: 18.3).
+// fragments, one k16 step ahead of the products.  The stages rotate: one is being multiplied, the next is complete, the others are
+// on their way; four, or eight with tiles small enough (down at one view, four stages: loop 22.1 us, eight: 18.3).
 // What bounds it: with a single wave per SIMD everything between two products is time the matrix cores stand still, so the
-// loop is straight-line code over a group of four stages - every LDS offset, every memory offset within a group and every
+// loop is straight-line code over a group of all stages - every LDS offset, every memory offset within a group and every
 // wait count is a constant, and reads and requests are issued one by one between the products (in front of them, the eight
 // reads of a step alone cost 200 of its 512 cycles; with stage indices computed at run time the step took 1240).  At 512
 // tokens the loop takes 537 cycles per 16 products of 32 cycles; the chip then clocks at 1.25 - 1.4 GHz instead of 2.4, so

@@ -50,7 +50,7 @@ __device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx,
   constexpr int L = NF / W;                      // fragments a wave requests per stage
   static_assert(NF % W == 0, "even shares");
   constexpr int ROWS = XB * 32;
-  // shared memory: row statistics, then [stage][fragment][1 KiB]; in the persistent kernel, where planes want the room, the stages first
+  // shared memory: row statistics, then [stage][fragment][1 KiB]; in the persistent kernel the stages first
   float2* sstat = reinterpret_cast<float2*>(smem + (Cx::kPersistent ? LT_STAGES * NF * 1024 : 0));
   unsigned char* const smem_raw = smem + (Cx::kPersistent || PRO == PRO_NONE ? 0 : (WALK ? 2 : 1) * lds_tile_stat_bytes(MT));
 
@@ -113,7 +113,7 @@ __device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx,
   // to its first product 4.3 us at 256 and 512 tokens, as against 1.9 without statistics;
   // prefill at 512 / 768 / 816 tokens 4.432 / 5.822 / 6.350 -> 4.414 / 5.790 / 6.310 ms).
   constexpr int PAIRS = ROWS / 2, RR = (ROWS + 64 * W - 1) / (64 * W);
-  constexpr int PLANES = Cx::kPersistent ? (LT_SMEM - (LT_STAGES - 1) * NF * 1024) / (ROWS * 8) : lds_tile_planes(MT, NT);
+  constexpr int PLANES = lds_tile_planes(MT, NT);
   static_assert(PRO == PRO_NONE || PLANES >= 1, "room for a plane");
   float2 sum[RR] = {};
   const int parts = PRO != PRO_NONE ? p.rowstat_parts : 0;
@@ -151,7 +151,7 @@ __device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx,
   constexpr int RC = ROWS / 64;
   float gsum[SG > 1 ? 2 : 1][SG > 1 ? RC : 1] = {};
   float gv[SG > 1 ? 2 : 1][SG > 1 ? SG : 1][SG > 1 ? RC : 1];
-  static_assert(SG == 1 || (SG == 2 * W && PRO == PRO_RMS && Cx::kPersistent), "two groups for each wave");
+  static_assert(SG == (PRO != PRO_NONE && Cx::kPersistent ? 2 * W : 1), "in the persistent kernel planes in groups, two for each wave");
   if constexpr (SG > 1) {
 #pragma unroll
     for (int g = 0; g < 2; g++)
@@ -204,11 +204,6 @@ __device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx,
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     add_planes(parts - plane);
-    if (Cx::kPersistent) {   // the statistics' place is behind the stages, where planes were
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-    }
 #pragma unroll
     for (int i = 0; i < RR; i++) sstat[min(t + i * 64 * W, ROWS - 1)] = sum[i];   // the last row's extra threads store the same
   }
@@ -237,7 +232,7 @@ __device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx,
       else if (r <= NT) wf[u][r - 1] = *reinterpret_cast<const bf16x8*>(ws + o + (r - 1) * LT_KC * 1024);
       else xf[u][r - NT] = *reinterpret_cast<const bf16x8*>(xs + o + (r - NT) * LT_KC * 1024);
     };
-    // stage 0 (stages 1 and 2 may be on their way) and the row statistics are complete for everybody; where the weights went
+    // stage 0 (the other stages requested may be on their way) and the row statistics are complete for everybody; where the weights went
     // ahead stage 1 too, because the count in front of it below takes its requests for whole ones
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(Cx::kPersistent ? LX : (LT_STAGES - 2) * L) : "memory");
     __builtin_amdgcn_s_barrier();
@@ -245,9 +240,9 @@ __device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx,
 #pragma unroll
     for (int r = 0; r < R; r++) read(0, 0, r);
 
-    // One group of four stages; LAST: nothing beyond it is requested.  Step s multiplies the fragments of set s % 2 and reads
+    // One group of LT_STAGES stages; LAST: nothing beyond it is requested.  Step s multiplies the fragments of set s % 2 and reads
     // those of step s + 1 into the other set.  In the second step of stage q the next stage must be complete for everybody
-    // (one more may be on its way); everybody has then read stage q - 1, whose place stage q + 3 takes.
+    // (LT_STAGES - 3 more may be on their way); everybody has then read stage q - 1, whose place stage q + LT_STAGES - 1 takes.
     auto group = [&](auto last_group) {
       constexpr bool LAST = decltype(last_group)::value != 0;
       turn = turn + 1 == groups ? 0 : turn + 1;
@@ -348,6 +343,7 @@ __device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx,
 constexpr int ROWS_STAGES = 8, ROWS_NT = 4, ROWS_PARTS = 32;   // stages, feature tiles, most planes of row statistics
 constexpr int ROWS_GROUP = 16;   // k16 steps of a turn of the loop
 constexpr int GEMM_ROWS_SMEM = ROWS_STAGES * ROWS_NT * LT_KC * 1024 + 256 * 4;
+static_assert(GEMM_ROWS_SMEM <= LT_SMEM, "what the persistent kernel asks for");
 template <class Cx>
 __device__ __forceinline__ void gemm_rows_body(const GemmParams& p, const Cx& cx, unsigned char* smem) {
   constexpr int W = 4, MT = 2, NT = ROWS_NT, SF = NT * LT_KC, L = SF / W;   // fragments of a stage, of a wave's share of it
