@@ -31,11 +31,9 @@ static_assert(PK_TAIL >= SK_WAVES * 8 * 1024 && ATTN_SUFFIX_SMEM >= SK_WAVES * 6
 // step, so an operation's weight request - issued when the operation before ends - goes all the way to HBM (the same loop
 // run on one layer's weights throughout, i.e. from that cache, is 0.46 ms faster).  The attention has 64 items for 256
 // blocks: the blocks without one use the time to read the weights that the following operations will ask for, which puts
-// them into the memory-side cache.  Part `part` of `nparts` of n16 16-byte pieces, piece i at addr(i): 16 bytes per lane,
-// 8 loads in flight (4 finish too late, 16 disturb the working blocks' loads more than they gain: pi0_denoise
-// 5.47 / 5.42 / 5.48 ms on one device, before the flag barrier); the values are folded into a word that is stored only if it equals a constant, so no result
-// depends on them.
-// The same for a packed weight matrix of n_tiles 32-feature tiles of kc16 KiB, shared out so that a block reads what
+// them into the memory-side cache (read_ahead_part; 8 loads in flight: 4 finish too late, 16 disturb the working blocks' loads more than
+// they gain, pi0_denoise 5.47 / 5.42 / 5.48 ms on one device, before the flag barrier).
+// A packed weight matrix of n_tiles 32-feature tiles of kc16 KiB is shared out so that a block reads what
 // blocks of its own die will ask for (their L2 then holds it: the second request is one die-local round trip).  Work
 // items go to blocks in turn and consecutive blocks to different dies, so items u, u + 8, ... share a die.  UNIT: what
 // consecutive items take: 2 = pairs of tiles (gate||up), 1 = a tile (QKV), 0 = half a tile, i.e. 16 of its 32 features

@@ -86,7 +86,13 @@ hipError_t lds_tile_launch(hipStream_t s, GemmParams p, int z) {
 bool gemm_lds_ok(int k_pad) { return k_pad % 128 == 0; }
 
 // Eight ranges, one for each die, unless the cost finds fewer better: at 816 tokens down and its reduction take 78 us with eight
-// (256 x 256 tiles) and 73 with six (192 x 256 in five token tiles)
+// (256 x 256 tiles) and 73 with six (192 x 256 in five token tiles).
+// The line was drawn at 2048 features and k = 16384.  At other widths, pi0_prefill with as many ranges as the cost asks for up to 16, all dies
+// on all of them -> this, features x k, 256 .. 768 tokens: where the cost asked for more than eight (k 16384 and 32768) +11 .. -2 % in speed, 1024 x 16384
+// 685 / 773 / 972 / 1252 -> 692 / 710 / 915 / 1203 us at 256 / 263 / 512 / 768 tokens, 2048 x 32768 1412 / 1582 -> 1428 / 1611 at 256 / 263; with eight both
+// times (512 and 1024 x 2048 .. 8192) mostly +1 .. +7 %.  Slower by more than 2 % is only a range of less than 1024 that
+// keeps all units of a die busy, whose reduction then waits for the partial sums: 1024 x 4096 at 768 tokens 781 -> 825, 1280 x 4096 at 512
+// 718 -> 764, 768 x 4096 at 544 629 -> 645, 1024 x 6144 at 768 858 -> 882; next to them, 1280 x 4096 at 544, the same rule gains (809 -> 795).
 int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max) {
   int best_z = 1;
   float best = -1.f;

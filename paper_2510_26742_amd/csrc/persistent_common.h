@@ -1,4 +1,4 @@
-// What the persistent kernels share (expert_persistent.hip, vision_persistent.hip): reading their parameter block, handing out items.
+// What the persistent kernels share (expert_persistent.hip, vision_persistent.hip, prefix_persistent.hip): reading their parameter block, handing out items.
 #pragma once
 #include "exec_ctx.h"
 #include "pi0_internal.h"

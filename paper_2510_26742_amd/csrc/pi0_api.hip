@@ -465,8 +465,8 @@ struct pi0_ctx {
   unsigned char* static_scratch = nullptr;   // that device's copy of the library's static scratch array
   long long* loop_trace = nullptr;     // optional timeline buffer of the persistent denoise kernel (pi0_set_loop_trace)
   int loop_trace_ops = 0;
-  bool vk_ok = false, xk_ok = false;   // ... and the persistent vision and prefix kernels'
   bool pk_ok = false;                  // the device can hold the persistent denoise kernel's 256 blocks at once
+  bool vk_ok = false, xk_ok = false;   // ... and the persistent vision and prefix kernels'
   bool graph_mode = true;
   int precision = PI0_PRECISION_BF16;   // PI0_PRECISION_MXFP8_PREFIX_MLP: prefix gate||up / down on MXFP8 operands
   int cur_views = 0, cur_prompt = 0;   // shape of the valid prefill (0 views = none)
@@ -896,8 +896,8 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
   // Beyond 256 tokens a launch of its own adds up the partial sums that an O projection leaves.  For the prefix that is the quicker
   // way: without the 17 launches (fkl=1) the prefill takes +87 / +30 / -5 / +25 / +9 / +18 us at 263 / 304 / 512 / 533 / 768 / 816
   // tokens.  For the vision tower it is not: without the 27 launches (fko=1) it takes 4.330 -> 4.263 ms at 2 views and
-  // 5.731 -> 5.662 at 3.  They stay because the number of launches that pi0_kernel_count and pi0_debug_profile report there is
-  // relied on.  A consumer takes 64 planes at most.
+  // 5.731 -> 5.662 at 3.  They stay because the number of launches of a prefill that pi0_kernel_count and pi0_debug_profile report
+  // is relied on.  A consumer takes 64 planes at most.
   auto sum_vision = [&](int tokens_over) {
     if (vplanes > 64 || (vplanes > 0 && I > tokens_over)) {
       r.cls = PI0_OP_REDUCE;

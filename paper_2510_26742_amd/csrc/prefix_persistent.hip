@@ -9,8 +9,9 @@
 // memory path hand out, beyond the clock that the matrix cores' power leaves).  Between two operations lie 1.0 .. 1.5 us from the
 // last block's end to the first block's release, where launches have a boundary, cold code and arguments, and from 257 tokens on a
 // launch that adds up row statistics; the partial sums of down take another 5 .. 8 us to reach memory at two and three views.
-// Per layer at 1 / 2 / 3 views, us: attention 6.5 / 11.2 / 16.3, O 8.1 / 12.3 / 16.2, gate||up 37 (gemm_rows_body) / 60 / 91, down 25.6 / 41 / 54, its reduction
-// 6.4 / 6.2 / 7.0, QKV 10.3 / 14.3 / 15.8.  pi0_infer, one device, ms, launches -> here: 1 view 6.408 -> 6.259 (-> 6.18 with gemm_rows_body), 1 view + 7 tokens 6.640 -> 6.511,
+// Per layer with what lies between it and the next operation, at 1 / 2 / 3 views, us (profiles/loop_timeline_prefill_full_pi0.txt): attention
+// 6.3 / 11.7 / 16.3, O 8.4 / 12.6 / 16.5, gate||up 38.6 (gemm_rows_body) / 59.7 / 90.7, down 26.0 / 40.6 / 54.4, its reduction 6.5 / 6.2 / 7.3, QKV
+// 10.3 / 14.8 / 16.0.  pi0_infer, one device, ms, launches -> here: 1 view 6.408 -> 6.259 (-> 6.18 with gemm_rows_body), 1 view + 7 tokens 6.640 -> 6.511,
 // 2 views 7.837 -> 7.752, 3 views 9.252 -> 9.061.  Not beyond 768 tokens: 816 tokens 9.867 -> 9.843 .. 9.89 with the tiles of that range
 // (256 x 256 for gate||up in two rounds, 192 x 256 for down).
 #include "attention_body.h"
@@ -23,7 +24,8 @@ namespace {
 
 constexpr int PL_THREADS = 256;
 
-// Variants by number of prefix tokens: 256, 257 .. 320, 512, 513 .. 576, 768.  Stream GEMMs: tile, parts of the
+// Variants by number of prefix tokens, with the full model's feed-forward: 193 .. 256, 257 .. 320, 385 .. 512, 513 .. 576, 641 .. 768 (what lies
+// between has other tiles and runs as launches; a narrower feed-forward sends fewer than 193 to the first one too).  Stream GEMMs: tile, parts of the
 // k range (two per wave where there are eight), stages in flight (the most that do not spill), groups of the row statistics' sum as
 // the launch has them, k16 steps of a part.
 template <int MB_, int NB_, int W_, int D_, int SG_, int NS_>

@@ -8,12 +8,12 @@
 // instructions, then 1.5 us from the last block's stores to everybody's first loads.  A launch spent 1.4 .. 2.0 us between the last
 // block of the one before and its first, and 3.1 .. 5.0 us until its first operands were there: arguments, code and weights cold.
 // Here weights wait in registers (the first stages) and in the die's L2 (the readers), code in the instruction cache.
-// Per operation with what lies between it and the next, us at 1 / 2 / 3 views, launches -> here:
-//   QKV        9.4 / 13.7 / 16.7 -> 6.5 / 8.9 / 11.8
-//   attention  6.6 /  8.5 /  9.8 -> 4.4 / 5.3 /  6.6
-//   O          6.5 /  8.0 /  8.9 -> 4.6 / 7.1 /  8.8
-//   up        11.5 / 17.9 / 20.9 -> 7.6 / 11.6 / 14.4   (launches: with the statistics' launch at 2 and 3 views)
-//   down      13.5 / 17.8 / 19.7 -> 11.5 / 17.6 / 18.9
+// Per operation with what lies between it and the next, us at 1 / 2 / 3 views, launches -> here (profiles/loop_timeline_prefill_full_pi0.txt):
+//   QKV        9.4 / 13.7 / 16.7 -> 6.1 / 8.9 / 11.8
+//   attention  6.6 /  8.5 /  9.8 -> 4.9 / 5.2 /  7.2
+//   O          6.5 /  8.0 /  8.9 -> 4.7 / 7.3 /  8.8
+//   up        11.5 / 17.9 / 20.9 -> 7.3 / 11.5 / 14.1   (launches: with the statistics' launch at 2 and 3 views)
+//   down      13.5 / 17.8 / 19.7 -> 11.3 / 17.2 / 18.1
 // pi0_infer 6605 / 8015 / 9395 us -> 6279 / 7645 / 8953.  Without the readers' L2 lines 6600 -> 6490 at 1 view on a slower device (then
 // the polls of a barrier return behind 2 us of cold weights); the die's tiles cut by tokens too, so that it reads half of the activations and
 // twice the weights: -20 .. +60 us.
