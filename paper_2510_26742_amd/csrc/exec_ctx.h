@@ -117,8 +117,10 @@ enum {
   GB_WORDS = GB_FLAGS + 8 * GB_MAX_BLOCKS
 };
 
-// TRACE: a timeline is recorded (a kernel of its own: the code for it in every operation costs instruction cache)
-template <bool TRACE>
+// TRACE: a timeline is recorded (a kernel of its own: the code for it in every operation costs instruction cache).  LEAN: no address of the
+// barrier's words stays in registers from one barrier to the next, for kernels with an operation that takes all there are (a spilled
+// address is a round trip in every barrier)
+template <bool TRACE, bool LEAN = false>
 struct GridBarrierT {
   unsigned* w;          // GB_WORDS words, zeroed before the launch
   unsigned xcc;         // die of this block
@@ -166,6 +168,12 @@ struct GridBarrierT {
     return spins > spin_limit || ((spins & 63u) == 0u && ld_dev(&w[GB_ERR]) != 0u);
   }
 
+  __device__ __forceinline__ static unsigned thread() {
+    unsigned t = threadIdx.x;
+    if (LEAN) asm volatile("" : "+v"(t));
+    return t;
+  }
+
   // all threads of the block, after the block's last store of the operation
   __device__ __forceinline__ void arrive() {
     // A block without a work item in an operation arrives without having waited for the operation before (flags and epochs
@@ -174,21 +182,22 @@ struct GridBarrierT {
                                                         // fence does not wait for them)
     __syncthreads();
     epoch++;
+    const unsigned t = thread();
     unsigned* const flags = w + GB_FLAGS + GB_MAX_BLOCKS * xcc;
-    if (threadIdx.x == 0) __hip_atomic_store(flags + rank, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (t == 0) __hip_atomic_store(flags + rank, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (leader) {
-      if (threadIdx.x < 64) {
+      if (t < 64) {
         unsigned spins = 0;
         while (true) {
           bool behind = false;
-          for (unsigned r = threadIdx.x; r < members; r += 64) behind |= ld_dev(flags + r) < epoch;
+          for (unsigned r = t; r < members; r += 64) behind |= ld_dev(flags + r) < epoch;
           if (__builtin_amdgcn_ballot_w64(behind) == 0ull) break;
           if (give_up(++spins)) {
-            if (threadIdx.x == 0) st_dev(&w[GB_ERR], 1u);
+            if (t == 0) st_dev(&w[GB_ERR], 1u);
             break;
           }
         }
-        if (threadIdx.x < 8) st_dev(&w[GB_DONE + 32 * threadIdx.x + xcc], epoch);
+        if (t < 8) st_dev(&w[GB_DONE + 32 * t + xcc], epoch);
       }
       __syncthreads();   // loads return in order per compute unit: no prefetch of the leader's other waves in front of its polls
     }
@@ -196,8 +205,9 @@ struct GridBarrierT {
 
   // all threads of the block: returns once every block has arrived at the barrier this block arrived at last
   __device__ __forceinline__ void wait() {
-    if (threadIdx.x < 8) {   // lane x reads what die x has told this die
-      const unsigned lane = threadIdx.x;
+    const unsigned t = thread();
+    if (t < 8) {   // lane x reads what die x has told this die
+      const unsigned lane = t;
       const bool counts = ((present >> lane) & 1u) != 0u;
       unsigned spins = 0;
       while (true) {
@@ -224,13 +234,13 @@ struct GridBarrierT {
 // That is only coherent if no cache of the reading die can hold an older copy of those addresses, which the caller
 // guarantees by giving every operation instance of the loop its own never-read buffers whose cache lines are each
 // written by one block only ("fresh" data path of the barrier experiment).
-template <bool BULK_CACHED, bool TRACE>
+template <bool BULK_CACHED, bool TRACE, bool LEAN = false>
 struct PersistCtxT {
   static constexpr bool kPersistent = true;
   int bx, by, bz;                  // work item of the current operation
   __amdgpu_buffer_rsrc_t arena;    // buffer resource over the activation arena
   const char* arena_base;
-  GridBarrierT<TRACE>* bar;
+  GridBarrierT<TRACE, LEAN>* bar;
   bool staged = false;             // weights of the item's first feature tile are in the body's shared memory already
   int thread;                      // threadIdx.x, made opaque per operation: per-lane address arithmetic of one operation
                                    // is then not hoisted out of the layer loop, where it would hold registers throughout

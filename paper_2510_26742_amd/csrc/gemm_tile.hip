@@ -14,6 +14,7 @@
 // loads in flight; their completion is counted here.
 // The other bound is what shared memory hands out: a step of (MT, NT) writes 2 (MT + NT) KiB and reads twice that, and loops whose
 // products do not fill the time run at 87 .. 99 bytes per clock of it.
+// Since it is power, rows that only fill a tile cost what others cost: gemm_cols_body has tiles of seven and nine blocks of 32 rows.
 // gate||up (32768 x 2048), cold weights, us, against the register-staged tiles of gemm.hip: 256 tokens 42.7 (47 - 51),
 // 304 48 (56), 512 65 (82), 768 100 (106), 816 124 (140).
 #include "pi0_internal.h"
@@ -28,6 +29,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   if (EPI == EPI_PARTIAL && p.range_per_die) cx = LaunchCtx{(int)blockIdx.x >> 3, (int)blockIdx.x & 7, 0};
   gemm_lds_body<MT, NT, 1, PRO, EPI, WALK>(p, cx, smem);
 }
+
+template <int H, int EPI>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_cols_kernel(GemmParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if (EPI == EPI_PARTIAL) gemm_cols_item<H, 1, EPI>(p, LaunchCtx{(int)blockIdx.x >> 3, (int)blockIdx.x & 7, 0}, smem);
+  else gemm_cols_item<H, 1, EPI>(p, LaunchCtx{(int)blockIdx.x, 0, 0}, smem);
+}
+// heights of gemm_cols_body in blocks of 32 rows, of gate||up and of down
+#define COLS_HEIGHTS(X) X(7, EPI_GEGLU) X(9, EPI_GEGLU) X(7, EPI_PARTIAL)
 
 // tiles (MT, NT): 256 x 128, 320 x 128, 192 x 256, 256 x 256 (tokens x features).  One token tile of 320 takes a view and its
 // prompt, one of 256 a view; four of 192 take three views.
@@ -81,12 +91,19 @@ hipError_t lds_tile_launch(hipStream_t s, GemmParams p, int z) {
   return hipGetLastError();
 }
 
+template <int H, int EPI>
+hipError_t cols_launch(hipStream_t s, GemmParams p) {
+  p.m_tiles = ceil_div(p.M, 32 * H);
+  const int total = ceil_div(p.n_tiles, COLS_TILES) * p.m_tiles;
+  gemm_cols_kernel<H, EPI><<<dim3(EPI == EPI_PARTIAL ? 8 * total : 8 * ceil_div(total, 8)), dim3(256), LT_SMEM, s>>>(p);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 bool gemm_lds_ok(int k_pad) { return k_pad % 128 == 0; }
 
-// Eight ranges, one for each die, unless the cost finds fewer better: at 816 tokens down and its reduction take 78 us with eight
-// (256 x 256 tiles) and 73 with six (192 x 256 in five token tiles).
+// Eight ranges, one for each die, unless the cost finds fewer better.
 // The line was drawn at 2048 features and k = 16384.  At other widths, pi0_prefill with as many ranges as the cost asks for up to 16, all dies
 // on all of them -> this, features x k, 256 .. 768 tokens: where the cost asked for more than eight (k 16384 and 32768) +11 .. -2 % in speed, 1024 x 16384
 // 685 / 773 / 972 / 1252 -> 692 / 710 / 915 / 1203 us at 256 / 263 / 512 / 768 tokens, 2048 x 32768 1412 / 1582 -> 1428 / 1611 at 256 / 263; with eight both
@@ -107,6 +124,9 @@ int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max) {
     LDS_TILES(X)
 #undef X
   }
+  // where eight ranges fit gemm_cols_body's height, they are the better choice (the same 1024 rows of k as above)
+  const int kps = round_up(ceil_div(k_pad, LDS_DIES), 128);
+  if (z_max >= LDS_DIES && kps >= 1024 && ceil_div(k_pad, kps) == LDS_DIES && gemm_cols_height(M, n_tiles, k_pad, kps, LDS_DIES, true) != 0) return LDS_DIES;
   return best_z;
 }
 
@@ -134,6 +154,28 @@ void gemm_lds_tile(int M, int n_tiles, int k_pad, int k_per_split, int z, bool p
 #undef X
 }
 
+// Height of gemm_cols_body's tiles where a compute unit then gets fewer products than with the tile of gemm_lds_tile (rounds of the chip's, or a
+// die's, blocks x products of a wave and step), else 0.  2048 features, k 2048 (gate||up) and 16384 (down), pi0_prefill in ms, gemm_lds_body -> this:
+//   513 .. 576 tokens  gate||up 2 x 12 -> 18:             515 4.67 -> 4.47, 533 4.77 -> 4.54, 560 4.79 -> 4.58
+//   769 .. 896         gate||up 2 x 16 -> 2 x 14:         771 6.09 -> 5.92, 816 6.26 -> 5.98
+//                      down, eight ranges, 16 -> 14:      771 5.91 -> 5.78, 816 5.99 -> 5.88 (six ranges of gemm_lds_body: 5.98)
+// Not up to 512 tokens: the persistent prefix has gemm_lds_body's tiles there.
+int gemm_cols_height(int M, int n_tiles, int k_pad, int k_per_split, int z, bool partial) {
+  if (M <= 512 || k_pad % (16 * COLS_GROUP) != 0 || k_per_split % (16 * COLS_GROUP) != 0 || (partial && z != LDS_DIES)) return 0;
+  const int units = partial ? 256 / LDS_DIES : 256;
+  int mt, nt;
+  gemm_lds_tile(M, n_tiles, k_pad, k_per_split, z, partial, &mt, &nt);
+  int best = 0, cost = ceil_div(ceil_div(M, 64 * mt) * ceil_div(n_tiles, 2 * nt), units) * mt * nt;
+#define X(H, EPI)                                                                                                       \
+  if (partial == (EPI == EPI_PARTIAL)) {                                                                                \
+    const int c = ceil_div(ceil_div(M, 32 * H) * ceil_div(n_tiles, COLS_TILES), units) * H * COLS_NT;                   \
+    if (c < cost) { cost = c; best = H; }                                                                               \
+  }
+  COLS_HEIGHTS(X)
+#undef X
+  return best;
+}
+
 hipError_t gemm_lds_init_attributes() {
   hipError_t e = hipSuccess;
 #define X(MT, NT)                                                                                                                       \
@@ -152,6 +194,10 @@ hipError_t gemm_lds_init_attributes() {
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, LT_SMEM);
   LDS_TILES(X)
 #undef X
+#define X(H, EPI)                                                                                                                          \
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_cols_kernel<H, EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, LT_SMEM);
+  COLS_HEIGHTS(X)
+#undef X
   return e;
 }
 
@@ -169,6 +215,11 @@ hipError_t launch_gemm_lds(hipStream_t s, int pro, int epi, const GemmParams& p,
   } else if (pro != PRO_NONE || epi != EPI_PARTIAL || p.out_f32 == nullptr) {
     return hipErrorInvalidValue;
   }
+  // (partial row statistics beyond 512 rows: only where pi0_tune leaves out the launch that adds them up)
+  const int height = epi == EPI_GEGLU && p.rowstat_parts > 1 ? 0 : gemm_cols_height(p.M, p.n_tiles, p.W.k_pad, p.k_per_split, z, epi == EPI_PARTIAL);
+#define X(H, EPI) if (height == H && epi == EPI) return cols_launch<H, EPI>(s, p);
+  COLS_HEIGHTS(X)
+#undef X
   int mt, nt;
   gemm_lds_tile(p.M, p.n_tiles, p.W.k_pad, p.k_per_split, z, epi == EPI_PARTIAL, &mt, &nt);
 #define X(MT, NT)                                                                                            \

@@ -478,3 +478,234 @@ __device__ __forceinline__ void gemm_rows_body(const GemmParams& p, const Cx& cx
     }
   }
 }
+
+// gate||up and down of more than 512 rows: H blocks of 32 rows, which the four waves share, and eight feature tiles, two to a wave.  A
+// wave's weights are nobody else's and go from memory straight into registers, a turn of the loop ahead; the activations go to LDS, four
+// stages of four k16 steps.  What it is for is the height: such a GEMM runs at the clock that the matrix cores' power leaves, so rows that
+// are only there to fill a tile cost as much as others, and H may be any number up to what the accumulators allow (nine blocks are 288 of a
+// lane's 512 registers; gemm_lds_body has none left at ten), with a lower body for the rows that are left over.  A step takes 5 H KiB through
+// LDS (gemm_lds_body 6 (MT + NT)).  At heights that gemm_lds_body has it is no quicker: prefill at 512 tokens 4.26 -> 4.28 ms, 768 5.43 -> 5.46.
+// An accumulator's order of k is gemm_lds_body's with several token tiles, so the bits are the same.
+// SG: as in gemm_lds_body.
+constexpr int COLS_STAGES = 4, COLS_KS = 4, COLS_GROUP = COLS_STAGES * COLS_KS;   // stages, k16 steps of a stage, of a turn
+constexpr int COLS_NT = 2, COLS_TILES = 4 * COLS_NT;                              // feature tiles of a wave, of a block
+constexpr int cols_smem(int H) { return COLS_STAGES * COLS_KS * H * 1024 + H * 32 * 4; }
+template <int H, int SG, int EPI, class Cx>
+__device__ __forceinline__ void gemm_cols_body(const GemmParams& p, const Cx& cx, unsigned char* smem, int nb, int m0) {
+  static_assert(EPI == EPI_GEGLU || EPI == EPI_PARTIAL, "RMS in front of the one, nothing in front of the other");
+  static_assert(cols_smem(H) <= LT_SMEM, "what the kernels ask for");
+  constexpr int W = 4, S = COLS_STAGES, KS = COLS_KS, G = COLS_GROUP, NT = COLS_NT, ROWS = H * 32;
+  constexpr bool STATS = EPI == EPI_GEGLU;
+  constexpr int SB = H * KS * 1024;                      // bytes of a stage: [row block][k16 step][1 KiB]
+  constexpr int RX = 8, AHEAD = H < 6 ? H : 6;           // activation fragments in registers, of them requested ahead of the products
+  static_assert(G * H % RX == 0 && AHEAD < RX, "what is read ahead is in a stage's last step");
+  float* const ssq = reinterpret_cast<float*>(smem + S * SB);   // [ROWS]
+  const int t = cx.tid();
+  const int lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lq = lane & 31;
+  const int lh = lane >> 5;
+  const int mb_last = (p.M - 1) >> 5;
+  const int KC16 = p.W.k_pad >> 4, XKC16 = p.ldx >> 4;
+  const int kbeg = EPI == EPI_PARTIAL ? cx.by * (p.k_per_split >> 4) : 0;
+  const int groups = ((EPI == EPI_PARTIAL ? min(kbeg + (p.k_per_split >> 4), KC16) : KC16) - kbeg) / G;
+
+  const char* wsrc[NT];
+#pragma unroll
+  for (int j = 0; j < NT; j++) wsrc[j] = reinterpret_cast<const char*>(p.W.w) + ((size_t)min(nb * COLS_TILES + w * NT + j, p.n_tiles - 1) * KC16 + kbeg) * 1024;
+  const char* xsrc[H];   // the wave requests k16 step w of every stage; blocks beyond the rows repeat the last one and are not stored
+#pragma unroll
+  for (int b = 0; b < H; b++) xsrc[b] = reinterpret_cast<const char*>(p.X) + ((size_t)min((m0 >> 5) + b, mb_last) * XKC16 + kbeg + w) * 1024;
+  const unsigned lds0 = lds_address(smem) + (unsigned)w * 1024u;
+  // stages 0 .. 3 of a group are at 4096 q - 4096 behind v, v + 8192: a 13-bit constant, which counts towards both addresses
+  unsigned voff = (unsigned)lane * 16u + 4096u;
+  auto request = [&](auto Q, auto B, unsigned v) {
+    constexpr int q = decltype(Q)::value, b = decltype(B)::value, off = q % 2 * 4096 - 4096;
+    const unsigned l0 = lds0;
+    const char* const s = xsrc[b];
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4" ::"s"(l0), "v"(v + (unsigned)(q / 2) * 8192u), "s"(s),
+                 "n"((q * H + b) * KS * 1024 - off), "n"(off)
+                 : "memory", "scc");
+  };
+  bf16x8 wr[G][NT];
+  auto pinned = [&]() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load_w = [&](int s, unsigned v) {
+#pragma unroll
+    for (int j = 0; j < NT; j++) wr[s][j] = *reinterpret_cast<const bf16x8*>(wsrc[j] + (v - 4096u) + s * 1024);
+  };
+  constexpr int EARLY = Cx::kPersistent ? G : 0;   // the weights are constant: ahead of the wait for the inputs
+  if constexpr (Cx::kPersistent) {
+#pragma unroll
+    for (int s = 0; s < EARLY; s++) load_w(s, voff);
+    pinned();
+    cx.wait_inputs();
+  }
+  // row statistics, of which RMS wants the sum of squares: whole-row sums, or planes of partial sums added in groups (a wave takes two)
+  constexpr int RR = (ROWS + 64 * W - 1) / (64 * W), RC = (ROWS + 63) / 64;
+  static_assert(SG == (STATS && Cx::kPersistent ? 2 * W : 1), "in the persistent kernel planes in groups, two for each wave");
+  float gv[SG > 1 ? 2 : 1][SG > 1 ? SG : 1][SG > 1 ? RC : RR];
+  const int parts = STATS ? p.rowstat_parts : 0;
+  if constexpr (SG > 1) {
+#pragma unroll
+    for (int g = 0; g < 2; g++)
+#pragma unroll
+      for (int j = 0; j < SG; j++)
+#pragma unroll
+        for (int c = 0; c < RC; c++)   // clamped, unconditional
+          gv[g][j][c] = cx.ld_bulk(p.rowstat + 2 * ((size_t)min(w + W * g + SG * j, parts - 1) * p.stat_rows + min(m0 + min(64 * c + lane, ROWS - 1), p.M - 1)) + 1);
+  } else if constexpr (STATS) {
+#pragma unroll
+    for (int i = 0; i < RR; i++) gv[0][0][i] = p.rowstat[2 * (size_t)min(m0 + min(t + i * 64 * W, ROWS - 1), p.M - 1) + 1];
+  }
+  pinned();
+  for_each<2>([&](auto Q) { for_each<H>([&](auto B) { request(Q, B, voff); }); });
+#pragma unroll
+  for (int s = EARLY; s < G; s++) load_w(s, voff);
+  pinned();
+  for_each<H>([&](auto B) { request(Int<2>{}, B, voff); });
+  if constexpr (SG > 1) {
+    float* const sums = reinterpret_cast<float*>(smem + (S - 1) * SB);   // [SG][ROWS], where the last stage will be
+#pragma unroll
+    for (int g = 0; g < 2; g++)
+#pragma unroll
+      for (int c = 0; c < RC; c++) {
+        float a = 0.f;
+#pragma unroll
+        for (int j = 0; j < SG; j++) a += w + W * g + SG * j < parts ? gv[g][j][c] : 0.f;
+        sums[(w + W * g) * ROWS + min(64 * c + lane, ROWS - 1)] = a;   // the last row's extra lanes store the same
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < RR; i++) {
+      const int r = min(t + i * 64 * W, ROWS - 1);
+      float a = sums[r];
+#pragma unroll
+      for (int g = 1; g < SG; g++) a += sums[g * ROWS + r];
+      ssq[r] = a;
+    }
+  } else if constexpr (STATS) {
+#pragma unroll
+    for (int i = 0; i < RR; i++) ssq[min(t + i * 64 * W, ROWS - 1)] = gv[0][0][i];
+  }
+
+  f32x16 acc[NT][H];
+#pragma unroll
+  for (int j = 0; j < NT; j++)
+#pragma unroll
+    for (int b = 0; b < H; b++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[j][b][r] = 0.f;
+  bf16x8 xf[RX];
+  // an LDS read reaches 64 KiB: a base for each (left alone, the compiler keeps an address in a register for every read beyond the first)
+  unsigned base[(S * SB + 65535) / 65536];
+#pragma unroll
+  for (int i = 0; i < (S * SB + 65535) / 65536; i++) {
+    base[i] = (unsigned)lane * 16u + (unsigned)i * 65536u;
+    asm volatile("" : "+v"(base[i]));
+  }
+  auto read = [&](int f) {   // fragment f of a group: k16 step f / H, row block f % H
+    const int s = f / H, b = f % H, at = ((s / KS * H + b) * KS + s % KS) * 1024;
+    xf[f % RX] = *reinterpret_cast<const bf16x8*>(smem + base[at >> 16] + (at & 65535));
+  };
+  // the first two stages are complete for everybody; the third one's requests and the other weights are behind them
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(H + (G - EARLY) * NT) : "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int f = 0; f < AHEAD; f++) read(f);
+
+  // One group of four stages; LAST: nothing beyond it is requested.  AHEAD products in front of a stage's end, where the next one is first
+  // read, that one must be complete for everybody, and everybody is through with the one before, whose place the stage three on takes.
+  // Behind the next stage's requests are, at least: those of one stage (LAST, from its second on: of none that it asked for itself) and
+  // the weights of seven steps, of which six are counted (LAST: of four, then none; three counted).  The first group
+  // finds its second stage complete, and behind the third one's requests the loads of its own six steps.
+  auto group = [&](auto last_group) {
+    constexpr bool LAST = decltype(last_group)::value != 0;
+    const unsigned vnext = voff + (unsigned)G * 1024u;
+    for_each<G * H>([&](auto FF) {
+      constexpr int f = decltype(FF)::value, s = f / H, b = f % H, q = s / KS, at = f - ((q + 1) * KS * H - AHEAD);
+      if constexpr (at == 0 && !(LAST && q == S - 1)) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(!LAST ? H + 12 : q == 0 ? H + 6 : q == 1 ? H : 0) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      if constexpr (!LAST || f + AHEAD < G * H) read((f + AHEAD) % (G * H));
+      if constexpr (at >= 0 && (!LAST || q == 0)) {
+        for_each<H>([&](auto B) {
+          if constexpr (decltype(B)::value * AHEAD / H == at) request(Int<(q + S - 1) % S>{}, B, q == 0 ? voff : vnext);
+        });
+      }
+#pragma unroll
+      for (int j = 0; j < NT; j++) {
+        // The ninth block's accumulators are ordinary vector registers, written down as such (the compiler keeps them all in the other
+        // half, 256 of a lane, and spills)
+        if constexpr (b < 8) acc[j][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[s][j], xf[f % RX], acc[j][b], 0, 0, 0);
+        else asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc[j][b]) : "v"(wr[s][j]), "v"(xf[f % RX]));
+        __builtin_amdgcn_sched_barrier(0);   // this order
+      }
+      if constexpr (!LAST && b == H - 1) {
+        load_w(s, vnext);
+        pinned();
+      }
+    });
+    voff = vnext;
+  };
+  for (int g = 0; g + 1 < groups; g++) group(Int<0>{});
+  group(Int<1>{});
+  if constexpr (H > 8) asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[0][8]), "+v"(acc[1][8]));   // products that the compiler does not know as such: written by now
+  if constexpr (EPI == EPI_PARTIAL) {   // whole tiles, see partial_tile_at; rows beyond the last are never read
+    const int mbs = (p.M + 31) >> 5;
+#pragma unroll
+    for (int b = 0; b < H; b++) {
+      const int mb = (m0 >> 5) + b;
+#pragma unroll
+      for (int j = 0; j < NT; j++) {
+        const int nt = nb * COLS_TILES + w * NT + j;
+        if (mb < mbs && nt < p.n_tiles) {   // uniform
+          float* const dst = p.out_f32 + (((size_t)cx.by * mbs + mb) * p.n_tiles + nt) * 1024 + lane * 4;
+#pragma unroll
+          for (int q = 0; q < 4; q++) cx.st(reinterpret_cast<f32x4*>(dst + q * 256), f32x4{acc[j][b][4 * q], acc[j][b][4 * q + 1], acc[j][b][4 * q + 2], acc[j][b][4 * q + 3]});
+        }
+      }
+    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < H; b++) {
+      const int row = b * 32 + lq, m = m0 + row;
+      if (m < p.M) {
+        const float sq = ssq[row];
+#pragma unroll
+        for (int j = 0; j < NT; j++) {
+          const int nt = nb * COLS_TILES + w * NT + j;
+          if (nt < p.n_tiles) {
+            EpiOps ops;
+            epilogue_preload<PRO_RMS, EPI_GEGLU>(p, nt, m, lh, ops, cx);
+            epilogue_tile<PRO_RMS, EPI_GEGLU>(p, acc[j][b], nt, m, lh, 0.f, sq, 0, ops, cx);
+          }
+        }
+      }
+    }
+  }
+}
+
+// Height of the rows that are left over: five blocks (769 .. 800 and 816 tokens behind three tiles of seven), eight (513 .. 544 behind one of nine)
+constexpr int cols_short(int H) { return H == 7 ? 5 : H - 1; }
+template <int H, int SG, int EPI, class Cx>
+__device__ __forceinline__ void gemm_cols_item(const GemmParams& p, const Cx& cx, unsigned char* smem) {
+  // tiles as in gemm_lds_body; partial sums: in order, a k range (cx.by) for each die
+  const int total = (p.n_tiles + COLS_TILES - 1) / COLS_TILES * p.m_tiles;
+  int first = 0, of_die = total, rank = cx.bx;
+  if (EPI != EPI_PARTIAL) {
+    lds_tile_share(cx.bx & 7, total, first, of_die);
+    rank = cx.bx >> 3;
+  }
+  if (rank >= of_die) return;
+  const int nb = (first + rank) / p.m_tiles, m0 = ((first + rank) - nb * p.m_tiles) * H * 32;
+  if (p.M - m0 <= cols_short(H) * 32) gemm_cols_body<cols_short(H), SG, EPI>(p, cx, smem, nb, m0);
+  else gemm_cols_body<H, SG, EPI>(p, cx, smem, nb, m0);
+}

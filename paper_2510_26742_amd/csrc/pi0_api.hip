@@ -806,14 +806,15 @@ int prefix_persistent(Run& r, int P, int stat_rows, int z, int k_per_split, Pref
       int mb, nb, parts;
       return gemm_stream_tile(pro, epi, P, pw.n_pad / 32, pw.k_pad, &mb, &nb, &parts, value_tile) && mb == s.mb && nb == s.nb && parts == s.parts && pw.k_pad == 16 * s.steps * s.parts;
     };
-    auto tile = [&](const auto& s, const PW& pw, int kps, int ranges, bool partial) {
+    auto tile = [&](int height, const auto& s, const PW& pw, int kps, int ranges, bool partial) {
+      if (gemm_cols_height(P, pw.n_pad / 32, pw.k_pad, kps, ranges, partial) != height) return false;
       int mt, nt;
       gemm_lds_tile(P, pw.n_pad / 32, pw.k_pad, kps, ranges, partial, &mt, &nt);
-      return mt == s.mt && nt == s.nt;
+      return height != 0 || (mt == s.mt && nt == s.nt);
     };
-    const int gu_rows = ceil_div(P, t.gu.mt * 64);
+    const int gu_rows = ceil_div(P, t.gu_tile_rows());
     if (stream(t.qkv, PRO_RMS, EPI_QKV, L0.qkv, P % 32 != 0 ? (d.H + 1) * 8 : 0) && stream(t.o, PRO_NONE, EPI_RESID, L0.o, 0) &&
-        tile(t.gu, L0.gu, L0.gu.k_pad, 1, false) && tile(t.dn, L0.down, k_per_split, z, true) && chunks <= t.att_chunks && (t.att_rows == 16) == (chunks <= 10) &&
+        tile(t.gu_height, t.gu, L0.gu, L0.gu.k_pad, 1, false) && tile(0, t.dn, L0.down, k_per_split, z, true) && chunks <= t.att_chunks && (t.att_rows == 16) == (chunks <= 10) &&
         (!t.gu_rows || (P <= 256 && L0.gu.k_pad % 256 == 0)) && t.o_groups == (P > 256 ? 8 : 1) && (!t.walk || PK_BLOCKS / 8 % gu_rows == 0))
       variant = v;
   }
@@ -853,9 +854,9 @@ int prefix_persistent(Run& r, int P, int stat_rows, int z, int k_per_split, Pref
   E.red.ldo = d.E; E.red.ldo2 = d.E;
   E.qkv.m_tiles = ceil_div(P, t.qkv.mb * 32);
   E.o.m_tiles = ceil_div(P, t.o.mb * 32);
-  E.gu.m_tiles = ceil_div(P, t.gu.mt * 64);
+  E.gu.m_tiles = ceil_div(P, t.gu_tile_rows());
   E.dn.m_tiles = ceil_div(P, t.dn.mt * 64);
-  E.gu_blocks = round_up(ceil_div(E.gu.n_tiles, 2 * t.gu.nt) * E.gu.m_tiles, 8);
+  E.gu_blocks = round_up(ceil_div(E.gu.n_tiles, t.gu_tile_features()) * E.gu.m_tiles, 8);
   E.dn_blocks = ceil_div(E.dn.n_tiles, 2 * t.dn.nt) * E.dn.m_tiles;
   if (!E.dn.range_per_die) E.dn_blocks = round_up(E.dn_blocks, 8);
   E.att_tiles = ceil_div(P, t.att_rows);

@@ -245,7 +245,8 @@ int gemm_stream_stat_planes(int pro, int M, int n_tiles, int k_pad);
 // token blocks, feature tiles and parts of the k range of the tile that launch_gemm_stream takes (value_tile: of QKV where M is no multiple
 // of 32, the feature tile that the values start at); false: none
 bool gemm_stream_tile(int pro, int epi, int M, int n_tiles, int k_pad, int* mb, int* nb, int* parts, int value_tile = 0);
-// the tile that launch_gemm_lds takes: 64 mt tokens x 64 nt features
+// the tile that launch_gemm_lds takes: 32 x gemm_cols_height tokens x 256 features, where that is 0 64 mt tokens x 64 nt features
+int gemm_cols_height(int M, int n_tiles, int k_pad, int k_per_split, int z, bool partial);
 void gemm_lds_tile(int M, int n_tiles, int k_pad, int k_per_split, int z, bool partial, int* mt, int* nt);
 // out[m] = (sum, sum of squares) of row m from partial statistics [planes][stat_rows][2]
 hipError_t launch_row_sums(hipStream_t s, const float* parts, int planes, int stat_rows, int M, float* out);

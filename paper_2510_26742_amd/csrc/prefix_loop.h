@@ -32,6 +32,9 @@ struct PrefixLoopParams {
 struct PrefixTiles {
   struct { int mb, nb, parts, steps; } qkv, o;   // gemm_stream_tile's; steps: k16 steps of a part
   struct { int mt, nt; } gu, dn;                 // gemm_lds_tile's
+  int gu_height;                                 // gemm_cols_height's of gate||up; not 0: instead of the tile gu
+  int gu_tile_rows() const { return gu_height != 0 ? 32 * gu_height : 64 * gu.mt; }
+  int gu_tile_features() const { return gu_height != 0 ? 8 : 2 * gu.nt; }   // of 32
   bool walk;                                     // gate||up: a block's tiles one after the other in the same rows
   int att_rows, att_chunks;                      // query rows of an attention item, most chunks of keys
   int o_groups;                                  // groups in which the planes of the O projection's row statistics are added

@@ -12,7 +12,7 @@
 // Per layer with what lies between it and the next operation, at 1 / 2 / 3 views, us (profiles/loop_timeline_prefill_full_pi0.txt): attention
 // 6.3 / 11.7 / 16.3, O 8.4 / 12.6 / 16.5, gate||up 38.6 (gemm_rows_body) / 59.7 / 90.7, down 26.0 / 40.6 / 54.4, its reduction 6.5 / 6.2 / 7.3, QKV
 // 10.3 / 14.8 / 16.0.  pi0_infer, one device, ms, launches -> here: 1 view 6.408 -> 6.259 (-> 6.18 with gemm_rows_body), 1 view + 7 tokens 6.640 -> 6.511,
-// 2 views 7.837 -> 7.752, 3 views 9.252 -> 9.061.  Not beyond 768 tokens: 816 tokens 9.867 -> 9.843 .. 9.89 with the tiles of that range
+// 2 views 7.837 -> 7.752, 3 views 9.252 -> 9.061; with gemm_cols_body for gate||up 515 tokens 8.25 -> 7.96, 560 tokens 8.37 -> 8.09.  Not beyond 768 tokens: 816 tokens 9.867 -> 9.843 .. 9.89 with the tiles of that range
 // (256 x 256 for gate||up in two rounds, 192 x 256 for down).
 #include "attention_body.h"
 #include "gemm_stream_body.h"
@@ -24,21 +24,23 @@ namespace {
 
 constexpr int PL_THREADS = 256;
 
-// Variants by number of prefix tokens, with the full model's feed-forward: 193 .. 256, 257 .. 320, 385 .. 512, 513 .. 576, 641 .. 768 (what lies
-// between has other tiles and runs as launches; a narrower feed-forward sends fewer than 193 to the first one too).  Stream GEMMs: tile, parts of the
+// Variants by number of prefix tokens, with the full model's feed-forward: 193 .. 256, 257 .. 320, 385 .. 512, 641 .. 768 and, the last one, 513 .. 576
+// (what lies between has other tiles and runs as launches; a narrower feed-forward sends fewer than 193 to the first one too, and 513 .. 576 to the
+// fourth where gate||up has no use for tiles of nine blocks: gemm_cols_height).  Stream GEMMs: tile, parts of the
 // k range (two per wave where there are eight), stages in flight (the most that do not spill), groups of the row statistics' sum as
 // the launch has them, k16 steps of a part.
 template <int MB_, int NB_, int W_, int D_, int SG_, int NS_>
 struct StreamOp { static constexpr int MB = MB_, NB = NB_, W = W_, V = W_ / 4, D = D_, SG = SG_, NS = NS_; };
 template <int MT_, int NT_>
 struct TileOp { static constexpr int MT = MT_, NT = NT_; };
-template <class QKV, class O, class GU, class DN, bool WALK_, int ATT_CM_, int O_GROUPS_, bool ROWS_ = false>
+template <class QKV, class O, class GU, class DN, bool WALK_, int ATT_CM_, int O_GROUPS_, bool ROWS_ = false, int GU_HEIGHT_ = 0>
 struct Variant {
   using Qkv = QKV;
   using Out = O;
   using Gu = GU;
   using Dn = DN;
   static constexpr bool WALK = WALK_, ROWS = ROWS_;   // ROWS: gemm_rows_body for gate||up
+  static constexpr int GU_HEIGHT = GU_HEIGHT_;        // not 0: gemm_cols_body for gate||up
   static constexpr int ATT_CM = ATT_CM_, O_GROUPS = O_GROUPS_;   // ATT_CM: 0: 16 query rows over at most 10 chunks, else 32 over at most 4 ATT_CM
 };
 template <int I> struct Variants;
@@ -47,7 +49,8 @@ template <> struct Variants<1> { using T = Variant<StreamOp<2, 2, 8, 8, 8, 16>, 
 template <> struct Variants<2> { using T = Variant<StreamOp<2, 3, 8, 5, 8, 16>, StreamOp<2, 2, 8, 6, 1, 16>, TileOp<4, 4>, TileOp<4, 2>, false, 4, 8>; };
 template <> struct Variants<3> { using T = Variant<StreamOp<2, 3, 8, 5, 8, 16>, StreamOp<3, 2, 8, 5, 1, 16>, TileOp<3, 4>, TileOp<5, 2>, false, 5, 8>; };
 template <> struct Variants<4> { using T = Variant<StreamOp<2, 4, 4, 8, 4, 32>, StreamOp<3, 2, 8, 5, 1, 16>, TileOp<3, 4>, TileOp<3, 4>, true, 6, 8>; };
-constexpr int VARIANTS = 5;
+template <> struct Variants<5> { using T = Variant<StreamOp<2, 3, 8, 5, 8, 16>, StreamOp<3, 2, 8, 5, 1, 16>, TileOp<0, 0>, TileOp<5, 2>, false, 5, 8, false, 9>; };
+constexpr int VARIANTS = 6;
 constexpr int ATT_EARLY = 5, ATT_RING = 12;
 
 constexpr int PREP_THREADS = 256;
@@ -62,10 +65,11 @@ __global__ __launch_bounds__(PREP_THREADS) void prefix_loop_prepare_kernel(Prefi
 template <int VARIANT>
 __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefix_loop_kernel(const PrefixLoopParams* __restrict__ params) {
   using C = typename Variants<VARIANT>::T;
-  using Cx = PersistCtxT<true, false>;
+  constexpr bool LEAN = C::GU_HEIGHT != 0;   // (gate||up takes every register)
+  using Cx = PersistCtxT<true, false, LEAN>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const ParamsPtr<PrefixLoopParams> Pg = (ParamsPtr<PrefixLoopParams>)params;
-  GridBarrierT<false> bar;
+  GridBarrierT<false, LEAN> bar;
   Cx cx;
   int layers;
   {
@@ -134,6 +138,8 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       if constexpr (C::ROWS) {
         static_assert(G::MT == 4 && G::NT == 2 && C::O_GROUPS == 1, "the same tile and order of the planes");
         for_items(F.gu_blocks, [&](int it) { gemm_rows_body(g, item(it, 0), smem_raw); });
+      } else if constexpr (C::GU_HEIGHT != 0) {
+        for_items(F.gu_blocks, [&](int it) { gemm_cols_item<C::GU_HEIGHT, C::O_GROUPS, EPI_GEGLU>(g, item(it, 0), smem_raw); });
       } else if constexpr (C::WALK) {
         gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, true>(g, item(blockIdx.x, 0), smem_raw);
       } else {
@@ -212,7 +218,7 @@ Kernel kernel_of() {
   using Q = typename C::Qkv;
   using O = typename C::Out;
   return Kernel{reinterpret_cast<const void*>(&prefix_loop_kernel<I>), smem_of<C>(),
-                PrefixTiles{{Q::MB, Q::NB, Q::W, Q::NS}, {O::MB, O::NB, O::W, O::NS}, {C::Gu::MT, C::Gu::NT}, {C::Dn::MT, C::Dn::NT}, C::WALK,
+                PrefixTiles{{Q::MB, Q::NB, Q::W, Q::NS}, {O::MB, O::NB, O::W, O::NS}, {C::Gu::MT, C::Gu::NT}, {C::Dn::MT, C::Dn::NT}, C::GU_HEIGHT, C::WALK,
                             C::ATT_CM == 0 ? 16 : 32, C::ATT_CM == 0 ? ATT_SHARE : 4 * C::ATT_CM, C::O_GROUPS, C::ROWS}};
 }
 Kernel kernel_for(int v) {
@@ -221,7 +227,8 @@ Kernel kernel_for(int v) {
     case 1: return kernel_of<1>();
     case 2: return kernel_of<2>();
     case 3: return kernel_of<3>();
-    default: return kernel_of<4>();
+    case 4: return kernel_of<4>();
+    default: return kernel_of<5>();
   }
 }
 
@@ -289,12 +296,13 @@ bool prefix_loop_takes(int variant, const PrefixLoopParams& P, int blocks) {
   if (P.gu.rowstat_parts != ceil_div(P.o.n_tiles, T.o.nb) || P.gu.rowstat_parts < 2) return false;
   if (P.o.ldo != E || P.o.ldo2 != E || P.o.n_valid != E || P.o.gain == nullptr || P.o.resid != P.o.out_f32 || !in_arena(P.o.out_f32, (size_t)M * E * 4)) return false;
   // gate||up and down
-  const int gu_total = ceil_div(P.gu.n_tiles, 2 * T.gu.nt) * P.gu.m_tiles, dn_total = ceil_div(P.dn.n_tiles, 2 * T.dn.nt) * P.dn.m_tiles;
-  if (P.gu.m_tiles != ceil_div(M, T.gu.mt * 64) || P.dn.m_tiles != ceil_div(M, T.dn.mt * 64) || P.gu_blocks != 8 * ceil_div(gu_total, 8) || P.dn_blocks != (P.dn.range_per_die ? dn_total : 8 * ceil_div(dn_total, 8))) return false;
+  const int gu_total = ceil_div(P.gu.n_tiles, T.gu_tile_features()) * P.gu.m_tiles, dn_total = ceil_div(P.dn.n_tiles, 2 * T.dn.nt) * P.dn.m_tiles;
+  if (P.gu.m_tiles != ceil_div(M, T.gu_tile_rows()) || P.dn.m_tiles != ceil_div(M, T.dn.mt * 64) || P.gu_blocks != 8 * ceil_div(gu_total, 8) || P.dn_blocks != (P.dn.range_per_die ? dn_total : 8 * ceil_div(dn_total, 8))) return false;
   if (P.gu.W.k_pad % 128 != 0 || P.gu.k_per_split != P.gu.W.k_pad || P.dn.k_per_split % 128 != 0 || P.dn.W.k_pad % 128 != 0 || P.red.Z < 1 || P.dn.range_per_die != (P.red.Z == LDS_DIES) ||
       P.dn.k_per_split % lds_tile_group(T.dn.mt, T.dn.nt) != 0 || (P.dn.W.k_pad - P.dn.k_per_split * (P.red.Z - 1)) % lds_tile_group(T.dn.mt, T.dn.nt) != 0 ||
       (long)P.dn.k_per_split * P.red.Z < P.dn.W.k_pad || (long)P.dn.k_per_split * (P.red.Z - 1) >= P.dn.W.k_pad)
     return false;
+  if (T.gu_height != 0 && P.gu.W.k_pad % (16 * COLS_GROUP) != 0) return false;
   if (T.gu_rows && (M > 256 || P.gu.W.k_pad % (16 * ROWS_GROUP) != 0 || P.gu.rowstat_parts > ROWS_PARTS)) return false;
   if (T.walk && ((blocks >> 3) % P.gu.m_tiles != 0)) return false;   // a block's tiles are in the same rows
   if (P.gu.ldo * 2 != P.gu.W.n_pad || P.dn.ldx != P.gu.ldo || P.dn.W.k_pad != P.gu.ldo) return false;
