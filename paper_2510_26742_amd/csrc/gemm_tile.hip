@@ -110,7 +110,7 @@ bool gemm_lds_ok(int k_pad) { return k_pad % 128 == 0; }
 // times (512 and 1024 x 2048 .. 8192) mostly +1 .. +7 %.  Slower by more than 2 % is only a range of less than 1024 that
 // keeps all units of a die busy, whose reduction then waits for the partial sums: 1024 x 4096 at 768 tokens 781 -> 825, 1280 x 4096 at 512
 // 718 -> 764, 768 x 4096 at 544 629 -> 645, 1024 x 6144 at 768 858 -> 882; next to them, 1280 x 4096 at 544, the same rule gains (809 -> 795).
-int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max) {
+int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max, bool cols) {
   int best_z = 1;
   float best = -1.f;
   for (int z = 1; z <= z_max && z <= LDS_DIES; z++) {
@@ -126,7 +126,7 @@ int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max) {
   }
   // where eight ranges fit gemm_cols_body's height, they are the better choice (the same 1024 rows of k as above)
   const int kps = round_up(ceil_div(k_pad, LDS_DIES), 128);
-  if (z_max >= LDS_DIES && kps >= 1024 && ceil_div(k_pad, kps) == LDS_DIES && gemm_cols_height(M, n_tiles, k_pad, kps, LDS_DIES, true) != 0) return LDS_DIES;
+  if (cols && z_max >= LDS_DIES && kps >= 1024 && ceil_div(k_pad, kps) == LDS_DIES && gemm_cols_height(M, n_tiles, k_pad, kps, LDS_DIES, true) != 0) return LDS_DIES;
   return best_z;
 }
 

@@ -1099,19 +1099,18 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
       memset(&q, 0, sizeof(q));
       q.X8 = c->ws + w.lx8; q.XS = c->ws + w.lx8s; q.ldx = d.E; q.M = P;
       q.W8 = c->ws + L.gu8; q.WS = c->ws + L.gu8s; q.n_pad = L.gu.n_pad; q.k_pad = L.gu.k_pad;
-      q.m_tiles = ceil_div(P, 128); q.k_per_split = L.gu.k_pad; q.k_true = d.E;
+      q.k_per_split = L.gu.k_pad; q.k_true = d.E;
       q.rowstat = at<float>(c, w.lstat);
       q.out8 = c->ws + w.lmid8; q.out_scales = c->ws + w.lmid8s; q.ldo8 = d.F;
       RUN(r, launch_gemm_mx(r.s, MX_EPI_GEGLU, q, 1));
       r.cls = PI0_OP_LLM_DOWN;
-      const int zmx = std::max(1, std::min(16, 256 / std::max(1, ceil_div(P, 128) * ceil_div(L.down.n_pad, 256))));
-      const int kps = round_up(ceil_div(L.down.k_pad, zmx), 256);
+      const int kps = gemm_mx_k_per_split(P, L.down.n_pad, L.down.k_pad);
       const int zeff = ceil_div(L.down.k_pad, kps);
       MxGemmParams u;
       memset(&u, 0, sizeof(u));
       u.X8 = c->ws + w.lmid8; u.XS = c->ws + w.lmid8s; u.ldx = d.F; u.M = P;
       u.W8 = c->ws + L.down8; u.WS = c->ws + L.down8s; u.n_pad = L.down.n_pad; u.k_pad = L.down.k_pad;
-      u.m_tiles = ceil_div(P, 128); u.k_per_split = kps; u.k_true = d.F;
+      u.k_per_split = kps; u.k_true = d.F;
       u.out_f32 = at<float>(c, w.part); u.ldo = L.down.n_pad;
       RUN(r, launch_gemm_mx(r.s, MX_EPI_PARTIAL, u, zeff));
       r.cls = PI0_OP_REDUCE;

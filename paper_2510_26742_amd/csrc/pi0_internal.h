@@ -212,7 +212,7 @@ struct MxGemmParams {
   const unsigned char* W8;   // weights, MX fragment order [n / 32][k / 64]
   const unsigned char* WS;   // their scales [n / 32][k / 256][64][4]
   int n_pad, k_pad;          // n_pad multiple of 256, k_pad multiple of 256
-  int m_tiles;               // 128-row tiles
+  int m_tiles;               // set by launch_gemm_mx
   int k_per_split;           // multiple of 256
   int k_true;                // divisor of the row statistics (GEGLU epilogue: RMS)
   const float* rowstat;      // [rows][2] whole-row (sum, sum of squares) of the fp32 input rows
@@ -223,8 +223,8 @@ struct MxGemmParams {
   int ldo8;
 };
 enum MxEpi { MX_EPI_PARTIAL = 0, MX_EPI_GEGLU = 1 };
-// 128 x 256 block tiles; grid = (n_pad / 256 rounded up to 8) x m_tiles blocks, z_splits in y
 hipError_t launch_gemm_mx(hipStream_t s, int epi, const MxGemmParams& p, int z_splits);
+int gemm_mx_k_per_split(int M, int n_pad, int k_pad);   // of the split GEMM: its best k range (a multiple of 256, no range empty)
 hipError_t gemm_mx_init_attributes();
 // weights -> MX fragments + scales (same row maps as launch_pack_weights)
 hipError_t launch_pack_weights_mx(hipStream_t s, const PackSrc& src, unsigned char* dst, unsigned char* scales, int n_pad, int k_pad);
@@ -237,7 +237,8 @@ hipError_t launch_gemm_stream(hipStream_t s, int pro, int epi, const GemmParams&
 hipError_t launch_gemm_lds(hipStream_t s, int pro, int epi, const GemmParams& p, int z_splits);
 bool gemm_lds_ok(int k_pad);                                             // TILE_LDS takes this contraction
 constexpr int LDS_DIES = 8;
-int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max);           // k ranges of a split-K launch
+// k ranges of a split-K launch; cols: gemm_cols_body is there for them
+int gemm_lds_splits(int M, int n_tiles, int k_pad, int z_max, bool cols = true);
 hipError_t gemm_lds_init_attributes();
 hipError_t gemm_stream_init_attributes();
 // planes of row statistics that the residual projection of this shape leaves (one per block column; 0: no such kernel)
