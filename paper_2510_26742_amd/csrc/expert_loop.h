@@ -12,8 +12,9 @@ struct ExpertLoopParams {
   struct {
     ActionEmbedArgs a;            // a.bias_k = row of step 0 (rows a.X floats apart)
     float* x_rw[2];               // x of the Euler integration [chunk][action_dim], inside the arena: a step reads what the one before
-                                  // wrote into the other buffer; [0] holds the actions at the end
+                                  // wrote into the other buffer
   } emb;
+  float* actions;                 // [x_elems] where the last step leaves x (the caller's buffer)
   const float* noise;             // [x_elems] initial x (staged input, constant during the kernel), inside the arena
   int x_elems;
   int layers, steps;
@@ -56,5 +57,26 @@ struct ExpertLoopParams {
 int expert_loop_smem_bytes();
 hipError_t expert_loop_init_attributes();
 hipError_t expert_loop_max_blocks_per_cu(int* out);
-// d_params: device memory for one ExpertLoopParams (16-byte aligned), written by a small launch ahead of the loop kernel
-hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLoopParams* d_params, int blocks);
+// Ranges of 32-bit words to be copied (a call's inputs to where its kernels read them)
+struct CopySeg { const uint32_t* src; uint32_t* dst; unsigned n; };
+struct CopyArgs { CopySeg seg[4]; int n; };
+__device__ __forceinline__ void copy_segment(const CopySeg& s, unsigned first, unsigned stride) {   // 16 bytes per lane where a segment's ends allow it
+  unsigned done = 0;
+  if (((reinterpret_cast<uintptr_t>(s.src) | reinterpret_cast<uintptr_t>(s.dst)) & 15) == 0) {
+    const uint4* src = reinterpret_cast<const uint4*>(s.src);
+    uint4* dst = reinterpret_cast<uint4*>(s.dst);
+    for (unsigned i = first; i < s.n / 4; i += stride) dst[i] = src[i];
+    done = s.n / 4 * 4;
+  }
+  for (unsigned i = done + first; i < s.n; i += stride) s.dst[i] = s.src[i];
+}
+inline unsigned copy_blocks(const CopyArgs& a) {   // of 256 threads, per segment
+  unsigned longest = 1;
+  for (int i = 0; i < a.n; i++) longest = a.seg[i].n > longest ? a.seg[i].n : longest;
+  return longest > 256u * 1024u ? 256u : (longest + 1023u) / 1024u;
+}
+// Two launches.  The first one, ahead of a call's other kernels: the call's inputs, the parameter block to d_params (device memory for one
+// ExpertLoopParams, 16-byte aligned) and the barrier words to zero.  Checks everything the loop's indexing assumes.
+hipError_t prepare_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLoopParams* d_params, int blocks, const CopyArgs& inputs);
+// The loop itself, with what was prepared.  dn_ns, trace: of the prepared block
+hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams* d_params, int dn_ns, bool trace, int blocks);

@@ -67,21 +67,28 @@ struct EulerCtx : PersistCtxT<true, TRACE> {
   float* lds;
   int first;      // element of x that comes first in LDS
   bool publish;
-  __device__ __forceinline__ EulerCtx(const PersistCtxT<true, TRACE>& c, const float* from_, float* to_, float* lds_, int first_, bool publish_)
-      : PersistCtxT<true, TRACE>(c), from(from_), to(to_), lds(lds_), first(first_), publish(publish_) {}
+  float* actions;   // not null: instead of `to`, and not for other blocks
+  __device__ __forceinline__ EulerCtx(const PersistCtxT<true, TRACE>& c, const float* from_, float* to_, float* lds_, int first_, bool publish_, float* actions_)
+      : PersistCtxT<true, TRACE>(c), from(from_), to(to_), lds(lds_), first(first_), publish(publish_), actions(actions_) {}
   using PersistCtxT<true, TRACE>::st;
   __device__ __forceinline__ void st(float* p, const float& v) const {
     const int i = (int)(p - from);
     lds[i - first] = v;
-    if (publish) PersistCtxT<true, TRACE>::st(to + i, v);
+    if (publish && actions != nullptr) actions[i] = v;
+    else if (publish) PersistCtxT<true, TRACE>::st(to + i, v);
   }
 };
 
-// parameter block to device memory and barrier words to zero (the error word, first, stays as it is).  A piece per thread,
-// both in one launch: the block copied by one thread took 7 us and the words a launch of their own.
+// parameter block to device memory and barrier words to zero (the error word, first, stays as it is), a piece per thread, and the call's
+// inputs.  Three launches before, with the copy of the actions that the loop now stores itself; pi0_denoise over two layers, one view, with the state token's
+// operation taken in as well 484.6 -> 482.1 us (a launch of that size costs 1 us between others, whatever its own 4.7 us in a trace)
 constexpr int PREP_THREADS = 256;
 static_assert(sizeof(ExpertLoopParams) % 4 == 0 && (GB_WORDS - GB_START) % 4 == 0, "whole pieces");
-__global__ __launch_bounds__(PREP_THREADS) void expert_loop_prepare_kernel(ExpertLoopParams P, ExpertLoopParams* dst, unsigned* sync) {
+__global__ __launch_bounds__(PREP_THREADS) void expert_loop_prepare_kernel(ExpertLoopParams P, ExpertLoopParams* dst, unsigned* sync, CopyArgs inputs) {
+  if (blockIdx.y != 0) {
+    copy_segment(inputs.seg[blockIdx.y - 1], blockIdx.x * PREP_THREADS + threadIdx.x, gridDim.x * PREP_THREADS);
+    return;
+  }
   const unsigned i = blockIdx.x * PREP_THREADS + threadIdx.x;
   if (i < sizeof(ExpertLoopParams) / 4) reinterpret_cast<unsigned*>(dst)[i] = reinterpret_cast<const unsigned*>(&P)[i];
   if (i < (GB_WORDS - GB_START) / 4) reinterpret_cast<uint4*>(sync + GB_START)[i] = uint4{0u, 0u, 0u, 0u};
@@ -148,17 +155,15 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
     return c;
   };
 
-  op_begin();
-  // ---- C0: state token -----------------------------------------------------------------------------
-  for_items((P.stok.X + 255) / 256, [&](int it) { state_token_body(P.stok, item(it, 0, 0)); });
-  op_end();
+  op_skip();   // C0, the state token, is part of the first embedding: an operation less in the chain
 
   const int emb_cols = (P.emb.a.X + 255) / 256;
   const int steps = P.steps, layers = P.layers;
   // ---- C9 of step k: final RMS -> out-projection (+bias), Euler update x <- x + dt * v; C1 of step k + 1: folded action/time
   // embedding + SiLU, suffix row 0 <- state token.  One operation: the 32 rows of x that hold a block's row are one item of
   // the out-projection, which every block computes for itself (64 KB behind the wait, as for QKV) and leaves in LDS; one block
-  // of each half also writes them out.  As two operations they were 3.4 + 0.6 + 3.1 us, ten times.  k = -1: the embedding alone.
+  // of each half also writes them out.  As two operations they were 3.4 + 0.6 + 3.1 us, ten times.  k = -1: the embedding alone, and in front of it
+  // C0, the state token, by the blocks that need it at once (their own columns of it).
   auto euler_embed = [&](int k) {
     const ExpertLoopParams& F = fresh<ExpertLoopParams>(Pg);
     const bool more = k + 1 < steps;
@@ -181,8 +186,12 @@ __global__ __launch_bounds__(PK_THREADS) void expert_loop_kernel(const ExpertLoo
       const PersistCtx c = item(bx, r, 0);
       ActionEmbedWeights e;
       if (more) action_embed_load(a, c, e);
+      if (k < 0 && !row) {
+        state_token_body(F.stok, c);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // it is where action_embed_finish reads it
+      }
       if (k >= 0 && row) {
-        gemm_skinny_body<PRO_RMS, EPI_EULER, 1>(u, EulerCtx<TRACE>(item(0, 0, half).template as<true>(), read, written, xs, (32 * half - 1) * a.A, publish), smem_raw);
+        gemm_skinny_body<PRO_RMS, EPI_EULER, 1>(u, EulerCtx<TRACE>(item(0, 0, half).template as<true>(), read, written, xs, (32 * half - 1) * a.A, publish, more ? nullptr : as_global(F.actions)), smem_raw);
       } else {
         bar.wait();
         if (row && c.thread < a.A) xs[((r + 1) & 31) * a.A + c.thread] = cx.ld(read + (size_t)r * a.A + c.thread);
@@ -358,7 +367,8 @@ hipError_t expert_loop_max_blocks_per_cu(int* out) {
 }
 
 // Host-side checks of everything the kernel's indexing assumes.
-hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLoopParams* d_params, int blocks) {
+hipError_t prepare_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLoopParams* d_params, int blocks, const CopyArgs& inputs) {
+  if (inputs.n < 0 || inputs.n > 4 || P.actions == nullptr) return hipErrorInvalidValue;
   if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0) return hipErrorInvalidValue;
   if (blocks < 1 || blocks > GB_MAX_BLOCKS || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.arena == nullptr || P.arena_bytes == 0 || P.spin_limit == 0)
     return hipErrorInvalidValue;
@@ -420,9 +430,13 @@ hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams& P, ExpertLo
   if (P.ring == nullptr || P.ring_stride % 256 != 0 || !in_arena(P.ring, P.ring_stride * (size_t)P.layers * P.steps)) return hipErrorInvalidValue;
   if (P.r_mid >= P.ring_stride || P.r_attn >= P.ring_stride) return hipErrorInvalidValue;
   constexpr int pieces = (int)sizeof(ExpertLoopParams) / 4 > (GB_WORDS - GB_START) / 4 ? (int)sizeof(ExpertLoopParams) / 4 : (GB_WORDS - GB_START) / 4;
-  hipLaunchKernelGGL(expert_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, P.sync);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const unsigned rows = (unsigned)ceil_div(pieces, PREP_THREADS), wide = copy_blocks(inputs);
+  hipLaunchKernelGGL(expert_loop_prepare_kernel, dim3(rows > wide ? rows : wide, 1 + inputs.n), dim3(PREP_THREADS), 0, s, P, d_params, P.sync, inputs);
+  return hipGetLastError();
+}
+
+hipError_t launch_expert_loop(hipStream_t s, const ExpertLoopParams* d_params, int dn_ns, bool trace, int blocks) {
+  if (d_params == nullptr || blocks < 1 || blocks > GB_MAX_BLOCKS) return hipErrorInvalidValue;
   void* args[] = {&d_params};
-  return hipLaunchKernel(kernels[(P.trace != nullptr ? 2 : 0) + (P.dn_ns == 16 ? 1 : 0)], dim3(blocks), dim3(PK_THREADS), args, expert_loop_smem_bytes(), s);
+  return hipLaunchKernel(kernels[(trace ? 2 : 0) + (dn_ns == 16 ? 1 : 0)], dim3(blocks), dim3(PK_THREADS), args, expert_loop_smem_bytes(), s);
 }

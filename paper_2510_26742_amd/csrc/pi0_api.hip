@@ -1207,12 +1207,11 @@ bool persistent_feasible(const pi0_ctx* c, int P) {
   return w.total - w.act_begin < ((size_t)1 << 32);   // offsets inside the arena are 32-bit
 }
 
-bool run_denoise_persistent(Run& r, int P) {
-  pi0_ctx* c = r.c;
+// Its parameters over the cache copy slot_r, the actions going to `actions`; of a shape that persistent_feasible takes
+void expert_loop_params(pi0_ctx* c, int P, int slot_r, float* actions, ExpertLoopParams& E) {
   const Dims& d = c->d;
   const WsLayout& w = c->wl;
   const Tune& T = c->tune;
-  if (!r.persistent_ok || r.timer != nullptr || !persistent_feasible(c, P)) return false;
   const int chunk = c->cfg.chunk;
   const int pchunks = ceil_div(P, 32);
   const ExpertShares es = expert_shares(c, pchunks);
@@ -1220,12 +1219,6 @@ bool run_denoise_persistent(Run& r, int P) {
   const WsTr& L0 = w.exp[0];
   const size_t wst = d.Le > 1 ? w.exp[1].qkv.w - w.exp[0].qkv.w : 0, gst = d.Le > 1 ? w.g_e1[1] - w.g_e1[0] : 0;
   const size_t arena_bytes = w.total - w.act_begin;
-  if (r.count_only) {
-    r.launches += 2;   // parameter block and barrier words, the loop kernel
-    return true;
-  }
-  if (!r.ok()) return true;
-  ExpertLoopParams E;
   memset(&E, 0, sizeof(E));
   float* xa = at<float>(c, w.xa);
   E.stok = StateTokenArgs{at<float>(c, w.st_state), d.SD, at<float>(c, w.state_w), at<float>(c, w.state_b), d.X, at<float>(c, w.stok), nullptr};
@@ -1233,6 +1226,7 @@ bool run_denoise_persistent(Run& r, int P) {
                             at<float>(c, w.y), at<bf16>(c, w.y_b), at<float>(c, w.g_e1[0]), at<float>(c, w.estat_parts)};
   E.emb.x_rw[0] = xa;
   E.emb.x_rw[1] = at<float>(c, w.xb);
+  E.actions = actions;
   E.noise = at<float>(c, w.st_noise);
   E.x_elems = chunk * d.A;
   E.layers = d.Le;
@@ -1276,8 +1270,8 @@ bool run_denoise_persistent(Run& r, int P) {
     memset(&a, 0, sizeof(a));
     a.q = at<bf16>(c, w.eq); a.q_head_stride = 2 * 16 * 512;
     a.Tq = 64; a.heads = d.H;
-    a.k0 = reinterpret_cast<bf16*>(c->ws + w.kcache + (size_t)r.slot_r * w.kcache_slot);
-    a.v0 = reinterpret_cast<bf16*>(c->ws + w.vcache + (size_t)r.slot_r * w.vcache_slot);
+    a.k0 = reinterpret_cast<bf16*>(c->ws + w.kcache + (size_t)slot_r * w.kcache_slot);
+    a.v0 = reinterpret_cast<bf16*>(c->ws + w.vcache + (size_t)slot_r * w.vcache_slot);
     a.chunks0 = pchunks; a.valid0 = P;
     a.k1 = at<bf16>(c, w.ek); a.v1 = at<bf16>(c, w.ev); a.chunks1 = 2;
     a.suffix_mask = 1;
@@ -1340,11 +1334,20 @@ bool run_denoise_persistent(Run& r, int P) {
   E.spin_limit = 1u << 20;
   E.trace = c->loop_trace;
   E.trace_ops = c->loop_trace_ops;
+}
+int expert_loop_blocks(int persist_blocks) { return persist_blocks > 0 ? persist_blocks : PK_BLOCKS; }
+// ahead of everything else that the call launches: its inputs, the parameter block, the barrier words
+hipError_t prepare_denoise_loop(pi0_ctx* c, hipStream_t s, int P, int slot_r, int persist_blocks, float* actions, const CopyArgs& inputs) {
+  ExpertLoopParams E;
+  expert_loop_params(c, P, slot_r, actions, E);
+  return prepare_expert_loop(s, E, at<ExpertLoopParams>(c, c->wl.eparams), expert_loop_blocks(persist_blocks), inputs);
+}
+bool run_denoise_persistent(Run& r, int P) {
+  pi0_ctx* c = r.c;
+  if (!r.persistent_ok || r.timer != nullptr || !persistent_feasible(c, P)) return false;
   r.cls = PI0_OP_MISC;
-  if (r.ok()) {
-    r.did(launch_expert_loop(r.s, E, at<ExpertLoopParams>(c, w.eparams), r.persist_blocks > 0 ? r.persist_blocks : PK_BLOCKS));
-    r.launches++;   // two launches: parameter block and barrier words, loop kernel
-  }
+  RUN(r, launch_expert_loop(r.s, at<ExpertLoopParams>(c, c->wl.eparams), c->wl.exp[0].down.k_pad == 4096 ? 16 : 8, c->loop_trace != nullptr, expert_loop_blocks(r.persist_blocks)));
+  r.launches++;   // two launches: the call's first one (prepare_denoise_loop), loop kernel
   return true;
 }
 
@@ -1592,24 +1595,10 @@ void run_denoise(Run& r, int P, Taps* taps) {
 
 // inputs -> static staging buffers (replayed graphs read constant addresses).  16 bytes per lane where a segment's ends
 // allow it: a view is 602 KB, and in 4-byte pieces on 64 blocks three of them took 13 us.
-struct CopySeg { const uint32_t* src; uint32_t* dst; unsigned n; };
-struct CopyArgs { CopySeg seg[4]; };
-__global__ __launch_bounds__(256) void copy_segments_kernel(CopyArgs a) {
-  const CopySeg s = a.seg[blockIdx.y];
-  const unsigned first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
-  unsigned done = 0;
-  if (((reinterpret_cast<uintptr_t>(s.src) | reinterpret_cast<uintptr_t>(s.dst)) & 15) == 0) {
-    const uint4* src = reinterpret_cast<const uint4*>(s.src);
-    uint4* dst = reinterpret_cast<uint4*>(s.dst);
-    for (unsigned i = first; i < s.n / 4; i += stride) dst[i] = src[i];
-    done = s.n / 4 * 4;
-  }
-  for (unsigned i = done + first; i < s.n; i += stride) s.dst[i] = s.src[i];
-}
+__global__ __launch_bounds__(256) void copy_segments_kernel(CopyArgs a) { copy_segment(a.seg[blockIdx.y], blockIdx.x * 256 + threadIdx.x, gridDim.x * 256); }
 
-hipError_t stage_inputs(pi0_ctx* c, hipStream_t s, const float* images, int n_views, const int32_t* ids, int n_prompt,
-                        const float* state, const float* noise, unsigned char* ebase = nullptr) {
-  Run where{c, s, false};   // only to say where the expert's scratch block is
+CopyArgs input_segments(pi0_ctx* c, const float* images, int n_views, const int32_t* ids, int n_prompt, const float* state, const float* noise, unsigned char* ebase = nullptr) {
+  Run where{c, nullptr, false};   // only to say where the expert's scratch block is
   where.ebase = ebase;
   CopyArgs a;
   memset(&a, 0, sizeof(a));
@@ -1626,11 +1615,17 @@ hipError_t stage_inputs(pi0_ctx* c, hipStream_t s, const float* images, int n_vi
     a.seg[n++] = CopySeg{reinterpret_cast<const uint32_t*>(noise), ex<uint32_t>(where, c->wl.st_noise),
                          (unsigned)(c->cfg.chunk * c->d.A)};
   }
-  if (n == 0) return hipSuccess;
-  unsigned longest = 0;
-  for (int i = 0; i < n; i++) longest = std::max(longest, a.seg[i].n);
-  hipLaunchKernelGGL(copy_segments_kernel, dim3(std::min(256u, (longest + 1023) / 1024), n), dim3(256), 0, s, a);
+  a.n = n;
+  return a;
+}
+hipError_t stage(hipStream_t s, const CopyArgs& a) {
+  if (a.n == 0) return hipSuccess;
+  hipLaunchKernelGGL(copy_segments_kernel, dim3(copy_blocks(a), a.n), dim3(256), 0, s, a);
   return hipGetLastError();
+}
+hipError_t stage_inputs(pi0_ctx* c, hipStream_t s, const float* images, int n_views, const int32_t* ids, int n_prompt, const float* state, const float* noise,
+                        unsigned char* ebase = nullptr) {
+  return stage(s, input_segments(c, images, n_views, ids, n_prompt, state, noise, ebase));
 }
 
 int fail_hip(pi0_ctx* c, hipError_t e) {
@@ -2095,10 +2090,13 @@ int pi0_denoise(pi0_ctx* c, const float* d_state, const float* d_noise, float* d
   if (c == nullptr || d_state == nullptr || d_noise == nullptr || d_actions == nullptr) return PI0_EINVAL;
   if (!c->loaded || c->cur_views == 0) return PI0_ESTATE;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  hipError_t e = stage_inputs(c, s, nullptr, 0, nullptr, 0, d_state, d_noise);
+  const int P = c->cur_views * c->d.T + c->cur_prompt;
+  const bool loop = persistent_feasible(c, P);
+  const CopyArgs inputs = input_segments(c, nullptr, 0, nullptr, 0, d_state, d_noise);
+  hipError_t e = loop ? prepare_denoise_loop(c, s, P, c->cur_slot, 0, d_actions, inputs) : stage(s, inputs);
   if (e != hipSuccess) return fail_hip(c, e);
   int rc = execute(c, KIND_DENOISE, c->cur_views, c->cur_prompt, s);
-  if (rc != PI0_OK) return rc;
+  if (rc != PI0_OK || loop) return rc;
   e = launch_copy_f32(s, at<float>(c, c->wl.xa), d_actions, (size_t)c->cfg.chunk * c->d.A);
   return e == hipSuccess ? PI0_OK : fail_hip(c, e);
 }
@@ -2133,7 +2131,10 @@ int pi0_infer(pi0_ctx* c, const float* d_images, int n_views, const int32_t* d_p
   if (!c->loaded) return PI0_ESTATE;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   c->cur_views = 0;
-  hipError_t e = stage_inputs(c, s, d_images, n_views, d_prompt_ids, n_prompt, d_state, d_noise);
+  const int P = n_views * c->d.T + n_prompt;
+  const bool loop = persistent_feasible(c, P);
+  const CopyArgs inputs = input_segments(c, d_images, n_views, d_prompt_ids, n_prompt, d_state, d_noise);
+  hipError_t e = loop ? prepare_denoise_loop(c, s, P, c->cur_slot, 0, d_actions, inputs) : stage(s, inputs);
   if (e != hipSuccess) return fail_hip(c, e);
   int rc = execute(c, KIND_INFER, n_views, n_prompt, s);
   if (rc != PI0_OK) return rc;
@@ -2143,6 +2144,7 @@ int pi0_infer(pi0_ctx* c, const float* d_images, int n_views, const int32_t* d_p
   }
   c->cur_views = n_views;
   c->cur_prompt = n_prompt;
+  if (loop) return PI0_OK;
   e = launch_copy_f32(s, at<float>(c, c->wl.xa), d_actions, (size_t)c->cfg.chunk * c->d.A);
   return e == hipSuccess ? PI0_OK : fail_hip(c, e);
 }
@@ -2173,7 +2175,10 @@ int pi0_stream_frame(pi0_ctx* c, const float* d_images, int n_views, const int32
   e = hipEventRecord(c->ev_prefill[nxt], sp);
   // denoise against the copy the previous frame filled
   if (e == hipSuccess) e = hipStreamWaitEvent(sd, c->ev_prefill[cur], 0);
-  if (e == hipSuccess) e = stage_inputs(c, sd, nullptr, 0, nullptr, 0, d_state, d_noise);
+  const int P = c->cur_views * c->d.T + c->cur_prompt, blocks = frame_loop_blocks(c, P);
+  const bool loop = blocks > 0 && persistent_feasible(c, P);
+  const CopyArgs inputs = input_segments(c, nullptr, 0, nullptr, 0, d_state, d_noise);
+  if (e == hipSuccess) e = loop ? prepare_denoise_loop(c, sd, P, cur, blocks, d_actions, inputs) : stage(sd, inputs);
   if (e != hipSuccess) return fail_hip(c, e);
   // The denoise of a frame is the persistent loop on a part of the chip (frame_loop_blocks): a resident block of the
   // loop holds a whole compute unit, so its grid is what shares the chip between the two streams - the prefill's blocks
@@ -2183,7 +2188,7 @@ int pi0_stream_frame(pi0_ctx* c, const float* d_images, int n_views, const int32
   // +1.2 ms); warm-up blocks inside the launches cost +0.2 .. +0.3 ms.
   rc = execute(c, KIND_DENOISE, c->cur_views, c->cur_prompt, sd, cur, cur, false);
   if (rc != PI0_OK) return rc;
-  e = launch_copy_f32(sd, at<float>(c, c->wl.xa), d_actions, (size_t)c->cfg.chunk * c->d.A);
+  if (!loop) e = launch_copy_f32(sd, at<float>(c, c->wl.xa), d_actions, (size_t)c->cfg.chunk * c->d.A);
   if (e == hipSuccess) e = hipEventRecord(c->ev_denoise[cur], sd);
   if (e != hipSuccess) return fail_hip(c, e);
   c->cur_slot = nxt;
