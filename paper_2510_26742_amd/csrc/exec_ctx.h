@@ -61,7 +61,7 @@ __device__ __forceinline__ float max_xor16(float v) {
 }
 
 struct LaunchCtx {
-  static constexpr bool kPersistent = false;
+  static constexpr bool kPersistent = false, kLean = false;
   int bx, by, bz;
   __device__ __forceinline__ static LaunchCtx from_block_idx() { return LaunchCtx{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z}; }
   template <class T>
@@ -237,6 +237,7 @@ struct GridBarrierT {
 template <bool BULK_CACHED, bool TRACE, bool LEAN = false>
 struct PersistCtxT {
   static constexpr bool kPersistent = true;
+  static constexpr bool kLean = LEAN;
   int bx, by, bz;                  // work item of the current operation
   __amdgpu_buffer_rsrc_t arena;    // buffer resource over the activation arena
   const char* arena_base;

@@ -145,9 +145,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
     for (int j = 0; j < NT; j++)
 #pragma unroll
-      for (int i = 0; i < MT; i++)
-#pragma unroll
-        for (int r = 0; r < 16; r++) acc[j][i][r] = 0.f;
+      for (int i = 0; i < MT; i++) zero_accumulator(acc[j][i]);
     i32x4 xf[2][MT][2], wf[2][NT][2];
     int sx[2][MT], sw[2][NT];
     constexpr int R = 2 * (MT + NT), P = MT * NT;   // reads and products of a step
