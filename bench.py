@@ -263,8 +263,8 @@ def main() -> int:
         log(f"[bench] {v} view(s): median {views_ms[str(v)]:.3f} ms")
 
     # stage split and per-class kernel durations at every view count: separate graphs for prefill and denoise; classes
-    # from HIP event pairs on the stream around eager launches (pi0_debug_profile, 3 passes), which is how pi0_prefill runs
-    # them; inside pi0_infer the vision tower's layers and the prefix's are one persistent kernel each (`vision_loop_kernel`,
+    # from HIP event pairs on the stream around eager launches (pi0_debug_profile, 3 passes);
+    # inside pi0_prefill and pi0_infer the vision tower's layers and the prefix's are one persistent kernel each (`vision_loop_kernel`,
     # `prefix_loop_kernel`), and the pass less the denoise is what they and the launches around them take.  The expert's
     # operations do not appear as classes: they are one persistent kernel (`expert_loop_kernel`) in both, whose launch is the
     # denoise figure.
@@ -340,7 +340,7 @@ def main() -> int:
                 "traffic_profile_commit": traffic_commit}
     log(f"[bench] expert_loop_kernel: {loop_bytes / 1e9:.3f} GB algorithmic in {denoise_ms[hv]:.3f} ms = {loop_gbps:.0f} GB/s "
         f"= {loop_gbps / 8000.0:.3f} of the HBM peak")
-    # prefill kernels by template family (eager, event-bracketed launches, as pi0_prefill runs them)
+    # prefill kernels by template family (eager, event-bracketed launches)
     timing_h = m.pi0_debug_profile(images_of[hv], hv, None, 0, state, noise, actions, passes=3, stream=stream)
     fam_traffic = (traffic_prof or {}).get("by_views", {}).get(str(hv), {}).get("families", {})
     krows = [r for r in roofline.kernel_rooflines(work, timing_h, None, prefix_tokens=hv * cfg.tokens_per_view)
@@ -483,9 +483,9 @@ def main() -> int:
         "attainable_peaks": {"hbm_read_GBps": round(peak_hbm, 1), "mfma_bf16_TFLOPs": round(peak_mfma, 1),
                              "l2_hit_read_GBps": round(peak_cache, 1),
                              "published": {"hbm_GBps": 8000.0, "mfma_bf16_TFLOPs": 2500.0}},
-        # the denoise loop's kernel, which the timed pass runs; then the prefill's operations as pi0_prefill launches them
+        # the denoise loop's kernel, which the timed pass runs; then the prefill's operations as pi0_debug_profile launches them
         # (operation_rows_of), where the timed pass has the persistent kernels of the vision tower and of the prefix
-        "operation_rows_of": "pi0_prefill", "persistent_kernels_of_pass": ["vision_loop_kernel", "prefix_loop_kernel", "expert_loop_kernel"],
+        "operation_rows_of": "pi0_debug_profile", "persistent_kernels_of_pass": ["vision_loop_kernel", "prefix_loop_kernel", "expert_loop_kernel"],
         "roofline_kernels": [dominant] + krows,
         "roofline_classes": class_rows[hv],
         # Section 5.2: ms for 1378 dependent updates; the paper's RTX 4090 figures for the same experiment; and the

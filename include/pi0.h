@@ -20,8 +20,10 @@
  *  - Every call only enqueues work on `hip_stream` (a hipStream_t, may be NULL for the default
  *    stream); results are valid after the caller synchronises that stream.  pi0_denoise / pi0_infer
  *    run the expert's loop as one persistent kernel of 256 blocks that must all be resident at once,
- *    and pi0_infer the vision tower (1 .. 3 views of 256 tokens) and the prefix's layers (bf16; with the full model's feed-forward
- *    193 .. 320, 385 .. 576 and 641 .. 768 tokens) as two more, at the full model's widths (launches otherwise, same bits):
+ *    and pi0_infer and pi0_prefill the vision tower (1 .. 3 views of 256 tokens) and the prefix's layers (bf16; with the full model's
+ *    feed-forward 193 .. 320, 385 .. 576 and 641 .. 768 tokens) as two more, at the full model's widths (launches otherwise, same bits).
+ *    pi0_prefill asks for no residency: its two kernels go on, after 100 us, with the blocks that are there, the fewer the slower
+ *    (a ctx that has had two-stream frames launches one kernel per operation):
  *    on a device with fewer than 256 compute units, or when the shape is outside what that kernel
  *    covers, the loop is issued as one launch per operation instead, together with one read-ahead
  *    kernel (it only loads the expert's weights ahead of the compute launches, Section 5.2) forked onto

@@ -17,6 +17,11 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
 
 // Sum over groups of 8 adjacent lanes with DPP (no LDS traffic): xor 1, xor 2 inside quads, then
 // the mirror inside each half row pairs quad 0 with quad 1.  Every lane of the group gets the sum.
+// v of this lane and of the one with bit 3 the other way: a rotation by half of the row of 16 (a shuffle goes through LDS, and the lane's number for it
+// stays in a register of a persistent kernel throughout)
+__device__ __forceinline__ float add_xor8(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xf, 0xf, true));
+}
 __device__ __forceinline__ float sum8_dpp(float v) {
   v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
   v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true));
@@ -760,8 +765,8 @@ __device__ __forceinline__ void tile_reduce_body(const ReduceParams& p, const Cx
       cx.st(reinterpret_cast<bf16x4*>(p.out_bf16 + xf_index(m, n, p.ldo2 >> 4)), bf16x4{(bf16)a[v][0], (bf16)a[v][1], (bf16)a[v][2], (bf16)a[v][3]});
     }
     if (p.stat_out != nullptr) {
-      sa = add_xor32(add_xor16(sa + __shfl_xor(sa, 8, 64)));
-      sb = add_xor32(add_xor16(sb + __shfl_xor(sb, 8, 64)));
+      sa = add_xor32(add_xor16(add_xor8(sa)));
+      sb = add_xor32(add_xor16(add_xor8(sb)));
       if ((t & 63) < 8) sred[t >> 6][r] = make_float2(sa, sb);
     }
   }

@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   };
   issue_first();
 
-  for (int next = rank + ((int)gridDim.x >> 3);; next += (int)gridDim.x >> 3) {
+  for (int next = rank + WALK_BLOCKS / 8;; next += WALK_BLOCKS / 8) {
     f32x16 acc[NT][MT];
 #pragma unroll
     for (int j = 0; j < NT; j++)
@@ -334,7 +334,7 @@ hipError_t mx_launch(hipStream_t s, MxGemmParams p, int z) {
   const int total = (p.n_pad >> 5) / (2 * NT) * p.m_tiles;
   if constexpr (EPI == MX_EPI_GEGLU && MT * NT <= 12) {   // (as in gemm_tile.hip; tiles of 256 x 256 spill)
     if (total > 256 && p.m_tiles > 1) {
-      gemm_mx_kernel<MT, NT, EPI, true><<<dim3(256), dim3(256), mx_smem(MT, NT), s>>>(p, 0);
+      gemm_mx_kernel<MT, NT, EPI, true><<<dim3(WALK_BLOCKS), dim3(256), mx_smem(MT, NT), s>>>(p, 0);
       return hipGetLastError();
     }
   }

@@ -82,7 +82,7 @@ hipError_t lds_tile_launch(hipStream_t s, GemmParams p, int z) {
   // alone 20 us faster, beside a denoise loop on half of the chip 9.50 -> 9.55 ms
   if constexpr (EPI == EPI_GEGLU && MT * NT <= 12) {
     if (total > 256 && p.m_tiles > 1 && p.rowstat_parts <= 1) {
-      gemm_lds_kernel<MT, NT, PRO, EPI, true><<<dim3(256), dim3(256), LT_SMEM, s>>>(p);
+      gemm_lds_kernel<MT, NT, PRO, EPI, true><<<dim3(WALK_BLOCKS), dim3(256), LT_SMEM, s>>>(p);
       return hipGetLastError();
     }
   }

@@ -35,6 +35,7 @@ __device__ __forceinline__ void zero_accumulator(f32x16& a) {
 }
 
 constexpr int lds_tile_stages(int MT, int NT) { return MT * NT <= 6 ? 8 : 4; }   // stages in LDS
+constexpr int WALK_BLOCKS = 256;               // that walk (WALK), a compute unit's each
 constexpr int LT_KC = 2;                       // k16 steps of a stage
 constexpr int lds_tile_group(int MT, int NT) { return 16 * LT_KC * lds_tile_stages(MT, NT); }   // of k, of a turn of the loop: k ranges are multiples of it
 
@@ -224,7 +225,7 @@ __device__ __forceinline__ void gemm_lds_body(const GemmParams& p, const Cx& cx,
   // places) are on their way during the epilogue.  The persistent kernel walks where the tiles of a block are in the same
   // rows, and keeps the statistics.
   int nb_now = nb, m0_now = m0;
-  for (int next = die_rank + ((int)gridDim.x >> 3);; next += (int)gridDim.x >> 3) {
+  for (int next = die_rank + WALK_BLOCKS / 8;; next += WALK_BLOCKS / 8) {
     f32x16 acc[NT][MT];
 #pragma unroll
     for (int j = 0; j < NT; j++)

@@ -3,14 +3,25 @@
 #include "exec_ctx.h"
 #include "pi0_internal.h"
 
-// block: this block's place in the order in which the operation's items are handed out
+// block: this block's place in the order in which the operation's items are handed out; blocks: that take part
 template <class F>
-__device__ __forceinline__ void for_items(int n_items, F&& f, int block = (int)blockIdx.x) {
+__device__ __forceinline__ void for_items(int n_items, F&& f, int block = (int)blockIdx.x, int blocks = (int)gridDim.x) {
   bool first = true;
-  for (int it = block; it < n_items; it += (int)gridDim.x) {
+  for (int it = block; it < n_items; it += blocks) {
     if (!first) __syncthreads();   // shared memory of the item before is free
     f(it);
     first = false;
+  }
+}
+
+// The same for an operation with an item for every block of the grid, of which usually each takes one: block < N
+template <int N, class F>
+__device__ __forceinline__ void for_all_items(F&& f, int block, int blocks) {
+  for (int it = block;;) {
+    f(it);
+    it += blocks;
+    if (__builtin_expect(it >= N, 1)) break;
+    __syncthreads();   // shared memory of the item before is free
   }
 }
 

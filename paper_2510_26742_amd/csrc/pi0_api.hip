@@ -447,6 +447,7 @@ struct Tune {
   // the vision tower of pi0_infer as one persistent kernel (1) or as launches (0)
   int pvl = 1;
   int ppl = 1;            // the same for the prefix's layers
+  int pmb = 256;          // most of their blocks that take part (fewer: as where other work holds compute units, for tests)
   // two-stream frames: blocks of the persistent loop beside the prefill (0: per-operation launches).  A resident block
   // of the loop holds a whole compute unit, so its grid decides how the chip is shared between the two streams
   int psb = -1;           // -1: from the number of prefix tokens (frame_loop_blocks)
@@ -498,7 +499,8 @@ struct Run {
                                 // blocks inside the launches with pi0_tune "ras=0"); false: neither
   int cls = PI0_OP_MISC;        // class of the launches that follow
   OpTimer* timer = nullptr;     // when set, every RUN / RUN_GEMM launch is bracketed by an event pair
-  bool prefill_loops = false;   // the vision tower and the prefix may run as one persistent kernel each (plain pi0_infer calls)
+  bool prefill_loops = false;   // the vision tower and the prefix may run as one persistent kernel each (plain pi0_prefill / pi0_infer calls)
+  bool resident = false;        // ... whose blocks may wait for all of the grid (pi0_infer, whose denoise loop asks for the chip as well)
   bool persistent_ok = false;   // the denoise loop may run as one persistent kernel (plain pi0_denoise / pi0_infer calls)
   int persist_blocks = 0;       // its grid (0: one block per compute unit)
   unsigned char* ebase = nullptr;   // where the expert's scratch block lives minus its workspace offset (null: in the workspace)
@@ -743,6 +745,7 @@ bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_ro
   E.r_q = w.rv_q; E.r_k = w.rv_k; E.r_v = w.rv_v; E.r_attn = w.rv_attn; E.r_mid = w.rv_mid;
   E.sync = at<unsigned>(c, w.vsync);
   E.spin_limit = 1u << 20;
+  E.most_blocks = r.resident && T.pmb == PK_BLOCKS ? 0u : (unsigned)T.pmb;
   if (!vision_loop_takes(n_views, E, PK_BLOCKS)) return false;
   r.cls = PI0_OP_MISC;
   RUN(r, launch_vision_loop(r.s, n_views, E, at<VisionLoopParams>(c, w.vparams), PK_BLOCKS));
@@ -873,6 +876,7 @@ int prefix_persistent(Run& r, int P, int stat_rows, int z, int k_per_split, Pref
   E.arena_bytes = (unsigned)arena_bytes;
   E.sync = at<unsigned>(c, w.psync);
   E.spin_limit = 1u << 20;
+  E.most_blocks = r.resident && T.pmb == PK_BLOCKS ? 0u : (unsigned)T.pmb;
   return prefix_loop_takes(variant, E, PK_BLOCKS) ? variant : -1;
 }
 
@@ -1656,6 +1660,9 @@ int frame_loop_blocks(const pi0_ctx* c, int P) {
 // Runs `kind` either through a cached graph or eagerly.
 int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int slot_w = -1, int slot_r = -1, bool read_ahead = true) {
   const int P = n_views * c->d.T + n_prompt;
+  // Not beside the denoise of a two-stream frame: the loops' buffers lie where the expert's do, and that denoise may still be on its
+  // way when the next plain prefill comes on the other stream
+  const bool prefill_loops = kind == KIND_INFER || (kind == KIND_PREFILL && c->ev_prefill[0] == nullptr);
   if (slot_w < 0) slot_w = c->cur_slot;
   if (slot_r < 0) slot_r = c->cur_slot;
   // the second stream of the read-ahead kernel exists only where the per-operation launches will use it (a stream
@@ -1675,12 +1682,13 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     // two-stream frames: per-operation launches, or the loop on a part of the chip (the prefill's blocks need compute units too)
     r.persist_blocks = read_ahead ? 0 : frame_loop_blocks(c, P);
     r.persistent_ok = read_ahead || r.persist_blocks > 0;
-    r.prefill_loops = kind == KIND_INFER;
+    r.prefill_loops = prefill_loops;
+    r.resident = kind == KIND_INFER;
     body(r);
     return r.ok() ? PI0_OK : fail_hip(c, r.err);
   }
   GraphKey key{kind, n_views, n_prompt, kind == KIND_DENOISE ? 0 : slot_w, kind == KIND_PREFILL ? 0 : slot_r,
-               kind == KIND_DENOISE ? 0 : c->precision, kind == KIND_PREFILL ? 0 : (int)read_ahead};
+               kind == KIND_DENOISE ? 0 : c->precision, kind == KIND_PREFILL ? (int)prefill_loops : (int)read_ahead};
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
     hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
@@ -1692,7 +1700,8 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     // two-stream frames: per-operation launches, or the loop on a part of the chip (the prefill's blocks need compute units too)
     r.persist_blocks = read_ahead ? 0 : frame_loop_blocks(c, P);
     r.persistent_ok = read_ahead || r.persist_blocks > 0;
-    r.prefill_loops = kind == KIND_INFER;
+    r.prefill_loops = prefill_loops;
+    r.resident = kind == KIND_INFER;
     body(r);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(s, &g);
@@ -1844,7 +1853,7 @@ int pi0_tune(pi0_ctx* c, const char* env) {
         {"zld", &c->tune.zld, 1, Z_MAX}, {"zvd", &c->tune.zvd, 1, Z_MAX},
         {"pfq", &c->tune.pfq, 0, 1024}, {"pfa", &c->tune.pfa, 0, 1024}, {"pfo", &c->tune.pfo, 0, 1024},
         {"pfd", &c->tune.pfd, 0, 1024}, {"ae16", &c->tune.ae16, 0, 1}, {"ksplit", &c->tune.ksplit, 0, 1}, {"kcps", &c->tune.kcps, 2, 16}, {"qms", &c->tune.qms, 0, 1},
-        {"ppl", &c->tune.ppl, 0, 1}, {"fko", &c->tune.fko, 0, 1}, {"fkl", &c->tune.fkl, 0, 1}, {"ras", &c->tune.ras, 0, 4096}, {"ral", &c->tune.ral, 1, 8}, {"rat", &c->tune.rat, 64, 256}, {"rad", &c->tune.rad, 1, 8 /* 7: no such variant, see below */}, {"avs", &c->tune.avs, 1, 8}, {"pdn", &c->tune.pdn, 0, 1}, {"pra", &c->tune.pra, 0, 63}, {"psb", &c->tune.psb, -1, 256}, {"pvl", &c->tune.pvl, 0, 1}};
+        {"ppl", &c->tune.ppl, 0, 1}, {"pmb", &c->tune.pmb, 1, 256}, {"fko", &c->tune.fko, 0, 1}, {"fkl", &c->tune.fkl, 0, 1}, {"ras", &c->tune.ras, 0, 4096}, {"ral", &c->tune.ral, 1, 8}, {"rat", &c->tune.rat, 64, 256}, {"rad", &c->tune.rad, 1, 8 /* 7: no such variant, see below */}, {"avs", &c->tune.avs, 1, 8}, {"pdn", &c->tune.pdn, 0, 1}, {"pra", &c->tune.pra, 0, 63}, {"psb", &c->tune.psb, -1, 256}, {"pvl", &c->tune.pvl, 0, 1}};
     for (auto& k : keys) {
       const char* f = strstr(env, k.key);
       while (f != nullptr && !((f == env || f[-1] == ',') && f[strlen(k.key)] == '=')) f = strstr(f + 1, k.key);

@@ -26,6 +26,7 @@ struct PrefixLoopParams {
   const char* arena;              // everything that blocks exchange lies in [arena, arena + arena_bytes)
   unsigned arena_bytes;
   unsigned spin_limit;            // bound of one barrier wait, in polls
+  unsigned most_blocks;           // that take part at most (GridBarrierT::init_some); 0: all, which are resident
 };
 
 // What a variant of the kernel is built for, to be compared with the launches' own choices for the shape

@@ -22,7 +22,8 @@
 
 namespace {
 
-constexpr int PL_THREADS = 256;
+constexpr int PL_THREADS = 256, PREFIX_LOOP_BLOCKS = 256;
+static_assert(PREFIX_LOOP_BLOCKS == WALK_BLOCKS, "gate||up walks with as many");
 
 // Variants by number of prefix tokens, with the full model's feed-forward: 193 .. 256, 257 .. 320, 385 .. 512, 641 .. 768 and, the last one, 513 .. 576
 // (what lies between has other tiles and runs as launches; a narrower feed-forward sends fewer than 193 to the first one too, and 513 .. 576 to the
@@ -71,11 +72,11 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
   const ParamsPtr<PrefixLoopParams> Pg = (ParamsPtr<PrefixLoopParams>)params;
   GridBarrierT<false, LEAN> bar;
   Cx cx;
-  int layers;
+  int layers, first, blocks;
   {
     const PrefixLoopParams& P = fresh<PrefixLoopParams>(Pg);
     layers = P.layers;
-    bar.init(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == 31);
+    if (!bar.init_some(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == 31, P.most_blocks, reinterpret_cast<unsigned*>(smem_raw), first, blocks)) return;
     cx.arena = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(P.arena), 0, (int)P.arena_bytes, 0x00020000);
     cx.arena_base = P.arena;
   }
@@ -90,6 +91,8 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
     c.thread = t;
     return c;
   };
+  auto each = [&](int n_items, auto&& f) { for_items(n_items, f, first, blocks); };   // this block's items
+  auto each_block = [&](auto&& f) { for_all_items<PREFIX_LOOP_BLOCKS>(f, first, blocks); };
   auto moved = [](const auto* p, size_t bytes) { return reinterpret_cast<decltype(p)>(reinterpret_cast<const char*>(p) + bytes); };
 
   for (int l = 0; l < layers; l++) {
@@ -102,12 +105,12 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       a.v0 = moved(as_global(a.v0), (size_t)l * F.vcache_stride);
       a.out = reinterpret_cast<bf16*>(slot + F.r_attn);
       const int tiles = F.att_tiles;
-      if ((int)blockIdx.x < tiles * a.heads) {
-        const Cx c = item((int)blockIdx.x % tiles, (int)blockIdx.x / tiles);
+      each(tiles * a.heads, [&](int it) {
+        const Cx c = item(it % tiles, it / tiles);
         c.wait_inputs();
         if constexpr (C::ATT_CM == 0) attention_prefix16_body(a, c, smem_raw);
         else attention_prefix32_body<C::ATT_CM, ATT_EARLY, ATT_RING>(a, c, smem_raw);
-      }
+      });
       bar.arrive();
     }
     {  // ---- O projection + residual -----------------------------------------------------------------
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       o.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_xb_o);
       o.stat_out = reinterpret_cast<float*>(slot + F.r_st_o);
       using O = typename C::Out;
-      gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, 1, O::NS, PRO_NONE, EPI_RESID>(o, item(blockIdx.x, 0), smem_raw);
+      each_block([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, 1, O::NS, PRO_NONE, EPI_RESID>(o, item(it, 0), smem_raw); });
       bar.arrive();
     }
     {  // ---- RMS -> gate||up, fused gate -------------------------------------------------------------
@@ -137,13 +140,13 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       using G = typename C::Gu;
       if constexpr (C::ROWS) {
         static_assert(G::MT == 4 && G::NT == 2 && C::O_GROUPS == 1, "the same tile and order of the planes");
-        for_items(F.gu_blocks, [&](int it) { gemm_rows_body(g, item(it, 0), smem_raw); });
+        each(F.gu_blocks, [&](int it) { gemm_rows_body(g, item(it, 0), smem_raw); });
       } else if constexpr (C::GU_HEIGHT != 0) {
-        for_items(F.gu_blocks, [&](int it) { gemm_cols_item<C::GU_HEIGHT, C::O_GROUPS, EPI_GEGLU>(g, item(it, 0), smem_raw); });
+        each(F.gu_blocks, [&](int it) { gemm_cols_item<C::GU_HEIGHT, C::O_GROUPS, EPI_GEGLU>(g, item(it, 0), smem_raw); });
       } else if constexpr (C::WALK) {
-        gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, true>(g, item(blockIdx.x, 0), smem_raw);
+        each_block([&](int it) { gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, true>(g, item(it, 0), smem_raw); });
       } else {
-        for_items(F.gu_blocks, [&](int it) { gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, false>(g, item(it, 0), smem_raw); });
+        each(F.gu_blocks, [&](int it) { gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, false>(g, item(it, 0), smem_raw); });
       }
       bar.arrive();
     }
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       using G = typename C::Dn;
       const int gx = F.dn_blocks, z = F.red.Z;
       const bool ranges = d.range_per_die != 0;
-      for_items(gx * z, [&](int it) {
+      each(gx * z, [&](int it) {
         gemm_lds_body<G::MT, G::NT, 1, PRO_NONE, EPI_PARTIAL, false>(d, ranges ? item(it >> 3, it & 7) : item(it % gx, it / gx), smem_raw);
       });
       bar.arrive();
@@ -174,7 +177,7 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       r.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_xb_d);
       r.stat_out = reinterpret_cast<float*>(slot + F.r_st_d);
       const int rows = (r.M + 7) >> 3;
-      for_items(rows * PREFIX_QKV_PLANES, [&](int it) {
+      each(rows * PREFIX_QKV_PLANES, [&](int it) {
         tile_reduce_body<PL_THREADS>(r, item(it % rows, it / rows), reinterpret_cast<float2 (*)[8]>(smem_raw));
       });
       bar.arrive();
@@ -192,7 +195,7 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       q.kfrag = reinterpret_cast<bf16*>(reinterpret_cast<char*>(q.kfrag) + (size_t)(l + 1) * F.kcache_stride);
       q.vfrag = reinterpret_cast<bf16*>(reinterpret_cast<char*>(q.vfrag) + (size_t)(l + 1) * F.vcache_stride);
       using O = typename C::Qkv;
-      gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, PREFIX_QKV_PLANES, O::NS, PRO_RMS, EPI_QKV, true>(q, item(blockIdx.x, 0), smem_raw);
+      each_block([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, PREFIX_QKV_PLANES, O::NS, PRO_RMS, EPI_QKV, true>(q, item(it, 0), smem_raw); });
       bar.arrive();
     }
   }
@@ -262,7 +265,7 @@ hipError_t prefix_loop_max_blocks_per_cu(int* out) {
 bool prefix_loop_takes(int variant, const PrefixLoopParams& P, int blocks) {
   if (variant < 0 || variant >= VARIANTS) return false;
   const PrefixTiles T = prefix_loop_tiles(variant);
-  if (blocks < 8 || blocks > GB_MAX_BLOCKS || blocks % 8 != 0 || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.spin_limit == 0)
+  if (blocks != PREFIX_LOOP_BLOCKS || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.spin_limit == 0)
     return false;
   if (P.layers < 1 || P.ring == nullptr || (reinterpret_cast<uintptr_t>(P.ring) & 255) != 0 || P.ring_stride % 256 != 0 || P.arena == nullptr || P.arena_bytes == 0 ||
       P.layer_stride % 16 != 0 || P.gain_stride % 16 != 0 || P.kcache_stride % 16 != 0 || P.vcache_stride % 16 != 0)
@@ -304,7 +307,7 @@ bool prefix_loop_takes(int variant, const PrefixLoopParams& P, int blocks) {
     return false;
   if (T.gu_height != 0 && P.gu.W.k_pad % (16 * COLS_GROUP) != 0) return false;
   if (T.gu_rows && (M > 256 || P.gu.W.k_pad % (16 * ROWS_GROUP) != 0 || P.gu.rowstat_parts > ROWS_PARTS)) return false;
-  if (T.walk && ((blocks >> 3) % P.gu.m_tiles != 0)) return false;   // a block's tiles are in the same rows
+  if (T.walk && (WALK_BLOCKS / 8 % P.gu.m_tiles != 0)) return false;   // a block's tiles are in the same rows
   if (P.gu.ldo * 2 != P.gu.W.n_pad || P.dn.ldx != P.gu.ldo || P.dn.W.k_pad != P.gu.ldo) return false;
   if (P.red.M != M || P.red.N != E || P.red.ldp != E || P.red.ldo != E || P.red.ldo2 != E || P.red.part != P.dn.out_f32 || P.red.out_f32 != P.o.out_f32 ||
       P.red.resid != P.o.out_f32 || P.red.bias != nullptr || P.red.gain == nullptr || P.red.out8 != nullptr || !in_arena(P.red.part, (size_t)P.red.Z * chunks * 32 * E * 4))

@@ -26,6 +26,7 @@ struct VisionLoopParams {
   unsigned* sync;                 // GB_WORDS words, words >= GB_START zeroed before the launch
   const char* arena;              // the ring and the residual stream lie in [arena, arena + arena_bytes)
   unsigned arena_bytes;
+  unsigned most_blocks;           // that take part at most (GridBarrierT::init_some); 0: all, which are resident
   unsigned spin_limit;            // bound of one barrier wait, in polls
 };
 

@@ -54,7 +54,7 @@ template <> struct Cfg<3> {
 
 // Blocks 27 .. 30 of each die, which have no item but at two views in the attention (27 blocks a die are the most that the GEMMs use),
 // read the weights of the operations ahead into the die's L2.  Block 31 leads the die's barrier.
-constexpr int READER_RANK = 27, LEADER_RANK = 31;
+constexpr int READER_RANK = 27, LEADER_RANK = 31, VISION_LOOP_BLOCKS = 8 * (LEADER_RANK + 1);
 
 template <class O, int EPI>
 constexpr int op_smem() { return stream_body_smem<O::MB, O::NB, O::W, O::SG, EPI>(); }
@@ -84,11 +84,11 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
   const ParamsPtr<VisionLoopParams> Pg = (ParamsPtr<VisionLoopParams>)params;
   GridBarrierT<false> bar;
   Cx cx;
-  int layers;
+  int layers, first, blocks;
   {
     const VisionLoopParams& P = fresh<VisionLoopParams>(Pg);
     layers = P.layers;
-    bar.init(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == LEADER_RANK);   // (no item but at two views in the attention)
+    if (!bar.init_some(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == LEADER_RANK, P.most_blocks, reinterpret_cast<unsigned*>(smem_raw), first, blocks)) return;   // (no item but at two views in the attention)
     cx.arena = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(P.arena), 0, (int)P.arena_bytes, 0x00020000);
     cx.arena_base = P.arena;
   }
@@ -117,12 +117,24 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
       const Cx c = item(it / a.heads, it % a.heads);
       c.wait_inputs();
       attention_view_body<C::WAVES, C::QT>(a, c, smem_raw);
-    });
+    }, first, blocks);
     bar.arrive();
   };
 
+  // the columns of the up projection's output that only pad the down projection's k
+  auto clear_padding = [&](int l, int begin, int step) {
+    const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
+    const int kc16 = F.down.ldx >> 4, pad16 = (F.down.ldx - F.up.n_valid) >> 4;
+    char* const mid = as_global(F.ring) + ((size_t)l * F.ring_stride + F.r_mid);
+    for (int mb = begin; mb < F.down.M >> 5; mb += step) {
+      for (int i = (int)threadIdx.x; i < pad16 * 64; i += 64 * C::WAVES)
+        cx.st(reinterpret_cast<u32x4_t*>(mid + ((size_t)(mb + 1) * kc16 - pad16) * 1024u + (unsigned)i * 16u), u32x4_t{0u, 0u, 0u, 0u});
+    }
+  };
+
   const int rank = (int)blockIdx.x >> 3;
-  if (rank >= READER_RANK && rank < LEADER_RANK) {
+  const bool all = blocks == VISION_LOOP_BLOCKS;   // fewer than all of the grid share the items of all and read nothing ahead
+  if (all && rank >= READER_RANK && rank < LEADER_RANK) {
     unsigned fold = 0;
     for (int op = 0; op < 5 * layers; op++) {   // QKV, attention, O, up, down
       const int l = op / 5, k = op - l * 5;
@@ -132,15 +144,7 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
           continue;
         }
       }
-      if (k == 0 && rank == READER_RANK) {   // the columns of the up projection's output that only pad the down projection's k
-        const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
-        const int kc16 = F.down.ldx >> 4, pad16 = (F.down.ldx - F.up.n_valid) >> 4;
-        char* const mid = as_global(F.ring) + ((size_t)l * F.ring_stride + F.r_mid);
-        for (int mb = (int)blockIdx.x & 7; mb < F.down.M >> 5; mb += 8) {
-          for (int i = (int)threadIdx.x; i < pad16 * 64; i += 64 * C::WAVES)
-            cx.st(reinterpret_cast<u32x4_t*>(mid + ((size_t)(mb + 1) * kc16 - pad16) * 1024u + (unsigned)i * 16u), u32x4_t{0u, 0u, 0u, 0u});
-        }
-      }
+      if (k == 0 && rank == READER_RANK) clear_padding(l, (int)blockIdx.x & 7, 8);
       bar.arrive();   // nobody waits for what is read here
       // QKV, attention: up.  O, up: down.  Down: the next layer's QKV and O, and where the attention leaves no time to read a part of its up
       for (int i = 0; i < (k < 4 ? 1 : l + 1 == layers ? 0 : C::READERS_ATTEND ? 3 : 2); i++) {
@@ -167,6 +171,7 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
   }
 
   for (int l = 0; l < layers; l++) {
+    if (!all) clear_padding(l, first, blocks);
     {  // ---- LN -> QKV, keys and values in the attention's fragment order ----------------------------
       const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
       GemmParams q = global(F.qkv);
@@ -184,7 +189,7 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
         q.rowstat = reinterpret_cast<const float*>(slot - F.ring_stride + F.r_st_d);
       }
       using O = typename C::Qkv;
-      gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, C::PARTS, O::NS, PRO_LN, EPI_QKV>(q, item(blockIdx.x, 0), smem_raw);
+      for_all_items<VISION_LOOP_BLOCKS>([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, C::PARTS, O::NS, PRO_LN, EPI_QKV>(q, item(it, 0), smem_raw); }, first, blocks);
       bar.arrive();
     }
     attention(l);
@@ -208,7 +213,7 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
         __builtin_assume(o.bias != nullptr && o.gain != nullptr && o.resid != nullptr);
         o.out_bf16 = reinterpret_cast<bf16*>(slot + (second ? F.r_xb_d : F.r_xb_o));
         o.stat_out = reinterpret_cast<float*>(slot + (second ? F.r_st_d : F.r_st_o));
-        gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, 1, 0, PRO_NONE, EPI_RESID>(o, item(blockIdx.x, 0), smem_raw);
+        for_all_items<VISION_LOOP_BLOCKS>([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, 1, 0, PRO_NONE, EPI_RESID>(o, item(it, 0), smem_raw); }, first, blocks);
         bar.arrive();
       }
       if (second) break;
@@ -225,7 +230,7 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
         u.rowstat = reinterpret_cast<const float*>(slot + F.r_st_o);
         u.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_mid);
         using U = typename C::Up;
-        gemm_stream_body<U::MB, U::NB, U::W, U::V, U::D, U::SG, C::PARTS, U::NS, PRO_LN, EPI_BF16>(u, item(blockIdx.x, 0), smem_raw);
+        for_all_items<VISION_LOOP_BLOCKS>([&](int it) { gemm_stream_body<U::MB, U::NB, U::W, U::V, U::D, U::SG, C::PARTS, U::NS, PRO_LN, EPI_BF16>(u, item(it, 0), smem_raw); }, first, blocks);
         bar.arrive();
       }
     }
@@ -281,7 +286,7 @@ hipError_t vision_loop_max_blocks_per_cu(int* out) {
 bool vision_loop_takes(int views, const VisionLoopParams& P, int blocks) {
   VisionTiles T;
   if (!vision_loop_tiles(views, &T)) return false;
-  if (blocks != 8 * (LEADER_RANK + 1) || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.spin_limit == 0) return false;
+  if (blocks != VISION_LOOP_BLOCKS || P.sync == nullptr || (reinterpret_cast<uintptr_t>(P.sync) & 15) != 0 || P.spin_limit == 0) return false;
   if (P.layers < 1 || P.ring == nullptr || (reinterpret_cast<uintptr_t>(P.ring) & 255) != 0 || P.ring_stride % 256 != 0 ||
       P.arena == nullptr || P.arena_bytes == 0 || P.ring < P.arena || P.ring + P.ring_stride * (size_t)P.layers > P.arena + P.arena_bytes || P.layer_stride % 16 != 0 || P.gain_stride % 16 != 0)
     return false;

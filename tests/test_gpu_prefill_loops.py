@@ -1,0 +1,96 @@
+"""pi0_prefill runs the vision tower and the prefix's layers as the persistent kernels of pi0_infer, which go on with the blocks that are resident:
+the cache that it leaves gives the bits of the launches (pvl=0, ppl=0) with every number of blocks that takes part, at tile edges of every
+variant, and beside a kernel of another context that holds the chip."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_26742_amd import synth
+from tests.test_gpu_parity import Case, say
+
+CFG = dataclasses.replace(synth.reduced_config(vocab=64), vis_layers=2, llm_layers=3, exp_layers=3, max_prompt=64)
+SHAPES = [(1, 0), (1, 7), (1, 64), (2, 0), (2, 21), (2, 64), (3, 0)]   # a shape of every variant, and its last one where that is ragged
+
+
+def prefill_and_denoise(case, img, st, nz, ids):
+    d_img, d_st, d_nz, d_ids = case.to_dev(img, st, nz, ids)
+    d_act = torch.empty((case.cfg.chunk, case.cfg.action_dim), dtype=torch.float32, device=case.dev)
+    case.m.pi0_prefill(d_img, img.shape[0], d_ids, len(ids), case.stream)
+    case.m.pi0_denoise(d_st, d_nz, d_act, case.stream)
+    case.stream.synchronize()
+    return d_act.cpu().numpy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("graphs", [True, False])
+def test_any_number_of_blocks_gives_the_launches_bits(graphs):
+    case = Case(CFG)
+    try:
+        case.m.pi0_set_graph_mode(graphs)
+        for n_views, n_prompt in SHAPES:
+            img, st, nz, ids = case.inputs(n_views, n_prompt)
+            case.m.pi0_tune("pvl=0,ppl=0,pmb=256")
+            want = prefill_and_denoise(case, img, st, nz, ids)
+            for blocks in (256, 255, 216, 97, 1):
+                say(f"[gpu] prefill loops, {n_views} views + {n_prompt}, {blocks} blocks, graphs={graphs}")
+                case.m.pi0_tune(f"pvl=1,ppl=1,pmb={blocks}")
+                np.testing.assert_array_equal(prefill_and_denoise(case, img, st, nz, ids), want)
+                assert np.isnan(prefill_and_denoise(case, np.full_like(img, np.nan), st, nz, ids)).all()
+                np.testing.assert_array_equal(prefill_and_denoise(case, img, st, nz, ids), want)
+                np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+        case.m.pi0_device_status(case.stream)   # raises if a bounded wait ran out
+    finally:
+        case.close()
+
+
+@pytest.mark.gpu
+def test_prefill_beside_another_contexts_denoise():
+    """Both contexts' kernels ask for the whole chip.  The denoise waits for all of its blocks, the prefill's loops for none that does not come."""
+    a, b = Case(CFG), Case(CFG, seed=1)
+    try:
+        ia, ib = a.inputs(1, 0), b.inputs(2, 21)
+        want_a, want_b = prefill_and_denoise(a, *ia), prefill_and_denoise(b, *ib)
+        d_img, d_st, d_nz, d_ids = b.to_dev(*ib)
+        _, a_st, a_nz, _ = a.to_dev(*ia)
+        act_a = [torch.empty((CFG.chunk, CFG.action_dim), device=a.dev) for _ in range(6)]
+        for i in range(6):
+            say(f"[gpu] prefill beside a denoise, pass {i}")
+            a.m.pi0_denoise(a_st, a_nz, act_a[i], a.stream)
+            b.m.pi0_prefill(d_img, 2, d_ids, 21, b.stream)
+        a.stream.synchronize()
+        b.stream.synchronize()
+        act_b = torch.empty((CFG.chunk, CFG.action_dim), device=b.dev)
+        b.m.pi0_denoise(d_st, d_nz, act_b, b.stream)
+        b.stream.synchronize()
+        for act in act_a:
+            np.testing.assert_array_equal(act.cpu().numpy(), want_a)
+        np.testing.assert_array_equal(act_b.cpu().numpy(), want_b)
+        a.m.pi0_device_status(a.stream)
+        b.m.pi0_device_status(b.stream)
+    finally:
+        a.close()
+        b.close()
+
+
+@pytest.mark.gpu
+def test_prefill_after_frames():
+    """Once a context has had two-stream frames its plain prefill is launches again: a frame's denoise may still be on its way on the other stream."""
+    case = Case(CFG)
+    try:
+        img, st, nz, ids = case.inputs(1, 7)
+        want = prefill_and_denoise(case, img, st, nz, ids)
+        side = torch.cuda.Stream(device=case.dev)
+        d_img, d_st, d_nz, d_ids = case.to_dev(img, st, nz, ids)
+        act = [torch.empty((CFG.chunk, CFG.action_dim), device=case.dev) for _ in range(3)]
+        for i in range(3):
+            case.m.pi0_stream_frame(d_img, 1, d_ids, 7, d_st, d_nz, act[i], case.stream, side)
+            case.m.pi0_prefill(d_img, 1, d_ids, 7, case.stream)
+        case.stream.synchronize()
+        side.synchronize()
+        for a in act:
+            np.testing.assert_array_equal(a.cpu().numpy(), want)
+        np.testing.assert_array_equal(prefill_and_denoise(case, img, st, nz, ids), want)
+    finally:
+        case.close()

@@ -1,4 +1,4 @@
-"""The prefix of pi0_infer runs as one persistent kernel with grid barriers; pi0_prefill launches its operations one by one.  Both add up
+"""The prefix of pi0_infer and pi0_prefill runs as one persistent kernel with grid barriers; with ppl=0 its operations are launched one by one.  Both add up
 every sum in the same order, so they agree bit for bit: at both ends of every range of prefix tokens that has a variant of its own, inside it
 and next to it, and whatever a replay before left in the kernel's buffers.  (The launches are compared with the oracle in
 test_gpu_parity.py.)"""

@@ -1,4 +1,4 @@
-"""The vision tower of pi0_infer runs as one persistent kernel with grid barriers; pi0_prefill launches its operations one by one.  Both
+"""The vision tower of pi0_infer and pi0_prefill runs as one persistent kernel with grid barriers; with pvl=0 its operations are launched one by one.  Both
 add up every sum in the same order, so they agree bit for bit, whatever the number of views and whatever a replay before left in the
 kernel's buffers.  (The launches are compared with the oracle in test_gpu_parity.py.)"""
 import dataclasses
