@@ -11,7 +11,8 @@
  * prefix layer only produces keys/values), Section 4.2 (fused gated MLP) and Section 4.4 (norm
  * statistics applied after accumulation) are done inside the library at load time / in kernels.
  * Section 3.1's graph replay: pi0_prefill / pi0_denoise / pi0_infer record their kernel
- * sequence into a HIP graph on first use of a shape and replay it afterwards.
+ * sequence into a HIP graph on first use of a shape and replay it afterwards; a sequence of no more than 16 kernels,
+ * which is what the persistent kernels below leave of most, is launched as it is.
  *
  * Conventions
  *  - Every pointer named d_* is a DEVICE pointer (HIP global memory), row-major, contiguous.
@@ -164,7 +165,7 @@ int pi0_denoise(pi0_ctx* ctx, const float* d_state, const float* d_noise, float*
 int pi0_denoise_static(pi0_ctx* ctx, const float* d_state, const float* d_noise, float* d_actions,
                        void* hip_stream);
 
-/* pi0_prefill followed by pi0_denoise as one graph launch. */
+/* pi0_prefill followed by pi0_denoise as one sequence of kernels. */
 int pi0_infer(pi0_ctx* ctx, const float* d_images, int n_views, const int32_t* d_prompt_ids,
               int n_prompt, const float* d_state, const float* d_noise, float* d_actions,
               void* hip_stream);

@@ -1632,6 +1632,12 @@ hipError_t stage_inputs(pi0_ctx* c, hipStream_t s, const float* images, int n_vi
   return stage(s, input_segments(c, images, n_views, ids, n_prompt, state, noise, ebase));
 }
 
+void destroy_graphs(pi0_ctx* c) {
+  for (auto& kv : c->graphs) {
+    if (kv.second != nullptr) (void)hipGraphExecDestroy(kv.second);
+  }
+  c->graphs.clear();
+}
 int fail_hip(pi0_ctx* c, hipError_t e) {
   c->last_hip = (int)e;
   return PI0_EHIP;
@@ -1657,7 +1663,12 @@ int frame_loop_blocks(const pi0_ctx* c, int P) {
   return P <= 384 ? 160 : 128;
 }
 
-// Runs `kind` either through a cached graph or eagerly.
+// Calls of at most this many kernels are launched one by one in graph mode too: a replay begins 8 us later than a kernel (pi0_denoise over two layers 480 us by
+// graph, 471 by launches; pi0_infer over two 708 and 701, over eighteen 6271 and 6250, 11 kernels), and up to here the host spends
+// no longer on the launches than on the replay (11 kernels 32 us either way; 118 kernels 400 and 65).
+constexpr int DIRECT_LAUNCHES = 16;
+
+// Runs `kind` through a cached graph (null in the map: launches), or eagerly.
 int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int slot_w = -1, int slot_r = -1, bool read_ahead = true) {
   const int P = n_views * c->d.T + n_prompt;
   // Not beside the denoise of a two-stream frame: the loops' buffers lie where the expert's do, and that denoise may still be on its
@@ -1674,8 +1685,8 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     if (kind == KIND_PREFILL || kind == KIND_INFER) run_prefill(r, n_views, n_prompt, nullptr);
     if (kind == KIND_DENOISE || kind == KIND_INFER) run_denoise(r, P, nullptr);
   };
-  if (!c->graph_mode || s == nullptr) {   // the legacy default stream cannot be captured
-    Run r{c, s, false};
+  auto fresh_run = [&](hipStream_t stream, bool count_only) {
+    Run r{c, stream, count_only};
     r.slot_w = slot_w;
     r.slot_r = slot_r;
     r.read_ahead = read_ahead;
@@ -1684,24 +1695,26 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     r.persistent_ok = read_ahead || r.persist_blocks > 0;
     r.prefill_loops = prefill_loops;
     r.resident = kind == KIND_INFER;
+    return r;
+  };
+  auto launch = [&]() {
+    Run r = fresh_run(s, false);
     body(r);
     return r.ok() ? PI0_OK : fail_hip(c, r.err);
-  }
+  };
+  if (!c->graph_mode || s == nullptr) return launch();   // the legacy default stream cannot be captured
   GraphKey key{kind, n_views, n_prompt, kind == KIND_DENOISE ? 0 : slot_w, kind == KIND_PREFILL ? 0 : slot_r,
                kind == KIND_DENOISE ? 0 : c->precision, kind == KIND_PREFILL ? (int)prefill_loops : (int)read_ahead};
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
+    Run count = fresh_run(nullptr, true);
+    body(count);
+    if (count.launches <= DIRECT_LAUNCHES) it = c->graphs.emplace(key, nullptr).first;
+  }
+  if (it == c->graphs.end()) {
     hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return fail_hip(c, e);
-    Run r{c, s, false};
-    r.slot_w = slot_w;
-    r.slot_r = slot_r;
-    r.read_ahead = read_ahead;
-    // two-stream frames: per-operation launches, or the loop on a part of the chip (the prefill's blocks need compute units too)
-    r.persist_blocks = read_ahead ? 0 : frame_loop_blocks(c, P);
-    r.persistent_ok = read_ahead || r.persist_blocks > 0;
-    r.prefill_loops = prefill_loops;
-    r.resident = kind == KIND_INFER;
+    Run r = fresh_run(s, false);
     body(r);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(s, &g);
@@ -1714,6 +1727,12 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) return fail_hip(c, e);
     it = c->graphs.emplace(key, ge).first;
+  }
+  if (it->second == nullptr) {
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;   // graph mode refuses a stream that is being captured
+    hipError_t e = hipStreamIsCapturing(s, &capturing);
+    if (e == hipSuccess && capturing != hipStreamCaptureStatusNone) e = hipErrorIllegalState;
+    return e == hipSuccess ? launch() : fail_hip(c, e);
   }
   hipError_t e = hipGraphLaunch(it->second, s);
   return e == hipSuccess ? PI0_OK : fail_hip(c, e);
@@ -1816,7 +1835,7 @@ int pi0_create(const pi0_config* cfg, pi0_ctx** out) {
 
 void pi0_destroy(pi0_ctx* c) {
   if (c == nullptr) return;
-  for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
+  destroy_graphs(c);
   for (int i = 0; i < 2; i++) {
     if (c->ev_prefill[i]) (void)hipEventDestroy(c->ev_prefill[i]);
     if (c->ev_denoise[i]) (void)hipEventDestroy(c->ev_denoise[i]);
@@ -1868,8 +1887,7 @@ int pi0_tune(pi0_ctx* c, const char* env) {
     for (int* v : {&c->tune.pfq, &c->tune.pfa, &c->tune.pfo, &c->tune.pfd}) *v &= ~15;
     if (c->tune.rad == 7) c->tune.rad = 6;   // the read-ahead kernel exists with 1 .. 6 and 8 loads in flight
   }
-  for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
-  c->graphs.clear();
+  destroy_graphs(c);
   return PI0_OK;
 }
 
@@ -1879,8 +1897,7 @@ int pi0_set_loop_trace(pi0_ctx* c, long long* d_trace, int ops_cap) {
   if (c == nullptr || ops_cap < 0 || (d_trace == nullptr) != (ops_cap == 0) || (reinterpret_cast<uintptr_t>(d_trace) & 7) != 0) return PI0_EINVAL;
   c->loop_trace = d_trace;
   c->loop_trace_ops = ops_cap;
-  for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
-  c->graphs.clear();
+  destroy_graphs(c);
   return PI0_OK;
 }
 
@@ -1930,8 +1947,7 @@ int pi0_load_weights(pi0_ctx* c, const void* d_blob, size_t blob_bytes, void* d_
   const Dims& d = c->d;
   const BlobLayout& b = c->bl;
   const WsLayout& w = c->wl;
-  for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
-  c->graphs.clear();
+  destroy_graphs(c);
   c->loaded = false;
   c->cur_views = 0;
   c->ws = reinterpret_cast<unsigned char*>(d_workspace);
