@@ -10,7 +10,7 @@ configuration (3 views + 48 prompt tokens from the 257152-row table) and the str
 each view count with its own roofline fractions.  Prints ONE JSON line.
 
 Other modes (for profilers; no JSON metric line):
-  --trace-pass      warm-up, then `--steps` graph replays of pi0_infer at `--views` and nothing else
+  --trace-pass      warm-up, then `--steps` passes of pi0_infer at `--views` and nothing else
   --counters-pass   one 1 GiB device-to-device copy (calibration point of the byte counters) and ONE eager pass
 """
 from __future__ import annotations
@@ -216,7 +216,7 @@ def main() -> int:
                   f"{f('barrier'):7.0f}   " + " ".join(f"{x:6.0f}" for x in mk if x > 0))
         print(f"sum of span + next over the operations of one Euler step: {total / 2e3:.1f} us "
               f"({total / 2e3 / cfg.exp_layers:.2f} us per layer incl. the step's own operations)")
-        print(f"kernel span (first entry -> last arrive): {(t[-1][:, 3].max() - t[0][:, 0].min()) * 10 / 1e6:.3f} ms")
+        print(f"kernel span (first entry -> last arrive): {(t[-1][:, 3].max() - next(x for x in t if x[:, 0].any())[:, 0].min()) * 10 / 1e6:.3f} ms")
         m.close()
         return 0
 
