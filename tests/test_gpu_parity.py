@@ -103,6 +103,23 @@ class Case:
         self.stream.synchronize()
         return d_act.cpu().numpy()
 
+    def prefill_and_denoise(self, img, st, nz, ids):
+        d_img, d_st, d_nz, d_ids = self.to_dev(img, st, nz, ids)
+        d_act = torch.empty((self.cfg.chunk, self.cfg.action_dim), dtype=torch.float32, device=self.dev)
+        self.m.pi0_prefill(d_img, img.shape[0], d_ids, len(ids), self.stream)
+        self.m.pi0_denoise(d_st, d_nz, d_act, self.stream)
+        self.stream.synchronize()
+        return d_act.cpu().numpy()
+
+    def by_launches(self, img, st, nz, ids):
+        """The same with the vision tower and the prefix as one launch per operation, which the launch count shows."""
+        self.m.pi0_tune("pvl=0,ppl=0")
+        try:
+            assert self.m.pi0_kernel_count(img.shape[0], len(ids)) >= 5 * (self.cfg.vis_layers + self.cfg.llm_layers - 1)
+            return self.prefill_and_denoise(img, st, nz, ids)
+        finally:
+            self.m.pi0_tune("pvl=1,ppl=1")
+
     def denoise_only(self, st, nz):
         """pi0_denoise on the cache of the last prefill."""
         cfg = self.cfg

@@ -14,15 +14,6 @@ CFG = dataclasses.replace(synth.reduced_config(vocab=64), vis_layers=2, llm_laye
 SHAPES = [(1, 0), (1, 7), (1, 64), (2, 0), (2, 21), (2, 64), (3, 0)]   # a shape of every variant, and its last one where that is ragged
 
 
-def prefill_and_denoise(case, img, st, nz, ids):
-    d_img, d_st, d_nz, d_ids = case.to_dev(img, st, nz, ids)
-    d_act = torch.empty((case.cfg.chunk, case.cfg.action_dim), dtype=torch.float32, device=case.dev)
-    case.m.pi0_prefill(d_img, img.shape[0], d_ids, len(ids), case.stream)
-    case.m.pi0_denoise(d_st, d_nz, d_act, case.stream)
-    case.stream.synchronize()
-    return d_act.cpu().numpy()
-
-
 @pytest.mark.gpu
 @pytest.mark.parametrize("graphs", [True, False])
 def test_any_number_of_blocks_gives_the_launches_bits(graphs):
@@ -31,14 +22,13 @@ def test_any_number_of_blocks_gives_the_launches_bits(graphs):
         case.m.pi0_set_graph_mode(graphs)
         for n_views, n_prompt in SHAPES:
             img, st, nz, ids = case.inputs(n_views, n_prompt)
-            case.m.pi0_tune("pvl=0,ppl=0,pmb=256")
-            want = prefill_and_denoise(case, img, st, nz, ids)
+            want = case.by_launches(img, st, nz, ids)
             for blocks in (256, 255, 216, 97, 1):
                 say(f"[gpu] prefill loops, {n_views} views + {n_prompt}, {blocks} blocks, graphs={graphs}")
-                case.m.pi0_tune(f"pvl=1,ppl=1,pmb={blocks}")
-                np.testing.assert_array_equal(prefill_and_denoise(case, img, st, nz, ids), want)
-                assert np.isnan(prefill_and_denoise(case, np.full_like(img, np.nan), st, nz, ids)).all()
-                np.testing.assert_array_equal(prefill_and_denoise(case, img, st, nz, ids), want)
+                case.m.pi0_tune(f"pmb={blocks}")
+                np.testing.assert_array_equal(case.prefill_and_denoise(img, st, nz, ids), want)
+                assert np.isnan(case.prefill_and_denoise(np.full_like(img, np.nan), st, nz, ids)).all()
+                np.testing.assert_array_equal(case.prefill_and_denoise(img, st, nz, ids), want)
                 np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
         case.m.pi0_device_status(case.stream)   # raises if a bounded wait ran out
     finally:
@@ -51,7 +41,7 @@ def test_prefill_beside_another_contexts_denoise():
     a, b = Case(CFG), Case(CFG, seed=1)
     try:
         ia, ib = a.inputs(1, 0), b.inputs(2, 21)
-        want_a, want_b = prefill_and_denoise(a, *ia), prefill_and_denoise(b, *ib)
+        want_a, want_b = a.prefill_and_denoise(*ia), b.prefill_and_denoise(*ib)
         d_img, d_st, d_nz, d_ids = b.to_dev(*ib)
         _, a_st, a_nz, _ = a.to_dev(*ia)
         act_a = [torch.empty((CFG.chunk, CFG.action_dim), device=a.dev) for _ in range(6)]
@@ -80,7 +70,7 @@ def test_prefill_after_frames():
     case = Case(CFG)
     try:
         img, st, nz, ids = case.inputs(1, 7)
-        want = prefill_and_denoise(case, img, st, nz, ids)
+        want = case.prefill_and_denoise(img, st, nz, ids)
         side = torch.cuda.Stream(device=case.dev)
         d_img, d_st, d_nz, d_ids = case.to_dev(img, st, nz, ids)
         act = [torch.empty((CFG.chunk, CFG.action_dim), device=case.dev) for _ in range(3)]
@@ -91,6 +81,6 @@ def test_prefill_after_frames():
         side.synchronize()
         for a in act:
             np.testing.assert_array_equal(a.cpu().numpy(), want)
-        np.testing.assert_array_equal(prefill_and_denoise(case, img, st, nz, ids), want)
+        np.testing.assert_array_equal(case.prefill_and_denoise(img, st, nz, ids), want)
     finally:
         case.close()

@@ -5,22 +5,12 @@ import dataclasses
 
 import numpy as np
 import pytest
-import torch
 
 from paper_2510_26742_amd import binding, build, synth
 from tests.test_gpu_parity import Case, say
 from tests.test_loop_code_size import INSTRUCTION_CACHE, code_objects, symbols
 
 CFG = dataclasses.replace(synth.reduced_config(vocab=64), vis_layers=3, max_views=4, max_prompt=0)   # a first, a middle and a last layer
-
-
-def by_launches(case, img, st, nz, ids):
-    d_img, d_st, d_nz, _ = case.to_dev(img, st, nz, ids)
-    d_act = torch.empty((case.cfg.chunk, case.cfg.action_dim), dtype=torch.float32, device=case.dev)
-    case.m.pi0_prefill(d_img, img.shape[0], None, 0, case.stream)
-    case.m.pi0_denoise(d_st, d_nz, d_act, case.stream)
-    case.stream.synchronize()
-    return d_act.cpu().numpy()
 
 
 @pytest.mark.gpu
@@ -33,11 +23,12 @@ def test_infer_equals_prefill_and_denoise(graphs):
         for n_views in (1, 3, 2, 4, 1, 2, 3):
             img, st, nz, ids = case.inputs(n_views, 0)
             say(f"[gpu] vision loop views={n_views} graphs={graphs}")
-            want = by_launches(case, img, st, nz, ids)
+            want = case.by_launches(img, st, nz, ids)
             np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
             assert np.isnan(case.infer(np.full_like(img, np.nan), st, nz, ids)).all()
             for _ in range(3):
                 np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
+            np.testing.assert_array_equal(case.prefill_and_denoise(img, st, nz, ids), want)
             launches = case.m.pi0_kernel_count(n_views, 0)
             case.m.pi0_tune("pvl=0")
             np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
@@ -58,7 +49,7 @@ def test_feed_forward_widths_around_one_round(vis_mlp, views):
     try:
         img, st, nz, ids = case.inputs(views, 0)
         say(f"[gpu] vision loop vis_mlp={vis_mlp} views={views}")
-        want = by_launches(case, img, st, nz, ids)
+        want = case.by_launches(img, st, nz, ids)
         for _ in range(2):
             np.testing.assert_array_equal(case.infer(img, st, nz, ids), want)
         case.m.pi0_device_status(case.stream)
