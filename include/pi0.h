@@ -227,7 +227,11 @@ int pi0_debug_forward(pi0_ctx* ctx, const float* d_images, int n_views, const in
 enum pi0_precision { PI0_PRECISION_BF16 = 0, PI0_PRECISION_MXFP8_PREFIX_MLP = 1 };
 int pi0_set_precision(pi0_ctx* ctx, int precision);
 
-/* Graph replay on (1, default) or off (0: every call launches kernels eagerly). */
+/*
+ * Graph replay on (1, default) or off (0: every call launches kernels eagerly).  While it is on, a call on a stream that is itself being
+ * captured is refused (PI0_EHIP, hipErrorIllegalState), whether or not its shape has been used before; the launch that stages
+ * the call's inputs may be in the capture by then.
+ */
 int pi0_set_graph_mode(pi0_ctx* ctx, int enabled);
 
 /*

@@ -1703,6 +1703,12 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     return r.ok() ? PI0_OK : fail_hip(c, r.err);
   };
   if (!c->graph_mode || s == nullptr) return launch();   // the legacy default stream cannot be captured
+  // Graph mode refuses a stream that is being captured, whether this call would capture, replay or launch: a replay does not become a part of the
+  // caller's graph, it runs at once
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(s, &capturing);
+  if (e == hipSuccess && capturing != hipStreamCaptureStatusNone) e = hipErrorIllegalState;
+  if (e != hipSuccess) return fail_hip(c, e);
   GraphKey key{kind, n_views, n_prompt, kind == KIND_DENOISE ? 0 : slot_w, kind == KIND_PREFILL ? 0 : slot_r,
                kind == KIND_DENOISE ? 0 : c->precision, kind == KIND_PREFILL ? (int)prefill_loops : (int)read_ahead};
   auto it = c->graphs.find(key);
@@ -1712,7 +1718,7 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     if (count.launches <= DIRECT_LAUNCHES) it = c->graphs.emplace(key, nullptr).first;
   }
   if (it == c->graphs.end()) {
-    hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+    e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return fail_hip(c, e);
     Run r = fresh_run(s, false);
     body(r);
@@ -1728,13 +1734,8 @@ int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int 
     if (e != hipSuccess) return fail_hip(c, e);
     it = c->graphs.emplace(key, ge).first;
   }
-  if (it->second == nullptr) {
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;   // graph mode refuses a stream that is being captured
-    hipError_t e = hipStreamIsCapturing(s, &capturing);
-    if (e == hipSuccess && capturing != hipStreamCaptureStatusNone) e = hipErrorIllegalState;
-    return e == hipSuccess ? launch() : fail_hip(c, e);
-  }
-  hipError_t e = hipGraphLaunch(it->second, s);
+  if (it->second == nullptr) return launch();
+  e = hipGraphLaunch(it->second, s);
   return e == hipSuccess ? PI0_OK : fail_hip(c, e);
 }
 

@@ -6,6 +6,7 @@ key/value cache has cosine similarity >= 0.999 with the oracle.  Integer-free pa
 here is bit-exact against the oracle; bit-exactness is required between the library's own
 eager, graph and replayed runs.
 """
+import ctypes
 import math
 import sys
 
@@ -270,6 +271,31 @@ def test_graph_replay_is_bitwise_equal_to_eager(reduced, replayed):
         np.testing.assert_array_equal(reduced.infer(img, st, nz, ids), eager)
     finally:
         reduced.m.pi0_set_graph_mode(True)
+        reduced.m.pi0_tune("pvl=1,ppl=1")
+
+
+@pytest.mark.parametrize("replayed", [False, True])
+def test_graph_mode_refuses_a_stream_that_is_being_captured(reduced, replayed):
+    """A shape's first call and a later one, as launches and as a replay: a replay would run at once instead of becoming a part of the
+    caller's graph.  Afterwards the same calls give the same results."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    img, st, nz, ids = reduced.inputs(2, 0)
+    d_img, d_st, d_nz, _ = reduced.to_dev(img, st, nz, ids)
+    d_act = torch.empty((reduced.cfg.chunk, reduced.cfg.action_dim), dtype=torch.float32, device=reduced.dev)
+    want = reduced.infer(img, st, nz, ids)
+    stream, graph = ctypes.c_void_p(reduced.stream.cuda_stream), ctypes.c_void_p()
+    reduced.m.pi0_tune("pvl=0,ppl=0" if replayed else "pvl=1,ppl=1")   # (drops the graphs)
+    try:
+        for call in ("first", "second"):
+            say(f"[gpu] captured stream, replayed={replayed}, {call} call")
+            assert hip.hipStreamBeginCapture(stream, 1) == 0   # thread local
+            with pytest.raises(binding.Pi0Error) as e:
+                reduced.m.pi0_infer(d_img, 2, None, 0, d_st, d_nz, d_act, reduced.stream)
+            assert hip.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0
+            assert hip.hipGraphDestroy(graph) == 0
+            assert e.value.code == binding.PI0_EHIP
+            np.testing.assert_array_equal(reduced.infer(img, st, nz, ids), want)
+    finally:
         reduced.m.pi0_tune("pvl=1,ppl=1")
 
 
