@@ -217,7 +217,8 @@ int pi0_set_loop_trace(pi0_ctx* ctx, long long* d_trace, int ops_cap);
  * one persistent kernel, 0: one launch per operation) and pra (what the persistent kernel's blocks without a work item read
  * ahead: 1 gate||up, 2 down, 4 next layer's QKV, 8 next layer's O weights during the attention; 16 this layer's O weights
  * during QKV; 32: every block what blocks of its own die will ask for), pvl and ppl (pi0_prefill and pi0_infer: 1 the vision tower,
- * the prefix's layers as one persistent kernel, 0 as launches), pmb (1 .. 256: most blocks of these two that take part) and psb (blocks of the persistent kernel inside a two-stream frame;
+ * the prefix's layers as one persistent kernel, 0 as launches), pmb (1 .. 256: most blocks of these two that take part), spl (1 .. 2^20, the default: polls
+ * that a wait inside a persistent kernel lasts at most) and psb (blocks of the persistent kernel inside a two-stream frame;
  * 0: per-operation launches there, -1: chosen from the prefix size).
  * Drops every captured graph, so the next call of a shape captures again.  Must not be called while work of this
  * ctx is in flight.  The library itself never reads the environment.  Errors: EINVAL (null).

@@ -169,7 +169,7 @@ struct GridBarrierT {
 
   // As init, for kernels whose operations any number of blocks can share out: goes on as soon as all blocks of the grid have come, or GB_WINDOW after this
   // one came with those that are there by then, so that no wait depends on compute units that other work holds.  A block that
-  // comes later takes no part (false: it ends).  most: with no more than this many, at once; 0: init, all of the grid (a round trip less).  first, stride: this block's items are first, first + stride, ..
+  // comes later takes no part (false: it ends), nor does one whose wait ran out here.  most: with no more than this many, at once; 0: init, all of the grid (a round trip less).  first, stride: this block's items are first, first + stride, ..
   // (all of the grid: blockIdx.x, gridDim.x).  pi0_prefill, which promises its caller no resident grid, runs its loops so: 2 views + 21 tokens and two
   // denoises, as launches -> so, 12.16 -> 11.87 ms.  shared: three words of shared memory that nothing else uses yet.
   __device__ __forceinline__ bool init_some(unsigned* words, unsigned limit, bool may_lead, unsigned most, unsigned* shared, int& first, int& stride) {
@@ -214,7 +214,7 @@ struct GridBarrierT {
           __builtin_amdgcn_s_sleep(2);
           if (++spins > spin_limit || ld_dev(&w[GB_ERR]) != 0u) {
             st_dev(&w[GB_ERR], 1u);
-            n = n != 0u ? n : 1u;
+            n = 0;   // takes no part (a stride of one in its place would have every block do all of the work)
             break;
           }
         }

@@ -448,6 +448,7 @@ struct Tune {
   int pvl = 1;
   int ppl = 1;            // the same for the prefix's layers
   int pmb = 256;          // most of their blocks that take part (fewer: as where other work holds compute units, for tests)
+  int spl = 1 << 20;      // polls that a wait of a persistent kernel lasts at most (few: for tests of what follows when one runs out)
   // two-stream frames: blocks of the persistent loop beside the prefill (0: per-operation launches).  A resident block
   // of the loop holds a whole compute unit, so its grid decides how the chip is shared between the two streams
   int psb = -1;           // -1: from the number of prefix tokens (frame_loop_blocks)
@@ -744,7 +745,7 @@ bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_ro
   E.r_xb_o = w.rv_xb_o; E.r_st_o = w.rv_st_o; E.r_xb_d = w.rv_xb_d; E.r_st_d = w.rv_st_d;
   E.r_q = w.rv_q; E.r_k = w.rv_k; E.r_v = w.rv_v; E.r_attn = w.rv_attn; E.r_mid = w.rv_mid;
   E.sync = at<unsigned>(c, w.vsync);
-  E.spin_limit = 1u << 20;
+  E.spin_limit = (unsigned)T.spl;
   E.most_blocks = r.resident && T.pmb == PK_BLOCKS ? 0u : (unsigned)T.pmb;
   if (!vision_loop_takes(n_views, E, PK_BLOCKS)) return false;
   r.cls = PI0_OP_MISC;
@@ -875,7 +876,7 @@ int prefix_persistent(Run& r, int P, int stat_rows, int z, int k_per_split, Pref
   E.arena = reinterpret_cast<const char*>(c->ws + w.act_begin);
   E.arena_bytes = (unsigned)arena_bytes;
   E.sync = at<unsigned>(c, w.psync);
-  E.spin_limit = 1u << 20;
+  E.spin_limit = (unsigned)T.spl;
   E.most_blocks = r.resident && T.pmb == PK_BLOCKS ? 0u : (unsigned)T.pmb;
   return prefix_loop_takes(variant, E, PK_BLOCKS) ? variant : -1;
 }
@@ -1335,7 +1336,7 @@ void expert_loop_params(pi0_ctx* c, int P, int slot_r, float* actions, ExpertLoo
   E.sync = at<unsigned>(c, w.esync);
   E.arena = reinterpret_cast<const char*>(c->ws + w.act_begin);
   E.arena_bytes = (unsigned)arena_bytes;
-  E.spin_limit = 1u << 20;
+  E.spin_limit = (unsigned)T.spl;
   E.trace = c->loop_trace;
   E.trace_ops = c->loop_trace_ops;
 }
@@ -1873,7 +1874,7 @@ int pi0_tune(pi0_ctx* c, const char* env) {
         {"zld", &c->tune.zld, 1, Z_MAX}, {"zvd", &c->tune.zvd, 1, Z_MAX},
         {"pfq", &c->tune.pfq, 0, 1024}, {"pfa", &c->tune.pfa, 0, 1024}, {"pfo", &c->tune.pfo, 0, 1024},
         {"pfd", &c->tune.pfd, 0, 1024}, {"ae16", &c->tune.ae16, 0, 1}, {"ksplit", &c->tune.ksplit, 0, 1}, {"kcps", &c->tune.kcps, 2, 16}, {"qms", &c->tune.qms, 0, 1},
-        {"ppl", &c->tune.ppl, 0, 1}, {"pmb", &c->tune.pmb, 1, 256}, {"fko", &c->tune.fko, 0, 1}, {"fkl", &c->tune.fkl, 0, 1}, {"ras", &c->tune.ras, 0, 4096}, {"ral", &c->tune.ral, 1, 8}, {"rat", &c->tune.rat, 64, 256}, {"rad", &c->tune.rad, 1, 8 /* 7: no such variant, see below */}, {"avs", &c->tune.avs, 1, 8}, {"pdn", &c->tune.pdn, 0, 1}, {"pra", &c->tune.pra, 0, 63}, {"psb", &c->tune.psb, -1, 256}, {"pvl", &c->tune.pvl, 0, 1}};
+        {"ppl", &c->tune.ppl, 0, 1}, {"pmb", &c->tune.pmb, 1, 256}, {"spl", &c->tune.spl, 1, 1 << 20}, {"fko", &c->tune.fko, 0, 1}, {"fkl", &c->tune.fkl, 0, 1}, {"ras", &c->tune.ras, 0, 4096}, {"ral", &c->tune.ral, 1, 8}, {"rat", &c->tune.rat, 64, 256}, {"rad", &c->tune.rad, 1, 8 /* 7: no such variant, see below */}, {"avs", &c->tune.avs, 1, 8}, {"pdn", &c->tune.pdn, 0, 1}, {"pra", &c->tune.pra, 0, 63}, {"psb", &c->tune.psb, -1, 256}, {"pvl", &c->tune.pvl, 0, 1}};
     for (auto& k : keys) {
       const char* f = strstr(env, k.key);
       while (f != nullptr && !((f == env || f[-1] == ',') && f[strlen(k.key)] == '=')) f = strstr(f + 1, k.key);

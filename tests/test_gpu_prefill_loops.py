@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2510_26742_amd import synth
+from paper_2510_26742_amd import binding, synth
 from tests.test_gpu_parity import Case, say
 
 CFG = dataclasses.replace(synth.reduced_config(vocab=64), vis_layers=2, llm_layers=3, exp_layers=3, max_prompt=64)
@@ -82,5 +82,49 @@ def test_prefill_after_frames():
         for a in act:
             np.testing.assert_array_equal(a.cpu().numpy(), want)
         np.testing.assert_array_equal(case.prefill_and_denoise(img, st, nz, ids), want)
+    finally:
+        case.close()
+
+
+def timed(case, n_views, inputs, calls=1):
+    """ms that `calls` pi0_prefill take, the first begun on an idle device."""
+    d_img, _, _, d_ids = case.to_dev(*inputs)
+    begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda.synchronize()
+    begin.record(case.stream)
+    for _ in range(calls):
+        case.m.pi0_prefill(d_img, n_views, d_ids, len(inputs[3]), case.stream)
+    end.record(case.stream)
+    end.synchronize()
+    return begin.elapsed_time(end)
+
+
+@pytest.mark.gpu
+def test_prefill_after_a_wait_that_ran_out_is_quick_and_reported():
+    """One poll is not enough for all blocks to come.  The error word stays raised until the weights are loaded again, and the blocks of a
+    later prefill that find it raised end: with the work of all blocks for each of them, nine layers took some hundred times as long."""
+    case = Case(dataclasses.replace(CFG, vis_layers=9))
+    try:
+        inputs = case.inputs(2, 21)
+        want = case.by_launches(*inputs)
+        np.testing.assert_array_equal(case.prefill_and_denoise(*inputs), want)
+        whole = min(timed(case, 2, inputs) for _ in range(3))
+        case.m.pi0_tune("spl=1")
+        say("[gpu] prefill whose waits end at once")
+        timed(case, 2, inputs)
+        with pytest.raises(binding.Pi0Error):
+            case.m.pi0_device_status(case.stream)
+        case.m.pi0_tune("spl=1048576")
+        say("[gpu] prefill with the error word raised")
+        late = min(timed(case, 2, inputs) for _ in range(3))
+        say(f"[gpu] {whole:.2f} ms before, {late:.2f} ms with the error word raised")
+        assert late < 4 * whole
+        with pytest.raises(binding.Pi0Error):
+            case.m.pi0_device_status(case.stream)
+        d_blob = torch.from_numpy(case.blob.view(np.int16)).to(case.dev)
+        torch.cuda.synchronize()
+        case.m.pi0_load_weights(d_blob, case.stream)
+        np.testing.assert_array_equal(case.prefill_and_denoise(*inputs), want)
+        case.m.pi0_device_status(case.stream)
     finally:
         case.close()
