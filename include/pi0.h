@@ -20,18 +20,21 @@
  *    The library allocates no device memory; it owns only the host-side pi0_ctx.
  *  - Every call only enqueues work on `hip_stream` (a hipStream_t, may be NULL for the default
  *    stream); results are valid after the caller synchronises that stream.  pi0_denoise / pi0_infer
- *    run the expert's loop as one persistent kernel of 256 blocks that must all be resident at once,
- *    and pi0_infer and pi0_prefill the vision tower (1 .. 3 views of 256 tokens) and the prefix's layers (bf16; with the full model's
- *    feed-forward 193 .. 320, 385 .. 576 and 641 .. 768 tokens) as two more, at the full model's widths (launches otherwise, same bits).
- *    pi0_prefill asks for no residency: its two kernels go on, after 100 us, with the blocks that are there, the fewer the slower
- *    (a ctx that has had two-stream frames launches one kernel per operation):
- *    on a device with fewer than 256 compute units, or when the shape is outside what that kernel
+ *    run the expert's loop as one persistent kernel of 256 blocks that must all be resident at once.
+ *    On a device with fewer than 256 compute units, or when the shape is outside what that kernel
  *    covers, the loop is issued as one launch per operation instead, together with one read-ahead
  *    kernel (it only loads the expert's weights ahead of the compute launches, Section 5.2) forked onto
  *    a stream the ctx owns and joined back into `hip_stream` before the call's last launch, with events,
  *    also inside the captured graph; work enqueued on `hip_stream` after the call is ordered after both.
+ *    pi0_infer and pi0_prefill run the vision tower (1 .. 3 views of 256 tokens) and the prefix's layers (bf16; with the full
+ *    model's feed-forward 193 .. 320, 385 .. 576 and 641 .. 768 tokens) as two more, at the full model's widths (launches otherwise,
+ *    same bits; a ctx that has had two-stream frames launches one kernel per operation in pi0_prefill).
+ *    pi0_infer's wait for all of their blocks as well.  pi0_prefill's ask for no residency: they go on with the blocks that are
+ *    there 25 us after the last one came (up to 25 us x 256 / n the first time, with n of 256), do one layer with those, and try
+ *    again for three, for nine and for the rest, each time doing all that are left once all blocks are there.
  *    Do not run other kernels that occupy whole compute units for long beside pi0_denoise / pi0_infer:
- *    the persistent kernel's blocks wait for each other (bounded, see pi0_device_status).
+ *    the persistent kernels' blocks wait for each other (bounded, see pi0_device_status).  pi0_prefill of another ctx is such a kernel
+ *    for the time of a tower or of a prefix (milliseconds), or of the layers above where it shares the chip.
  *  - Return value: 0 on success, a negative PI0_E* code otherwise.  Argument checks happen before
  *    any GPU call, so error paths touch no GPU state.  Nothing throws or aborts across the ABI.
  *  - Calls on one ctx must not overlap in time (one workspace, one set of activations); the only

@@ -110,6 +110,7 @@ enum {
   GB_START = 32,       // start-up counter: blocks registered
   GB_TICKETS = 33,     // init_some: blocks that asked to take part, | GB_CLOSED once it goes on without the others
   GB_TAKEN = 34,       // init_some: blocks that take part, once that is decided
+  GB_NEXT = 35,        // init_some, of the first launch's words: layers that the launches before have done
   GB_MEMBERS = 64,     // + 32 x: blocks resident on die x
   GB_LEADER = 320,     // + 32 x: 1 + index of the block that leads die x (+ 2^16 if it asked to)
   GB_DONE = 576,       // + 32 y + x: last epoch that die x completed, as told to die y (one cache line per reading die)
@@ -119,7 +120,19 @@ enum {
   GB_WORDS = GB_FLAGS + 8 * GB_MAX_BLOCKS
 };
 constexpr unsigned GB_CLOSED = 1u << 16;
-constexpr long long GB_WINDOW = 10000;   // of the 100 MHz counter: 100 us, within which the blocks of a launch on an otherwise idle device have long come
+constexpr long long GB_WINDOW = 2500;   // of the 100 MHz counter: 25 us from one block to the next (on an otherwise idle device all come within 10); the first of the launches
+                                        // below, which knows nothing of the device yet, waits 25 us x 256 / n when n have come, half of what a layer then takes them
+// A loop that goes on with the blocks that have come is launched GB_LAUNCHES times, with barrier words for each.  A launch that has all blocks does all
+// layers that are left, another one no more than gb_quota of them, and then lets go of its compute units: a moment in which other work holds
+// the chip costs one layer on the few units that were free, and a kernel that waits for those units gets them.
+constexpr int GB_LAUNCHES = 4;
+__host__ __device__ constexpr int gb_quota(int launch) { return launch == 0 ? 1 : launch == 1 ? 3 : launch == 2 ? 9 : 1 << 30; }
+
+// Barrier words to zero, in a launch ahead of the kernel's
+__device__ __forceinline__ void gb_clear(unsigned* sync, int launches, unsigned i) {   // piece i of the words of that many launches; the error words stay as they are
+  constexpr unsigned PIECES = (GB_WORDS - GB_START) / 4;
+  if (i < PIECES * (unsigned)launches) reinterpret_cast<uint4*>(sync + i / PIECES * GB_WORDS + GB_START)[i % PIECES] = uint4{0u, 0u, 0u, 0u};
+}
 
 // TRACE: a timeline is recorded (a kernel of its own: the code for it in every operation costs instruction cache).  LEAN: no address of the
 // barrier's words stays in registers from one barrier to the next, for kernels with an operation that takes all there are (a spilled
@@ -167,12 +180,14 @@ struct GridBarrierT {
     for (unsigned k = 0; k < 8u; k++) present |= ld_dev(&w[GB_MEMBERS + 32 * k]) != 0u ? 1u << k : 0u;
   }
 
-  // As init, for kernels whose operations any number of blocks can share out: goes on as soon as all blocks of the grid have come, or GB_WINDOW after this
-  // one came with those that are there by then, so that no wait depends on compute units that other work holds.  A block that
-  // comes later takes no part (false: it ends), nor does one whose wait ran out here.  most: with no more than this many, at once; 0: init, all of the grid (a round trip less).  first, stride: this block's items are first, first + stride, ..
-  // (all of the grid: blockIdx.x, gridDim.x).  pi0_prefill, which promises its caller no resident grid, runs its loops so: 2 views + 21 tokens and two
-  // denoises, as launches -> so, 12.16 -> 11.87 ms.  shared: three words of shared memory that nothing else uses yet.
-  __device__ __forceinline__ bool init_some(unsigned* words, unsigned limit, bool may_lead, unsigned most, unsigned* shared, int& first, int& stride) {
+  // As init, for kernels whose operations any number of blocks can share out: goes on as soon as all blocks of the grid have come, or with fewer once
+  // none has come for GB_WINDOW, so that no wait depends on compute units that other work holds.  A block that
+  // comes later takes no part (false: it ends), nor does one whose wait ran out here, nor any once a wait of one of the launches has (the error words stay raised).  most: with no more than this many, at once; 0: init, all of the grid (a round trip
+  // less, and one launch).  words: of the first of the launches, of which this one is number `launch`.  first, stride: this block's items are first, first + stride, ..
+  // (all of the grid: blockIdx.x, gridDim.x).  begin, end: the layers to do; end: all there are, before.  pi0_prefill, which promises its caller no resident grid,
+  // runs its loops so: 2 views + 21 tokens and two denoises, as launches -> so, 12.16 -> 11.87 ms.  shared: four words of shared memory that nothing else uses yet.
+  __device__ __forceinline__ bool init_some(unsigned* words, unsigned limit, bool may_lead, unsigned most, int launch, unsigned* shared, int& first, int& stride, int& begin,
+                                            int& end) {
     // (opaque: the compiler knows these values as the same in all lanes, drops the builtin and then has addresses in vector registers.  Not
     // the instruction itself as assembly, in front of which the compiler leaves no wait state for the register that it reads)
     auto scalar = [](unsigned v) {
@@ -183,31 +198,37 @@ struct GridBarrierT {
       init(words, limit, may_lead);
       first = (int)scalar(blockIdx.x);
       stride = (int)scalar(gridDim.x);
+      begin = 0;
       return true;
     }
-    w = as_global(words);
+    w = as_global(words) + launch * GB_WORDS;
     spin_limit = limit;
     epoch = 0;
     trace = nullptr;
     xcc = (unsigned)__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7u;   // XCC_ID, bits 3:0
     if (threadIdx.x == 0) {
       if (most > gridDim.x) most = gridDim.x;
-      unsigned r = 0, n = 0;
-      const unsigned ticket = __hip_atomic_fetch_add(&w[GB_TICKETS], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned r = 0, n = 0, ticket = most;
+      const unsigned done = ld_dev(as_global(words) + GB_NEXT);
+      unsigned failed = 0;
+      for (int k = 0; k < GB_LAUNCHES; k++) failed |= ld_dev(as_global(words) + k * GB_WORDS + GB_ERR);
+      if (done < (unsigned)end && failed == 0u) ticket = __hip_atomic_fetch_add(&w[GB_TICKETS], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (ticket < most) {   // (GB_CLOSED is more than any grid)
         if (ticket + 1 == most) st_dev(&w[GB_TAKEN], most);
         __hip_atomic_fetch_max(&w[GB_LEADER + 32 * xcc], (unsigned)blockIdx.x + 1u + (may_lead ? 1u << 16 : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         r = __hip_atomic_fetch_add(&w[GB_MEMBERS + 32 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // both are in place before this block counts as registered
         __hip_atomic_fetch_add(&w[GB_START], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const long long begin = (long long)wall_clock64();
-        bool asked = false;
-        unsigned spins = 0;
+        long long since = (long long)wall_clock64();
+        unsigned seen = ticket, spins = 0;
         while (true) {
           n = ld_dev(&w[GB_TAKEN]);
-          if (n != 0u && ld_dev(&w[GB_START]) >= n) break;
-          if (n == 0u && !asked && (long long)wall_clock64() - begin > GB_WINDOW) {
-            asked = true;
+          const unsigned started = ld_dev(&w[GB_START]), tickets = ld_dev(&w[GB_TICKETS]);
+          if (n != 0u && started >= n) break;
+          if (tickets != seen) {
+            seen = tickets;
+            since = (long long)wall_clock64();
+          } else if (n == 0u && ((long long)wall_clock64() - since) * (launch == 0 ? tickets : gridDim.x) > GB_WINDOW * gridDim.x) {
             const unsigned before = __hip_atomic_fetch_or(&w[GB_TICKETS], GB_CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (before < GB_CLOSED) st_dev(&w[GB_TAKEN], before < most ? before : most);
           }
@@ -222,19 +243,27 @@ struct GridBarrierT {
       shared[0] = n;
       shared[1] = ticket;
       shared[2] = r;
+      shared[3] = done;
     }
     __syncthreads();
     const unsigned n = scalar(shared[0]), ticket = scalar(shared[1]);
     first = (int)scalar(n == gridDim.x ? blockIdx.x : ticket);
     stride = (int)n;
     rank = scalar(shared[2]);
+    begin = (int)scalar(shared[3]);
     __syncthreads();
     if (n == 0u) return false;
+    if (n != gridDim.x) end = end - begin > gb_quota(launch) ? begin + gb_quota(launch) : end;
     members = ld_dev(&w[GB_MEMBERS + 32 * xcc]);
     leader = (ld_dev(&w[GB_LEADER + 32 * xcc]) & 0xffffu) == (unsigned)blockIdx.x + 1u;
     present = 0;
     for (unsigned k = 0; k < 8u; k++) present |= ld_dev(&w[GB_MEMBERS + 32 * k]) != 0u ? 1u << k : 0u;
     return true;
+  }
+
+  // One block of those that init_some let in, at the end of its last layer: where the next launch goes on
+  __device__ __forceinline__ static void done_some(unsigned* words, unsigned most, int first, int end) {
+    if (most != 0u && first == 0 && threadIdx.x == 0) st_dev(as_global(words) + GB_NEXT, (unsigned)end);
   }
 
   // the error word is looked at on every 64th poll: behind each poll it would double the time between two polls

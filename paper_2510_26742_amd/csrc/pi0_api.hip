@@ -381,9 +381,9 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
     w.pring = w.ering;
     if (bytes > ering_bytes) cur.take(bytes - ering_bytes);
   }
-  w.vsync = cur.take((size_t)GB_WORDS * 4);
+  w.vsync = cur.take((size_t)GB_WORDS * 4 * GB_LAUNCHES);
   w.vparams = cur.take(sizeof(VisionLoopParams));
-  w.psync = cur.take((size_t)GB_WORDS * 4);
+  w.psync = cur.take((size_t)GB_WORDS * 4 * GB_LAUNCHES);
   w.pparams = cur.take(sizeof(PrefixLoopParams));
   w.total = cur.off;
 }
@@ -444,7 +444,7 @@ struct Tune {
   // weights in LDS: down, by die.  pi0_denoise at 1 / 2 / 3 views and 3 views + 48 tokens, ms: nothing 3.74 / - / 4.06 / 4.34, next
   // QKV 3.664 / 3.825 / 3.969 / 4.269, down and next QKV 3.684 / 3.853 / 4.010 / 4.297, down 3.630 / 3.787 / 3.945 / 4.249
   int pra = 34;
-  // the vision tower of pi0_infer as one persistent kernel (1) or as launches (0)
+  // the vision tower of pi0_prefill and pi0_infer as one persistent kernel (1) or as launches (0)
   int pvl = 1;
   int ppl = 1;            // the same for the prefix's layers
   int pmb = 256;          // most of their blocks that take part (fewer: as where other work holds compute units, for tests)
@@ -750,7 +750,7 @@ bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_ro
   if (!vision_loop_takes(n_views, E, PK_BLOCKS)) return false;
   r.cls = PI0_OP_MISC;
   RUN(r, launch_vision_loop(r.s, n_views, E, at<VisionLoopParams>(c, w.vparams), PK_BLOCKS));
-  r.launches++;   // two launches: parameter block and barrier words, loop kernel
+  r.launches += vision_loop_launches(E);   // parameter block and barrier words, loop kernel
   const size_t last = w.vring + w.vring_slot * (size_t)(d.Lv - 1);
   *out = at<bf16>(c, last + w.rv_xb_d);
   *stats = at<float>(c, last + w.rv_st_d);
@@ -1063,7 +1063,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     if (loop >= 0) {   // everything between the first layer's QKV projection and the last one's
       r.cls = PI0_OP_MISC;
       RUN(r, launch_prefix_loop(r.s, loop, E, at<PrefixLoopParams>(c, w.pparams), PK_BLOCKS));
-      r.launches++;   // two launches, as for the tower
+      r.launches += prefix_loop_launches(E);   // as for the tower
       l = d.Ll - 2;
       continue;
     }
@@ -1922,19 +1922,24 @@ int pi0_device_status(pi0_ctx* c, void* hip_stream) {
   if (c == nullptr) return PI0_EINVAL;
   if (!c->loaded) return PI0_ESTATE;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  unsigned flags[3] = {0, 0, 0};
-  const size_t words[3] = {c->wl.esync, c->wl.vsync, c->wl.psync};
-  hipError_t e = hipSuccess;
-  for (int i = 0; i < 3 && e == hipSuccess; i++) e = hipMemcpyAsync(&flags[i], at<unsigned>(c, words[i]) + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
+  unsigned flags[1 + 2 * GB_LAUNCHES] = {};
+  hipError_t e = hipMemcpyAsync(&flags[0], at<unsigned>(c, c->wl.esync) + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
+  for (int i = 0; i < GB_LAUNCHES && e == hipSuccess; i++) {
+    e = hipMemcpyAsync(&flags[1 + 2 * i], at<unsigned>(c, c->wl.vsync) + i * GB_WORDS + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&flags[2 + 2 * i], at<unsigned>(c, c->wl.psync) + i * GB_WORDS + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail_hip(c, e);
-  return flags[0] == 0u && flags[1] == 0u && flags[2] == 0u ? PI0_OK : PI0_ESTATE;
+  for (unsigned f : flags) {
+    if (f != 0u) return PI0_ESTATE;
+  }
+  return PI0_OK;
 }
 
 int pi0_kernel_count(const pi0_ctx* c, int n_views, int n_prompt) {
   if (c == nullptr || n_views < 1 || n_views > c->cfg.max_views || n_prompt < 0 || n_prompt > c->cfg.max_prompt) return 0;
   Run r{const_cast<pi0_ctx*>(c), nullptr, true};
-  r.persistent_ok = r.prefill_loops = true;   // (before weights are loaded no device is known to hold them)
+  r.persistent_ok = r.prefill_loops = r.resident = true;   // (before weights are loaded no device is known to hold them)
   run_prefill(r, n_views, n_prompt, nullptr);
   run_denoise(r, n_views * c->d.T + n_prompt, nullptr);
   return r.launches;

@@ -56,15 +56,15 @@ constexpr int ATT_EARLY = 5, ATT_RING = 12;
 
 constexpr int PREP_THREADS = 256;
 static_assert(sizeof(PrefixLoopParams) % 4 == 0 && (GB_WORDS - GB_START) % 4 == 0, "whole pieces");
-// parameter block to device memory and barrier words to zero (the error word, first, stays as it is)
-__global__ __launch_bounds__(PREP_THREADS) void prefix_loop_prepare_kernel(PrefixLoopParams P, PrefixLoopParams* dst, unsigned* sync) {
+// parameter block to device memory and barrier words to zero
+__global__ __launch_bounds__(PREP_THREADS) void prefix_loop_prepare_kernel(PrefixLoopParams P, PrefixLoopParams* dst, int launches) {
   const unsigned i = blockIdx.x * PREP_THREADS + threadIdx.x;
   if (i < sizeof(PrefixLoopParams) / 4) reinterpret_cast<unsigned*>(dst)[i] = reinterpret_cast<const unsigned*>(&P)[i];
-  if (i < (GB_WORDS - GB_START) / 4) reinterpret_cast<uint4*>(sync + GB_START)[i] = uint4{0u, 0u, 0u, 0u};
+  gb_clear(P.sync, launches, i);
 }
 
 template <int VARIANT>
-__global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefix_loop_kernel(const PrefixLoopParams* __restrict__ params) {
+__global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefix_loop_kernel(const PrefixLoopParams* __restrict__ params, int launch) {
   using C = typename Variants<VARIANT>::T;
   constexpr bool LEAN = C::GU_HEIGHT != 0;   // (gate||up takes every register)
   using Cx = PersistCtxT<true, false, LEAN>;
@@ -72,11 +72,11 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
   const ParamsPtr<PrefixLoopParams> Pg = (ParamsPtr<PrefixLoopParams>)params;
   GridBarrierT<false, LEAN> bar;
   Cx cx;
-  int layers, first, blocks;
+  int layers, begin, end, first, blocks;   // end: of this launch's layers
   {
     const PrefixLoopParams& P = fresh<PrefixLoopParams>(Pg);
-    layers = P.layers;
-    if (!bar.init_some(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == 31, P.most_blocks, reinterpret_cast<unsigned*>(smem_raw), first, blocks)) return;
+    layers = end = P.layers;
+    if (!bar.init_some(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == 31, P.most_blocks, launch, reinterpret_cast<unsigned*>(smem_raw), first, blocks, begin, end)) return;
     cx.arena = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(P.arena), 0, (int)P.arena_bytes, 0x00020000);
     cx.arena_base = P.arena;
   }
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
   auto each_block = [&](auto&& f) { for_all_items<PREFIX_LOOP_BLOCKS>(f, first, blocks); };
   auto moved = [](const auto* p, size_t bytes) { return reinterpret_cast<decltype(p)>(reinterpret_cast<const char*>(p) + bytes); };
 
-  for (int l = 0; l < layers; l++) {
+  for (int l = begin; l < end; l++) {
     {  // ---- attention, whole prefix visible ---------------------------------------------------------
       const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
       AttnParams a = F.att;
@@ -199,6 +199,8 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       bar.arrive();
     }
   }
+  const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
+  bar.done_some(F.sync, F.most_blocks, first, end);
 }
 
 constexpr int max_int(int a, int b) { return a > b ? a : b; }
@@ -334,11 +336,12 @@ bool prefix_loop_takes(int variant, const PrefixLoopParams& P, int blocks) {
 
 hipError_t launch_prefix_loop(hipStream_t s, int variant, const PrefixLoopParams& P, PrefixLoopParams* d_params, int blocks) {
   if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0 || !prefix_loop_takes(variant, P, blocks)) return hipErrorInvalidValue;
+  int launch = 0;
+  const int launches = prefix_loop_launches(P), pieces = std::max((int)sizeof(PrefixLoopParams) / 4, (GB_WORDS - GB_START) / 4 * launches);
+  hipLaunchKernelGGL(prefix_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, launches);
+  hipError_t e = hipGetLastError();
   const Kernel k = kernel_for(variant);
-  constexpr int pieces = (int)sizeof(PrefixLoopParams) / 4 > (GB_WORDS - GB_START) / 4 ? (int)sizeof(PrefixLoopParams) / 4 : (GB_WORDS - GB_START) / 4;
-  hipLaunchKernelGGL(prefix_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, P.sync);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  void* args[] = {&d_params};
-  return hipLaunchKernel(k.f, dim3(blocks), dim3(PL_THREADS), args, k.smem, s);
+  void* args[] = {&d_params, &launch};
+  for (; launch < launches && e == hipSuccess; launch++) e = hipLaunchKernel(k.f, dim3(blocks), dim3(PL_THREADS), args, k.smem, s);
+  return e;
 }

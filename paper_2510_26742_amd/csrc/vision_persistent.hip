@@ -68,27 +68,27 @@ constexpr int vision_smem() {
 
 constexpr int PREP_THREADS = 256;
 static_assert(sizeof(VisionLoopParams) % 4 == 0 && (GB_WORDS - GB_START) % 4 == 0, "whole pieces");
-// parameter block to device memory and barrier words to zero (the error word, first, stays as it is)
-__global__ __launch_bounds__(PREP_THREADS) void vision_loop_prepare_kernel(VisionLoopParams P, VisionLoopParams* dst, unsigned* sync) {
+// parameter block to device memory and barrier words to zero
+__global__ __launch_bounds__(PREP_THREADS) void vision_loop_prepare_kernel(VisionLoopParams P, VisionLoopParams* dst, int launches) {
   const unsigned i = blockIdx.x * PREP_THREADS + threadIdx.x;
   if (i < sizeof(VisionLoopParams) / 4) reinterpret_cast<unsigned*>(dst)[i] = reinterpret_cast<const unsigned*>(&P)[i];
-  if (i < (GB_WORDS - GB_START) / 4) reinterpret_cast<uint4*>(sync + GB_START)[i] = uint4{0u, 0u, 0u, 0u};
+  gb_clear(P.sync, launches, i);
 }
 
 template <int VIEWS>
 __global__ __launch_bounds__(64 * Cfg<VIEWS>::WAVES) __attribute__((amdgpu_waves_per_eu(Cfg<VIEWS>::WAVES / 4, Cfg<VIEWS>::WAVES / 4)))
-void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
+void vision_loop_kernel(const VisionLoopParams* __restrict__ params, int launch) {
   using C = Cfg<VIEWS>;
   using Cx = PersistCtxT<true, false>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const ParamsPtr<VisionLoopParams> Pg = (ParamsPtr<VisionLoopParams>)params;
   GridBarrierT<false> bar;
   Cx cx;
-  int layers, first, blocks;
+  int begin, end, first, blocks;   // end: of this launch's layers
   {
     const VisionLoopParams& P = fresh<VisionLoopParams>(Pg);
-    layers = P.layers;
-    if (!bar.init_some(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == LEADER_RANK, P.most_blocks, reinterpret_cast<unsigned*>(smem_raw), first, blocks)) return;   // (no item but at two views in the attention)
+    end = P.layers;
+    if (!bar.init_some(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == LEADER_RANK, P.most_blocks, launch, reinterpret_cast<unsigned*>(smem_raw), first, blocks, begin, end)) return;   // (no item but at two views in the attention)
     cx.arena = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(P.arena), 0, (int)P.arena_bytes, 0x00020000);
     cx.arena_base = P.arena;
   }
@@ -136,7 +136,7 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
   const bool all = blocks == VISION_LOOP_BLOCKS;   // fewer than all of the grid share the items of all and read nothing ahead
   if (all && rank >= READER_RANK && rank < LEADER_RANK) {
     unsigned fold = 0;
-    for (int op = 0; op < 5 * layers; op++) {   // QKV, attention, O, up, down
+    for (int op = 5 * begin; op < 5 * end; op++) {   // QKV, attention, O, up, down
       const int l = op / 5, k = op - l * 5;
       if constexpr (C::READERS_ATTEND) {
         if (k == 1) {
@@ -147,7 +147,7 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
       if (k == 0 && rank == READER_RANK) clear_padding(l, (int)blockIdx.x & 7, 8);
       bar.arrive();   // nobody waits for what is read here
       // QKV, attention: up.  O, up: down.  Down: the next layer's QKV and O, and where the attention leaves no time to read a part of its up
-      for (int i = 0; i < (k < 4 ? 1 : l + 1 == layers ? 0 : C::READERS_ATTEND ? 3 : 2); i++) {
+      for (int i = 0; i < (k < 4 ? 1 : l + 1 == end ? 0 : C::READERS_ATTEND ? 3 : 2); i++) {
         // part num of den of what the blocks of this die will ask for, in gemm_stream_body's order of items
         const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
         const GemmParams& g = k < 2 || i == 2 ? F.up : k < 4 ? F.down : i == 1 ? F.o : F.qkv;
@@ -170,7 +170,7 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
     return;
   }
 
-  for (int l = 0; l < layers; l++) {
+  for (int l = begin; l < end; l++) {
     if (!all) clear_padding(l, first, blocks);
     {  // ---- LN -> QKV, keys and values in the attention's fragment order ----------------------------
       const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
@@ -235,6 +235,8 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
       }
     }
   }
+  const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
+  bar.done_some(F.sync, F.most_blocks, first, end);
 }
 
 struct Kernel { const void* f; int threads, smem; };
@@ -338,11 +340,12 @@ bool vision_loop_takes(int views, const VisionLoopParams& P, int blocks) {
 
 hipError_t launch_vision_loop(hipStream_t s, int views, const VisionLoopParams& P, VisionLoopParams* d_params, int blocks) {
   if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0 || !vision_loop_takes(views, P, blocks)) return hipErrorInvalidValue;
-  constexpr int pieces = (int)sizeof(VisionLoopParams) / 4 > (GB_WORDS - GB_START) / 4 ? (int)sizeof(VisionLoopParams) / 4 : (GB_WORDS - GB_START) / 4;
-  hipLaunchKernelGGL(vision_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, P.sync);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  int launch = 0;
+  const int launches = vision_loop_launches(P), pieces = std::max((int)sizeof(VisionLoopParams) / 4, (GB_WORDS - GB_START) / 4 * launches);
+  hipLaunchKernelGGL(vision_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, launches);
+  hipError_t e = hipGetLastError();
   const Kernel k = kernel_for(views);
-  void* args[] = {&d_params};
-  return hipLaunchKernel(k.f, dim3(blocks), dim3(k.threads), args, k.smem, s);
+  void* args[] = {&d_params, &launch};
+  for (; launch < launches && e == hipSuccess; launch++) e = hipLaunchKernel(k.f, dim3(blocks), dim3(k.threads), args, k.smem, s);
+  return e;
 }
