@@ -28,7 +28,7 @@
  *    also inside the captured graph; work enqueued on `hip_stream` after the call is ordered after both.
  *    pi0_infer and pi0_prefill run the vision tower (1 .. 3 views of 256 tokens) and the prefix's layers (bf16; with the full
  *    model's feed-forward 193 .. 320, 385 .. 576 and 641 .. 768 tokens) as two more, at the full model's widths (launches otherwise,
- *    same bits; a ctx that has had two-stream frames launches one kernel per operation in pi0_prefill).
+ *    same bits; so does pi0_prefill while the denoise of a two-stream frame of its ctx is under way).
  *    pi0_infer's wait for all of their blocks as well.  pi0_prefill's ask for no residency: they go on with the blocks that are
  *    there 25 us after the last one came (up to 25 us x 256 / n the first time, with n of 256), do one layer with those, and try
  *    again for three, for nine and for the rest, each time doing all that are left once all blocks are there.

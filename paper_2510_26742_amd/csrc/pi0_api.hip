@@ -1669,12 +1669,21 @@ int frame_loop_blocks(const pi0_ctx* c, int P) {
 // no longer on the launches than on the replay (11 kernels 32 us either way; 118 kernels 400 and 65).
 constexpr int DIRECT_LAUNCHES = 16;
 
+// The loops' buffers lie where the expert's do, and the denoise of a two-stream frame may still be on its way when a plain prefill comes on the other
+// stream: that one takes the launches, as does one that is captured, which may be replayed beside a later frame.
+bool no_frame_under_way(pi0_ctx* c, hipStream_t s) {
+  if (c->ev_prefill[0] == nullptr) return true;
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  bool done = s == nullptr || (hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone);
+  for (int i = 0; i < 2 && done; i++) done = c->ev_denoise[i] == nullptr || hipEventQuery(c->ev_denoise[i]) == hipSuccess;
+  if (!done) (void)hipGetLastError();   // "not ready" is an answer
+  return done;
+}
+
 // Runs `kind` through a cached graph (null in the map: launches), or eagerly.
 int execute(pi0_ctx* c, int kind, int n_views, int n_prompt, hipStream_t s, int slot_w = -1, int slot_r = -1, bool read_ahead = true) {
   const int P = n_views * c->d.T + n_prompt;
-  // Not beside the denoise of a two-stream frame: the loops' buffers lie where the expert's do, and that denoise may still be on its
-  // way when the next plain prefill comes on the other stream
-  const bool prefill_loops = kind == KIND_INFER || (kind == KIND_PREFILL && c->ev_prefill[0] == nullptr);
+  const bool prefill_loops = kind == KIND_INFER || (kind == KIND_PREFILL && slot_w < 0 && no_frame_under_way(c, s));   // (a frame's own prefill names its slot)
   if (slot_w < 0) slot_w = c->cur_slot;
   if (slot_r < 0) slot_r = c->cur_slot;
   // the second stream of the read-ahead kernel exists only where the per-operation launches will use it (a stream

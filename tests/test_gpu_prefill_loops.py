@@ -66,11 +66,12 @@ def test_prefill_beside_another_contexts_denoise():
 
 @pytest.mark.gpu
 def test_prefill_after_frames():
-    """Once a context has had two-stream frames its plain prefill is launches again: a frame's denoise may still be on its way on the other stream."""
-    case = Case(CFG)
+    """While the denoise of a two-stream frame may be on its way on the other stream, a plain prefill is launches; once it is done, the persistent kernels again."""
+    case = Case(dataclasses.replace(CFG, vis_layers=9))
     try:
         img, st, nz, ids = case.inputs(1, 7)
         want = case.prefill_and_denoise(img, st, nz, ids)
+        before = min(timed(case, 1, (img, st, nz, ids)) for _ in range(5))
         side = torch.cuda.Stream(device=case.dev)
         d_img, d_st, d_nz, d_ids = case.to_dev(img, st, nz, ids)
         act = [torch.empty((CFG.chunk, CFG.action_dim), device=case.dev) for _ in range(3)]
@@ -82,6 +83,12 @@ def test_prefill_after_frames():
         for a in act:
             np.testing.assert_array_equal(a.cpu().numpy(), want)
         np.testing.assert_array_equal(case.prefill_and_denoise(img, st, nz, ids), want)
+        after = min(timed(case, 1, (img, st, nz, ids)) for _ in range(5))
+        case.m.pi0_tune("pvl=0,ppl=0")
+        launches = min(timed(case, 1, (img, st, nz, ids)) for _ in range(5))
+        case.m.pi0_tune("pvl=1,ppl=1")
+        say(f"[gpu] pi0_prefill before frames {before:.3f} ms, after them {after:.3f}, as launches {launches:.3f}")
+        assert after - before < 0.5 * (launches - before)
     finally:
         case.close()
 
