@@ -657,7 +657,8 @@ __device__ __forceinline__ void gemm_cols_body(const GemmParams& p, const Cx& cx
 #pragma unroll
       for (int j = 0; j < NT; j++) {
         // The ninth block's accumulators are ordinary vector registers, written down as such (the compiler keeps them all in the other
-        // half, 256 of a lane, and spills)
+        // half, 256 of a lane, and spills).  It leaves no wait states behind them, so nothing but the next product may name those registers here:
+        // test_gpu_cols_gemm.py looks at the code as built
         if constexpr (b < 8) acc[j][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[s][j], xf[f % RX], acc[j][b], 0, 0, 0);
         else asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc[j][b]) : "v"(wr[s][j]), "v"(xf[f % RX]));
         __builtin_amdgcn_sched_barrier(0);   // this order
