@@ -15,13 +15,13 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(e));
 }
 
-// Sum over groups of 8 adjacent lanes with DPP (no LDS traffic): xor 1, xor 2 inside quads, then
-// the mirror inside each half row pairs quad 0 with quad 1.  Every lane of the group gets the sum.
 // v of this lane and of the one with bit 3 the other way: a rotation by half of the row of 16 (a shuffle goes through LDS, and the lane's number for it
 // stays in a register of a persistent kernel throughout)
 __device__ __forceinline__ float add_xor8(float v) {
   return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xf, 0xf, true));
 }
+// Sum over groups of 8 adjacent lanes with DPP (no LDS traffic): xor 1, xor 2 inside quads, then
+// the mirror inside each half row pairs quad 0 with quad 1.  Every lane of the group gets the sum.
 __device__ __forceinline__ float sum8_dpp(float v) {
   v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
   v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true));
