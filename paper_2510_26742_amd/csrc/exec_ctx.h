@@ -110,7 +110,7 @@ enum {
   GB_START = 32,       // start-up counter: blocks registered
   GB_TICKETS = 33,     // init_some: blocks that asked to take part, | GB_CLOSED once it goes on without the others
   GB_TAKEN = 34,       // init_some: blocks that take part, once that is decided
-  GB_NEXT = 35,        // init_some, of the first launch's words: layers that the launches before have done
+  GB_NEXT = 35,        // init_some, of the first launch's words: layers that the launches before have done, or GB_ALL_DONE
   GB_MEMBERS = 64,     // + 32 x: blocks resident on die x
   GB_LEADER = 320,     // + 32 x: 1 + index of the block that leads die x (+ 2^16 if it asked to)
   GB_DONE = 576,       // + 32 y + x: last epoch that die x completed, as told to die y (one cache line per reading die)
@@ -124,9 +124,13 @@ constexpr long long GB_WINDOW = 2500;   // of the 100 MHz counter: 25 us from on
                                         // below, which knows nothing of the device yet, waits 25 us x 256 / n when n have come, half of what a layer then takes them
 // A loop that goes on with the blocks that have come is launched GB_LAUNCHES times, with barrier words for each.  A launch that has all blocks does all
 // layers that are left, another one no more than gb_quota of them, and then lets go of its compute units: a moment in which other work holds
-// the chip costs one layer on the few units that were free, and a kernel that waits for those units gets them.
-constexpr int GB_LAUNCHES = 4;
-__host__ __device__ constexpr int gb_quota(int launch) { return launch == 0 ? 1 : launch == 1 ? 3 : launch == 2 ? 9 : 1 << 30; }
+// the chip costs one layer on the few units that were free, a longer one about as much again as it lasted, and a kernel that waits for those
+// units gets them.  pi0_prefill of 27 / 3 layers (1.8 ms alone) beside a loop on 224 units for 3 ms: 8.8 ms with one launch, 5.7 with four of 1, 3, 9 and
+// the rest, 9.0 with three of 1, 4 and the rest, 6.3 with these.  A launch that finds nothing left looks at one word and ends: eight of them in
+// 2 views + 21 tokens and two denoises, 12073 -> 12074 us (runs differ by 0.6 %), in shallower ones +0 .. +2 us.
+constexpr int GB_LAUNCHES = 5;
+constexpr unsigned GB_ALL_DONE = 1u << 16;
+__host__ __device__ constexpr int gb_quota(int launch) { return launch < GB_LAUNCHES - 1 ? 1 << launch : 1 << 30; }
 
 // Barrier words to zero, in a launch ahead of the kernel's
 __device__ __forceinline__ void gb_clear(unsigned* sync, int launches, unsigned i) {   // piece i of the words of that many launches; the error words stay as they are
@@ -181,11 +185,12 @@ struct GridBarrierT {
   }
 
   // As init, for kernels whose operations any number of blocks can share out: goes on as soon as all blocks of the grid have come, or with fewer once
-  // none has come for GB_WINDOW, so that no wait depends on compute units that other work holds.  A block that
-  // comes later takes no part (false: it ends), nor does one whose wait ran out here, nor any once a wait of one of the launches has (the error words stay raised).  most: with no more than this many, at once; 0: init, all of the grid (a round trip
-  // less, and one launch).  words: of the first of the launches, of which this one is number `launch`.  first, stride: this block's items are first, first + stride, ..
-  // (all of the grid: blockIdx.x, gridDim.x).  begin, end: the layers to do; end: all there are, before.  pi0_prefill, which promises its caller no resident grid,
-  // runs its loops so: 2 views + 21 tokens and two denoises, as launches -> so, 12.16 -> 11.87 ms.  shared: four words of shared memory that nothing else uses yet.
+  // none has come for GB_WINDOW, so that no wait depends on compute units that other work holds.  A block that comes later takes no part (false: it
+  // ends), nor does one whose wait ran out here, nor any once a wait of one of the launches has (the error words stay raised).
+  // most: with no more than this many, at once; 0: init, all of the grid (a round trip less, and one launch).  words: of the first of the launches, of
+  // which this one is number `launch`.  first, stride: this block's items are first, first + stride, .. (all of the grid: blockIdx.x, gridDim.x).
+  // begin, end: the layers to do; end: all there are, before.  shared: four words of shared memory that nothing else uses yet.
+  // pi0_prefill, which promises its caller no resident grid, runs its loops so: 2 views + 21 tokens and two denoises, as launches -> so, 12.16 -> 11.87 ms.
   __device__ __forceinline__ bool init_some(unsigned* words, unsigned limit, bool may_lead, unsigned most, int launch, unsigned* shared, int& first, int& stride, int& begin,
                                             int& end) {
     // (opaque: the compiler knows these values as the same in all lanes, drops the builtin and then has addresses in vector registers.  Not
@@ -253,7 +258,10 @@ struct GridBarrierT {
     begin = (int)scalar(shared[3]);
     __syncthreads();
     if (n == 0u) return false;
-    if (n != gridDim.x) end = end - begin > gb_quota(launch) ? begin + gb_quota(launch) : end;
+    const bool rest = n == gridDim.x || end - begin <= gb_quota(launch);
+    if (!rest) end = begin + gb_quota(launch);
+    // where the next launch goes on: written already here (every block that takes part has read the word, and one that comes later finds nothing to do)
+    if (first == 0 && threadIdx.x == 0) st_dev(as_global(words) + GB_NEXT, rest ? GB_ALL_DONE : (unsigned)end);
     members = ld_dev(&w[GB_MEMBERS + 32 * xcc]);
     leader = (ld_dev(&w[GB_LEADER + 32 * xcc]) & 0xffffu) == (unsigned)blockIdx.x + 1u;
     present = 0;
@@ -261,10 +269,8 @@ struct GridBarrierT {
     return true;
   }
 
-  // One block of those that init_some let in, at the end of its last layer: where the next launch goes on
-  __device__ __forceinline__ static void done_some(unsigned* words, unsigned most, int first, int end) {
-    if (most != 0u && first == 0 && threadIdx.x == 0) st_dev(as_global(words) + GB_NEXT, (unsigned)end);
-  }
+  // Ahead of everything else in a launch behind the first: nothing is left for it
+  __device__ __forceinline__ static bool all_done(const unsigned* words, int launch) { return launch != 0 && ld_dev(as_global(words) + GB_NEXT) == GB_ALL_DONE; }
 
   // the error word is looked at on every 64th poll: behind each poll it would double the time between two polls
   __device__ __forceinline__ bool give_up(unsigned spins) const {

@@ -1666,8 +1666,9 @@ int frame_loop_blocks(const pi0_ctx* c, int P) {
 
 // Calls of at most this many kernels are launched one by one in graph mode too: a replay begins 8 us later than a kernel (pi0_denoise over two layers 480 us by
 // graph, 471 by launches; pi0_infer over two 708 and 701, over eighteen 6271 and 6250, 11 kernels), and up to here the host spends
-// no longer on the launches than on the replay (11 kernels 32 us either way; 118 kernels 400 and 65).
-constexpr int DIRECT_LAUNCHES = 16;
+// no longer on the launches than on the replay (11 kernels 32 us either way; 118 kernels 400 and 65).  pi0_prefill has 17, eight of which
+// mostly end at once; captured, a new shape's first call takes 0.35 ms more.
+constexpr int DIRECT_LAUNCHES = 20;
 
 // The loops' buffers lie where the expert's do, and the denoise of a two-stream frame may still be on its way when a plain prefill comes on the other
 // stream: that one takes the launches, as does one that is captured, which may be replayed beside a later frame.

@@ -64,7 +64,8 @@ __global__ __launch_bounds__(PREP_THREADS) void prefix_loop_prepare_kernel(Prefi
 }
 
 template <int VARIANT>
-__global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefix_loop_kernel(const PrefixLoopParams* __restrict__ params, int launch) {
+__global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefix_loop_kernel(const PrefixLoopParams* __restrict__ params, const unsigned* words, int launch) {
+  if (GridBarrierT<false>::all_done(words, launch)) return;
   using C = typename Variants<VARIANT>::T;
   constexpr bool LEAN = C::GU_HEIGHT != 0;   // (gate||up takes every register)
   using Cx = PersistCtxT<true, false, LEAN>;
@@ -199,8 +200,6 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
       bar.arrive();
     }
   }
-  const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
-  bar.done_some(F.sync, F.most_blocks, first, end);
 }
 
 constexpr int max_int(int a, int b) { return a > b ? a : b; }
@@ -341,7 +340,8 @@ hipError_t launch_prefix_loop(hipStream_t s, int variant, const PrefixLoopParams
   hipLaunchKernelGGL(prefix_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, launches);
   hipError_t e = hipGetLastError();
   const Kernel k = kernel_for(variant);
-  void* args[] = {&d_params, &launch};
+  const unsigned* words = P.sync;
+  void* args[] = {&d_params, &words, &launch};
   for (; launch < launches && e == hipSuccess; launch++) e = hipLaunchKernel(k.f, dim3(blocks), dim3(PL_THREADS), args, k.smem, s);
   return e;
 }

@@ -77,7 +77,8 @@ __global__ __launch_bounds__(PREP_THREADS) void vision_loop_prepare_kernel(Visio
 
 template <int VIEWS>
 __global__ __launch_bounds__(64 * Cfg<VIEWS>::WAVES) __attribute__((amdgpu_waves_per_eu(Cfg<VIEWS>::WAVES / 4, Cfg<VIEWS>::WAVES / 4)))
-void vision_loop_kernel(const VisionLoopParams* __restrict__ params, int launch) {
+void vision_loop_kernel(const VisionLoopParams* __restrict__ params, const unsigned* words, int launch) {
+  if (GridBarrierT<false>::all_done(words, launch)) return;
   using C = Cfg<VIEWS>;
   using Cx = PersistCtxT<true, false>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -235,8 +236,6 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params, int launch)
       }
     }
   }
-  const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
-  bar.done_some(F.sync, F.most_blocks, first, end);
 }
 
 struct Kernel { const void* f; int threads, smem; };
@@ -345,7 +344,8 @@ hipError_t launch_vision_loop(hipStream_t s, int views, const VisionLoopParams& 
   hipLaunchKernelGGL(vision_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, launches);
   hipError_t e = hipGetLastError();
   const Kernel k = kernel_for(views);
-  void* args[] = {&d_params, &launch};
+  const unsigned* words = P.sync;
+  void* args[] = {&d_params, &words, &launch};
   for (; launch < launches && e == hipSuccess; launch++) e = hipLaunchKernel(k.f, dim3(blocks), dim3(k.threads), args, k.smem, s);
   return e;
 }

@@ -167,7 +167,7 @@ def test_a_chip_that_is_busy_for_a_moment_costs_prefill_no_more_than_layers():
             np.testing.assert_array_equal(act.cpu().numpy(), want_a)
             np.testing.assert_array_equal(b.denoise_only(ib[1], ib[2]), want_b)
         say(f"[gpu] pi0_prefill alone {alone:.2f} ms, beside the frames " + ", ".join(f"{t:.2f} (frame done after {f:.2f})" for t, f in zip(beside, frame)))
-        assert min(beside[1:]) < max(frame[1:]) + 2.4 * alone   # 1.5 (launches of a layer, three, nine); one launch of all layers: 3.2
+        assert min(beside[1:]) < max(frame[1:]) + 2.4 * alone   # measured 1.8; with one launch of all layers 3.2
         a.m.pi0_device_status(a.stream)
         b.m.pi0_device_status(b.stream)
     finally:
