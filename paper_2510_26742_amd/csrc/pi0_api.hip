@@ -1676,7 +1676,12 @@ bool no_frame_under_way(pi0_ctx* c, hipStream_t s) {
   if (c->ev_prefill[0] == nullptr) return true;
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   bool done = s == nullptr || (hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone);
+  // (a query ends a capture that any other stream or thread has going in global mode, unless this thread says that it knows what it does)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  done = done && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  const bool exchanged = done;
   for (int i = 0; i < 2 && done; i++) done = c->ev_denoise[i] == nullptr || hipEventQuery(c->ev_denoise[i]) == hipSuccess;
+  if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
   if (!done) (void)hipGetLastError();   // "not ready" is an answer
   return done;
 }

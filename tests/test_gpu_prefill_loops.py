@@ -1,6 +1,7 @@
 """pi0_prefill runs the vision tower and the prefix's layers as the persistent kernels of pi0_infer, which go on with the blocks that are resident:
 the cache that it leaves gives the bits of the launches (pvl=0, ppl=0) with every number of blocks that takes part, at tile edges of every
 variant, and beside a kernel of another context that holds the chip."""
+import ctypes
 import dataclasses
 
 import numpy as np
@@ -104,6 +105,39 @@ def timed(case, n_views, inputs, calls=1):
     end.record(case.stream)
     end.synchronize()
     return begin.elapsed_time(end)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", ["global", "thread local", "relaxed"])
+def test_prefill_after_frames_leaves_another_streams_capture_alone(mode):
+    """Whether a frame's denoise is under way is asked of an event, and such a question ends a capture in global mode, whosever it is."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    case = Case(CFG)
+    try:
+        img, st, nz, ids = case.inputs(1, 7)
+        want = case.prefill_and_denoise(img, st, nz, ids)
+        side, captured = (torch.cuda.Stream(device=case.dev) for _ in range(2))
+        d_img, d_st, d_nz, d_ids = case.to_dev(img, st, nz, ids)
+        act = torch.empty((CFG.chunk, CFG.action_dim), device=case.dev)
+        for _ in range(2):   # (its launches become a graph here, one for each copy of the cache)
+            case.m.pi0_stream_frame(d_img, 1, d_ids, 7, d_st, d_nz, act, case.stream, side)
+            case.m.pi0_prefill(d_img, 1, d_ids, 7, case.stream)
+        torch.cuda.synchronize()
+        for under_way in (False, True):
+            say(f"[gpu] prefill beside a capture in {mode} mode, frame under way: {under_way}")
+            case.m.pi0_stream_frame(d_img, 1, d_ids, 7, d_st, d_nz, act, case.stream, side)
+            if not under_way:
+                torch.cuda.synchronize()
+            graph = ctypes.c_void_p()
+            assert hip.hipStreamBeginCapture(ctypes.c_void_p(captured.cuda_stream), ["global", "thread local", "relaxed"].index(mode)) == 0
+            case.m.pi0_prefill(d_img, 1, d_ids, 7, case.stream)
+            assert hip.hipStreamEndCapture(ctypes.c_void_p(captured.cuda_stream), ctypes.byref(graph)) == 0
+            assert hip.hipGraphDestroy(graph) == 0
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(act.cpu().numpy(), want)
+            np.testing.assert_array_equal(case.denoise_only(st, nz), want)
+    finally:
+        case.close()
 
 
 @pytest.mark.gpu
