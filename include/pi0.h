@@ -11,7 +11,7 @@
  * prefix layer only produces keys/values), Section 4.2 (fused gated MLP) and Section 4.4 (norm
  * statistics applied after accumulation) are done inside the library at load time / in kernels.
  * Section 3.1's graph replay: pi0_prefill / pi0_denoise / pi0_infer record their kernel
- * sequence into a HIP graph on first use of a shape and replay it afterwards; a sequence of no more than 20 kernels,
+ * sequence into a HIP graph on first use of a shape and replay it afterwards; a sequence of no more than 16 kernels,
  * which is what the persistent kernels below leave of most, is launched as it is.
  *
  * Conventions
@@ -29,12 +29,12 @@
  *    pi0_infer and pi0_prefill run the vision tower (1 .. 3 views of 256 tokens) and the prefix's layers (bf16; with the full
  *    model's feed-forward 193 .. 320, 385 .. 576 and 641 .. 768 tokens) as two more, at the full model's widths (launches otherwise,
  *    same bits; so does pi0_prefill while the denoise of a two-stream frame of its ctx is under way).
- *    pi0_infer's wait for all of their blocks as well.  pi0_prefill's ask for no residency: they go on with the blocks that are
- *    there 25 us after the last one came (up to 25 us x 256 / n the first time, with n of 256), do one layer with those, and try
- *    again for two, four, eight and the rest, each time doing all that are left once all blocks are there.
+ *    pi0_infer's wait for all of their blocks as well.  pi0_prefill's ask for no residency: they go on with the n blocks that are
+ *    there 25 us x 256 / n after the last one came, the fewer the slower, and the others join in front of a later layer (of the first
+ *    16) as compute units become free for them.
  *    Do not run other kernels that occupy whole compute units for long beside pi0_denoise / pi0_infer:
  *    the persistent kernels' blocks wait for each other (bounded, see pi0_device_status).  pi0_prefill of another ctx is such a kernel
- *    for the time of a tower or of a prefix (milliseconds), or of the layers above where it shares the chip.
+ *    for the time of a tower or of a prefix: milliseconds, and 256 / n times that where it gets n blocks only.
  *  - Return value: 0 on success, a negative PI0_E* code otherwise.  Argument checks happen before
  *    any GPU call, so error paths touch no GPU state.  Nothing throws or aborts across the ABI.
  *  - Calls on one ctx must not overlap in time (one workspace, one set of activations); the only

@@ -134,9 +134,9 @@ int pi0_clock_sample(long long* d_out, void* hip_stream);
 int pi0_read_ahead_probe(const void* d_buf, size_t bytes, int layers, int steps, int lead, const int* d_progress,
                          long long wait_ticks, int blocks, unsigned* d_sink, double* h_ms, void* hip_stream);
 
-/* Number of kernel launches of one pi0_infer's graph for the given shape (0 on bad arguments); before the weights are loaded, on a device
- * that runs none of the persistent kernels.  The copies of the inputs before it and of the actions behind it (a launch each) and the
- * read-ahead kernel on the ctx's own stream are not counted. */
+/* Number of kernel launches of one pi0_infer for the given shape (0 on bad arguments); before the weights are loaded, on a device
+ * that runs none of the persistent kernels.  The copies of the inputs before it and of the actions behind it (a launch each; where the
+ * denoise is the persistent kernel, they are done by its two) and the read-ahead kernel on the ctx's own stream are not counted. */
 int pi0_kernel_count(const pi0_ctx* ctx, int n_views, int n_prompt);
 
 /*
@@ -217,7 +217,7 @@ int pi0_set_loop_trace(pi0_ctx* ctx, long long* d_trace, int ops_cap);
  * one persistent kernel, 0: one launch per operation) and pra (what the persistent kernel's blocks without a work item read
  * ahead: 1 gate||up, 2 down, 4 next layer's QKV, 8 next layer's O weights during the attention; 16 this layer's O weights
  * during QKV; 32: every block what blocks of its own die will ask for), pvl and ppl (pi0_prefill and pi0_infer: 1 the vision tower,
- * the prefix's layers as one persistent kernel, 0 as launches), pmb (1 .. 256: most blocks of these two that take part), spl (1 .. 2^20, the default: polls
+ * the prefix's layers as one persistent kernel, 0 as launches), pmb (1 .. 256: most blocks of these two that take part at once), spl (1 .. 2^20, the default: polls
  * that a wait inside a persistent kernel lasts at most) and psb (blocks of the persistent kernel inside a two-stream frame;
  * 0: per-operation launches there, -1: chosen from the prefix size).
  * Drops every captured graph, so the next call of a shape captures again.  Must not be called while work of this

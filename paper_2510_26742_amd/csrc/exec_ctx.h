@@ -108,9 +108,8 @@ __device__ __forceinline__ unsigned lds_address(const unsigned char* p) {
 enum {
   GB_ERR = 0,          // != 0: a bounded wait ran out
   GB_START = 32,       // start-up counter: blocks registered
-  GB_TICKETS = 33,     // init_some: blocks that asked to take part, | GB_CLOSED once it goes on without the others
-  GB_TAKEN = 34,       // init_some: blocks that take part, once that is decided
-  GB_NEXT = 35,        // init_some, of the first launch's words: layers that the launches before have done, or GB_ALL_DONE
+  GB_TICKETS = 33,     // init_some: blocks that asked to take part, + GB_BACK for each that did in the turn before, | GB_CLOSED once it goes on without the others
+  GB_TAKEN = 34,       // init_some: blocks that take part, once that is decided, | GB_REST if they do all that is left
   GB_MEMBERS = 64,     // + 32 x: blocks resident on die x
   GB_LEADER = 320,     // + 32 x: 1 + index of the block that leads die x (+ 2^16 if it asked to)
   GB_DONE = 576,       // + 32 y + x: last epoch that die x completed, as told to die y (one cache line per reading die)
@@ -119,23 +118,19 @@ enum {
   GB_MAX_BLOCKS = 256, // largest grid
   GB_WORDS = GB_FLAGS + 8 * GB_MAX_BLOCKS
 };
-constexpr unsigned GB_CLOSED = 1u << 16;
-constexpr long long GB_WINDOW = 2500;   // of the 100 MHz counter: 25 us from one block to the next (on an otherwise idle device all come within 10); the first of the launches
-                                        // below, which knows nothing of the device yet, waits 25 us x 256 / n when n have come, half of what a layer then takes them
-// A loop that goes on with the blocks that have come is launched GB_LAUNCHES times, with barrier words for each.  A launch that has all blocks does all
-// layers that are left, another one no more than gb_quota of them, and then lets go of its compute units: a moment in which other work holds
-// the chip costs one layer on the few units that were free, a longer one about as much again as it lasted, and a kernel that waits for those
-// units gets them.  pi0_prefill of 27 / 3 layers (1.8 ms alone) beside a loop on 224 units for 3 ms: 8.8 ms with one launch, 5.7 with four of 1, 3, 9 and
-// the rest, 9.0 with three of 1, 4 and the rest, 6.3 with these.  A launch that finds nothing left looks at one word and ends: eight of them in
-// 2 views + 21 tokens and two denoises, 12073 -> 12074 us (runs differ by 0.6 %), in shallower ones +0 .. +2 us.
-constexpr int GB_LAUNCHES = 5;
-constexpr unsigned GB_ALL_DONE = 1u << 16;
-__host__ __device__ constexpr int gb_quota(int launch) { return launch < GB_LAUNCHES - 1 ? 1 << launch : 1 << 30; }
+constexpr unsigned GB_CLOSED = 1u << 16, GB_BACK = 1u << 20, GB_REST = 1u << 16;   // (more than any grid)
+constexpr long long GB_WINDOW = 2500;   // of the 100 MHz counter: 25 us, within which the blocks of a launch on an otherwise idle device have long come (10)
+// A loop that goes on with the blocks that have come does so in turns of a layer, with barrier words for each; the blocks that have come meanwhile join in
+// between.  With all of the grid a turn does all layers that are left, and so does the last one.  So a moment in which other work holds the chip costs no
+// more than that and a layer on the few units that were free.  pi0_prefill of 27 / 3 layers (1.8 ms alone) beside a loop on 224 units for 3 ms:
+// 8.8 ms with the blocks of the start throughout, 6.3 with a kernel that ends and is launched four more times, of which the launches that find nothing
+// left cost 1.7 us each (a prefill over two layers 222 -> 236 us), 4.6 with these turns (222 -> 223).
+constexpr int GB_TURNS = 16;
 
 // Barrier words to zero, in a launch ahead of the kernel's
-__device__ __forceinline__ void gb_clear(unsigned* sync, int launches, unsigned i) {   // piece i of the words of that many launches; the error words stay as they are
+__device__ __forceinline__ void gb_clear(unsigned* sync, int turns, unsigned i) {   // piece i of the words of that many turns; the error words stay as they are
   constexpr unsigned PIECES = (GB_WORDS - GB_START) / 4;
-  if (i < PIECES * (unsigned)launches) reinterpret_cast<uint4*>(sync + i / PIECES * GB_WORDS + GB_START)[i % PIECES] = uint4{0u, 0u, 0u, 0u};
+  if (i < PIECES * (unsigned)turns) reinterpret_cast<uint4*>(sync + i / PIECES * GB_WORDS + GB_START)[i % PIECES] = uint4{0u, 0u, 0u, 0u};
 }
 
 // TRACE: a timeline is recorded (a kernel of its own: the code for it in every operation costs instruction cache).  LEAN: no address of the
@@ -156,6 +151,19 @@ struct GridBarrierT {
   __device__ __forceinline__ static unsigned ld_dev(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
   __device__ __forceinline__ static void st_dev(unsigned* p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+  // (opaque: the compiler knows these values as the same in all lanes, drops the builtin and then has addresses in vector registers.  Not
+  // the instruction itself as assembly, in front of which the compiler leaves no wait state for the register that it reads)
+  __device__ __forceinline__ static unsigned scalar(unsigned v) {
+    asm volatile("" : "+v"(v));
+    return (unsigned)__builtin_amdgcn_readfirstlane((int)v);
+  }
+
+  // a constant, made here each time: ahead of a loop that this code is in, it would hold a register throughout
+  __device__ __forceinline__ static unsigned here(unsigned v) {
+    asm volatile("" : "+s"(v));
+    return v;
+  }
+
   // all threads of the block; one counter barrier, after which every block knows who shares its die
   // may_lead: the block is one of those that should lead their die (if a die has none, another one does)
   __device__ __forceinline__ void init(unsigned* words, unsigned limit, bool may_lead) {
@@ -166,7 +174,7 @@ struct GridBarrierT {
     xcc = (unsigned)__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7u;   // XCC_ID, bits 3:0
     unsigned r = 0;
     if (threadIdx.x == 0) {
-      __hip_atomic_fetch_max(&w[GB_LEADER + 32 * xcc], (unsigned)blockIdx.x + 1u + (may_lead ? 1u << 16 : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_max(&w[GB_LEADER + 32 * xcc], here(blockIdx.x + 1u + (may_lead ? 1u << 16 : 0u)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       r = __hip_atomic_fetch_add(&w[GB_MEMBERS + 32 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // both are in place before this block counts as registered
       __hip_atomic_fetch_add(&w[GB_START], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -185,92 +193,109 @@ struct GridBarrierT {
   }
 
   // As init, for kernels whose operations any number of blocks can share out: goes on as soon as all blocks of the grid have come, or with fewer once
-  // none has come for GB_WINDOW, so that no wait depends on compute units that other work holds.  A block that comes later takes no part (false: it
-  // ends), nor does one whose wait ran out here, nor any once a wait of one of the launches has (the error words stay raised).
-  // most: with no more than this many, at once; 0: init, all of the grid (a round trip less, and one launch).  words: of the first of the launches, of
-  // which this one is number `launch`.  first, stride: this block's items are first, first + stride, .. (all of the grid: blockIdx.x, gridDim.x).
-  // begin, end: the layers to do; end: all there are, before.  shared: four words of shared memory that nothing else uses yet.
+  // none has come for GB_WINDOW x grid / n with n there, half of what a layer then takes them at most, so that no wait depends on compute units that other work holds.
+  // A block that comes later waits for the next turn, in front of which the blocks of the one before come here again; one for which none is
+  // left ends (false), and so does one whose wait ran out here, and any once a wait has (the error words stay raised).
+  // most: no more than this many at once; 0: init, all of the grid (a round trip less).  first, stride: this block's items are first, first + stride, ..
+  // (all of the grid: blockIdx.x, gridDim.x).  begin, end: the layers to do.  first, stride, end: before, those of the turn before, 0 at the
+  // start.  shared: four words of shared memory that nothing else uses.
   // pi0_prefill, which promises its caller no resident grid, runs its loops so: 2 views + 21 tokens and two denoises, as launches -> so, 12.16 -> 11.87 ms.
-  __device__ __forceinline__ bool init_some(unsigned* words, unsigned limit, bool may_lead, unsigned most, int launch, unsigned* shared, int& first, int& stride, int& begin,
+  __device__ __forceinline__ bool init_some(unsigned* words, unsigned limit, bool may_lead, unsigned most, unsigned* shared, int layers, int& first, int& stride, int& begin,
                                             int& end) {
-    // (opaque: the compiler knows these values as the same in all lanes, drops the builtin and then has addresses in vector registers.  Not
-    // the instruction itself as assembly, in front of which the compiler leaves no wait state for the register that it reads)
-    auto scalar = [](unsigned v) {
-      asm volatile("" : "+v"(v));
-      return (unsigned)__builtin_amdgcn_readfirstlane((int)v);
-    };
     if (scalar(most) == 0u) {
       init(words, limit, may_lead);
+      if (LEAN) {
+        members = scalar(members);
+        present = scalar(present);
+      }
       first = (int)scalar(blockIdx.x);
       stride = (int)scalar(gridDim.x);
       begin = 0;
+      end = layers;
       return true;
     }
-    w = as_global(words) + launch * GB_WORDS;
     spin_limit = limit;
     epoch = 0;
     trace = nullptr;
     xcc = (unsigned)__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7u;   // XCC_ID, bits 3:0
-    if (threadIdx.x == 0) {
-      if (most > gridDim.x) most = gridDim.x;
-      unsigned r = 0, n = 0, ticket = most;
-      const unsigned done = ld_dev(as_global(words) + GB_NEXT);
-      unsigned failed = 0;
-      for (int k = 0; k < GB_LAUNCHES; k++) failed |= ld_dev(as_global(words) + k * GB_WORDS + GB_ERR);
-      if (done < (unsigned)end && failed == 0u) ticket = __hip_atomic_fetch_add(&w[GB_TICKETS], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (ticket < most) {   // (GB_CLOSED is more than any grid)
-        if (ticket + 1 == most) st_dev(&w[GB_TAKEN], most);
-        __hip_atomic_fetch_max(&w[GB_LEADER + 32 * xcc], (unsigned)blockIdx.x + 1u + (may_lead ? 1u << 16 : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        r = __hip_atomic_fetch_add(&w[GB_MEMBERS + 32 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // both are in place before this block counts as registered
-        __hip_atomic_fetch_add(&w[GB_START], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (thread() == 0u) {
+      const unsigned grid = gridDim.x;
+      if (most > grid) most = grid;
+      unsigned ticket = 0, r = 0, taken = 0, k = (unsigned)end;
+      bool in = false;
+      for (bool back = k != 0u;; back = false, k++) {
+        unsigned* const v = as_global(words) + k * GB_WORDS;
+        const unsigned before = __hip_atomic_fetch_add(&v[GB_TICKETS], back ? here(GB_BACK + 1u) : here(1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ticket = before & (GB_CLOSED - 1u);
+        in = (before & GB_CLOSED) == 0u && ticket < most;
+        const unsigned last = k == GB_TURNS - 1 || (int)k + 1 >= layers ? GB_REST : 0u;
+        if (in) {
+          if (k == 0u && ticket + 1u == most) st_dev(&v[GB_TAKEN], most | (most == grid ? GB_REST : last));
+          __hip_atomic_fetch_max(&v[GB_LEADER + 32 * xcc], here(blockIdx.x + 1u + (may_lead ? 1u << 16 : 0u)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          r = __hip_atomic_fetch_add(&v[GB_MEMBERS + 32 * xcc], here(1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // both are in place before this block counts as registered
+          __hip_atomic_fetch_add(&v[GB_START], here(1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // who closes the count: in the first turn any block that is tired of waiting, later the first one of the turn before, once all of that one are back
+        const bool closes = k == 0u ? in : back && first == 0;
         long long since = (long long)wall_clock64();
         unsigned seen = ticket, spins = 0;
         while (true) {
-          n = ld_dev(&w[GB_TAKEN]);
-          const unsigned started = ld_dev(&w[GB_START]), tickets = ld_dev(&w[GB_TICKETS]);
-          if (n != 0u && started >= n) break;
-          if (tickets != seen) {
-            seen = tickets;
-            since = (long long)wall_clock64();
-          } else if (n == 0u && ((long long)wall_clock64() - since) * (launch == 0 ? tickets : gridDim.x) > GB_WINDOW * gridDim.x) {
-            const unsigned before = __hip_atomic_fetch_or(&w[GB_TICKETS], GB_CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (before < GB_CLOSED) st_dev(&w[GB_TAKEN], before < most ? before : most);
-          }
-          __builtin_amdgcn_s_sleep(2);
-          if (++spins > spin_limit || ld_dev(&w[GB_ERR]) != 0u) {
-            st_dev(&w[GB_ERR], 1u);
-            n = 0;   // takes no part (a stride of one in its place would have every block do all of the work)
+          taken = ld_dev(&v[GB_TAKEN]);   // (all loads of a poll at once)
+          const unsigned started = ld_dev(&v[GB_START]), tickets = ld_dev(&v[GB_TICKETS]), error = ld_dev(&v[GB_ERR]) | (k != 0u ? ld_dev(&v[GB_ERR] - GB_WORDS) : 0u);
+          if (++spins > spin_limit || error != 0u) {
+            st_dev(&v[GB_ERR], here(1u));
+            taken = 0;   // takes no part (a stride of one in its place would have every block do all of the work)
             break;
           }
+          if (taken != 0u && (!in || started >= (taken & (GB_REST - 1u)))) break;
+          if (closes && taken == 0u) {
+            bool close = k != 0u && tickets / GB_BACK == (unsigned)stride;
+            if (k == 0u) {
+              if (tickets != seen) {
+                seen = tickets;
+                since = (long long)wall_clock64();
+              } else {
+                close = ((long long)wall_clock64() - since) * (tickets & (GB_CLOSED - 1u)) > GB_WINDOW * grid;
+              }
+            }
+            if (close) {
+              const unsigned came = __hip_atomic_fetch_or(&v[GB_TICKETS], here(GB_CLOSED), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              const unsigned n = (came & (GB_CLOSED - 1u)) < most ? came & (GB_CLOSED - 1u) : most;
+              if ((came & GB_CLOSED) == 0u) st_dev(&v[GB_TAKEN], n | (n == grid ? GB_REST : last));
+            }
+          }
+          if (in) __builtin_amdgcn_s_sleep(2);
+          else __builtin_amdgcn_s_sleep(32);   // waits for a turn's end
         }
+        if (in || taken == 0u || taken >= GB_REST) break;
       }
-      shared[0] = n;
+      shared[0] = in ? taken : 0u;
       shared[1] = ticket;
       shared[2] = r;
-      shared[3] = done;
+      shared[3] = k;
     }
     __syncthreads();
-    const unsigned n = scalar(shared[0]), ticket = scalar(shared[1]);
+    const unsigned taken = scalar(shared[0]), ticket = scalar(shared[1]), n = taken & (GB_REST - 1u);
     first = (int)scalar(n == gridDim.x ? blockIdx.x : ticket);
     stride = (int)n;
     rank = scalar(shared[2]);
-    begin = (int)scalar(shared[3]);
+    const int turn = (int)scalar(shared[3]);
     __syncthreads();
     if (n == 0u) return false;
-    const bool rest = n == gridDim.x || end - begin <= gb_quota(launch);
-    if (!rest) end = begin + gb_quota(launch);
-    // where the next launch goes on: written already here (every block that takes part has read the word, and one that comes later finds nothing to do)
-    if (first == 0 && threadIdx.x == 0) st_dev(as_global(words) + GB_NEXT, rest ? GB_ALL_DONE : (unsigned)end);
+    w = as_global(words) + turn * GB_WORDS;
+    begin = turn;
+    end = taken < GB_REST ? turn + 1 : layers;
     members = ld_dev(&w[GB_MEMBERS + 32 * xcc]);
     leader = (ld_dev(&w[GB_LEADER + 32 * xcc]) & 0xffffu) == (unsigned)blockIdx.x + 1u;
     present = 0;
     for (unsigned k = 0; k < 8u; k++) present |= ld_dev(&w[GB_MEMBERS + 32 * k]) != 0u ? 1u << k : 0u;
+    if (LEAN) {
+      members = scalar(members);
+      present = scalar(present);
+    }
     return true;
   }
-
-  // Ahead of everything else in a launch behind the first: nothing is left for it
-  __device__ __forceinline__ static bool all_done(const unsigned* words, int launch) { return launch != 0 && ld_dev(as_global(words) + GB_NEXT) == GB_ALL_DONE; }
 
   // the error word is looked at on every 64th poll: behind each poll it would double the time between two polls
   __device__ __forceinline__ bool give_up(unsigned spins) const {

@@ -381,9 +381,9 @@ void ws_layout(const pi0_config& c, const Dims& d, WsLayout& w) {
     w.pring = w.ering;
     if (bytes > ering_bytes) cur.take(bytes - ering_bytes);
   }
-  w.vsync = cur.take((size_t)GB_WORDS * 4 * GB_LAUNCHES);
+  w.vsync = cur.take((size_t)GB_WORDS * 4 * GB_TURNS);
   w.vparams = cur.take(sizeof(VisionLoopParams));
-  w.psync = cur.take((size_t)GB_WORDS * 4 * GB_LAUNCHES);
+  w.psync = cur.take((size_t)GB_WORDS * 4 * GB_TURNS);
   w.pparams = cur.take(sizeof(PrefixLoopParams));
   w.total = cur.off;
 }
@@ -750,7 +750,7 @@ bool vision_tower_persistent(Run& r, int I, int n_views, int planes, int stat_ro
   if (!vision_loop_takes(n_views, E, PK_BLOCKS)) return false;
   r.cls = PI0_OP_MISC;
   RUN(r, launch_vision_loop(r.s, n_views, E, at<VisionLoopParams>(c, w.vparams), PK_BLOCKS));
-  r.launches += vision_loop_launches(E);   // parameter block and barrier words, loop kernel
+  r.launches++;   // two launches: parameter block and barrier words, loop kernel
   const size_t last = w.vring + w.vring_slot * (size_t)(d.Lv - 1);
   *out = at<bf16>(c, last + w.rv_xb_d);
   *stats = at<float>(c, last + w.rv_st_d);
@@ -1063,7 +1063,7 @@ void run_prefill(Run& r, int n_views, int n_prompt, Taps* taps) {
     if (loop >= 0) {   // everything between the first layer's QKV projection and the last one's
       r.cls = PI0_OP_MISC;
       RUN(r, launch_prefix_loop(r.s, loop, E, at<PrefixLoopParams>(c, w.pparams), PK_BLOCKS));
-      r.launches += prefix_loop_launches(E);   // as for the tower
+      r.launches++;   // two launches, as for the tower
       l = d.Ll - 2;
       continue;
     }
@@ -1666,9 +1666,8 @@ int frame_loop_blocks(const pi0_ctx* c, int P) {
 
 // Calls of at most this many kernels are launched one by one in graph mode too: a replay begins 8 us later than a kernel (pi0_denoise over two layers 480 us by
 // graph, 471 by launches; pi0_infer over two 708 and 701, over eighteen 6271 and 6250, 11 kernels), and up to here the host spends
-// no longer on the launches than on the replay (11 kernels 32 us either way; 118 kernels 400 and 65).  pi0_prefill has 17, eight of which
-// mostly end at once; captured, a new shape's first call takes 0.35 ms more.
-constexpr int DIRECT_LAUNCHES = 20;
+// no longer on the launches than on the replay (11 kernels 32 us either way; 118 kernels 400 and 65).
+constexpr int DIRECT_LAUNCHES = 16;
 
 // The loops' buffers lie where the expert's do, and the denoise of a two-stream frame may still be on its way when a plain prefill comes on the other
 // stream: that one takes the launches, as does one that is captured, which may be replayed beside a later frame.
@@ -1937,12 +1936,11 @@ int pi0_device_status(pi0_ctx* c, void* hip_stream) {
   if (c == nullptr) return PI0_EINVAL;
   if (!c->loaded) return PI0_ESTATE;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  unsigned flags[1 + 2 * GB_LAUNCHES] = {};
+  unsigned flags[1 + 2 * GB_TURNS] = {};
   hipError_t e = hipMemcpyAsync(&flags[0], at<unsigned>(c, c->wl.esync) + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
-  for (int i = 0; i < GB_LAUNCHES && e == hipSuccess; i++) {
-    e = hipMemcpyAsync(&flags[1 + 2 * i], at<unsigned>(c, c->wl.vsync) + i * GB_WORDS + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&flags[2 + 2 * i], at<unsigned>(c, c->wl.psync) + i * GB_WORDS + GB_ERR, sizeof(unsigned), hipMemcpyDeviceToHost, s);
-  }
+  for (int i = 0; i < 2 && e == hipSuccess; i++)
+    e = hipMemcpy2DAsync(&flags[1 + i * GB_TURNS], sizeof(unsigned), at<unsigned>(c, i == 0 ? c->wl.vsync : c->wl.psync) + GB_ERR, GB_WORDS * sizeof(unsigned), sizeof(unsigned), GB_TURNS,
+                         hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail_hip(c, e);
   for (unsigned f : flags) {

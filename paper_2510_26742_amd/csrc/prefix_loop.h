@@ -22,7 +22,7 @@ struct PrefixLoopParams {
   char* ring;
   size_t ring_stride;
   unsigned r_xb_o, r_st_o, r_xb_d, r_st_d, r_q, r_attn, r_mid;
-  unsigned* sync;                 // GB_WORDS words for each launch, those from GB_START on zeroed before the first one
+  unsigned* sync;                 // GB_WORDS words for each turn (GB_TURNS), those from GB_START on zeroed before the launch
   const char* arena;              // everything that blocks exchange lies in [arena, arena + arena_bytes)
   unsigned arena_bytes;
   unsigned spin_limit;            // bound of one barrier wait, in polls
@@ -49,6 +49,5 @@ constexpr int PREFIX_QKV_PLANES = 8;              // planes of row statistics th
 hipError_t prefix_loop_init_attributes();
 hipError_t prefix_loop_max_blocks_per_cu(int* out);
 bool prefix_loop_takes(int variant, const PrefixLoopParams& P, int blocks);   // the variant covers this shape
-// d_params: device memory for one PrefixLoopParams (16-byte aligned), written by a small launch ahead of the kernel's launches
-inline int prefix_loop_launches(const PrefixLoopParams& P) { return P.most_blocks != 0 ? GB_LAUNCHES : 1; }
+// d_params: device memory for one PrefixLoopParams (16-byte aligned), written by a small launch ahead of the kernel
 hipError_t launch_prefix_loop(hipStream_t s, int variant, const PrefixLoopParams& P, PrefixLoopParams* d_params, int blocks);

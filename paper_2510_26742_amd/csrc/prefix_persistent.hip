@@ -57,15 +57,14 @@ constexpr int ATT_EARLY = 5, ATT_RING = 12;
 constexpr int PREP_THREADS = 256;
 static_assert(sizeof(PrefixLoopParams) % 4 == 0 && (GB_WORDS - GB_START) % 4 == 0, "whole pieces");
 // parameter block to device memory and barrier words to zero
-__global__ __launch_bounds__(PREP_THREADS) void prefix_loop_prepare_kernel(PrefixLoopParams P, PrefixLoopParams* dst, int launches) {
+__global__ __launch_bounds__(PREP_THREADS) void prefix_loop_prepare_kernel(PrefixLoopParams P, PrefixLoopParams* dst, int turns) {
   const unsigned i = blockIdx.x * PREP_THREADS + threadIdx.x;
   if (i < sizeof(PrefixLoopParams) / 4) reinterpret_cast<unsigned*>(dst)[i] = reinterpret_cast<const unsigned*>(&P)[i];
-  gb_clear(P.sync, launches, i);
+  gb_clear(P.sync, turns, i);
 }
 
 template <int VARIANT>
-__global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefix_loop_kernel(const PrefixLoopParams* __restrict__ params, const unsigned* words, int launch) {
-  if (GridBarrierT<false>::all_done(words, launch)) return;
+__global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefix_loop_kernel(const PrefixLoopParams* __restrict__ params) {
   using C = typename Variants<VARIANT>::T;
   constexpr bool LEAN = C::GU_HEIGHT != 0;   // (gate||up takes every register)
   using Cx = PersistCtxT<true, false, LEAN>;
@@ -73,11 +72,9 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
   const ParamsPtr<PrefixLoopParams> Pg = (ParamsPtr<PrefixLoopParams>)params;
   GridBarrierT<false, LEAN> bar;
   Cx cx;
-  int layers, begin, end, first, blocks;   // end: of this launch's layers
+  int layers, begin, end = 0, first = 0, blocks = 0;   // begin, end: the turn's layers
   {
     const PrefixLoopParams& P = fresh<PrefixLoopParams>(Pg);
-    layers = end = P.layers;
-    if (!bar.init_some(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == 31, P.most_blocks, launch, reinterpret_cast<unsigned*>(smem_raw), first, blocks, begin, end)) return;
     cx.arena = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(P.arena), 0, (int)P.arena_bytes, 0x00020000);
     cx.arena_base = P.arena;
   }
@@ -96,110 +93,118 @@ __global__ __launch_bounds__(PL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
   auto each_block = [&](auto&& f) { for_all_items<PREFIX_LOOP_BLOCKS>(f, first, blocks); };
   auto moved = [](const auto* p, size_t bytes) { return reinterpret_cast<decltype(p)>(reinterpret_cast<const char*>(p) + bytes); };
 
-  for (int l = begin; l < end; l++) {
-    {  // ---- attention, whole prefix visible ---------------------------------------------------------
-      const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
-      AttnParams a = F.att;
-      char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
-      a.q = reinterpret_cast<const bf16*>(slot + F.r_q);
-      a.k0 = moved(as_global(a.k0), (size_t)l * F.kcache_stride);
-      a.v0 = moved(as_global(a.v0), (size_t)l * F.vcache_stride);
-      a.out = reinterpret_cast<bf16*>(slot + F.r_attn);
-      const int tiles = F.att_tiles;
-      each(tiles * a.heads, [&](int it) {
-        const Cx c = item(it % tiles, it / tiles);
-        c.wait_inputs();
-        if constexpr (C::ATT_CM == 0) attention_prefix16_body(a, c, smem_raw);
-        else attention_prefix32_body<C::ATT_CM, ATT_EARLY, ATT_RING>(a, c, smem_raw);
-      });
-      bar.arrive();
+  const bool may_lead = (int)(blockIdx.x >> 3) == 31;
+  do {
+    {
+      const PrefixLoopParams& P = fresh<PrefixLoopParams>(Pg);
+      layers = P.layers;
+      if (!bar.init_some(P.sync, P.spin_limit, may_lead, P.most_blocks, reinterpret_cast<unsigned*>(smem_raw), layers, first, blocks, begin, end)) return;
     }
-    {  // ---- O projection + residual -----------------------------------------------------------------
-      const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
-      char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
-      GemmParams o = global(F.o);
-      o.W.w = moved(o.W.w, (size_t)l * F.layer_stride);
-      o.gain = moved(o.gain, (size_t)l * F.gain_stride);
-      o.X = reinterpret_cast<const bf16*>(slot + F.r_attn);
-      o.bias = nullptr;
-      o.resid_mod = o.row_offset = 0;
-      __builtin_assume(o.gain != nullptr && o.resid != nullptr);
-      o.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_xb_o);
-      o.stat_out = reinterpret_cast<float*>(slot + F.r_st_o);
-      using O = typename C::Out;
-      each_block([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, 1, O::NS, PRO_NONE, EPI_RESID>(o, item(it, 0), smem_raw); });
-      bar.arrive();
-    }
-    {  // ---- RMS -> gate||up, fused gate -------------------------------------------------------------
-      const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
-      char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
-      GemmParams g = global(F.gu);
-      g.W.w = moved(g.W.w, (size_t)l * F.layer_stride);
-      g.X = reinterpret_cast<const bf16*>(slot + F.r_xb_o);
-      g.rowstat = reinterpret_cast<const float*>(slot + F.r_st_o);
-      g.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_mid);
-      using G = typename C::Gu;
-      if constexpr (C::ROWS) {
-        static_assert(G::MT == 4 && G::NT == 2 && C::O_GROUPS == 1, "the same tile and order of the planes");
-        each(F.gu_blocks, [&](int it) { gemm_rows_body(g, item(it, 0), smem_raw); });
-      } else if constexpr (C::GU_HEIGHT != 0) {
-        each(F.gu_blocks, [&](int it) { gemm_cols_item<C::GU_HEIGHT, C::O_GROUPS, EPI_GEGLU>(g, item(it, 0), smem_raw); });
-      } else if constexpr (C::WALK) {
-        each_block([&](int it) { gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, true>(g, item(it, 0), smem_raw); });
-      } else {
-        each(F.gu_blocks, [&](int it) { gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, false>(g, item(it, 0), smem_raw); });
+    for (int l = begin; l < end; l++) {
+      {  // ---- attention, whole prefix visible ---------------------------------------------------------
+        const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
+        AttnParams a = F.att;
+        char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
+        a.q = reinterpret_cast<const bf16*>(slot + F.r_q);
+        a.k0 = moved(as_global(a.k0), (size_t)l * F.kcache_stride);
+        a.v0 = moved(as_global(a.v0), (size_t)l * F.vcache_stride);
+        a.out = reinterpret_cast<bf16*>(slot + F.r_attn);
+        const int tiles = F.att_tiles;
+        each(tiles * a.heads, [&](int it) {
+          const Cx c = item(it % tiles, it / tiles);
+          c.wait_inputs();
+          if constexpr (C::ATT_CM == 0) attention_prefix16_body(a, c, smem_raw);
+          else attention_prefix32_body<C::ATT_CM, ATT_EARLY, ATT_RING>(a, c, smem_raw);
+        });
+        bar.arrive();
       }
-      bar.arrive();
+      {  // ---- O projection + residual -----------------------------------------------------------------
+        const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
+        char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
+        GemmParams o = global(F.o);
+        o.W.w = moved(o.W.w, (size_t)l * F.layer_stride);
+        o.gain = moved(o.gain, (size_t)l * F.gain_stride);
+        o.X = reinterpret_cast<const bf16*>(slot + F.r_attn);
+        o.bias = nullptr;
+        o.resid_mod = o.row_offset = 0;
+        __builtin_assume(o.gain != nullptr && o.resid != nullptr);
+        o.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_xb_o);
+        o.stat_out = reinterpret_cast<float*>(slot + F.r_st_o);
+        using O = typename C::Out;
+        each_block([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, 1, O::NS, PRO_NONE, EPI_RESID>(o, item(it, 0), smem_raw); });
+        bar.arrive();
+      }
+      {  // ---- RMS -> gate||up, fused gate -------------------------------------------------------------
+        const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
+        char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
+        GemmParams g = global(F.gu);
+        g.W.w = moved(g.W.w, (size_t)l * F.layer_stride);
+        g.X = reinterpret_cast<const bf16*>(slot + F.r_xb_o);
+        g.rowstat = reinterpret_cast<const float*>(slot + F.r_st_o);
+        g.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_mid);
+        using G = typename C::Gu;
+        if constexpr (C::ROWS) {
+          static_assert(G::MT == 4 && G::NT == 2 && C::O_GROUPS == 1, "the same tile and order of the planes");
+          each(F.gu_blocks, [&](int it) { gemm_rows_body(g, item(it, 0), smem_raw); });
+        } else if constexpr (C::GU_HEIGHT != 0) {
+          each(F.gu_blocks, [&](int it) { gemm_cols_item<C::GU_HEIGHT, C::O_GROUPS, EPI_GEGLU>(g, item(it, 0), smem_raw); });
+        } else if constexpr (C::WALK) {
+          each_block([&](int it) { gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, true>(g, item(it, 0), smem_raw); });
+        } else {
+          each(F.gu_blocks, [&](int it) { gemm_lds_body<G::MT, G::NT, C::O_GROUPS, PRO_RMS, EPI_GEGLU, false>(g, item(it, 0), smem_raw); });
+        }
+        bar.arrive();
+      }
+      {  // ---- down, partial sums of each k range ------------------------------------------------------
+        const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
+        GemmParams d = global(F.dn);
+        d.W.w = moved(d.W.w, (size_t)l * F.layer_stride);
+        d.X = reinterpret_cast<const bf16*>(as_global(F.ring) + (size_t)l * F.ring_stride + F.r_mid);
+        using G = typename C::Dn;
+        const int gx = F.dn_blocks, z = F.red.Z;
+        const bool ranges = d.range_per_die != 0;
+        each(gx * z, [&](int it) {
+          gemm_lds_body<G::MT, G::NT, 1, PRO_NONE, EPI_PARTIAL, false>(d, ranges ? item(it >> 3, it & 7) : item(it % gx, it / gx), smem_raw);
+        });
+        bar.arrive();
+      }
+      {  // ---- their sum + residual --------------------------------------------------------------------
+        const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
+        char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
+        ReduceParams r = F.red;
+        r.part = as_global(r.part);
+        r.resid = as_global(r.resid);
+        r.out_f32 = as_global(r.out_f32);
+        r.bias = nullptr;
+        r.resid_mod = 0;
+        r.gain = moved(as_global(r.gain), (size_t)l * F.gain_stride);
+        __builtin_assume(r.gain != nullptr && r.resid != nullptr);
+        r.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_xb_d);
+        r.stat_out = reinterpret_cast<float*>(slot + F.r_st_d);
+        const int rows = (r.M + 7) >> 3;
+        each(rows * PREFIX_QKV_PLANES, [&](int it) {
+          tile_reduce_body<PL_THREADS>(r, item(it % rows, it / rows), reinterpret_cast<float2 (*)[8]>(smem_raw));
+        });
+        bar.arrive();
+      }
+      if (l + 1 < layers) {  // ---- RMS -> next layer's QKV, RoPE, keys and values into the cache ---------
+        const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
+        char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
+        GemmParams q = global(F.qkv);
+        q.W.w = moved(q.W.w, (size_t)(l + 1) * F.layer_stride);
+        q.bias = nullptr;
+        __builtin_assume(q.rope != nullptr);
+        q.X = reinterpret_cast<const bf16*>(slot + F.r_xb_d);
+        q.rowstat = reinterpret_cast<const float*>(slot + F.r_st_d);
+        q.out_bf16 = reinterpret_cast<bf16*>(slot + F.ring_stride + F.r_q);
+        q.kfrag = reinterpret_cast<bf16*>(reinterpret_cast<char*>(q.kfrag) + (size_t)(l + 1) * F.kcache_stride);
+        q.vfrag = reinterpret_cast<bf16*>(reinterpret_cast<char*>(q.vfrag) + (size_t)(l + 1) * F.vcache_stride);
+        using O = typename C::Qkv;
+        each_block([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, PREFIX_QKV_PLANES, O::NS, PRO_RMS, EPI_QKV, true>(q, item(it, 0), smem_raw); });
+        bar.arrive();
+      }
     }
-    {  // ---- down, partial sums of each k range ------------------------------------------------------
-      const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
-      GemmParams d = global(F.dn);
-      d.W.w = moved(d.W.w, (size_t)l * F.layer_stride);
-      d.X = reinterpret_cast<const bf16*>(as_global(F.ring) + (size_t)l * F.ring_stride + F.r_mid);
-      using G = typename C::Dn;
-      const int gx = F.dn_blocks, z = F.red.Z;
-      const bool ranges = d.range_per_die != 0;
-      each(gx * z, [&](int it) {
-        gemm_lds_body<G::MT, G::NT, 1, PRO_NONE, EPI_PARTIAL, false>(d, ranges ? item(it >> 3, it & 7) : item(it % gx, it / gx), smem_raw);
-      });
-      bar.arrive();
-    }
-    {  // ---- their sum + residual --------------------------------------------------------------------
-      const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
-      char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
-      ReduceParams r = F.red;
-      r.part = as_global(r.part);
-      r.resid = as_global(r.resid);
-      r.out_f32 = as_global(r.out_f32);
-      r.bias = nullptr;
-      r.resid_mod = 0;
-      r.gain = moved(as_global(r.gain), (size_t)l * F.gain_stride);
-      __builtin_assume(r.gain != nullptr && r.resid != nullptr);
-      r.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_xb_d);
-      r.stat_out = reinterpret_cast<float*>(slot + F.r_st_d);
-      const int rows = (r.M + 7) >> 3;
-      each(rows * PREFIX_QKV_PLANES, [&](int it) {
-        tile_reduce_body<PL_THREADS>(r, item(it % rows, it / rows), reinterpret_cast<float2 (*)[8]>(smem_raw));
-      });
-      bar.arrive();
-    }
-    if (l + 1 < layers) {  // ---- RMS -> next layer's QKV, RoPE, keys and values into the cache ---------
-      const PrefixLoopParams& F = fresh<PrefixLoopParams>(Pg);
-      char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
-      GemmParams q = global(F.qkv);
-      q.W.w = moved(q.W.w, (size_t)(l + 1) * F.layer_stride);
-      q.bias = nullptr;
-      __builtin_assume(q.rope != nullptr);
-      q.X = reinterpret_cast<const bf16*>(slot + F.r_xb_d);
-      q.rowstat = reinterpret_cast<const float*>(slot + F.r_st_d);
-      q.out_bf16 = reinterpret_cast<bf16*>(slot + F.ring_stride + F.r_q);
-      q.kfrag = reinterpret_cast<bf16*>(reinterpret_cast<char*>(q.kfrag) + (size_t)(l + 1) * F.kcache_stride);
-      q.vfrag = reinterpret_cast<bf16*>(reinterpret_cast<char*>(q.vfrag) + (size_t)(l + 1) * F.vcache_stride);
-      using O = typename C::Qkv;
-      each_block([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, PREFIX_QKV_PLANES, O::NS, PRO_RMS, EPI_QKV, true>(q, item(it, 0), smem_raw); });
-      bar.arrive();
-    }
-  }
+  } while (end < layers);
 }
 
 constexpr int max_int(int a, int b) { return a > b ? a : b; }
@@ -335,13 +340,11 @@ bool prefix_loop_takes(int variant, const PrefixLoopParams& P, int blocks) {
 
 hipError_t launch_prefix_loop(hipStream_t s, int variant, const PrefixLoopParams& P, PrefixLoopParams* d_params, int blocks) {
   if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0 || !prefix_loop_takes(variant, P, blocks)) return hipErrorInvalidValue;
-  int launch = 0;
-  const int launches = prefix_loop_launches(P), pieces = std::max((int)sizeof(PrefixLoopParams) / 4, (GB_WORDS - GB_START) / 4 * launches);
-  hipLaunchKernelGGL(prefix_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, launches);
-  hipError_t e = hipGetLastError();
+  const int turns = P.most_blocks != 0 ? std::min(GB_TURNS, P.layers) : 1, pieces = std::max((int)sizeof(PrefixLoopParams) / 4, (GB_WORDS - GB_START) / 4 * turns);
+  hipLaunchKernelGGL(prefix_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, turns);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   const Kernel k = kernel_for(variant);
-  const unsigned* words = P.sync;
-  void* args[] = {&d_params, &words, &launch};
-  for (; launch < launches && e == hipSuccess; launch++) e = hipLaunchKernel(k.f, dim3(blocks), dim3(PL_THREADS), args, k.smem, s);
-  return e;
+  void* args[] = {&d_params};
+  return hipLaunchKernel(k.f, dim3(blocks), dim3(PL_THREADS), args, k.smem, s);
 }

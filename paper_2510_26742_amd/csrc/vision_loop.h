@@ -23,7 +23,7 @@ struct VisionLoopParams {
   char* ring;
   size_t ring_stride;
   unsigned r_xb_o, r_st_o, r_xb_d, r_st_d, r_q, r_k, r_v, r_attn, r_mid;
-  unsigned* sync;                 // GB_WORDS words for each launch, those from GB_START on zeroed before the first one
+  unsigned* sync;                 // GB_WORDS words for each turn (GB_TURNS), those from GB_START on zeroed before the launch
   const char* arena;              // the ring and the residual stream lie in [arena, arena + arena_bytes)
   unsigned arena_bytes;
   unsigned most_blocks;           // that take part at most (GridBarrierT::init_some); 0: all, which are resident
@@ -45,6 +45,5 @@ int vision_loop_attention_items(int views, int heads);
 hipError_t vision_loop_init_attributes();
 hipError_t vision_loop_max_blocks_per_cu(int* out);
 bool vision_loop_takes(int views, const VisionLoopParams& P, int blocks);   // the kernel covers this shape
-// d_params: device memory for one VisionLoopParams (16-byte aligned), written by a small launch ahead of the kernel's launches
-inline int vision_loop_launches(const VisionLoopParams& P) { return P.most_blocks != 0 ? GB_LAUNCHES : 1; }
+// d_params: device memory for one VisionLoopParams (16-byte aligned), written by a small launch ahead of the kernel
 hipError_t launch_vision_loop(hipStream_t s, int views, const VisionLoopParams& P, VisionLoopParams* d_params, int blocks);

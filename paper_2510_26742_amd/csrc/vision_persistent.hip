@@ -69,27 +69,24 @@ constexpr int vision_smem() {
 constexpr int PREP_THREADS = 256;
 static_assert(sizeof(VisionLoopParams) % 4 == 0 && (GB_WORDS - GB_START) % 4 == 0, "whole pieces");
 // parameter block to device memory and barrier words to zero
-__global__ __launch_bounds__(PREP_THREADS) void vision_loop_prepare_kernel(VisionLoopParams P, VisionLoopParams* dst, int launches) {
+__global__ __launch_bounds__(PREP_THREADS) void vision_loop_prepare_kernel(VisionLoopParams P, VisionLoopParams* dst, int turns) {
   const unsigned i = blockIdx.x * PREP_THREADS + threadIdx.x;
   if (i < sizeof(VisionLoopParams) / 4) reinterpret_cast<unsigned*>(dst)[i] = reinterpret_cast<const unsigned*>(&P)[i];
-  gb_clear(P.sync, launches, i);
+  gb_clear(P.sync, turns, i);
 }
 
 template <int VIEWS>
 __global__ __launch_bounds__(64 * Cfg<VIEWS>::WAVES) __attribute__((amdgpu_waves_per_eu(Cfg<VIEWS>::WAVES / 4, Cfg<VIEWS>::WAVES / 4)))
-void vision_loop_kernel(const VisionLoopParams* __restrict__ params, const unsigned* words, int launch) {
-  if (GridBarrierT<false>::all_done(words, launch)) return;
+void vision_loop_kernel(const VisionLoopParams* __restrict__ params) {
   using C = Cfg<VIEWS>;
   using Cx = PersistCtxT<true, false>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const ParamsPtr<VisionLoopParams> Pg = (ParamsPtr<VisionLoopParams>)params;
   GridBarrierT<false> bar;
   Cx cx;
-  int begin, end, first, blocks;   // end: of this launch's layers
+  int begin, end = 0, first = 0, blocks = 0;   // begin, end: the turn's layers
   {
     const VisionLoopParams& P = fresh<VisionLoopParams>(Pg);
-    end = P.layers;
-    if (!bar.init_some(P.sync, P.spin_limit, (int)(blockIdx.x >> 3) == LEADER_RANK, P.most_blocks, launch, reinterpret_cast<unsigned*>(smem_raw), first, blocks, begin, end)) return;   // (no item but at two views in the attention)
     cx.arena = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(P.arena), 0, (int)P.arena_bytes, 0x00020000);
     cx.arena_base = P.arena;
   }
@@ -134,108 +131,115 @@ void vision_loop_kernel(const VisionLoopParams* __restrict__ params, const unsig
   };
 
   const int rank = (int)blockIdx.x >> 3;
-  const bool all = blocks == VISION_LOOP_BLOCKS;   // fewer than all of the grid share the items of all and read nothing ahead
-  if (all && rank >= READER_RANK && rank < LEADER_RANK) {
-    unsigned fold = 0;
-    for (int op = 5 * begin; op < 5 * end; op++) {   // QKV, attention, O, up, down
-      const int l = op / 5, k = op - l * 5;
-      if constexpr (C::READERS_ATTEND) {
-        if (k == 1) {
-          attention(l);
-          continue;
-        }
-      }
-      if (k == 0 && rank == READER_RANK) clear_padding(l, (int)blockIdx.x & 7, 8);
-      bar.arrive();   // nobody waits for what is read here
-      // QKV, attention: up.  O, up: down.  Down: the next layer's QKV and O, and where the attention leaves no time to read a part of its up
-      for (int i = 0; i < (k < 4 ? 1 : l + 1 == end ? 0 : C::READERS_ATTEND ? 3 : 2); i++) {
-        // part num of den of what the blocks of this die will ask for, in gemm_stream_body's order of items
-        const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
-        const GemmParams& g = k < 2 || i == 2 ? F.up : k < 4 ? F.down : i == 1 ? F.o : F.qkv;
-        const int nb = k < 2 || i == 2 ? C::Up::NB : k < 4 || i == 1 ? C::Resid::NB : C::Qkv::NB;
-        const int den = k == 4 && i < 2 ? 1 : 2, num = k == 4 ? 0 : C::READERS_ATTEND && k == 0 ? 1 : k & 1;
-        int first, count;
-        stream_share((int)blockIdx.x & 7, (g.n_tiles + nb - 1) / nb * g.m_tiles, first, count);
-        const int t0 = first / g.m_tiles * nb, t1 = min(((first + count - 1) / g.m_tiles + 1) * nb, g.n_tiles);
-        const unsigned tile16 = (unsigned)(g.W.k_pad >> 4) * 64u;
-        const char* const base = reinterpret_cast<const char*>(as_global(g.W.w)) + ((size_t)(l + (k == 4)) * F.layer_stride + (size_t)t0 * tile16 * 16u);
-        int t = (int)threadIdx.x;
-        asm volatile("" : "+v"(t));
-        constexpr int READERS = LEADER_RANK - READER_RANK;
-        fold = read_ahead_part<64 * C::WAVES>((unsigned)(t1 - t0) * tile16, rank - READER_RANK + READERS * num, READERS * den, t, fold,
-                                              [&](unsigned i) { return base + (size_t)i * 16u; });
-      }
-      bar.wait();   // the next operation begins
+  const bool may_lead = rank == LEADER_RANK;   // (no item but at two views in the attention)
+  do {
+    {
+      const VisionLoopParams& P = fresh<VisionLoopParams>(Pg);
+      if (!bar.init_some(P.sync, P.spin_limit, may_lead, P.most_blocks, reinterpret_cast<unsigned*>(smem_raw), P.layers, first, blocks, begin, end)) return;
     }
-    if (fold == 0x9e3779b9u) as_global(fresh<VisionLoopParams>(Pg).sync)[GB_SINK] = fold;
-    return;
-  }
+    const bool all = blocks == VISION_LOOP_BLOCKS;   // fewer than all of the grid share the items of all and read nothing ahead
+    if (all && rank >= READER_RANK && rank < LEADER_RANK) {
+      unsigned fold = 0;
+      for (int op = 5 * begin; op < 5 * end; op++) {   // QKV, attention, O, up, down
+        const int l = op / 5, k = op - l * 5;
+        if constexpr (C::READERS_ATTEND) {
+          if (k == 1) {
+            attention(l);
+            continue;
+          }
+        }
+        if (k == 0 && rank == READER_RANK) clear_padding(l, (int)blockIdx.x & 7, 8);
+        bar.arrive();   // nobody waits for what is read here
+        // QKV, attention: up.  O, up: down.  Down: the next layer's QKV and O, and where the attention leaves no time to read a part of its up
+        for (int i = 0; i < (k < 4 ? 1 : l + 1 == end ? 0 : C::READERS_ATTEND ? 3 : 2); i++) {
+          // part num of den of what the blocks of this die will ask for, in gemm_stream_body's order of items
+          const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
+          const GemmParams& g = k < 2 || i == 2 ? F.up : k < 4 ? F.down : i == 1 ? F.o : F.qkv;
+          const int nb = k < 2 || i == 2 ? C::Up::NB : k < 4 || i == 1 ? C::Resid::NB : C::Qkv::NB;
+          const int den = k == 4 && i < 2 ? 1 : 2, num = k == 4 ? 0 : C::READERS_ATTEND && k == 0 ? 1 : k & 1;
+          int first, count;
+          stream_share((int)blockIdx.x & 7, (g.n_tiles + nb - 1) / nb * g.m_tiles, first, count);
+          const int t0 = first / g.m_tiles * nb, t1 = min(((first + count - 1) / g.m_tiles + 1) * nb, g.n_tiles);
+          const unsigned tile16 = (unsigned)(g.W.k_pad >> 4) * 64u;
+          const char* const base = reinterpret_cast<const char*>(as_global(g.W.w)) + ((size_t)(l + (k == 4)) * F.layer_stride + (size_t)t0 * tile16 * 16u);
+          int t = (int)threadIdx.x;
+          asm volatile("" : "+v"(t));
+          constexpr int READERS = LEADER_RANK - READER_RANK;
+          fold = read_ahead_part<64 * C::WAVES>((unsigned)(t1 - t0) * tile16, rank - READER_RANK + READERS * num, READERS * den, t, fold,
+                                                [&](unsigned i) { return base + (size_t)i * 16u; });
+        }
+        bar.wait();   // the next operation begins
+      }
+      if (fold == 0x9e3779b9u) as_global(fresh<VisionLoopParams>(Pg).sync)[GB_SINK] = fold;
+      return;
+    }
 
-  for (int l = begin; l < end; l++) {
-    if (!all) clear_padding(l, first, blocks);
-    {  // ---- LN -> QKV, keys and values in the attention's fragment order ----------------------------
-      const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
-      GemmParams q = global(F.qkv);
-      char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
-      q.W.w = moved(q.W.w, (size_t)l * F.layer_stride);
-      q.bias = moved(q.bias, (size_t)l * F.layer_stride);
-      q.colsum = moved(q.colsum, (size_t)l * F.layer_stride);
-      q.rope = nullptr;   // (the launch checks it, and what follows below: no code for the other cases)
-      __builtin_assume(q.bias != nullptr);
-      q.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_q);
-      q.kfrag = reinterpret_cast<bf16*>(slot + F.r_k);
-      q.vfrag = reinterpret_cast<bf16*>(slot + F.r_v);
-      if (l != 0) {
-        q.X = reinterpret_cast<const bf16*>(slot - F.ring_stride + F.r_xb_d);
-        q.rowstat = reinterpret_cast<const float*>(slot - F.ring_stride + F.r_st_d);
-      }
-      using O = typename C::Qkv;
-      for_all_items<VISION_LOOP_BLOCKS>([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, C::PARTS, O::NS, PRO_LN, EPI_QKV>(q, item(it, 0), smem_raw); }, first, blocks);
-      bar.arrive();
-    }
-    attention(l);
-    using O = typename C::Resid;
-    // the two residual projections: one copy of their code
-    for (int second = 0; second < 2; second++) {
-      {
+    for (int l = begin; l < end; l++) {
+      if (!all) clear_padding(l, first, blocks);
+      {  // ---- LN -> QKV, keys and values in the attention's fragment order ----------------------------
         const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
+        GemmParams q = global(F.qkv);
         char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
-        GemmParams o = global(second ? F.down : F.o);
-        o.W.w = moved(o.W.w, (size_t)l * F.layer_stride);
-        o.bias = moved(o.bias, (size_t)l * F.layer_stride);
-        if (second) {
-          o.X = reinterpret_cast<const bf16*>(slot + F.r_mid);
-          o.gain = l + 1 < F.layers ? moved(as_global(F.g_attn0), (size_t)(l + 1) * F.gain_stride) : as_global(F.g_final);
-        } else {
-          o.X = reinterpret_cast<const bf16*>(slot + F.r_attn);
-          o.gain = moved(as_global(F.g_mlp0), (size_t)l * F.gain_stride);
+        q.W.w = moved(q.W.w, (size_t)l * F.layer_stride);
+        q.bias = moved(q.bias, (size_t)l * F.layer_stride);
+        q.colsum = moved(q.colsum, (size_t)l * F.layer_stride);
+        q.rope = nullptr;   // (the launch checks it, and what follows below: no code for the other cases)
+        __builtin_assume(q.bias != nullptr);
+        q.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_q);
+        q.kfrag = reinterpret_cast<bf16*>(slot + F.r_k);
+        q.vfrag = reinterpret_cast<bf16*>(slot + F.r_v);
+        if (l != 0) {
+          q.X = reinterpret_cast<const bf16*>(slot - F.ring_stride + F.r_xb_d);
+          q.rowstat = reinterpret_cast<const float*>(slot - F.ring_stride + F.r_st_d);
         }
-        o.resid_mod = o.row_offset = 0;
-        __builtin_assume(o.bias != nullptr && o.gain != nullptr && o.resid != nullptr);
-        o.out_bf16 = reinterpret_cast<bf16*>(slot + (second ? F.r_xb_d : F.r_xb_o));
-        o.stat_out = reinterpret_cast<float*>(slot + (second ? F.r_st_d : F.r_st_o));
-        for_all_items<VISION_LOOP_BLOCKS>([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, 1, 0, PRO_NONE, EPI_RESID>(o, item(it, 0), smem_raw); }, first, blocks);
+        using O = typename C::Qkv;
+        for_all_items<VISION_LOOP_BLOCKS>([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, C::PARTS, O::NS, PRO_LN, EPI_QKV>(q, item(it, 0), smem_raw); }, first, blocks);
         bar.arrive();
       }
-      if (second) break;
-      {  // ---- LN -> up, GELU -------------------------------------------------------------------------
-        const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
-        char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
-        GemmParams u = global(F.up);
-        u.W.w = moved(u.W.w, (size_t)l * F.layer_stride);
-        u.bias = moved(u.bias, (size_t)l * F.layer_stride);
-        u.colsum = moved(u.colsum, (size_t)l * F.layer_stride);
-        u.act = ACT_GELU;
-        __builtin_assume(u.bias != nullptr);
-        u.X = reinterpret_cast<const bf16*>(slot + F.r_xb_o);
-        u.rowstat = reinterpret_cast<const float*>(slot + F.r_st_o);
-        u.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_mid);
-        using U = typename C::Up;
-        for_all_items<VISION_LOOP_BLOCKS>([&](int it) { gemm_stream_body<U::MB, U::NB, U::W, U::V, U::D, U::SG, C::PARTS, U::NS, PRO_LN, EPI_BF16>(u, item(it, 0), smem_raw); }, first, blocks);
-        bar.arrive();
+      attention(l);
+      using O = typename C::Resid;
+      // the two residual projections: one copy of their code
+      for (int second = 0; second < 2; second++) {
+        {
+          const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
+          char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
+          GemmParams o = global(second ? F.down : F.o);
+          o.W.w = moved(o.W.w, (size_t)l * F.layer_stride);
+          o.bias = moved(o.bias, (size_t)l * F.layer_stride);
+          if (second) {
+            o.X = reinterpret_cast<const bf16*>(slot + F.r_mid);
+            o.gain = l + 1 < F.layers ? moved(as_global(F.g_attn0), (size_t)(l + 1) * F.gain_stride) : as_global(F.g_final);
+          } else {
+            o.X = reinterpret_cast<const bf16*>(slot + F.r_attn);
+            o.gain = moved(as_global(F.g_mlp0), (size_t)l * F.gain_stride);
+          }
+          o.resid_mod = o.row_offset = 0;
+          __builtin_assume(o.bias != nullptr && o.gain != nullptr && o.resid != nullptr);
+          o.out_bf16 = reinterpret_cast<bf16*>(slot + (second ? F.r_xb_d : F.r_xb_o));
+          o.stat_out = reinterpret_cast<float*>(slot + (second ? F.r_st_d : F.r_st_o));
+          for_all_items<VISION_LOOP_BLOCKS>([&](int it) { gemm_stream_body<O::MB, O::NB, O::W, O::V, O::D, O::SG, 1, 0, PRO_NONE, EPI_RESID>(o, item(it, 0), smem_raw); }, first, blocks);
+          bar.arrive();
+        }
+        if (second) break;
+        {  // ---- LN -> up, GELU -------------------------------------------------------------------------
+          const VisionLoopParams& F = fresh<VisionLoopParams>(Pg);
+          char* const slot = as_global(F.ring) + (size_t)l * F.ring_stride;
+          GemmParams u = global(F.up);
+          u.W.w = moved(u.W.w, (size_t)l * F.layer_stride);
+          u.bias = moved(u.bias, (size_t)l * F.layer_stride);
+          u.colsum = moved(u.colsum, (size_t)l * F.layer_stride);
+          u.act = ACT_GELU;
+          __builtin_assume(u.bias != nullptr);
+          u.X = reinterpret_cast<const bf16*>(slot + F.r_xb_o);
+          u.rowstat = reinterpret_cast<const float*>(slot + F.r_st_o);
+          u.out_bf16 = reinterpret_cast<bf16*>(slot + F.r_mid);
+          using U = typename C::Up;
+          for_all_items<VISION_LOOP_BLOCKS>([&](int it) { gemm_stream_body<U::MB, U::NB, U::W, U::V, U::D, U::SG, C::PARTS, U::NS, PRO_LN, EPI_BF16>(u, item(it, 0), smem_raw); }, first, blocks);
+          bar.arrive();
+        }
       }
     }
-  }
+  } while (end < fresh<VisionLoopParams>(Pg).layers);
 }
 
 struct Kernel { const void* f; int threads, smem; };
@@ -339,13 +343,11 @@ bool vision_loop_takes(int views, const VisionLoopParams& P, int blocks) {
 
 hipError_t launch_vision_loop(hipStream_t s, int views, const VisionLoopParams& P, VisionLoopParams* d_params, int blocks) {
   if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0 || !vision_loop_takes(views, P, blocks)) return hipErrorInvalidValue;
-  int launch = 0;
-  const int launches = vision_loop_launches(P), pieces = std::max((int)sizeof(VisionLoopParams) / 4, (GB_WORDS - GB_START) / 4 * launches);
-  hipLaunchKernelGGL(vision_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, launches);
-  hipError_t e = hipGetLastError();
+  const int turns = P.most_blocks != 0 ? std::min(GB_TURNS, P.layers) : 1, pieces = std::max((int)sizeof(VisionLoopParams) / 4, (GB_WORDS - GB_START) / 4 * turns);
+  hipLaunchKernelGGL(vision_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, turns);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   const Kernel k = kernel_for(views);
-  const unsigned* words = P.sync;
-  void* args[] = {&d_params, &words, &launch};
-  for (; launch < launches && e == hipSuccess; launch++) e = hipLaunchKernel(k.f, dim3(blocks), dim3(k.threads), args, k.smem, s);
-  return e;
+  void* args[] = {&d_params};
+  return hipLaunchKernel(k.f, dim3(blocks), dim3(k.threads), args, k.smem, s);
 }
