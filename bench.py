@@ -2,7 +2,8 @@
 """Benchmark: end-to-end pi0 inference latency on one MI355X (the paper's Table 1 metric).
 
 A "step" is one complete forward pass (vision encoder, prefix transformer, 10 Euler steps of
-the action expert) at batch 1 with inputs already resident in HBM, replayed from a HIP graph.
+the action expert) at batch 1 with inputs already resident in HBM, as a call of pi0_infer comes (graph mode,
+in which a sequence of no more than 16 kernels, which this one is, is launched and a longer one replayed).
 Workload at N=1: full-depth pi0, 1 view, empty prompt, chunk 63 (seeded random-init bf16
 weights, synthetic inputs).  The 2- and 3-view latencies of the same metric, the largest
 configuration (3 views + 48 prompt tokens from the 257152-row table) and the streaming use

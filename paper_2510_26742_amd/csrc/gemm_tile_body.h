@@ -25,8 +25,8 @@ __device__ __forceinline__ void for_each(F&& f) {
 // Zero, which the compiler does not know as such.  A constant it writes once for the loop and once for the last turn without one (there are as many
 // writes as registers, behind the wait for the first stage), keeps the accumulators of the two apart and moves all of them from the one to the other:
 // 500 instructions of a 256 x 256 tile, and a quarter of its code.  OPAQUE = false: the constant, where the registers do not suffice otherwise (the
-// persistent kernel with nine blocks of rows).  pi0_infer, before -> after, us: 2 views 7598 -> 7576,
-// 3 views 8902 -> 8870, 3 views + 48 tokens 9306 -> 9269, 1 view 6146 -> 6141; two-stream frame at 2 views 7090 -> 7065.
+// persistent kernel with nine blocks of rows).  Constant -> this, in turn, us, and what the runs of one side differ by: pi0_infer at 2 views 7727 -> 7678 (0.3 %),
+// 3 views 9038 -> 9001 (0.0 %), 3 views + 48 tokens 9478 -> 9429 (0.1 %), two-stream frame at 2 views 7146 -> 7120 (0.1 %); 1 view 6237 -> 6230 (0.5 %, nothing).
 template <bool OPAQUE = true>
 __device__ __forceinline__ void zero_accumulator(f32x16& a) {
 #pragma unroll

@@ -13,7 +13,7 @@
 // 6.3 / 11.7 / 16.3, O 8.4 / 12.6 / 16.5, gate||up 38.6 (gemm_rows_body) / 59.7 / 90.7, down 26.0 / 40.6 / 54.4, its reduction 6.5 / 6.2 / 7.3, QKV
 // 10.3 / 14.8 / 16.0.  pi0_infer, one device, ms, launches -> here: 1 view 6.408 -> 6.259 (-> 6.18 with gemm_rows_body), 1 view + 7 tokens 6.640 -> 6.511,
 // 2 views 7.837 -> 7.752, 3 views 9.252 -> 9.061; with gemm_cols_body for gate||up 515 tokens 8.25 -> 7.96, 560 tokens 8.37 -> 8.09.  Not beyond 768 tokens: 816 tokens 9.867 -> 9.843 .. 9.89 with the tiles that range
-// then had (256 x 256 for gate||up in two rounds, 192 x 256 for down).  Beyond 320 tokens the kernel is larger than the instruction cache (78 .. 133 KB).
+// then had (256 x 256 for gate||up in two rounds, 192 x 256 for down).  Beyond 320 tokens the kernel is larger than the instruction cache (80 .. 135 KB).
 #include "attention_body.h"
 #include "gemm_stream_body.h"
 #include "gemm_tile_body.h"
