@@ -85,6 +85,29 @@ def test_prefill_beside_another_contexts_denoise():
 
 
 @pytest.mark.gpu
+def test_two_contexts_prefill_at_once():
+    """Neither gets all of the chip at its start; the blocks of each join its turns as the other's end."""
+    cases = [Case(dataclasses.replace(CFG, vis_layers=9), seed=i) for i in range(2)]
+    try:
+        inputs = [c.inputs(*shape) for c, shape in zip(cases, ((1, 7), (2, 21)))]
+        want = [c.by_launches(*i) for c, i in zip(cases, inputs)]
+        dev = [c.to_dev(*i) for c, i in zip(cases, inputs)]
+        for i in range(8):
+            say(f"[gpu] two prefills at once, pass {i}")
+            torch.cuda.synchronize()
+            for c, (img, st, nz, ids), views in list(zip(cases, dev, (1, 2)))[:: 1 if i % 2 else -1]:
+                c.m.pi0_prefill(img, views, ids, ids.numel(), c.stream)
+            torch.cuda.synchronize()
+            for c, (_, st, nz, _), w in zip(cases, inputs, want):
+                np.testing.assert_array_equal(c.denoise_only(st, nz), w)
+        for c in cases:
+            c.m.pi0_device_status(c.stream)
+    finally:
+        for c in cases:
+            c.close()
+
+
+@pytest.mark.gpu
 def test_prefill_after_frames():
     """While the denoise of a two-stream frame may be on its way on the other stream, a plain prefill is launches; once it is done, the persistent kernels again."""
     case = Case(dataclasses.replace(CFG, vis_layers=9))
