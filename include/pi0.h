@@ -30,8 +30,8 @@
  *    model's feed-forward 193 .. 320, 385 .. 576 and 641 .. 768 tokens) as two more, at the full model's widths (launches otherwise,
  *    same bits; so does pi0_prefill while the denoise of a two-stream frame of its ctx is under way).
  *    pi0_infer's wait for all of their blocks as well.  pi0_prefill's ask for no residency: they go on with the n blocks that are
- *    there 25 us x 256 / n after the last one came, the fewer the slower, and the others join in front of a later layer (of the first
- *    16) as compute units become free for them.
+ *    there 25 us x 256 / n after the last one came, the fewer the slower, and the others join in front of every fourth
+ *    layer (up to the 28th) as compute units become free for them.
  *    Do not run other kernels that occupy whole compute units for long beside pi0_denoise / pi0_infer:
  *    the persistent kernels' blocks wait for each other (bounded, see pi0_device_status).  pi0_prefill of another ctx is such a kernel
  *    for the time of a tower or of a prefix: milliseconds, and 256 / n times that where it gets n blocks only.

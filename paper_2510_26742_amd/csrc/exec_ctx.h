@@ -120,12 +120,15 @@ enum {
 };
 constexpr unsigned GB_CLOSED = 1u << 16, GB_BACK = 1u << 20, GB_REST = 1u << 16;   // (more than any grid)
 constexpr long long GB_WINDOW = 2500;   // of the 100 MHz counter: 25 us, within which the blocks of a launch on an otherwise idle device have long come (10)
-// A loop that goes on with the blocks that have come does so in turns of a layer, with barrier words for each; the blocks that have come meanwhile join in
+// A loop that goes on with the blocks that have come does so in turns of GB_LAYERS, with barrier words for each; the blocks that have come meanwhile join in
 // between.  With all of the grid a turn does all layers that are left, and so does the last one.  So a moment in which other work holds the chip costs no
-// more than that and a layer on the few units that were free.  pi0_prefill of 27 / 3 layers (1.8 ms alone) beside a loop on 224 units for 3 ms:
-// 8.8 ms with the blocks of the start throughout, 6.3 with a kernel that ends and is launched four more times, of which the launches that find nothing
-// left cost 1.7 us each (a prefill over two layers 222 -> 236 us), 4.6 with these turns (222 -> 223).
-constexpr int GB_TURNS = 16;
+// more than that and a turn on the few units that were free.  ms of pi0_prefill, the blocks of the start throughout / turns of 1 / 2 / 4 layers:
+// 27 / 3 layers (1.8 alone) beside a loop on 224 units for 3 ms  8.8 / 4.6 / 4.8 / 5.25,
+// 27 / 18 layers beside a loop that stays, on 64 units 7.43 / 7.93 / 7.61 / 7.46, 128 7.94 / 8.38 / 8.22 / 8.04, 160 10.43 / 10.75 / 10.68 / 10.52.
+// (A kernel that ends after 1, 2, 4, 8 layers and is launched again: 6.3 in the first case, and the launches that find nothing left cost 1.7 us each,
+// 222 -> 236 us over two layers, where turns cost less than 1.)
+constexpr int GB_LAYERS = 4, GB_TURNS = 8;
+inline int gb_turns(int layers) { return layers >= GB_LAYERS * GB_TURNS ? GB_TURNS : (layers + GB_LAYERS - 1) / GB_LAYERS; }
 
 // Barrier words to zero, in a launch ahead of the kernel's
 __device__ __forceinline__ void gb_clear(unsigned* sync, int turns, unsigned i) {   // piece i of the words of that many turns; the error words stay as they are
@@ -221,14 +224,14 @@ struct GridBarrierT {
     if (thread() == 0u) {
       const unsigned grid = gridDim.x;
       if (most > grid) most = grid;
-      unsigned ticket = 0, r = 0, taken = 0, k = (unsigned)end;
+      unsigned ticket = 0, r = 0, taken = 0, k = (unsigned)end / GB_LAYERS;
       bool in = false;
       for (bool back = k != 0u;; back = false, k++) {
         unsigned* const v = as_global(words) + k * GB_WORDS;
         const unsigned before = __hip_atomic_fetch_add(&v[GB_TICKETS], back ? here(GB_BACK + 1u) : here(1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         ticket = before & (GB_CLOSED - 1u);
         in = (before & GB_CLOSED) == 0u && ticket < most;
-        const unsigned last = k == GB_TURNS - 1 || (int)k + 1 >= layers ? GB_REST : 0u;
+        const unsigned last = k == GB_TURNS - 1 || ((int)k + 1) * GB_LAYERS >= layers ? GB_REST : 0u;
         if (in) {
           if (k == 0u && ticket + 1u == most) st_dev(&v[GB_TAKEN], most | (most == grid ? GB_REST : last));
           __hip_atomic_fetch_max(&v[GB_LEADER + 32 * xcc], here(blockIdx.x + 1u + (may_lead ? 1u << 16 : 0u)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -284,8 +287,8 @@ struct GridBarrierT {
     __syncthreads();
     if (n == 0u) return false;
     w = as_global(words) + turn * GB_WORDS;
-    begin = turn;
-    end = taken < GB_REST ? turn + 1 : layers;
+    begin = turn * GB_LAYERS;
+    end = taken < GB_REST ? begin + GB_LAYERS : layers;
     members = ld_dev(&w[GB_MEMBERS + 32 * xcc]);
     leader = (ld_dev(&w[GB_LEADER + 32 * xcc]) & 0xffffu) == (unsigned)blockIdx.x + 1u;
     present = 0;

@@ -343,7 +343,7 @@ bool vision_loop_takes(int views, const VisionLoopParams& P, int blocks) {
 
 hipError_t launch_vision_loop(hipStream_t s, int views, const VisionLoopParams& P, VisionLoopParams* d_params, int blocks) {
   if (d_params == nullptr || (reinterpret_cast<uintptr_t>(d_params) & 15) != 0 || !vision_loop_takes(views, P, blocks)) return hipErrorInvalidValue;
-  const int turns = P.most_blocks != 0 ? std::min(GB_TURNS, P.layers) : 1, pieces = std::max((int)sizeof(VisionLoopParams) / 4, (GB_WORDS - GB_START) / 4 * turns);
+  const int turns = P.most_blocks != 0 ? gb_turns(P.layers) : 1, pieces = std::max((int)sizeof(VisionLoopParams) / 4, (GB_WORDS - GB_START) / 4 * turns);
   hipLaunchKernelGGL(vision_loop_prepare_kernel, dim3(ceil_div(pieces, PREP_THREADS)), dim3(PREP_THREADS), 0, s, P, d_params, turns);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

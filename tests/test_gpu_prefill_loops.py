@@ -38,11 +38,11 @@ def test_any_number_of_blocks_gives_the_launches_bits(graphs):
 
 @pytest.mark.gpu
 def test_every_turn_of_a_loop_that_does_not_get_the_chip():
-    """Twenty layers of the tower by fewer blocks than the grid has are sixteen turns (15 layers, then five at once), in front of each of which the blocks
-    that take part are others: those that were left out before come ahead of some that took part."""
-    case = Case(dataclasses.replace(CFG, vis_layers=20))
+    """Turns are four layers, and the eighth is all that are left: 38 layers of the tower and six of the prefix by fewer blocks than the grid has.  In front
+    of each turn the blocks that take part are others: those that were left out before come ahead of some that took part."""
+    case = Case(dataclasses.replace(CFG, vis_layers=38, llm_layers=7, exp_layers=7))
     try:
-        for n_views, n_prompt in ((1, 7), (2, 21), (3, 0)):
+        for n_views, n_prompt in SHAPES:
             img, st, nz, ids = case.inputs(n_views, n_prompt)
             want = case.by_launches(img, st, nz, ids)
             for blocks in (255, 200, 33, 256):
@@ -87,7 +87,7 @@ def test_prefill_beside_another_contexts_denoise():
 @pytest.mark.gpu
 def test_two_contexts_prefill_at_once():
     """Neither gets all of the chip at its start; the blocks of each join its turns as the other's end."""
-    cases = [Case(dataclasses.replace(CFG, vis_layers=9), seed=i) for i in range(2)]
+    cases = [Case(dataclasses.replace(CFG, vis_layers=18), seed=i) for i in range(2)]
     try:
         inputs = [c.inputs(*shape) for c, shape in zip(cases, ((1, 7), (2, 21)))]
         want = [c.by_launches(*i) for c, i in zip(cases, inputs)]
@@ -214,9 +214,9 @@ def test_prefill_after_a_wait_that_ran_out_is_quick_and_reported():
 
 
 @pytest.mark.gpu
-def test_a_chip_that_is_busy_for_a_moment_costs_prefill_no_more_than_a_layer():
+def test_a_chip_that_is_busy_for_a_moment_costs_prefill_no_more_than_a_turn():
     """Another context's denoise holds 224 compute units when pi0_prefill's tower begins, for a quarter of the time that 27 layers take on the
-    other 32: the blocks that come when it is done join in front of the next layer."""
+    other 32: the blocks that come when it is done join in front of the next turn."""
     b = Case(dataclasses.replace(CFG, vis_layers=27), seed=1)
     a = Case(dataclasses.replace(CFG, steps=32), tune="psb=224")
     try:
@@ -243,7 +243,7 @@ def test_a_chip_that_is_busy_for_a_moment_costs_prefill_no_more_than_a_layer():
             np.testing.assert_array_equal(act.cpu().numpy(), want_a)
             np.testing.assert_array_equal(b.denoise_only(ib[1], ib[2]), want_b)
         say(f"[gpu] pi0_prefill alone {alone:.2f} ms, beside the frames " + ", ".join(f"{t:.2f} (frame done after {f:.2f})" for t, f in zip(beside, frame)))
-        assert min(beside[1:]) < max(frame[1:]) + 1.4 * alone   # measured 0.9; with the blocks of the start throughout 3.2
+        assert min(beside[1:]) < max(frame[1:]) + 2 * alone   # measured 1.3; with the blocks of the start throughout 3.2
         a.m.pi0_device_status(a.stream)
         b.m.pi0_device_status(b.stream)
     finally:
